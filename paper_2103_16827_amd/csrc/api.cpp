@@ -119,6 +119,9 @@ qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
 
 qasr_status launch(const ConvParams& p, hipStream_t st) { return launch_with(pick_kernel(p), p, st); }
 
+// frames between rows of an encoder's own tensors: the row length rounded up to 16
+int32_t row_pad(int32_t T) { return (16 - T % 16) % 16; }
+
 size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -134,11 +137,18 @@ struct qasr_encoder {
     bool has_act = false;
     bool act_fused = false;   // the layer's own kernel applies it (p.act_lut)
     qasr::ActParams act;   // applied in place to the output when has_act
+    int32_t in_channels = 0;  // channels of the slot read (p.Cin, or more for a channel-prefix view)
   };
   std::vector<Op> ops;
   std::vector<size_t> slot_off;   // byte offset of slot i in the workspace (slot 0 unused)
   size_t ws_bytes = 0;
-  size_t in_elems = 0, out_elems = 0;   // int8 elements of the network input and output
+  int64_t in_rows = 0, out_rows = 0;    // rows (batch items x channels) of the network input and output
+  int32_t in_T = 0, out_T = 0;          // and their lengths
+  bool pitched = false;                 // the slots' rows have a pitch of their own (see rows_of)
+  // int8 forwards of a pitched encoder: the input / output goes through a pitched copy in the
+  // workspace (the pipelined pointwise kernels take aligned rows only)
+  bool copy_in = false, copy_out = false;
+  size_t copy_in_off = 0, copy_out_off = 0;
   int8_t* packed = nullptr;       // device: packed weights of all groups == 1 layers
   // Runs of consecutive ops that one launch of the persistent team kernel executes (team.hip); the
   // ops outside them are launched one by one.
@@ -180,7 +190,7 @@ static bool team_record(const qasr_encoder::Op& op, qasr::TeamOp& t) {
 static qasr_status plan_team_runs(qasr_encoder* e, int32_t n_slots) {
   const int32_t n = (int32_t)e->ops.size();
   e->run_of.assign(n, -1);
-  if (!qasr::tuning().team || n < kMinRunOps || e->ops[0].d.B < 8 || n > qasr::kTeamMaxStamps - 2) return QASR_OK;
+  if (!qasr::tuning().team || e->pitched || n < kMinRunOps || e->ops[0].d.B < 8 || n > qasr::kTeamMaxStamps - 2) return QASR_OK;
   std::vector<qasr::TeamOp> rec(n);
   std::vector<char> can(n, 0);
   bool any = false;
@@ -256,6 +266,27 @@ static qasr_status plan_team_runs(qasr_encoder* e, int32_t n_slots) {
     if (me != hipSuccess) return hip_status(me);
   }
   return QASR_OK;
+}
+
+// Rows of op i as it runs: where a tensor lives decides the pitch of its rows.  The slots inside an
+// encoder whose lengths are not all multiples of 16 have rows rounded up to 16 frames (`pitched`);
+// the network input and output have xpad / ypad frames between rows (0: the caller's dense tensors).
+// Every kernel family then sees 16-byte aligned rows whatever the utterance length: before, one frame
+// more or less than a multiple of 4 sent every pointwise and dense layer to the one-thread-per-output
+// fallback (QuartzNet-15x5, one utterance of 1237 frames: 15.4 ms).
+// A pointwise layer between two tensors of equal pitch is run over the pitch itself: its columns are
+// independent, the pad columns are computed and ignored.
+static void rows_of(const qasr_encoder* e, size_t i, int32_t xpad, int32_t ypad, ConvParams& p) {
+  const qasr_encoder::Op& op = e->ops[i];
+  p.xpad = op.in_slot == 0 ? xpad : (e->pitched ? row_pad(p.Tin) : 0);
+  p.ypad = i + 1 == e->ops.size() ? ypad : (e->pitched ? row_pad(p.Tout) : 0);
+  p.xbs = (int64_t)op.in_channels * (p.Tin + p.xpad);
+  p.ybs = (int64_t)p.Cout * (p.Tout + p.ypad);
+  if (!p.depthwise && p.k == 1 && p.stride == 1 && p.pl == 0 && p.Tin == p.Tout && p.xpad == p.ypad) {
+    p.Tin += p.xpad;
+    p.Tout += p.ypad;
+    p.xpad = p.ypad = 0;
+  }
 }
 
 extern "C" {
@@ -339,10 +370,14 @@ qasr_status qasr_requant(const int32_t* acc, int32_t B, int32_t C, int32_t T, co
   return hip_status(e);
 }
 
-qasr_status qasr_quantize(const float* x, size_t n, float alpha, int8_t* q, void* stream) {
+static qasr_status check_alpha(float alpha) {
   if (!(alpha > 0.0f) || !std::isfinite(alpha)) return QASR_ERR_PARAM;
+  return alpha / 127.0f > 0.0f ? QASR_OK : QASR_ERR_PARAM;   // (an alpha so small that the step underflows)
+}
+
+qasr_status qasr_quantize(const float* x, size_t n, float alpha, int8_t* q, void* stream) {
+  if (check_alpha(alpha) != QASR_OK) return QASR_ERR_PARAM;
   const float S = alpha / 127.0f;
-  if (!(S > 0.0f)) return QASR_ERR_PARAM;                 // alpha so small that the step underflows
   if (n == 0) return QASR_OK;
   if (!x || !q) return QASR_ERR_NULL;
   if (n > ((size_t)1 << 40)) return QASR_ERR_SHAPE;
@@ -593,6 +628,9 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
   struct SlotState { bool live = false; int32_t C = 0, T = 0; };
   std::vector<SlotState> slot(n_slots);
   size_t packed_bytes = 0;
+  // rows with a pitch of their own: wanted when some length is not a multiple of 16, and possible
+  // unless a residual operand would then have another pitch than the output it is added to
+  bool ragged = false, pitchable = true, copy_in = false;
   for (int32_t i = 0; i < n_ops; ++i) {
     const qasr_op& o = ops[i];
     const qasr_status st = check_desc(&o.d);
@@ -637,6 +675,13 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       const SlotState& r = slot[o.more_res_slots[q]];
       if (!r.live || r.C != o.d.Cout || r.T != Tout) return QASR_ERR_PARAM;
     }
+    ragged = ragged || row_pad(o.d.Tin) || row_pad(Tout);
+    if (row_pad(Tout) && o.res_slot >= 0) {
+      if (i + 1 == n_ops || o.res_slot == 0) pitchable = false;
+      for (int32_t q = 0; q < o.n_more_res; ++q) pitchable = pitchable && o.more_res_slots[q] != 0;
+    }
+    if (o.d.Tin < 4 || Tout < 4) pitchable = false;
+    if (o.in_slot == 0 && row_pad(o.d.Tin) && o.d.k == 1 && has_packed_form(&o.d)) copy_in = true;
     slot[o.out_slot].live = true;
     slot[o.out_slot].C = o.d.Cout;
     slot[o.out_slot].T = Tout;
@@ -646,6 +691,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
 
   qasr_encoder* e = new (std::nothrow) qasr_encoder();
   if (!e) return QASR_ERR_HIP;
+  e->pitched = ragged && pitchable;
   SlotPlan plan;
   {
     std::vector<SlotWire> wires(n_ops);
@@ -654,7 +700,8 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       wires[i] = SlotWire{o.in_slot, o.res_slot, o.out_slot,
                           std::vector<int32_t>(o.more_res_slots, o.more_res_slots + o.n_more_res),
                           i + 1 == n_ops ? (size_t)0   // (the last op writes the caller's output)
-                                         : (size_t)o.d.B * o.d.Cout * (size_t)out_len64(&o.d)};
+                                         : (size_t)o.d.B * o.d.Cout *
+                                               (size_t)(out_len64(&o.d) + (e->pitched ? row_pad((int32_t)out_len64(&o.d)) : 0))};
     }
     // The buffers should stay inside the 256 MB memory-side cache together: the deepest plan up to
     // the configured depth whose buffers take at most three quarters of it (QuartzNet-15x5 shape:
@@ -676,12 +723,25 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
     e->slot_off[sidx] = off;
     off += round256(plan.bytes[sidx]);
   }
-  e->ws_bytes = off;
-  e->in_elems = (size_t)ops[0].d.B * slot[0].C * slot[0].T;
+  e->in_rows = (int64_t)ops[0].d.B * slot[0].C;
+  e->in_T = slot[0].T;
   {
     const qasr_conv1d_desc& ld = ops[n_ops - 1].d;
-    e->out_elems = (size_t)ld.B * ld.Cout * (size_t)out_len64(&ld);
+    e->out_rows = (int64_t)ld.B * ld.Cout;
+    e->out_T = (int32_t)out_len64(&ld);
+    // (a layer of less than one 256-channel pass is as fast on gemm_mfma, which stores rows of any length)
+    e->copy_out = e->pitched && row_pad(e->out_T) && ld.k == 1 && has_packed_form(&ld) && ld.Cout >= 256;
   }
+  e->copy_in = e->pitched && copy_in;
+  if (e->copy_in) {
+    e->copy_in_off = off;
+    off += round256((size_t)e->in_rows * (e->in_T + row_pad(e->in_T)));
+  }
+  if (e->copy_out) {
+    e->copy_out_off = off;
+    off += round256((size_t)e->out_rows * (e->out_T + row_pad(e->out_T)));
+  }
+  e->ws_bytes = off;
 
   // ---- one-time device work: pack the dense k>1 weights
   if (packed_bytes) {
@@ -711,7 +771,12 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
     op.n_more_res = o.n_more_res;
     op.p.n_res_more = o.n_more_res;
     for (int32_t r = 0; r < o.n_more_res; ++r) op.more_res_slots[r] = plan.more[i][r];
-    op.kernel = pick_kernel(op.p);
+    op.in_channels = (int32_t)(op.p.xbs / op.p.Tin);
+    {
+      ConvParams rp = op.p;               // (the pointers are unknown yet: the choice for aligned ones)
+      rows_of(e, i, e->copy_in ? row_pad(e->in_T) : 0, e->copy_out ? row_pad(e->out_T) : 0, rp);
+      op.kernel = pick_kernel(rp);
+    }
     if (o.act) {
       op.has_act = true;
       op.act = act_params(o.act->kind, o.act->m, o.act->s, o.act->e);
@@ -772,13 +837,28 @@ int32_t qasr_encoder_op_in_team(const qasr_encoder* e, int32_t i) {
   return e->run_of.empty() ? 0 : (e->run_of[i] >= 0 ? 1 : 0);
 }
 
+// xpad, ypad: frames between the rows of x and y (pitched encoders only; 0 = the caller's dense tensors)
 static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,
-                                size_t workspace_bytes, hipStream_t st, hipEvent_t* ev, int team = 1) {
+                                size_t workspace_bytes, hipStream_t st, hipEvent_t* ev, int team = 1,
+                                int32_t xpad = 0, int32_t ypad = 0) {
   if (!e || !x || !y) return QASR_ERR_NULL;
   if (e->ws_bytes && (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < e->ws_bytes))
     return QASR_ERR_WORKSPACE;
   int8_t* ws = (int8_t*)workspace;
   const size_t n = e->ops.size();
+  if (e->copy_in && xpad == 0) {
+    xpad = row_pad(e->in_T);
+    int8_t* const xc = ws + e->copy_in_off;
+    const hipError_t ce = qasr::launch_repitch(x, e->in_rows, e->in_T, e->in_T, xc, e->in_T + xpad, st);
+    if (ce != hipSuccess) return hip_status(ce);
+    x = xc;
+  }
+  int8_t* const y_user = y;
+  const bool copy_y = e->copy_out && ypad == 0;
+  if (copy_y) {
+    ypad = row_pad(e->out_T);
+    y = ws + e->copy_out_off;
+  }
   // (the team kernel's loads want 16-byte aligned tensors, like the kernels it replaces)
   const bool use_team = team && !ev && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);
   for (size_t i = 0; i < n; ++i) {
@@ -792,6 +872,7 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     }
     const qasr_encoder::Op& op = e->ops[i];
     ConvParams p = op.p;
+    rows_of(e, i, xpad, ypad, p);
     p.x = op.in_slot == 0 ? x : ws + e->slot_off[op.in_slot];
     p.res = op.res_slot < 0 ? nullptr : (op.res_slot == 0 ? x : ws + e->slot_off[op.res_slot]);
     p.y = (i + 1 == n) ? y : ws + e->slot_off[op.out_slot];
@@ -805,10 +886,14 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     if (s != QASR_OK) return s;
     if (op.has_act && !(op.act_fused && applies_act_table(kk))) {
       const bool glu = op.act.kind == QASR_ACT_GLU;
-      const int64_t n_out = (int64_t)(glu ? p.Cout / 2 : p.Cout) * p.Tout;
+      const int64_t n_out = (int64_t)(glu ? p.Cout / 2 : p.Cout) * (p.Tout + p.ypad);
       const hipError_t ae = qasr::launch_act(op.act, p.y, p.y, p.B, n_out, p.ybs, p.ybs, st);
       if (ae != hipSuccess) return hip_status(ae);
     }
+  }
+  if (copy_y) {
+    const hipError_t ce = qasr::launch_repitch(y, e->out_rows, e->out_T, e->out_T + ypad, y_user, e->out_T, st);
+    if (ce != hipSuccess) return hip_status(ce);
   }
   if (ev) { const hipError_t re = hipEventRecord(ev[n], st); if (re != hipSuccess) return hip_status(re); }
   return QASR_OK;
@@ -900,8 +985,13 @@ qasr_status qasr_encoder_forward_team_stamps(const qasr_encoder* e, const int8_t
   return st;
 }
 
+// int8 copies of the network input and output of a float forward, in rows of the slots' pitch
+static size_t f32_copy_bytes(const qasr_encoder* e, int64_t rows, int32_t T) {
+  return round256((size_t)rows * (T + (e->pitched ? row_pad(T) : 0)));
+}
+
 size_t qasr_encoder_workspace_bytes_f32(const qasr_encoder* e) {
-  return e ? e->ws_bytes + round256(e->in_elems) + round256(e->out_elems) : 0;
+  return e ? e->ws_bytes + f32_copy_bytes(e, e->in_rows, e->in_T) + f32_copy_bytes(e, e->out_rows, e->out_T) : 0;
 }
 
 qasr_status qasr_encoder_forward_f32(const qasr_encoder* e, const float* x, float alpha, float S_out, float* y,
@@ -910,11 +1000,23 @@ qasr_status qasr_encoder_forward_f32(const qasr_encoder* e, const float* x, floa
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < qasr_encoder_workspace_bytes_f32(e))
     return QASR_ERR_WORKSPACE;
   int8_t* xq = (int8_t*)workspace + e->ws_bytes;
-  int8_t* yq = xq + round256(e->in_elems);
-  qasr_status st = qasr_quantize(x, e->in_elems, alpha, xq, stream);
-  if (st == QASR_OK) st = forward_impl(e, xq, yq, workspace, e->ws_bytes ? e->ws_bytes : workspace_bytes, (hipStream_t)stream, nullptr);
-  if (st == QASR_OK) st = qasr_dequantize(yq, e->out_elems, S_out, y, stream);
-  return st;
+  int8_t* yq = xq + f32_copy_bytes(e, e->in_rows, e->in_T);
+  const int32_t xpad = e->pitched ? row_pad(e->in_T) : 0, ypad = e->pitched ? row_pad(e->out_T) : 0;
+  const hipStream_t st_ = (hipStream_t)stream;
+  qasr_status st;
+  if (xpad == 0) {
+    st = qasr_quantize(x, (size_t)e->in_rows * e->in_T, alpha, xq, stream);
+  } else {
+    st = check_alpha(alpha);
+    if (st == QASR_OK)
+      st = hip_status(qasr::launch_quantize_rows(x, e->in_rows, e->in_T, alpha, alpha / 127.0f, xq, e->in_T + xpad, st_));
+  }
+  if (st == QASR_OK)
+    st = forward_impl(e, xq, yq, workspace, e->ws_bytes ? e->ws_bytes : workspace_bytes, st_, nullptr, 1, xpad, ypad);
+  if (st != QASR_OK) return st;
+  if (ypad == 0) return qasr_dequantize(yq, (size_t)e->out_rows * e->out_T, S_out, y, stream);
+  if (!std::isfinite(S_out)) return QASR_ERR_PARAM;
+  return hip_status(qasr::launch_dequantize_rows(yq, e->out_rows, e->out_T, e->out_T + ypad, S_out, y, st_));
 }
 
 qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,

@@ -29,8 +29,46 @@ struct ConvParams {
   // unary activation fused into the epilogue: 256 bytes, entry (code + 128) = the activation's int8
   // output for that int8 code (built once by act_table_kernel); null = none.  Only pw_pipe and dw_pipe read it.
   const uint8_t* act_lut;
+  // Row pitch: a row of x (one channel of one batch item) starts Tin + xpad bytes after the row before
+  // it, a row of y and of the residuals Tout + ypad bytes.  0 at the C ABI; the encoder gives its
+  // own tensors rows rounded up to 16 frames, so that every layer between its input and its output has
+  // aligned rows whatever the utterance length.  The pad bytes hold arbitrary values: a kernel that
+  // reads across frames (k > 1) zeroes what it loads of them, and any kernel may overwrite them.  The
+  // kernels without taps that know no pitch (pw_pipe, pw_tile) are given the pitch as the length.
+  int32_t xpad, ypad;
 };
 constexpr int kMaxMoreRes = 11;
+
+// bytes >= keep of a 16-byte chunk set to zero (1 <= keep <= 15)
+typedef int chunk16 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ chunk16 keep_bytes(chunk16 v, int keep) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int b = keep - 4 * i;                          // bytes of this dword that stay
+    v[i] = b >= 4 ? v[i] : b <= 0 ? 0 : v[i] & ((1 << (8 * b)) - 1);
+  }
+  return v;
+}
+
+// dword at any byte address (one global_load_dword / global_store_dword: the hardware takes unaligned ones)
+typedef uint32_t __attribute__((aligned(1), may_alias)) unaligned_u32;
+__device__ __forceinline__ uint32_t load_u32(const int8_t* p) { return *reinterpret_cast<const unaligned_u32*>(p); }
+__device__ __forceinline__ void store_u32(int8_t* p, uint32_t v) { *reinterpret_cast<unaligned_u32*>(p) = v; }
+
+// Bytes [t, t + 4) of a row of T >= 4 bytes whose frames past T do not exist: the dword is loaded from
+// inside the row and shifted, the missing bytes are 0 (t < T).
+__device__ __forceinline__ uint32_t load_row_u32(const int8_t* row, int t, int T) {
+  const int tl = min(t, T - 4);
+  return load_u32(row + tl) >> (8 * (t - tl));
+}
+// bytes [t, min(t + 4, T)) of a row
+__device__ __forceinline__ void store_row_u32(int8_t* row, int t, int T, uint32_t v) {
+  if (t + 4 <= T) {
+    store_u32(row + t, v);
+  } else {
+    for (int i = 0; t + i < T; ++i) row[t + i] = (int8_t)(v >> (8 * i));
+  }
+}
 
 // Packed weight layout (groups == 1, Cin % 64 == 0): [k][ceil(Cout/16)][Cin/64][64 lanes][16 bytes].
 // Lane l = 16*gi + n of block (j, co16, kc) holds output channel co = 16*co16 + n (zeros beyond

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(256) void conv_generic_kernel(ConvParams p) {
   const int8_t* xb = p.x + (int64_t)b * p.xbs;
   const int t0 = to * p.stride - p.pl;
   if (p.depthwise) {
-    const int8_t* xr = xb + (int64_t)co * p.Tin;
+    const int8_t* xr = xb + (int64_t)co * (p.Tin + p.xpad);
     const int8_t* wr = p.w + (int64_t)co * p.k;
     for (int j = 0; j < p.k; ++j) {
       const int ti = t0 + j * p.dil;
@@ -24,7 +24,7 @@ __global__ __launch_bounds__(256) void conv_generic_kernel(ConvParams p) {
     }
   } else {
     for (int ci = 0; ci < p.Cin; ++ci) {
-      const int8_t* xr = xb + (int64_t)ci * p.Tin;
+      const int8_t* xr = xb + (int64_t)ci * (p.Tin + p.xpad);
       for (int j = 0; j < p.k; ++j) {
         const int ti = t0 + j * p.dil;
         if (ti >= 0 && ti < p.Tin) {
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void conv_generic_kernel(ConvParams p) {
     }
   }
   int32_t v = dyadic_rescale(A, p.m[co], p.s[co]);
-  const int64_t o = (int64_t)b * p.ybs + (int64_t)co * p.Tout + to;
+  const int64_t o = (int64_t)b * p.ybs + (int64_t)co * (p.Tout + p.ypad) + to;
   if (p.res) v += (int32_t)p.res[o];
 #pragma unroll
   for (int r = 0; r < kMaxMoreRes; ++r)

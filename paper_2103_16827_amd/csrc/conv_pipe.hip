@@ -91,7 +91,13 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
   const int rot = (u_fq >> 2) & 3;
   const int u_f = fa + 4 * u_fq;                    // first input frame of the unit
   const bool u_on = u_cg < 4 && u_f >= 0 && u_f < p.Tin;
-  const uint32_t xoff = u_on ? (uint32_t)(8 * u_cg * p.Tin + u_f) : 0u;   // (Cin Tin < 2^31)
+  const int xpitch = p.Tin + p.xpad;
+  // A unit at a row's end whose last frames do not exist is loaded from inside the row (any byte
+  // address will do) and shifted down: the missing frames come out as the implicit zeros.
+  const int u_fl = min(u_f, p.Tin - 4);
+  const int u_shr = u_on ? 8 * (u_f - u_fl) : 0;
+  const bool ragged = (p.Tin & 3) != 0;             // (uniform)
+  const uint32_t xoff = u_on ? (uint32_t)(8 * u_cg * xpitch + u_fl) : 0u;   // (Cin x pitch < 2^31)
   uint32_t sel_lo, sel_hi;                          // frames rot, rot+1 | rot+2, rot+3 of two rows
   {
     const uint32_t f0s = rot, f1s = (rot + 1) & 3, f2s = (rot + 2) & 3, f3s = (rot + 3) & 3;
@@ -100,17 +106,23 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
   }
   uint32_t xr[4][4];
   auto issue_chunk = [&](int kc) __attribute__((always_inline)) {
-    const int8_t* base = xb + (int64_t)(64 * kc) * p.Tin;
+    const int8_t* base = xb + (int64_t)(64 * kc) * xpitch;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int c = 4 * ((i & 1) + 8 * (i >> 1)) + e;
-        xr[i][e] = u_on ? *reinterpret_cast<const uint32_t*>(base + (int64_t)c * p.Tin + xoff) : 0u;
+        xr[i][e] = u_on ? load_u32(base + (int64_t)c * xpitch + xoff) : 0u;
       }
   };
   auto commit_chunk = [&](int buf) __attribute__((always_inline)) {
     if (u_cg < 4) {
+      if (ragged) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) xr[i][e] >>= u_shr;
+      }
       unsigned char* dst = xs + buf * bufbytes + 4 * u_fq * kXS + 16 * u_cg;
       uint32_t c[4][4];
 #pragma unroll
@@ -228,30 +240,30 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
     const int co = co_w + 16 * nt + n;
     if (co >= p.Cout) continue;
     const int32_t mc = p.m[co], sc = p.s[co];
-    const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * p.Tout;
+    const int trow = p.Tout + p.ypad;               // (pad bytes may be written)
+    const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * trow;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int t = t0 + 16 * mt + 4 * gi;
-      if (t >= p.Tout) continue;                    // Tout % 4 == 0: the whole dword is in or out
+      if (t >= p.Tout) continue;
       uint32_t rr = 0;
-      if (p.res) rr = *reinterpret_cast<const uint32_t*>(p.res + orow + t);
+      if (p.res) rr = load_row_u32(p.res + orow, t, trow);
       int32_t radd[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) radd[i] = (int32_t)(int8_t)(rr >> (8 * i));
+#pragma unroll 1
+      for (int r = 0; r < p.n_res_more; ++r) {       // dense-residual layers: further operands
+        const uint32_t rw = load_row_u32(p.res_more[r] + orow, t, trow);
 #pragma unroll
-      for (int r = 0; r < kMaxMoreRes; ++r)          // dense-residual layers: further operands
-        if (r < p.n_res_more) {
-          const uint32_t rw = *reinterpret_cast<const uint32_t*>(p.res_more[r] + orow + t);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) radd[i] += (int32_t)(int8_t)(rw >> (8 * i));
-        }
+        for (int i = 0; i < 4; ++i) radd[i] += (int32_t)(int8_t)(rw >> (8 * i));
+      }
       uint32_t pk = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int32_t v = dyadic_rescale(acc[mt][nt][i], mc, sc) + radd[i];
         pk |= (uint32_t)(clamp_i8(v, lo) & 0xff) << (8 * i);
       }
-      *reinterpret_cast<uint32_t*>(p.y + orow + t) = pk;
+      store_row_u32(p.y + orow, t, trow, pk);
     }
   }
 }
@@ -282,11 +294,7 @@ bool pick(const ConvParams& p, int& MT, int& NT) {
   if (tuning().no_conv_pipe) return false;                // tuning: fall through to gemm_mfma
   if (p.depthwise || p.Cin % 64 != 0 || !p.w_packed || p.k < 2) return false;
   if (p.Cout < 64) return false;
-  if (p.Tin % 4 != 0 || p.Tout % 4 != 0 || p.xbs % 4 != 0 || p.ybs % 4 != 0) return false;
-  if ((uintptr_t)p.x % 4 || (uintptr_t)p.y % 4 || (uintptr_t)p.w % 16 || (p.res && (uintptr_t)p.res % 4))
-    return false;
-  for (int r = 0; r < p.n_res_more; ++r)
-    if ((uintptr_t)p.res_more[r] % 4) return false;
+  if (p.Tin < 4 || p.Tout < 4 || (uintptr_t)p.w % 16) return false;   // (rows are read in dwords, at any address)
   // the kernel addresses the packed weights with 32-bit offsets
   if ((int64_t)p.k * ((p.Cout + 15) / 16) * (p.Cin / 64) * 1024 > 0x7fffffffLL) return false;
   // frames per tile: 96 or 64 (128 would need all 256 registers and leave one wave per SIMD:
@@ -300,7 +308,7 @@ bool pick(const ConvParams& p, int& MT, int& NT) {
       if ((force_mt && mt != force_mt) || (force_nt && nt != force_nt)) continue;
       const int TM = 16 * mt;
       const int rows = lds_rows(p, TM);
-      if (rows > kMaxRows || (int64_t)p.Cin * p.Tin > 0x7fffffffLL) continue;
+      if (rows > kMaxRows || (int64_t)p.Cin * (p.Tin + p.xpad) > 0x7fffffffLL) continue;
       const int64_t n_tt = (p.Tout + TM - 1) / TM, n_co = (p.Cout + 64 * nt - 1) / (64 * nt);
       const int64_t blocks = (int64_t)p.B * n_tt * n_co;
       if (blocks > 0x7ffffff0LL) continue;

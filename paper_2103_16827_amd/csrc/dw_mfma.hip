@@ -25,6 +25,7 @@
 namespace qasr {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int unaligned_v4i __attribute__((ext_vector_type(4), aligned(1), may_alias));
 
 namespace {
 
@@ -59,10 +60,10 @@ __global__ __launch_bounds__(256) void dw_mfma_kernel(ConvParams p, DwGeom g) {
   unsigned char* my = strips_lds + (size_t)wave * g.R * g.NCH * 16;
 
   // ---- 1. start the global loads of this wave's strips (chunk u of strip r -> lane u % 64)
-  int4 xv[8];
+  v4i xv[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    xv[i] = make_int4(0, 0, 0, 0);
+    xv[i] = (v4i){0, 0, 0, 0};
     if (i < g.R * g.NI) {
       const int r = g.NI == 2 ? (i >> 1) : i;
       const int u = lane + 64 * (g.NI == 2 ? (i & 1) : 0);
@@ -71,17 +72,22 @@ __global__ __launch_bounds__(256) void dw_mfma_kernel(ConvParams p, DwGeom g) {
         const int b = strip / g.nseg;
         const int T0 = (strip - b * g.nseg) * kSeg;
         const int t = T0 + 16 * (u - g.PH);                        // first frame of the chunk
-        const int8_t* row = p.x + (int64_t)b * p.xbs + (int64_t)c * p.Tin;
+        const int8_t* row = p.x + (int64_t)b * p.xbs + (int64_t)c * (p.Tin + p.xpad);
+        // (t is a multiple of 16: a chunk never starts before the row and ends inside it)
         if (ALIGNED) {
-          if (t >= 0 && t < p.Tin) xv[i] = *reinterpret_cast<const int4*>(row + t);
-        } else if (t > -16 && t < p.Tin) {
+          if (t >= 0 && t < p.Tin) {
+            v4i d = *reinterpret_cast<const v4i*>(row + t);
+            if (p.Tin - t < 16) d = keep_bytes(d, p.Tin - t);
+            xv[i] = d;
+          }
+        } else if (t >= 0 && t + 16 <= p.Tin) {
+          xv[i] = *reinterpret_cast<const unaligned_v4i*>(row + t);
+        } else if (t >= 0 && t < p.Tin) {
           uint32_t d[4] = {0, 0, 0, 0};
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int tt = t + e;
-            if (tt >= 0 && tt < p.Tin) d[e >> 2] |= (uint32_t)(uint8_t)row[tt] << (8 * (e & 3));
-          }
-          xv[i] = make_int4((int)d[0], (int)d[1], (int)d[2], (int)d[3]);
+          for (int e = 0; e < 16; ++e)
+            if (t + e < p.Tin) d[e >> 2] |= (uint32_t)(uint8_t)row[t + e] << (8 * (e & 3));
+          xv[i] = (v4i){(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
         }
       }
     }
@@ -121,7 +127,7 @@ __global__ __launch_bounds__(256) void dw_mfma_kernel(ConvParams p, DwGeom g) {
     if (i < g.R * g.NI) {
       const int r = g.NI == 2 ? (i >> 1) : i;
       const int u = lane + 64 * (g.NI == 2 ? (i & 1) : 0);
-      if (u < g.NCH) *reinterpret_cast<int4*>(my + ((size_t)r * g.NCH + u) * 16) = xv[i];
+      if (u < g.NCH) *reinterpret_cast<v4i*>(my + ((size_t)r * g.NCH + u) * 16) = xv[i];
     }
   }
   __syncthreads();
@@ -140,7 +146,7 @@ __global__ __launch_bounds__(256) void dw_mfma_kernel(ConvParams p, DwGeom g) {
 
   // Output addressing: wave-uniform 64-bit base + a 32-bit per-lane offset.  Strip r of the wave is
   // batch item b0 + r (nseg == 1) or the only strip (R == 1); the host keeps R * ybs below 2^31.
-  const int64_t obase = (int64_t)b0 * p.ybs + (int64_t)c * p.Tout + T0w;
+  const int64_t obase = (int64_t)b0 * p.ybs + (int64_t)c * (p.Tout + p.ypad) + T0w;
   int8_t* const yb = p.y + obase;
   const int8_t* const rb = p.res ? p.res + obase : nullptr;
   const int strip_pitch = g.nseg == 1 ? (int)p.ybs : 0;
@@ -182,6 +188,16 @@ __global__ __launch_bounds__(256) void dw_mfma_kernel(ConvParams p, DwGeom g) {
           const uint32_t p01 = __builtin_amdgcn_perm((uint32_t)v[1], (uint32_t)v[0], 0x0c0c0400u);
           const uint32_t p23 = __builtin_amdgcn_perm((uint32_t)v[3], (uint32_t)v[2], 0x04000c0cu);
           *reinterpret_cast<uint32_t*>(yb + o) = p01 | p23;
+        } else if (t + 4 <= Tleft) {
+          if (rb) {
+            const uint32_t rw = load_u32(rb + o);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] += (int32_t)(int8_t)(rw >> (8 * i));
+          }
+          uint32_t pk = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pk |= (uint32_t)(clamp_i8(v[i], lo) & 0xff) << (8 * i);
+          store_u32(yb + o, pk);
         } else {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -236,7 +252,7 @@ bool geometry(const ConvParams& p, DwGeom& g, int& KC) {
   const int64_t gy = (nstrips + 4 * g.R - 1) / (4 * g.R);
   if (gy > 65535) return false;
   g.c_per_xcd = (p.Cout + 7) / 8;
-  g.aligned_out = (p.Tout % 4 == 0) && ((uintptr_t)p.y % 4 == 0) && (p.ybs % 4 == 0) &&
+  g.aligned_out = ((p.Tout + p.ypad) % 4 == 0) && ((uintptr_t)p.y % 4 == 0) && (p.ybs % 4 == 0) &&
                   (!p.res || (uintptr_t)p.res % 4 == 0);
   return true;
 }
@@ -245,7 +261,7 @@ template <int KC>
 hipError_t launch_kc(const ConvParams& p, const DwGeom& g, hipStream_t st) {
   const dim3 grid(8 * g.c_per_xcd, (g.nstrips + 4 * g.R - 1) / (4 * g.R));
   const size_t shmem = (size_t)4 * g.R * g.NCH * 16;
-  const bool aligned = (p.Tin % 16 == 0) && ((uintptr_t)p.x % 16 == 0) && (p.xbs % 16 == 0);
+  const bool aligned = ((p.Tin + p.xpad) % 16 == 0) && ((uintptr_t)p.x % 16 == 0) && (p.xbs % 16 == 0);
   if (aligned) return launch_kernel(dw_mfma_kernel<KC, true>, grid, dim3(256), shmem, st, p, g);
   return launch_kernel(dw_mfma_kernel<KC, false>, grid, dim3(256), shmem, st, p, g);
 }

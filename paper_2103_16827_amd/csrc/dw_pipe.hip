@@ -25,8 +25,8 @@
 // iteration i the wave allows exactly the requests issued after the loads of iteration i to stay
 // outstanding:  loads(i+1), loads(i+2) [L each] + stores(i-2), stores(i-1) [one per 256-frame tile
 // of the iteration's whole pairs of tiles].
-// Needs 16-byte aligned rows that are a multiple of 16 frames and at most ~1000 frames long,
-// 4-byte aligned outputs and no residual operand; everything else is served by dw_mfma.hip.
+// Needs 16-byte aligned rows (a pitch that is a multiple of 16; a row itself may have any length up
+// to ~1000 frames), 4-byte aligned outputs and no residual operand; everything else is served by dw_mfma.hip.
 #include "kernels.hpp"
 #include "vmem.hpp"
 #include "tuning.hpp"
@@ -78,8 +78,10 @@ __global__ __launch_bounds__(256) void dw_pipe_kernel(ConvParams p, DwpGeom g) {
 
   // Requests of one iteration (always L of them, see below): rows `row` .. `row + R - 1` into buffer `buf`.
   // Chunk u of a row holds frames 16 (u - PH) .. +15; lanes whose chunk is padding stay out.
-  const int8_t* const xc = p.x + (int64_t)c * p.Tin;
+  const int8_t* const xc = p.x + (int64_t)c * (p.Tin + p.xpad);
   const int rowbytes = g.NCH * 16;
+  // byte offset of the chunk in which a row ends, -1 if it ends with a chunk (or beyond the buffer)
+  const int tail_at = (p.Tin & 15) && (p.Tin >> 4) + g.PH < g.NCH ? ((p.Tin >> 4) + g.PH) * 16 : -1;
   bool lane_in[NI];
   int64_t lane_off[NI];
 #pragma unroll
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(256) void dw_pipe_kernel(ConvParams p, DwpGeom g) {
   const int sh = fast ? sc - 32 : sc, rnd = fast ? 1 << (sc - 33) : 0;
 
   const int pairs = (g.tiles + 1) >> 1;
-  int8_t* const yc = p.y + (int64_t)c * p.Tout;
+  int8_t* const yc = p.y + (int64_t)c * (p.Tout + p.ypad);
 
   // One iteration, software-pipelined over its NP tile pairs: the matrix products of pair q are
   // issued, then the operands of pair q + 1 are read from LDS, then pair q - 1 is rescaled and
@@ -199,10 +201,16 @@ __global__ __launch_bounds__(256) void dw_pipe_kernel(ConvParams p, DwpGeom g) {
     const unsigned char* const rows_lds = my + buf * R * rowbytes;
     wait_vm_dyn(2 * L + min(it, 2) * 2 * NP);      // the rows of this iteration are in LDS
     asm volatile("" ::: "memory");
+    // Rows that end inside a chunk: what the chunk holds beyond the row is pad of unknown content and
+    // is zeroed here, a byte per lane (a wave's LDS accesses stay in order: the reads below see it).
+    if (tail_at >= 0 && lane >= (p.Tin & 15) && lane < 16) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) my[(buf * R + r) * rowbytes + tail_at + lane] = 0;
+    }
 
     const int Rv = min(R, s_end - row);
     const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
-        yc + (int64_t)row * p.ybs, 0, (int)((uint32_t)(Rv - 1) * (uint32_t)p.ybs + (uint32_t)p.Tout), 0x00027000);
+        yc + (int64_t)row * p.ybs, 0, (int)((uint32_t)(Rv - 1) * (uint32_t)p.ybs + (uint32_t)((p.Tout + 3) & ~3)), 0x00027000);
     const v4i bias4 = {bias, bias, bias, bias};
     v4i xb[2][2][KC];                              // [pair parity][tile of the pair][chunk]
     v4i acc[2][2];
@@ -271,8 +279,8 @@ struct Plan { int KC, R, NI, S; };
 
 bool plan(const ConvParams& p, DwpGeom& g, Plan& pl) {
   if (!p.depthwise || p.stride != 1 || p.Tout < 1 || p.res) return false;
-  if (p.Tin % 16 != 0 || p.xbs % 16 != 0 || (uintptr_t)p.x % 16 != 0) return false;
-  if (p.Tout % 4 != 0 || p.ybs % 4 != 0 || (uintptr_t)p.y % 4 != 0) return false;
+  if ((p.Tin + p.xpad) % 16 != 0 || p.xbs % 16 != 0 || (uintptr_t)p.x % 16 != 0) return false;
+  if ((p.Tout + p.ypad) % 4 != 0 || p.ybs % 4 != 0 || (uintptr_t)p.y % 4 != 0) return false;
   if (p.ybs >= 0x20000000LL) return false;               // row offsets within an iteration are 32-bit
   g.delta = ((-p.pl) % 16 + 16) % 16;
   g.PH = (p.pl + g.delta) / 16;

@@ -108,9 +108,9 @@ __global__ __launch_bounds__(256) void gemm_conv_kernel(ConvParams p, GemmGeom g
       const int f = fa + 4 * fq;
       uint32_t r[4] = {0, 0, 0, 0};
       if (f >= 0 && f < p.Tin) {
-        const int8_t* src = xb + (int64_t)(64 * kc + 4 * cq) * p.Tin + f;
+        const int8_t* src = xb + (int64_t)(64 * kc + 4 * cq) * (p.Tin + p.xpad);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = *reinterpret_cast<const uint32_t*>(src + (int64_t)e * p.Tin);
+        for (int e = 0; e < 4; ++e) r[e] = load_row_u32(src + (int64_t)e * (p.Tin + p.xpad), f, p.Tin);
       }
       uint32_t c[4];
       transpose4x4(r[0], r[1], r[2], r[3], c);
@@ -156,20 +156,21 @@ __global__ __launch_bounds__(256) void gemm_conv_kernel(ConvParams p, GemmGeom g
     const int co = co_w + 16 * nt + n;
     if (co >= p.Cout) continue;
     const int32_t mc = p.m[co], sc = p.s[co];
-    const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * p.Tout;
+    const int trow = p.Tout + p.ypad;               // (pad bytes may be written)
+    const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * trow;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int t = t0 + 16 * mt + 4 * gi;
-      if (t >= p.Tout) continue;                    // Tout % 4 == 0: the whole dword is in or out
+      if (t >= p.Tout) continue;
       uint32_t rr = 0;
-      if (p.res) rr = *reinterpret_cast<const uint32_t*>(p.res + orow + t);
+      if (p.res) rr = load_row_u32(p.res + orow, t, trow);
       uint32_t pk = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int32_t v = dyadic_rescale(acc[mt][nt][i], mc, sc) + (int32_t)(int8_t)(rr >> (8 * i));
         pk |= (uint32_t)(clamp_i8(v, lo) & 0xff) << (8 * i);
       }
-      *reinterpret_cast<uint32_t*>(p.y + orow + t) = pk;
+      store_row_u32(p.y + orow, t, trow, pk);
     }
   }
 }
@@ -219,9 +220,7 @@ hipError_t launch_t(const ConvParams& p, hipStream_t st) {
 bool gemm_mfma_supported(const ConvParams& p) {
   if (p.depthwise || p.Cin % 64 != 0) return false;
   if (p.k > 1 && !p.w_packed) return false;
-  if (p.Tin % 4 != 0 || p.Tout % 4 != 0 || p.xbs % 4 != 0 || p.ybs % 4 != 0) return false;
-  if ((uintptr_t)p.x % 4 || (uintptr_t)p.y % 4 || (uintptr_t)p.w % 16 || (p.res && (uintptr_t)p.res % 4))
-    return false;
+  if (p.Tin < 4 || p.Tout < 4 || (uintptr_t)p.w % 16) return false;   // (rows are read in dwords, at any address)
   Choice c;
   return pick(p, c);
 }

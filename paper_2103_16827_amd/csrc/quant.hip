@@ -51,6 +51,52 @@ __global__ __launch_bounds__(256) void dequantize_kernel(const int8_t* __restric
   for (size_t i = 4 * n4 + tid; i < n; i += stride) x[i] = __fmul_rn(S, (float)q[i]);
 }
 
+// ---- the row forms: int8 rows with a pitch of their own on one side.  A thread takes 4 consecutive
+// frames of a row; the int8 side is one dword at an aligned address, the other side is whatever the
+// row length makes of it.  HBM-bound in principle (5 bytes per element), launch-bound at the sizes of
+// an encoder's input and output.
+struct RowQuads {
+  int64_t n;        // rows * quads per row
+  int per_row;      // quads per row
+};
+
+__global__ __launch_bounds__(256) void quantize_rows_kernel(const float* __restrict__ x, RowQuads g, int T, float alpha,
+                                                            float S, int8_t* __restrict__ q, int pitch) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += stride) {
+    const int64_t row = i / g.per_row;
+    const int t = 4 * (int)(i - row * g.per_row);
+    uint32_t pk = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (t + e < T) pk |= ((uint32_t)quantize_one(x[row * T + t + e], alpha, S) & 0xffu) << (8 * e);
+    *reinterpret_cast<uint32_t*>(q + row * pitch + t) = pk;
+  }
+}
+
+__global__ __launch_bounds__(256) void dequantize_rows_kernel(const int8_t* __restrict__ q, RowQuads g, int T, int pitch,
+                                                              float S, float* __restrict__ x) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += stride) {
+    const int64_t row = i / g.per_row;
+    const int t = 4 * (int)(i - row * g.per_row);
+    const uint32_t pk = *reinterpret_cast<const uint32_t*>(q + row * pitch + t);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (t + e < T) x[row * T + t + e] = __fmul_rn(S, (float)(int8_t)(pk >> (8 * e)));
+  }
+}
+
+__global__ __launch_bounds__(256) void repitch_kernel(const int8_t* __restrict__ x, RowQuads g, int T, int xpitch,
+                                                      int8_t* __restrict__ y, int ypitch) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += stride) {
+    const int64_t row = i / g.per_row;
+    const int t = 4 * (int)(i - row * g.per_row);
+    store_row_u32(y + row * ypitch, t, ypitch, load_row_u32(x + row * xpitch, t, T));
+  }
+}
+
 unsigned grid_for(size_t n) {
   const size_t quads = (n + 3) / 4;
   const size_t blocks = (quads + 255) / 256;
@@ -67,6 +113,23 @@ hipError_t launch_quantize(const float* x, size_t n, float alpha, float S, int8_
 hipError_t launch_dequantize(const int8_t* q, size_t n, float S, float* x, hipStream_t st) {
   const int vec_ok = ((uintptr_t)x % 16 == 0 && (uintptr_t)q % 4 == 0) ? 1 : 0;
   return launch_kernel(dequantize_kernel, dim3(grid_for(n)), dim3(256), 0, st, q, n, S, x, vec_ok);
+}
+
+hipError_t launch_quantize_rows(const float* x, int64_t rows, int T, float alpha, float S, int8_t* q, int pitch,
+                                hipStream_t st) {
+  const RowQuads g{rows * ((T + 3) / 4), (T + 3) / 4};
+  return launch_kernel(quantize_rows_kernel, dim3(grid_for(4 * (size_t)g.n)), dim3(256), 0, st, x, g, T, alpha, S, q, pitch);
+}
+
+hipError_t launch_dequantize_rows(const int8_t* q, int64_t rows, int T, int pitch, float S, float* x, hipStream_t st) {
+  const RowQuads g{rows * ((T + 3) / 4), (T + 3) / 4};
+  return launch_kernel(dequantize_rows_kernel, dim3(grid_for(4 * (size_t)g.n)), dim3(256), 0, st, q, g, T, pitch, S, x);
+}
+
+hipError_t launch_repitch(const int8_t* x, int64_t rows, int T, int xpitch, int8_t* y, int ypitch, hipStream_t st) {
+  if (T < 4) return hipErrorInvalidValue;
+  const RowQuads g{rows * ((T + 3) / 4), (T + 3) / 4};
+  return launch_kernel(repitch_kernel, dim3(grid_for(4 * (size_t)g.n)), dim3(256), 0, st, x, g, T, xpitch, y, ypitch);
 }
 
 }  // namespace qasr
