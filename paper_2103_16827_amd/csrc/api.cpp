@@ -2,6 +2,7 @@
 // encoder executor (a flat op list over activation slots).  See include/qasr.h.
 #include "../../include/qasr.h"
 #include "kernels.hpp"
+#include "sep.hpp"
 #include "team.hpp"
 #include "tuning.hpp"
 
@@ -137,6 +138,11 @@ struct qasr_encoder {
     bool has_act = false;
     bool act_fused = false;   // the layer's own kernel applies it (p.act_lut)
     qasr::ActParams act;   // applied in place to the output when has_act
+    // This depthwise op and the pointwise op after it may run as one launch (sep.hpp): nothing else reads
+    // what it writes.  Its weight image, and the table of the activation between the two (or null).
+    bool sep = false;
+    const uint32_t* sep_img = nullptr;
+    const uint8_t* sep_lut = nullptr;
     int32_t in_channels = 0;  // channels of the slot read (p.Cin, or more for a channel-prefix view)
   };
   std::vector<Op> ops;
@@ -159,6 +165,7 @@ struct qasr_encoder {
   };
   std::vector<TeamRun> runs;
   std::vector<int32_t> run_of;    // per op: index into runs, or -1
+  uint32_t* sep_images = nullptr; // device: weight images of the depthwise ops with `sep`
   int8_t* toeplitz = nullptr;     // device: Toeplitz operand images of the depthwise layers inside runs
   int32_t team_wgs = 0;           // workgroups of a team launch (one per compute unit)
 };
@@ -750,6 +757,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
   }
   size_t poff = 0;
   e->ops.resize(n_ops);
+  std::vector<uint8_t*> act_table(n_ops, nullptr);
   for (int32_t i = 0; i < n_ops; ++i) {
     const qasr_op& o = ops[i];
     qasr_encoder::Op& op = e->ops[i];
@@ -784,7 +792,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       // that kernel's epilogue through a 256-entry table (one int8 output per int8 code), built here
       // once by the activation's own integer arithmetic; everything else keeps the separate pass.
       if (o.act->kind != QASR_ACT_GLU) {
-        uint8_t* table = reinterpret_cast<uint8_t*>(e->packed + poff);
+        uint8_t* table = act_table[i] = reinterpret_cast<uint8_t*>(e->packed + poff);
         poff += 256;
         if (applies_act_table(op.kernel)) {
           const hipError_t te = qasr::launch_act_table(op.act, table, nullptr);
@@ -798,6 +806,46 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       }
     }
   }
+  // ---- depthwise + pointwise pairs that run as one launch
+  if (!e->pitched && qasr::tuning().team) {
+    // (the experimental team kernel takes such layers one by one)
+  } else {
+    std::vector<size_t> img_off(n_ops, 0);
+    size_t img_bytes = 0;
+    for (int32_t i = 0; i + 1 < n_ops; ++i) {
+      const qasr_op &o = ops[i], &q = ops[i + 1];
+      if (o.d.groups == 1 || q.in_slot != o.out_slot || q.res_slot == o.out_slot || o.out_slot == 0) continue;
+      if ((o.act && o.act->kind == QASR_ACT_GLU) || q.act) continue;
+      bool only = e->ops[i + 1].out_slot != e->ops[i].in_slot || i + 2 == n_ops;   // (tiles read their neighbours' input)
+      for (int32_t r = 0; r < q.n_more_res; ++r) only = only && q.more_res_slots[r] != o.out_slot;
+      for (int32_t j = i + 2; j < n_ops && only && ops[j - 1].out_slot != o.out_slot; ++j) {
+        only = ops[j].in_slot != o.out_slot && ops[j].res_slot != o.out_slot;
+        for (int32_t r = 0; r < ops[j].n_more_res; ++r) only = only && ops[j].more_res_slots[r] != o.out_slot;
+      }
+      if (!only) continue;
+      ConvParams dp = e->ops[i].p, qp = e->ops[i + 1].p;
+      rows_of(e, i, row_pad(dp.Tin), row_pad(dp.Tout), dp);
+      rows_of(e, i + 1, row_pad(qp.Tin), row_pad(qp.Tout), qp);
+      if (!qasr::sep_supported(dp, qp)) continue;
+      e->ops[i].sep = true;
+      img_off[i] = img_bytes;
+      img_bytes += round256(qasr::sep_image_bytes(dp));
+    }
+    hipError_t he = img_bytes ? hipMalloc((void**)&e->sep_images, img_bytes) : hipSuccess;
+    for (int32_t i = 0; i < n_ops && he == hipSuccess; ++i) {
+      qasr_encoder::Op& op = e->ops[i];
+      if (!op.sep) continue;
+      uint32_t* const img = e->sep_images + img_off[i] / 4;
+      op.sep_img = img;
+      op.sep_lut = act_table[i];
+      he = qasr::launch_sep_image(op.p, img, nullptr);
+      if (he == hipSuccess && op.has_act && !op.act_fused) he = qasr::launch_act_table(op.act, act_table[i], nullptr);
+    }
+    if (he != hipSuccess) {
+      qasr_encoder_destroy(e);
+      return hip_status(he);
+    }
+  }
   {
     const qasr_status ts = plan_team_runs(e, n_bufs);
     if (ts != QASR_OK) {
@@ -805,7 +853,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       return ts;
     }
   }
-  if (packed_bytes || !e->runs.empty()) {
+  if (packed_bytes || e->sep_images || !e->runs.empty()) {
     const hipError_t se = hipStreamSynchronize(nullptr);
     if (se != hipSuccess) {
       qasr_encoder_destroy(e);
@@ -861,6 +909,18 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
   }
   // (the team kernel's loads want 16-byte aligned tensors, like the kernels it replaces)
   const bool use_team = team && !ev && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);
+  // layer i's parameters with this call's tensors
+  auto bind = [&](size_t i, ConvParams& p) {
+    const qasr_encoder::Op& op = e->ops[i];
+    p = op.p;
+    rows_of(e, i, xpad, ypad, p);
+    p.x = op.in_slot == 0 ? x : ws + e->slot_off[op.in_slot];
+    p.res = op.res_slot < 0 ? nullptr : (op.res_slot == 0 ? x : ws + e->slot_off[op.res_slot]);
+    p.y = (i + 1 == n) ? y : ws + e->slot_off[op.out_slot];
+    for (int32_t r = 0; r < op.n_more_res; ++r)
+      p.res_more[r] = op.more_res_slots[r] == 0 ? x : ws + e->slot_off[op.more_res_slots[r]];
+  };
+  const bool fuse = team && !ev;                // (timed and layer-by-layer forwards launch every layer by itself)
   for (size_t i = 0; i < n; ++i) {
     if (use_team && e->run_of[i] >= 0) {
       const qasr_encoder::TeamRun& r = e->runs[e->run_of[i]];
@@ -871,13 +931,20 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
       continue;
     }
     const qasr_encoder::Op& op = e->ops[i];
-    ConvParams p = op.p;
-    rows_of(e, i, xpad, ypad, p);
-    p.x = op.in_slot == 0 ? x : ws + e->slot_off[op.in_slot];
-    p.res = op.res_slot < 0 ? nullptr : (op.res_slot == 0 ? x : ws + e->slot_off[op.res_slot]);
-    p.y = (i + 1 == n) ? y : ws + e->slot_off[op.out_slot];
-    for (int32_t r = 0; r < op.n_more_res; ++r)
-      p.res_more[r] = op.more_res_slots[r] == 0 ? x : ws + e->slot_off[op.more_res_slots[r]];
+    ConvParams p;
+    bind(i, p);
+    if (op.sep && fuse) {
+      ConvParams q;
+      bind(i + 1, q);
+      p.act_lut = op.sep_lut;
+      if (qasr::sep_supported(p, q)) {
+        const hipError_t se = qasr::launch_sep(p, op.sep_img, q, st);
+        if (se != hipSuccess) return hip_status(se);
+        ++i;
+        continue;
+      }
+      p.act_lut = op.p.act_lut;
+    }
     if (ev) { const hipError_t re = hipEventRecord(ev[i], st); if (re != hipSuccess) return hip_status(re); }
     // (the choice depends on the caller's pointers too: a fused activation's table is only read
     // by the two pipelined kernels, any other choice is followed by the separate pass)
@@ -1108,6 +1175,7 @@ void qasr_encoder_graph_destroy(qasr_encoder_graph* g) {
 void qasr_encoder_destroy(qasr_encoder* e) {
   if (!e) return;
   if (e->packed) (void)hipFree(e->packed);
+  if (e->sep_images) (void)hipFree(e->sep_images);
   if (e->toeplitz) (void)hipFree(e->toeplitz);
   for (qasr_encoder::TeamRun& r : e->runs) {
     if (r.ops_dev) (void)hipFree(r.ops_dev);

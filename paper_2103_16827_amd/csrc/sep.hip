@@ -1,0 +1,154 @@
+// Planning and launching of the fused separable module (sep_body.hpp), and the weight image its depthwise
+// half multiplies with.
+#include "sep_body.hpp"
+#include "tuning.hpp"
+
+namespace qasr {
+
+namespace {
+
+struct Geometry { int delta, r, nk, NA; };
+
+bool geometry(const ConvParams& d, Geometry& g) {
+  if (!d.depthwise || d.stride != 1 || d.res || d.n_res_more || d.Tout < 1) return false;
+  g.delta = ((-d.pl) % 16 + 16) % 16;                    // rows are loaded from a multiple of 16 frames
+  g.r = g.delta & 3;                                     // (whole dwords of it are an address offset)
+  const int64_t span = (int64_t)d.dil * (d.k - 1) + 1;
+  if (span > 96) return false;
+  g.nk = (int)((span + 3 + g.r + 3) / 4);
+  g.NA = g.nk <= 12 ? 3 : (g.nk + 3) / 4;
+  return g.NA <= 6;
+}
+
+int units_of(const ConvParams& d, const Geometry& g, int MT) {
+  const int need = (g.delta + 16 * MT + d.dil * (d.k - 1) + 15) / 16;
+  return need | 1;
+}
+
+// Image: [Cout / 16][NA][64 lanes][4 dwords]; dword i of quad a, lane (channel block b = lane / 4, row
+// m = lane % 4) holds the weights of kappa = 4 (4 a + i) .. + 3: tap j sits at kappa = m + r + j dil.
+__global__ __launch_bounds__(256) void sep_image_kernel(const int8_t* __restrict__ w, int C, int k, int dil, int r, int NA,
+                                                        uint32_t* __restrict__ img) {
+  const int n = C / 16 * NA * 256;
+  const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (idx >= n) return;
+  const int i = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) % NA, blk = (idx >> 8) / NA;
+  const int c = 16 * blk + (lane >> 2), m = lane & 3;
+  uint32_t v = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int rel = 4 * (4 * a + i) + e - m - r;
+    const int j = rel >= 0 ? rel / dil : -1;
+    if (j >= 0 && j < k && j * dil == rel) v |= (uint32_t)(uint8_t)w[(int64_t)c * k + j] << (8 * e);
+  }
+  img[idx] = v;
+}
+
+size_t lds_bytes(int KCH, int units, int MT, int NA) { return (size_t)KCH * 8192 + 8 * (size_t)sep::row_bytes(units, MT, NA) + 256; }
+
+// Tile (MT groups x 128 NT output channels per workgroup) with the least time on the busiest compute
+// unit: the workgroups a unit holds together share its matrix pipes (10 cycles per 4x4x4 product, 17.7
+// per 16x16x64 one) and its 64 bytes per cycle from the L2 (weight image and packed weights, which every
+// workgroup streams whole); a round costs the latency of its first loads and of its last stores.
+bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int groups_per_row, int cus, SepChoice& c) {
+  static const int MTs[] = {1, 2, 4, 7};
+  c.KCH = d.Cout / 64;
+  c.NA = g.NA;
+  double best = 1e300;
+  const int force_mt = tuning().sep_mt, force_nt = tuning().sep_nt;
+  for (int NT = 1; NT <= (c.KCH == 8 ? 4 : 2); NT *= 2) {
+    if (q.Cout % (128 * NT) || (force_nt && NT != force_nt)) continue;
+    for (int MT : MTs) {
+      if (force_mt && MT != force_mt) continue;
+      const int units = units_of(d, g, MT);
+      if (units > sep::kMaxUnits) continue;
+      const size_t lds = lds_bytes(c.KCH, units, MT, c.NA);
+      if (lds > 160 * 1024) continue;
+      const int splits = q.Cout / (128 * NT);
+      const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
+      if (wgs > 0x3fffffff) continue;
+      const int occ = (lds <= 80 * 1024 && MT * NT <= 8) ? 2 : 1;
+      const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 2;
+      const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 8.0 * c.KCH * 1024 + c.KCH * 64.0 * units * 16;
+      const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
+      const int64_t n = (wgs + cus - 1) / cus;
+      const double cost = (double)((n + occ - 1) / occ) * 3.5 + (double)n * work;
+      if (cost < best) { best = cost; c.MT = MT; c.NT = NT; c.splits = splits; }
+    }
+  }
+  return best < 1e300;
+}
+
+int num_cus() {
+  static int n = 0;
+  if (!n) {
+    int dev = 0, v = 0;
+    n = hipGetDevice(&dev) == hipSuccess &&
+                hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0
+            ? v
+            : 256;
+  }
+  return n;
+}
+
+bool plan(const ConvParams& d, const ConvParams& q, int cus, Geometry& g, SepChoice& c) {
+  if (tuning().no_sep || !geometry(d, g)) return false;
+  if (d.Cout != 256 && d.Cout != 512) return false;
+  if (q.depthwise || q.k != 1 || q.stride != 1 || q.pl != 0 || !q.w_packed || q.Cin != d.Cout || q.n_res_more || q.act_lut)
+    return false;
+  const int32_t ypitch = q.Tout + q.ypad;
+  if (q.Cout % 128 || q.Cout > 2048 || (d.Tin + d.xpad) % 16 || d.xbs % 16 || ypitch % 16 || q.ybs % 16) return false;
+  if ((d.Tout + 15) / 16 * 16 != ypitch) return false;
+  if ((uintptr_t)d.x % 16 || (uintptr_t)q.w % 16 || (uintptr_t)q.y % 16 || (uintptr_t)q.res % 16) return false;
+  if ((int64_t)q.Cout * ypitch >= 0x7fffffLL * 256) return false;                   // 32-bit offsets within a batch item
+  return pick(d, q, g, ypitch / 16, cus, c);
+}
+
+}  // namespace
+
+bool sep_supported(const ConvParams& d, const ConvParams& q) {
+  Geometry g;
+  SepChoice c;
+  return plan(d, q, 256, g, c);
+}
+
+size_t sep_image_bytes(const ConvParams& d) {
+  Geometry g;
+  return geometry(d, g) ? (size_t)d.Cout / 16 * g.NA * 1024 : 0;
+}
+
+hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st) {
+  Geometry g;
+  if (!geometry(d, g) || d.Cout % 16) return hipErrorInvalidValue;
+  return launch_kernel(sep_image_kernel, dim3((unsigned)(d.Cout / 16 * g.NA)), dim3(256), 0, st, d.w, d.Cout, d.k, d.dil, g.r,
+                       g.NA, img);
+}
+
+hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, hipStream_t st) {
+  Geometry g;
+  SepChoice c;
+  if (!plan(d, q, num_cus(), g, c)) return hipErrorInvalidValue;
+  SepParams p{};
+  p.x = d.x; p.img = img; p.dbias = d.bias; p.dm = d.m; p.ds = d.s; p.lut = d.act_lut;
+  p.xbs = d.xbs; p.xpitch = d.Tin + d.xpad; p.Tin = d.Tin;
+  p.o16 = -((d.pl + g.delta) / 16);
+  p.nk = g.nk;
+  p.units = units_of(d, g, c.MT);
+  p.dwoff = g.delta >> 2;
+  p.drelu = d.relu;
+  p.w = q.w; p.bias = q.bias; p.m = q.m; p.s = q.s; p.res = q.res; p.y = q.y;
+  p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.relu = q.relu;
+  p.B = d.B; p.gpr = p.ypitch / 16; p.tpr = (p.gpr + c.MT - 1) / c.MT;
+  p.splits = c.splits;
+  p.wgs = p.B * p.tpr * p.splits;
+  p.per_xcd = (p.wgs + 7) / 8;
+  const size_t lds = lds_bytes(c.KCH, p.units, c.MT, c.NA);
+  switch (c.NA) {
+    case 3: return launch_sep_na3(c, p, lds, st);
+    case 4: return launch_sep_na4(c, p, lds, st);
+    case 5: return launch_sep_na5(c, p, lds, st);
+    default: return launch_sep_na6(c, p, lds, st);
+  }
+}
+
+}  // namespace qasr

@@ -1,0 +1,51 @@
+// A depthwise layer and the pointwise layer that reads it as one launch (the separable module of the
+// QuartzNet family, the convolution module's tail of the Conformer): what sep.hip plans and launches and
+// sep_body.hpp computes.
+#pragma once
+#include "common.hpp"
+
+namespace qasr {
+
+struct SepParams {
+  // depthwise half: x rows (pitch xpitch, batch stride xbs, Tin frames), weight image (sep_image_*)
+  const int8_t* x;
+  const uint32_t* img;
+  const int32_t *dbias, *dm, *ds;    // dbias may be null
+  const uint8_t* lut;                // table of a unary activation between the two layers, or null
+  int64_t xbs;
+  int32_t xpitch, Tin;
+  int32_t o16;                       // first chunk of a tile's rows relative to its first frame: (-pl - delta) / 16
+  int32_t nk;                        // 4-tap steps
+  int32_t units;                     // 16-byte chunks per row in LDS (odd: 16 rows then start in different banks)
+  int32_t dwoff;                     // dwords between a row's start and the first window
+  int32_t drelu;
+  // pointwise half
+  const int8_t* w;                   // packed (common.hpp)
+  const int32_t *bias, *m, *s;       // bias may be null
+  const int8_t* res;                 // may be null
+  int8_t* y;
+  int64_t ybs;
+  int32_t ypitch, relu;
+  // tiles: row (batch item) b's groups [i gpr / tpr, (i + 1) gpr / tpr) of 16 frames make its tile i
+  int32_t B, gpr, tpr;
+  int32_t splits;                    // workgroups per tile, each with its own run of output channels
+  int32_t wgs, per_xcd;              // workgroups in all, and per XCD
+};
+
+struct SepChoice { int KCH, MT, NA, NT, splits; };
+
+// Can depthwise op d and pointwise op q (q reads d's output and nobody else does) run as one launch?
+bool sep_supported(const ConvParams& d, const ConvParams& q);
+// The 4-row Toeplitz image of a depthwise layer's weights (see sep_body.hpp)
+size_t sep_image_bytes(const ConvParams& d);
+hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st);
+// d.x, q.res, q.y set; d.y and q.x are not used
+hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, hipStream_t st);
+
+// one translation unit per tap range (sep_na3.hip ...): the launcher of its instantiations
+hipError_t launch_sep_na3(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st);
+hipError_t launch_sep_na4(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st);
+hipError_t launch_sep_na5(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st);
+hipError_t launch_sep_na6(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st);
+
+}  // namespace qasr

@@ -1,0 +1,8 @@
+// Instantiations of the fused separable module for 13 to 16 four-tap steps.
+#include "sep_body.hpp"
+
+namespace qasr {
+hipError_t launch_sep_na4(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st) {
+  return sep::launch_na<4>(c, p, lds, st);
+}
+}  // namespace qasr

@@ -35,6 +35,11 @@ Tuning read_env() {
     int mt = 0, nt = 0;
     if (sscanf(e, "%d,%d", &mt, &nt) >= 1) { t.cp_mt = mt; t.cp_nt = nt; }
   }
+  t.no_sep = getenv("QASR_NO_SEP") != nullptr;
+  if (const char* e = getenv("QASR_SEP")) {
+    int mt = 0, nt = 0;
+    if (sscanf(e, "%d,%d", &mt, &nt) >= 1) { t.sep_mt = mt; t.sep_nt = nt; }
+  }
   if (const char* e = getenv("QASR_PWT_MT")) t.pwt_mt = atoi(e);
   if (const char* e = getenv("QASR_SLOT_DEPTH")) {
     const int d = atoi(e);

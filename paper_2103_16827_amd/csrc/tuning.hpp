@@ -14,6 +14,8 @@
 //   QASR_NO_PW_LEAN                         pw_pipe: never the lean form (one pass per workgroup, two workgroups per unit)
 //   QASR_SLOT_DEPTH                         encoder: an op's output avoids the buffers the last N ops touched
 //                                           (default 4; 0 = the caller's slots are the buffers)
+//   QASR_NO_SEP                             encoder: no depthwise + pointwise pair in one launch
+//   QASR_SEP = "MT,NT"                      the same: groups per tile, 16-channel columns per wave (0: free)
 //   QASR_TEAM                               encoder: plan runs of layers for the persistent team kernel
 //                                           (experimental, off unless set)
 #pragma once
@@ -21,12 +23,13 @@
 namespace qasr {
 
 struct Tuning {
-  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false;
+  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false, no_sep = false;
   int pwp_mt = 0, pwp_split = 0;
   int dwp_r = 0, dwp_s = 0;
   int dw_r = 0;
   int cp_mt = 0, cp_nt = 0;
   int pwt_mt = 0;
+  int sep_mt = 0, sep_nt = 0;
   int slot_depth = 4;
 };
 
