@@ -286,14 +286,16 @@ qasr_status qasr_plan_slot_buffers(const int32_t* in_slot, const int32_t* res_sl
                                    int32_t* res_buf, int32_t* out_buf, int32_t* n_buffers);
 
 /* Bytes of workspace qasr_encoder_forward needs (all buffers of the plan above except the input
- * and the output, each rounded up to 256 bytes).  Known at create time because every shape and scale of the
+ * and the output, in rows rounded up to 16 frames, each buffer rounded up to 256 bytes).  Known at create time because every shape and scale of the
  * integer model is static (Sec. 2.1: static quantisation, nothing is sized at inference).  HOST only. */
 size_t qasr_encoder_workspace_bytes(const qasr_encoder* e);
 
 /* Runs every op in order on `stream`.  x: [B,Cin,Tin] of the first op's descriptor; y: output
  * of the last op; workspace: device, 256-byte aligned, >= qasr_encoder_workspace_bytes(e).
- * Enqueues n_ops kernels (plus one per activation) and returns; allocates nothing; may be
- * captured into a HIP graph. */
+ * Enqueues at most n_ops kernels (plus one per activation, plus a copy of x and of y where their rows
+ * are not multiples of 16 frames and a layer there wants aligned ones) and returns; allocates nothing;
+ * may be captured into a HIP graph.  A depthwise layer and the pointwise layer that is the only
+ * reader of its output run as one launch where their shapes allow (same bits). */
 qasr_status qasr_encoder_forward(const qasr_encoder* e, const int8_t* x, int8_t* y,
                                  void* workspace, size_t workspace_bytes, void* stream);
 
@@ -337,7 +339,7 @@ qasr_status qasr_encoder_graph_create(const qasr_encoder* e, const int8_t* x, in
 qasr_status qasr_encoder_graph_launch(qasr_encoder_graph* g, void* stream);
 void qasr_encoder_graph_destroy(qasr_encoder_graph* g);
 
-/* Same as qasr_encoder_forward, but brackets every op with HIP events, waits for completion and
+/* Same as qasr_encoder_forward_layerwise, but brackets every op with HIP events, waits for completion and
  * writes each op's device time in milliseconds to op_ms[0..n_ops) (HOST memory): the interval
  * between the events around the op minus an equal share of what the inner events cost (the
  * forward is also run once without them in the same call; the op times add up to that run's
@@ -370,8 +372,8 @@ int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i);
  * _forward_f32 and the graph entry points use the plan; x and y must then be 16-byte aligned
  * (otherwise every layer is launched by itself).
  *   qasr_encoder_op_in_team: 1 if op i is inside such a run, 0 if not, -1 if i is out of range.
- *   qasr_encoder_forward_layerwise: the forward with every layer as a launch of its own, whatever
- *     the plan (same arguments and errors as qasr_encoder_forward).
+ *   qasr_encoder_forward_layerwise: the forward with every layer as a launch of its own (depthwise +
+ *     pointwise pairs too), whatever the plan (same arguments and errors as qasr_encoder_forward).
  *   qasr_encoder_team_check: after the caller has synchronised the stream: *aborted = 1 if a wait
  *     inside a persistent kernel of the last forward gave up (its waits are bounded: about a second;
  *     the outputs of that forward are then invalid), else 0.  Synchronous (a small copy).

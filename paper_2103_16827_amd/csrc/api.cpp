@@ -902,7 +902,9 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     x = xc;
   }
   int8_t* const y_user = y;
-  const bool copy_y = e->copy_out && ypad == 0;
+  const bool fuse = team && !ev;                // (timed and layer-by-layer forwards launch every layer by itself)
+  // (a fused pair stores rows of any length by itself)
+  const bool copy_y = e->copy_out && ypad == 0 && !(fuse && n > 1 && e->ops[n - 2].sep);
   if (copy_y) {
     ypad = row_pad(e->out_T);
     y = ws + e->copy_out_off;
@@ -920,7 +922,6 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     for (int32_t r = 0; r < op.n_more_res; ++r)
       p.res_more[r] = op.more_res_slots[r] == 0 ? x : ws + e->slot_off[op.more_res_slots[r]];
   };
-  const bool fuse = team && !ev;                // (timed and layer-by-layer forwards launch every layer by itself)
   for (size_t i = 0; i < n; ++i) {
     if (use_team && e->run_of[i] >= 0) {
       const qasr_encoder::TeamRun& r = e->runs[e->run_of[i]];

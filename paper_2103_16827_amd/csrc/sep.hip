@@ -20,6 +20,12 @@ bool geometry(const ConvParams& d, Geometry& g) {
   return g.NA <= 6;
 }
 
+// rows that start at 16-byte boundaries and are padded to them are moved in whole chunks
+bool x_ragged(const ConvParams& d) { return (d.Tin + d.xpad) % 16 || d.xbs % 16 || (uintptr_t)d.x % 16; }
+bool y_ragged(const ConvParams& q) {
+  return (q.Tout + q.ypad) % 16 || q.ybs % 16 || (uintptr_t)q.y % 16 || (uintptr_t)q.res % 16;
+}
+
 int units_of(const ConvParams& d, const Geometry& g, int MT) {
   const int need = (g.delta + 16 * MT + d.dil * (d.k - 1) + 15) / 16;
   return need | 1;
@@ -44,35 +50,34 @@ __global__ __launch_bounds__(256) void sep_image_kernel(const int8_t* __restrict
   img[idx] = v;
 }
 
-size_t lds_bytes(int KCH, int units, int MT, int NA) { return (size_t)KCH * 8192 + 8 * (size_t)sep::row_bytes(units, MT, NA) + 256; }
+size_t lds_bytes(int KCH, int units, int MT, int NA) { return (size_t)KCH * 8192 + sep::kWaves * (size_t)sep::row_bytes(units, MT, NA) + 256; }
 
-// Tile (MT groups x 128 NT output channels per workgroup) with the least time on the busiest compute
-// unit: the workgroups a unit holds together share its matrix pipes (10 cycles per 4x4x4 product, 17.7
-// per 16x16x64 one) and its 64 bytes per cycle from the L2 (weight image and packed weights, which every
-// workgroup streams whole); a round costs the latency of its first loads and of its last stores.
+// Tile (MT groups x 256 NT output channels per workgroup) with the least time on the busiest compute
+// unit, one workgroup at a time: its matrix pipes (10 cycles per 4x4x4 product, 17.7 per 16x16x64 one),
+// half hidden under them its 64 bytes per cycle from the L2 (weight image and packed weights, which every
+// workgroup streams whole), and the latency of its first loads and last stores.
 bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int groups_per_row, int cus, SepChoice& c) {
   static const int MTs[] = {1, 2, 4, 7};
   c.KCH = d.Cout / 64;
   c.NA = g.NA;
   double best = 1e300;
   const int force_mt = tuning().sep_mt, force_nt = tuning().sep_nt;
-  for (int NT = 1; NT <= (c.KCH == 8 ? 4 : 2); NT *= 2) {
-    if (q.Cout % (128 * NT) || (force_nt && NT != force_nt)) continue;
+  for (int NT = 1; NT <= 2; ++NT) {
+    if (q.Cout % (256 * NT) || (force_nt && NT != force_nt)) continue;
     for (int MT : MTs) {
-      if (force_mt && MT != force_mt) continue;
+      if ((force_mt && MT != force_mt) || (c.ragged && MT > 4)) continue;
       const int units = units_of(d, g, MT);
       if (units > sep::kMaxUnits) continue;
       const size_t lds = lds_bytes(c.KCH, units, MT, c.NA);
       if (lds > 160 * 1024) continue;
-      const int splits = q.Cout / (128 * NT);
+      const int splits = q.Cout / (256 * NT);
       const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
       if (wgs > 0x3fffffff) continue;
-      const int occ = (lds <= 80 * 1024 && MT * NT <= 8) ? 2 : 1;
-      const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 2;
-      const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 8.0 * c.KCH * 1024 + c.KCH * 64.0 * units * 16;
+      const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 4;
+      const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 16.0 * c.KCH * 1024 + c.KCH * 64.0 * units * 16;
       const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
       const int64_t n = (wgs + cus - 1) / cus;
-      const double cost = (double)((n + occ - 1) / occ) * 3.5 + (double)n * work;
+      const double cost = (double)n * (3.5 + work);
       if (cost < best) { best = cost; c.MT = MT; c.NT = NT; c.splits = splits; }
     }
   }
@@ -96,12 +101,13 @@ bool plan(const ConvParams& d, const ConvParams& q, int cus, Geometry& g, SepCho
   if (d.Cout != 256 && d.Cout != 512) return false;
   if (q.depthwise || q.k != 1 || q.stride != 1 || q.pl != 0 || !q.w_packed || q.Cin != d.Cout || q.n_res_more || q.act_lut)
     return false;
-  const int32_t ypitch = q.Tout + q.ypad;
-  if (q.Cout % 128 || q.Cout > 2048 || (d.Tin + d.xpad) % 16 || d.xbs % 16 || ypitch % 16 || q.ybs % 16) return false;
-  if ((d.Tout + 15) / 16 * 16 != ypitch) return false;
-  if ((uintptr_t)d.x % 16 || (uintptr_t)q.w % 16 || (uintptr_t)q.y % 16 || (uintptr_t)q.res % 16) return false;
-  if ((int64_t)q.Cout * ypitch >= 0x7fffffLL * 256) return false;                   // 32-bit offsets within a batch item
-  return pick(d, q, g, ypitch / 16, cus, c);
+  if (q.Cout % 256 || q.Cout > 2048 || (uintptr_t)q.w % 16 || q.Cin != d.Cout) return false;
+  if (d.Tout != q.Tin && (d.Tout + 15) / 16 * 16 != q.Tin) return false;            // (q may run over the pitch)
+  // 32-bit offsets within 16 rows of x and a batch item of y
+  if ((int64_t)16 * (d.Tin + d.xpad) > 0x7fffffffLL || (int64_t)q.Cout * (q.Tout + q.ypad) > 0x7fffff00LL) return false;
+  if (d.Tin < 4 || q.Tout < 4) return false;
+  c.ragged = x_ragged(d) || y_ragged(q);
+  return pick(d, q, g, (q.Tout + 15) / 16, cus, c);
 }
 
 }  // namespace
@@ -137,8 +143,9 @@ hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams
   p.dwoff = g.delta >> 2;
   p.drelu = d.relu;
   p.w = q.w; p.bias = q.bias; p.m = q.m; p.s = q.s; p.res = q.res; p.y = q.y;
-  p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.relu = q.relu;
-  p.B = d.B; p.gpr = p.ypitch / 16; p.tpr = (p.gpr + c.MT - 1) / c.MT;
+  p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.Tout = q.Tout; p.relu = q.relu;
+  p.B = d.B; p.gpr = (q.Tout + 15) / 16; p.tpr = (p.gpr + c.MT - 1) / c.MT;
+  p.yragged = y_ragged(q);
   p.splits = c.splits;
   p.wgs = p.B * p.tpr * p.splits;
   p.per_xcd = (p.wgs + 7) / 8;

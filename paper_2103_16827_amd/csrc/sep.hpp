@@ -26,13 +26,14 @@ struct SepParams {
   int8_t* y;
   int64_t ybs;
   int32_t ypitch, relu;
+  int32_t Tout, yragged;             // frames per row; rows (y and residual) not padded to whole aligned chunks
   // tiles: row (batch item) b's groups [i gpr / tpr, (i + 1) gpr / tpr) of 16 frames make its tile i
   int32_t B, gpr, tpr;
   int32_t splits;                    // workgroups per tile, each with its own run of output channels
   int32_t wgs, per_xcd;              // workgroups in all, and per XCD
 };
 
-struct SepChoice { int KCH, MT, NA, NT, splits; };
+struct SepChoice { int KCH, MT, NA, NT, splits; bool ragged; };
 
 // Can depthwise op d and pointwise op q (q reads d's output and nobody else does) run as one launch?
 bool sep_supported(const ConvParams& d, const ConvParams& q);

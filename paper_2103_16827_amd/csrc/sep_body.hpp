@@ -5,8 +5,8 @@
 //
 // As two launches a module costs two launch gaps and two chains of first loads (about 5 us each, most
 // of the 8 us a depthwise and the 14 us a pointwise layer of 512 channels take at batch 32), and h
-// travels to memory and back.  Here a workgroup of 8 waves owns up to MT 16-frame groups of one batch
-// item and all channels of them: every wave computes the depthwise layer of Cin / 8 channels for those
+// travels to memory and back.  Here a workgroup of 16 waves owns up to MT 16-frame groups of one batch
+// item and all channels of them: every wave computes the depthwise layer of Cin / 16 channels for those
 // frames into the LDS tile that the pointwise half multiplies from.  Only x is read twice (the halo
 // of k - 1 frames between neighbouring tiles, out of the L2).
 //
@@ -21,7 +21,7 @@
 // address measured 59 cycles against 16.
 //
 // Pointwise half: as pw_pipe_body.hpp (transposing LDS reads, packed weights straight from L2), one
-// pass of 16 NT channels per wave, NT up to 4, compiler-visible loads.
+// pass of 16 NT channels per wave, compiler-visible loads.
 #pragma once
 #include "sep.hpp"
 
@@ -35,6 +35,7 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kStoreThrough = 17;    // sc0 sc1: the output rows are written through (see pw_pipe_body.hpp)
+constexpr int kWaves = 16;           // 4 per SIMD: each phase's latencies pass under another wave's products
 constexpr int kMaxUnits = 15;        // chunks per row in LDS: 16 rows are at most four 64-lane loads
 
 __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
@@ -42,17 +43,42 @@ __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
       (v2i __attribute__((address_space(3)))*)(const_cast<unsigned char*>(p)));
 }
 
-// bytes of a wave's row buffer: 16 rows, what the windows of the last row read past it, and room for
-// two 16-row blocks of the output staging
+// bytes of a wave's row buffer: 16 rows and what the windows of the last row read past it, at least
+// the 16 x 128 bytes of the output staging
 __host__ __device__ inline int row_bytes(int units, int MT, int NA) {
   const int rows = 15 * 16 * units + 16 * (MT + NA) + 32;
-  return ((rows > 4096 ? rows : 4096) + 15) & ~15;
+  return ((rows > 2048 ? rows : 2048) + 15) & ~15;
 }
 
-template <int KCH, int MT, int NA, int NT>
-__global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
-  extern __shared__ __align__(128) unsigned char lds[];   // [Cin][128 B] tile, [8 waves] row buffers, table
-  constexpr int NBLK = KCH / 2;                     // 16-channel blocks per wave
+typedef int unaligned_v4i __attribute__((ext_vector_type(4), aligned(1), may_alias));
+
+// 16 frames of a row of T (4 <= T), at any byte address; frames past the end are 0.  (A row may be the
+// last thing in its allocation: only its own bytes are read and written.)
+__device__ __forceinline__ v4i load_chunk(const int8_t* row, int t, int T) {
+  v4i v;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) v[d] = t + 4 * d < T ? (int)load_row_u32(row, t + 4 * d, T) : 0;
+  return v;
+}
+__device__ __forceinline__ void store_chunk(int8_t* row, int t, int T, v4i v) {
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const int td = t + 4 * d;
+    if (td + 4 <= T) store_u32(row + td, (uint32_t)v[d]);
+    if (td + 4 > T && td < T) {
+      row[td] = (int8_t)v[d];
+      if (td + 1 < T) row[td + 1] = (int8_t)(v[d] >> 8);
+      if (td + 2 < T) row[td + 2] = (int8_t)(v[d] >> 16);
+    }
+  }
+}
+
+// RAGGED: x or y (and the residual) are the caller's, rows of any length at any address
+template <int KCH, int MT, int NA, int NT, bool RAGGED>
+__global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
+  extern __shared__ __align__(128) unsigned char lds[];   // [Cin][128 B] tile, [kWaves] row buffers, table
+  constexpr int CPW = KCH * 64 / kWaves;            // depthwise channels per wave
+  constexpr int NBLK = CPW / 16;                    // in blocks of 16
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive workgroups go round-robin to the 8 XCDs: each XCD takes a contiguous run of tiles
@@ -66,20 +92,22 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
   unsigned char* const xs = lds;
   const int rb = row_bytes(p.units, MT, NA);
   unsigned char* const rows = lds + KCH * 64 * 128 + wave * rb;
-  unsigned char* const lut = lds + KCH * 64 * 128 + 8 * rb;
+  unsigned char* const lut = lds + KCH * 64 * 128 + kWaves * rb;
   if (p.lut && tid < 64) reinterpret_cast<uint32_t*>(lut)[tid] = reinterpret_cast<const uint32_t*>(p.lut)[tid];
 
   // ---- depthwise half: 16 channels at a time.  Chunk L of the 16 rows (row L / units, chunk L % units)
   // is loaded by lane L % 64; chunks outside [0, Tin) are zero, the chunk a row ends in is masked.
-  const int c_wave = wave * (KCH * 8);
-  int64_t xoff[4];
-  int keep[4];                                      // frames of the chunk that exist: 0 = none, >= 16 = all
+  const int c_wave = wave * CPW;
+  int32_t xoff[4];                                  // byte offset of the chunk within the 16 rows
+  uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
+  const int t_last = p.Tin & ~15;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int L = lane + 64 * j, ch = L / p.units, u = L - ch * p.units;
     const int t = 16 * (g0 + p.o16 + u);
-    keep[j] = (ch < 16 && t >= 0) ? p.Tin - t : 0;
-    xoff[j] = (int64_t)ch * p.xpitch + t;
+    if (ch < 16 && t >= 0 && t < p.Tin) in |= 1u << j;
+    if (t == t_last) last |= 1u << j;
+    xoff[j] = ch * p.xpitch + t;
   }
   const int8_t* const xw = p.x + (int64_t)b * p.xbs + (int64_t)c_wave * p.xpitch;
   v4i xr[4];
@@ -88,23 +116,27 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       xr[j] = (v4i){0, 0, 0, 0};
-      if (keep[j] > 0) xr[j] = *reinterpret_cast<const v4i*>(src + xoff[j]);
+      if (in & (1u << j)) {
+        if (RAGGED && (last & (1u << j))) xr[j] = load_chunk(src + xoff[j] - t_last, t_last, p.Tin);
+        else xr[j] = *reinterpret_cast<const unaligned_v4i*>(src + xoff[j]);
+      }
     }
   };
   auto put_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (keep[j] > 0 && keep[j] < 16) xr[j] = keep_bytes(xr[j], keep[j]);
+      if (!RAGGED && (last & (1u << j))) xr[j] = keep_bytes(xr[j], p.Tin & 15);
       if (lane + 64 * j < 16 * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = xr[j];
     }
   };
   const int ch_l = lane >> 2, n_l = lane & 3;
-  v4i aw[NA];
+  v4i aw[3];                                        // weight quads, two steps ahead
   int32_t db, dm, dsv;
+  const v4i* const asrc = reinterpret_cast<const v4i*>(p.img) + (int64_t)(wave * NBLK) * (NA * 64) + lane;
+  auto load_quad_weights = [&](int blk, int a) __attribute__((always_inline)) { aw[a % 3] = asrc[(blk * NA + a) * 64]; };
   auto load_weights = [&](int blk) __attribute__((always_inline)) {
-    const v4i* src = reinterpret_cast<const v4i*>(p.img) + (int64_t)(wave * NBLK + blk) * (NA * 64) + lane;
-#pragma unroll
-    for (int a = 0; a < NA; ++a) aw[a] = src[a * 64];
+    load_quad_weights(blk, 0);
+    load_quad_weights(blk, 1);
     const int c = c_wave + 16 * blk + ch_l;
     db = p.dbias ? p.dbias[c] : 0;
     dm = p.dm[c];
@@ -122,20 +154,31 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
     put_rows();
     asm volatile("" ::: "memory");                  // (lanes read what other lanes of the wave wrote: LDS is in order)
     __builtin_amdgcn_sched_barrier(0);
-    if (blk + 1 < NBLK) load_rows(blk + 1);         // on their way under this block's products
-    uint32_t wd[4 * (MT - 1 + NA)];
+    // window quads a .. a + MT - 1 are what step quad a multiplies; one more is on its way
+    uint32_t wd[MT + 1][4];
+    auto read_quad = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < 4 * (MT - 1 + NA); ++c) wd[c] = *reinterpret_cast<const uint32_t*>(win + 4 * c);
+      for (int i = 0; i < 4; ++i) wd[a % (MT + 1)][i] = *reinterpret_cast<const uint32_t*>(win + 16 * a + 4 * i);
+    };
+#pragma unroll
+    for (int a = 0; a < MT; ++a) read_quad(a);
     v4i acc[MT];
 #pragma unroll
     for (int q = 0; q < MT; ++q) acc[q] = (v4i){db, db, db, db};
 #pragma unroll
-    for (int i = 0; i < 4 * NA; ++i)
-      if (i < 4 * (NA - 1) + 1 || i < p.nk) {
+    for (int a = 0; a < NA; ++a) {
+      if (a + 1 < NA) read_quad(a + MT);
+      if (a + 2 < NA) load_quad_weights(blk, a + 2);
 #pragma unroll
-        for (int q = 0; q < MT; ++q)
-          acc[q] = __builtin_amdgcn_mfma_i32_4x4x4i8(aw[i >> 2][i & 3], (int)wd[4 * q + i], acc[q], 0, 0, 0);
-      }
+      for (int i = 0; i < 4; ++i)
+        if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
+#pragma unroll
+          for (int q = 0; q < MT; ++q)
+            acc[q] = __builtin_amdgcn_mfma_i32_4x4x4i8(aw[a % 3][i], (int)wd[(a + q) % (MT + 1)][i], acc[q], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      if (a == 1 && blk + 1 < NBLK) load_rows(blk + 1);   // on their way under the rest of the block
+    }
     const int32_t m = dm, s = dsv;
     if (blk + 1 < NBLK) load_weights(blk + 1);
     auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
@@ -162,7 +205,7 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
 
   // ---- pointwise half: 16 NT output channels of this wave
   const int n = lane & 15, gi = lane >> 4;
-  const int co_w = (cs * 8 + wave) * 16 * NT;
+  const int co_w = (cs * kWaves + wave) * 16 * NT;
   v4i wb[3][NT];
   const v4i* const wsrc = reinterpret_cast<const v4i*>(p.w) + (int64_t)(co_w >> 4) * (KCH * 64) + lane;
   auto load_w = [&](int kc, v4i (&dst)[NT]) __attribute__((always_inline)) {
@@ -185,23 +228,25 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
   // residual rows and output rows: lane -> (row lane / 8 of 8, slot lane % 8), the unit in that slot
   const int u_l = (lane & 7) ^ (lane >> 3);
   const bool u_ok = u_l < gn;
-  const int64_t yoff = (int64_t)b * p.ybs + (int64_t)(co_w + (lane >> 3)) * p.ypitch + 16 * (g0 + u_l);
-  v4i rr[2][2];
-  auto load_res = [&](int nt, v4i (&dst)[2]) __attribute__((always_inline)) {
+  const int t_l = 16 * (g0 + u_l);
+  const int64_t yrow = (int64_t)b * p.ybs + (int64_t)(co_w + (lane >> 3)) * p.ypitch;   // of this lane's first row
+  v4i rr[NT][2];
+  auto load_res = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (u_ok) dst[h] = *reinterpret_cast<const v4i*>(p.res + yoff + (int64_t)(16 * nt + 8 * h) * p.ypitch);
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int8_t* const row = p.res + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch;
+        if (u_ok) rr[nt][h] = RAGGED && p.yragged ? load_chunk(row, t_l, p.Tout) : *reinterpret_cast<const v4i*>(row + t_l);
+      }
   };
-  if (p.res) {
-    load_res(0, rr[0]);
-    if (NT > 1) load_res(1, rr[1]);
-  }
   __syncthreads();                                  // the tile is complete
   const int l16 = lane & 15, jr = l16 >> 1;
   const uint32_t abase = (uint32_t)((8 * gi + jr) * 128 + 8 * (l16 & 1)) | (uint32_t)(jr << 4);
 #pragma unroll
   for (int kc = 0; kc < KCH; ++kc) {
     if (kc + 2 < KCH) load_w(kc + 2, wb[(kc + 2) % 3]);
+    if (kc + 2 == KCH && p.res) load_res();         // (into what the weight ring no longer needs)
     __builtin_amdgcn_sched_barrier(0);
     const unsigned char* ab = xs + kc * 8192;
     v2i ar[3][2];
@@ -233,16 +278,15 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
   const bool fast = __all(ok);
   const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
       p.y + (int64_t)b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
-  const uint32_t ylane = (uint32_t)(lane >> 3) * (uint32_t)p.ypitch + 16u * (uint32_t)(g0 + u_l);
+  const uint32_t ylane = (uint32_t)(lane >> 3) * (uint32_t)p.ypitch + (uint32_t)t_l;
   auto epilogue = [&](auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      unsigned char* const st = rows + 2048 * (nt & 1);
+      unsigned char* const st = rows;
       if (RES) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) *reinterpret_cast<v4i*>(st + 1024 * h + 16 * lane) = rr[nt & 1][h];
-        if (nt + 2 < NT) load_res(nt + 2, rr[nt & 1]);
+        for (int h = 0; h < 2; ++h) *reinterpret_cast<v4i*>(st + 1024 * h + 16 * lane) = rr[nt][h];
         asm volatile("" ::: "memory");
       }
 #pragma unroll
@@ -260,6 +304,10 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const v4i o = *reinterpret_cast<const v4i*>(st + 1024 * h + 16 * lane);
+        if (RAGGED && p.yragged) {                  // (uniform)
+          if (u_ok) store_chunk(p.y + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch, t_l, p.Tout, o);
+          continue;
+        }
         const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};
         const uint32_t off = u_ok ? ylane + (uint32_t)(16 * nt + 8 * h) * (uint32_t)p.ypitch : 0xfffffff0u;
         __builtin_amdgcn_raw_buffer_store_b128(ov, yrs, off, 0, kStoreThrough);
@@ -279,20 +327,21 @@ __global__ __launch_bounds__(512, 2) void sep_kernel(SepParams p) {
   }
 }
 
-template <int KCH, int MT, int NA, int NT>
+template <int KCH, int MT, int NA, int NT, bool RAGGED>
 hipError_t launch_t(const SepParams& p, size_t lds, hipStream_t st) {
   static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
-  if (const hipError_t e = ensure_max_dynamic_lds((const void*)sep_kernel<KCH, MT, NA, NT>, lds_raised); e != hipSuccess)
+  if (const hipError_t e = ensure_max_dynamic_lds((const void*)sep_kernel<KCH, MT, NA, NT, RAGGED>, lds_raised); e != hipSuccess)
     return e;
-  return launch_kernel(sep_kernel<KCH, MT, NA, NT>, dim3((unsigned)(8 * p.per_xcd)), dim3(512), lds, st, p);
+  return launch_kernel(sep_kernel<KCH, MT, NA, NT, RAGGED>, dim3((unsigned)(8 * p.per_xcd)), dim3(64 * kWaves), lds, st, p);
 }
 
-// the instantiations of one tap range
+// the instantiations of one tap range (ragged rows: at most 4 groups, more do not fit the registers)
 template <int NA>
 hipError_t launch_na(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st) {
-#define QASR_CASE(K, M, N) if (c.KCH == K && c.MT == M && c.NT == N) return launch_t<K, M, NA, N>(p, lds, st);
-#define QASR_MTS(K, N) QASR_CASE(K, 1, N) QASR_CASE(K, 2, N) QASR_CASE(K, 4, N) QASR_CASE(K, 7, N)
-  QASR_MTS(4, 1) QASR_MTS(4, 2) QASR_MTS(8, 1) QASR_MTS(8, 2) QASR_MTS(8, 4)
+#define QASR_CASE(K, M, N, R) if (c.KCH == K && c.MT == M && c.NT == N && c.ragged == R) return launch_t<K, M, NA, N, R>(p, lds, st);
+#define QASR_MTS(K, N) QASR_CASE(K, 1, N, false) QASR_CASE(K, 2, N, false) QASR_CASE(K, 4, N, false) QASR_CASE(K, 7, N, false) \
+                       QASR_CASE(K, 1, N, true) QASR_CASE(K, 2, N, true) QASR_CASE(K, 4, N, true)
+  QASR_MTS(4, 1) QASR_MTS(4, 2) QASR_MTS(8, 1) QASR_MTS(8, 2)
 #undef QASR_MTS
 #undef QASR_CASE
   return hipErrorInvalidValue;
