@@ -47,12 +47,18 @@ struct CpGeom {
   int per_xcd;        // ceil(tiles / 8): tiles of one XCD (the grid is 8 * per_xcd workgroups)
 };
 
-template <int MT, int NT>
-__global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) {
-  extern __shared__ __align__(16) unsigned char xs[];   // [2 buffers][rows][kXS]
+// KG > 1: the taps of a chunk are split over KG groups of 4 waves that share the chunk in LDS, and their
+// accumulators are summed through LDS at the end.  A launch with fewer tiles than the chip has SIMDs to
+// feed leaves one wave per SIMD, which spends most of a step waiting (a 64 x 128 tile: 128 cycles of
+// products, 380 per step); with four groups the latencies pass under the other groups' products.
+template <int MT, int NT, int KG>
+__global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeom g) {
+  extern __shared__ __align__(16) unsigned char xs[];   // [2 buffers][rows][kXS]; KG > 1: the partial sums after that
   constexpr int TM = 16 * MT, TN = 64 * NT;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;   // within the group
+  const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8)) : 0;
+  const int j0 = KG > 1 ? kg * p.k / KG : 0, j1 = KG > 1 ? (kg + 1) * p.k / KG : p.k;   // this group's taps
   const int n = lane & 15, gi = lane >> 4;
 
   // Workgroup -> tile.  Consecutive workgroups go round-robin to the 8 XCDs, each with an L2 of its
@@ -146,8 +152,8 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
   };
 
   // ---- weights: step q = (chunk, tap) of the flat contraction, ring of three steps
-  const int Q = g.kchunks * p.k;
-  int wkc = 0, wj = 0;                              // chunk and tap of the next step to request
+  const int Q = g.kchunks * (j1 - j0);
+  int wkc = 0, wj = j0;                             // chunk and tap of the next step to request
   // (the packed buffer is below 2 GiB: a wave-uniform base per step plus a 32-bit lane offset)
   uint32_t woff[NT];
 #pragma unroll
@@ -157,8 +163,8 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
     const int8_t* wbase = p.w + (int64_t)(wj * g.co16n * g.kchunks + wkc) * 1024;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) dst[nt] = *reinterpret_cast<const v4i*>(wbase + woff[nt]);
-    if (wkc * p.k + wj < Q - 1) {                   // (the stream stays on its last step at the end)
-      if (++wj == p.k) { wj = 0; ++wkc; }
+    if (++wj == j1) {                               // (the stream stays on its last step at the end)
+      if (wkc + 1 < g.kchunks) { wj = j0; ++wkc; } else { --wj; }
     }
   };
 
@@ -169,17 +175,18 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
   v4i acc[MT][NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    const int32_t bv = p.bias ? p.bias[co_ld[nt]] : 0;
+    const int32_t bv = p.bias && kg == 0 ? p.bias[co_ld[nt]] : 0;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = (v4i){bv, bv, bv, bv};
   }
 
   // ---- prologue: chunk 0 into buffer 0, weights of steps 0 and 1
   v4i wb[3][NT];
-  issue_chunk(0);
+  // (the groups take turns at bringing in a chunk: chunk kc is group kc mod KG's)
+  if (kg == 0) issue_chunk(0);
   load_w(wb[0]);
   load_w(wb[1]);
-  commit_chunk(0);
+  if (kg == 0) commit_chunk(0);
   __syncthreads();
 
   // The A operands (one 16-byte LDS read per 16 frames) go through a ring of three registers,
@@ -192,19 +199,19 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
   auto read_a = [&](const unsigned char* arow, int mt) __attribute__((always_inline)) {
     return *reinterpret_cast<const v4i*>(arow + 16 * mt * p.stride * kXS);
   };
-  const int jmid = p.k >> 1;                        // the tap at which the next chunk is committed
-  int kc = 0, j = 0;                                // chunk and tap of the current step
-  if (g.kchunks > 1) issue_chunk(1);
+  const int jmid = j0 + ((j1 - j0) >> 1);           // the tap at which the next chunk is committed
+  int kc = 0, j = j0;                               // chunk and tap of the current step
+  if (g.kchunks > 1 && kg == 1 % KG) issue_chunk(1);
   v4i ar[3];
-  ar[0] = read_a(arow_of(0, 0), 0);
-  ar[1] = read_a(arow_of(0, 0), 1);
+  ar[0] = read_a(arow_of(0, j0), 0);
+  ar[1] = read_a(arow_of(0, j0), 1);
   for (int q = 0; q < Q; q += 3) {
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
       if (q + u < Q) {
         load_w(wb[(u + 2) % 3]);
         const unsigned char* arow = arow_of(kc, j);
-        const bool last_tap = j + 1 == p.k;
+        const bool last_tap = j + 1 == j1;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           if (mt + 2 < MT) {
@@ -216,21 +223,50 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
           for (int nt = 0; nt < NT; ++nt)
             acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[(u * MT + mt) % 3], wb[u][nt], acc[mt][nt], 0, 0, 0);
         }
-        if (j == jmid && kc + 1 < g.kchunks) commit_chunk((kc + 1) & 1);
+        if (j == jmid && kc + 1 < g.kchunks && kg == (kc + 1) % KG) commit_chunk((kc + 1) & 1);
         if (last_tap) {
-          j = 0;
+          j = j0;
           ++kc;
           __syncthreads();                          // chunk kc is in LDS; chunk kc - 1 has been read by all
-          if (kc + 1 < g.kchunks) issue_chunk(kc + 1);
+          if (kc + 1 < g.kchunks && kg == (kc + 1) % KG) issue_chunk(kc + 1);
           if (kc < g.kchunks) {
-            ar[((u + 1) * MT) % 3] = read_a(arow_of(kc, 0), 0);
-            ar[((u + 1) * MT + 1) % 3] = read_a(arow_of(kc, 0), 1);
+            ar[((u + 1) * MT) % 3] = read_a(arow_of(kc, j0), 0);
+            ar[((u + 1) * MT + 1) % 3] = read_a(arow_of(kc, j0), 1);
           }
         } else {
           ++j;
         }
       }
     }
+  }
+
+  // ---- KG > 1: group o finishes the frame groups mt with mt KG / MT == o; every other group's sums of
+  // them reach it through LDS (past the activation buffers: no wave may be reading those any more)
+  if constexpr (KG > 1) {
+    static_assert(MT % KG == 0, "frame groups per wave group");
+    // [owner][the other groups][frame group of the owner][nt][wave][lane]
+    v4i* const red = reinterpret_cast<v4i*>(xs + 2 * bufbytes);
+    auto slot = [&](int o, int src, int mt, int nt) __attribute__((always_inline)) {
+      const int rank = src < o ? src : src - 1;
+      return red + ((((o * (KG - 1) + rank) * (MT / KG) + mt % (MT / KG)) * NT + nt) * 4 + wave) * 64 + lane;
+    };
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (mt * KG / MT != kg) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) *slot(mt / (MT / KG), kg, mt, nt) = acc[mt][nt];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (mt * KG / MT == kg) {
+#pragma unroll
+        for (int o = 1; o < KG; ++o) {
+          const int src = (kg + o) % KG;
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += *slot(kg, src, mt, nt);
+        }
+      }
   }
 
   // ---- epilogue: lane (n, gi) holds frames t0 + 16 mt + 4 gi + (0..3) of channel co_w + 16 nt + n
@@ -245,7 +281,7 @@ __global__ __launch_bounds__(256) void conv_pipe_kernel(ConvParams p, CpGeom g) 
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int t = t0 + 16 * mt + 4 * gi;
-      if (t >= p.Tout) continue;
+      if (t >= p.Tout || (KG > 1 && mt * KG / MT != kg)) continue;
       uint32_t rr = 0;
       if (p.res) rr = load_row_u32(p.res + orow, t, trow);
       int32_t radd[4];
@@ -273,16 +309,25 @@ int lds_rows(const ConvParams& p, int TM) {
   return (((TM - 1) * p.stride + p.dil * (p.k - 1) + 1 + 3) + 3) & ~3;
 }
 
+struct CpTile { int MT, NT, KG; };
+
+size_t lds_bytes(const ConvParams& p, const CpTile& c) {
+  const size_t x = (size_t)2 * lds_rows(p, 16 * c.MT) * kXS;
+  return c.KG > 1 ? x + (size_t)(c.KG - 1) * c.MT * c.NT * 4096 : x;
+}
+
 // Cycles per (chunk, tap) step on the busiest compute unit, from a small model: a unit holds `occ`
-// workgroups (one wave each per SIMD); a SIMD with w resident waves spends w M cycles in the matrix
+// workgroups, KG waves each per SIMD; a SIMD with w workgroups spends w M cycles in the matrix
 // pipe per step (M = 16 MT NT), a lone wave cannot go below M plus its own latencies (operand reads,
-// weight request, loop), and the operand reads of all waves share the unit's LDS port.
-double step_cycles(int MT, int NT, int64_t blocks) {
-  const int occ = NT == 4 ? 2 : MT > 4 ? 3 : 4;           // bound by registers
+// weight request, loop) for each of its group's steps, and the operand reads of all waves share the
+// unit's LDS port.
+double step_cycles(const CpTile& c, int64_t blocks) {
+  const int MT = c.MT, NT = c.NT;
+  const int occ = c.KG == 4 ? 1 : c.KG == 2 ? (MT * NT <= 8 ? 2 : 1) : NT == 4 ? 2 : MT > 4 ? 3 : 4;   // bound by registers
   // (a fourth bound: every wave streams its own NT KiB of weights per step out of L2; fitted, with
   // the lone wave's latency, to per-layer times of the Jasper shape under every forced tile: only
   // the widest layer, 768 -> 896 with k = 29, changes its tile, 250 -> 221 us)
-  const double M = 16.0 * MT * NT, alone = M + 250.0, lds = 32.0 * MT, wstream = 80.0 * NT;
+  const double M = 16.0 * MT * NT, alone = (M + 250.0) / c.KG, lds = 32.0 * MT, wstream = 80.0 * NT;
   auto T = [&](int64_t w) {
     return w == 0 ? 0.0 : fmax(fmax(fmax((double)w * M, alone), (double)w * lds), (double)w * wstream);
   };
@@ -290,7 +335,7 @@ double step_cycles(int MT, int NT, int64_t blocks) {
   return (double)(n / occ) * T(occ) + T(n % occ);
 }
 
-bool pick(const ConvParams& p, int& MT, int& NT) {
+bool pick(const ConvParams& p, CpTile& best_tile) {
   if (tuning().no_conv_pipe) return false;                // tuning: fall through to gemm_mfma
   if (p.depthwise || p.Cin % 64 != 0 || !p.w_packed || p.k < 2) return false;
   if (p.Cout < 64) return false;
@@ -299,27 +344,30 @@ bool pick(const ConvParams& p, int& MT, int& NT) {
   if ((int64_t)p.k * ((p.Cout + 15) / 16) * (p.Cin / 64) * 1024 > 0x7fffffffLL) return false;
   // frames per tile: 96 or 64 (128 would need all 256 registers and leave one wave per SIMD:
   // measured slower than 96 with two); channels per tile: 256 or 128
-  const int force_mt = tuning().cp_mt, force_nt = tuning().cp_nt;   // tuning
-  static const int MTs[] = {8, 7, 6, 5, 4}, NTs[] = {4, 2};
+  const int force_mt = tuning().cp_mt, force_nt = tuning().cp_nt, force_kg = tuning().cp_kg;   // tuning
+  static const CpTile tiles[] = {{8, 4, 1}, {7, 4, 1}, {6, 4, 1}, {5, 4, 1}, {4, 4, 1}, {8, 2, 1}, {7, 2, 1}, {6, 2, 1},
+                                 {5, 2, 1}, {4, 2, 1}, {6, 4, 2}, {4, 4, 2}, {6, 2, 2}, {4, 2, 2}, {4, 2, 4}};
+  const int steps = p.Cin / 64 * p.k;
   double best = 1e300;
   bool found = false;
-  for (int nt : NTs)
-    for (int mt : MTs) {
-      if ((force_mt && mt != force_mt) || (force_nt && nt != force_nt)) continue;
-      const int TM = 16 * mt;
-      const int rows = lds_rows(p, TM);
-      if (rows > kMaxRows || (int64_t)p.Cin * (p.Tin + p.xpad) > 0x7fffffffLL) continue;
-      const int64_t n_tt = (p.Tout + TM - 1) / TM, n_co = (p.Cout + 64 * nt - 1) / (64 * nt);
-      const int64_t blocks = (int64_t)p.B * n_tt * n_co;
-      if (blocks > 0x7ffffff0LL) continue;
-      // halo read and transposed per tile, relative to the products
-      const double cost = step_cycles(mt, nt, blocks) * (1.0 + 0.25 / mt);
-      if (cost < best * 0.999) { best = cost; MT = mt; NT = nt; found = true; }
-    }
+  for (const CpTile& c : tiles) {
+    if ((force_mt && c.MT != force_mt) || (force_nt && c.NT != force_nt) || (force_mt && c.KG != (force_kg ? force_kg : 1))) continue;
+    if (c.KG > p.k || lds_bytes(p, c) > 160 * 1024) continue;
+    const int TM = 16 * c.MT;
+    const int rows = lds_rows(p, TM);
+    if (rows > kMaxRows || (int64_t)p.Cin * (p.Tin + p.xpad) > 0x7fffffffLL) continue;
+    const int64_t n_tt = (p.Tout + TM - 1) / TM, n_co = (p.Cout + 64 * c.NT - 1) / (64 * c.NT);
+    const int64_t blocks = (int64_t)p.B * n_tt * n_co;
+    if (blocks > 0x7ffffff0LL) continue;
+    // halo read and transposed per tile, relative to the products; uneven tap splits; the final sums
+    const double uneven = c.KG > 1 ? (double)((p.k + c.KG - 1) / c.KG * c.KG) / p.k : 1.0;
+    const double cost = steps * step_cycles(c, blocks) * (1.0 + 0.25 / c.MT) * uneven + (c.KG > 1 ? 2000.0 : 0.0);
+    if (cost < best * 0.999) { best = cost; best_tile = c; found = true; }
+  }
   return found;
 }
 
-template <int MT, int NT>
+template <int MT, int NT, int KG>
 hipError_t launch_t(const ConvParams& p, hipStream_t st) {
   constexpr int TM = 16 * MT, TN = 64 * NT;
   CpGeom g;
@@ -331,32 +379,32 @@ hipError_t launch_t(const ConvParams& p, hipStream_t st) {
   const int64_t blocks = (int64_t)p.B * g.n_tt * g.n_co;
   g.tiles = (int)blocks;
   g.per_xcd = tuning().cp_plain_order ? 0 : (int)((blocks + 7) / 8);
-  return launch_kernel(conv_pipe_kernel<MT, NT>, dim3((unsigned)(g.per_xcd ? 8 * g.per_xcd : (int)blocks)), dim3(256),
-                       (size_t)2 * g.rows * kXS, st, p, g);
+  const size_t lds = lds_bytes(p, CpTile{MT, NT, KG});
+  if constexpr (KG > 1) {
+    static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
+    if (const hipError_t e = ensure_max_dynamic_lds((const void*)conv_pipe_kernel<MT, NT, KG>, lds_raised); e != hipSuccess)
+      return e;
+  }
+  return launch_kernel(conv_pipe_kernel<MT, NT, KG>, dim3((unsigned)(g.per_xcd ? 8 * g.per_xcd : (int)blocks)), dim3(256 * KG),
+                       lds, st, p, g);
 }
 
 }  // namespace
 
 bool conv_pipe_supported(const ConvParams& p) {
-  int MT, NT;
-  return pick(p, MT, NT);
+  CpTile c;
+  return pick(p, c);
 }
 
 hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st) {
-  int MT, NT;
-  if (!pick(p, MT, NT)) return hipErrorInvalidValue;
-  switch (10 * MT + NT) {
-    case 84: return launch_t<8, 4>(p, st);
-    case 74: return launch_t<7, 4>(p, st);
-    case 64: return launch_t<6, 4>(p, st);
-    case 54: return launch_t<5, 4>(p, st);
-    case 44: return launch_t<4, 4>(p, st);
-    case 82: return launch_t<8, 2>(p, st);
-    case 72: return launch_t<7, 2>(p, st);
-    case 62: return launch_t<6, 2>(p, st);
-    case 52: return launch_t<5, 2>(p, st);
-    default: return launch_t<4, 2>(p, st);
-  }
+  CpTile c;
+  if (!pick(p, c)) return hipErrorInvalidValue;
+#define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KG == K) return launch_t<M, N, K>(p, st);
+  QASR_CASE(8, 4, 1) QASR_CASE(7, 4, 1) QASR_CASE(6, 4, 1) QASR_CASE(5, 4, 1) QASR_CASE(4, 4, 1)
+  QASR_CASE(8, 2, 1) QASR_CASE(7, 2, 1) QASR_CASE(6, 2, 1) QASR_CASE(5, 2, 1) QASR_CASE(4, 2, 1)
+  QASR_CASE(6, 4, 2) QASR_CASE(4, 4, 2) QASR_CASE(6, 2, 2) QASR_CASE(4, 2, 2) QASR_CASE(4, 2, 4)
+#undef QASR_CASE
+  return hipErrorInvalidValue;
 }
 
 }  // namespace qasr

@@ -32,8 +32,8 @@ Tuning read_env() {
   }
   if (const char* e = getenv("QASR_DW_R")) t.dw_r = atoi(e);
   if (const char* e = getenv("QASR_CP_TILE")) {
-    int mt = 0, nt = 0;
-    if (sscanf(e, "%d,%d", &mt, &nt) >= 1) { t.cp_mt = mt; t.cp_nt = nt; }
+    int mt = 0, nt = 0, kg = 0;
+    if (sscanf(e, "%d,%d,%d", &mt, &nt, &kg) >= 1) { t.cp_mt = mt; t.cp_nt = nt; t.cp_kg = kg; }
   }
   t.no_sep = getenv("QASR_NO_SEP") != nullptr;
   if (const char* e = getenv("QASR_SEP")) {

@@ -1,0 +1,36 @@
+"""Dense layers whose taps are split over groups of waves (csrc/conv_pipe.hip, KG > 1): uneven tap splits,
+as many groups as taps, one chunk and several, ragged frames and channels, strides, several residual
+operands, the choice the library makes by itself for small launches."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import gpu_layer
+from test_gpu_parity import draw, layer_case, run_layer_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    dict(name="k4_one_chunk", B=1, Cin=64, Cout=128, T=100, k=4, packed=True),
+    dict(name="k5_ragged", B=2, Cin=192, Cout=200, T=131, k=5, packed=True, res=True, relu=False),
+    dict(name="k11_wide", B=1, Cin=256, Cout=384, T=203, k=11, packed=True),
+    dict(name="k13_s2", B=2, Cin=128, Cout=256, T=333, k=13, stride=2, pad=(6, 6), packed=True, bias=False),
+    dict(name="k29_d2", B=1, Cin=320, Cout=72, T=97, k=29, dil=2, packed=True, s_lo=20, s_hi=40),
+]
+
+
+@pytest.mark.parametrize("tile", ["4,2,2", "4,2,4", "6,2,2", "4,4,2", "6,4,2"])
+@pytest.mark.parametrize("kw", SHAPES, ids=[c["name"] for c in SHAPES])
+def test_forced_groups(kw, tile, tuning_env):
+    tuning_env("QASR_CP_TILE", tile)
+    assert run_layer_case(layer_case(**kw)) == "conv_pipe"
+
+
+@pytest.mark.parametrize("n_res", [0, 1, 5])
+def test_small_launch_with_residuals(n_res):
+    op, p, x, _, packed = layer_case("small", 2, 640, 640, 203, k=21, packed=True)
+    rs = [draw(77 + r, (2, op.Cout, op.Tout), -128, 127, np.int8) for r in range(n_res)]
+    print(f"[case] dense 640 -> 640 k=21 with {n_res} residuals", flush=True)
+    ref = oracle.run_op(op, p, x, rs if n_res > 1 else (rs[0] if rs else None))
+    got = gpu_layer(op, 2, p, x, rs if n_res > 1 else (rs[0] if rs else None), packed=packed)
+    assert np.array_equal(got, ref)
