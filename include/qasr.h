@@ -351,7 +351,9 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
 
 /* Number of ops, and the name of the kernel family op i is dispatched to (depthwise:
  * "dw_pipe", "dw_mfma"; pointwise: "pw_pipe", "pw_tile"; dense and any other pointwise shape:
- * "conv_pipe", "gemm_mfma"; any shape: "conv_generic"; static storage, NULL if i is out of range). */
+ * "conv_pipe", "gemm_mfma"; any shape: "conv_generic"; static storage, NULL if i is out of range).
+ * Families launch forms of their own: packed pointwise layers of the pw_pipe, pw_tile and gemm_mfma families' shapes may run
+ * as pw_wide, a depthwise + pointwise pair as one kernel. */
 int32_t qasr_encoder_num_ops(const qasr_encoder* e);
 const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i);
 /* 1 if op i's activation (qasr_op.act) is applied inside the layer's own kernel (a unary

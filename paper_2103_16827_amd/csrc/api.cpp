@@ -73,7 +73,7 @@ ConvParams make_params(const qasr_conv1d_desc* d, const int8_t* x, const int8_t*
   return p;
 }
 
-enum class Kernel { Generic, DwMfma, DwPipe, GemmMfma, PwTile, PwPipe, ConvPipe };
+enum class Kernel { Generic, DwMfma, DwPipe, GemmMfma, PwTile, PwPipe, PwWide, ConvPipe };
 
 Kernel pick_kernel(const ConvParams& p) {
   if (p.n_res_more > 0)      // dense-residual layers: the two kernels whose epilogue adds several operands
@@ -84,21 +84,23 @@ Kernel pick_kernel(const ConvParams& p) {
   }
   if (qasr::pw_pipe_supported(p)) return Kernel::PwPipe;
   if (qasr::pw_tile_supported(p)) return Kernel::PwTile;
+  if (qasr::pw_wide_supported(p)) return Kernel::PwWide;
   if (qasr::conv_pipe_supported(p)) return Kernel::ConvPipe;
   if (qasr::gemm_mfma_supported(p)) return Kernel::GemmMfma;
   return Kernel::Generic;
 }
 
 // kernels whose epilogue applies a unary activation's table (ConvParams::act_lut)
-bool applies_act_table(Kernel k) { return k == Kernel::PwPipe || k == Kernel::DwPipe; }
+bool applies_act_table(Kernel k) { return k == Kernel::PwPipe || k == Kernel::PwWide || k == Kernel::DwPipe; }
 
 const char* kernel_name(Kernel k) {
   switch (k) {
     case Kernel::DwMfma: return "dw_mfma";
     case Kernel::DwPipe: return "dw_pipe";
-    case Kernel::GemmMfma: return "gemm_mfma";
     case Kernel::PwTile: return "pw_tile";
     case Kernel::PwPipe: return "pw_pipe";
+    case Kernel::PwWide:      // (launches the packed pointwise layers of that family)
+    case Kernel::GemmMfma: return "gemm_mfma";
     case Kernel::ConvPipe: return "conv_pipe";
     default: return "conv_generic";
   }
@@ -110,8 +112,10 @@ qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
     case Kernel::DwMfma: e = qasr::launch_dw_mfma(p, st); break;
     case Kernel::DwPipe: e = qasr::launch_dw_pipe(p, st); break;
     case Kernel::GemmMfma: e = qasr::launch_gemm_mfma(p, st); break;
-    case Kernel::PwTile: e = qasr::launch_pw_tile(p, st); break;
-    case Kernel::PwPipe: e = qasr::launch_pw_pipe(p, st); break;
+    // (the two families of the benchmark's widths hand launches of some sizes to pw_wide)
+    case Kernel::PwTile: e = qasr::pw_wide_better(p, false) ? qasr::launch_pw_wide(p, st) : qasr::launch_pw_tile(p, st); break;
+    case Kernel::PwPipe: e = qasr::pw_wide_better(p, true) ? qasr::launch_pw_wide(p, st) : qasr::launch_pw_pipe(p, st); break;
+    case Kernel::PwWide: e = qasr::launch_pw_wide(p, st); break;
     case Kernel::ConvPipe: e = qasr::launch_conv_pipe(p, st); break;
     default: e = qasr::launch_conv_generic(p, st); break;
   }
@@ -151,10 +155,6 @@ struct qasr_encoder {
   int64_t in_rows = 0, out_rows = 0;    // rows (batch items x channels) of the network input and output
   int32_t in_T = 0, out_T = 0;          // and their lengths
   bool pitched = false;                 // the slots' rows have a pitch of their own (see rows_of)
-  // int8 forwards of a pitched encoder: the input / output goes through a pitched copy in the
-  // workspace (the pipelined pointwise kernels take aligned rows only)
-  bool copy_in = false, copy_out = false;
-  size_t copy_in_off = 0, copy_out_off = 0;
   int8_t* packed = nullptr;       // device: packed weights of all groups == 1 layers
   // Runs of consecutive ops that one launch of the persistent team kernel executes (team.hip); the
   // ops outside them are launched one by one.
@@ -637,7 +637,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
   size_t packed_bytes = 0;
   // rows with a pitch of their own: wanted when some length is not a multiple of 16, and possible
   // unless a residual operand would then have another pitch than the output it is added to
-  bool ragged = false, pitchable = true, copy_in = false;
+  bool ragged = false, pitchable = true;
   for (int32_t i = 0; i < n_ops; ++i) {
     const qasr_op& o = ops[i];
     const qasr_status st = check_desc(&o.d);
@@ -688,7 +688,6 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       for (int32_t q = 0; q < o.n_more_res; ++q) pitchable = pitchable && o.more_res_slots[q] != 0;
     }
     if (o.d.Tin < 4 || Tout < 4) pitchable = false;
-    if (o.in_slot == 0 && row_pad(o.d.Tin) && o.d.k == 1 && has_packed_form(&o.d)) copy_in = true;
     slot[o.out_slot].live = true;
     slot[o.out_slot].C = o.d.Cout;
     slot[o.out_slot].T = Tout;
@@ -736,17 +735,6 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
     const qasr_conv1d_desc& ld = ops[n_ops - 1].d;
     e->out_rows = (int64_t)ld.B * ld.Cout;
     e->out_T = (int32_t)out_len64(&ld);
-    // (a layer of less than one 256-channel pass is as fast on gemm_mfma, which stores rows of any length)
-    e->copy_out = e->pitched && row_pad(e->out_T) && ld.k == 1 && has_packed_form(&ld) && ld.Cout >= 256;
-  }
-  e->copy_in = e->pitched && copy_in;
-  if (e->copy_in) {
-    e->copy_in_off = off;
-    off += round256((size_t)e->in_rows * (e->in_T + row_pad(e->in_T)));
-  }
-  if (e->copy_out) {
-    e->copy_out_off = off;
-    off += round256((size_t)e->out_rows * (e->out_T + row_pad(e->out_T)));
   }
   e->ws_bytes = off;
 
@@ -782,7 +770,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
     op.in_channels = (int32_t)(op.p.xbs / op.p.Tin);
     {
       ConvParams rp = op.p;               // (the pointers are unknown yet: the choice for aligned ones)
-      rows_of(e, i, e->copy_in ? row_pad(e->in_T) : 0, e->copy_out ? row_pad(e->out_T) : 0, rp);
+      rows_of(e, i, 0, 0, rp);
       op.kernel = pick_kernel(rp);
     }
     if (o.act) {
@@ -894,21 +882,7 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     return QASR_ERR_WORKSPACE;
   int8_t* ws = (int8_t*)workspace;
   const size_t n = e->ops.size();
-  if (e->copy_in && xpad == 0) {
-    xpad = row_pad(e->in_T);
-    int8_t* const xc = ws + e->copy_in_off;
-    const hipError_t ce = qasr::launch_repitch(x, e->in_rows, e->in_T, e->in_T, xc, e->in_T + xpad, st);
-    if (ce != hipSuccess) return hip_status(ce);
-    x = xc;
-  }
-  int8_t* const y_user = y;
   const bool fuse = team && !ev;                // (timed and layer-by-layer forwards launch every layer by itself)
-  // (a fused pair stores rows of any length by itself)
-  const bool copy_y = e->copy_out && ypad == 0 && !(fuse && n > 1 && e->ops[n - 2].sep);
-  if (copy_y) {
-    ypad = row_pad(e->out_T);
-    y = ws + e->copy_out_off;
-  }
   // (the team kernel's loads want 16-byte aligned tensors, like the kernels it replaces)
   const bool use_team = team && !ev && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);
   // layer i's parameters with this call's tensors
@@ -958,10 +932,6 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
       const hipError_t ae = qasr::launch_act(op.act, p.y, p.y, p.B, n_out, p.ybs, p.ybs, st);
       if (ae != hipSuccess) return hip_status(ae);
     }
-  }
-  if (copy_y) {
-    const hipError_t ce = qasr::launch_repitch(y, e->out_rows, e->out_T, e->out_T + ypad, y_user, e->out_T, st);
-    if (ce != hipSuccess) return hip_status(ce);
   }
   if (ev) { const hipError_t re = hipEventRecord(ev[n], st); if (re != hipSuccess) return hip_status(re); }
   return QASR_OK;

@@ -41,6 +41,13 @@ hipError_t launch_pw_tile(const ConvParams& p, hipStream_t st);
 bool pw_pipe_supported(const ConvParams& p);
 hipError_t launch_pw_pipe(const ConvParams& p, hipStream_t st);
 
+// Pointwise convolution (k = 1), 16 waves per workgroup, the whole tile in flight at once; packed weights,
+// Cin a multiple of 64 up to 2048, rows of any length.  pw_wide_better: whether it is the faster choice for
+// a layer that pw_pipe (pipe) or pw_tile takes.
+bool pw_wide_supported(const ConvParams& p);
+bool pw_wide_better(const ConvParams& p, bool pipe);
+hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st);
+
 // Dense convolution (k >= 2) as an implicit GEMM pipelined over (chunk, tap) steps; needs packed
 // weights, Cin % 64 == 0, Cout >= 64.
 bool conv_pipe_supported(const ConvParams& p);
@@ -58,11 +65,9 @@ hipError_t launch_probe_mfma(int iters, int32_t* out, hipStream_t st);
 hipError_t launch_quantize(const float* x, size_t n, float alpha, float S, int8_t* q, hipStream_t st);
 hipError_t launch_dequantize(const int8_t* q, size_t n, float S, float* x, hipStream_t st);
 // The same between dense float rows of T frames and int8 rows of `pitch` >= T bytes (a multiple of 4,
-// 4-byte aligned), and the plain copy between int8 rows of two pitches (one of them a multiple of 4 and
-// >= T rounded up to 4; T >= 4).
+// 4-byte aligned).
 hipError_t launch_quantize_rows(const float* x, int64_t rows, int T, float alpha, float S, int8_t* q, int pitch, hipStream_t st);
 hipError_t launch_dequantize_rows(const int8_t* q, int64_t rows, int T, int pitch, float S, float* x, hipStream_t st);
-hipError_t launch_repitch(const int8_t* x, int64_t rows, int T, int xpitch, int8_t* y, int ypitch, hipStream_t st);
 
 // Integer-only activations (Sec. 2.2: second-order polynomial exponential).  kind 1 sigmoid,
 // 2 swish, 3 GLU; u refines an int8 code to scale S / 2^u; q_ln2, q_b, q_c are the host-side

@@ -87,16 +87,6 @@ __global__ __launch_bounds__(256) void dequantize_rows_kernel(const int8_t* __re
   }
 }
 
-__global__ __launch_bounds__(256) void repitch_kernel(const int8_t* __restrict__ x, RowQuads g, int T, int xpitch,
-                                                      int8_t* __restrict__ y, int ypitch) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += stride) {
-    const int64_t row = i / g.per_row;
-    const int t = 4 * (int)(i - row * g.per_row);
-    store_row_u32(y + row * ypitch, t, ypitch, load_row_u32(x + row * xpitch, t, T));
-  }
-}
-
 unsigned grid_for(size_t n) {
   const size_t quads = (n + 3) / 4;
   const size_t blocks = (quads + 255) / 256;
@@ -124,12 +114,6 @@ hipError_t launch_quantize_rows(const float* x, int64_t rows, int T, float alpha
 hipError_t launch_dequantize_rows(const int8_t* q, int64_t rows, int T, int pitch, float S, float* x, hipStream_t st) {
   const RowQuads g{rows * ((T + 3) / 4), (T + 3) / 4};
   return launch_kernel(dequantize_rows_kernel, dim3(grid_for(4 * (size_t)g.n)), dim3(256), 0, st, q, g, T, pitch, S, x);
-}
-
-hipError_t launch_repitch(const int8_t* x, int64_t rows, int T, int xpitch, int8_t* y, int ypitch, hipStream_t st) {
-  if (T < 4) return hipErrorInvalidValue;
-  const RowQuads g{rows * ((T + 3) / 4), (T + 3) / 4};
-  return launch_kernel(repitch_kernel, dim3(grid_for(4 * (size_t)g.n)), dim3(256), 0, st, x, g, T, xpitch, y, ypitch);
 }
 
 }  // namespace qasr

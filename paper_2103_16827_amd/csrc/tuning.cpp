@@ -36,6 +36,12 @@ Tuning read_env() {
     if (sscanf(e, "%d,%d,%d", &mt, &nt, &kg) >= 1) { t.cp_mt = mt; t.cp_nt = nt; t.cp_kg = kg; }
   }
   t.no_sep = getenv("QASR_NO_SEP") != nullptr;
+  t.no_pw_wide = getenv("QASR_NO_PW_WIDE") != nullptr;
+  t.pw_wide_force = getenv("QASR_PW_WIDE") != nullptr;
+  if (const char* e = getenv("QASR_PWW")) {
+    int mt = 0, ks = 0;
+    if (sscanf(e, "%d,%d", &mt, &ks) >= 1) { t.pww_mt = mt; t.pww_ks = ks; }
+  }
   if (const char* e = getenv("QASR_SEP")) {
     int mt = 0, nt = 0;
     if (sscanf(e, "%d,%d", &mt, &nt) >= 1) { t.sep_mt = mt; t.sep_nt = nt; }

@@ -14,6 +14,8 @@
 //   QASR_NO_PW_LEAN                         pw_pipe: never the lean form (one pass per workgroup, two workgroups per unit)
 //   QASR_SLOT_DEPTH                         encoder: an op's output avoids the buffers the last N ops touched
 //                                           (default 4; 0 = the caller's slots are the buffers)
+//   QASR_NO_PW_WIDE, QASR_PW_WIDE            pw_wide: never / wherever it can
+//   QASR_PWW = "MT,KS"                      pw_wide: groups per tile, wave groups over the input channels (0: free)
 //   QASR_NO_SEP                             encoder: no depthwise + pointwise pair in one launch
 //   QASR_SEP = "MT,NT"                      the same: groups per tile, 16-channel columns per wave (0: free)
 //   QASR_TEAM                               encoder: plan runs of layers for the persistent team kernel
@@ -23,13 +25,13 @@
 namespace qasr {
 
 struct Tuning {
-  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false, no_sep = false;
+  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false, no_sep = false, no_pw_wide = false, pw_wide_force = false;
   int pwp_mt = 0, pwp_split = 0;
   int dwp_r = 0, dwp_s = 0;
   int dw_r = 0;
   int cp_mt = 0, cp_nt = 0, cp_kg = 0;
   int pwt_mt = 0;
-  int sep_mt = 0, sep_nt = 0;
+  int sep_mt = 0, sep_nt = 0, pww_mt = 0, pww_ks = 0;
   int slot_depth = 4;
 };
 
