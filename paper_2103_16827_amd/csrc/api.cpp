@@ -1097,7 +1097,15 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
 
 struct qasr_encoder_graph {
   hipGraphExec_t exec = nullptr;
+  // Launching a graph costs the host 16 us however small it is, a kernel by itself 3 us: forwards of up to
+  // kDirectKernels kernels are enqueued one by one (exec stays null), which also runs them sooner.
+  const qasr_encoder* e = nullptr;
+  const int8_t* x = nullptr;
+  int8_t* y = nullptr;
+  void* workspace = nullptr;
+  size_t workspace_bytes = 0;
 };
+static constexpr size_t kDirectKernels = 4;
 
 qasr_status qasr_encoder_graph_create(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,
                                       size_t workspace_bytes, qasr_encoder_graph** out) {
@@ -1120,19 +1128,27 @@ qasr_status qasr_encoder_graph_create(const qasr_encoder* e, const int8_t* x, in
       if (st == QASR_OK && (ee != hipSuccess || !graph)) st = QASR_ERR_HIP;
     }
   }
-  if (st == QASR_OK && hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) st = QASR_ERR_HIP;
+  size_t nodes = 0;
+  if (st == QASR_OK && hipGraphGetNodes(graph, nullptr, &nodes) != hipSuccess) st = QASR_ERR_HIP;
+  const bool direct = nodes <= kDirectKernels;
+  if (st == QASR_OK && !direct && hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) st = QASR_ERR_HIP;
   if (graph) (void)hipGraphDestroy(graph);
   (void)hipStreamDestroy(cap);
   if (st != QASR_OK) return st;
   qasr_encoder_graph* g = new (std::nothrow) qasr_encoder_graph();
-  if (!g) { (void)hipGraphExecDestroy(exec); return QASR_ERR_HIP; }
+  if (!g) {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    return QASR_ERR_HIP;
+  }
   g->exec = exec;
+  g->e = e; g->x = x; g->y = y; g->workspace = workspace; g->workspace_bytes = workspace_bytes;
   *out = g;
   return QASR_OK;
 }
 
 qasr_status qasr_encoder_graph_launch(qasr_encoder_graph* g, void* stream) {
-  if (!g || !g->exec) return QASR_ERR_NULL;
+  if (!g) return QASR_ERR_NULL;
+  if (!g->exec) return forward_impl(g->e, g->x, g->y, g->workspace, g->workspace_bytes, (hipStream_t)stream, nullptr);
   const hipError_t e = hipGraphLaunch(g->exec, (hipStream_t)stream);
   return e == hipSuccess ? QASR_OK : hip_status(e);
 }
