@@ -54,6 +54,15 @@ struct DwpGeom {
   int c_per_xcd;  // channels per XCD: ceil(C / 8)
 };
 
+// the short-form rescale of four accumulators, clamped to int8 (see requant_short4; off the GPU by the plain form)
+__device__ __forceinline__ uint32_t short4(const int32_t (&a)[4], int32_t m, int32_t sh, int32_t rnd) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return requant_short4<false, false>(a, m, sh, rnd, 0u);
+#else
+  return requant_pack4<true, false>(a, m, sh, rnd, 0u, -128, 127);
+#endif
+}
+
 // ACT: a unary activation's table is applied after the clamp (its own instantiation: the plain
 // layers keep their code as it is)
 template <int KC, int R, int NI, bool ACT>
@@ -195,7 +204,7 @@ __global__ __launch_bounds__(256) void dw_pipe_kernel(ConvParams p, DwpGeom g) {
   // issued, then the operands of pair q + 1 are read from LDS, then pair q - 1 is rescaled and
   // stored, so that LDS and matrix-pipeline latencies pass under the vector arithmetic.
   auto iteration = [&](int it, int buf, auto fast_tag, auto np_tag) __attribute__((always_inline)) {
-    constexpr bool FAST = decltype(fast_tag)::value;
+    constexpr int FORM = decltype(fast_tag)::value;   // 0: 64-bit rescale, 1: short form with relu, 2: short form
     constexpr int NP = decltype(np_tag)::value;
     const int row = s_begin + it * R;
     const unsigned char* const rows_lds = my + buf * R * rowbytes;
@@ -233,7 +242,9 @@ __global__ __launch_bounds__(256) void dw_pipe_kernel(ConvParams p, DwpGeom g) {
       for (int e = 0; e < 2; ++e) {
         const v4i av = acc[q & 1][e];
         const int32_t a4[4] = {av[0], av[1], av[2], av[3]};
-        uint32_t pk = requant_pack4<FAST, false>(a4, mc, sh, rnd, 0u, lo, hi127);
+        uint32_t pk;
+        if constexpr (FORM == 2) pk = short4(a4, mc, sh, rnd);
+        else pk = requant_pack4<FORM == 1, false>(a4, mc, sh, rnd, 0u, lo, hi127);
         if (has_act) {                               // table[code + 128], byte by byte
           const uint32_t cd = pk ^ 0x80808080u;
           pk = (uint32_t)lutw[cd & 0xffu] | ((uint32_t)lutw[(cd >> 8) & 0xffu] << 8) |
@@ -264,7 +275,9 @@ __global__ __launch_bounds__(256) void dw_pipe_kernel(ConvParams p, DwpGeom g) {
     }
   };
   auto run_np = [&](auto np_tag) __attribute__((always_inline)) {
-    if (fast) run(std::true_type{}, np_tag); else run(std::false_type{}, np_tag);
+    if (!fast) run(std::integral_constant<int, 0>{}, np_tag);
+    else if (p.relu) run(std::integral_constant<int, 1>{}, np_tag);
+    else run(std::integral_constant<int, 2>{}, np_tag);
   };
   switch (pairs) {
     case 1: run_np(std::integral_constant<int, 1>{}); break;

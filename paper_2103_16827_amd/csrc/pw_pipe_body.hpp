@@ -33,6 +33,18 @@ struct PwpGeom {
   int nopipe;        // tuning: every pass does its epilogue right after its own products
 };
 
+// the short-form epilogue of four accumulators (33 <= s <= 54, sh = s - 32; see requant_short4; off the
+// GPU, where the instructions do not exist, by the plain form)
+constexpr int kShortS0 = 33, kShortS1 = 54;
+template <bool RES, bool RELU>
+__device__ __forceinline__ uint32_t short4(const int32_t (&a)[4], int32_t m, int32_t sh, int32_t rnd, uint32_t resw) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return requant_short4<RES, RELU>(a, m, sh, rnd, resw);
+#else
+  return requant_pack4<true, RES>(a, m, sh, rnd, resw, RELU ? 0 : -128, 127);
+#endif
+}
+
 __device__ __forceinline__ v2i lds_read_tr8(const unsigned char* p) {
   return __builtin_amdgcn_ds_read_tr8_b64_v2i32(
       (v2i __attribute__((address_space(3)))*)(const_cast<unsigned char*>(p)));
@@ -206,14 +218,16 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
   int32_t mc[NT], sh[NT], rnd[NT];                // rescale constants of the pass whose epilogue is pending
 
   // one epilogue block: lane (n, gi) holds frames 16 mt + 4 gi + (0..3) of channel 16 nt + n
-  auto block = [&](int par, int e, auto fast_tag, auto res_tag) __attribute__((always_inline)) {
-    constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value;
+  auto block = [&](int par, int e, auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
+    constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
     const int mt = e / NT, nt = e % NT;
     uint32_t* const sp = reinterpret_cast<uint32_t*>(stage0 + (LEAN ? 0 : par * (ROWS * 128) + nt * 2048) + (sbase ^ (uint32_t)(mt << 4)));
     const uint32_t rw = !RES ? 0u : LEAN ? *reinterpret_cast<const uint32_t*>(lres0 + nt * 2048 + (sbase ^ (uint32_t)(mt << 4))) : *sp;
     const v4i av = acc[par][mt][nt];
     const int32_t a4[4] = {av[0], av[1], av[2], av[3]};
-    uint32_t pk = requant_pack4<FAST, RES>(a4, mc[nt], sh[nt], rnd[nt], rw, lo, hi127);
+    uint32_t pk;
+    if constexpr (FAST) pk = short4<RES, RELU>(a4, mc[nt], sh[nt], rnd[nt], rw);
+    else pk = requant_pack4<false, RES>(a4, mc[nt], sh[nt], rnd[nt], rw, lo, hi127);
     if (has_act) {                                 // table[code + 128], byte by byte
       const uint32_t c = pk ^ 0x80808080u;
       pk = (uint32_t)lutw[c & 0xffu] | ((uint32_t)lutw[(c >> 8) & 0xffu] << 8) |
@@ -291,46 +305,40 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
     }
   };
   constexpr int STORE_REQS = 2 * NT;              // requests of one store_rows
-  // the epilogue of pass ps on its own
-  auto epilogue_alone = [&](int ps, int par, auto fast_tag) __attribute__((always_inline)) {
+  // the epilogue of pass ps on its own (a relu instantiation for the short form only)
+  auto epilogue_of = [&](int ps, int par, auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     if constexpr (LEAN) {
-      if (has_res) wait_vm_dyn(seq - mark_r[0]);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        if (has_res) {
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            block(par, mt * NT + nt, fast_tag, std::true_type{});
-            if (mt & 1) __builtin_amdgcn_sched_barrier(0);
-          }
-        } else {
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            block(par, mt * NT + nt, fast_tag, std::false_type{});
-            if (mt & 1) __builtin_amdgcn_sched_barrier(0);
-          }
+        for (int mt = 0; mt < MT; ++mt) {
+          block(par, mt * NT + nt, fast_tag, res_tag, relu_tag);
+          if (mt & 1) __builtin_amdgcn_sched_barrier(0);      // bounds the live temporaries
         }
         store_rows_lean(ps, nt);
-      }
-      seq += STORE_REQS;
-      return;
-    }
-    if (has_res) wait_vm_dyn(seq - mark_r[par]);          // residual rows of this pass
-    if (has_res) {
-#pragma unroll
-      for (int e = 0; e < NB; ++e) {
-        block(par, e, fast_tag, std::true_type{});
-        if (e & 1) __builtin_amdgcn_sched_barrier(0);       // bounds the live temporaries
       }
     } else {
 #pragma unroll
       for (int e = 0; e < NB; ++e) {
-        block(par, e, fast_tag, std::false_type{});
+        block(par, e, fast_tag, res_tag, relu_tag);
         if (e & 1) __builtin_amdgcn_sched_barrier(0);
       }
+      store_rows(ps, par);
     }
-    store_rows(ps, par);
     seq += STORE_REQS;
+  };
+  auto epilogue_alone = [&](int ps, int par, auto fast_tag) __attribute__((always_inline)) {
+    constexpr bool FAST = decltype(fast_tag)::value;
+    const std::true_type T{};
+    const std::false_type F{};
+    if (has_res) {
+      wait_vm_dyn(seq - mark_r[LEAN ? 0 : par]);            // residual rows of this pass
+      if (FAST && p.relu) epilogue_of(ps, par, fast_tag, T, T);
+      else epilogue_of(ps, par, fast_tag, T, F);
+    } else {
+      if (FAST && p.relu) epilogue_of(ps, par, fast_tag, F, T);
+      else epilogue_of(ps, par, fast_tag, F, F);
+    }
   };
 
   bool pending = false;       // the pass before awaits its (short-form) epilogue
@@ -439,7 +447,7 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
     for (int nt = 0; nt < NT; ++nt) {
       mc[nt] = *reinterpret_cast<const int32_t*>(c + nt * 192 + 64);
       s_[nt] = *reinterpret_cast<const int32_t*>(c + nt * 192 + 128);
-      fast = fast && s_[nt] >= 33;
+      fast = fast && s_[nt] >= kShortS0 && s_[nt] <= kShortS1;
     }
     const bool all_fast = __builtin_amdgcn_readfirstlane((int)__all(fast)) != 0;   // wave-uniform, and known to be
 #pragma unroll
