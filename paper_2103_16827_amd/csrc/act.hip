@@ -17,7 +17,9 @@
 // tensor through it, 16 bytes per lane and access.  The pass is memory-bound (2 bytes per element,
 // 3 for GLU); the table costs each workgroup a few hundred cycles once.
 //
-// Softmax: one wave per row up to 512 logits (no barrier, the row in registers), one workgroup per
+// Softmax of rows of up to 4096 logits whose exponentials stay below 2^24 and their sum below 2^31
+// (every scale of about 2^-11 and coarser): softmax_small_kernel below, 32-bit throughout.  Otherwise:
+// one wave per row up to 512 logits (no barrier, the row in registers), one workgroup per
 // row beyond: extremes of the row, exponentials (kept in registers for rows up
 // to 2048 logits, recomputed beyond) and their 64-bit sum, quotients.  The two divisions per
 // element are 32-bit whenever the row's spread allows it (the choice is made per row and is
@@ -313,6 +315,132 @@ __global__ __launch_bounds__(256) void softmax_wave_kernel(ActParams c, const in
   }
 }
 
+// Rows of up to 4096 logits, exponentials below 2^24, sums below 2^31 (launch_softmax checks).  The
+// kernel is bound by its 5 bytes per logit; what it must not do is add instructions to them:
+//   * G lanes own a row, C chunks of 4 consecutive logits each (16-byte loads, 4-byte stores at any
+//     alignment), so short rows share a wave and the extremes need log2 G lane exchanges of 32 bits;
+//   * z = floor(-r / q_ln2) without a correction: -r is clamped to 31 q_ln2 (E < 2^24 is 0 from there
+//     on, and below 2^20 with q_ln2 < 2^15), half a unit is added, and the quotient is then at least
+//     0.5 / q_ln2 > 2^-16 away from any whole number while single precision is within 2^-17;
+//   * floor(E 2^7 / sum) is one multiply-high by a reciprocal of the sum, made once per row: with
+//     2^(l-1) < sum <= 2^l and M = floor(2^(31+l) / sum) + 1, M sum = 2^(31+l) + e, 0 < e <= sum, so
+//     E M / 2^(24+l) exceeds E 2^7 / sum by less than E / 2^24 / sum < 1 / sum: same floor.  (The
+//     2^-10 added below covers the rounding of the double quotient; E < 2^24 - 2^15 pays for it.)
+//     The shift that is left saturates at 127 and packs in the same instruction.
+// About 13 instructions per logit.  51200 x 400 logits: 43.2 us with 64-bit exponentials and sums and
+// a corrected quotient each, 24.0 us so (19.3 at the rate of a large copy).
+struct SoftmaxSmall {
+  const int32_t* x;
+  int8_t* y;
+  int64_t rows;
+  int32_t L, ql, qb, qc, pow_u;                      // pow_u = 2^u <= q_ln2
+  uint32_t cap;                                      // ceil(31 q_ln2 / 2^u)
+  float k1, k2;                                      // 2^u / q_ln2, 0.5 / q_ln2
+};
+
+typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4), may_alias));
+
+// maximum / sum over the G lanes of a group, in every lane of it
+template <int G, bool MAX>
+__device__ __forceinline__ int32_t group_reduce(int32_t v) {
+  auto op = [](int32_t a, int32_t b) { return MAX ? max(a, b) : a + b; };
+  if constexpr (G >= 2) v = op(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true));    // lane ^ 1
+  if constexpr (G >= 4) v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true));    // lane ^ 2
+  if constexpr (G >= 8) v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true));   // mirrored in 8 lanes
+  if constexpr (G >= 16) v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true));  // mirrored in 16
+  if constexpr (G >= 32) {
+    const auto w = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = op((int32_t)w[0], (int32_t)w[1]);
+  }
+  if constexpr (G >= 64) {
+    const auto w = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = op((int32_t)w[0], (int32_t)w[1]);
+  }
+  return v;
+}
+
+template <int G, int C>
+__global__ __launch_bounds__(256) void softmax_small_kernel(SoftmaxSmall p) {
+  __shared__ int32_t sh[8];
+  const int g = (int)threadIdx.x % G, wave = (int)threadIdx.x >> 6;
+  const int64_t row = (int64_t)blockIdx.x * (256 / G) + (int)threadIdx.x / G;
+  if (G <= 64 && row >= p.rows) return;              // (whole groups; G = 256: a row per workgroup, all there)
+  const int32_t* const xr = p.x + row * p.L;
+  int32_t v[C][4];
+  int nv[C];                                         // logits in the chunk: >= 4, or the row ends inside it or before
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int j = 4 * (g + G * c);
+    nv[c] = p.L - j;
+    if (nv[c] >= 4) {
+      const v4i_a4 w = *reinterpret_cast<const v4i_a4*>(xr + j);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[c][i] = w[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[c][i] = i < nv[c] ? xr[j + i] : INT32_MIN;
+    }
+  }
+  int32_t mx = INT32_MIN;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mx = max(mx, v[c][i]);
+  mx = group_reduce<(G < 64 ? G : 64), true>(mx);
+  if constexpr (G > 64) {
+    if ((threadIdx.x & 63) == 0) sh[wave] = mx;
+    __syncthreads();
+    mx = max(max(sh[0], sh[1]), max(sh[2], sh[3]));
+  }
+  int32_t sum = 0;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t d = min((uint32_t)mx - (uint32_t)v[c][i], p.cap);
+      const int32_t z = (int32_t)fmaf((float)d, p.k1, p.k2);
+      const int32_t t = __mul24(z, p.ql) + (p.qb - __mul24((int32_t)d, p.pow_u));   // p + q_b
+      v[c][i] = (int32_t)((uint32_t)(__mul24(t, t) + p.qc) >> z);
+      sum += v[c][i];
+    }
+  if ((uint32_t)mx - (uint32_t)INT32_MIN < p.cap) {  // logits near the bottom of the range: what stands for the missing ones counts
+    sum = 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum += i < nv[c] ? v[c][i] : 0;
+  }
+  sum = group_reduce<(G < 64 ? G : 64), false>(sum);
+  if constexpr (G > 64) {
+    if ((threadIdx.x & 63) == 0) sh[4 + wave] = sum;
+    __syncthreads();
+    sum = sh[4] + sh[5] + sh[6] + sh[7];
+  }
+  const int l = 32 - __clz(sum - 1);                 // 8 .. 31
+  const uint32_t M = (uint32_t)(__builtin_ldexp(1.0 / (double)sum, 31 + l) + 0x1p-10) + 1u;
+  int8_t* const yr = p.y + row * p.L;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    int32_t h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h[i] = (int32_t)__umulhi((uint32_t)v[c][i], M);
+    const uint32_t pk = join16(__builtin_amdgcn_ashr_pk_i8_i32(h[0], h[1], l - 8), __builtin_amdgcn_ashr_pk_i8_i32(h[2], h[3], l - 8));
+    int8_t* const yc = yr + 4 * (g + G * c);
+    if (nv[c] >= 4) store_u32(yc, pk);
+    else {
+      if (nv[c] > 0) yc[0] = (int8_t)pk;
+      if (nv[c] > 1) yc[1] = (int8_t)(pk >> 8);
+      if (nv[c] > 2) yc[2] = (int8_t)(pk >> 16);
+    }
+  }
+}
+
+template <int G, int C>
+hipError_t launch_softmax_small(const SoftmaxSmall& p, hipStream_t st) {
+  const int64_t wgs = (p.rows + 256 / G - 1) / (256 / G);
+  return launch_kernel(softmax_small_kernel<G, C>, dim3((unsigned)wgs), dim3(256), 0, st, p);
+}
+
 }  // namespace
 
 hipError_t launch_act_table(const ActParams& c, uint8_t* table, hipStream_t st) {
@@ -336,6 +464,28 @@ hipError_t launch_act(const ActParams& c, const int8_t* x, int8_t* y, int32_t B,
 }
 
 hipError_t launch_softmax(const ActParams& c, const int32_t* x, int64_t rows, int32_t L, int8_t* y, hipStream_t st) {
+  // p + q_b lies in (q_b - q_ln2, q_b]
+  const int64_t t = c.q_b > c.q_ln2 - 1 - c.q_b ? c.q_b : c.q_ln2 - 1 - c.q_b, Emax = t * t + c.q_c, E0 = c.q_b * c.q_b + c.q_c;
+  if (L <= 4096 && rows <= (1ll << 30) && c.q_ln2 < (1 << 15) && (1ll << c.u) <= c.q_ln2 && Emax < (1 << 24) - (1 << 15) && E0 >= 256 &&
+      L * Emax < (1ll << 31)) {
+    SoftmaxSmall p;
+    p.x = x; p.y = y; p.rows = rows; p.L = L;
+    p.ql = (int32_t)c.q_ln2; p.qb = (int32_t)c.q_b; p.qc = (int32_t)c.q_c; p.pow_u = 1 << c.u;
+    p.cap = (uint32_t)((31 * c.q_ln2 + p.pow_u - 1) >> c.u);
+    p.k1 = (float)((double)p.pow_u / (double)c.q_ln2);
+    p.k2 = (float)(0.5 / (double)c.q_ln2);
+    // two loads in flight per lane, one where the launch would not give every SIMD two waves with two
+    const bool few = rows * ((L + 7) / 8) < 64 * 2048;
+    if (L <= 16) return launch_softmax_small<4, 1>(p, st);
+    if (L <= 32) return few ? launch_softmax_small<8, 1>(p, st) : launch_softmax_small<4, 2>(p, st);
+    if (L <= 64) return few ? launch_softmax_small<16, 1>(p, st) : launch_softmax_small<8, 2>(p, st);
+    if (L <= 128) return few ? launch_softmax_small<32, 1>(p, st) : launch_softmax_small<16, 2>(p, st);
+    if (L <= 256) return few ? launch_softmax_small<64, 1>(p, st) : launch_softmax_small<32, 2>(p, st);
+    if (L <= 512) return few ? launch_softmax_small<256, 1>(p, st) : launch_softmax_small<64, 2>(p, st);
+    if (L <= 1024) return few ? launch_softmax_small<256, 1>(p, st) : launch_softmax_small<64, 4>(p, st);
+    if (L <= 2048) return launch_softmax_small<256, 2>(p, st);
+    return launch_softmax_small<256, 4>(p, st);
+  }
   if (L <= 512) {
     const int64_t wgs = (rows + 3) / 4;
     return launch_kernel(softmax_wave_kernel, dim3((unsigned)(wgs < 2048 ? wgs : 2048)), dim3(256), 0, st, c, x, rows, L, y);
