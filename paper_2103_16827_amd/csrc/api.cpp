@@ -6,6 +6,7 @@
 #include "team.hpp"
 #include "tuning.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <new>
@@ -151,7 +152,8 @@ struct qasr_encoder {
   };
   std::vector<Op> ops;
   std::vector<size_t> slot_off;   // byte offset of slot i in the workspace (slot 0 unused)
-  size_t ws_bytes = 0;
+  size_t ws_bytes = 0;            // activation buffers, then (from split_off on) what split contractions need
+  size_t split_off = 0;
   int64_t in_rows = 0, out_rows = 0;    // rows (batch items x channels) of the network input and output
   int32_t in_T = 0, out_T = 0;          // and their lengths
   bool pitched = false;                 // the slots' rows have a pitch of their own (see rows_of)
@@ -736,6 +738,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
     e->out_rows = (int64_t)ld.B * ld.Cout;
     e->out_T = (int32_t)out_len64(&ld);
   }
+  e->split_off = off;
   e->ws_bytes = off;
 
   // ---- one-time device work: pack the dense k>1 weights
@@ -743,7 +746,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
     const hipError_t me = hipMalloc((void**)&e->packed, packed_bytes);
     if (me != hipSuccess) { delete e; return hip_status(me); }
   }
-  size_t poff = 0;
+  size_t poff = 0, split_bytes = 0;
   e->ops.resize(n_ops);
   std::vector<uint8_t*> act_table(n_ops, nullptr);
   for (int32_t i = 0; i < n_ops; ++i) {
@@ -772,6 +775,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       ConvParams rp = op.p;               // (the pointers are unknown yet: the choice for aligned ones)
       rows_of(e, i, 0, 0, rp);
       op.kernel = pick_kernel(rp);
+      if (op.kernel == Kernel::ConvPipe) split_bytes = std::max(split_bytes, qasr::conv_pipe_split_bytes(rp));
     }
     if (o.act) {
       op.has_act = true;
@@ -794,6 +798,8 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       }
     }
   }
+  if (split_bytes && e->split_off) e->ws_bytes =   // (an encoder that needs no workspace goes on needing none)
+      e->split_off + round256(split_bytes) + round256(4 * qasr::kConvSplitCounters);
   // ---- depthwise + pointwise pairs that run as one launch
   if (!e->pitched && qasr::tuning().team) {
     // (the experimental team kernel takes such layers one by one)
@@ -876,20 +882,32 @@ int32_t qasr_encoder_op_in_team(const qasr_encoder* e, int32_t i) {
 // xpad, ypad: frames between the rows of x and y (pitched encoders only; 0 = the caller's dense tensors)
 static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,
                                 size_t workspace_bytes, hipStream_t st, hipEvent_t* ev, int team = 1,
-                                int32_t xpad = 0, int32_t ypad = 0) {
+                                int32_t xpad = 0, int32_t ypad = 0, bool split = true) {
   if (!e || !x || !y) return QASR_ERR_NULL;
-  if (e->ws_bytes && (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < e->ws_bytes))
+  if (e->ws_bytes && (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < (split ? e->ws_bytes : e->split_off)))
     return QASR_ERR_WORKSPACE;
   int8_t* ws = (int8_t*)workspace;
   const size_t n = e->ops.size();
   const bool fuse = team && !ev;                // (timed and layer-by-layer forwards launch every layer by itself)
   // (the team kernel's loads want 16-byte aligned tensors, like the kernels it replaces)
   const bool use_team = team && !ev && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);
+  // room for the partial sums of split contractions, and their counters (zero between layers from here on)
+  split = split && e->ws_bytes > e->split_off;
+  const size_t split_bytes = split ? e->ws_bytes - e->split_off - round256(4 * qasr::kConvSplitCounters) : 0;
+  if (split) {
+    const hipError_t ce = qasr::launch_conv_split_clear((unsigned*)(ws + e->split_off + split_bytes), st);
+    if (ce != hipSuccess) return hip_status(ce);
+  }
   // layer i's parameters with this call's tensors
   auto bind = [&](size_t i, ConvParams& p) {
     const qasr_encoder::Op& op = e->ops[i];
     p = op.p;
     rows_of(e, i, xpad, ypad, p);
+    if (split) {
+      p.part = (int32_t*)(ws + e->split_off);
+      p.part_bytes = split_bytes;
+      p.part_count = (unsigned*)(ws + e->split_off + split_bytes);
+    }
     p.x = op.in_slot == 0 ? x : ws + e->slot_off[op.in_slot];
     p.res = op.res_slot < 0 ? nullptr : (op.res_slot == 0 ? x : ws + e->slot_off[op.res_slot]);
     p.y = (i + 1 == n) ? y : ws + e->slot_off[op.out_slot];
@@ -978,13 +996,14 @@ size_t qasr_static_workspace_bytes(void) { return QASR_STATIC_WORKSPACE_BYTES; }
 
 qasr_status qasr_encoder_forward_static(const qasr_encoder* e, const int8_t* x, int8_t* y, void* stream) {
   if (!e || !x || !y) return QASR_ERR_NULL;
-  if (e->ws_bytes > QASR_STATIC_WORKSPACE_BYTES) return QASR_ERR_WORKSPACE;     // before any HIP call
+  if (e->split_off > QASR_STATIC_WORKSPACE_BYTES) return QASR_ERR_WORKSPACE;    // before any HIP call
   void* ws = nullptr;
   const qasr_status st = static_scratch(&ws);
   if (st != QASR_OK) return st;
   // every slot is written in full by the op that produces it before any op reads it: nothing in the
   // array has to start at zero, whatever an earlier call left there
-  return forward_impl(e, x, y, ws, QASR_STATIC_WORKSPACE_BYTES, (hipStream_t)stream, nullptr);
+  return forward_impl(e, x, y, ws, QASR_STATIC_WORKSPACE_BYTES, (hipStream_t)stream, nullptr, 1, 0, 0,
+                      e->ws_bytes <= QASR_STATIC_WORKSPACE_BYTES);
 }
 
 qasr_status qasr_encoder_forward_layerwise(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,

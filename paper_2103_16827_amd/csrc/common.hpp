@@ -36,6 +36,11 @@ struct ConvParams {
   // reads across frames (k > 1) zeroes what it loads of them, and any kernel may overwrite them.  The
   // kernels without taps that know no pitch (pw_pipe, pw_tile) are given the pitch as the length.
   int32_t xpad, ypad;
+  // dense layers with taps: room for partial sums (conv_pipe_split_bytes) and kConvSplitCounters zeros, in
+  // the encoder's workspace; null = a tile's contraction stays in one workgroup
+  int32_t* part;
+  int64_t part_bytes;
+  unsigned* part_count;
 };
 constexpr int kMaxMoreRes = 11;
 

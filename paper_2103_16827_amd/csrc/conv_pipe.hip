@@ -34,6 +34,10 @@ namespace qasr {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+constexpr int kPastCaches = 17;   // sc0 sc1: stores written through to memory, loads from there
+constexpr int kMaxSplits = 8;
 
 constexpr int kXS = 80;       // LDS row pitch in bytes: 64 channels + 16 pad
 constexpr int kMaxRows = 256; // one 4-frame x 16-channel unit per thread and chunk
@@ -43,7 +47,8 @@ struct CpGeom {
   int rows;           // LDS rows (input frames incl. halo, rounded to 4)
   int kchunks;        // Cin / 64
   int co16n;          // ceil(Cout / 16)
-  int tiles;          // B * n_tt * n_co
+  int splits;         // workgroups per tile, each with a range of the chunks
+  int tiles;          // B * n_tt * n_co * splits
   int per_xcd;        // ceil(tiles / 8): tiles of one XCD (the grid is 8 * per_xcd workgroups)
 };
 
@@ -71,8 +76,11 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   // (per_xcd == 0, a tuning override: the plain order, tile = workgroup index, for comparisons)
   const int v = g.per_xcd ? (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
   if (v >= g.tiles) return;                         // whole workgroup, before any barrier
-  const int bt = v % (g.tiles / g.n_co);            // (b, t_tile) of the tile
-  const int co_tile = v / (g.tiles / g.n_co);
+  const int nbt = p.B * g.n_tt;
+  const int cs = v / nbt, bt = v - cs * nbt;        // bt: (b, t_tile) of the tile
+  const int co_tile = cs / g.splits, split = cs - co_tile * g.splits;
+  const int c0 = split * g.kchunks / g.splits;      // this workgroup's chunks
+  const int nkc = (split + 1) * g.kchunks / g.splits - c0;
   const int t_tile = bt % g.n_tt;
   const int b = bt / g.n_tt;
 
@@ -83,7 +91,7 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   const int co_w = co_tile * TN + wave * 16 * NT;   // first output channel of this wave
   const int bufbytes = g.rows * kXS;
 
-  const int8_t* xb = p.x + (int64_t)b * p.xbs;
+  const int8_t* xb = p.x + (int64_t)b * p.xbs + (int64_t)(64 * c0) * (p.Tin + p.xpad);
 
   // ---- activation chunk kc: global -> registers (issue), registers -> LDS transposed (commit).
   // A thread owns one unit of the chunk: frames 4 fq..+4 of the 16 channels that make one 16-byte
@@ -152,7 +160,7 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   };
 
   // ---- weights: step q = (chunk, tap) of the flat contraction, ring of three steps
-  const int Q = g.kchunks * (j1 - j0);
+  const int Q = nkc * (j1 - j0);
   int wkc = 0, wj = j0;                             // chunk and tap of the next step to request
   // (the packed buffer is below 2 GiB: a wave-uniform base per step plus a 32-bit lane offset)
   uint32_t woff[NT];
@@ -160,11 +168,11 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   for (int nt = 0; nt < NT; ++nt)
     woff[nt] = (uint32_t)((min((co_w >> 4) + nt, g.co16n - 1) * g.kchunks * 64 + lane) * 16);
   auto load_w = [&](v4i (&dst)[NT]) __attribute__((always_inline)) {
-    const int8_t* wbase = p.w + (int64_t)(wj * g.co16n * g.kchunks + wkc) * 1024;
+    const int8_t* wbase = p.w + (int64_t)(wj * g.co16n * g.kchunks + c0 + wkc) * 1024;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) dst[nt] = *reinterpret_cast<const v4i*>(wbase + woff[nt]);
     if (++wj == j1) {                               // (the stream stays on its last step at the end)
-      if (wkc + 1 < g.kchunks) { wj = j0; ++wkc; } else { --wj; }
+      if (wkc + 1 < nkc) { wj = j0; ++wkc; } else { --wj; }
     }
   };
 
@@ -175,18 +183,23 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   v4i acc[MT][NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    const int32_t bv = p.bias && kg == 0 ? p.bias[co_ld[nt]] : 0;
+    const int32_t bv = p.bias && kg == 0 && split == 0 ? p.bias[co_ld[nt]] : 0;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = (v4i){bv, bv, bv, bv};
   }
 
   // ---- prologue: chunk 0 into buffer 0, weights of steps 0 and 1
   v4i wb[3][NT];
-  // (the groups take turns at bringing in a chunk: chunk kc is group kc mod KG's)
-  if (kg == 0) issue_chunk(0);
+  // (the groups take turns at bringing in a chunk: chunk kc is group kc mod KG's, which with several groups
+  // asks for its next one as soon as it has put one into LDS: with few taps per group a chunk lasts less
+  // than the memory latency)
+  if (kg < nkc) issue_chunk(kg);
   load_w(wb[0]);
   load_w(wb[1]);
-  if (kg == 0) commit_chunk(0);
+  if (kg == 0) {
+    commit_chunk(0);
+    if (KG < nkc) issue_chunk(KG);
+  }
   __syncthreads();
 
   // The A operands (one 16-byte LDS read per 16 frames) go through a ring of three registers,
@@ -201,7 +214,6 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   };
   const int jmid = j0 + ((j1 - j0) >> 1);           // the tap at which the next chunk is committed
   int kc = 0, j = j0;                               // chunk and tap of the current step
-  if (g.kchunks > 1 && kg == 1 % KG) issue_chunk(1);
   v4i ar[3];
   ar[0] = read_a(arow_of(0, j0), 0);
   ar[1] = read_a(arow_of(0, j0), 1);
@@ -223,13 +235,16 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
           for (int nt = 0; nt < NT; ++nt)
             acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[(u * MT + mt) % 3], wb[u][nt], acc[mt][nt], 0, 0, 0);
         }
-        if (j == jmid && kc + 1 < g.kchunks && kg == (kc + 1) % KG) commit_chunk((kc + 1) & 1);
+        if (j == jmid && kc + 1 < nkc && kg == (kc + 1) % KG) {
+          commit_chunk((kc + 1) & 1);
+          if (KG > 1 && kc + 1 + KG < nkc) issue_chunk(kc + 1 + KG);
+        }
         if (last_tap) {
           j = j0;
           ++kc;
           __syncthreads();                          // chunk kc is in LDS; chunk kc - 1 has been read by all
-          if (kc + 1 < g.kchunks && kg == (kc + 1) % KG) issue_chunk(kc + 1);
-          if (kc < g.kchunks) {
+          if (KG == 1 && kc + 1 < nkc) issue_chunk(kc + 1);
+          if (kc < nkc) {
             ar[((u + 1) * MT) % 3] = read_a(arow_of(kc, j0), 0);
             ar[((u + 1) * MT + 1) % 3] = read_a(arow_of(kc, j0), 1);
           }
@@ -267,6 +282,50 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
           for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += *slot(kg, src, mt, nt);
         }
       }
+  }
+
+  // ---- splits > 1 (a launch of few tiles would leave most compute units idle while each of its
+  // workgroups goes through the whole contraction: 768 channels, 25 taps, 2 x 200 frames 50 -> 20 us
+  // with four): the sums of this range go to memory, and the workgroup of the tile that comes last
+  // adds those of the others to its own and goes on.  Another compute die's writes do not appear in
+  // this one's L2 by themselves: the stores are written through (sc0 sc1) and complete before the
+  // arrival is counted, the loads are made after it and go past the caches.
+  if (g.splits > 1) {
+    auto part_of = [&](int s_) __attribute__((always_inline)) {
+      return __builtin_amdgcn_make_buffer_rsrc(p.part + ((int64_t)(co_tile * nbt + bt) * g.splits + s_) * (MT * NT * 1024), 0,
+                                               MT * NT * 4096, 0x00027000);
+    };
+    const uint32_t poff = (uint32_t)(wave * 64 + lane) * 16;
+    auto owned = [&](int mt) { return KG == 1 || mt * KG / MT == kg; };
+    const __amdgpu_buffer_rsrc_t mine = part_of(split);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (owned(mt)) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, acc[mt][nt]), mine, poff, (mt * NT + nt) * 4096, kPastCaches);
+      }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                // (the LDS buffers have been read by all, too)
+    if (threadIdx.x == 0) {
+      const unsigned before = __hip_atomic_fetch_add(p.part_count + co_tile * nbt + bt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *reinterpret_cast<volatile unsigned*>(xs) = before;
+    }
+    __syncthreads();
+    if (*reinterpret_cast<volatile unsigned*>(xs) + 1 != (unsigned)g.splits) return;   // whole workgroup
+    if (threadIdx.x == 0)                           // (for the next layer)
+      __hip_atomic_store(p.part_count + co_tile * nbt + bt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+    for (int o = 1; o < g.splits; ++o) {
+      const __amdgpu_buffer_rsrc_t from = part_of(split + o < g.splits ? split + o : split + o - g.splits);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        if (owned(mt)) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            acc[mt][nt] += __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(from, poff, (mt * NT + nt) * 4096, kPastCaches));
+        }
+    }
   }
 
   // ---- epilogue: lane (n, gi) holds frames t0 + 16 mt + 4 gi + (0..3) of channel co_w + 16 nt + n
@@ -309,7 +368,9 @@ int lds_rows(const ConvParams& p, int TM) {
   return (((TM - 1) * p.stride + p.dil * (p.k - 1) + 1 + 3) + 3) & ~3;
 }
 
-struct CpTile { int MT, NT, KG; };
+struct CpTile { int MT, NT, KG, S; };
+
+constexpr int64_t kMaxSplitTiles = kConvSplitCounters;   // (one arrival counter each)
 
 size_t lds_bytes(const ConvParams& p, const CpTile& c) {
   const size_t x = (size_t)2 * lds_rows(p, 16 * c.MT) * kXS;
@@ -317,17 +378,17 @@ size_t lds_bytes(const ConvParams& p, const CpTile& c) {
 }
 
 // Cycles per (chunk, tap) step on the busiest compute unit, from a small model: a unit holds `occ`
-// workgroups, KG waves each per SIMD; a SIMD with w workgroups spends w M cycles in the matrix
-// pipe per step (M = 16 MT NT), a lone wave cannot go below M plus its own latencies (operand reads,
-// weight request, loop) for each of its group's steps, and the operand reads of all waves share the
-// unit's LDS port.
+// workgroups, KG waves each per SIMD; a SIMD with w workgroups spends w M cycles per step in the
+// matrix pipe (M = 24 MT NT with everything that does not overlap), a lone wave cannot go below M plus
+// its own latencies (operand reads, weight request, loop) for each of its group's steps, and the
+// operand reads and the NT KiB of weights that every wave streams per step share the unit's ports.
+// The constants (and those of the split in pick) are fitted to the times of every tile, group and split
+// count for 256 .. 768 channels, 11 .. 25 taps and 50 .. 12800 frames with weights that are in no
+// cache: the choices are within 0.7 % of the best one on average, 9 % at worst.
 double step_cycles(const CpTile& c, int64_t blocks) {
   const int MT = c.MT, NT = c.NT;
   const int occ = c.KG == 4 ? 1 : c.KG == 2 ? (MT * NT <= 8 ? 2 : 1) : NT == 4 ? 2 : MT > 4 ? 3 : 4;   // bound by registers
-  // (a fourth bound: every wave streams its own NT KiB of weights per step out of L2; fitted, with
-  // the lone wave's latency, to per-layer times of the Jasper shape under every forced tile: only
-  // the widest layer, 768 -> 896 with k = 29, changes its tile, 250 -> 221 us)
-  const double M = 16.0 * MT * NT, alone = (M + 250.0) / c.KG, lds = 32.0 * MT, wstream = 80.0 * NT;
+  const double M = 24.0 * MT * NT, alone = (M + 400.0) / c.KG, lds = 10.0 * MT, wstream = 100.0 * NT;
   auto T = [&](int64_t w) {
     return w == 0 ? 0.0 : fmax(fmax(fmax((double)w * M, alone), (double)w * lds), (double)w * wstream);
   };
@@ -335,7 +396,7 @@ double step_cycles(const CpTile& c, int64_t blocks) {
   return (double)(n / occ) * T(occ) + T(n % occ);
 }
 
-bool pick(const ConvParams& p, CpTile& best_tile) {
+bool pick(const ConvParams& p, bool split, CpTile& best_tile) {
   if (tuning().no_conv_pipe) return false;                // tuning: fall through to gemm_mfma
   if (p.depthwise || p.Cin % 64 != 0 || !p.w_packed || p.k < 2) return false;
   if (p.Cout < 64) return false;
@@ -345,9 +406,9 @@ bool pick(const ConvParams& p, CpTile& best_tile) {
   // frames per tile: 96 or 64 (128 would need all 256 registers and leave one wave per SIMD:
   // measured slower than 96 with two); channels per tile: 256 or 128
   const int force_mt = tuning().cp_mt, force_nt = tuning().cp_nt, force_kg = tuning().cp_kg;   // tuning
-  static const CpTile tiles[] = {{8, 4, 1}, {7, 4, 1}, {6, 4, 1}, {5, 4, 1}, {4, 4, 1}, {8, 2, 1}, {7, 2, 1}, {6, 2, 1},
-                                 {5, 2, 1}, {4, 2, 1}, {6, 4, 2}, {4, 4, 2}, {6, 2, 2}, {4, 2, 2}, {4, 2, 4}};
-  const int steps = p.Cin / 64 * p.k;
+  static const CpTile tiles[] = {{8, 4, 1, 1}, {7, 4, 1, 1}, {6, 4, 1, 1}, {5, 4, 1, 1}, {4, 4, 1, 1}, {8, 2, 1, 1}, {7, 2, 1, 1}, {6, 2, 1, 1},
+                                 {5, 2, 1, 1}, {4, 2, 1, 1}, {6, 4, 2, 1}, {4, 4, 2, 1}, {6, 2, 2, 1}, {4, 2, 2, 1}, {4, 2, 4, 1}};
+  const int force_s = tuning().cp_s;
   double best = 1e300;
   bool found = false;
   for (const CpTile& c : tiles) {
@@ -359,16 +420,30 @@ bool pick(const ConvParams& p, CpTile& best_tile) {
     const int64_t n_tt = (p.Tout + TM - 1) / TM, n_co = (p.Cout + 64 * c.NT - 1) / (64 * c.NT);
     const int64_t blocks = (int64_t)p.B * n_tt * n_co;
     if (blocks > 0x7ffffff0LL) continue;
-    // halo read and transposed per tile, relative to the products; uneven tap splits; the final sums
+    // halo read and transposed per tile, relative to the products; uneven tap splits; the groups' final sums
     const double uneven = c.KG > 1 ? (double)((p.k + c.KG - 1) / c.KG * c.KG) / p.k : 1.0;
-    const double cost = steps * step_cycles(c, blocks) * (1.0 + 0.25 / c.MT) * uneven + (c.KG > 1 ? 2000.0 : 0.0);
-    if (cost < best * 0.999) { best = cost; best_tile = c; found = true; }
+    for (int S = 1; S <= (split && blocks <= kMaxSplitTiles ? kMaxSplits : 1) && S <= p.Cin / 64; ++S) {
+      if (force_s && split && S != force_s) continue;
+      // the longest range's steps; the other splits' sums read back by one unit, and all sums through memory
+      const int longest = (p.Cin / 64 + S - 1) / S * p.k;
+      const double cost = longest * step_cycles(c, blocks * S) * (1.0 + 0.3 / c.MT) * uneven + (c.KG > 1 ? 2100.0 : 0.0) +
+                          (S > 1 ? c.MT * c.NT * (120.0 * (S - 1) + 2.0 * (double)(blocks * S)) : 0.0);
+      if (cost < best * 0.999) { best = cost; best_tile = c; best_tile.S = S; found = true; }
+    }
   }
   return found;
 }
 
+size_t part_bytes(const ConvParams& p, const CpTile& c) {
+  if (c.S == 1) return 0;
+  const int64_t n_tt = (p.Tout + 16 * c.MT - 1) / (16 * c.MT), n_co = (p.Cout + 64 * c.NT - 1) / (64 * c.NT);
+  return (size_t)(p.B * n_tt * n_co) * c.S * (c.MT * c.NT * 4096);
+}
+
+__global__ __launch_bounds__(kConvSplitCounters) void conv_split_clear_kernel(unsigned* counters) { counters[threadIdx.x] = 0; }
+
 template <int MT, int NT, int KG>
-hipError_t launch_t(const ConvParams& p, hipStream_t st) {
+hipError_t launch_t(const ConvParams& p, int splits, hipStream_t st) {
   constexpr int TM = 16 * MT, TN = 64 * NT;
   CpGeom g;
   g.n_tt = (p.Tout + TM - 1) / TM;
@@ -376,10 +451,11 @@ hipError_t launch_t(const ConvParams& p, hipStream_t st) {
   g.rows = lds_rows(p, TM);
   g.kchunks = p.Cin / 64;
   g.co16n = (p.Cout + 15) / 16;
-  const int64_t blocks = (int64_t)p.B * g.n_tt * g.n_co;
+  g.splits = splits;
+  const int64_t blocks = (int64_t)p.B * g.n_tt * g.n_co * splits;
   g.tiles = (int)blocks;
   g.per_xcd = tuning().cp_plain_order ? 0 : (int)((blocks + 7) / 8);
-  const size_t lds = lds_bytes(p, CpTile{MT, NT, KG});
+  const size_t lds = lds_bytes(p, CpTile{MT, NT, KG, 1});
   if constexpr (KG > 1) {
     static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
     if (const hipError_t e = ensure_max_dynamic_lds((const void*)conv_pipe_kernel<MT, NT, KG>, lds_raised); e != hipSuccess)
@@ -393,13 +469,24 @@ hipError_t launch_t(const ConvParams& p, hipStream_t st) {
 
 bool conv_pipe_supported(const ConvParams& p) {
   CpTile c;
-  return pick(p, c);
+  return pick(p, false, c);
+}
+
+size_t conv_pipe_split_bytes(const ConvParams& p) {
+  CpTile c;
+  return pick(p, true, c) ? part_bytes(p, c) : 0;
+}
+
+hipError_t launch_conv_split_clear(unsigned* counters, hipStream_t st) {
+  return launch_kernel(conv_split_clear_kernel, dim3(1), dim3(kConvSplitCounters), 0, st, counters);
 }
 
 hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st) {
   CpTile c;
-  if (!pick(p, c)) return hipErrorInvalidValue;
-#define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KG == K) return launch_t<M, N, K>(p, st);
+  bool ok = pick(p, p.part != nullptr, c);
+  if (!ok || (int64_t)part_bytes(p, c) > p.part_bytes) ok = pick(p, false, c);   // (tuning changed since the room was made)
+  if (!ok) return hipErrorInvalidValue;
+#define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KG == K) return launch_t<M, N, K>(p, c.S, st);
   QASR_CASE(8, 4, 1) QASR_CASE(7, 4, 1) QASR_CASE(6, 4, 1) QASR_CASE(5, 4, 1) QASR_CASE(4, 4, 1)
   QASR_CASE(8, 2, 1) QASR_CASE(7, 2, 1) QASR_CASE(6, 2, 1) QASR_CASE(5, 2, 1) QASR_CASE(4, 2, 1)
   QASR_CASE(6, 4, 2) QASR_CASE(4, 4, 2) QASR_CASE(6, 2, 2) QASR_CASE(4, 2, 2) QASR_CASE(4, 2, 4)

@@ -51,6 +51,11 @@ hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st);
 // Dense convolution (k >= 2) as an implicit GEMM pipelined over (chunk, tap) steps; needs packed
 // weights, Cin % 64 == 0, Cout >= 64.
 bool conv_pipe_supported(const ConvParams& p);
+// Bytes of ConvParams::part with which the layer's launch would split its contraction over several
+// workgroups per tile, 0 if it would not; the counters beside it are zero before and after each launch.
+constexpr int kConvSplitCounters = 1024;
+size_t conv_pipe_split_bytes(const ConvParams& p);
+hipError_t launch_conv_split_clear(unsigned* counters, hipStream_t st);
 hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st);
 
 // Measured ceilings (probe.hip): a streaming copy of `bytes` (a multiple of 16) and a register-resident

@@ -32,8 +32,8 @@ Tuning read_env() {
   }
   if (const char* e = getenv("QASR_DW_R")) t.dw_r = atoi(e);
   if (const char* e = getenv("QASR_CP_TILE")) {
-    int mt = 0, nt = 0, kg = 0;
-    if (sscanf(e, "%d,%d,%d", &mt, &nt, &kg) >= 1) { t.cp_mt = mt; t.cp_nt = nt; t.cp_kg = kg; }
+    int mt = 0, nt = 0, kg = 0, s = 0;
+    if (sscanf(e, "%d,%d,%d,%d", &mt, &nt, &kg, &s) >= 1) { t.cp_mt = mt; t.cp_nt = nt; t.cp_kg = kg; t.cp_s = s; }
   }
   t.no_sep = getenv("QASR_NO_SEP") != nullptr;
   t.no_pw_wide = getenv("QASR_NO_PW_WIDE") != nullptr;

@@ -5,7 +5,7 @@
 //   QASR_PWP_MT, QASR_PWP_SPLIT             pw_pipe: groups per tile, workgroups per tile
 //   QASR_DWP = "R,S"                        dw_pipe: rows per iteration, batch splits
 //   QASR_DW_R                               dw_mfma: strips per wave
-//   QASR_CP_TILE = "MT,NT[,KG]"             conv_pipe: tile, wave groups the taps are split over
+//   QASR_CP_TILE = "MT,NT[,KG[,S]]"         conv_pipe: tile, wave groups the taps and workgroups the chunks are split over
 //   QASR_CP_PLAIN_ORDER                     conv_pipe: tile = workgroup index (no per-XCD runs of the channel-major order)
 //   QASR_PWT_MT                             pw_tile: groups per tile
 //   QASR_PWP_NOPIPE                         pw_pipe: no epilogue under the next pass's products
@@ -29,7 +29,7 @@ struct Tuning {
   int pwp_mt = 0, pwp_split = 0;
   int dwp_r = 0, dwp_s = 0;
   int dw_r = 0;
-  int cp_mt = 0, cp_nt = 0, cp_kg = 0;
+  int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0;
   int pwt_mt = 0;
   int sep_mt = 0, sep_nt = 0, pww_mt = 0, pww_ks = 0;
   int slot_depth = 4;

@@ -1,11 +1,16 @@
 """Dense layers whose taps are split over groups of waves (csrc/conv_pipe.hip, KG > 1): uneven tap splits,
 as many groups as taps, one chunk and several, ragged frames and channels, strides, several residual
-operands, the choice the library makes by itself for small launches."""
+operands, the choice the library makes by itself for small launches.  In an encoder the chunks are split
+over workgroups as well (S > 1): as many as chunks, uneven ranges, with and without groups, replays."""
+import functools
+
 import numpy as np
 import pytest
+import torch
 
 import oracle
-from gpu_util import gpu_layer
+import qasr_workloads as W
+from gpu_util import GpuNet, dev, gpu_layer
 from test_gpu_parity import draw, layer_case, run_layer_case
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +39,36 @@ def test_small_launch_with_residuals(n_res):
     ref = oracle.run_op(op, p, x, rs if n_res > 1 else (rs[0] if rs else None))
     got = gpu_layer(op, 2, p, x, rs if n_res > 1 else (rs[0] if rs else None), packed=packed)
     assert np.array_equal(got, ref)
+
+
+@functools.lru_cache(maxsize=None)
+def jasper_dr_case(B, T):
+    net = W.jasper(B, T, 3, widths=(320, 512), kernels=(11, 4), per_width=1, C_epi=200, k_epi=5, C_epi2=128, dense_residual=True)
+    params, x = W.draw_net_params(net, 9), W.draw_input(net, 9)
+    return net, params, x, oracle.encoder_forward(net, params, x)
+
+
+@pytest.mark.parametrize("tile", ["", "4,2,1,2", "4,2,1,5", "8,4,1,3", "7,2,1,8", "4,2,2,4", "6,4,2,2", "4,2,4,3"])
+@pytest.mark.parametrize("B,T", [(1, 50), (3, 203), (2, 512)])
+def test_split_contraction(B, T, tile, tuning_env):
+    if tile:
+        tuning_env("QASR_CP_TILE", tile)
+    print(f"[case] jasper_dr B={B} T={T} tile {tile}", flush=True)
+    net, params, x, ref = jasper_dr_case(B, T)
+    g = GpuNet(net, params)
+    assert "conv_pipe" in g.kernels()
+    for _ in range(3):                               # (each forward finds the counters the last one left)
+        assert np.array_equal(g.forward(dev(x)).cpu().numpy(), ref)
+    g.check_guards()
+    y = torch.zeros(ref.shape, dtype=torch.int8, device="cuda")
+    ws = torch.full((max(1, g.enc.workspace_bytes),), 77, dtype=torch.int8, device="cuda")
+    xd = dev(x)
+    graph = g.enc.graph(xd, y, ws)
+    for _ in range(3):
+        y.zero_()
+        graph.launch()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy(), ref)
+        g.forward(xd)
+    graph.close()
+    g.enc.close()
