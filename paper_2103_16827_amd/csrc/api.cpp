@@ -76,7 +76,8 @@ ConvParams make_params(const qasr_conv1d_desc* d, const int8_t* x, const int8_t*
 
 enum class Kernel { Generic, DwMfma, DwPipe, GemmMfma, PwTile, PwPipe, PwWide, ConvPipe };
 
-Kernel pick_kernel(const ConvParams& p) {
+// the family whose shapes a layer has
+Kernel family_of(const ConvParams& p) {
   if (p.n_res_more > 0)      // dense-residual layers: the two kernels whose epilogue adds several operands
     return (!p.depthwise && qasr::conv_pipe_supported(p)) ? Kernel::ConvPipe : Kernel::Generic;
   if (p.depthwise) {
@@ -89,6 +90,17 @@ Kernel pick_kernel(const ConvParams& p) {
   if (qasr::conv_pipe_supported(p)) return Kernel::ConvPipe;
   if (qasr::gemm_mfma_supported(p)) return Kernel::GemmMfma;
   return Kernel::Generic;
+}
+
+// The kernel that runs a layer.  The one place that decides it: the two families of the benchmark's widths
+// hand launches of some sizes to pw_wide.  It depends on lengths, row pitches and pointers (their alignment),
+// not on act_lut, so a layer may get another kernel in another call (a float forward gives the ends of an
+// encoder padded rows); whoever asks goes by the answer for the call at hand, also for the activation.
+Kernel pick_kernel(const ConvParams& p) {
+  const Kernel f = family_of(p);
+  if (f == Kernel::PwTile && qasr::pw_wide_better(p, false)) return Kernel::PwWide;
+  if (f == Kernel::PwPipe && qasr::pw_wide_better(p, true)) return Kernel::PwWide;
+  return f;
 }
 
 // kernels whose epilogue applies a unary activation's table (ConvParams::act_lut)
@@ -113,9 +125,8 @@ qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
     case Kernel::DwMfma: e = qasr::launch_dw_mfma(p, st); break;
     case Kernel::DwPipe: e = qasr::launch_dw_pipe(p, st); break;
     case Kernel::GemmMfma: e = qasr::launch_gemm_mfma(p, st); break;
-    // (the two families of the benchmark's widths hand launches of some sizes to pw_wide)
-    case Kernel::PwTile: e = qasr::pw_wide_better(p, false) ? qasr::launch_pw_wide(p, st) : qasr::launch_pw_tile(p, st); break;
-    case Kernel::PwPipe: e = qasr::pw_wide_better(p, true) ? qasr::launch_pw_wide(p, st) : qasr::launch_pw_pipe(p, st); break;
+    case Kernel::PwTile: e = qasr::launch_pw_tile(p, st); break;
+    case Kernel::PwPipe: e = qasr::launch_pw_pipe(p, st); break;
     case Kernel::PwWide: e = qasr::launch_pw_wide(p, st); break;
     case Kernel::ConvPipe: e = qasr::launch_conv_pipe(p, st); break;
     default: e = qasr::launch_conv_generic(p, st); break;
@@ -137,17 +148,17 @@ struct qasr_encoder {
     qasr_conv1d_desc d;
     ConvParams p;          // pointers to weights/constants filled in; x / res / y set per forward
     int32_t in_slot, res_slot, out_slot;
-    Kernel kernel;
+    Kernel family;         // for 16-byte aligned, dense input and output
     int32_t n_more_res = 0;
     int32_t more_res_slots[QASR_MAX_RESIDUALS - 1];
     bool has_act = false;
-    bool act_fused = false;   // the layer's own kernel applies it (p.act_lut)
+    bool act_fused = false;   // the layer's own kernel applies it (for 16-byte aligned, dense input and output)
     qasr::ActParams act;   // applied in place to the output when has_act
+    const uint8_t* act_table = nullptr;   // unary activations: one int8 output per int8 code (kernels with applies_act_table)
     // This depthwise op and the pointwise op after it may run as one launch (sep.hpp): nothing else reads
-    // what it writes.  Its weight image, and the table of the activation between the two (or null).
+    // what it writes.  Its weight image.
     bool sep = false;
     const uint32_t* sep_img = nullptr;
-    const uint8_t* sep_lut = nullptr;
     int32_t in_channels = 0;  // channels of the slot read (p.Cin, or more for a channel-prefix view)
   };
   std::vector<Op> ops;
@@ -309,7 +320,7 @@ int32_t qasr_conv1d_out_len(const qasr_conv1d_desc* d) {
 const char* qasr_conv1d_kernel_name(const qasr_conv1d_desc* d) {
   if (check_desc(d) != QASR_OK) return nullptr;
   const ConvParams p = make_params(d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-  return kernel_name(pick_kernel(p));
+  return kernel_name(family_of(p));
 }
 
 qasr_status qasr_conv1d_int8(const qasr_conv1d_desc* d, const int8_t* x, const int8_t* w,
@@ -748,7 +759,6 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
   }
   size_t poff = 0, split_bytes = 0;
   e->ops.resize(n_ops);
-  std::vector<uint8_t*> act_table(n_ops, nullptr);
   for (int32_t i = 0; i < n_ops; ++i) {
     const qasr_op& o = ops[i];
     qasr_encoder::Op& op = e->ops[i];
@@ -774,27 +784,26 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
     {
       ConvParams rp = op.p;               // (the pointers are unknown yet: the choice for aligned ones)
       rows_of(e, i, 0, 0, rp);
-      op.kernel = pick_kernel(rp);
-      if (op.kernel == Kernel::ConvPipe) split_bytes = std::max(split_bytes, qasr::conv_pipe_split_bytes(rp));
+      op.family = family_of(rp);
+      op.act_fused = o.act && o.act->kind != QASR_ACT_GLU && applies_act_table(pick_kernel(rp));
+      if (op.family == Kernel::ConvPipe) split_bytes = std::max(split_bytes, qasr::conv_pipe_split_bytes(rp));
     }
     if (o.act) {
       op.has_act = true;
       op.act = act_params(o.act->kind, o.act->m, o.act->s, o.act->e);
-      // A unary activation after a layer of the pipelined pointwise or depthwise kernel is applied in
-      // that kernel's epilogue through a 256-entry table (one int8 output per int8 code), built here
-      // once by the activation's own integer arithmetic; everything else keeps the separate pass.
+      // A unary activation's table (one int8 output per int8 code) is built here once by the activation's
+      // own integer arithmetic: the pipelined depthwise, the pipelined and the wide pointwise kernel and the
+      // depthwise + pointwise pairs apply it in their epilogue, after any other kernel the activation is a
+      // pass of its own.
       if (o.act->kind != QASR_ACT_GLU) {
-        uint8_t* table = act_table[i] = reinterpret_cast<uint8_t*>(e->packed + poff);
+        uint8_t* const table = reinterpret_cast<uint8_t*>(e->packed + poff);
         poff += 256;
-        if (applies_act_table(op.kernel)) {
-          const hipError_t te = qasr::launch_act_table(op.act, table, nullptr);
-          if (te != hipSuccess) {
-            qasr_encoder_destroy(e);
-            return hip_status(te);
-          }
-          op.p.act_lut = table;
-          op.act_fused = true;
+        const hipError_t te = qasr::launch_act_table(op.act, table, nullptr);
+        if (te != hipSuccess) {
+          qasr_encoder_destroy(e);
+          return hip_status(te);
         }
+        op.act_table = table;
       }
     }
   }
@@ -831,9 +840,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
       if (!op.sep) continue;
       uint32_t* const img = e->sep_images + img_off[i] / 4;
       op.sep_img = img;
-      op.sep_lut = act_table[i];
       he = qasr::launch_sep_image(op.p, img, nullptr);
-      if (he == hipSuccess && op.has_act && !op.act_fused) he = qasr::launch_act_table(op.act, act_table[i], nullptr);
     }
     if (he != hipSuccess) {
       qasr_encoder_destroy(e);
@@ -864,7 +871,7 @@ int32_t qasr_encoder_num_ops(const qasr_encoder* e) { return e ? (int32_t)e->ops
 
 const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i) {
   if (!e || i < 0 || i >= (int32_t)e->ops.size()) return nullptr;
-  return kernel_name(e->ops[i].kernel);
+  return kernel_name(e->ops[i].family);
 }
 
 int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i) {
@@ -929,22 +936,21 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     if (op.sep && fuse) {
       ConvParams q;
       bind(i + 1, q);
-      p.act_lut = op.sep_lut;
+      p.act_lut = op.act_table;                  // (of the activation between the two)
       if (qasr::sep_supported(p, q)) {
         const hipError_t se = qasr::launch_sep(p, op.sep_img, q, st);
         if (se != hipSuccess) return hip_status(se);
         ++i;
         continue;
       }
-      p.act_lut = op.p.act_lut;
     }
     if (ev) { const hipError_t re = hipEventRecord(ev[i], st); if (re != hipSuccess) return hip_status(re); }
-    // (the choice depends on the caller's pointers too: a fused activation's table is only read
-    // by the two pipelined kernels, any other choice is followed by the separate pass)
+    // (the kernel of this call decides who applies a unary activation: its epilogue, or a pass of its own)
     const Kernel kk = pick_kernel(p);
+    p.act_lut = applies_act_table(kk) ? op.act_table : nullptr;
     const qasr_status s = launch_with(kk, p, st);
     if (s != QASR_OK) return s;
-    if (op.has_act && !(op.act_fused && applies_act_table(kk))) {
+    if (op.has_act && !p.act_lut) {
       const bool glu = op.act.kind == QASR_ACT_GLU;
       const int64_t n_out = (int64_t)(glu ? p.Cout / 2 : p.Cout) * (p.Tout + p.ypad);
       const hipError_t ae = qasr::launch_act(op.act, p.y, p.y, p.B, n_out, p.ybs, p.ybs, st);

@@ -27,7 +27,8 @@ struct ConvParams {
   int32_t n_res_more;
   const int8_t* res_more[11];
   // unary activation fused into the epilogue: 256 bytes, entry (code + 128) = the activation's int8
-  // output for that int8 code (built once by act_table_kernel); null = none.  Only pw_pipe and dw_pipe read it.
+  // output for that int8 code (built once by act_table_kernel); null = none.  Read by pw_pipe, pw_wide, dw_pipe
+  // and sep; set only for a launch of one of them.
   const uint8_t* act_lut;
   // Row pitch: a row of x (one channel of one batch item) starts Tin + xpad bytes after the row before
   // it, a row of y and of the residuals Tout + ypad bytes.  0 at the C ABI; the encoder gives its

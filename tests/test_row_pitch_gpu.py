@@ -9,6 +9,7 @@ import torch
 import oracle
 import qasr_workloads as W
 from gpu_util import dev, GpuNet
+from qasr_workloads.nets import _Builder
 
 pytestmark = pytest.mark.gpu
 
@@ -50,4 +51,31 @@ def test_encoders_on_utterances_of_any_length(net, B, T):
     g.enc.forward_f32(torch.from_numpy(xf).cuda(), alpha, S, y, ws)
     torch.cuda.synchronize()
     assert np.array_equal(y.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    g.enc.close()
+
+
+@pytest.mark.parametrize("C", [384, 640])
+def test_activation_at_both_ends_of_a_float_forward(C):
+    """The first and the last layer are pointwise layers with a unary activation: the float entry runs them on
+    padded rows, the int8 entry on the caller's dense ones, which may be another kernel's.  Each applies the
+    activation once."""
+    print(f"[case] activations at both ends C={C}", flush=True)
+    b = _Builder("act_ends", 91, 2, C, 61)
+    b.op("first", 4 * C, relu=False, act=2)
+    b.op("mid", C, relu=False)
+    b.op("last", 4 * C, relu=False, act=1)
+    spec = b.done()
+    params = W.draw_net_params(spec, 6)
+    x = W.draw_input(spec, 6)
+    g = GpuNet(spec, params)
+    assert np.array_equal(g.forward(dev(x)).cpu().numpy(), oracle.encoder_forward(spec, params, x))
+    alpha, S = 3.0, 0.125
+    xf = (x.astype(np.float32) * np.float32(alpha / 127))
+    want = oracle.dequantize(oracle.encoder_forward(spec, params, oracle.quantize(xf, alpha)), S)
+    ws = torch.full((g.enc.workspace_bytes_f32,), 77, dtype=torch.int8, device="cuda")
+    y = torch.full(want.shape, 77.0, dtype=torch.float32, device="cuda")
+    g.enc.forward_f32(torch.from_numpy(xf).cuda(), alpha, S, y, ws)
+    torch.cuda.synchronize()
+    bad = np.argwhere(y.cpu().numpy() != want)
+    assert bad.size == 0, f"{len(bad)} of {want.size} differ, first at {bad[0]}"
     g.enc.close()
