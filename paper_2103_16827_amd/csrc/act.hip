@@ -26,6 +26,7 @@
 // wave-uniform): floor(-r / q_ln2) directly, and E 2^7 / sum through a 24-bit cut of both operands
 // whose quotient the exact 64-bit remainder corrects by at most one.
 #include "kernels.hpp"
+#include "launch_shape.hpp"
 
 namespace qasr {
 
@@ -363,8 +364,8 @@ template <int G, int C>
 __global__ __launch_bounds__(256) void softmax_small_kernel(SoftmaxSmall p) {
   __shared__ int32_t sh[8];
   const int g = (int)threadIdx.x % G, wave = (int)threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * (256 / G) + (int)threadIdx.x / G;
-  if (G <= 64 && row >= p.rows) return;              // (whole groups; G = 256: a row per workgroup, all there)
+  const int64_t row = (((int64_t)blockIdx.y << kGridShift) + blockIdx.x) * (256 / G) + (int)threadIdx.x / G;
+  if (row >= p.rows) return;                         // (whole groups; G = 256: the whole workgroup, before any barrier)
   const int32_t* const xr = p.x + row * p.L;
   int32_t v[C][4];
   int nv[C];                                         // logits in the chunk: >= 4, or the row ends inside it or before
@@ -437,8 +438,8 @@ __global__ __launch_bounds__(256) void softmax_small_kernel(SoftmaxSmall p) {
 
 template <int G, int C>
 hipError_t launch_softmax_small(const SoftmaxSmall& p, hipStream_t st) {
-  const int64_t wgs = (p.rows + 256 / G - 1) / (256 / G);
-  return launch_kernel(softmax_small_kernel<G, C>, dim3((unsigned)wgs), dim3(256), 0, st, p);
+  const GridShape g = grid_shape((p.rows + 256 / G - 1) / (256 / G));
+  return launch_kernel(softmax_small_kernel<G, C>, dim3(g.x, g.y), dim3(256), 0, st, p);
 }
 
 }  // namespace

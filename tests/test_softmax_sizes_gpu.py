@@ -36,3 +36,20 @@ def test_softmax_sizes(rows, L):
         got = yd.cpu().numpy()
         assert np.array_equal(got[: rows * L].reshape(rows, L), ref)
         assert np.all(got[rows * L:] == 99)
+
+
+def test_more_rows_than_one_grid_dimension():
+    """2^30 - 3 rows: one lane group per row is more than 2^32 work items along one dimension of a grid."""
+    rows, L, S, u = (1 << 30) - 3, 2, 0.01, 2
+    print(f"[case] softmax rows={rows} L={L}", flush=True)
+    period = 1 << 12
+    x = randint_array(11, (period, L), -400, 401, np.int32)
+    ref = torch.from_numpy(oracle.softmax(x, oracle.iexp_constants(S, u))).cuda()
+    xd = torch.from_numpy(x).cuda().repeat(-(-rows // period), 1)
+    yd = torch.full((rows + 16, L), 99, dtype=torch.int8, device="cuda")
+    Q.softmax_int32(Q.iexp_init(S, u), xd[:rows], yd[:rows])
+    torch.cuda.synchronize()
+    whole = rows // period
+    assert bool((yd[: whole * period].view(whole, period, L) == ref).all())
+    assert bool((yd[whole * period: rows] == ref[: rows - whole * period]).all())
+    assert bool((yd[rows:] == 99).all())
