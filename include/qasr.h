@@ -304,13 +304,15 @@ qasr_status qasr_encoder_forward(const qasr_encoder* e, const int8_t* x, int8_t*
  * activation slots live in a static device array inside the library, qasr_static_workspace_bytes()
  * = 32 MiB per GPU, held from the moment the library is loaded on that GPU until the process ends.
  * The call allocates nothing and frees nothing; x and y are still the caller's.  An encoder whose
- * qasr_encoder_workspace_bytes exceeds the array gives QASR_ERR_WORKSPACE (before any HIP call).
+ * activation buffers exceed the array gives QASR_ERR_WORKSPACE (before any HIP call).  Where only
+ * their rows' pitch makes them exceed it, the forward runs over dense rows (such an encoder holds its
+ * weights twice); where only the room for partial sums does, no contraction is split.
  * All calls on one GPU share that GPU's array, on every stream: two such forwards that overlap in
  * time on one GPU race (order them on one stream, or use qasr_encoder_forward with workspaces of
  * their own).  The array keeps what the last call left; no slot is read before this forward has
  * written it, so nothing needs clearing.  The device address of the array is looked up at the first
  * call on each GPU (that first call should not happen under stream capture).  Otherwise as
- * qasr_encoder_forward: same kernels, same bits. */
+ * qasr_encoder_forward: same bits. */
 size_t qasr_static_workspace_bytes(void);
 qasr_status qasr_encoder_forward_static(const qasr_encoder* e, const int8_t* x, int8_t* y, void* stream);
 

@@ -141,6 +141,9 @@ int32_t row_pad(int32_t T) { return (16 - T % 16) % 16; }
 
 size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 
+// the library's static device array (qasr_encoder_forward_static)
+#define QASR_STATIC_WORKSPACE_BYTES ((size_t)32 << 20)
+
 }  // namespace
 
 struct qasr_encoder {
@@ -168,6 +171,9 @@ struct qasr_encoder {
   int64_t in_rows = 0, out_rows = 0;    // rows (batch items x channels) of the network input and output
   int32_t in_T = 0, out_T = 0;          // and their lengths
   bool pitched = false;                 // the slots' rows have a pitch of their own (see rows_of)
+  // The same layers over dense rows, for qasr_encoder_forward_static: only where the pitched slots do not
+  // fit the static array and the dense ones do (else null).
+  qasr_encoder* dense = nullptr;
   int8_t* packed = nullptr;       // device: packed weights of all groups == 1 layers
   // Runs of consecutive ops that one launch of the persistent team kernel executes (team.hip); the
   // ops outside them are launched one by one.
@@ -639,7 +645,8 @@ qasr_status qasr_plan_slot_buffers(const int32_t* in_slot, const int32_t* res_sl
   return QASR_OK;
 }
 
-qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slots, qasr_encoder** out) {
+// may_pitch: rows may get a pitch of their own
+static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_slots, bool may_pitch, qasr_encoder** out) {
   if (!ops || !out) return QASR_ERR_NULL;
   if (n_ops < 1 || n_slots < 2) return QASR_ERR_SHAPE;
   *out = nullptr;
@@ -710,29 +717,43 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
 
   qasr_encoder* e = new (std::nothrow) qasr_encoder();
   if (!e) return QASR_ERR_HIP;
-  e->pitched = ragged && pitchable;
-  SlotPlan plan;
-  {
+  e->pitched = may_pitch && ragged && pitchable;
+  // The buffers of the slots with rows of either kind; their bytes in all.
+  // They should stay inside the 256 MB memory-side cache together: the deepest plan up to
+  // the configured depth whose buffers take at most three quarters of it (QuartzNet-15x5 shape:
+  // depth 4 at batch 32, 118 MB; depth 2 at batch 64, 2.44 against 2.46 ms with depth 4 and 2.60
+  // with the slots as buffers; at batch 128 even those take 264 MB and every further buffer
+  // costs: 4.78 ms with depth 0, 4.92 with 1, 5.53 with 4).
+  auto plan_buffers = [&](bool pitched, SlotPlan& pl) {
     std::vector<SlotWire> wires(n_ops);
     for (int32_t i = 0; i < n_ops; ++i) {
       const qasr_op& o = ops[i];
+      const int64_t T = out_len64(&o.d);
       wires[i] = SlotWire{o.in_slot, o.res_slot, o.out_slot,
                           std::vector<int32_t>(o.more_res_slots, o.more_res_slots + o.n_more_res),
                           i + 1 == n_ops ? (size_t)0   // (the last op writes the caller's output)
-                                         : (size_t)o.d.B * o.d.Cout *
-                                               (size_t)(out_len64(&o.d) + (e->pitched ? row_pad((int32_t)out_len64(&o.d)) : 0))};
+                                         : (size_t)o.d.B * o.d.Cout * (size_t)(T + (pitched ? row_pad((int32_t)T) : 0))};
     }
-    // The buffers should stay inside the 256 MB memory-side cache together: the deepest plan up to
-    // the configured depth whose buffers take at most three quarters of it (QuartzNet-15x5 shape:
-    // depth 4 at batch 32, 118 MB; depth 2 at batch 64, 2.44 against 2.46 ms with depth 4 and 2.60
-    // with the slots as buffers; at batch 128 even those take 264 MB and every further buffer
-    // costs: 4.78 ms with depth 0, 4.92 with 1, 5.53 with 4).
     const size_t budget = (size_t)192 << 20;
+    size_t total = 0;
     for (int depth = qasr::tuning().slot_depth; depth >= 0; --depth) {
-      plan_slots(wires, n_slots, depth, plan);
-      size_t total = 0;
-      for (size_t b = 1; b < plan.bytes.size(); ++b) total += round256(plan.bytes[b]);
+      plan_slots(wires, n_slots, depth, pl);
+      total = 0;
+      for (size_t b = 1; b < pl.bytes.size(); ++b) total += round256(pl.bytes[b]);
       if (total <= budget) break;
+    }
+    return total;
+  };
+  SlotPlan plan;
+  const size_t plan_bytes = plan_buffers(e->pitched, plan);
+  if (e->pitched && plan_bytes > QASR_STATIC_WORKSPACE_BYTES) {
+    SlotPlan dense_plan;
+    if (plan_buffers(false, dense_plan) <= QASR_STATIC_WORKSPACE_BYTES) {
+      const qasr_status ds = create_encoder(ops, n_ops, n_slots, false, &e->dense);
+      if (ds != QASR_OK) {
+        delete e;
+        return ds;
+      }
     }
   }
   const int32_t n_bufs = (int32_t)plan.bytes.size();
@@ -755,7 +776,7 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
   // ---- one-time device work: pack the dense k>1 weights
   if (packed_bytes) {
     const hipError_t me = hipMalloc((void**)&e->packed, packed_bytes);
-    if (me != hipSuccess) { delete e; return hip_status(me); }
+    if (me != hipSuccess) { qasr_encoder_destroy(e); return hip_status(me); }
   }
   size_t poff = 0, split_bytes = 0;
   e->ops.resize(n_ops);
@@ -865,6 +886,10 @@ qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slo
   return QASR_OK;
 }
 
+qasr_status qasr_encoder_create(const qasr_op* ops, int32_t n_ops, int32_t n_slots, qasr_encoder** out) {
+  return create_encoder(ops, n_ops, n_slots, true, out);
+}
+
 size_t qasr_encoder_workspace_bytes(const qasr_encoder* e) { return e ? e->ws_bytes : 0; }
 
 int32_t qasr_encoder_num_ops(const qasr_encoder* e) { return e ? (int32_t)e->ops.size() : 0; }
@@ -969,7 +994,6 @@ qasr_status qasr_encoder_forward(const qasr_encoder* e, const int8_t* x, int8_t*
 // ---- the forward for callers that can neither allocate nor pass a workspace: the activation slots
 // live in a static device array of the library.  The array's name is only a host-side stand-in; its
 // device address is looked up once per device and kept.
-#define QASR_STATIC_WORKSPACE_BYTES ((size_t)32 << 20)
 static __device__ __align__(256) unsigned char scratch[QASR_STATIC_WORKSPACE_BYTES];
 
 namespace {
@@ -1002,6 +1026,7 @@ size_t qasr_static_workspace_bytes(void) { return QASR_STATIC_WORKSPACE_BYTES; }
 
 qasr_status qasr_encoder_forward_static(const qasr_encoder* e, const int8_t* x, int8_t* y, void* stream) {
   if (!e || !x || !y) return QASR_ERR_NULL;
+  if (e->dense) e = e->dense;
   if (e->split_off > QASR_STATIC_WORKSPACE_BYTES) return QASR_ERR_WORKSPACE;    // before any HIP call
   void* ws = nullptr;
   const qasr_status st = static_scratch(&ws);
@@ -1193,6 +1218,7 @@ void qasr_encoder_destroy(qasr_encoder* e) {
     if (r.ops_dev) (void)hipFree(r.ops_dev);
     if (r.ctl) (void)hipFree(r.ctl);
   }
+  qasr_encoder_destroy(e->dense);
   delete e;
 }
 

@@ -7,9 +7,11 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2103_16827_amd as Q
 import qasr_workloads as W
 from gpu_util import dev, GpuNet
+from qasr_workloads.nets import _Builder
 
 pytestmark = pytest.mark.gpu
 
@@ -56,4 +58,25 @@ def test_static_workspace_limit_is_an_error_before_any_launch():
     assert e.value.status == -6
     torch.cuda.synchronize()
     assert bool((y == 5).all())
+    g.enc.close()
+
+
+def test_ragged_encoder_whose_dense_slots_fit():
+    """Four frames per row: the rows of a pitch of 16 take four times the dense ones, 48 MiB against 12 MiB."""
+    print("[case] static forward: short ragged rows", flush=True)
+    b = _Builder("short_rows", 92, 1024, 64, 4)
+    for i in range(6):
+        b.op(f"p{i}", 512, relu=True, act=2 if i == 1 else 0)
+    b.op("out", 29, relu=False)
+    net = b.done()
+    params = W.draw_net_params(net, 3)
+    x = W.draw_input(net, 3)
+    ref = oracle.encoder_forward(net, params, x)
+    g = GpuNet(net, params)
+    assert g.enc.workspace_bytes > Q.static_workspace_bytes()
+    assert np.array_equal(g.forward(dev(x)).cpu().numpy(), ref)
+    y = torch.full((net.B, net.Cout, net.Tout), 5, dtype=torch.int8, device="cuda")
+    g.enc.forward_static(dev(x), y)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), ref)
     g.enc.close()
