@@ -36,7 +36,7 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-constexpr int kPastCaches = 17;   // sc0 sc1: stores written through to memory, loads from there
+constexpr int kStoreThrough = 17;   // sc0 sc1: partial sums are written through, which leaves the release little to write back
 constexpr int kMaxSplits = 8;
 
 constexpr int kXS = 80;       // LDS row pitch in bytes: 64 channels + 16 pad
@@ -287,9 +287,13 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   // ---- splits > 1 (a launch of few tiles would leave most compute units idle while each of its
   // workgroups goes through the whole contraction: 768 channels, 25 taps, 2 x 200 frames 50 -> 20 us
   // with four): the sums of this range go to memory, and the workgroup of the tile that comes last
-  // adds those of the others to its own and goes on.  Another compute die's writes do not appear in
-  // this one's L2 by themselves: the stores are written through (sc0 sc1) and complete before the
-  // arrival is counted, the loads are made after it and go past the caches.
+  // adds those of the others to its own and goes on.  The handover is release and acquire at device scope,
+  // which on this chip is what makes one die's writes appear behind another die's L2: every wave's stores
+  // are complete before the barrier, thread 0 counts the arrival with release order (what its L2 still holds
+  // of them is written back), and the thread that finds itself last makes the acquire fence (its die's
+  // stale lines go) before the barrier behind which the others' sums are loaded.  Nobody waits for anybody.
+  // (Dense-residual Jasper, 2 x 811 frames: 1366 us; 1487 with write-back stores; 1278 with a relaxed count and
+  // loads past the caches, an order that nothing promises; of the 88 us the write-back is 62, the fence 26.)
   if (g.splits > 1) {
     auto part_of = [&](int s_) __attribute__((always_inline)) {
       return __builtin_amdgcn_make_buffer_rsrc(p.part + ((int64_t)(co_tile * nbt + bt) * g.splits + s_) * (MT * NT * 1024), 0,
@@ -303,18 +307,21 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
       if (owned(mt)) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, acc[mt][nt]), mine, poff, (mt * NT + nt) * 4096, kPastCaches);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, acc[mt][nt]), mine, poff, (mt * NT + nt) * 4096, kStoreThrough);
       }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();                                // (the LDS buffers have been read by all, too)
     if (threadIdx.x == 0) {
-      const unsigned before = __hip_atomic_fetch_add(p.part_count + co_tile * nbt + bt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned* const count = p.part_count + co_tile * nbt + bt;
+      const unsigned before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (before + 1 == (unsigned)g.splits) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (for the next layer)
+      }
       *reinterpret_cast<volatile unsigned*>(xs) = before;
     }
     __syncthreads();
     if (*reinterpret_cast<volatile unsigned*>(xs) + 1 != (unsigned)g.splits) return;   // whole workgroup
-    if (threadIdx.x == 0)                           // (for the next layer)
-      __hip_atomic_store(p.part_count + co_tile * nbt + bt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll 1
     for (int o = 1; o < g.splits; ++o) {
       const __amdgpu_buffer_rsrc_t from = part_of(split + o < g.splits ? split + o : split + o - g.splits);
@@ -323,7 +330,7 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
         if (owned(mt)) {
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
-            acc[mt][nt] += __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(from, poff, (mt * NT + nt) * 4096, kPastCaches));
+            acc[mt][nt] += __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(from, poff, (mt * NT + nt) * 4096, 0));
         }
     }
   }

@@ -170,3 +170,33 @@ def test_no_plain_dereference_of_layer_operands_where_loads_are_hand_counted():
                                      f"{text[m.start():m.end() + 20]!r}")
     assert re.search(rf"\b[pv](?:\.|->){OPERANDS}\s*\[", "x = p.m[co];") and re.search(
         rf"\*\s*\(?\s*[pv](?:\.|->){OPERANDS}\b(?!\s*[?!=])", "int b = *p.bias;")
+
+
+def handover_orders(body):
+    """Positions of a split contraction's steps: partial sums stored, all waves' stores complete, arrival counted
+    with release order, acquire fence of the last workgroup, barrier, the others' sums loaded."""
+    steps = [r"raw_buffer_store_b128\s*\([^;]*\bmine\b", r"s_waitcnt vmcnt\(0\)", r"__syncthreads\s*\(\s*\)",
+             r"__hip_atomic_fetch_add\s*\([^;]*__ATOMIC_(?:RELEASE|ACQ_REL)\s*,\s*__HIP_MEMORY_SCOPE_AGENT",
+             r"__builtin_amdgcn_fence\s*\(\s*__ATOMIC_ACQUIRE\s*,\s*\"agent\"\s*\)", r"__syncthreads\s*\(\s*\)",
+             r"raw_buffer_load_b128\s*\([^;]*\bfrom\b"]
+    at, found = 0, []
+    for s in steps:
+        m = re.compile(s).search(body, at)
+        if not m:
+            return None
+        at = m.end()
+        found.append(m.start())
+    return found
+
+
+def test_partial_sums_are_handed_over_with_release_and_acquire():
+    """Workgroups of one tile may run on different dies, whose caches see each other's writes only through
+    device-scope release and acquire."""
+    (body,) = [b for n, b in functions(sources()["conv_pipe.hip"]) if n == "conv_pipe_kernel"]
+    assert handover_orders(body)
+    assert not handover_orders(body.replace("__ATOMIC_RELEASE", "__ATOMIC_RELAXED"))
+    assert not handover_orders(body.replace("__ATOMIC_ACQUIRE", "__ATOMIC_RELAXED"))
+    for name, text in sources().items():          # no other kernel counts arrivals with less
+        if name in ("team.hip",):                 # (bounded polls of one die's team, off by default)
+            continue
+        assert not re.search(r"__hip_atomic_fetch_add\s*\([^;]*__ATOMIC_RELAXED", text), name
