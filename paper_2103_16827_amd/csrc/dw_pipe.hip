@@ -54,15 +54,6 @@ struct DwpGeom {
   int c_per_xcd;  // channels per XCD: ceil(C / 8)
 };
 
-// the short-form rescale of four accumulators, clamped to int8 (see requant_short4; off the GPU by the plain form)
-__device__ __forceinline__ uint32_t short4(const int32_t (&a)[4], int32_t m, int32_t sh, int32_t rnd) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return requant_short4<false, false>(a, m, sh, rnd, 0u);
-#else
-  return requant_pack4<true, false>(a, m, sh, rnd, 0u, -128, 127);
-#endif
-}
-
 // ACT: a unary activation's table is applied after the clamp (its own instantiation: the plain
 // layers keep their code as it is)
 template <int KC, int R, int NI, bool ACT>
@@ -243,7 +234,7 @@ __global__ __launch_bounds__(256) void dw_pipe_kernel(ConvParams p, DwpGeom g) {
         const v4i av = acc[q & 1][e];
         const int32_t a4[4] = {av[0], av[1], av[2], av[3]};
         uint32_t pk;
-        if constexpr (FORM == 2) pk = short4(a4, mc, sh, rnd);
+        if constexpr (FORM == 2) pk = requant_short4<false, false>(a4, mc, sh, rnd, 0u);
         else pk = requant_pack4<FORM == 1, false>(a4, mc, sh, rnd, 0u, lo, hi127);
         if (has_act) {                               // table[code + 128], byte by byte
           const uint32_t cd = pk ^ 0x80808080u;

@@ -33,18 +33,6 @@ struct PwpGeom {
   int nopipe;        // tuning: every pass does its epilogue right after its own products
 };
 
-// the short-form epilogue of four accumulators (33 <= s <= 54, sh = s - 32; see requant_short4; off the
-// GPU, where the instructions do not exist, by the plain form)
-constexpr int kShortS0 = 33, kShortS1 = 54;
-template <bool RES, bool RELU>
-__device__ __forceinline__ uint32_t short4(const int32_t (&a)[4], int32_t m, int32_t sh, int32_t rnd, uint32_t resw) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return requant_short4<RES, RELU>(a, m, sh, rnd, resw);
-#else
-  return requant_pack4<true, RES>(a, m, sh, rnd, resw, RELU ? 0 : -128, 127);
-#endif
-}
-
 __device__ __forceinline__ v2i lds_read_tr8(const unsigned char* p) {
   return __builtin_amdgcn_ds_read_tr8_b64_v2i32(
       (v2i __attribute__((address_space(3)))*)(const_cast<unsigned char*>(p)));
@@ -226,7 +214,7 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
     const v4i av = acc[par][mt][nt];
     const int32_t a4[4] = {av[0], av[1], av[2], av[3]};
     uint32_t pk;
-    if constexpr (FAST) pk = short4<RES, RELU>(a4, mc[nt], sh[nt], rnd[nt], rw);
+    if constexpr (FAST) pk = requant_short4<RES, RELU>(a4, mc[nt], sh[nt], rnd[nt], rw);
     else pk = requant_pack4<false, RES>(a4, mc[nt], sh[nt], rnd[nt], rw, lo, hi127);
     if (has_act) {                                 // table[code + 128], byte by byte
       const uint32_t c = pk ^ 0x80808080u;
@@ -447,7 +435,7 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
     for (int nt = 0; nt < NT; ++nt) {
       mc[nt] = *reinterpret_cast<const int32_t*>(c + nt * 192 + 64);
       s_[nt] = *reinterpret_cast<const int32_t*>(c + nt * 192 + 128);
-      fast = fast && s_[nt] >= kShortS0 && s_[nt] <= kShortS1;
+      fast = fast && s_[nt] >= kShortMin && s_[nt] <= kShortMax;
     }
     const bool all_fast = __builtin_amdgcn_readfirstlane((int)__all(fast)) != 0;   // wave-uniform, and known to be
 #pragma unroll

@@ -153,6 +153,24 @@ inline int32_t dyadic_rescale64(int32_t A, int32_t m, int32_t s) {
   v = v < -(1 << 20) ? -(1 << 20) : v;
   return (int32_t)v;
 }
+// v_ashr_pk_{i8,u8}_i32: both values shifted, saturated to a signed / an unsigned byte, packed
+inline unsigned short sim_ashr_pk_i8(int32_t a, int32_t b, uint32_t sh) {
+  auto byte = [&](int32_t v) { return (unsigned)(uint8_t)med3_i32(v >> (sh & 31), -128, 127); };
+  return (unsigned short)(byte(a) | byte(b) << 8);
+}
+inline unsigned short sim_ashr_pk_u8(int32_t a, int32_t b, uint32_t sh) {
+  auto byte = [&](int32_t v) { return (unsigned)med3_i32(v >> (sh & 31), 0, 255); };
+  return (unsigned short)(byte(a) | byte(b) << 8);
+}
+#define __builtin_amdgcn_ashr_pk_i8_i32(a, b, sh) sim_ashr_pk_i8(a, b, sh)
+#define __builtin_amdgcn_ashr_pk_u8_i32(a, b, sh) sim_ashr_pk_u8(a, b, sh)
+inline int32_t __mulhi(int32_t a, int32_t b) { return mulhi_i32(a, b); }
+}  // namespace qasr
+
+// the short-form rescale as common.hpp has it (pasted by the test)
+#include "short_form_extract.hpp"
+
+namespace qasr {
 template <bool FAST, bool RES>
 inline uint32_t requant_pack4(const int32_t (&a)[4], int32_t m, int32_t sh, int32_t rnd, uint32_t resw, int32_t lo,
                               int32_t hi127) {

@@ -34,6 +34,9 @@ def generate(tmp, mutate=None):
     assert m, "ConvParams not found in common.hpp"
     open(os.path.join(tmp, "conv_params_extract.hpp"), "w").write(
         "#pragma once\n#include <cstdint>\nnamespace qasr {\n" + m.group(0) + "\n}\n")
+    m = re.search(r"constexpr int kShortMin = .*?\n(?=\n?\}  // namespace qasr)", common, flags=re.S)
+    assert m and "requant_short4" in m.group(0), "the short-form rescale not found in common.hpp"
+    open(os.path.join(tmp, "short_form_extract.hpp"), "w").write("namespace qasr {\n" + m.group(0) + "\n}\n")
 
 
 def build_and_run(tmp, small=False):
@@ -134,3 +137,15 @@ def test_the_depthwise_replay_catches_planted_mistakes(tmp_path, what):
     generate_dw(str(tmp_path), mutate)
     r = build_and_run_dw(str(tmp_path))
     assert r.returncode != 0 and "SIM FAILURE" in r.stderr, (r.stdout[-2000:], r.stderr[-2000:])
+
+
+@pytest.mark.skipif(not os.path.exists(CLANG), reason="no host clang beside the HIP toolchain")
+def test_short_form_rescale_is_the_64_bit_one(tmp_path):
+    generate(str(tmp_path))
+    exe = os.path.join(str(tmp_path), "short_form")
+    c = subprocess.run([CLANG, "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize=shift", "-fno-sanitize-recover=all",
+                        "-Wno-unknown-attributes", "-Wno-ignored-attributes", "-I", str(tmp_path), "-I", SIM,
+                        os.path.join(SIM, "short_form_main.cpp"), "-o", exe], capture_output=True, text=True, timeout=300)
+    assert c.returncode == 0, c.stderr[-3000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "values right" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
