@@ -184,14 +184,15 @@ __device__ __forceinline__ uint32_t requant_pack4(const int32_t (&a)[4], int32_t
   return p01 | p23;
 }
 
-// ---- short-form epilogue in fewer instructions (33 <= s <= 54): v_ashr_pk_{i8,u8}_i32 shifts,
-// saturates and packs two values in one instruction.  The residual byte is added before the shift as
-// residual * 2^sh, exactly (|mulhi| <= 2^30, |residual * 2^22| <= 2^29, rnd <= 2^21).  With relu the
+// ---- short-form epilogue in fewer instructions (33 <= s <= 62; 54 with a residual): v_ashr_pk_{i8,u8}_i32
+// shifts, saturates and packs two values in one instruction.  The residual byte is added before the shift
+// as residual * 2^sh, exactly (|mulhi| <= 2^30, |residual * 2^22| <= 2^29, rnd <= 2^21; without one
+// rnd <= 2^29).  With relu the
 // unsigned form is taken one bit short, [0, 255], and halved: floor(floor(h / 2^(sh-1)) / 2) =
 // floor(h / 2^sh) and 255 / 2 = 127, so the clamp to [0, 127] costs two instructions per four outputs.
 // 13 instructions per four outputs (11 without relu, 4 more with a residual) against 19 (27) for
 // multiply-high, add, shift, median and pack; all of them issue at the same rate.
-constexpr int kShortMin = 33, kShortMax = 54;   // s of the short form
+constexpr int kShortMin = 33, kShortMax = 62, kShortMaxRes = 54;   // s of the short form; with a residual
 
 // two 16-bit halves in one dword (as a vector: the compiler then needs no masks)
 typedef unsigned short half16x2 __attribute__((ext_vector_type(2)));

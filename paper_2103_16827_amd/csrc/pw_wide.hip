@@ -252,7 +252,7 @@ __global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) 
   else asm volatile("" ::: "memory");
   bool ok_s = true;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) ok_s = ok_s && sc[nt] >= kShortMin && sc[nt] <= kShortMax;
+  for (int nt = 0; nt < NT; ++nt) ok_s = ok_s && sc[nt] >= kShortMin && sc[nt] <= (p.res ? kShortMaxRes : kShortMax);
   const bool fast = __all(ok_s);
   auto finish = [&](auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   const uint32_t sbase = (uint32_t)(n * 128 + 4 * gi) | (uint32_t)((n & 7) << 4);
   bool ok = true;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= kShortMax;
+  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (p.res ? kShortMaxRes : kShortMax);
   const bool fast = __all(ok);
   const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
       p.y + (int64_t)b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);

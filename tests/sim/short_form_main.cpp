@@ -69,7 +69,7 @@ void check_range(int s_max) {
 
 int main() {
   check_range<false>(kShortMax);
-  check_range<true>(kShortMax);
+  check_range<true>(kShortMaxRes);
   std::printf("%ld values right\n", checked);
   return 0;
 }
