@@ -292,9 +292,8 @@ size_t qasr_encoder_workspace_bytes(const qasr_encoder* e);
 
 /* Runs every op in order on `stream`.  x: [B,Cin,Tin] of the first op's descriptor; y: output
  * of the last op; workspace: device, 256-byte aligned, >= qasr_encoder_workspace_bytes(e).
- * Enqueues at most n_ops kernels (plus one per activation, plus a copy of x and of y where their rows
- * are not multiples of 16 frames and a layer there wants aligned ones) and returns; allocates nothing;
- * may be captured into a HIP graph.  A depthwise layer and the pointwise layer that is the only
+ * Enqueues at most n_ops kernels (plus one per activation, plus one where contractions are split)
+ * and returns; allocates nothing; may be captured into a HIP graph.  A depthwise layer and the pointwise layer that is the only
  * reader of its output run as one launch where their shapes allow (same bits). */
 qasr_status qasr_encoder_forward(const qasr_encoder* e, const int8_t* x, int8_t* y,
                                  void* workspace, size_t workspace_bytes, void* stream);
@@ -320,15 +319,16 @@ qasr_status qasr_encoder_forward_static(const qasr_encoder* e, const int8_t* x, 
  * [B,Cin,Tin], clipping range alpha, see qasr_quantize), the integer encoder, the dequantiser
  * S_out * q on its output (float32 [B,Cout,Tout], see qasr_dequantize).  The int8 copies of input
  * and output live in the workspace too: it must hold qasr_encoder_workspace_bytes_f32(e) bytes
- * (256-byte aligned).  Enqueues n_ops + 2 kernels (plus one per activation) and returns; errors
+ * (256-byte aligned).  Enqueues two kernels more than qasr_encoder_forward and returns; errors
  * as for the three calls it is made of. */
 size_t qasr_encoder_workspace_bytes_f32(const qasr_encoder* e);
 qasr_status qasr_encoder_forward_f32(const qasr_encoder* e, const float* x, float alpha, float S_out,
                                      float* y, void* workspace, size_t workspace_bytes,
                                      void* stream);
 
-/* The same forward as a HIP graph: one launch replays all n_ops kernels with the pointers given
- * here (x, y and workspace must stay valid and in place as long as the graph is used; their
+/* The same forward as a HIP graph: one launch replays all its kernels (a forward of up to four kernels
+ * is enqueued kernel by kernel instead, which runs sooner) with the pointers given here (x, y and
+ * workspace must stay valid and in place as long as the graph is used; their
  * contents may change between launches).  qasr_encoder_graph_create runs one ordinary forward on
  * a stream of its own (so y and the workspace are written), captures a second one, instantiates
  * it and returns the handle in *out (HOST); it synchronises and allocates, so call it at set-up.
@@ -341,27 +341,32 @@ qasr_status qasr_encoder_graph_create(const qasr_encoder* e, const int8_t* x, in
 qasr_status qasr_encoder_graph_launch(qasr_encoder_graph* g, void* stream);
 void qasr_encoder_graph_destroy(qasr_encoder_graph* g);
 
-/* Same as qasr_encoder_forward_layerwise, but brackets every op with HIP events, waits for completion and
- * writes each op's device time in milliseconds to op_ms[0..n_ops) (HOST memory): the interval
- * between the events around the op minus an equal share of what the inner events cost (the
- * forward is also run once without them in the same call; the op times add up to that run's
- * duration).  For profiling only: it runs the forward twice, synchronises and creates/destroys
- * events. */
+/* Same as qasr_encoder_forward (without team runs, see below), but brackets every launch with HIP events,
+ * waits for completion and writes the device times in milliseconds to op_ms[0..n_ops) (HOST memory):
+ * for the op that a launch begins with, the interval between the events around the launch (and its
+ * separate activation pass, if any) minus an equal share of what the inner events cost; 0 for an op
+ * that ran in the launch before (qasr_encoder_op_launch).  The forward is also run once without the
+ * inner events in the same call; the times add up to that run's duration.  For profiling only: it
+ * runs the forward twice, synchronises and creates/destroys events. */
 qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, int8_t* y,
                                        void* workspace, size_t workspace_bytes, void* stream,
                                        float* op_ms);
 
-/* Number of ops, and the name of the kernel family op i is dispatched to (depthwise:
+/* Number of ops, and the name of the kernel family op i belongs to by its shape (depthwise:
  * "dw_pipe", "dw_mfma"; pointwise: "pw_pipe", "pw_tile"; dense and any other pointwise shape:
  * "conv_pipe", "gemm_mfma"; any shape: "conv_generic"; static storage, NULL if i is out of range).
- * Families launch forms of their own: packed pointwise layers of the pw_pipe, pw_tile and gemm_mfma families' shapes may run
- * as pw_wide, a depthwise + pointwise pair as one kernel. */
+ *   qasr_encoder_op_launch: what qasr_encoder_forward launches for it over 16-byte aligned x and y:
+ *     the op that the launch begins with (i, or i - 1 where op i is the pointwise half of a depthwise +
+ *     pointwise pair; -1 if i is out of range), and in *kernel (unless NULL) the kernel's name: "sep"
+ *     for such a pair, "pw_wide" for pointwise layers of the pw_pipe, pw_tile and gemm_mfma families
+ *     that this kernel runs faster, else the family's.  HOST only. */
 int32_t qasr_encoder_num_ops(const qasr_encoder* e);
 const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i);
-/* 1 if op i's activation (qasr_op.act) is applied inside the layer's own kernel (a unary
- * activation after a layer of the "pw_pipe" or "dw_pipe" family, through a 256-entry table of the
- * activation's int8 outputs built at create time), 0 if it runs as the separate in-place pass or
- * the op has none; -1 if i is out of range.  Same bits either way. */
+int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** kernel);
+/* 1 if op i's activation (qasr_op.act) is applied inside the layer's own kernel over 16-byte aligned x and
+ * y (a unary activation after a layer that pw_pipe, pw_wide or dw_pipe runs, through a 256-entry table of
+ * the activation's int8 outputs built at create time), 0 if it runs as the separate in-place pass or
+ * the op has none; -1 if i is out of range.  Same bits either way.  (In a pair it always is.) */
 int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i);
 
 /* Runs of layers in one launch (EXPERIMENTAL: only with QASR_TEAM set in the environment when the
@@ -408,8 +413,10 @@ qasr_status qasr_probe_copy(const void* src, void* dst, size_t bytes, void* stre
 int32_t qasr_probe_mfma_i8_outputs(void);
 qasr_status qasr_probe_mfma_i8(int32_t iters, int32_t* out, double* ops, void* stream);
 
-/* Name of the kernel family qasr_conv1d_int8 would dispatch this descriptor to (host-only). */
+/* Name of the kernel family this descriptor belongs to, and of the kernel that qasr_conv1d_int8 launches for
+ * it over 16-byte aligned tensors (names as for qasr_encoder_op_kernel and _op_launch; host-only). */
 const char* qasr_conv1d_kernel_name(const qasr_conv1d_desc* d);
+const char* qasr_conv1d_launch_name(const qasr_conv1d_desc* d);
 
 const char* qasr_status_string(qasr_status st);
 

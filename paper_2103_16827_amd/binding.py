@@ -121,6 +121,10 @@ def lib():
         L.qasr_encoder_num_ops.argtypes = [_vp]
         L.qasr_encoder_op_kernel.restype = ctypes.c_char_p
         L.qasr_encoder_op_kernel.argtypes = [_vp, _i32]
+        L.qasr_encoder_op_launch.restype = _i32
+        L.qasr_encoder_op_launch.argtypes = [_vp, _i32, ctypes.POINTER(ctypes.c_char_p)]
+        L.qasr_conv1d_launch_name.restype = ctypes.c_char_p
+        L.qasr_conv1d_launch_name.argtypes = [dp]
         L.qasr_encoder_op_act_fused.restype = _i32
         L.qasr_encoder_op_act_fused.argtypes = [_vp, _i32]
         L.qasr_encoder_destroy.restype = None
@@ -206,6 +210,12 @@ def conv1d_out_len(d: ConvDesc) -> int:
 
 def conv1d_kernel_name(d: ConvDesc) -> Optional[str]:
     r = lib().qasr_conv1d_kernel_name(ctypes.byref(d))
+    return r.decode() if r else None
+
+
+def conv1d_launch_name(d: ConvDesc) -> Optional[str]:
+    """The kernel that conv1d_int8 launches for this descriptor (16-byte aligned tensors)."""
+    r = lib().qasr_conv1d_launch_name(ctypes.byref(d))
     return r.decode() if r else None
 
 
@@ -357,6 +367,11 @@ class Encoder:
     def op_kernel(self, i: int) -> str:
         return lib().qasr_encoder_op_kernel(self._h, i).decode()
 
+    def op_launch(self, i: int):
+        """(first op of the launch that runs op i, its kernel's name) in a forward over aligned tensors."""
+        name = ctypes.c_char_p()
+        return lib().qasr_encoder_op_launch(self._h, i, ctypes.byref(name)), name.value.decode()
+
     def op_act_fused(self, i: int) -> bool:
         return lib().qasr_encoder_op_act_fused(self._h, i) == 1
 
@@ -407,6 +422,7 @@ class Encoder:
         return y
 
     def forward_timed(self, x, y, workspace):
+        """Device milliseconds per launch, at the op each launch begins with (0 at the others, see op_launch)."""
         ms = (ctypes.c_float * self.n_ops)()
         _check(lib().qasr_encoder_forward_timed(self._h, _ptr(x), _ptr(y), _ptr(workspace),
                                                 workspace.numel() * workspace.element_size(), _stream(), ms),

@@ -106,18 +106,20 @@ Kernel pick_kernel(const ConvParams& p) {
 // kernels whose epilogue applies a unary activation's table (ConvParams::act_lut)
 bool applies_act_table(Kernel k) { return k == Kernel::PwPipe || k == Kernel::PwWide || k == Kernel::DwPipe; }
 
+// the kernel's own name, and the name of the family it is counted to
 const char* kernel_name(Kernel k) {
   switch (k) {
     case Kernel::DwMfma: return "dw_mfma";
     case Kernel::DwPipe: return "dw_pipe";
     case Kernel::PwTile: return "pw_tile";
     case Kernel::PwPipe: return "pw_pipe";
-    case Kernel::PwWide:      // (launches the packed pointwise layers of that family)
+    case Kernel::PwWide: return "pw_wide";
     case Kernel::GemmMfma: return "gemm_mfma";
     case Kernel::ConvPipe: return "conv_pipe";
     default: return "conv_generic";
   }
 }
+const char* family_name(Kernel k) { return kernel_name(k == Kernel::PwWide ? Kernel::GemmMfma : k); }
 
 qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
   hipError_t e;
@@ -326,7 +328,13 @@ int32_t qasr_conv1d_out_len(const qasr_conv1d_desc* d) {
 const char* qasr_conv1d_kernel_name(const qasr_conv1d_desc* d) {
   if (check_desc(d) != QASR_OK) return nullptr;
   const ConvParams p = make_params(d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-  return kernel_name(family_of(p));
+  return family_name(family_of(p));
+}
+
+const char* qasr_conv1d_launch_name(const qasr_conv1d_desc* d) {
+  if (check_desc(d) != QASR_OK) return nullptr;
+  const ConvParams p = make_params(d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+  return kernel_name(pick_kernel(p));
 }
 
 qasr_status qasr_conv1d_int8(const qasr_conv1d_desc* d, const int8_t* x, const int8_t* w,
@@ -896,7 +904,27 @@ int32_t qasr_encoder_num_ops(const qasr_encoder* e) { return e ? (int32_t)e->ops
 
 const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i) {
   if (!e || i < 0 || i >= (int32_t)e->ops.size()) return nullptr;
-  return kernel_name(e->ops[i].family);
+  return family_name(e->ops[i].family);
+}
+
+// whether op i and op i + 1 run as one launch over 16-byte aligned, dense input and output
+static bool runs_as_pair(const qasr_encoder* e, size_t i) {
+  if (!e->ops[i].sep) return false;
+  ConvParams p = e->ops[i].p, q = e->ops[i + 1].p;
+  rows_of(e, i, 0, 0, p);
+  rows_of(e, i + 1, 0, 0, q);
+  return qasr::sep_supported(p, q);
+}
+
+int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** kernel) {
+  if (!e || i < 0 || i >= (int32_t)e->ops.size()) return -1;
+  const bool second = i > 0 && runs_as_pair(e, (size_t)i - 1);
+  if (kernel) {
+    ConvParams p = e->ops[i].p;
+    rows_of(e, (size_t)i, 0, 0, p);
+    *kernel = second || runs_as_pair(e, (size_t)i) ? "sep" : kernel_name(pick_kernel(p));
+  }
+  return second ? i - 1 : i;
 }
 
 int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i) {
@@ -904,28 +932,41 @@ int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i) {
   return e->ops[i].act_fused ? 1 : 0;
 }
 
-// team: 0 = every op as a launch of its own, 1 = the planned runs through the team kernel,
-// 2 = the same with the team kernel's per-layer clock stamps switched on
 int32_t qasr_encoder_op_in_team(const qasr_encoder* e, int32_t i) {
   if (!e || i < 0 || i >= (int32_t)e->ops.size()) return -1;
   return e->run_of.empty() ? 0 : (e->run_of[i] >= 0 ? 1 : 0);
 }
 
-// xpad, ypad: frames between the rows of x and y (pitched encoders only; 0 = the caller's dense tensors)
+struct ForwardHow {
+  int team = 1;                   // 0: no team runs, 1: the planned ones, 2: with the team kernel's clock stamps
+  bool pairs = true;              // depthwise + pointwise pairs as one launch
+  int32_t xpad = 0, ypad = 0;     // frames between the rows of x and y (pitched encoders only; 0 = the caller's dense tensors)
+  bool split = true;              // the workspace has room for the partial sums of split contractions
+  // ev[i] is recorded where the launch that begins with op i begins (and began[i] set), ev[n] at the end
+  hipEvent_t* ev = nullptr;
+  char* began = nullptr;
+};
+
 static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,
-                                size_t workspace_bytes, hipStream_t st, hipEvent_t* ev, int team = 1,
-                                int32_t xpad = 0, int32_t ypad = 0, bool split = true) {
+                                size_t workspace_bytes, hipStream_t st, const ForwardHow& how = ForwardHow()) {
+  const int32_t xpad = how.xpad, ypad = how.ypad;
+  bool split = how.split;
+  auto begin = [&](size_t i) {
+    if (!how.ev) return hipSuccess;
+    how.began[i] = 1;
+    return hipEventRecord(how.ev[i], st);
+  };
   if (!e || !x || !y) return QASR_ERR_NULL;
   if (e->ws_bytes && (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < (split ? e->ws_bytes : e->split_off)))
     return QASR_ERR_WORKSPACE;
   int8_t* ws = (int8_t*)workspace;
   const size_t n = e->ops.size();
-  const bool fuse = team && !ev;                // (timed and layer-by-layer forwards launch every layer by itself)
   // (the team kernel's loads want 16-byte aligned tensors, like the kernels it replaces)
-  const bool use_team = team && !ev && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);
+  const bool use_team = how.team && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);
   // room for the partial sums of split contractions, and their counters (zero between layers from here on)
   split = split && e->ws_bytes > e->split_off;
   const size_t split_bytes = split ? e->ws_bytes - e->split_off - round256(4 * qasr::kConvSplitCounters) : 0;
+  if (const hipError_t be = begin(0); be != hipSuccess) return hip_status(be);
   if (split) {
     const hipError_t ce = qasr::launch_conv_split_clear((unsigned*)(ws + e->split_off + split_bytes), st);
     if (ce != hipSuccess) return hip_status(ce);
@@ -950,7 +991,7 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     if (use_team && e->run_of[i] >= 0) {
       const qasr_encoder::TeamRun& r = e->runs[e->run_of[i]];
       const hipError_t te = qasr::launch_team(r.ops_dev, r.count, x, ws, y, e->ops[0].d.B, r.ctl, e->team_wgs,
-                                              team == 2 ? 1 : 0, st);
+                                              how.team == 2 ? 1 : 0, st);
       if (te != hipSuccess) return hip_status(te);
       i = (size_t)(r.first + r.count) - 1;
       continue;
@@ -958,7 +999,9 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     const qasr_encoder::Op& op = e->ops[i];
     ConvParams p;
     bind(i, p);
-    if (op.sep && fuse) {
+    if (i > 0)
+      if (const hipError_t be = begin(i); be != hipSuccess) return hip_status(be);
+    if (op.sep && how.pairs) {
       ConvParams q;
       bind(i + 1, q);
       p.act_lut = op.act_table;                  // (of the activation between the two)
@@ -969,7 +1012,6 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
         continue;
       }
     }
-    if (ev) { const hipError_t re = hipEventRecord(ev[i], st); if (re != hipSuccess) return hip_status(re); }
     // (the kernel of this call decides who applies a unary activation: its epilogue, or a pass of its own)
     const Kernel kk = pick_kernel(p);
     p.act_lut = applies_act_table(kk) ? op.act_table : nullptr;
@@ -982,13 +1024,12 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
       if (ae != hipSuccess) return hip_status(ae);
     }
   }
-  if (ev) { const hipError_t re = hipEventRecord(ev[n], st); if (re != hipSuccess) return hip_status(re); }
-  return QASR_OK;
+  return hip_status(how.ev ? hipEventRecord(how.ev[n], st) : hipSuccess);
 }
 
 qasr_status qasr_encoder_forward(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,
                                  size_t workspace_bytes, void* stream) {
-  return forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, nullptr);
+  return forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 // ---- the forward for callers that can neither allocate nor pass a workspace: the activation slots
@@ -1033,13 +1074,17 @@ qasr_status qasr_encoder_forward_static(const qasr_encoder* e, const int8_t* x, 
   if (st != QASR_OK) return st;
   // every slot is written in full by the op that produces it before any op reads it: nothing in the
   // array has to start at zero, whatever an earlier call left there
-  return forward_impl(e, x, y, ws, QASR_STATIC_WORKSPACE_BYTES, (hipStream_t)stream, nullptr, 1, 0, 0,
-                      e->ws_bytes <= QASR_STATIC_WORKSPACE_BYTES);
+  ForwardHow how;
+  how.split = e->ws_bytes <= QASR_STATIC_WORKSPACE_BYTES;
+  return forward_impl(e, x, y, ws, QASR_STATIC_WORKSPACE_BYTES, (hipStream_t)stream, how);
 }
 
 qasr_status qasr_encoder_forward_layerwise(const qasr_encoder* e, const int8_t* x, int8_t* y, void* workspace,
                                            size_t workspace_bytes, void* stream) {
-  return forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, nullptr, 0);
+  ForwardHow how;
+  how.team = 0;
+  how.pairs = false;
+  return forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, how);
 }
 
 qasr_status qasr_encoder_team_check(const qasr_encoder* e, int32_t* aborted) {
@@ -1059,7 +1104,9 @@ qasr_status qasr_encoder_forward_team_stamps(const qasr_encoder* e, const int8_t
   if (!e || !op_us) return QASR_ERR_NULL;
   const size_t n = e->ops.size();
   for (size_t i = 0; i < n; ++i) op_us[i] = 0.f;
-  qasr_status st = forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, nullptr, 2);
+  ForwardHow how;
+  how.team = 2;
+  qasr_status st = forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, how);
   if (st != QASR_OK) return st;
   if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return QASR_ERR_HIP;
   std::vector<unsigned long long> stamp(qasr::kTeamMaxStamps);
@@ -1099,8 +1146,12 @@ qasr_status qasr_encoder_forward_f32(const qasr_encoder* e, const float* x, floa
     if (st == QASR_OK)
       st = hip_status(qasr::launch_quantize_rows(x, e->in_rows, e->in_T, alpha, alpha / 127.0f, xq, e->in_T + xpad, st_));
   }
-  if (st == QASR_OK)
-    st = forward_impl(e, xq, yq, workspace, e->ws_bytes ? e->ws_bytes : workspace_bytes, st_, nullptr, 1, xpad, ypad);
+  if (st == QASR_OK) {
+    ForwardHow how;
+    how.xpad = xpad;
+    how.ypad = ypad;
+    st = forward_impl(e, xq, yq, workspace, e->ws_bytes ? e->ws_bytes : workspace_bytes, st_, how);
+  }
   if (st != QASR_OK) return st;
   if (ypad == 0) return qasr_dequantize(yq, (size_t)e->out_rows * e->out_T, S_out, y, stream);
   if (!std::isfinite(S_out)) return QASR_ERR_PARAM;
@@ -1120,22 +1171,33 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
     if (hipEventCreate(&cal[i]) != hipSuccess) st = QASR_ERR_HIP;
   // An event record between two kernels costs device time of its own.  The same forward is run
   // once without inner events (bracketed by two) and once with them; the difference of the two
-  // totals, spread evenly, is taken off every op's interval, so that the op times add up to the
-  // duration of the undisturbed forward.
+  // totals, spread evenly over the launches, is taken off every launch's interval, so that the times add
+  // up to the duration of the undisturbed forward.
+  std::vector<char> began(n + 1, 0);
+  ForwardHow plain_how, how;
+  plain_how.team = how.team = 0;
+  how.ev = ev.data();
+  how.began = began.data();
   if (st == QASR_OK && hipEventRecord(cal[0], (hipStream_t)stream) != hipSuccess) st = QASR_ERR_HIP;
-  if (st == QASR_OK) st = forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, nullptr, 0);
+  if (st == QASR_OK) st = forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, plain_how);
   if (st == QASR_OK && hipEventRecord(cal[1], (hipStream_t)stream) != hipSuccess) st = QASR_ERR_HIP;
-  if (st == QASR_OK) st = forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, ev.data());
+  if (st == QASR_OK) st = forward_impl(e, x, y, workspace, workspace_bytes, (hipStream_t)stream, how);
   if (st == QASR_OK && hipEventSynchronize(ev[n]) != hipSuccess) st = QASR_ERR_HIP;
   float per_event_ms = 0.f;
-  if (st == QASR_OK && n > 0) {
+  if (st == QASR_OK) {
     float plain = 0.f, evented = 0.f;
     if (hipEventElapsedTime(&plain, cal[0], cal[1]) != hipSuccess || hipEventElapsedTime(&evented, ev[0], ev[n]) != hipSuccess)
       st = QASR_ERR_HIP;
-    per_event_ms = evented > plain ? (evented - plain) / (float)n : 0.f;
+    const size_t launches = (size_t)std::count(began.begin(), began.end(), 1);
+    per_event_ms = evented > plain ? (evented - plain) / (float)launches : 0.f;
   }
+  began[n] = 1;
   for (size_t i = 0; i < n && st == QASR_OK; ++i) {
-    if (hipEventElapsedTime(&op_ms[i], ev[i], ev[i + 1]) != hipSuccess) st = QASR_ERR_HIP;
+    op_ms[i] = 0.f;
+    if (!began[i]) continue;                      // (part of the launch before)
+    size_t next = i + 1;
+    while (!began[next]) ++next;
+    if (hipEventElapsedTime(&op_ms[i], ev[i], ev[next]) != hipSuccess) st = QASR_ERR_HIP;
     op_ms[i] = op_ms[i] > per_event_ms ? op_ms[i] - per_event_ms : 0.f;
   }
   for (hipEvent_t v : cal)
@@ -1167,13 +1229,13 @@ qasr_status qasr_encoder_graph_create(const qasr_encoder* e, const int8_t* x, in
   hipGraphExec_t exec = nullptr;
   // One ordinary forward first: argument checks, and the one-time per-kernel set-up (attribute
   // calls) that must not happen while the stream is capturing.
-  qasr_status st = forward_impl(e, x, y, workspace, workspace_bytes, cap, nullptr);
+  qasr_status st = forward_impl(e, x, y, workspace, workspace_bytes, cap);
   if (st == QASR_OK && hipStreamSynchronize(cap) != hipSuccess) st = QASR_ERR_HIP;
   if (st == QASR_OK) {
     if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
       st = QASR_ERR_HIP;
     } else {
-      st = forward_impl(e, x, y, workspace, workspace_bytes, cap, nullptr);
+      st = forward_impl(e, x, y, workspace, workspace_bytes, cap);
       const hipError_t ee = hipStreamEndCapture(cap, &graph);      // always ends the capture
       if (st == QASR_OK && (ee != hipSuccess || !graph)) st = QASR_ERR_HIP;
     }
@@ -1198,7 +1260,7 @@ qasr_status qasr_encoder_graph_create(const qasr_encoder* e, const int8_t* x, in
 
 qasr_status qasr_encoder_graph_launch(qasr_encoder_graph* g, void* stream) {
   if (!g) return QASR_ERR_NULL;
-  if (!g->exec) return forward_impl(g->e, g->x, g->y, g->workspace, g->workspace_bytes, (hipStream_t)stream, nullptr);
+  if (!g->exec) return forward_impl(g->e, g->x, g->y, g->workspace, g->workspace_bytes, (hipStream_t)stream);
   const hipError_t e = hipGraphLaunch(g->exec, (hipStream_t)stream);
   return e == hipSuccess ? QASR_OK : hip_status(e);
 }

@@ -57,6 +57,12 @@ def test_split_contraction(B, T, tile, tuning_env):
     net, params, x, ref = jasper_dr_case(B, T)
     g = GpuNet(net, params)
     assert "conv_pipe" in g.kernels()
+    if tile:                                         # (the forced number of splits has its room in the workspace)
+        tuning_env("QASR_CP_TILE", ",".join(tile.split(",")[:3] + ["1"]))
+        whole = GpuNet(net, params)
+        assert g.enc.workspace_bytes > whole.enc.workspace_bytes
+        whole.enc.close()
+        tuning_env("QASR_CP_TILE", tile)
     for _ in range(3):                               # (each forward finds the counters the last one left)
         assert np.array_equal(g.forward(dev(x)).cpu().numpy(), ref)
     g.check_guards()

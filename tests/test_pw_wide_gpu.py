@@ -3,14 +3,24 @@ channels, residual, both clamps, the 64-bit rescale, batch strides, an activatio
 its widths."""
 import pytest
 
+import paper_2103_16827_amd as Q
 import qasr_workloads as W
-from gpu_util import dev, GpuNet
+from gpu_util import desc_of, dev, GpuNet
 from qasr_workloads.nets import _Builder
 import numpy as np
 import oracle
 from test_gpu_parity import layer_case, run_layer_case
 
 pytestmark = pytest.mark.gpu
+
+
+def run_wide(case, extra=None):
+    op, _, x, _, _ = case
+    d = desc_of(op, x.shape[0], Q.FLAG_W_PACKED)
+    d.y_batch_stride = 0 if extra is None else op.Cout * op.Tout + extra
+    assert Q.conv1d_launch_name(d) == "pw_wide"
+    run_layer_case(case, extra)
+
 
 TILES = ["1,1", "2,1", "4,1", "7,1", "1,2", "2,2", "4,2", "7,2", "1,4", "2,4", "4,4", "1,8", "2,8", "4,8"]
 SHAPES = [
@@ -29,7 +39,7 @@ def test_tiles(kw, tile, tuning_env):
     tuning_env("QASR_PW_WIDE", "1")
     tuning_env("QASR_PWW", tile)
     print(f"[case] tile {tile}", flush=True)
-    assert run_layer_case(layer_case(**kw)) in ("gemm_mfma", "pw_pipe", "pw_tile")
+    run_wide(layer_case(**kw))
 
 
 @pytest.mark.parametrize("extra", [16, 4])
@@ -39,7 +49,7 @@ def test_tiles(kw, tile, tuning_env):
                                 dict(name="w512_T1", B=3, Cin=512, Cout=512, T=1601, packed=True)], ids=lambda k: k["name"])
 def test_edges_and_batch_strides(kw, extra, tuning_env):
     tuning_env("QASR_PW_WIDE", "1")
-    run_layer_case(layer_case(**kw), extra)
+    run_wide(layer_case(**kw), extra)
 
 
 @pytest.mark.parametrize("T", [80, 61])
@@ -53,7 +63,8 @@ def test_activation_table(T, tuning_env):
     params = W.draw_net_params(net, 2)
     x = W.draw_input(net, 2)
     g = GpuNet(net, params)
-    print(f"[case] activations in pw_wide, kernels {g.kernels()}", flush=True)
+    print(f"[case] activations in pw_wide, kernels {[g.enc.op_launch(i) for i in range(3)]}", flush=True)
+    assert [g.enc.op_launch(i) for i in range(3)] == [(i, "pw_wide") for i in range(3)]
     assert [g.enc.op_act_fused(i) for i in range(3)] == [True, True, True]
     assert np.array_equal(g.forward(dev(x)).cpu().numpy(), oracle.encoder_forward(net, params, x))
     g.check_guards()
