@@ -17,6 +17,7 @@
 // LDS: row = input channel, TW units of 16 frames, unit u in slot u ^ swizzle(row) so that the 8 rows a
 // transposing read touches lie in different banks (see pw_tile.hip for the operand layout).
 #include "kernels.hpp"
+#include "launch_shape.hpp"
 #include "tuning.hpp"
 
 #include <type_traits>
@@ -356,7 +357,7 @@ bool pick(const ConvParams& p, int cus, Choice& best, double& us) {
     if ((tuning().pww_mt && c.MT != tuning().pww_mt) || (tuning().pww_ks && c.KS != tuning().pww_ks)) continue;
     if (c.KS > kch || (p.Cin * TW + 1023) / 1024 > kMaxLoads || lds_bytes(p, c) > 160 * 1024) continue;
     const int64_t splits = (p.Cout + nch - 1) / nch, wgs = (G + c.MT - 1) / c.MT * splits;
-    if (wgs > 0x3fffffff) continue;
+    if (wgs > max_workgroups(1024)) continue;       // (the other families' tiles cover more frames per thread)
     const int steps = (kch + c.KS - 1) / c.KS;
     const double mfma = c.MT * c.NT * steps * 17.7 * 4, lds = 16.0 * c.MT * steps * 8;
     const double l1 = 16.0 * c.NT * steps * 16 + p.Cin * 16.0 * c.MT / 64;

@@ -1,5 +1,6 @@
 // Planning and launching of the fused separable module (sep_body.hpp), and the weight image its depthwise
 // half multiplies with.
+#include "launch_shape.hpp"
 #include "sep_body.hpp"
 #include "tuning.hpp"
 
@@ -72,7 +73,7 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
       if (lds > 160 * 1024) continue;
       const int splits = q.Cout / (256 * NT);
       const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
-      if (wgs > 0x3fffffff) continue;
+      if (wgs > max_workgroups(64 * sep::kWaves)) continue;
       const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 4;
       const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 16.0 * c.KCH * 1024 + c.KCH * 64.0 * units * 16;
       const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
