@@ -67,6 +67,27 @@ __device__ __forceinline__ uint32_t load_row_u32(const int8_t* row, int t, int T
   const int tl = min(t, T - 4);
   return load_u32(row + tl) >> (8 * (t - tl));
 }
+// The same for 16 bytes (a row may be the last thing in its allocation: only its own bytes are touched).
+typedef int __attribute__((ext_vector_type(4), aligned(1), may_alias)) unaligned_chunk16;
+__device__ __forceinline__ chunk16 load_row16(const int8_t* row, int t, int T) {
+  if (t + 16 <= T) return *reinterpret_cast<const unaligned_chunk16*>(row + t);
+  chunk16 v;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) v[d] = t + 4 * d < T ? (int)load_row_u32(row, t + 4 * d, T) : 0;
+  return v;
+}
+__device__ __forceinline__ void store_row16(int8_t* row, int t, int T, chunk16 v) {
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const int td = t + 4 * d;
+    if (td + 4 <= T) store_u32(row + td, (uint32_t)v[d]);
+    if (td + 4 > T && td < T) {
+      row[td] = (int8_t)v[d];
+      if (td + 1 < T) row[td + 1] = (int8_t)(v[d] >> 8);
+      if (td + 2 < T) row[td + 2] = (int8_t)(v[d] >> 16);
+    }
+  }
+}
 // bytes [t, min(t + 4, T)) of a row
 __device__ __forceinline__ void store_row_u32(int8_t* row, int t, int T, uint32_t v) {
   if (t + 4 <= T) {
@@ -143,6 +164,20 @@ inline hipError_t ensure_max_dynamic_lds(const void* kernel, std::atomic<uint64_
   const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
   return e;
+}
+
+// Compute units of the current device, asked once per device (256, the whole chip's, if it cannot be asked).
+inline int compute_units() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> units[kDevices];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return 256;
+  int n = units[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    units[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
 }
 
 __device__ __forceinline__ int32_t clamp_i8(int32_t v, int32_t lo) {

@@ -56,19 +56,6 @@ struct Choice { int MT, KCH, splits; bool lean; };
 
 size_t lds_bytes(int KCH) { return KCH == 4 ? lds_bytes_c<4>() : lds_bytes_c<8>(); }   // (8 chunks at most are resident)
 
-int num_cus() {
-  static int n = 0;
-  if (!n) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      n = v;
-    else
-      n = 256;
-  }
-  return n;
-}
-
 // Shape-only part of the choice (no device query: usable without a GPU).
 bool pick(const ConvParams& p, Choice& c, int cus) {
   if (tuning().no_pw_pipe) return false;                  // tuning: fall through to the other kernels
@@ -180,7 +167,7 @@ bool pw_pipe_supported(const ConvParams& p) {
 
 hipError_t launch_pw_pipe(const ConvParams& p, hipStream_t st) {
   Choice c;
-  if (!pick(p, c, num_cus())) return hipErrorInvalidValue;
+  if (!pick(p, c, compute_units())) return hipErrorInvalidValue;
 #define QASR_CASE(M, K) if (c.lean && c.MT == M && c.KCH == K) return launch_lean<M, K>(p, st);
   QASR_CASE(4, 4) QASR_CASE(5, 4) QASR_CASE(6, 4) QASR_CASE(7, 4)
   QASR_CASE(4, 8) QASR_CASE(5, 8) QASR_CASE(6, 8) QASR_CASE(7, 8)

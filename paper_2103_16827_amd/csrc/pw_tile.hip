@@ -272,19 +272,6 @@ struct Choice { int MT, NT; };
 // activation tile + per-wave staging + per-wave park space for m and s
 size_t lds_bytes(const ConvParams& p, int NT) { return (size_t)p.Cin * 128 + (size_t)8 * 16 * NT * 128 + (size_t)8 * 2 * NT * 64 * 4; }
 
-int num_cus() {
-  static int n = 0;
-  if (!n) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      n = v;
-    else
-      n = 256;
-  }
-  return n;
-}
-
 // Shape-only part of the choice (no device query: usable without a GPU).
 bool pick(const ConvParams& p, Choice& c, int cus) {
   if (p.Tin % 16) return false;
@@ -339,7 +326,7 @@ bool pw_tile_supported(const ConvParams& p) {
 
 hipError_t launch_pw_tile(const ConvParams& p, hipStream_t st) {
   Choice c;
-  if (!pw_tile_supported(p) || !pick(p, c, num_cus())) return hipErrorInvalidValue;
+  if (!pw_tile_supported(p) || !pick(p, c, compute_units())) return hipErrorInvalidValue;
 #define QASR_CASE(M, N) if (c.MT == M && c.NT == N) return launch_t<M, N>(p, st);
   QASR_CASE(4, 1) QASR_CASE(4, 2) QASR_CASE(4, 4)
   QASR_CASE(5, 1) QASR_CASE(5, 2) QASR_CASE(5, 4)

@@ -28,7 +28,6 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-typedef int unaligned_v4i __attribute__((ext_vector_type(4), aligned(1), may_alias));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kStoreThrough = 17;    // sc0 sc1: the output rows are written through (see pw_pipe_body.hpp)
@@ -54,27 +53,6 @@ __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
 // the same banks every fourth row
 template <int TW>
 __host__ __device__ constexpr int swizzle(int row) { return TW == 8 ? row & 7 : (row >> 2) & 3; }
-
-// 16 frames of a row of T >= 4 at any byte address; frames past the end are 0 and are not touched
-__device__ __forceinline__ v4i load_piece(const int8_t* row, int t, int T) {
-  if (t + 16 <= T) return *reinterpret_cast<const unaligned_v4i*>(row + t);
-  v4i v;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) v[d] = t + 4 * d < T ? (int)load_row_u32(row, t + 4 * d, T) : 0;
-  return v;
-}
-__device__ __forceinline__ void store_piece(int8_t* row, int t, int T, v4i v) {
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const int td = t + 4 * d;
-    if (td + 4 <= T) store_u32(row + td, (uint32_t)v[d]);
-    if (td + 4 > T && td < T) {
-      row[td] = (int8_t)v[d];
-      if (td + 1 < T) row[td + 1] = (int8_t)(v[d] >> 8);
-      if (td + 2 < T) row[td + 2] = (int8_t)(v[d] >> 16);
-    }
-  }
-}
 
 // RAGGED: rows of x, y or the residual that are not padded to whole 16-byte aligned units
 template <int MT, int NT, int KS, bool RAGGED>
@@ -106,7 +84,7 @@ __global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) 
       const int row = tid / TW + i * (1024 / TW);
       if (i < n && on && row < p.Cin) {
         const int8_t* const s = src + (int64_t)i * (1024 / TW) * xpitch;
-        r[i] = RAGGED ? load_piece(s, t, p.Tin) : *reinterpret_cast<const v4i*>(s + t);
+        r[i] = RAGGED ? load_row16(s, t, p.Tin) : *reinterpret_cast<const v4i*>(s + t);
       }
     }
     if (p.act_lut && tid < 64)
@@ -222,7 +200,7 @@ __global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) 
       uint32_t at;
       if (piece(it, at, t)) {
         const int8_t* const r = p.res + ybase + at;
-        rr[it] = RAGGED ? load_piece(r, t, p.Tout) : *reinterpret_cast<const v4i*>(r + t);
+        rr[it] = RAGGED ? load_row16(r, t, p.Tout) : *reinterpret_cast<const v4i*>(r + t);
       }
     }
   }
@@ -309,7 +287,7 @@ __global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) 
     const bool ok = piece(it, at, t);
     const v4i o = *reinterpret_cast<const v4i*>(stage + (wave * RPW + it * RPI) * (16 * TW) + lane * 16);
     if (RAGGED) {
-      if (ok) store_piece(p.y + ybase + at, t, p.Tout, o);
+      if (ok) store_row16(p.y + ybase + at, t, p.Tout, o);
     } else {
       const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};
       __builtin_amdgcn_raw_buffer_store_b128(ov, yrs, ok ? at + (uint32_t)t : 0xfffffff0u, 0, kStoreThrough);
@@ -369,18 +347,6 @@ bool pick(const ConvParams& p, int cus, Choice& best, double& us) {
   return us < 1e300;
 }
 
-int num_cus() {
-  static int n = 0;
-  if (!n) {
-    int dev = 0, v = 0;
-    n = hipGetDevice(&dev) == hipSuccess &&
-                hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0
-            ? v
-            : 256;
-  }
-  return n;
-}
-
 template <int MT, int NT, int KS, bool RAGGED>
 hipError_t launch_t(const ConvParams& p, hipStream_t st) {
   const Choice c{MT, NT, KS};
@@ -436,7 +402,7 @@ bool pw_wide_better(const ConvParams& p, bool pipe) {
 hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st) {
   Choice c;
   double t;
-  if (!pick(p, num_cus(), c, t)) return hipErrorInvalidValue;
+  if (!pick(p, compute_units(), c, t)) return hipErrorInvalidValue;
   const bool ragged = ragged_rows(p);
 #define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KS == K) return ragged ? launch_t<M, N, K, true>(p, st) : launch_t<M, N, K, false>(p, st);
   QASR_CASE(1, 2, 1) QASR_CASE(2, 2, 1) QASR_CASE(4, 2, 1) QASR_CASE(7, 2, 1)

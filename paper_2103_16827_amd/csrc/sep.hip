@@ -85,18 +85,6 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
   return best < 1e300;
 }
 
-int num_cus() {
-  static int n = 0;
-  if (!n) {
-    int dev = 0, v = 0;
-    n = hipGetDevice(&dev) == hipSuccess &&
-                hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0
-            ? v
-            : 256;
-  }
-  return n;
-}
-
 bool plan(const ConvParams& d, const ConvParams& q, int cus, Geometry& g, SepChoice& c) {
   if (tuning().no_sep || !geometry(d, g)) return false;
   if (d.Cout != 256 && d.Cout != 512) return false;
@@ -134,7 +122,7 @@ hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st) 
 hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, hipStream_t st) {
   Geometry g;
   SepChoice c;
-  if (!plan(d, q, num_cus(), g, c)) return hipErrorInvalidValue;
+  if (!plan(d, q, compute_units(), g, c)) return hipErrorInvalidValue;
   SepParams p{};
   p.x = d.x; p.img = img; p.dbias = d.bias; p.dm = d.m; p.ds = d.s; p.lut = d.act_lut;
   p.xbs = d.xbs; p.xpitch = d.Tin + d.xpad; p.Tin = d.Tin;

@@ -50,29 +50,6 @@ __host__ __device__ inline int row_bytes(int units, int MT, int NA) {
   return ((rows > 2048 ? rows : 2048) + 15) & ~15;
 }
 
-typedef int unaligned_v4i __attribute__((ext_vector_type(4), aligned(1), may_alias));
-
-// 16 frames of a row of T (4 <= T), at any byte address; frames past the end are 0.  (A row may be the
-// last thing in its allocation: only its own bytes are read and written.)
-__device__ __forceinline__ v4i load_chunk(const int8_t* row, int t, int T) {
-  v4i v;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) v[d] = t + 4 * d < T ? (int)load_row_u32(row, t + 4 * d, T) : 0;
-  return v;
-}
-__device__ __forceinline__ void store_chunk(int8_t* row, int t, int T, v4i v) {
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const int td = t + 4 * d;
-    if (td + 4 <= T) store_u32(row + td, (uint32_t)v[d]);
-    if (td + 4 > T && td < T) {
-      row[td] = (int8_t)v[d];
-      if (td + 1 < T) row[td + 1] = (int8_t)(v[d] >> 8);
-      if (td + 2 < T) row[td + 2] = (int8_t)(v[d] >> 16);
-    }
-  }
-}
-
 // RAGGED: x or y (and the residual) are the caller's, rows of any length at any address
 template <int KCH, int MT, int NA, int NT, bool RAGGED>
 __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
@@ -117,8 +94,8 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     for (int j = 0; j < 4; ++j) {
       xr[j] = (v4i){0, 0, 0, 0};
       if (in & (1u << j)) {
-        if (RAGGED && (last & (1u << j))) xr[j] = load_chunk(src + xoff[j] - t_last, t_last, p.Tin);
-        else xr[j] = *reinterpret_cast<const unaligned_v4i*>(src + xoff[j]);
+        if (RAGGED && (last & (1u << j))) xr[j] = load_row16(src + xoff[j] - t_last, t_last, p.Tin);
+        else xr[j] = *reinterpret_cast<const unaligned_chunk16*>(src + xoff[j]);
       }
     }
   };
@@ -237,7 +214,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int8_t* const row = p.res + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch;
-        if (u_ok) rr[nt][h] = RAGGED && p.yragged ? load_chunk(row, t_l, p.Tout) : *reinterpret_cast<const v4i*>(row + t_l);
+        if (u_ok) rr[nt][h] = RAGGED && p.yragged ? load_row16(row, t_l, p.Tout) : *reinterpret_cast<const v4i*>(row + t_l);
       }
   };
   __syncthreads();                                  // the tile is complete
@@ -305,7 +282,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       for (int h = 0; h < 2; ++h) {
         const v4i o = *reinterpret_cast<const v4i*>(st + 1024 * h + 16 * lane);
         if (RAGGED && p.yragged) {                  // (uniform)
-          if (u_ok) store_chunk(p.y + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch, t_l, p.Tout, o);
+          if (u_ok) store_row16(p.y + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch, t_l, p.Tout, o);
           continue;
         }
         const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};

@@ -1,4 +1,4 @@
-// Instantiations of the fused separable module for 9 to 12 four-tap steps.
+// Instantiations of the fused separable module for 1 to 12 four-tap steps.
 #include "sep_body.hpp"
 
 namespace qasr {
