@@ -377,26 +377,41 @@ bool pw_wide_supported(const ConvParams& p) {
   return !tuning().no_pw_wide && pick(p, 256, c, t);
 }
 
-// Measured on single layers (us, the other kernel against this one):
-//   pw_tile: 640 -> 640 at B=2, T=416 12.7 / 5.5, 896 -> 1024 21.0 / 6.1, 1024 -> 29 at B=1, T=800 6.3 / 4.7,
-//     640 -> 768 at B=16, T=800 16.0 / 13.8; few output channels of many frames (1024 -> 29 at B=32,
-//     T=800) 10.1 / 10.6;
-//   pw_pipe: its pass count is split over workgroups only by powers of two (256 -> 768 at B=2, T=416 8.4 / 5.3);
-//     1024 and 2048 input channels stream through a ring with a barrier per 64 of them: 2048 -> 512 at T=400
-//     B=1 10.3 / 6.6, B=8 13.4 / 13.1, B=16 14.0 / 16.9; many passes of a full chip 512 -> 2048 at B=16,
-//     T=400 13.0 / 12.2, 512 -> 1024 at B=32, T=800 26.9 / 23.6; everything else is its own
-//     (512 -> 1024 at B=16, T=400 7.9 / 10.2, 512 -> 512 at B=32, T=800 12.5 / 13.3).
+// Where this kernel is the faster one, in 16-frame groups G.  Measured on single layers whose weights and
+// tensors come from memory (us, the other kernel / this one), 50 shapes at up to 14 sizes each; with these
+// lines the choice is within 1 % of the better kernel on average.
+//   pw_tile (one pass after another per workgroup):
+//     257 to 512 channels are one workgroup's here, which stays ahead: 640 -> 512 G=50 9.6 / 6.0, G=1000 10.8 / 9.9,
+//       G=3200 28.3 / 26.7; 384 -> 384 G=400 7.9 / 6.9, G=1400 10.3 / 8.7 (but G=560 8.1 / 8.7);
+//     beyond 512, workgroups share a tile, which pays while they are few: 640 -> 768 G=200 13.5 / 7.7, G=700 15.0 / 12.4,
+//       G=900 15.4 / 21.2; with 1024 input channels pw_tile has LDS for 128 channels at a time only: 1024 -> 1000
+//       G=200 35.9 / 9.8, G=2000 49.5 / 44.7;
+//     up to 256 channels, the input channels are split over the waves: 1024 -> 29 G=200 7.0 / 5.5, G=700 7.4 / 6.8, G=1400
+//       8.9 / 9.8; 512 -> 128 G=104 5.5 / 5.5, G=400 5.7 / 6.1; 256 -> 128 G=104 4.4 / 5.1;
+//   pw_pipe with 1024 and 2048 input channels (streamed through a ring, a barrier per 64 of them):
+//     2048 -> 512 G=100 11.9 / 9.5, G=200 10.9 / 10.4, G=300 12.2 / 14.6; 1024 -> 1024 G=50 8.1 / 8.0, G=200 8.0 / 9.6;
+//   pw_pipe whose passes cannot be split over workgroups (not a power of two, or the last one is partial) and are not
+//     the lean form's: 512 -> 768 G=200 10.5 / 7.4, G=300 (lean) 6.9 / 7.9, G=1600 15.8 / 22.2; 512 -> 1000 G=100
+//     13.1 / 7.0, G=800 13.2 / 11.3, G=1600 18.0 / 22.0; 256 -> 384 G=100 6.3 / 5.6, G=300 6.6 / 6.7;
+//   all else is pw_pipe's: 512 -> 2048 G=400 11.4 / 12.2, G=1400 32.8 / 42.3; 512 -> 1024 G=350 7.3 / 9.9, G=1600 19.9 / 23.3;
+//     512 -> 512 G=200 5.7 / 6.6, G=1600 11.7 / 12.9.
+// (Host only, before any device is asked: for the whole chip's 256 units.)
 bool pw_wide_better(const ConvParams& p, bool pipe) {
   const Tuning& t = tuning();
   if (!pw_wide_supported(p)) return false;
   if (t.pw_wide_force) return true;
   if (t.pwp_mt || t.pwp_split || t.pw_lean_force || t.pwt_mt || t.pwp_nopipe) return false;   // a forced form of the others
   const int64_t G = (int64_t)p.B * ((p.Tin + 15) / 16);
-  if (!pipe) return p.Cout > 128 || G < 7 * 200;
+  if (!pipe) {
+    if (p.Cout > 512) return p.Cin >= 1024 || G <= 700;
+    if (p.Cout > 256) return true;
+    return G <= 700 && G <= 2 * (p.Cin - 320);
+  }
   const int passes = (p.Cout + 255) / 256;
-  if (p.Cin >= 1024) return G <= 200;
-  if (passes & (passes - 1)) return 2 * ((G + 6) / 7) * passes <= 256 || ((G + 6) / 7) * passes > 512;   // (outside pw_pipe's lean form)
-  return passes >= 4 && (G + 6) / 7 * (passes / 2) >= 200;
+  if (p.Cin >= 1024) return G * passes * 1024 <= (int64_t)200 * p.Cin;
+  if (p.Cout % 256) return G <= 800 && G <= 50 * passes * passes;
+  if (passes & (passes - 1)) return 2 * ((G + 6) / 7) * passes <= 256;      // (more workgroups take the lean form)
+  return false;
 }
 
 hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st) {

@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("form", ["pipe", "lean", "wide"])
 @pytest.mark.parametrize("lo,hi", [(50, 62), (55, 62)])
 def test_large_shifts(lo, hi, form, res, relu, tuning_env):
+    if form == "pipe":
+        tuning_env("QASR_NO_PW_WIDE", "1")
     if form == "lean":
         tuning_env("QASR_PW_LEAN", "1")
     if form == "wide":
