@@ -206,18 +206,16 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
   int32_t mc[NT], sh[NT], rnd[NT];                // rescale constants of the pass whose epilogue is pending
 
   // one epilogue block: lane (n, gi) holds frames 16 mt + 4 gi + (0..3) of channel 16 nt + n
-  // FORM 2: short (requant_short4), 1: multiply-high, add, shift (a residual with s > 54), 0: 64 bits
-  auto block = [&](int par, int e, auto form_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
-    constexpr int FORM = decltype(form_tag)::value;
-    constexpr bool RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
+  auto block = [&](int par, int e, auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
+    constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
     const int mt = e / NT, nt = e % NT;
     uint32_t* const sp = reinterpret_cast<uint32_t*>(stage0 + (LEAN ? 0 : par * (ROWS * 128) + nt * 2048) + (sbase ^ (uint32_t)(mt << 4)));
     const uint32_t rw = !RES ? 0u : LEAN ? *reinterpret_cast<const uint32_t*>(lres0 + nt * 2048 + (sbase ^ (uint32_t)(mt << 4))) : *sp;
     const v4i av = acc[par][mt][nt];
     const int32_t a4[4] = {av[0], av[1], av[2], av[3]};
     uint32_t pk;
-    if constexpr (FORM == 2) pk = requant_short4<RES, RELU>(a4, mc[nt], sh[nt], rnd[nt], rw);
-    else pk = requant_pack4<FORM == 1, RES>(a4, mc[nt], sh[nt], rnd[nt], rw, lo, hi127);
+    if constexpr (FAST) pk = requant_short4<RES, RELU>(a4, mc[nt], sh[nt], rnd[nt], rw);
+    else pk = requant_pack4<false, RES>(a4, mc[nt], sh[nt], rnd[nt], rw, lo, hi127);
     if (has_act) {                                 // table[code + 128], byte by byte
       const uint32_t c = pk ^ 0x80808080u;
       pk = (uint32_t)lutw[c & 0xffu] | ((uint32_t)lutw[(c >> 8) & 0xffu] << 8) |
@@ -296,13 +294,13 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
   };
   constexpr int STORE_REQS = 2 * NT;              // requests of one store_rows
   // the epilogue of pass ps on its own (a relu instantiation for the short form only)
-  auto epilogue_of = [&](int ps, int par, auto form_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
+  auto epilogue_of = [&](int ps, int par, auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     if constexpr (LEAN) {
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-          block(par, mt * NT + nt, form_tag, res_tag, relu_tag);
+          block(par, mt * NT + nt, fast_tag, res_tag, relu_tag);
           if (mt & 1) __builtin_amdgcn_sched_barrier(0);      // bounds the live temporaries
         }
         store_rows_lean(ps, nt);
@@ -310,24 +308,24 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
     } else {
 #pragma unroll
       for (int e = 0; e < NB; ++e) {
-        block(par, e, form_tag, res_tag, relu_tag);
+        block(par, e, fast_tag, res_tag, relu_tag);
         if (e & 1) __builtin_amdgcn_sched_barrier(0);
       }
       store_rows(ps, par);
     }
     seq += STORE_REQS;
   };
-  auto epilogue_alone = [&](int ps, int par, auto form_tag) __attribute__((always_inline)) {
-    constexpr int FORM = decltype(form_tag)::value;
+  auto epilogue_alone = [&](int ps, int par, auto fast_tag) __attribute__((always_inline)) {
+    constexpr bool FAST = decltype(fast_tag)::value;
     const std::true_type T{};
     const std::false_type F{};
     if (has_res) {
       wait_vm_dyn(seq - mark_r[LEAN ? 0 : par]);            // residual rows of this pass
-      if (FORM == 2 && p.relu) epilogue_of(ps, par, form_tag, T, T);
-      else epilogue_of(ps, par, form_tag, T, F);
-    } else if constexpr (FORM != 1) {
-      if (FORM == 2 && p.relu) epilogue_of(ps, par, form_tag, F, T);
-      else epilogue_of(ps, par, form_tag, F, F);
+      if (FAST && p.relu) epilogue_of(ps, par, fast_tag, T, T);
+      else epilogue_of(ps, par, fast_tag, T, F);
+    } else {
+      if (FAST && p.relu) epilogue_of(ps, par, fast_tag, F, T);
+      else epilogue_of(ps, par, fast_tag, F, F);
     }
   };
 
@@ -431,14 +429,16 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
     seq += pending ? STORE_REQS : 0;      // rows of the pass before, stored at the end of the loop
     // rescale constants of this pass
     const unsigned char* c = cst0 + ps * (NT * 3 * 64) + 4 * n;
-    bool fast = true, narrow = true;
+    // (the pipelined epilogue adds a residual after the shift, the one on its own before it)
+    const bool pipelined = p.relu && !has_act && ps + 1 < P && !g.nopipe;
+    const int s_max = has_res && !pipelined ? kShortMaxRes : kShortMax;
+    bool fast = true;
     int32_t s_[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       mc[nt] = *reinterpret_cast<const int32_t*>(c + nt * 192 + 64);
       s_[nt] = *reinterpret_cast<const int32_t*>(c + nt * 192 + 128);
-      fast = fast && s_[nt] >= kShortMin && s_[nt] <= kShortMax;
-      narrow = narrow && s_[nt] <= kShortMaxRes;
+      fast = fast && s_[nt] >= kShortMin && s_[nt] <= s_max;
     }
     const bool all_fast = __builtin_amdgcn_readfirstlane((int)__all(fast)) != 0;   // wave-uniform, and known to be
 #pragma unroll
@@ -446,13 +446,9 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
       sh[nt] = all_fast ? s_[nt] - 32 : s_[nt];
       rnd[nt] = all_fast ? 1 << ((s_[nt] - 33) & 31) : 0;
     }
-    if (all_fast && p.relu && !has_act && ps + 1 < P && !g.nopipe) {
-      pending = true;
-    } else {
-      pending = false;
-      if (!all_fast) epilogue_alone(ps, par, std::integral_constant<int, 0>{});
-      else if (has_res && !__all(narrow)) epilogue_alone(ps, par, std::integral_constant<int, 1>{});
-      else epilogue_alone(ps, par, std::integral_constant<int, 2>{});
+    pending = all_fast && pipelined;
+    if (!pending) {
+      if (all_fast) epilogue_alone(ps, par, std::true_type{}); else epilogue_alone(ps, par, std::false_type{});
     }
   };
   do_pass(0, 0, std::true_type{});
