@@ -15,6 +15,7 @@
 //    A channel whose bias leaves int32 or whose multiplier has no dyadic form with 1 <= s <= 62
 //    gets bias 0 / (m, s) = (0, 1) and is counted in *bad_count.
 #include "kernels.hpp"
+#include "launch_shape.hpp"
 
 #include <cmath>
 
@@ -127,13 +128,14 @@ typedef float row_float4 __attribute__((ext_vector_type(4), aligned(4)));   // r
 template <int QUADS>
 __global__ __launch_bounds__(kFoldThreads) void fold_quantize_kernel(
     const float* __restrict__ w, const float* __restrict__ b, const float* __restrict__ gamma, const float* __restrict__ beta,
-    const float* __restrict__ mean, const float* __restrict__ var, float eps, int64_t per, float S_x, float S_y,
+    const float* __restrict__ mean, const float* __restrict__ var, float eps, int32_t Cout, int64_t per, float S_x, float S_y,
     int8_t* __restrict__ qw, int32_t* __restrict__ bias_q, int32_t* __restrict__ m, int32_t* __restrict__ s,
     float* __restrict__ S_w, int32_t* bad_count) {
   __shared__ float sh[kFoldThreads / 64];
-  const int c = blockIdx.x;
-  const float* const wc = w + (int64_t)c * per;
-  int8_t* const qc = qw + (int64_t)c * per;
+  const int64_t c = ((int64_t)blockIdx.y << kGridShift) + blockIdx.x;
+  if (c >= Cout) return;                                // whole workgroup
+  const float* const wc = w + c * per;
+  int8_t* const qc = qw + c * per;
   const int n = (int)per;                               // (QUADS > 0 only)
   row_float4 v[QUADS > 0 ? QUADS : 1];
 #pragma unroll
@@ -209,8 +211,9 @@ template <int QUADS>
 hipError_t launch_fold(const float* w, const float* b, const float* gamma, const float* beta, const float* mean,
                        const float* var, float eps, int32_t Cout, int64_t per, float S_x, float S_y, int8_t* qw,
                        int32_t* bias_q, int32_t* m, int32_t* s, float* S_w, int32_t* bad_count, hipStream_t st) {
-  return launch_kernel(fold_quantize_kernel<QUADS>, dim3((unsigned)Cout), dim3(kFoldThreads), 0, st, w, b, gamma, beta, mean,
-                       var, eps, per, S_x, S_y, qw, bias_q, m, s, S_w, bad_count);
+  const GridShape g = grid_shape(Cout);
+  return launch_kernel(fold_quantize_kernel<QUADS>, dim3(g.x, g.y), dim3(kFoldThreads), 0, st, w, b, gamma, beta, mean,
+                       var, eps, Cout, per, S_x, S_y, qw, bias_q, m, s, S_w, bad_count);
 }
 
 }  // namespace

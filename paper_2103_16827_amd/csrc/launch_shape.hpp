@@ -7,7 +7,7 @@ namespace qasr {
 // the most workgroups of a launch along one dimension that is rounded up to a multiple of 8 (one run per XCD)
 constexpr int64_t max_workgroups(int threads) { return (0xffffffffll / threads) & ~7ll; }
 
-// A workgroup of 256 threads per unit of work, in two dimensions beyond 2^20 of them: workgroup (x, y) takes
+// A workgroup (of up to 1024 threads) per unit of work, in two dimensions beyond 2^20 of them: workgroup (x, y) takes
 // unit y 2^20 + x, those past the last unit do nothing.
 constexpr int kGridShift = 20;
 struct GridShape { uint32_t x, y; };

@@ -34,3 +34,26 @@ def test_fold_sizes(per):
     for a, b in zip((bq, m, s), ref[1:4]):
         assert np.array_equal(a.cpu().numpy(), b)
     assert np.array_equal(Sw.cpu().numpy().view(np.uint32), ref[4].view(np.uint32))
+
+
+def test_more_channels_than_one_grid_dimension():
+    """2^23 + 3 channels: a workgroup of 512 threads per channel is more than 2^32 work items along one dimension."""
+    C, per, period = (1 << 23) + 3, 4, 1 << 10
+    print(f"[case] fold C={C} per={per}", flush=True)
+    rep = -(-C // period)
+    w = torch.from_numpy(randint_array(31, (period, per), -254, 254, np.int32).astype(np.float32)).cuda()
+    gamma, beta, mean, var = (torch.from_numpy(randint_array(32 + i, (period,), 1, 99, np.int32).astype(np.float32)).cuda() for i in range(4))
+
+    def fold(n, tile):
+        t = lambda a: a.repeat(*((tile,) + (1,) * (a.dim() - 1)))[:n].contiguous()
+        q = torch.full((n, per), 99, dtype=torch.int8, device="cuda")
+        b, m, s = (torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(3))
+        Sw = torch.zeros(n, dtype=torch.float32, device="cuda")
+        Q.fold_bn_quantize(t(w), None, t(gamma), t(beta), t(mean), t(var), 1e-3, 0.02, 0.03, q, b, m, s, Sw, None)
+        torch.cuda.synchronize()
+        return q, b, m, s, Sw
+
+    small = fold(period, 1)
+    for a, b in zip(fold(C, rep), small):
+        whole = C // period * period
+        assert bool((a[:whole].view(-1, *b.shape) == b).all()) and bool((a[whole:] == b[: C - whole]).all())

@@ -16,7 +16,7 @@ int main() {
   const int64_t units[] = {1, 2, 1000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, (1ll << 30) - 1, 1ll << 30};
   for (int64_t n : units) {
     const qasr::GridShape g = qasr::grid_shape(n);
-    const unsigned long long items = 256ull * g.x;
+    const unsigned long long items = 1024ull * g.x;
     // the last workgroup of the last row, and of the row before, in the kernel's numbering
     const int64_t last = ((int64_t)(g.y - 1) << qasr::kGridShift) + g.x - 1;
     const bool whole = g.y == 1 || g.x == 1u << qasr::kGridShift;
