@@ -4,13 +4,15 @@
 A "step" is one forward of the QuartzNet-15x5-shaped encoder at batch 32, T=1600 input frames
 (benchmark config 2), on seeded synthetic int8 inputs and random int8 weights already resident
 in HBM: one launch of the forward captured as a HIP graph (qasr_encoder_graph_launch), or with
---eager the 170 separate kernel launches of qasr_encoder_forward.  Prints ONE JSON line:
+--eager the separate kernel launches of qasr_encoder_forward.  Prints ONE JSON line:
 
   value       input frames per second (B*T_in*steps / wall time of the timed steps)
-  roofline    for the kernel family with the largest share of device time, measured live with
-              HIP events around every op (a separate, untimed-for-`value` pass)
-  stages      spec view: depthwise stages against HBM peak, pointwise stages against the
-              int8 MFMA peak (algorithmic bytes / MACs over summed per-op device time)
+  roofline    for the kernel with the largest share of device time, measured live with HIP events
+              around every launch of the forward (a separate, untimed-for-`value` pass); a depthwise and
+              a pointwise layer that run as one launch count as one, without the tensor between them
+  stages      the launches by what they compute (pairs of a depthwise and a pointwise layer, either
+              alone, dense layers) against the HBM and the int8 MFMA peak (algorithmic bytes / MACs over
+              summed device time)
   step_ms     mean / median / min / max of the timed steps, each bracketed by HIP events
   ceilings    what this chip sustained in this process: a streaming int8 copy and a register-resident
               int8 matrix-core loop; every fraction is given against the datasheet and against these
@@ -45,16 +47,25 @@ def op_algorithmic(op, B):
     return byts, op.macs(B)
 
 
-def measured_traffic(kernel, config):
-    """HBM bytes per launch of `kernel` on this configuration as the hardware counters saw them
-    (FETCH_SIZE + WRITE_SIZE, calibrated against a plain copy of known size): read from the committed
-    counter summary profiles/<kernel>_config<N>_hbm_traffic.txt, whose header gives the commands
-    that produced it; None when there is no such summary."""
-    path = os.path.join(ROOT, "profiles", f"{kernel}_config{config}_hbm_traffic.txt")
+def launch_algorithmic(ops, B):
+    """The same of one launch: of a depthwise + pointwise pair, the tensor between the two is neither
+    written nor read."""
+    byts, macs = (sum(v) for v in zip(*(op_algorithmic(o, B) for o in ops)))
+    for a, b in zip(ops, ops[1:]):
+        byts -= B * a.Cout * a.Tout + B * b.Cin * b.Tin
+    return byts, macs
+
+
+def measured(what, kernel, config):
+    """A figure of `kernel` on this configuration as the hardware counters saw it, from the committed summary
+    profiles/encoder_config<N>_counters.txt (its header gives the commands that produced it); None
+    without one.  "traffic_bytes_per_launch": FETCH_SIZE + WRITE_SIZE, calibrated against a plain copy of
+    known size; "mfma_busy": fraction of the launches' duration in which the matrix pipes were busy."""
+    path = os.path.join(ROOT, "profiles", f"encoder_config{config}_counters.txt")
     try:
         with open(path) as f:
             for line in f:
-                if line.startswith("traffic_bytes_per_launch:"):
+                if line.startswith(f"{what} {kernel}:"):
                     return float(line.split(":", 1)[1])
     except OSError:
         pass
@@ -92,20 +103,6 @@ def cpu_1thread(config, max_seconds):
     return json.loads(r.stdout.strip().splitlines()[-1])
 
 
-def measured_mfma_busy(kernel, config):
-    """Fraction of the kernels' duration in which the matrix pipes were busy, by the hardware counters
-    (profiles/<kernel>_config<N>_mfma_busy.txt, whose header gives the commands); None without one."""
-    path = os.path.join(ROOT, "profiles", f"{kernel}_config{config}_mfma_busy.txt")
-    try:
-        with open(path) as f:
-            for line in f:
-                if line.startswith(f"mfma_busy_{kernel}:"):
-                    return float(line.split(":", 1)[1])
-    except OSError:
-        pass
-    return None
-
-
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -116,7 +113,7 @@ def main():
     ap.add_argument("--seed", type=int, default=1)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--eager", action="store_true", help="time separate kernel launches instead of the HIP graph")
-    ap.add_argument("--profile-passes", type=int, default=5, help="per-op timed passes for the roofline")
+    ap.add_argument("--profile-passes", type=int, default=5, help="timed passes for the roofline")
     ap.add_argument("--softmax", default="", metavar="ROWS,LEN",
                     help="also run 12 qasr_softmax_int32 calls on seeded int32 logits of this shape (for profiler runs)")
     ap.add_argument("--observer-mib", type=int, default=0,
@@ -169,7 +166,7 @@ def main():
     torch.cuda.synchronize()
 
     # The timed step: one launch of the forward captured as a HIP graph (qasr_encoder_graph_*),
-    # unless --eager asks for qasr_encoder_forward's n_ops separate launches.
+    # unless --eager asks for qasr_encoder_forward's separate launches.
     graph = None if args.eager else enc.graph(x, y, ws)
     step = (lambda: enc.forward(x, y, ws)) if args.eager else graph.launch
 
@@ -229,14 +226,19 @@ def main():
     torch.cuda.empty_cache()
     # the other launch mode, for comparison (not the reported value)
     other_ms = None if args.eager else timed(lambda: enc.forward(x, y, ws), 3, max(5, args.steps // 5))[0]
-    # The launch floor of this op list: a graph of as many dependent one-element kernels as the
-    # forward has ops (nothing to compute or move), replayed the same way.  What the step costs
+    # What one launch of the forward computes, and with which kernel
+    first = [enc.op_launch(i) for i in range(enc.n_ops)]
+    launches = [(i, first[i][1], [j for j in range(i, enc.n_ops) if first[j][0] == i])
+                for i in range(enc.n_ops) if first[i][0] == i]
+    # The launch floor: a graph of as many dependent one-element kernels as the forward launches (nothing
+    # to compute or move; separate activation passes too), replayed the same way.  What the step costs
     # beyond it is what the layers' own work costs.
     floor_ms = None
-    if not args.eager:
+    n_launch = len(launches) + sum(1 for _, _, ops_ in launches for j in ops_
+                                   if "act" in params[j] and len(ops_) == 1 and not enc.op_act_fused(j))
+    if not args.eager and n_launch > 4:              # (fewer are not replayed as a graph)
         one_q = torch.zeros(1, dtype=torch.int8, device="cuda")
         one_x = torch.zeros(1, dtype=torch.float32, device="cuda")
-        n_launch = enc.n_ops + sum(1 for p in params if "act" in p)
         side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(side):
@@ -282,22 +284,22 @@ def main():
         torch.cuda.synchronize()
         del a, b
 
-    # ---- per-op device time (HIP events on the launch stream, inside the library)
-    kernels = [enc.op_kernel(i) for i in range(enc.n_ops)]
+    # ---- device time per launch (HIP events on the launch stream, inside the library)
     acc_ms = np.zeros(enc.n_ops)
     for _ in range(max(1, args.profile_passes)):
         acc_ms += np.array(enc.forward_timed(x, y, ws))
     op_ms = acc_ms / max(1, args.profile_passes)
 
     fam = {}
-    for i, (o, k) in enumerate(zip(net.ops, kernels)):
-        byts, macs = op_algorithmic(o, net.B)
+    for i, k, ops_ in launches:
+        byts, macs = launch_algorithmic([net.ops[j] for j in ops_], net.B)
         f = fam.setdefault(k, {"ms": 0.0, "bytes": 0, "macs": 0, "launches": 0})
         f["ms"] += op_ms[i]; f["bytes"] += byts; f["macs"] += macs; f["launches"] += 1
     dom = max(fam, key=lambda k: fam[k]["ms"])
     d = fam[dom]
     avg_ms = d["ms"] / d["launches"]
-    if dom.startswith("dw_") or dom == "conv_generic":
+    # (the peak that the launch's own work is closer to)
+    if d["bytes"] / (HBM_PEAK_GBS * 1e9) > 2.0 * d["macs"] / (INT8_PEAK_TOPS * 1e12):
         achieved = d["bytes"] / d["launches"] / (avg_ms * 1e-3) / 1e9
         roofline = {"kernel": dom, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": achieved / HBM_PEAK_GBS, "traffic": None}
@@ -307,35 +309,39 @@ def main():
                     "frac": achieved / INT8_PEAK_TOPS, "traffic": None}
     roofline["frac_of_measured_ceiling"] = achieved / (ceilings["hbm_copy_GBs"] if roofline["bound"] == "hbm"
                                                        else ceilings["int8_mfma_TOPs"])
-    roofline["traffic"] = measured_traffic(dom, args.config)
-    if roofline["bound"] == "mfma":
-        roofline["mfma_busy_by_counters"] = measured_mfma_busy(dom, args.config)
+    by_counters = (lambda what: None) if args.batch else (lambda what: measured(what, dom, args.config))
+    roofline["traffic"] = by_counters("traffic_bytes_per_launch")
+    roofline["mfma_frac"] = 2.0 * d["macs"] / (d["ms"] * 1e-3) / 1e12 / INT8_PEAK_TOPS
+    roofline["mfma_busy_by_counters"] = by_counters("mfma_busy")
     roofline["avg_launch_us"] = avg_ms * 1e3
     roofline["launches_per_step"] = d["launches"]
+    roofline["kernels"] = {k: {"launches": f["launches"], "ms": f["ms"]} for k, f in
+                           sorted(fam.items(), key=lambda kf: -kf[1]["ms"])}
     roofline["share_of_device_time"] = d["ms"] / float(op_ms.sum())
 
     def stage(sel, t_ms):
-        idx = [i for i, o in enumerate(net.ops) if sel(o)]
+        idx = [i for i, _, ops_ in launches if sel([net.ops[j] for j in ops_])]
         if not idx:
             return None
         ms = float(t_ms[idx].sum())
-        byts = sum(op_algorithmic(net.ops[i], net.B)[0] for i in idx)
-        macs = sum(op_algorithmic(net.ops[i], net.B)[1] for i in idx)
+        work = [launch_algorithmic([net.ops[j] for j in ops_], net.B) for i, _, ops_ in launches if i in idx]
+        byts, macs = (sum(v) for v in zip(*work))
         gbs, tops = byts / (ms * 1e-3) / 1e9, 2 * macs / (ms * 1e-3) / 1e12
-        return {"ops": len(idx), "ms": ms, "GB/s": gbs, "hbm_frac": gbs / HBM_PEAK_GBS,
+        return {"launches": len(idx), "ms": ms, "GB/s": gbs, "hbm_frac": gbs / HBM_PEAK_GBS,
                 "hbm_frac_of_measured_copy": gbs / ceilings["hbm_copy_GBs"],
                 "TOP/s": tops, "mfma_frac": tops / INT8_PEAK_TOPS,
                 "mfma_frac_of_measured_loop": tops / ceilings["int8_mfma_TOPs"]}
 
     def stage_table(t_ms):
-        return {"depthwise": stage(lambda o: o.depthwise, t_ms),
-                "pointwise": stage(lambda o: not o.depthwise and o.k == 1, t_ms),
-                "dense": stage(lambda o: not o.depthwise and o.k > 1, t_ms),
+        return {"depthwise_pointwise_pairs": stage(lambda o: len(o) > 1, t_ms),
+                "depthwise": stage(lambda o: len(o) == 1 and o[0].depthwise, t_ms),
+                "pointwise": stage(lambda o: len(o) == 1 and not o[0].depthwise and o[0].k == 1, t_ms),
+                "dense": stage(lambda o: len(o) == 1 and not o[0].depthwise and o[0].k > 1, t_ms),
                 "device_ms_sum": float(t_ms.sum())}
     stages = stage_table(op_ms)
     stages["ms_per_step_events"] = ms_per_step_events
 
-    # ---- the same per-op times with cold caches: the passes rotate through enough (x, workspace, y)
+    # ---- the same times with cold caches: the passes rotate through enough (x, workspace, y)
     # sets that a set, and the weights, were pushed out of L2 and the memory-side cache by more than
     # 512 MB of other traffic before they are touched again; within a pass a layer still finds the
     # previous layer's output where the pipeline leaves it
@@ -389,7 +395,7 @@ def main():
         "ms_per_step_separate_launches": other_ms,
         "launch_floor": None if floor_ms is None else {
             "ms_per_step": floor_ms, "kernels": n_launch,
-            "what": "graph replay of that many dependent one-element kernels"},
+            "what": "graph replay of as many dependent one-element kernels as the step launches"},
         "int8_TOPS_useful": 2 * total_macs / (ms_per_step * 1e-3) / 1e12,
         "int8_TOPS_frac_of_peak": 2 * total_macs / (ms_per_step * 1e-3) / 1e12 / INT8_PEAK_TOPS,
         "int8_TOPS_frac_of_measured_loop": 2 * total_macs / (ms_per_step * 1e-3) / 1e12 / ceilings["int8_mfma_TOPs"],

@@ -18,9 +18,10 @@
 //   - the global loads of chunk c + 1 are issued when chunk c starts, their transposition and LDS
 //     writes (into the other of two LDS buffers) happen in the middle of chunk c's taps, under
 //     the matrix products; one barrier per chunk, at its end.
-// Every wave streams its own weights from L2 (1 KiB per MT products); loading the same weights in
-// all four waves (a timing experiment with wrong results) changed nothing, so that stream is not
-// what bounds the kernel.  Small layers are bound by the number of workgroups instead: the tile
+// Every wave streams its own weights from L2 (1 KiB per MT products).  On the 768-channel, 25-tap layers
+// of 16 x 800 frames (150 us, 80 x 256 tiles) that is 2.4 GB per launch, 26 of the 64 bytes per cycle that
+// a vector cache takes; the matrix pipes are busy 50 % of the time, the waves (two per SIMD) wait for a
+// load or an LDS read 36 % of theirs.  Small layers are bound by the number of workgroups instead: the tile
 // (16 MT frames x 64 NT channels per wave) is chosen per layer by a small occupancy model.
 #include "kernels.hpp"
 #include "tuning.hpp"
@@ -391,7 +392,9 @@ size_t lds_bytes(const ConvParams& p, const CpTile& c) {
 // operand reads and the NT KiB of weights that every wave streams per step share the unit's ports.
 // The constants (and those of the split in pick) are fitted to the times of every tile, group and split
 // count for 256 .. 768 channels, 11 .. 25 taps and 50 .. 12800 frames with weights that are in no
-// cache: the choices are within 0.7 % of the best one on average, 9 % at worst.
+// cache.  Inside the Jasper-10x5 shape (16 x 800 frames, 52 layers) the choices take 3932 us, the best tile of
+// each forced 3829; the furthest off are 256 -> 256, 11 taps, 22.0 us against 19.2 with 64 x 128 tiles in two
+// groups, and 768 -> 896, 29 taps, dilation 2, 243 against 216 with 112 x 256 tiles.
 double step_cycles(const CpTile& c, int64_t blocks) {
   const int MT = c.MT, NT = c.NT;
   const int occ = c.KG == 4 ? 1 : c.KG == 2 ? (MT * NT <= 8 ? 2 : 1) : NT == 4 ? 2 : MT > 4 ? 3 : 4;   // bound by registers
