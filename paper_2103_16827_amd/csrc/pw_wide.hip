@@ -383,8 +383,8 @@ bool pw_wide_supported(const ConvParams& p) {
 //   pw_tile (one pass after another per workgroup):
 //     257 to 512 channels are one workgroup's here, which stays ahead: 640 -> 512 G=50 9.6 / 6.0, G=1000 10.8 / 9.9,
 //       G=3200 28.3 / 26.7; 384 -> 384 G=400 7.9 / 6.9, G=1400 10.3 / 8.7 (but G=560 8.1 / 8.7);
-//     beyond 512, workgroups share a tile, which pays while they are few: 640 -> 768 G=200 13.5 / 7.7, G=700 15.0 / 12.4,
-//       G=900 15.4 / 21.2; with 1024 input channels pw_tile has LDS for 128 channels at a time only: 1024 -> 1000
+//     beyond 512, workgroups share a tile, which pays while all of them (of 7 groups x 512 channels) run at once:
+//       640 -> 768 G=200 13.5 / 7.7, G=700 15.0 / 12.4, G=900 (258 workgroups) 15.4 / 21.2; with 1024 input channels pw_tile has LDS for 128 channels at a time only: 1024 -> 1000
 //       G=200 35.9 / 9.8, G=2000 49.5 / 44.7;
 //     up to 256 channels, the input channels are split over the waves: 1024 -> 29 G=200 7.0 / 5.5, G=700 7.4 / 6.8, G=1400
 //       8.9 / 9.8; 512 -> 128 G=104 5.5 / 5.5, G=400 5.7 / 6.1; 256 -> 128 G=104 4.4 / 5.1;
@@ -403,7 +403,7 @@ bool pw_wide_better(const ConvParams& p, bool pipe) {
   if (t.pwp_mt || t.pwp_split || t.pw_lean_force || t.pwt_mt || t.pwp_nopipe) return false;   // a forced form of the others
   const int64_t G = (int64_t)p.B * ((p.Tin + 15) / 16);
   if (!pipe) {
-    if (p.Cout > 512) return p.Cin >= 1024 || G <= 700;
+    if (p.Cout > 512) return p.Cin >= 1024 || (G + 6) / 7 * ((p.Cout + 511) / 512) <= 256;
     if (p.Cout > 256) return true;
     return G <= 700 && G <= 2 * (p.Cin - 320);
   }

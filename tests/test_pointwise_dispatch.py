@@ -12,7 +12,7 @@ def launched(Cin, Cout, G, B=2):
     return Q.conv1d_launch_name(make_desc(B, Cin, Cout, 16 * G // B, flags=Q.FLAG_W_PACKED))
 
 
-@pytest.mark.parametrize("Cin,Cout,last", [(640, 768, 700), (384, 200, 128), (640, 29, 640), (1024, 29, 700), (2048, 512, 200), (1024, 1024, 50),
+@pytest.mark.parametrize("Cin,Cout,last", [(640, 768, 896), (384, 1500, 594), (384, 200, 128), (640, 29, 640), (1024, 29, 700), (2048, 512, 200), (1024, 1024, 50),
                                            (1024, 256, 200), (512, 768, 294), (512, 1000, 800), (256, 384, 200)])
 def test_launches_up_to_a_line(Cin, Cout, last):
     assert launched(Cin, Cout, last) == "pw_wide"
