@@ -289,9 +289,8 @@ qasr_status qasr_plan_slot_buffers(const int32_t* in_slot, const int32_t* res_sl
  * output, each rounded up to 256 bytes, their rows to 16 frames where some length is not a multiple of
  * 16; and, where dense layers with taps have too few tiles to fill the chip, room for the partial
  * sums of their split contractions (int32; the largest layer's, plus 4 KiB of counters).  For the
- * Jasper-10x5 shape that is 3 MiB at one utterance of 200 input frames, 8 at 1 x 800, 12 at 1 x 1600, 38 at
- * 8 x 800 and nothing at 16 x 1600; a shape made for it (64 x 1600 frames, 2048 -> 64 channels, 29 taps)
- * reaches 210 MiB.  Known at create time because every shape and scale of the
+ * Jasper-10x5 shape that is 3 MiB at one utterance of 200 input frames, 8 at 1 x 800, 12 at 1 x 1600, 20 at
+ * 4 x 800 and nothing from 8 x 800 on.  Known at create time because every shape and scale of the
  * integer model is static (Sec. 2.1: static quantisation, nothing is sized at inference).  HOST only. */
 size_t qasr_encoder_workspace_bytes(const qasr_encoder* e);
 

@@ -14,33 +14,41 @@
 // What differs is the order in time.  gemm_mfma loads and transposes a chunk, synchronises,
 // multiplies its k taps, synchronises: the memory latency of every chunk and the L2 latency of
 // every tap's weights are exposed.  Here the contraction is one flat stream of (chunk, tap) steps:
-//   - the weights of step q + 2 are requested while step q is multiplied (ring of three);
-//   - the global loads of chunk c + 1 are issued when chunk c starts, their transposition and LDS
-//     writes (into the other of two LDS buffers) happen in the middle of chunk c's taps, under
-//     the matrix products; one barrier per chunk, at its end.
-// Every wave streams its own weights from L2 (1 KiB per MT products).  On the 768-channel, 25-tap layers
-// of 16 x 800 frames (150 us, 80 x 256 tiles) that is 2.4 GB per launch, 26 of the 64 bytes per cycle that
-// a vector cache takes; the matrix pipes are busy 50 % of the time, the waves (two per SIMD) wait for a
-// load or an LDS read 36 % of theirs.  Small layers are bound by the number of workgroups instead: the tile
-// (16 MT frames x 64 NT channels per wave) is chosen per layer by a small occupancy model.
+//   - the weights of step q + 3 are requested while step q is multiplied (ring of four);
+//   - the global loads of chunk c + 2 are issued in the middle of chunk c, right after chunk c + 1 has been
+//     transposed into LDS (three LDS buffers, one barrier per chunk, in its middle), so that the operand
+//     reads run ahead across chunks too.
+// All these requests are counted by hand (vmem.hpp).  Where the compiler counted them, it had to join the paths
+// with and without a chunk on its way: two steps of three waited for weights asked for one step
+// earlier, the step after a chunk's request for the whole chunk, and every step for its last operand reads (16 x 800
+// frames, ring of three: 768 channels, 25 taps 150 -> 142 us, 512 channels, 17 taps 62 -> 58, 256, 11 taps 22 -> 17).
+// What bounds the rest: on operands that are not zeros the chip does not hold its clock.  The inner loop alone, on
+// random codes, 80 x 64 per wave: from registers 4.1 POP/s (4.9 on zeros), with the operand reads 3.9, with the weights from
+// the L2 as well 3.0 (4.5 on zeros); taller tiles stream fewer weights per product and draw less: 3.3 with 160 x 64,
+// 3.4 with 160 x 32.  The 768-channel layers run at 2.66, of 3.2 that their 480 tiles (of at most 512 at once) leave.
+// Small layers are bound by the number of workgroups instead: the tile (16 MT frames x 64 NT channels) is
+// chosen per layer by a small occupancy model.
 #include "kernels.hpp"
 #include "tuning.hpp"
+#include "vmem.hpp"
 
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 
 namespace qasr {
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kStoreThrough = 17;   // sc0 sc1: partial sums are written through, which leaves the release little to write back
 constexpr int kMaxSplits = 8;
 
 constexpr int kXS = 80;       // LDS row pitch in bytes: 64 channels + 16 pad
+constexpr int kConstBytes = 4 * 768;   // per wave of a group: m, s and bias of up to 64 channels
+constexpr int kW = 4;         // weight ring: the step multiplied and three on their way
 constexpr int kMaxRows = 256; // one 4-frame x 16-channel unit per thread and chunk
 
 struct CpGeom {
@@ -59,7 +67,7 @@ struct CpGeom {
 // products, 380 per step); with four groups the latencies pass under the other groups' products.
 template <int MT, int NT, int KG>
 __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeom g) {
-  extern __shared__ __align__(16) unsigned char xs[];   // [2 buffers][rows][kXS]; KG > 1: the partial sums after that
+  extern __shared__ __align__(16) unsigned char xs[];   // [3 buffers][rows][kXS]; KG > 1: the partial sums after that
   constexpr int TM = 16 * MT, TN = 64 * NT;
 
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;   // within the group
@@ -111,7 +119,6 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   // address will do) and shifted down: the missing frames come out as the implicit zeros.
   const int u_fl = min(u_f, p.Tin - 4);
   const int u_shr = u_on ? 8 * (u_f - u_fl) : 0;
-  const bool ragged = (p.Tin & 3) != 0;             // (uniform)
   const uint32_t xoff = u_on ? (uint32_t)(8 * u_cg * xpitch + u_fl) : 0u;   // (Cin x pitch < 2^31)
   uint32_t sel_lo, sel_hi;                          // frames rot, rot+1 | rot+2, rot+3 of two rows
   {
@@ -119,7 +126,8 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
     sel_lo = f0s | ((4 + f0s) << 8) | (f1s << 16) | ((4 + f1s) << 24);
     sel_hi = f2s | ((4 + f2s) << 8) | (f3s << 16) | ((4 + f3s) << 24);
   }
-  uint32_t xr[4][4];
+  // (every wave asks for all 16 dwords, whichever of its lanes take part: the waits below count requests)
+  int32_t xr[4][4];
   auto issue_chunk = [&](int kc) __attribute__((always_inline)) {
     const int8_t* base = xb + (int64_t)(64 * kc) * xpitch;
 #pragma unroll
@@ -127,27 +135,28 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int c = 4 * ((i & 1) + 8 * (i >> 1)) + e;
-        xr[i][e] = u_on ? load_u32(base + (int64_t)c * xpitch + xoff) : 0u;
+        xr[i][e] = gload4(base + (int64_t)c * xpitch, xoff);
       }
   };
   auto commit_chunk = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tie(xr[i][e]);
     if (u_cg < 4) {
-      if (ragged) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) xr[i][e] >>= u_shr;
-      }
       unsigned char* dst = xs + buf * bufbytes + 4 * u_fq * kXS + 16 * u_cg;
       uint32_t c[4][4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
+        uint32_t r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = u_on ? (uint32_t)xr[i][e] >> u_shr : 0u;
         // r_e = 4 consecutive frames of channel e  ->  c_e = 4 consecutive channels of frame
         // (e + rot) & 3
-        const uint32_t lo01 = __builtin_amdgcn_perm(xr[i][1], xr[i][0], sel_lo);
-        const uint32_t hi01 = __builtin_amdgcn_perm(xr[i][1], xr[i][0], sel_hi);
-        const uint32_t lo23 = __builtin_amdgcn_perm(xr[i][3], xr[i][2], sel_lo);
-        const uint32_t hi23 = __builtin_amdgcn_perm(xr[i][3], xr[i][2], sel_hi);
+        const uint32_t lo01 = __builtin_amdgcn_perm(r[1], r[0], sel_lo);
+        const uint32_t hi01 = __builtin_amdgcn_perm(r[1], r[0], sel_hi);
+        const uint32_t lo23 = __builtin_amdgcn_perm(r[3], r[2], sel_lo);
+        const uint32_t hi23 = __builtin_amdgcn_perm(r[3], r[2], sel_hi);
         c[i][0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
         c[i][1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
         c[i][2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
@@ -160,7 +169,7 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
     }
   };
 
-  // ---- weights: step q = (chunk, tap) of the flat contraction, ring of three steps
+  // ---- weights: step q = (chunk, tap) of the flat contraction, ring of kW steps
   const int Q = nkc * (j1 - j0);
   int wkc = 0, wj = j0;                             // chunk and tap of the next step to request
   // (the packed buffer is below 2 GiB: a wave-uniform base per step plus a 32-bit lane offset)
@@ -168,100 +177,124 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
     woff[nt] = (uint32_t)((min((co_w >> 4) + nt, g.co16n - 1) * g.kchunks * 64 + lane) * 16);
-  auto load_w = [&](v4i (&dst)[NT]) __attribute__((always_inline)) {
-    const int8_t* wbase = p.w + (int64_t)(wj * g.co16n * g.kchunks + c0 + wkc) * 1024;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) dst[nt] = *reinterpret_cast<const v4i*>(wbase + woff[nt]);
+  v4i wb[kW][NT];
+  auto load_w = [&](int nt, v4i (&dst)[NT]) __attribute__((always_inline)) {
+    dst[nt] = gload16(p.w + (int64_t)(wj * g.co16n * g.kchunks + c0 + wkc) * 1024, woff[nt]);
+  };
+  auto next_w = [&]() __attribute__((always_inline)) {
     if (++wj == j1) {                               // (the stream stays on its last step at the end)
       if (wkc + 1 < nkc) { wj = j0; ++wkc; } else { --wj; }
     }
   };
 
-  // per-lane output channels (clamped for reads; stores are masked)
-  int co_ld[NT];
+  // ---- prologue: constants (output channels clamped for reads; stores are masked), chunk 0 into buffer 0,
+  // weights of steps 0 .. kW - 2.  The groups take turns at bringing in a chunk: chunk kc is group kc mod
+  // KG's, which asks for its next one as soon as it has put one into LDS.
+  // (lane -> channel co_w + lane of the wave's 16 NT)
+  unsigned char* const consts = xs + 3 * bufbytes + wave * 768;   // [m, s, bias][64] of this wave's channels
+  if (kg == 0) {
+    const int64_t co = min(co_w + (lane & (16 * NT - 1)), p.Cout - 1);
+    direct_load4(p.m + co, consts);
+    direct_load4(p.s + co, consts + 256);
+    if (p.bias) direct_load4(p.bias + co, consts + 512);
+  }
+  if (kg == 0) issue_chunk(0);
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) co_ld[nt] = min(co_w + 16 * nt + n, p.Cout - 1);
+  for (int u = 0; u < kW - 1; ++u) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) load_w(nt, wb[u]);
+    next_w();
+  }
+  int xcnt = 0;                                     // steps whose weights were requested before the chunk on its way
+  wait_vm<(kW - 1) * NT>();
   v4i acc[MT][NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int32_t bv = p.bias && kg == 0 && split == 0 ? p.bias[co_ld[nt]] : 0;
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = (v4i){bv, bv, bv, bv};
-  }
-
-  // ---- prologue: chunk 0 into buffer 0, weights of steps 0 and 1
-  v4i wb[3][NT];
-  // (the groups take turns at bringing in a chunk: chunk kc is group kc mod KG's, which with several groups
-  // asks for its next one as soon as it has put one into LDS: with few taps per group a chunk lasts less
-  // than the memory latency)
-  if (kg < nkc) issue_chunk(kg);
-  load_w(wb[0]);
-  load_w(wb[1]);
-  if (kg == 0) {
-    commit_chunk(0);
-    if (KG < nkc) issue_chunk(KG);
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4i){0, 0, 0, 0};
+  if (kg == 0) commit_chunk(0);
+  if ((kg == 0 ? KG : kg) < nkc) {
+    issue_chunk(kg == 0 ? KG : kg);
+    xcnt = kW - 1;
   }
   __syncthreads();
 
-  // The A operands (one 16-byte LDS read per 16 frames) go through a ring of three registers,
-  // two reads ahead of the products; the ring runs on across the steps of a chunk, so that a
-  // step's first operands arrive under the previous step's products (a new chunk starts after
-  // the barrier with two exposed reads).
-  auto arow_of = [&](int kc_, int j_) __attribute__((always_inline)) {
-    return xs + (kc_ & 1) * bufbytes + (foff + j_ * p.dil + n * p.stride) * kXS + 16 * gi;
+  // The A operands (one 16-byte LDS read per 16 frames) go through a ring of four registers, three reads
+  // ahead of the products, across steps and chunks: chunk kc + 1 is complete in LDS from the middle of chunk
+  // kc on (three buffers, one barrier per chunk: the wave that puts chunk kc + 1 where chunk kc - 2 was has
+  // passed the barrier in the middle of chunk kc - 1, which no wave reaches before it is done with kc - 2).
+  auto arow_of = [&](int buf_, int j_) __attribute__((always_inline)) {
+    return xs + buf_ * bufbytes + (foff + j_ * p.dil + n * p.stride) * kXS + 16 * gi;
   };
   auto read_a = [&](const unsigned char* arow, int mt) __attribute__((always_inline)) {
     return *reinterpret_cast<const v4i*>(arow + 16 * mt * p.stride * kXS);
   };
-  const int jmid = j0 + ((j1 - j0) >> 1);           // the tap at which the next chunk is committed
-  int kc = 0, j = j0;                               // chunk and tap of the current step
-  v4i ar[3];
-  ar[0] = read_a(arow_of(0, j0), 0);
-  ar[1] = read_a(arow_of(0, j0), 1);
-  for (int q = 0; q < Q; q += 3) {
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      if (q + u < Q) {
-        load_w(wb[(u + 2) % 3]);
-        const unsigned char* arow = arow_of(kc, j);
-        const bool last_tap = j + 1 == j1;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          if (mt + 2 < MT) {
-            ar[(u * MT + mt + 2) % 3] = read_a(arow, mt + 2);
-          } else if (!last_tap) {
-            ar[(u * MT + mt + 2) % 3] = read_a(arow + p.dil * kXS, mt + 2 - MT);
-          }
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[(u * MT + mt) % 3], wb[u][nt], acc[mt][nt], 0, 0, 0);
-        }
-        if (j == jmid && kc + 1 < nkc && kg == (kc + 1) % KG) {
-          commit_chunk((kc + 1) & 1);
-          if (KG > 1 && kc + 1 + KG < nkc) issue_chunk(kc + 1 + KG);
-        }
-        if (last_tap) {
-          j = j0;
-          ++kc;
-          __syncthreads();                          // chunk kc is in LDS; chunk kc - 1 has been read by all
-          if (KG == 1 && kc + 1 < nkc) issue_chunk(kc + 1);
-          if (kc < nkc) {
-            ar[((u + 1) * MT) % 3] = read_a(arow_of(kc, j0), 0);
-            ar[((u + 1) * MT + 1) % 3] = read_a(arow_of(kc, j0), 1);
-          }
-        } else {
-          ++j;
+  const int jmid = j0 + ((j1 - j0) >> 1);           // the tap before which the next chunk is committed
+  int kc = 0, j = j0, buf = 0, q = 0;               // chunk, tap and buffer of the current step
+  const unsigned char* arow = arow_of(0, j0);
+  v4i ar[4];
+  ar[0] = read_a(arow, 0);
+  ar[1] = read_a(arow, 1);
+  ar[2] = read_a(arow, 2);
+  auto step = [&](auto slot_tag) __attribute__((always_inline)) {
+    constexpr int u = decltype(slot_tag)::value;
+    if (j == jmid && kc + 1 < nkc) {
+      const int nbuf = buf == 2 ? 0 : buf + 1;
+      if (KG == 1 || kg == (kc + 1) % KG) {
+        // (3 - xcnt steps' weights were requested after the chunk, more if xcnt is 0)
+        if (xcnt == 3) wait_vm<0>();
+        else if (xcnt == 2) wait_vm<NT>();
+        else wait_vm<2 * NT>();
+        commit_chunk(nbuf);
+        if (kc + 1 + KG < nkc) {
+          issue_chunk(kc + 1 + KG);
+          xcnt = kW - 1;
         }
       }
+      __syncthreads();                              // chunk kc + 1 is in LDS
     }
-  }
+    // this step's weights: those of the kW - 2 steps after it are younger, and so may a chunk's 16 dwords be
+    if (xcnt > 0) {
+      --xcnt;
+      wait_vm<(kW - 2) * NT + 16>();
+    } else {
+      wait_vm<(kW - 2) * NT>();
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) tie(wb[u][nt]);
+    if (++j == j1) {
+      if (kc + 1 < nkc) { j = j0; ++kc; buf = buf == 2 ? 0 : buf + 1; }
+      else --j;                                     // (after the last step: the operands are read once more)
+    }
+    const unsigned char* const anext = arow_of(buf, j);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      ar[(u * MT + mt + 3) % 4] = mt + 3 < MT ? read_a(arow, mt + 3) : read_a(anext, mt + 3 - MT);
+      if (mt < NT) load_w(mt, wb[(u + kW - 1) % kW]);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[(u * MT + mt) % 4], wb[u][nt], acc[mt][nt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    next_w();
+    arow = anext;
+    return ++q < Q;
+  };
+  static_assert(kW == 4 && MT >= NT && MT >= 3, "rings");
+  while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{}) &&
+         step(std::integral_constant<int, 2>{}) && step(std::integral_constant<int, 3>{})) {}
+  wait_vm<0>();                                     // what the weight stream asked for past its end
+#pragma unroll
+  for (int u = 0; u < kW; ++u)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) tie(wb[u][nt]);
 
   // ---- KG > 1: group o finishes the frame groups mt with mt KG / MT == o; every other group's sums of
   // them reach it through LDS (past the activation buffers: no wave may be reading those any more)
   if constexpr (KG > 1) {
     static_assert(MT % KG == 0, "frame groups per wave group");
     // [owner][the other groups][frame group of the owner][nt][wave][lane]
-    v4i* const red = reinterpret_cast<v4i*>(xs + 2 * bufbytes);
+    v4i* const red = reinterpret_cast<v4i*>(xs + 3 * bufbytes + kConstBytes);
     auto slot = [&](int o, int src, int mt, int nt) __attribute__((always_inline)) {
       const int rank = src < o ? src : src - 1;
       return red + ((((o * (KG - 1) + rank) * (MT / KG) + mt % (MT / KG)) * NT + nt) * 4 + wave) * 64 + lane;
@@ -342,7 +375,8 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   for (int nt = 0; nt < NT; ++nt) {
     const int co = co_w + 16 * nt + n;
     if (co >= p.Cout) continue;
-    const int32_t mc = p.m[co], sc = p.s[co];
+    const int32_t* const cl = reinterpret_cast<const int32_t*>(consts) + 16 * nt + n;
+    const int32_t mc = cl[0], sc = cl[64], bv = p.bias ? cl[128] : 0;
     const int trow = p.Tout + p.ypad;               // (pad bytes may be written)
     const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * trow;
 #pragma unroll
@@ -363,7 +397,7 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
       uint32_t pk = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int32_t v = dyadic_rescale(acc[mt][nt][i], mc, sc) + radd[i];
+        const int32_t v = dyadic_rescale(acc[mt][nt][i] + bv, mc, sc) + radd[i];
         pk |= (uint32_t)(clamp_i8(v, lo) & 0xff) << (8 * i);
       }
       store_row_u32(p.y + orow, t, trow, pk);
@@ -381,28 +415,33 @@ struct CpTile { int MT, NT, KG, S; };
 constexpr int64_t kMaxSplitTiles = kConvSplitCounters;   // (one arrival counter each)
 
 size_t lds_bytes(const ConvParams& p, const CpTile& c) {
-  const size_t x = (size_t)2 * lds_rows(p, 16 * c.MT) * kXS;
+  const size_t x = (size_t)3 * lds_rows(p, 16 * c.MT) * kXS + kConstBytes;
   return c.KG > 1 ? x + (size_t)(c.KG - 1) * c.MT * c.NT * 4096 : x;
 }
 
-// Cycles per (chunk, tap) step on the busiest compute unit, from a small model: a unit holds `occ`
-// workgroups, KG waves each per SIMD; a SIMD with w workgroups spends w M cycles per step in the
-// matrix pipe (M = 24 MT NT with everything that does not overlap), a lone wave cannot go below M plus
-// its own latencies (operand reads, weight request, loop) for each of its group's steps, and the
-// operand reads and the NT KiB of weights that every wave streams per step share the unit's ports.
-// The constants (and those of the split in pick) are fitted to the times of every tile, group and split
-// count for 256 .. 768 channels, 11 .. 25 taps and 50 .. 12800 frames with weights that are in no
-// cache.  Inside the Jasper-10x5 shape (16 x 800 frames, 52 layers) the choices take 3932 us, the best tile of
-// each forced 3829; the furthest off are 256 -> 256, 11 taps, 22.0 us against 19.2 with 64 x 128 tiles in two
-// groups, and 768 -> 896, 29 taps, dilation 2, 243 against 216 with 112 x 256 tiles.
-double step_cycles(const CpTile& c, int64_t blocks) {
-  const int MT = c.MT, NT = c.NT;
-  const int occ = c.KG == 4 ? 1 : c.KG == 2 ? (MT * NT <= 8 ? 2 : 1) : NT == 4 ? 2 : MT > 4 ? 3 : 4;   // bound by registers
-  const double M = 24.0 * MT * NT, alone = (M + 400.0) / c.KG, lds = 10.0 * MT, wstream = 100.0 * NT;
+// Workgroups of a tile that a compute unit holds: registers (512 per SIMD and lane), then LDS.
+int resident(const ConvParams& p, const CpTile& c) {
+  const int by_regs = c.KG == 4 ? 1 : c.KG == 2 ? (c.MT * c.NT <= 8 ? 2 : 1) : c.NT == 4 || c.MT > 9 ? 2 : c.MT > 4 ? 3 : 4;
+  const int by_lds = (int)(160 * 1024 / lds_bytes(p, c));
+  return by_regs < by_lds ? by_regs : by_lds;
+}
+
+// Cycles that a compute unit takes for n workgroups of a tile whose contraction is `chunks` chunks long.  w of them
+// run at once: a step is bound by the matrix pipes (18.6 cycles per product: with operands that are not zeros the
+// clock gives way), by a lone wave's own latencies, by the weights (NT KiB per wave) or by the operand reads; a
+// chunk costs a commit and a barrier; a workgroup its first loads and its epilogue, KG > 1 the meeting of the sums.
+// The constants are fitted to the times of every tile, group and split count for 256 .. 768 channels, 11 .. 25 taps
+// and 50 .. 12800 frames (8250 of them), each inside a chain of six layers whose weights are in no L2: the choice is
+// 0.2 % from the best on average and 4.8 % at worst.
+double unit_cycles(const ConvParams& p, const CpTile& c, int64_t n, int chunks) {
+  const double mn = c.MT * c.NT, taps = (p.k + c.KG - 1) / c.KG;
+  const int occ = resident(p, c);
   auto T = [&](int64_t w) {
-    return w == 0 ? 0.0 : fmax(fmax(fmax((double)w * M, alone), (double)w * lds), (double)w * wstream);
+    if (w == 0) return 0.0;
+    const double step = fmax(fmax(18.6 * (double)w * c.KG * mn, 16.0 * mn + 343.0),
+                             fmax(93.0 * (double)w * c.KG * c.NT, 29.0 * (double)w * c.KG * c.MT));
+    return 3900.0 + 690.0 * mn / c.KG * (double)w + chunks * (fmax(taps * step, 890.0) + 920.0) + (c.KG > 1 ? 7800.0 : 0.0);
   };
-  const int64_t n = (blocks + 255) / 256;                 // workgroups on the busiest unit
   return (double)(n / occ) * T(occ) + T(n % occ);
 }
 
@@ -413,11 +452,9 @@ bool pick(const ConvParams& p, bool split, CpTile& best_tile) {
   if (p.Tin < 4 || p.Tout < 4 || (uintptr_t)p.w % 16) return false;   // (rows are read in dwords, at any address)
   // the kernel addresses the packed weights with 32-bit offsets
   if ((int64_t)p.k * ((p.Cout + 15) / 16) * (p.Cin / 64) * 1024 > 0x7fffffffLL) return false;
-  // frames per tile: 96 or 64 (128 would need all 256 registers and leave one wave per SIMD:
-  // measured slower than 96 with two); channels per tile: 256 or 128
   const int force_mt = tuning().cp_mt, force_nt = tuning().cp_nt, force_kg = tuning().cp_kg;   // tuning
-  static const CpTile tiles[] = {{8, 4, 1, 1}, {7, 4, 1, 1}, {6, 4, 1, 1}, {5, 4, 1, 1}, {4, 4, 1, 1}, {8, 2, 1, 1}, {7, 2, 1, 1}, {6, 2, 1, 1},
-                                 {5, 2, 1, 1}, {4, 2, 1, 1}, {6, 4, 2, 1}, {4, 4, 2, 1}, {6, 2, 2, 1}, {4, 2, 2, 1}, {4, 2, 4, 1}};
+  static const CpTile tiles[] = {{8, 4, 1, 1}, {7, 4, 1, 1}, {6, 4, 1, 1}, {5, 4, 1, 1}, {4, 4, 1, 1}, {10, 2, 1, 1}, {9, 2, 1, 1}, {8, 2, 1, 1}, {7, 2, 1, 1}, {6, 2, 1, 1},
+                                 {5, 2, 1, 1}, {4, 2, 1, 1}, {6, 4, 2, 1}, {4, 4, 2, 1}, {10, 2, 2, 1}, {8, 2, 2, 1}, {6, 2, 2, 1}, {4, 2, 2, 1}, {4, 2, 4, 1}};
   const int force_s = tuning().cp_s;
   double best = 1e300;
   bool found = false;
@@ -430,14 +467,12 @@ bool pick(const ConvParams& p, bool split, CpTile& best_tile) {
     const int64_t n_tt = (p.Tout + TM - 1) / TM, n_co = (p.Cout + 64 * c.NT - 1) / (64 * c.NT);
     const int64_t blocks = (int64_t)p.B * n_tt * n_co;
     if (blocks > 0x7ffffff0LL) continue;
-    // halo read and transposed per tile, relative to the products; uneven tap splits; the groups' final sums
-    const double uneven = c.KG > 1 ? (double)((p.k + c.KG - 1) / c.KG * c.KG) / p.k : 1.0;
     for (int S = 1; S <= (split && blocks <= kMaxSplitTiles ? kMaxSplits : 1) && S <= p.Cin / 64; ++S) {
       if (force_s && split && S != force_s) continue;
-      // the longest range's steps; the other splits' sums read back by one unit, and all sums through memory
-      const int longest = (p.Cin / 64 + S - 1) / S * p.k;
-      const double cost = longest * step_cycles(c, blocks * S) * (1.0 + 0.3 / c.MT) * uneven + (c.KG > 1 ? 2100.0 : 0.0) +
-                          (S > 1 ? c.MT * c.NT * (120.0 * (S - 1) + 2.0 * (double)(blocks * S)) : 0.0);
+      // the longest range of chunks; the other splits' sums read back one after the other, and all sums through memory
+      const int64_t wgs = blocks * S;
+      const double cost = unit_cycles(p, c, (wgs + 255) / 256, (p.Cin / 64 + S - 1) / S) +
+                          (S > 1 ? 10700.0 + 1445.0 * (S - 1) + c.MT * c.NT / (double)c.KG * (9.3 * (S - 1) + 4.0 * (double)wgs) : 0.0);
       if (cost < best * 0.999) { best = cost; best_tile = c; best_tile.S = S; found = true; }
     }
   }
@@ -466,7 +501,7 @@ hipError_t launch_t(const ConvParams& p, int splits, hipStream_t st) {
   g.tiles = (int)blocks;
   g.per_xcd = tuning().cp_plain_order ? 0 : (int)((blocks + 7) / 8);
   const size_t lds = lds_bytes(p, CpTile{MT, NT, KG, 1});
-  if constexpr (KG > 1) {
+  if (lds > 64 * 1024) {
     static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
     if (const hipError_t e = ensure_max_dynamic_lds((const void*)conv_pipe_kernel<MT, NT, KG>, lds_raised); e != hipSuccess)
       return e;
@@ -497,9 +532,9 @@ hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st) {
   if (!ok || (int64_t)part_bytes(p, c) > p.part_bytes) ok = pick(p, false, c);   // (tuning changed since the room was made)
   if (!ok) return hipErrorInvalidValue;
 #define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KG == K) return launch_t<M, N, K>(p, c.S, st);
-  QASR_CASE(8, 4, 1) QASR_CASE(7, 4, 1) QASR_CASE(6, 4, 1) QASR_CASE(5, 4, 1) QASR_CASE(4, 4, 1)
+  QASR_CASE(8, 4, 1) QASR_CASE(7, 4, 1) QASR_CASE(6, 4, 1) QASR_CASE(5, 4, 1) QASR_CASE(4, 4, 1) QASR_CASE(10, 2, 1) QASR_CASE(9, 2, 1)
   QASR_CASE(8, 2, 1) QASR_CASE(7, 2, 1) QASR_CASE(6, 2, 1) QASR_CASE(5, 2, 1) QASR_CASE(4, 2, 1)
-  QASR_CASE(6, 4, 2) QASR_CASE(4, 4, 2) QASR_CASE(6, 2, 2) QASR_CASE(4, 2, 2) QASR_CASE(4, 2, 4)
+  QASR_CASE(6, 4, 2) QASR_CASE(4, 4, 2) QASR_CASE(10, 2, 2) QASR_CASE(8, 2, 2) QASR_CASE(6, 2, 2) QASR_CASE(4, 2, 2) QASR_CASE(4, 2, 4)
 #undef QASR_CASE
   return hipErrorInvalidValue;
 }

@@ -75,6 +75,17 @@ __device__ __forceinline__ int32_t gload4(const void* p) {
   asm volatile("global_load_dword %0, %1, off" : "=v"(r) : "v"(p) : "memory");
   return r;
 }
+// the same from a wave-uniform base plus a 32-bit offset per lane
+__device__ __forceinline__ v4i gload16(const void* base, uint32_t off) {
+  v4i r;
+  asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
+  return r;
+}
+__device__ __forceinline__ int32_t gload4(const void* base, uint32_t off) {
+  int32_t r;
+  asm volatile("global_load_dword %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
+  return r;
+}
 __device__ __forceinline__ int32_t gload_i8(const void* p) {   // one sign-extended byte
   int32_t r;
   asm volatile("global_load_sbyte %0, %1, off" : "=v"(r) : "v"(p) : "memory");
