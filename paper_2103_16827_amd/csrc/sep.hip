@@ -32,26 +32,34 @@ int units_of(const ConvParams& d, const Geometry& g, int MT) {
   return need | 1;
 }
 
-// Image: [Cout / 16][NA][64 lanes][4 dwords]; dword i of quad a, lane (channel block b = lane / 4, row
-// m = lane % 4) holds the weights of kappa = 4 (4 a + i) .. + 3: tap j sits at kappa = m + r + j dil.
+// Two images of the weights.  Rows [C][16 NA bytes]: tap j sits at byte r + j dil (sep_small_kernel).  After them, at
+// a multiple of 256 bytes, Toeplitz operands [C / 16][NA][64 lanes][4 dwords]; dword i of quad a, lane (channel block
+// b = lane / 4, row m = lane % 4) holds the weights of kappa = 4 (4 a + i) .. + 3: tap j sits at kappa = m + r + j dil.
+size_t rows_image_bytes(int C, int NA) { return ((size_t)C * NA * 16 + 255) & ~(size_t)255; }
 __global__ __launch_bounds__(256) void sep_image_kernel(const int8_t* __restrict__ w, int C, int k, int dil, int r, int NA,
-                                                        uint32_t* __restrict__ img) {
-  const int n = C / 16 * NA * 256;
+                                                        uint32_t* __restrict__ rows, uint32_t* __restrict__ img) {
+  const int n = C / 16 * NA * 256, nr = C * NA * 4;
   const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (idx >= n) return;
-  const int i = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) % NA, blk = (idx >> 8) / NA;
-  const int c = 16 * blk + (lane >> 2), m = lane & 3;
-  uint32_t v = 0;
+  auto taps = [&](int c, int rel0) {                // four bytes from tap position rel0 on
+    uint32_t v = 0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int rel = 4 * (4 * a + i) + e - m - r;
-    const int j = rel >= 0 ? rel / dil : -1;
-    if (j >= 0 && j < k && j * dil == rel) v |= (uint32_t)(uint8_t)w[(int64_t)c * k + j] << (8 * e);
-  }
-  img[idx] = v;
+    for (int e = 0; e < 4; ++e) {
+      const int rel = rel0 + e;
+      const int j = rel >= 0 ? rel / dil : -1;
+      if (j >= 0 && j < k && j * dil == rel) v |= (uint32_t)(uint8_t)w[(int64_t)c * k + j] << (8 * e);
+    }
+    return v;
+  };
+  if (idx < nr) rows[idx] = taps(idx / (4 * NA), 4 * (idx % (4 * NA)) - r);
+  const int i = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) % NA, blk = (idx >> 8) / NA;
+  img[idx] = taps(16 * blk + (lane >> 2), 4 * (4 * a + i) - (lane & 3) - r);
 }
 
-size_t lds_bytes(int KCH, int units, int MT, int NA) { return (size_t)KCH * 8192 + sep::kWaves * (size_t)sep::row_bytes(units, MT, NA) + 256; }
+size_t lds_bytes(int KCH, int units, int MT, int NA) {
+  const int rows = MT <= 2 ? sep::small_row_bytes(4 * KCH, units, MT, NA) : sep::row_bytes(units, MT, NA);
+  return (size_t)KCH * 8192 + sep::kWaves * (size_t)(rows + 256);
+}
 
 // Tile (MT groups x 256 NT output channels per workgroup) with the least time on the busiest compute
 // unit, one workgroup at a time: its matrix pipes (10 cycles per 4x4x4 product, 17.7 per 16x16x64 one),
@@ -62,24 +70,28 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
   c.KCH = d.Cout / 64;
   c.NA = g.NA;
   double best = 1e300;
-  const int force_mt = tuning().sep_mt, force_nt = tuning().sep_nt;
-  for (int NT = 1; NT <= 2; ++NT) {
-    if (q.Cout % (256 * NT) || (force_nt && NT != force_nt)) continue;
-    for (int MT : MTs) {
-      if ((force_mt && MT != force_mt) || (c.ragged && MT > 4)) continue;
-      const int units = units_of(d, g, MT);
-      if (units > sep::kMaxUnits) continue;
-      const size_t lds = lds_bytes(c.KCH, units, MT, c.NA);
-      if (lds > 160 * 1024) continue;
-      const int splits = q.Cout / (256 * NT);
-      const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
-      if (wgs > max_workgroups(64 * sep::kWaves)) continue;
-      const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 4;
-      const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 16.0 * c.KCH * 1024 + c.KCH * 64.0 * units * 16;
-      const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
-      const int64_t n = (wgs + cus - 1) / cus;
-      const double cost = (double)n * (3.5 + work);
-      if (cost < best) { best = cost; c.MT = MT; c.NT = NT; c.splits = splits; }
+  const int force_mt = tuning().sep_mt, force_nt = tuning().sep_nt, force_ks = tuning().sep_ks;
+  for (int KS = 1; KS <= 2; ++KS) {
+    for (int NT = 1; NT <= 2; ++NT) {
+      if (q.Cout % (256 / KS * NT) || (force_nt && NT != force_nt)) continue;
+      for (int MT : MTs) {
+        if ((force_mt && MT != force_mt) || (c.ragged && MT > 4)) continue;
+        if ((KS > 1 && (MT > 2 || NT > 1)) || (force_nt && (force_ks ? force_ks : 1) != KS)) continue;
+        const int units = units_of(d, g, MT);
+        if (units > sep::kMaxUnits) continue;
+        if (MT <= 2 && (int64_t)4 * c.KCH * (d.Tin + d.xpad) > 0x7fffffffLL) continue;   // 32-bit offsets within a wave's rows
+        const size_t lds = lds_bytes(c.KCH, units, MT, c.NA);
+        if (lds > 160 * 1024) continue;
+        const int splits = q.Cout / (256 / KS * NT);
+        const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
+        if (wgs > max_workgroups(64 * sep::kWaves)) continue;
+        const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 4 / KS;
+        const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 64.0 * units * 16;
+        const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
+        const int64_t n = (wgs + cus - 1) / cus;
+        const double cost = (double)n * (3.5 + work);
+        if (cost < best) { best = cost; c.MT = MT; c.NT = NT; c.KS = KS; c.splits = splits; }
+      }
     }
   }
   return best < 1e300;
@@ -109,14 +121,14 @@ bool sep_supported(const ConvParams& d, const ConvParams& q) {
 
 size_t sep_image_bytes(const ConvParams& d) {
   Geometry g;
-  return geometry(d, g) ? (size_t)d.Cout / 16 * g.NA * 1024 : 0;
+  return geometry(d, g) ? rows_image_bytes(d.Cout, g.NA) + (size_t)d.Cout / 16 * g.NA * 1024 : 0;
 }
 
 hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st) {
   Geometry g;
   if (!geometry(d, g) || d.Cout % 16) return hipErrorInvalidValue;
   return launch_kernel(sep_image_kernel, dim3((unsigned)(d.Cout / 16 * g.NA)), dim3(256), 0, st, d.w, d.Cout, d.k, d.dil, g.r,
-                       g.NA, img);
+                       g.NA, img, img + rows_image_bytes(d.Cout, g.NA) / 4);
 }
 
 hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, hipStream_t st) {
@@ -124,7 +136,7 @@ hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams
   SepChoice c;
   if (!plan(d, q, compute_units(), g, c)) return hipErrorInvalidValue;
   SepParams p{};
-  p.x = d.x; p.img = img; p.dbias = d.bias; p.dm = d.m; p.ds = d.s; p.lut = d.act_lut;
+  p.x = d.x; p.img = c.MT <= 2 ? img : img + rows_image_bytes(d.Cout, g.NA) / 4; p.dbias = d.bias; p.dm = d.m; p.ds = d.s; p.lut = d.act_lut;
   p.xbs = d.xbs; p.xpitch = d.Tin + d.xpad; p.Tin = d.Tin;
   p.o16 = -((d.pl + g.delta) / 16);
   p.nk = g.nk;
@@ -133,10 +145,18 @@ hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams
   p.drelu = d.relu;
   p.w = q.w; p.bias = q.bias; p.m = q.m; p.s = q.s; p.res = q.res; p.y = q.y;
   p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.Tout = q.Tout; p.relu = q.relu;
-  p.B = d.B; p.gpr = (q.Tout + 15) / 16; p.tpr = (p.gpr + c.MT - 1) / c.MT;
+  const int gpr = (q.Tout + 15) / 16;
+  p.tpr = (gpr + c.MT - 1) / c.MT;
+  p.g_base = gpr / p.tpr;
+  p.g_more = gpr % p.tpr;
   p.yragged = y_ragged(q);
   p.splits = c.splits;
-  p.wgs = p.B * p.tpr * p.splits;
+  p.wgs = d.B * p.tpr * p.splits;                // (< 2^22: pick)
+  p.units_inv = (65536 + p.units - 1) / p.units;
+  p.r_splits = 1.0f / (float)p.splits;
+  p.r_tpr = 1.0f / (float)p.tpr;
+  const int C = c.MT <= 2 ? 4 * c.KCH : 16;      // rows a wave brings in at a time
+  if (C * p.units > 64 * sep::row_loads(C, c.MT, c.NA)) return hipErrorInvalidValue;
   p.per_xcd = (p.wgs + 7) / 8;
   const size_t lds = lds_bytes(c.KCH, p.units, c.MT, c.NA);
   switch (c.NA) {

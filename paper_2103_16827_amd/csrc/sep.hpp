@@ -27,17 +27,20 @@ struct SepParams {
   int64_t ybs;
   int32_t ypitch, relu;
   int32_t Tout, yragged;             // frames per row; rows (y and residual) not padded to whole aligned chunks
-  // tiles: row (batch item) b's groups [i gpr / tpr, (i + 1) gpr / tpr) of 16 frames make its tile i
-  int32_t B, gpr, tpr;
+  // tiles: the 16-frame groups of a row (batch item) make tpr tiles of g_base groups, the first g_more of them
+  // one group more
+  int32_t tpr, g_base, g_more;
   int32_t splits;                    // workgroups per tile, each with its own run of output channels
   int32_t wgs, per_xcd;              // workgroups in all, and per XCD
+  int32_t units_inv;                 // ceil(2^16 / units): L / units = L units_inv >> 16 for L < 512, units <= 15
+  float r_splits, r_tpr;             // reciprocals of the two
 };
 
-struct SepChoice { int KCH, MT, NA, NT, splits; bool ragged; };
+struct SepChoice { int KCH, MT, NA, NT, KS, splits; bool ragged; };   // KS: wave groups over the pointwise half's input channels
 
 // Can depthwise op d and pointwise op q (q reads d's output and nobody else does) run as one launch?
 bool sep_supported(const ConvParams& d, const ConvParams& q);
-// The 4-row Toeplitz image of a depthwise layer's weights (see sep_body.hpp)
+// The images of a depthwise layer's weights (sep.hip)
 size_t sep_image_bytes(const ConvParams& d);
 hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st);
 // d.x, q.res, q.y set; d.y and q.x are not used

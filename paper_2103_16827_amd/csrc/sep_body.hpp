@@ -22,6 +22,9 @@
 //
 // Pointwise half: as pw_pipe_body.hpp (transposing LDS reads, packed weights straight from L2), one
 // pass of 16 NT channels per wave, compiler-visible loads.
+//
+// Two kernels: launches of few frames are bound by what a workgroup loads (sep_small_kernel), the others by their
+// products (sep_kernel).  QuartzNet-15x5, one utterance of 1237 frames 626 -> 548 us, 32 utterances of 1600 1387 -> 1323.
 #pragma once
 #include "sep.hpp"
 
@@ -43,55 +46,125 @@ __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
       (v2i __attribute__((address_space(3)))*)(const_cast<unsigned char*>(p)));
 }
 
+// 64-lane loads that bring in C rows: at most (MT + NA + 1) | 1 chunks each (units_of: the first chunk starts up to
+// 15 frames early, NA quads hold up to 16 NA - 3 frames of taps)
+constexpr int row_loads(int C, int MT, int NA) {
+  const int u = (MT + NA + 1) | 1;
+  return (C * (u < kMaxUnits ? u : kMaxUnits) + 63) / 64;
+}
+
 // bytes of a wave's row buffer: 16 rows and what the windows of the last row read past it, at least
-// the 16 x 128 bytes of the output staging
+// the 16 x 128 bytes of the output staging; of the small kernel's: all C rows, at least
+// two 16 x 16 blocks of sums
 __host__ __device__ inline int row_bytes(int units, int MT, int NA) {
   const int rows = 15 * 16 * units + 16 * (MT + NA) + 32;
   return ((rows > 2048 ? rows : 2048) + 15) & ~15;
 }
+__host__ __device__ inline int small_row_bytes(int C, int units, int MT, int NA) {
+  const int rows = (C - 1) * 16 * units + 16 * (MT + NA) + 32;
+  return ((rows > 2048 ? rows : 2048) + 15) & ~15;
+}
 
-// RAGGED: x or y (and the residual) are the caller's, rows of any length at any address
-template <int KCH, int MT, int NA, int NT, bool RAGGED>
-__global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
-  extern __shared__ __align__(128) unsigned char lds[];   // [Cin][128 B] tile, [kWaves] row buffers, table
-  constexpr int CPW = KCH * 64 / kWaves;            // depthwise channels per wave
-  constexpr int NBLK = CPW / 16;                    // in blocks of 16
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+// v / d for 0 <= v < 2^24 and wave-uniform operands, rd = 1.0f / d: the estimate is off by one at most
+__device__ __forceinline__ int divide(int v, int d, float rd) {
+  const int q = __builtin_amdgcn_readfirstlane((int)((float)v * rd));
+  const int r = v - q * d;
+  return r < 0 ? q - 1 : r >= d ? q + 1 : q;
+}
+
+// The workgroup's tile and output channels, without a division (two 64-bit ones were 290 instructions in front
+// of the first load).  All arguments are read first, in one go: asked for where they are used, they were a
+// dozen dependent scalar loads.
+struct Place { int b, g0, gn, cs; };
+__device__ __forceinline__ bool place(const SepParams& p, Place& at) {
+  asm volatile("" ::"s"(p.x), "s"(p.img), "s"(p.dbias), "s"(p.dm), "s"(p.ds), "s"(p.lut), "s"(p.xbs), "s"(p.xpitch), "s"(p.Tin),
+               "s"(p.o16), "s"(p.nk), "s"(p.units), "s"(p.dwoff), "s"(p.drelu), "s"(p.units_inv));
+  asm volatile("" ::"s"(p.w), "s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.res), "s"(p.y), "s"(p.ybs), "s"(p.ypitch), "s"(p.relu),
+               "s"(p.Tout), "s"(p.yragged), "s"(p.tpr), "s"(p.splits), "s"(p.wgs), "s"(p.per_xcd), "s"(p.g_base), "s"(p.g_more),
+               "s"(p.r_splits), "s"(p.r_tpr));
   // consecutive workgroups go round-robin to the 8 XCDs: each XCD takes a contiguous run of tiles
   // (neighbours share halo rows, the workgroups of one tile its rows)
   const int v = (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= p.per_xcd || v >= p.wgs) return;                 // whole workgroup
-  const int tile = v / p.splits, cs = v - tile * p.splits;
-  const int b = tile / p.tpr, ti = tile - b * p.tpr;
-  const int g0 = (int)((int64_t)ti * p.gpr / p.tpr), gn = (int)((int64_t)(ti + 1) * p.gpr / p.tpr) - g0;   // gn <= MT
+  if ((int)(blockIdx.x >> 3) >= p.per_xcd || v >= p.wgs) return false;           // whole workgroup
+  const int tile = p.splits == 1 ? v : divide(v, p.splits, p.r_splits);
+  at.cs = v - tile * p.splits;
+  at.b = divide(tile, p.tpr, p.r_tpr);
+  const int ti = tile - at.b * p.tpr;
+  at.g0 = ti * p.g_base + min(ti, p.g_more);
+  at.gn = p.g_base + (ti < p.g_more ? 1 : 0);       // <= MT
+  return true;
+}
+
+// Constants of N = 16, 32 or 64 / 3 channels in one or two loads per wave: a load of any size holds the address path
+// of the unit for 16 cycles, so three 16-channel loads cost as much as 3 KiB of weights.  Lanes [0, N) ask for m,
+// [N, 2 N) for s, [2 N, 3 N) for the bias if that fits; get() brings a channel's to where it is used.
+template <int N>
+struct Consts {
+  int32_t ms = 0, b = 0;
+  bool bias = false;
+  __device__ __forceinline__ void load_bias(const int32_t* pb, int c0, int lane) {   // (before the others: it is on one path only)
+    bias = pb != nullptr;
+    if (N == 32 && pb) b = pb[c0 + (lane & 31)];
+  }
+  __device__ __forceinline__ void load(const int32_t* pm, const int32_t* ps, const int32_t* pb, int c0, int lane) {
+    const int which = lane / N;
+    const int32_t* const q = which == 0 ? pm : which == 1 ? ps : (N == 16 && pb) ? pb : pm;
+    ms = q[c0 + (lane & (N - 1))];
+  }
+  __device__ __forceinline__ int32_t get(int32_t v, int from) const { return __builtin_amdgcn_ds_bpermute(4 * from, v); }
+  __device__ __forceinline__ int32_t m(int c) const { return get(ms, c); }
+  __device__ __forceinline__ int32_t s(int c) const { return get(ms, N + c); }
+  __device__ __forceinline__ int32_t bias_of(int c) const { return !bias ? 0 : N == 32 ? get(b, c) : get(ms, 2 * N + c); }
+};
+
+__device__ __forceinline__ uint32_t through_table(const unsigned char* lut, uint32_t pk) {
+  const uint32_t cd = pk ^ 0x80808080u;
+  return (uint32_t)lut[cd & 0xffu] | ((uint32_t)lut[(cd >> 8) & 0xffu] << 8) | ((uint32_t)lut[(cd >> 16) & 0xffu] << 16) |
+         ((uint32_t)lut[cd >> 24] << 24);
+}
+
+// ---- Tiles of four and seven groups: enough products per step to cover the loads of the next ones.
+// RAGGED: x or y (and the residual) are the caller's, rows of any length at any address
+template <int KCH, int MT, int NA, int NT, bool RAGGED>
+__global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
+  extern __shared__ __align__(128) unsigned char lds[];   // [Cin][128 B] tile, [kWaves] row buffers and tables
+  constexpr int CPW = KCH * 64 / kWaves;            // depthwise channels per wave
+  constexpr int NBLK = CPW / 16;                    // in blocks of 16
+  constexpr int NL = row_loads(16, MT, NA);
+  constexpr bool TIGHT = MT * NT > 8;               // (registers)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Place at;
+  if (!place(p, at)) return;
+  const int b = at.b, g0 = at.g0, gn = at.gn, cs = at.cs;
 
   unsigned char* const xs = lds;
-  const int rb = row_bytes(p.units, MT, NA);
+  const int rb = row_bytes(p.units, MT, NA) + 256;
   unsigned char* const rows = lds + KCH * 64 * 128 + wave * rb;
-  unsigned char* const lut = lds + KCH * 64 * 128 + kWaves * rb;
-  if (p.lut && tid < 64) reinterpret_cast<uint32_t*>(lut)[tid] = reinterpret_cast<const uint32_t*>(p.lut)[tid];
+  unsigned char* const lut = rows + rb - 256;       // (every wave its own copy: no barrier)
+  uint32_t lut_word = 0;
+  if (p.lut) lut_word = reinterpret_cast<const uint32_t*>(p.lut)[lane];
 
   // ---- depthwise half: 16 channels at a time.  Chunk L of the 16 rows (row L / units, chunk L % units)
   // is loaded by lane L % 64; chunks outside [0, Tin) are zero, the chunk a row ends in is masked.
   const int c_wave = wave * CPW;
-  int32_t xoff[4];                                  // byte offset of the chunk within the 16 rows
+  int32_t xoff[NL];                                 // byte offset of the chunk within the 16 rows
   uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
   const int t_last = p.Tin & ~15;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int L = lane + 64 * j, ch = L / p.units, u = L - ch * p.units;
+  for (int j = 0; j < NL; ++j) {
+    const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
     const int t = 16 * (g0 + p.o16 + u);
     if (ch < 16 && t >= 0 && t < p.Tin) in |= 1u << j;
     if (t == t_last) last |= 1u << j;
     xoff[j] = ch * p.xpitch + t;
   }
   const int8_t* const xw = p.x + (int64_t)b * p.xbs + (int64_t)c_wave * p.xpitch;
-  v4i xr[4];
+  v4i xr[NL];
   auto load_rows = [&](int blk) __attribute__((always_inline)) {
     const int8_t* const src = xw + (int64_t)(16 * blk) * p.xpitch;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NL; ++j) {
       xr[j] = (v4i){0, 0, 0, 0};
       if (in & (1u << j)) {
         if (RAGGED && (last & (1u << j))) xr[j] = load_row16(src + xoff[j] - t_last, t_last, p.Tin);
@@ -101,31 +174,38 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   };
   auto put_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NL; ++j) {
       if (!RAGGED && (last & (1u << j))) xr[j] = keep_bytes(xr[j], p.Tin & 15);
       if (lane + 64 * j < 16 * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = xr[j];
     }
   };
   const int ch_l = lane >> 2, n_l = lane & 3;
   v4i aw[3];                                        // weight quads, two steps ahead
-  int32_t db, dm, dsv;
   const v4i* const asrc = reinterpret_cast<const v4i*>(p.img) + (int64_t)(wave * NBLK) * (NA * 64) + lane;
   auto load_quad_weights = [&](int blk, int a) __attribute__((always_inline)) { aw[a % 3] = asrc[(blk * NA + a) * 64]; };
-  auto load_weights = [&](int blk) __attribute__((always_inline)) {
-    load_quad_weights(blk, 0);
-    load_quad_weights(blk, 1);
-    const int c = c_wave + 16 * blk + ch_l;
-    db = p.dbias ? p.dbias[c] : 0;
-    dm = p.dm[c];
-    dsv = p.ds[c];
-  };
+  Consts<CPW> dc;
   const unsigned char* const win = rows + ch_l * (16 * p.units) + 4 * (n_l + p.dwoff);
   // dword n_l of group q, row (channel) ch of the tile; the tile's unit q of a row sits in slot q ^ (row & 7)
   const uint32_t tw = (uint32_t)((c_wave + ch_l) * 128 + 4 * n_l) | (uint32_t)((ch_l & 7) << 4);
 
+  // what the pointwise half reads: 16 NT output channels of this wave
+  const int n = lane & 15, gi = lane >> 4;
+  const int co_w = (cs * kWaves + wave) * 16 * NT;
+  v4i wb[3][NT];
+  const v4i* const wsrc = reinterpret_cast<const v4i*>(p.w) + (int64_t)(co_w >> 4) * (KCH * 64) + lane;
+  auto load_w = [&](int kc) __attribute__((always_inline)) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) wb[kc % 3][nt] = wsrc[(nt * KCH + kc) * 64];
+  };
+  Consts<16 * NT> pc;
+
+  dc.load_bias(p.dbias, c_wave, lane);
   load_rows(0);
-  load_weights(0);
-  if (p.lut) __syncthreads();                       // (the table is complete)
+  load_quad_weights(0, 0);
+  load_quad_weights(0, 1);
+  dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
 #pragma unroll
   for (int blk = 0; blk < NBLK; ++blk) {
     put_rows();
@@ -140,6 +220,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
 #pragma unroll
     for (int a = 0; a < MT; ++a) read_quad(a);
     v4i acc[MT];
+    const int32_t db = dc.bias_of(16 * blk + ch_l);
 #pragma unroll
     for (int q = 0; q < MT; ++q) acc[q] = (v4i){db, db, db, db};
 #pragma unroll
@@ -156,8 +237,14 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       __builtin_amdgcn_sched_barrier(0);
       if (a == 1 && blk + 1 < NBLK) load_rows(blk + 1);   // on their way under the rest of the block
     }
-    const int32_t m = dm, s = dsv;
-    if (blk + 1 < NBLK) load_weights(blk + 1);
+    if (blk + 1 < NBLK) {
+      load_quad_weights(blk + 1, 0);
+      load_quad_weights(blk + 1, 1);
+    } else if (!TIGHT) {
+      load_w(0);
+      load_w(1);
+    }
+    const int32_t m = dc.m(16 * blk + ch_l), s = dc.s(16 * blk + ch_l);
     auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
 #pragma unroll
       for (int q = 0; q < MT; ++q) {
@@ -167,11 +254,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
           pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
         else
           pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
-        if (p.lut) {
-          const uint32_t cd = pk ^ 0x80808080u;
-          pk = (uint32_t)lut[cd & 0xffu] | ((uint32_t)lut[(cd >> 8) & 0xffu] << 8) |
-               ((uint32_t)lut[(cd >> 16) & 0xffu] << 16) | ((uint32_t)lut[cd >> 24] << 24);
-        }
+        if (p.lut) pk = through_table(lut, pk);
         *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
       }
     };
@@ -180,28 +263,13 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     else finish(std::true_type{}, std::false_type{});
   }
 
-  // ---- pointwise half: 16 NT output channels of this wave
-  const int n = lane & 15, gi = lane >> 4;
-  const int co_w = (cs * kWaves + wave) * 16 * NT;
-  v4i wb[3][NT];
-  const v4i* const wsrc = reinterpret_cast<const v4i*>(p.w) + (int64_t)(co_w >> 4) * (KCH * 64) + lane;
-  auto load_w = [&](int kc, v4i (&dst)[NT]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) dst[nt] = wsrc[(nt * KCH + kc) * 64];
-  };
-  load_w(0, wb[0]);
-  load_w(1, wb[1]);
-  int32_t mc[NT], sc[NT];
-  v4i acc[MT][NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int co = co_w + 16 * nt + n;
-    const int32_t bv = p.bias ? p.bias[co] : 0;
-    mc[nt] = p.m[co];
-    sc[nt] = p.s[co];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = (v4i){bv, bv, bv, bv};
+  // ---- pointwise half
+  if (TIGHT) {
+    load_w(0);
+    load_w(1);
   }
+  pc.load_bias(p.bias, co_w, lane);
+  pc.load(p.m, p.s, p.bias, co_w, lane);
   // residual rows and output rows: lane -> (row lane / 8 of 8, slot lane % 8), the unit in that slot
   const int u_l = (lane & 7) ^ (lane >> 3);
   const bool u_ok = u_l < gn;
@@ -218,11 +286,18 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       }
   };
   __syncthreads();                                  // the tile is complete
+  v4i acc[MT][NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int32_t bv = pc.bias_of(16 * nt + n);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = (v4i){bv, bv, bv, bv};
+  }
   const int l16 = lane & 15, jr = l16 >> 1;
   const uint32_t abase = (uint32_t)((8 * gi + jr) * 128 + 8 * (l16 & 1)) | (uint32_t)(jr << 4);
 #pragma unroll
   for (int kc = 0; kc < KCH; ++kc) {
-    if (kc + 2 < KCH) load_w(kc + 2, wb[(kc + 2) % 3]);
+    if (kc + 2 < KCH) load_w(kc + 2);
     if (kc + 2 == KCH && p.res) load_res();         // (into what the weight ring no longer needs)
     __builtin_amdgcn_sched_barrier(0);
     const unsigned char* ab = xs + kc * 8192;
@@ -244,6 +319,12 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
         acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, wb[kc % 3][nt], acc[mt][nt], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  int32_t mc[NT], sc[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    mc[nt] = pc.m(16 * nt + n);
+    sc[nt] = pc.s(16 * nt + n);
   }
 
   // ---- epilogue, 16 channels at a time through the wave's own staging block (its row buffer is free):
@@ -304,21 +385,322 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   }
 }
 
-template <int KCH, int MT, int NA, int NT, bool RAGGED>
+// ---- Tiles of one and two groups: launches of few frames, where the products are nothing and the loads
+// everything.  A load instruction of any size holds a compute unit's address path for 16 cycles; with 16 waves asking
+// for weight images of four bytes per tap, for constants three at a time and for two blocks' rows apart, one workgroup
+// (512 -> 256 channels, k = 75) had 592 loads, 9500 of the 15300 cycles it took, and up to ten round trips
+// one after the other.  Here
+//   - the weights come as they are, zero-padded rows of 16 NA bytes (sep_image's first part), are laid into the
+//     wave's own rows of the pointwise tile, which are written later, and become Toeplitz rows by one byte
+//     permutation per dword;
+//   - rows, weights and constants of all the wave's channels are asked for at once, with them the residual, constants and
+//     weights of the pointwise half (of 512 x 32 channels per wave the second half after the depthwise products), and
+//     nothing waits in between;
+//   - both blocks of 16 channels are multiplied side by side; residual and output rows are two 16-byte
+//     units wide, one load and one store per wave.
+// 288 loads, 13400 cycles.  In a chain of such pairs over 50 groups, us a launch: 512 -> 512, k = 75 8.53 -> 7.87,
+// 7.54 with KS = 2 below; k = 51 7.91 -> 7.09, 6.67; 256 -> 256, k = 33 5.58 -> 4.99, 4.83.
+// KS = 2, where twice as many workgroups still find units of their own: the waves are two groups over the input
+// channels of the pointwise half, a workgroup has half as many output channels, its half of the weights and of the
+// tile's reads per wave, and the two partial sums meet in LDS.
+template <int KCH, int MT, int NA, int NT, int KS, bool RAGGED>
+__global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
+  static_assert(MT <= 2, "two units per staged row");
+  extern __shared__ __align__(128) unsigned char lds[];   // [Cin][128 B] tile, [kWaves] row buffers and tables
+  constexpr int CPW = KCH * 64 / kWaves;            // depthwise channels per wave
+  constexpr int NBLK = CPW / 16;                    // in blocks of 16
+  constexpr int NL = row_loads(CPW, MT, NA);
+  constexpr int WS = NA | 1;                        // 16-byte units of a weight row in LDS (odd: 16 rows in different banks)
+  constexpr int NWL = (CPW * NA + 63) / 64;
+  static_assert(WS <= 8, "weights fit the wave's tile rows");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Place at;
+  if (!place(p, at)) return;
+  const int g0 = at.g0, c_wave = wave * CPW;
+  unsigned char* const xs = lds;
+  const int rb = small_row_bytes(CPW, p.units, MT, NA) + 256;
+  unsigned char* const rows = lds + KCH * 64 * 128 + wave * rb;
+  unsigned char* const lut = rows + rb - 256;       // (every wave its own copy: no barrier)
+  unsigned char* const wlds = xs + c_wave * 128;
+  const int n = lane & 15, gi = lane >> 4;
+  constexpr int NWC = kWaves / KS, KC = KCH / KS;   // waves over output channels; chunks per wave
+  const int wc = wave % NWC, ks = wave / NWC;
+  const int co_w = (at.cs * NWC + wc) * 16 * NT;
+
+  // ---- everything is asked for; what only some launches have comes first, so that the waits for the rest stay exact
+  uint32_t lut_word = 0;
+  if (p.lut) lut_word = reinterpret_cast<const uint32_t*>(p.lut)[lane];
+  Consts<CPW> dc;
+  Consts<16 * NT> pc;
+  dc.load_bias(p.dbias, c_wave, lane);
+  pc.load_bias(p.bias, co_w, lane);
+  // residual and output: lane -> row lane / 2 of the wave's 16 NT, unit lane % 2
+  const int u_l = lane & 1, t_l = 16 * (g0 + u_l);
+  const bool y_ok = u_l < at.gn && lane < 32 * NT && ks == 0;
+  const int64_t yrow = (int64_t)at.b * p.ybs + (int64_t)(co_w + (lane >> 1)) * p.ypitch;
+  v4i rr = {0, 0, 0, 0};
+  if (p.res && y_ok) rr = RAGGED && p.yragged ? load_row16(p.res + yrow, t_l, p.Tout) : *reinterpret_cast<const v4i*>(p.res + yrow + t_l);
+  // weights: chunk L of the wave's CPW x NA
+  v4i wr[NWL];
+  {
+    const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
+#pragma unroll
+    for (int j = 0; j < NWL; ++j) wr[j] = src[min(lane + 64 * j, CPW * NA - 1)];
+  }
+  dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
+  // rows: chunk L of the wave's CPW x units; chunks outside [0, Tin) are zero, the chunk a row ends in is masked
+  v4i xr[NL];
+  uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
+  {
+    const int8_t* const xw = p.x + (int64_t)at.b * p.xbs + (int64_t)c_wave * p.xpitch;
+    const int t_last = p.Tin & ~15;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
+      const int t = 16 * (g0 + p.o16 + u);
+      const bool on = ch < CPW && t >= 0 && t < p.Tin;
+      if (on) in |= 1u << j;
+      if (t == t_last) last |= 1u << j;
+      xr[j] = (v4i){0, 0, 0, 0};
+      if (RAGGED) {
+        if (on) xr[j] = t == t_last ? load_row16(xw + ch * p.xpitch, t, p.Tin) : *reinterpret_cast<const unaligned_chunk16*>(xw + ch * p.xpitch + t);
+      } else if (64 * j < CPW * p.units) {          // (uniform; lanes without a chunk read the first one and drop it)
+        xr[j] = *reinterpret_cast<const v4i*>(xw + (on ? ch * p.xpitch + t : 0));
+      }
+    }
+  }
+  pc.load(p.m, p.s, p.bias, co_w, lane);
+  v4i wb[KC][NT];
+  const v4i* const wsrc = reinterpret_cast<const v4i*>(p.w) + (int64_t)(co_w >> 4) * (KCH * 64) + ks * (KC * 64) + lane;
+  auto load_w = [&](int kc) __attribute__((always_inline)) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) wb[kc][nt] = wsrc[(nt * KCH + kc) * 64];
+  };
+  constexpr int FIRST = KC * NT > 8 ? KC / 2 : KC;  // (registers)
+#pragma unroll
+  for (int kc = 0; kc < FIRST; ++kc) load_w(kc);
+  __builtin_amdgcn_sched_barrier(0);
+  if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
+
+  // ---- depthwise half
+#pragma unroll
+  for (int j = 0; j < NWL; ++j) {
+    const int L = lane + 64 * j, ch = L / NA;
+    if (L < CPW * NA) *reinterpret_cast<v4i*>(wlds + 16 * (ch * WS + L - ch * NA)) = wr[j];
+  }
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    v4i r = xr[j];
+    if (!RAGGED) {
+      if (!(in & (1u << j))) r = (v4i){0, 0, 0, 0};
+      if (last & (1u << j)) r = keep_bytes(r, p.Tin & 15);
+    }
+    if (lane + 64 * j < CPW * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = r;
+  }
+  asm volatile("" ::: "memory");                    // (lanes read what other lanes of the wave wrote: LDS is in order)
+  __builtin_amdgcn_sched_barrier(0);
+  const int ch_l = lane >> 2, n_l = lane & 3;
+  // Toeplitz row m = lane % 4 of four taps: bytes 4 - m .. 7 - m of (this dword, the one before)
+  const uint32_t sel = 0x07060504u - 0x01010101u * (uint32_t)n_l;
+  const unsigned char* const win = rows + ch_l * (16 * p.units) + 4 * (n_l + p.dwoff);
+  const unsigned char* const wrow = wlds + ch_l * (16 * WS);
+  constexpr int LA = 2, WQ = MT + LA;               // quads read ahead
+  uint32_t wd[NBLK][WQ][4];
+  v4i aq[NBLK][LA + 1];
+  uint32_t before[NBLK];
+  auto read_win = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        wd[blk][a % WQ][i] = *reinterpret_cast<const uint32_t*>(win + 256 * blk * p.units + 16 * a + 4 * i);
+  };
+  auto read_taps = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk) aq[blk][a % (LA + 1)] = *reinterpret_cast<const v4i*>(wrow + 256 * blk * WS + 16 * a);
+  };
+#pragma unroll
+  for (int a = 0; a < LA; ++a) read_taps(a);
+#pragma unroll
+  for (int a = 0; a < MT + LA - 1; ++a) read_win(a);
+  v4i dacc[NBLK][MT];
+#pragma unroll
+  for (int blk = 0; blk < NBLK; ++blk) {
+    const int32_t db = dc.bias_of(16 * blk + ch_l);
+    before[blk] = 0;
+#pragma unroll
+    for (int q = 0; q < MT; ++q) dacc[blk][q] = (v4i){db, db, db, db};
+  }
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    if (a + LA < NA) {
+      read_taps(a + LA);
+      read_win(a + MT + LA - 1);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t t[NBLK];
+#pragma unroll
+      for (int blk = 0; blk < NBLK; ++blk) {
+        const uint32_t d = (uint32_t)aq[blk][a % (LA + 1)][i];
+        t[blk] = __builtin_amdgcn_perm(d, before[blk], sel);
+        before[blk] = d;
+      }
+      if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
+#pragma unroll
+        for (int q = 0; q < MT; ++q)
+#pragma unroll
+          for (int blk = 0; blk < NBLK; ++blk)
+            dacc[blk][q] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)t[blk], (int)wd[blk][(a + q) % WQ][i], dacc[blk][q], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int kc = FIRST; kc < KC; ++kc) load_w(kc);
+  // dword n_l of group q, row (channel) ch of the tile; the tile's unit q of a row sits in slot q ^ (row & 7)
+  const uint32_t tw = (uint32_t)((c_wave + ch_l) * 128 + 4 * n_l) | (uint32_t)((ch_l & 7) << 4);
+#pragma unroll
+  for (int blk = 0; blk < NBLK; ++blk) {
+    const int32_t m = dc.m(16 * blk + ch_l), s = dc.s(16 * blk + ch_l);
+    auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < MT; ++q) {
+        const int32_t a4[4] = {dacc[blk][q][0], dacc[blk][q][1], dacc[blk][q][2], dacc[blk][q][3]};
+        uint32_t pk;
+        if constexpr (decltype(fast_tag)::value)
+          pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
+        else
+          pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
+        if (p.lut) pk = through_table(lut, pk);
+        *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
+      }
+    };
+    if (!__all(s >= kShortMin && s <= kShortMax)) finish(std::false_type{}, std::false_type{});
+    else if (p.drelu) finish(std::true_type{}, std::true_type{});
+    else finish(std::true_type{}, std::false_type{});
+  }
+
+  // ---- pointwise half; operand of group mt, chunk kc: item kc MT + mt of one stream, AH of them on their way
+  __syncthreads();                                  // the tile is complete
+  const int l16 = lane & 15, jr = l16 >> 1;
+  const uint32_t abase = (uint32_t)((8 * gi + jr) * 128 + 8 * (l16 & 1)) | (uint32_t)(jr << 4);
+  constexpr int AH = 3, AR = AH + 1;
+  v2i ar[AR][2];
+  auto read_item = [&](int i) __attribute__((always_inline)) {
+    const unsigned char* const q = xs + (ks * KC + i / MT) * 8192 + (abase ^ (uint32_t)((i % MT) << 4));
+    ar[i % AR][0] = read_tr8(q);
+    ar[i % AR][1] = read_tr8(q + 4096);
+  };
+#pragma unroll
+  for (int i = 0; i < AH; ++i) read_item(i);
+  v4i acc[MT][NT];
+  int32_t mc[NT], sc[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    int32_t bv = pc.bias_of(16 * nt + n);
+    if (ks != 0) bv = 0;
+    mc[nt] = pc.m(16 * nt + n);
+    sc[nt] = pc.s(16 * nt + n);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = (v4i){bv, bv, bv, bv};
+  }
+#pragma unroll
+  for (int i = 0; i < KC * MT; ++i) {
+    const v4i a = {ar[i % AR][0].x, ar[i % AR][0].y, ar[i % AR][1].x, ar[i % AR][1].y};
+    if (i + AH < KC * MT) read_item(i + AH);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+      acc[i % MT][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, wb[i / MT][nt], acc[i % MT][nt], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  if constexpr (KS == 2) {                          // (the row buffers are free)
+    static_assert(MT * NT <= 2, "the sums fit a row buffer");
+    if (ks == 1) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<v4i*>(rows + 1024 * (mt * NT + nt) + 16 * lane) = acc[mt][nt];
+    }
+    __syncthreads();
+    if (ks == 1) return;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += *reinterpret_cast<const v4i*>(rows + NWC * rb + 1024 * (mt * NT + nt) + 16 * lane);
+  }
+
+  // ---- epilogue through the wave's own staging block (its row buffer is free), 32 bytes per channel: lane
+  // (n, gi) holds frames 16 mt + 4 gi + (0..3) of channel 16 nt + n
+  unsigned char* const st = rows;
+  bool ok = true;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (p.res ? kShortMaxRes : kShortMax);
+  const bool fast = __all(ok);
+  auto epilogue = [&](auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
+    constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
+    if (RES) {
+      if (lane < 32 * NT) *reinterpret_cast<v4i*>(st + 16 * lane) = rr;
+      asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        uint32_t* const sp = reinterpret_cast<uint32_t*>(st + 32 * (16 * nt + n) + 16 * mt + 4 * gi);
+        const int32_t a4[4] = {acc[mt][nt][0], acc[mt][nt][1], acc[mt][nt][2], acc[mt][nt][3]};
+        const uint32_t rw = RES ? *sp : 0u;
+        if constexpr (FAST)
+          *sp = requant_short4<RES, RELU>(a4, mc[nt], sc[nt] - 32, 1 << ((sc[nt] - 33) & 31), rw);
+        else
+          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, p.relu ? 0 : -128, 127);
+      }
+    asm volatile("" ::: "memory");
+  };
+  const std::true_type T{};
+  const std::false_type F{};
+  if (p.res) {
+    if (!fast) epilogue(F, T, F);
+    else if (p.relu) epilogue(T, T, T);
+    else epilogue(T, T, F);
+  } else {
+    if (!fast) epilogue(F, F, F);
+    else if (p.relu) epilogue(T, F, T);
+    else epilogue(T, F, F);
+  }
+  const v4i o = *reinterpret_cast<const v4i*>(st + 16 * (lane & (32 * NT - 1)));
+  if (RAGGED && p.yragged) {                        // (uniform)
+    if (y_ok) store_row16(p.y + yrow, t_l, p.Tout, o);
+  } else {
+    const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
+        p.y + (int64_t)at.b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
+    const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};
+    __builtin_amdgcn_raw_buffer_store_b128(ov, yrs, y_ok ? (uint32_t)(lane >> 1) * (uint32_t)p.ypitch + (uint32_t)t_l : 0xfffffff0u, 0,
+                                           kStoreThrough);
+  }
+}
+
+template <int KCH, int MT, int NA, int NT, int KS, bool RAGGED>
 hipError_t launch_t(const SepParams& p, size_t lds, hipStream_t st) {
   static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
-  if (const hipError_t e = ensure_max_dynamic_lds((const void*)sep_kernel<KCH, MT, NA, NT, RAGGED>, lds_raised); e != hipSuccess)
-    return e;
-  return launch_kernel(sep_kernel<KCH, MT, NA, NT, RAGGED>, dim3((unsigned)(8 * p.per_xcd)), dim3(64 * kWaves), lds, st, p);
+  void (*kernel)(SepParams);
+  if constexpr (MT <= 2) kernel = sep_small_kernel<KCH, MT, NA, NT, KS, RAGGED>;
+  else kernel = sep_kernel<KCH, MT, NA, NT, RAGGED>;
+  if (const hipError_t e = ensure_max_dynamic_lds((const void*)kernel, lds_raised); e != hipSuccess) return e;
+  return launch_kernel(kernel, dim3((unsigned)(8 * p.per_xcd)), dim3(64 * kWaves), lds, st, p);
 }
 
 // the instantiations of one tap range (ragged rows: at most 4 groups, more do not fit the registers)
 template <int NA>
 hipError_t launch_na(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st) {
-#define QASR_CASE(K, M, N, R) if (c.KCH == K && c.MT == M && c.NT == N && c.ragged == R) return launch_t<K, M, NA, N, R>(p, lds, st);
-#define QASR_MTS(K, N) QASR_CASE(K, 1, N, false) QASR_CASE(K, 2, N, false) QASR_CASE(K, 4, N, false) QASR_CASE(K, 7, N, false) \
-                       QASR_CASE(K, 1, N, true) QASR_CASE(K, 2, N, true) QASR_CASE(K, 4, N, true)
+#define QASR_CASE(K, M, N, S, R) if (c.KCH == K && c.MT == M && c.NT == N && c.KS == S && c.ragged == R) return launch_t<K, M, NA, N, S, R>(p, lds, st);
+#define QASR_MTS(K, N) QASR_CASE(K, 1, N, 1, false) QASR_CASE(K, 2, N, 1, false) QASR_CASE(K, 4, N, 1, false) QASR_CASE(K, 7, N, 1, false) \
+                       QASR_CASE(K, 1, N, 1, true) QASR_CASE(K, 2, N, 1, true) QASR_CASE(K, 4, N, 1, true)
   QASR_MTS(4, 1) QASR_MTS(4, 2) QASR_MTS(8, 1) QASR_MTS(8, 2)
+  QASR_CASE(4, 1, 1, 2, false) QASR_CASE(4, 2, 1, 2, false) QASR_CASE(8, 1, 1, 2, false) QASR_CASE(8, 2, 1, 2, false)
+  QASR_CASE(4, 1, 1, 2, true) QASR_CASE(4, 2, 1, 2, true) QASR_CASE(8, 1, 1, 2, true) QASR_CASE(8, 2, 1, 2, true)
 #undef QASR_MTS
 #undef QASR_CASE
   return hipErrorInvalidValue;

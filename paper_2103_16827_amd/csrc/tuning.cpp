@@ -43,8 +43,8 @@ Tuning read_env() {
     if (sscanf(e, "%d,%d", &mt, &ks) >= 1) { t.pww_mt = mt; t.pww_ks = ks; }
   }
   if (const char* e = getenv("QASR_SEP")) {
-    int mt = 0, nt = 0;
-    if (sscanf(e, "%d,%d", &mt, &nt) >= 1) { t.sep_mt = mt; t.sep_nt = nt; }
+    int mt = 0, nt = 0, ks = 0;
+    if (sscanf(e, "%d,%d,%d", &mt, &nt, &ks) >= 1) { t.sep_mt = mt; t.sep_nt = nt; t.sep_ks = ks; }
   }
   if (const char* e = getenv("QASR_PWT_MT")) t.pwt_mt = atoi(e);
   if (const char* e = getenv("QASR_SLOT_DEPTH")) {

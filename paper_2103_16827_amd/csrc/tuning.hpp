@@ -17,7 +17,8 @@
 //   QASR_NO_PW_WIDE, QASR_PW_WIDE            pw_wide: never / wherever it can
 //   QASR_PWW = "MT,KS"                      pw_wide: groups per tile, wave groups over the input channels (0: free)
 //   QASR_NO_SEP                             encoder: no depthwise + pointwise pair in one launch
-//   QASR_SEP = "MT,NT"                      the same: groups per tile, 16-channel columns per wave (0: free)
+//   QASR_SEP = "MT,NT[,KS]"                 the same: groups per tile, 16-channel columns per wave (0: free), wave groups over
+//                                           the input channels (1 where NT is given alone)
 //   QASR_TEAM                               encoder: plan runs of layers for the persistent team kernel
 //                                           (experimental, off unless set)
 #pragma once
@@ -31,7 +32,7 @@ struct Tuning {
   int dw_r = 0;
   int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0;
   int pwt_mt = 0;
-  int sep_mt = 0, sep_nt = 0, pww_mt = 0, pww_ks = 0;
+  int sep_mt = 0, sep_nt = 0, sep_ks = 0, pww_mt = 0, pww_ks = 0;
   int slot_depth = 4;
 };
 
