@@ -49,10 +49,13 @@ def op_algorithmic(op, B):
 
 def launch_algorithmic(ops, B):
     """The same of one launch: of a depthwise + pointwise pair, the tensor between the two is neither
-    written nor read."""
+    written nor read; a projection in the pair's launch reads the input that the pair reads."""
     byts, macs = (sum(v) for v in zip(*(op_algorithmic(o, B) for o in ops)))
     for a, b in zip(ops, ops[1:]):
-        byts -= B * a.Cout * a.Tout + B * b.Cin * b.Tin
+        if b.depthwise:
+            byts -= B * b.Cin * b.Tin
+        else:
+            byts -= B * a.Cout * a.Tout + B * b.Cin * b.Tin
     return byts, macs
 
 

@@ -298,7 +298,8 @@ size_t qasr_encoder_workspace_bytes(const qasr_encoder* e);
  * of the last op; workspace: device, 256-byte aligned, >= qasr_encoder_workspace_bytes(e).
  * Enqueues at most n_ops kernels (plus one per activation, plus one where contractions are split)
  * and returns; allocates nothing; may be captured into a HIP graph.  A depthwise layer and the pointwise layer that is the only
- * reader of its output run as one launch where their shapes allow (same bits). */
+ * reader of its output run as one launch where their shapes allow (same bits), and with them a pointwise layer
+ * of the pair's input just before it, whose output neither of them reads. */
 qasr_status qasr_encoder_forward(const qasr_encoder* e, const int8_t* x, int8_t* y,
                                  void* workspace, size_t workspace_bytes, void* stream);
 
@@ -360,9 +361,10 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
  * "dw_pipe", "dw_mfma"; pointwise: "pw_pipe", "pw_tile"; dense and any other pointwise shape:
  * "conv_pipe", "gemm_mfma"; any shape: "conv_generic"; static storage, NULL if i is out of range).
  *   qasr_encoder_op_launch: what qasr_encoder_forward launches for it over 16-byte aligned x and y:
- *     the op that the launch begins with (i, or i - 1 where op i is the pointwise half of a depthwise +
- *     pointwise pair; -1 if i is out of range), and in *kernel (unless NULL) the kernel's name: "sep"
- *     for such a pair, "pw_wide" for pointwise layers of the pw_pipe, pw_tile and gemm_mfma families
+ *     the op that the launch begins with (i; i - 1 where op i is the pointwise half of a depthwise +
+ *     pointwise pair; one less for a pair that runs together with the pointwise layer before it, a residual
+ *     projection of the same tensor; -1 if i is out of range), and in *kernel (unless NULL) the kernel's
+ *     name: "sep" for these, "pw_wide" for pointwise layers of the pw_pipe, pw_tile and gemm_mfma families
  *     that this kernel runs faster, else the family's.  HOST only. */
 int32_t qasr_encoder_num_ops(const qasr_encoder* e);
 const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i);

@@ -164,6 +164,9 @@ struct qasr_encoder {
     // what it writes.  Its weight image.
     bool sep = false;
     const uint32_t* sep_img = nullptr;
+    // This pointwise op (a block's residual projection) and the pair after it read the same tensor and touch none of
+    // each other's: the three may run as one launch.
+    bool sep_proj = false;
     int32_t in_channels = 0;  // channels of the slot read (p.Cin, or more for a channel-prefix view)
   };
   std::vector<Op> ops;
@@ -863,6 +866,12 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
       img_off[i] = img_bytes;
       img_bytes += round256(qasr::sep_image_bytes(dp));
     }
+    for (int32_t i = 0; i + 2 < n_ops; ++i) {
+      const qasr_op &o = ops[i], &d = ops[i + 1];
+      if (!e->ops[i + 1].sep || o.act || o.res_slot >= 0 || o.d.groups != 1 || o.in_slot != d.in_slot) continue;
+      qasr_encoder::Op &r = e->ops[i], &dw = e->ops[i + 1], &pw = e->ops[i + 2];   // (their slots are buffers)
+      r.sep_proj = r.in_channels == dw.in_channels && r.out_slot != dw.in_slot && r.out_slot != pw.out_slot && r.out_slot != pw.res_slot;
+    }
     hipError_t he = img_bytes ? hipMalloc((void**)&e->sep_images, img_bytes) : hipSuccess;
     for (int32_t i = 0; i < n_ops && he == hipSuccess; ++i) {
       qasr_encoder::Op& op = e->ops[i];
@@ -907,6 +916,11 @@ const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i) {
   return family_name(e->ops[i].family);
 }
 
+// the pair at op i may take the projection r before it along
+static bool projection_with_pair(const ConvParams& r, const ConvParams& d, const ConvParams& q) {
+  return qasr::sep_supported(d, q) && qasr::sep_projection_supported(d, q, r);
+}
+
 // whether op i and op i + 1 run as one launch over 16-byte aligned, dense input and output
 static bool runs_as_pair(const qasr_encoder* e, size_t i) {
   if (!e->ops[i].sep) return false;
@@ -916,8 +930,23 @@ static bool runs_as_pair(const qasr_encoder* e, size_t i) {
   return qasr::sep_supported(p, q);
 }
 
+// the same for op i, a projection, with ops i + 1 and i + 2
+static bool runs_with_pair(const qasr_encoder* e, size_t i) {
+  if (!e->ops[i].sep_proj) return false;
+  ConvParams r = e->ops[i].p, p = e->ops[i + 1].p, q = e->ops[i + 2].p;
+  rows_of(e, i, 0, 0, r);
+  rows_of(e, i + 1, 0, 0, p);
+  rows_of(e, i + 2, 0, 0, q);
+  return projection_with_pair(r, p, q);
+}
+
 int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** kernel) {
   if (!e || i < 0 || i >= (int32_t)e->ops.size()) return -1;
+  for (int32_t first = i; first >= 0 && first >= i - 2; --first)
+    if (runs_with_pair(e, (size_t)first)) {
+      if (kernel) *kernel = "sep";
+      return first;
+    }
   const bool second = i > 0 && runs_as_pair(e, (size_t)i - 1);
   if (kernel) {
     ConvParams p = e->ops[i].p;
@@ -1001,6 +1030,18 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     bind(i, p);
     if (i > 0)
       if (const hipError_t be = begin(i); be != hipSuccess) return hip_status(be);
+    if (op.sep_proj && how.pairs) {
+      ConvParams d, q;
+      bind(i + 1, d);
+      bind(i + 2, q);
+      d.act_lut = e->ops[i + 1].act_table;
+      if (projection_with_pair(p, d, q)) {
+        const hipError_t se = qasr::launch_sep(d, e->ops[i + 1].sep_img, q, p, st);
+        if (se != hipSuccess) return hip_status(se);
+        i += 2;
+        continue;
+      }
+    }
     if (op.sep && how.pairs) {
       ConvParams q;
       bind(i + 1, q);

@@ -65,7 +65,7 @@ size_t lds_bytes(int KCH, int units, int MT, int NA) {
 // unit, one workgroup at a time: its matrix pipes (10 cycles per 4x4x4 product, 17.7 per 16x16x64 one),
 // half hidden under them its 64 bytes per cycle from the L2 (weight image and packed weights, which every
 // workgroup streams whole), and the latency of its first loads and last stores.
-bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int groups_per_row, int cus, SepChoice& c) {
+bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int groups_per_row, int cus, bool proj, SepChoice& c) {
   static const int MTs[] = {1, 2, 4, 7};
   c.KCH = d.Cout / 64;
   c.NA = g.NA;
@@ -84,12 +84,17 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
         if (lds > 160 * 1024) continue;
         const int splits = q.Cout / (256 / KS * NT);
         const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
-        if (wgs > max_workgroups(64 * sep::kWaves)) continue;
+        if (wgs * (proj ? 2 : 1) > max_workgroups(64 * sep::kWaves)) continue;
         const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 4 / KS;
         const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 64.0 * units * 16;
         const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
         const int64_t n = (wgs + cus - 1) / cus;
-        const double cost = (double)n * (3.5 + work);
+        double cost = (double)n * (3.5 + work);
+        if (proj) {                                 // as many workgroups again, without the depthwise half: as a list
+          const double work2 = (MT * NT * c.KCH * 17.7 * 4 / KS + 0.5 * (NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 1024.0 * MT) / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
+          const double list = (double)wgs * (5.0 + work + work2) / cus;
+          if (list > cost) cost = list;
+        }
         if (cost < best) { best = cost; c.MT = MT; c.NT = NT; c.KS = KS; c.splits = splits; }
       }
     }
@@ -97,7 +102,7 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
   return best < 1e300;
 }
 
-bool plan(const ConvParams& d, const ConvParams& q, int cus, Geometry& g, SepChoice& c) {
+bool plan(const ConvParams& d, const ConvParams& q, int cus, bool proj, Geometry& g, SepChoice& c) {
   if (tuning().no_sep || !geometry(d, g)) return false;
   if (d.Cout != 256 && d.Cout != 512) return false;
   if (q.depthwise || q.k != 1 || q.stride != 1 || q.pl != 0 || !q.w_packed || q.Cin != d.Cout || q.n_res_more || q.act_lut)
@@ -108,7 +113,7 @@ bool plan(const ConvParams& d, const ConvParams& q, int cus, Geometry& g, SepCho
   if ((int64_t)16 * (d.Tin + d.xpad) > 0x7fffffffLL || (int64_t)q.Cout * (q.Tout + q.ypad) > 0x7fffff00LL) return false;
   if (d.Tin < 4 || q.Tout < 4) return false;
   c.ragged = x_ragged(d) || y_ragged(q);
-  return pick(d, q, g, (q.Tout + 15) / 16, cus, c);
+  return pick(d, q, g, (q.Tout + 15) / 16, cus, proj, c);
 }
 
 }  // namespace
@@ -116,7 +121,17 @@ bool plan(const ConvParams& d, const ConvParams& q, int cus, Geometry& g, SepCho
 bool sep_supported(const ConvParams& d, const ConvParams& q) {
   Geometry g;
   SepChoice c;
-  return plan(d, q, 256, g, c);
+  return plan(d, q, 256, false, g, c);
+}
+
+bool sep_projection_supported(const ConvParams& d, const ConvParams& q, const ConvParams& r) {
+  Geometry g;
+  SepChoice c;
+  if (!plan(d, q, 256, true, g, c) || c.ragged) return false;
+  return !r.depthwise && r.k == 1 && r.stride == 1 && r.pl == 0 && r.w_packed && !r.res && !r.n_res_more && !r.act_lut &&
+         r.B == d.B && r.Cin == d.Cin && r.Cout == q.Cout && r.xbs == d.xbs && r.Tin + r.xpad == d.Tin + d.xpad && r.ybs == q.ybs &&
+         r.Tout + r.ypad == q.Tout + q.ypad && (r.Tout + 15) / 16 == (q.Tout + 15) / 16 && (uintptr_t)r.w % 16 == 0 &&
+         (uintptr_t)r.y % 16 == 0 && r.x == d.x;
 }
 
 size_t sep_image_bytes(const ConvParams& d) {
@@ -131,10 +146,10 @@ hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st) 
                        g.NA, img, img + rows_image_bytes(d.Cout, g.NA) / 4);
 }
 
-hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, hipStream_t st) {
+static hipError_t launch(const ConvParams& d, const uint32_t* img, const ConvParams& q, const ConvParams* r, hipStream_t st) {
   Geometry g;
   SepChoice c;
-  if (!plan(d, q, compute_units(), g, c)) return hipErrorInvalidValue;
+  if (!plan(d, q, compute_units(), r != nullptr, g, c)) return hipErrorInvalidValue;
   SepParams p{};
   p.x = d.x; p.img = c.MT <= 2 ? img : img + rows_image_bytes(d.Cout, g.NA) / 4; p.dbias = d.bias; p.dm = d.m; p.ds = d.s; p.lut = d.act_lut;
   p.xbs = d.xbs; p.xpitch = d.Tin + d.xpad; p.Tin = d.Tin;
@@ -158,6 +173,11 @@ hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams
   const int C = c.MT <= 2 ? 4 * c.KCH : 16;      // rows a wave brings in at a time
   if (C * p.units > 64 * sep::row_loads(C, c.MT, c.NA)) return hipErrorInvalidValue;
   p.per_xcd = (p.wgs + 7) / 8;
+  if (r) {
+    p.w2 = r->w; p.bias2 = r->bias; p.m2 = r->m; p.s2 = r->s; p.y2 = r->y; p.relu2 = r->relu;
+    p.wgs2 = p.wgs;
+    p.per_xcd2 = p.per_xcd;
+  }
   const size_t lds = lds_bytes(c.KCH, p.units, c.MT, c.NA);
   switch (c.NA) {
     case 3: return launch_sep_na3(c, p, lds, st);
@@ -165,6 +185,14 @@ hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams
     case 5: return launch_sep_na5(c, p, lds, st);
     default: return launch_sep_na6(c, p, lds, st);
   }
+}
+
+hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, hipStream_t st) {
+  return launch(d, img, q, nullptr, st);
+}
+hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, const ConvParams& r, hipStream_t st) {
+  if (!sep_projection_supported(d, q, r)) return hipErrorInvalidValue;
+  return launch(d, img, q, &r, st);
 }
 
 }  // namespace qasr

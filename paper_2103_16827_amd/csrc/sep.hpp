@@ -32,6 +32,12 @@ struct SepParams {
   int32_t tpr, g_base, g_more;
   int32_t splits;                    // workgroups per tile, each with its own run of output channels
   int32_t wgs, per_xcd;              // workgroups in all, and per XCD
+  // a second pointwise layer of x itself (a block's residual projection), by workgroups of its own in the same
+  // launch: widths, rows and tiles of the first; wgs2 == 0: none
+  const int8_t* w2;
+  const int32_t *bias2, *m2, *s2;
+  int8_t* y2;
+  int32_t relu2, wgs2, per_xcd2;
   int32_t units_inv;                 // ceil(2^16 / units): L / units = L units_inv >> 16 for L < 512, units <= 15
   float r_splits, r_tpr;             // reciprocals of the two
 };
@@ -45,6 +51,10 @@ size_t sep_image_bytes(const ConvParams& d);
 hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st);
 // d.x, q.res, q.y set; d.y and q.x are not used
 hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, hipStream_t st);
+// Can the pointwise layer r, which reads d's input and whose output neither d nor q touches, run in the pair's launch?
+// Only its geometry, and of its pointers their alignment, are looked at.
+bool sep_projection_supported(const ConvParams& d, const ConvParams& q, const ConvParams& r);
+hipError_t launch_sep(const ConvParams& d, const uint32_t* img, const ConvParams& q, const ConvParams& r, hipStream_t st);
 
 // one translation unit per tap range (sep_na3.hip ...): the launcher of its instantiations
 hipError_t launch_sep_na3(const SepChoice& c, const SepParams& p, size_t lds, hipStream_t st);

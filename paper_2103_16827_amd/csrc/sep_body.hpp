@@ -25,6 +25,11 @@
 //
 // Two kernels: launches of few frames are bound by what a workgroup loads (sep_small_kernel), the others by their
 // products (sep_kernel).  QuartzNet-15x5, one utterance of 1237 frames 626 -> 548 us, 32 utterances of 1600 1387 -> 1323.
+//
+// A block's residual projection, which reads what its first pair reads, runs in the pair's launch: workgroups of
+// their own take x itself for the tile and go on with the pointwise half.  At few frames they find units that the pair
+// leaves free, at many they start on each unit as it finishes; either way a launch and its chain of first loads
+// disappear (QuartzNet-15x5, 1 x 1237 548 -> 486 us, 32 x 1600 1316 -> 1245; 10x5, 8 x 1104 468 -> 441).
 #pragma once
 #include "sep.hpp"
 
@@ -75,17 +80,35 @@ __device__ __forceinline__ int divide(int v, int d, float rd) {
 // The workgroup's tile and output channels, without a division (two 64-bit ones were 290 instructions in front
 // of the first load).  All arguments are read first, in one go: asked for where they are used, they were a
 // dozen dependent scalar loads.
-struct Place { int b, g0, gn, cs; };
+struct Place {
+  int b, g0, gn, cs;
+  bool proj;                                        // of the second pointwise layer: the tile is x itself
+  const int8_t* w;
+  const int32_t *bias, *m, *s;
+  const int8_t* res;
+  int8_t* y;
+  int relu;
+};
 __device__ __forceinline__ bool place(const SepParams& p, Place& at) {
   asm volatile("" ::"s"(p.x), "s"(p.img), "s"(p.dbias), "s"(p.dm), "s"(p.ds), "s"(p.lut), "s"(p.xbs), "s"(p.xpitch), "s"(p.Tin),
                "s"(p.o16), "s"(p.nk), "s"(p.units), "s"(p.dwoff), "s"(p.drelu), "s"(p.units_inv));
   asm volatile("" ::"s"(p.w), "s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.res), "s"(p.y), "s"(p.ybs), "s"(p.ypitch), "s"(p.relu),
                "s"(p.Tout), "s"(p.yragged), "s"(p.tpr), "s"(p.splits), "s"(p.wgs), "s"(p.per_xcd), "s"(p.g_base), "s"(p.g_more),
                "s"(p.r_splits), "s"(p.r_tpr));
+  asm volatile("" ::"s"(p.w2), "s"(p.bias2), "s"(p.m2), "s"(p.s2), "s"(p.y2), "s"(p.relu2), "s"(p.wgs2), "s"(p.per_xcd2));
   // consecutive workgroups go round-robin to the 8 XCDs: each XCD takes a contiguous run of tiles
-  // (neighbours share halo rows, the workgroups of one tile its rows)
-  const int v = (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= p.per_xcd || v >= p.wgs) return false;           // whole workgroup
+  // (neighbours share halo rows, the workgroups of one tile its rows), first of the pair, then of the projection
+  const int xcd = (int)(blockIdx.x & 7), nth = (int)(blockIdx.x >> 3);
+  at.proj = nth >= p.per_xcd;
+  const int v = at.proj ? xcd * p.per_xcd2 + nth - p.per_xcd : xcd * p.per_xcd + nth;
+  if (at.proj ? nth - p.per_xcd >= p.per_xcd2 || v >= p.wgs2 : v >= p.wgs) return false;   // whole workgroup
+  at.w = at.proj ? p.w2 : p.w;
+  at.bias = at.proj ? p.bias2 : p.bias;
+  at.m = at.proj ? p.m2 : p.m;
+  at.s = at.proj ? p.s2 : p.s;
+  at.res = at.proj ? nullptr : p.res;
+  at.y = at.proj ? p.y2 : p.y;
+  at.relu = at.proj ? p.relu2 : p.relu;
   const int tile = p.splits == 1 ? v : divide(v, p.splits, p.r_splits);
   at.cs = v - tile * p.splits;
   at.b = divide(tile, p.tpr, p.r_tpr);
@@ -192,75 +215,92 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   const int n = lane & 15, gi = lane >> 4;
   const int co_w = (cs * kWaves + wave) * 16 * NT;
   v4i wb[3][NT];
-  const v4i* const wsrc = reinterpret_cast<const v4i*>(p.w) + (int64_t)(co_w >> 4) * (KCH * 64) + lane;
+  const v4i* const wsrc = reinterpret_cast<const v4i*>(at.w) + (int64_t)(co_w >> 4) * (KCH * 64) + lane;
   auto load_w = [&](int kc) __attribute__((always_inline)) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) wb[kc % 3][nt] = wsrc[(nt * KCH + kc) * 64];
   };
   Consts<16 * NT> pc;
 
-  dc.load_bias(p.dbias, c_wave, lane);
-  load_rows(0);
-  load_quad_weights(0, 0);
-  load_quad_weights(0, 1);
-  dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
-  __builtin_amdgcn_sched_barrier(0);
-  if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
-#pragma unroll
-  for (int blk = 0; blk < NBLK; ++blk) {
-    put_rows();
-    asm volatile("" ::: "memory");                  // (lanes read what other lanes of the wave wrote: LDS is in order)
+  if (RAGGED || !at.proj) {
+    dc.load_bias(p.dbias, c_wave, lane);
+    load_rows(0);
+    load_quad_weights(0, 0);
+    load_quad_weights(0, 1);
+    dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
     __builtin_amdgcn_sched_barrier(0);
-    // window quads a .. a + MT - 1 are what step quad a multiplies; one more is on its way
-    uint32_t wd[MT + 1][4];
-    auto read_quad = [&](int a) __attribute__((always_inline)) {
+    if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) wd[a % (MT + 1)][i] = *reinterpret_cast<const uint32_t*>(win + 16 * a + 4 * i);
-    };
-#pragma unroll
-    for (int a = 0; a < MT; ++a) read_quad(a);
-    v4i acc[MT];
-    const int32_t db = dc.bias_of(16 * blk + ch_l);
-#pragma unroll
-    for (int q = 0; q < MT; ++q) acc[q] = (v4i){db, db, db, db};
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      if (a + 1 < NA) read_quad(a + MT);
-      if (a + 2 < NA) load_quad_weights(blk, a + 2);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
-#pragma unroll
-          for (int q = 0; q < MT; ++q)
-            acc[q] = __builtin_amdgcn_mfma_i32_4x4x4i8(aw[a % 3][i], (int)wd[(a + q) % (MT + 1)][i], acc[q], 0, 0, 0);
-        }
+    for (int blk = 0; blk < NBLK; ++blk) {
+      put_rows();
+      asm volatile("" ::: "memory");                  // (lanes read what other lanes of the wave wrote: LDS is in order)
       __builtin_amdgcn_sched_barrier(0);
-      if (a == 1 && blk + 1 < NBLK) load_rows(blk + 1);   // on their way under the rest of the block
+      // window quads a .. a + MT - 1 are what step quad a multiplies; one more is on its way
+      uint32_t wd[MT + 1][4];
+      auto read_quad = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wd[a % (MT + 1)][i] = *reinterpret_cast<const uint32_t*>(win + 16 * a + 4 * i);
+      };
+#pragma unroll
+      for (int a = 0; a < MT; ++a) read_quad(a);
+      v4i acc[MT];
+      const int32_t db = dc.bias_of(16 * blk + ch_l);
+#pragma unroll
+      for (int q = 0; q < MT; ++q) acc[q] = (v4i){db, db, db, db};
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        if (a + 1 < NA) read_quad(a + MT);
+        if (a + 2 < NA) load_quad_weights(blk, a + 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
+#pragma unroll
+            for (int q = 0; q < MT; ++q)
+              acc[q] = __builtin_amdgcn_mfma_i32_4x4x4i8(aw[a % 3][i], (int)wd[(a + q) % (MT + 1)][i], acc[q], 0, 0, 0);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+        if (a == 1 && blk + 1 < NBLK) load_rows(blk + 1);   // on their way under the rest of the block
+      }
+      if (blk + 1 < NBLK) {
+        load_quad_weights(blk + 1, 0);
+        load_quad_weights(blk + 1, 1);
+      } else if (!TIGHT) {
+        load_w(0);
+        load_w(1);
+      }
+      const int32_t m = dc.m(16 * blk + ch_l), s = dc.s(16 * blk + ch_l);
+      auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+          const int32_t a4[4] = {acc[q][0], acc[q][1], acc[q][2], acc[q][3]};
+          uint32_t pk;
+          if constexpr (decltype(fast_tag)::value)
+            pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
+          else
+            pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
+          if (p.lut) pk = through_table(lut, pk);
+          *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
+        }
+      };
+      if (!__all(s >= kShortMin && s <= kShortMax)) finish(std::false_type{}, std::false_type{});
+      else if (p.drelu) finish(std::true_type{}, std::true_type{});
+      else finish(std::true_type{}, std::false_type{});
     }
-    if (blk + 1 < NBLK) {
-      load_quad_weights(blk + 1, 0);
-      load_quad_weights(blk + 1, 1);
-    } else if (!TIGHT) {
+  } else {
+    // the projection's tile: unit tid % 8 of rows tid / 8, + 128, ...
+    const int u = tid & 7;
+    const int8_t* const src = p.x + (int64_t)b * p.xbs + (int64_t)(tid >> 3) * p.xpitch + 16 * (g0 + u);
+    v4i r[KCH / 2];
+#pragma unroll
+    for (int i = 0; i < KCH / 2; ++i)
+      if (u < gn) r[i] = *reinterpret_cast<const v4i*>(src + (int64_t)(128 * i) * p.xpitch);
+    if (!TIGHT) {
       load_w(0);
       load_w(1);
     }
-    const int32_t m = dc.m(16 * blk + ch_l), s = dc.s(16 * blk + ch_l);
-    auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
 #pragma unroll
-      for (int q = 0; q < MT; ++q) {
-        const int32_t a4[4] = {acc[q][0], acc[q][1], acc[q][2], acc[q][3]};
-        uint32_t pk;
-        if constexpr (decltype(fast_tag)::value)
-          pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
-        else
-          pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
-        if (p.lut) pk = through_table(lut, pk);
-        *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
-      }
-    };
-    if (!__all(s >= kShortMin && s <= kShortMax)) finish(std::false_type{}, std::false_type{});
-    else if (p.drelu) finish(std::true_type{}, std::true_type{});
-    else finish(std::true_type{}, std::false_type{});
+    for (int i = 0; i < KCH / 2; ++i)
+      if (u < gn) *reinterpret_cast<v4i*>(xs + ((tid >> 3) + 128 * i) * 128 + ((u ^ (tid >> 3 & 7)) << 4)) = r[i];
   }
 
   // ---- pointwise half
@@ -268,8 +308,8 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     load_w(0);
     load_w(1);
   }
-  pc.load_bias(p.bias, co_w, lane);
-  pc.load(p.m, p.s, p.bias, co_w, lane);
+  pc.load_bias(at.bias, co_w, lane);
+  pc.load(at.m, at.s, at.bias, co_w, lane);
   // residual rows and output rows: lane -> (row lane / 8 of 8, slot lane % 8), the unit in that slot
   const int u_l = (lane & 7) ^ (lane >> 3);
   const bool u_ok = u_l < gn;
@@ -281,7 +321,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int8_t* const row = p.res + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch;
+        const int8_t* const row = at.res + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch;
         if (u_ok) rr[nt][h] = RAGGED && p.yragged ? load_row16(row, t_l, p.Tout) : *reinterpret_cast<const v4i*>(row + t_l);
       }
   };
@@ -298,7 +338,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
 #pragma unroll
   for (int kc = 0; kc < KCH; ++kc) {
     if (kc + 2 < KCH) load_w(kc + 2);
-    if (kc + 2 == KCH && p.res) load_res();         // (into what the weight ring no longer needs)
+    if (kc + 2 == KCH && at.res) load_res();         // (into what the weight ring no longer needs)
     __builtin_amdgcn_sched_barrier(0);
     const unsigned char* ab = xs + kc * 8192;
     v2i ar[3][2];
@@ -332,10 +372,10 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   const uint32_t sbase = (uint32_t)(n * 128 + 4 * gi) | (uint32_t)((n & 7) << 4);
   bool ok = true;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (p.res ? kShortMaxRes : kShortMax);
+  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (at.res ? kShortMaxRes : kShortMax);
   const bool fast = __all(ok);
   const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
-      p.y + (int64_t)b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
+      at.y + (int64_t)b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
   const uint32_t ylane = (uint32_t)(lane >> 3) * (uint32_t)p.ypitch + (uint32_t)t_l;
   auto epilogue = [&](auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
@@ -355,7 +395,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
         if constexpr (FAST)
           *sp = requant_short4<RES, RELU>(a4, mc[nt], sc[nt] - 32, 1 << ((sc[nt] - 33) & 31), rw);
         else
-          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, p.relu ? 0 : -128, 127);
+          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, at.relu ? 0 : -128, 127);
         if (mt & 1) __builtin_amdgcn_sched_barrier(0);
       }
       asm volatile("" ::: "memory");
@@ -363,7 +403,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       for (int h = 0; h < 2; ++h) {
         const v4i o = *reinterpret_cast<const v4i*>(st + 1024 * h + 16 * lane);
         if (RAGGED && p.yragged) {                  // (uniform)
-          if (u_ok) store_row16(p.y + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch, t_l, p.Tout, o);
+          if (u_ok) store_row16(at.y + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch, t_l, p.Tout, o);
           continue;
         }
         const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};
@@ -374,13 +414,13 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   };
   const std::true_type T{};
   const std::false_type F{};
-  if (p.res) {
+  if (at.res) {
     if (!fast) epilogue(F, T, F);
-    else if (p.relu) epilogue(T, T, T);
+    else if (at.relu) epilogue(T, T, T);
     else epilogue(T, T, F);
   } else {
     if (!fast) epilogue(F, F, F);
-    else if (p.relu) epilogue(T, F, T);
+    else if (at.relu) epilogue(T, F, T);
     else epilogue(T, F, F);
   }
 }
@@ -434,45 +474,49 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   Consts<CPW> dc;
   Consts<16 * NT> pc;
   dc.load_bias(p.dbias, c_wave, lane);
-  pc.load_bias(p.bias, co_w, lane);
+  pc.load_bias(at.bias, co_w, lane);
   // residual and output: lane -> row lane / 2 of the wave's 16 NT, unit lane % 2
   const int u_l = lane & 1, t_l = 16 * (g0 + u_l);
   const bool y_ok = u_l < at.gn && lane < 32 * NT && ks == 0;
   const int64_t yrow = (int64_t)at.b * p.ybs + (int64_t)(co_w + (lane >> 1)) * p.ypitch;
   v4i rr = {0, 0, 0, 0};
-  if (p.res && y_ok) rr = RAGGED && p.yragged ? load_row16(p.res + yrow, t_l, p.Tout) : *reinterpret_cast<const v4i*>(p.res + yrow + t_l);
-  // weights: chunk L of the wave's CPW x NA
-  v4i wr[NWL];
-  {
-    const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
-#pragma unroll
-    for (int j = 0; j < NWL; ++j) wr[j] = src[min(lane + 64 * j, CPW * NA - 1)];
-  }
-  dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
-  // rows: chunk L of the wave's CPW x units; chunks outside [0, Tin) are zero, the chunk a row ends in is masked
-  v4i xr[NL];
+  if (at.res && y_ok) rr = RAGGED && p.yragged ? load_row16(at.res + yrow, t_l, p.Tout) : *reinterpret_cast<const v4i*>(at.res + yrow + t_l);
+  v4i wr[NWL], xr[NL], tr = {0, 0, 0, 0};
   uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
-  {
-    const int8_t* const xw = p.x + (int64_t)at.b * p.xbs + (int64_t)c_wave * p.xpitch;
-    const int t_last = p.Tin & ~15;
+  if (RAGGED || !at.proj) {
+    // weights: chunk L of the wave's CPW x NA
+    {
+      const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
-      const int t = 16 * (g0 + p.o16 + u);
-      const bool on = ch < CPW && t >= 0 && t < p.Tin;
-      if (on) in |= 1u << j;
-      if (t == t_last) last |= 1u << j;
-      xr[j] = (v4i){0, 0, 0, 0};
-      if (RAGGED) {
-        if (on) xr[j] = t == t_last ? load_row16(xw + ch * p.xpitch, t, p.Tin) : *reinterpret_cast<const unaligned_chunk16*>(xw + ch * p.xpitch + t);
-      } else if (64 * j < CPW * p.units) {          // (uniform; lanes without a chunk read the first one and drop it)
-        xr[j] = *reinterpret_cast<const v4i*>(xw + (on ? ch * p.xpitch + t : 0));
+      for (int j = 0; j < NWL; ++j) wr[j] = src[min(lane + 64 * j, CPW * NA - 1)];
+    }
+    dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
+    // rows: chunk L of the wave's CPW x units; chunks outside [0, Tin) are zero, the chunk a row ends in is masked
+    {
+      const int8_t* const xw = p.x + (int64_t)at.b * p.xbs + (int64_t)c_wave * p.xpitch;
+      const int t_last = p.Tin & ~15;
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
+        const int t = 16 * (g0 + p.o16 + u);
+        const bool on = ch < CPW && t >= 0 && t < p.Tin;
+        if (on) in |= 1u << j;
+        if (t == t_last) last |= 1u << j;
+        xr[j] = (v4i){0, 0, 0, 0};
+        if (RAGGED) {
+          if (on) xr[j] = t == t_last ? load_row16(xw + ch * p.xpitch, t, p.Tin) : *reinterpret_cast<const unaligned_chunk16*>(xw + ch * p.xpitch + t);
+        } else if (64 * j < CPW * p.units) {          // (uniform; lanes without a chunk read the first one and drop it)
+          xr[j] = *reinterpret_cast<const v4i*>(xw + (on ? ch * p.xpitch + t : 0));
+        }
       }
     }
+  } else {                                          // the projection's tile: unit tid % 2 of row tid / 2
+    if ((tid >> 1) < 64 * KCH && u_l < at.gn)
+      tr = *reinterpret_cast<const v4i*>(p.x + (int64_t)at.b * p.xbs + (int64_t)(tid >> 1) * p.xpitch + t_l);
   }
-  pc.load(p.m, p.s, p.bias, co_w, lane);
+  pc.load(at.m, at.s, at.bias, co_w, lane);
   v4i wb[KC][NT];
-  const v4i* const wsrc = reinterpret_cast<const v4i*>(p.w) + (int64_t)(co_w >> 4) * (KCH * 64) + ks * (KC * 64) + lane;
+  const v4i* const wsrc = reinterpret_cast<const v4i*>(at.w) + (int64_t)(co_w >> 4) * (KCH * 64) + ks * (KC * 64) + lane;
   auto load_w = [&](int kc) __attribute__((always_inline)) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) wb[kc][nt] = wsrc[(nt * KCH + kc) * 64];
@@ -483,103 +527,110 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   __builtin_amdgcn_sched_barrier(0);
   if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
 
-  // ---- depthwise half
+  if (RAGGED || !at.proj) {
+    // ---- depthwise half
 #pragma unroll
-  for (int j = 0; j < NWL; ++j) {
-    const int L = lane + 64 * j, ch = L / NA;
-    if (L < CPW * NA) *reinterpret_cast<v4i*>(wlds + 16 * (ch * WS + L - ch * NA)) = wr[j];
-  }
-#pragma unroll
-  for (int j = 0; j < NL; ++j) {
-    v4i r = xr[j];
-    if (!RAGGED) {
-      if (!(in & (1u << j))) r = (v4i){0, 0, 0, 0};
-      if (last & (1u << j)) r = keep_bytes(r, p.Tin & 15);
-    }
-    if (lane + 64 * j < CPW * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = r;
-  }
-  asm volatile("" ::: "memory");                    // (lanes read what other lanes of the wave wrote: LDS is in order)
-  __builtin_amdgcn_sched_barrier(0);
-  const int ch_l = lane >> 2, n_l = lane & 3;
-  // Toeplitz row m = lane % 4 of four taps: bytes 4 - m .. 7 - m of (this dword, the one before)
-  const uint32_t sel = 0x07060504u - 0x01010101u * (uint32_t)n_l;
-  const unsigned char* const win = rows + ch_l * (16 * p.units) + 4 * (n_l + p.dwoff);
-  const unsigned char* const wrow = wlds + ch_l * (16 * WS);
-  constexpr int LA = 2, WQ = MT + LA;               // quads read ahead
-  uint32_t wd[NBLK][WQ][4];
-  v4i aq[NBLK][LA + 1];
-  uint32_t before[NBLK];
-  auto read_win = [&](int a) __attribute__((always_inline)) {
-#pragma unroll
-    for (int blk = 0; blk < NBLK; ++blk)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        wd[blk][a % WQ][i] = *reinterpret_cast<const uint32_t*>(win + 256 * blk * p.units + 16 * a + 4 * i);
-  };
-  auto read_taps = [&](int a) __attribute__((always_inline)) {
-#pragma unroll
-    for (int blk = 0; blk < NBLK; ++blk) aq[blk][a % (LA + 1)] = *reinterpret_cast<const v4i*>(wrow + 256 * blk * WS + 16 * a);
-  };
-#pragma unroll
-  for (int a = 0; a < LA; ++a) read_taps(a);
-#pragma unroll
-  for (int a = 0; a < MT + LA - 1; ++a) read_win(a);
-  v4i dacc[NBLK][MT];
-#pragma unroll
-  for (int blk = 0; blk < NBLK; ++blk) {
-    const int32_t db = dc.bias_of(16 * blk + ch_l);
-    before[blk] = 0;
-#pragma unroll
-    for (int q = 0; q < MT; ++q) dacc[blk][q] = (v4i){db, db, db, db};
-  }
-#pragma unroll
-  for (int a = 0; a < NA; ++a) {
-    if (a + LA < NA) {
-      read_taps(a + LA);
-      read_win(a + MT + LA - 1);
+    for (int j = 0; j < NWL; ++j) {
+      const int L = lane + 64 * j, ch = L / NA;
+      if (L < CPW * NA) *reinterpret_cast<v4i*>(wlds + 16 * (ch * WS + L - ch * NA)) = wr[j];
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint32_t t[NBLK];
-#pragma unroll
-      for (int blk = 0; blk < NBLK; ++blk) {
-        const uint32_t d = (uint32_t)aq[blk][a % (LA + 1)][i];
-        t[blk] = __builtin_amdgcn_perm(d, before[blk], sel);
-        before[blk] = d;
+    for (int j = 0; j < NL; ++j) {
+      v4i r = xr[j];
+      if (!RAGGED) {
+        if (!(in & (1u << j))) r = (v4i){0, 0, 0, 0};
+        if (last & (1u << j)) r = keep_bytes(r, p.Tin & 15);
       }
-      if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
-#pragma unroll
-        for (int q = 0; q < MT; ++q)
-#pragma unroll
-          for (int blk = 0; blk < NBLK; ++blk)
-            dacc[blk][q] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)t[blk], (int)wd[blk][(a + q) % WQ][i], dacc[blk][q], 0, 0, 0);
-      }
+      if (lane + 64 * j < CPW * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = r;
     }
+    asm volatile("" ::: "memory");                    // (lanes read what other lanes of the wave wrote: LDS is in order)
     __builtin_amdgcn_sched_barrier(0);
-  }
+    const int ch_l = lane >> 2, n_l = lane & 3;
+    // Toeplitz row m = lane % 4 of four taps: bytes 4 - m .. 7 - m of (this dword, the one before)
+    const uint32_t sel = 0x07060504u - 0x01010101u * (uint32_t)n_l;
+    const unsigned char* const win = rows + ch_l * (16 * p.units) + 4 * (n_l + p.dwoff);
+    const unsigned char* const wrow = wlds + ch_l * (16 * WS);
+    constexpr int LA = 2, WQ = MT + LA;               // quads read ahead
+    uint32_t wd[NBLK][WQ][4];
+    v4i aq[NBLK][LA + 1];
+    uint32_t before[NBLK];
+    auto read_win = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
-  for (int kc = FIRST; kc < KC; ++kc) load_w(kc);
-  // dword n_l of group q, row (channel) ch of the tile; the tile's unit q of a row sits in slot q ^ (row & 7)
-  const uint32_t tw = (uint32_t)((c_wave + ch_l) * 128 + 4 * n_l) | (uint32_t)((ch_l & 7) << 4);
+      for (int blk = 0; blk < NBLK; ++blk)
 #pragma unroll
-  for (int blk = 0; blk < NBLK; ++blk) {
-    const int32_t m = dc.m(16 * blk + ch_l), s = dc.s(16 * blk + ch_l);
-    auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
-#pragma unroll
-      for (int q = 0; q < MT; ++q) {
-        const int32_t a4[4] = {dacc[blk][q][0], dacc[blk][q][1], dacc[blk][q][2], dacc[blk][q][3]};
-        uint32_t pk;
-        if constexpr (decltype(fast_tag)::value)
-          pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
-        else
-          pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
-        if (p.lut) pk = through_table(lut, pk);
-        *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
-      }
+        for (int i = 0; i < 4; ++i)
+          wd[blk][a % WQ][i] = *reinterpret_cast<const uint32_t*>(win + 256 * blk * p.units + 16 * a + 4 * i);
     };
-    if (!__all(s >= kShortMin && s <= kShortMax)) finish(std::false_type{}, std::false_type{});
-    else if (p.drelu) finish(std::true_type{}, std::true_type{});
-    else finish(std::true_type{}, std::false_type{});
+    auto read_taps = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+      for (int blk = 0; blk < NBLK; ++blk) aq[blk][a % (LA + 1)] = *reinterpret_cast<const v4i*>(wrow + 256 * blk * WS + 16 * a);
+    };
+#pragma unroll
+    for (int a = 0; a < LA; ++a) read_taps(a);
+#pragma unroll
+    for (int a = 0; a < MT + LA - 1; ++a) read_win(a);
+    v4i dacc[NBLK][MT];
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk) {
+      const int32_t db = dc.bias_of(16 * blk + ch_l);
+      before[blk] = 0;
+#pragma unroll
+      for (int q = 0; q < MT; ++q) dacc[blk][q] = (v4i){db, db, db, db};
+    }
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      if (a + LA < NA) {
+        read_taps(a + LA);
+        read_win(a + MT + LA - 1);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t t[NBLK];
+#pragma unroll
+        for (int blk = 0; blk < NBLK; ++blk) {
+          const uint32_t d = (uint32_t)aq[blk][a % (LA + 1)][i];
+          t[blk] = __builtin_amdgcn_perm(d, before[blk], sel);
+          before[blk] = d;
+        }
+        if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
+#pragma unroll
+          for (int q = 0; q < MT; ++q)
+#pragma unroll
+            for (int blk = 0; blk < NBLK; ++blk)
+              dacc[blk][q] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)t[blk], (int)wd[blk][(a + q) % WQ][i], dacc[blk][q], 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int kc = FIRST; kc < KC; ++kc) load_w(kc);
+    // dword n_l of group q, row (channel) ch of the tile; the tile's unit q of a row sits in slot q ^ (row & 7)
+    const uint32_t tw = (uint32_t)((c_wave + ch_l) * 128 + 4 * n_l) | (uint32_t)((ch_l & 7) << 4);
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk) {
+      const int32_t m = dc.m(16 * blk + ch_l), s = dc.s(16 * blk + ch_l);
+      auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+          const int32_t a4[4] = {dacc[blk][q][0], dacc[blk][q][1], dacc[blk][q][2], dacc[blk][q][3]};
+          uint32_t pk;
+          if constexpr (decltype(fast_tag)::value)
+            pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
+          else
+            pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
+          if (p.lut) pk = through_table(lut, pk);
+          *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
+        }
+      };
+      if (!__all(s >= kShortMin && s <= kShortMax)) finish(std::false_type{}, std::false_type{});
+      else if (p.drelu) finish(std::true_type{}, std::true_type{});
+      else finish(std::true_type{}, std::false_type{});
+    }
+  } else {
+    const int row = tid >> 1;
+    if (row < 64 * KCH) *reinterpret_cast<v4i*>(xs + row * 128 + ((u_l ^ (row & 7)) << 4)) = tr;
+#pragma unroll
+    for (int kc = FIRST; kc < KC; ++kc) load_w(kc);
   }
 
   // ---- pointwise half; operand of group mt, chunk kc: item kc MT + mt of one stream, AH of them on their way
@@ -637,7 +688,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   unsigned char* const st = rows;
   bool ok = true;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (p.res ? kShortMaxRes : kShortMax);
+  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (at.res ? kShortMaxRes : kShortMax);
   const bool fast = __all(ok);
   auto epilogue = [&](auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
@@ -655,27 +706,27 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
         if constexpr (FAST)
           *sp = requant_short4<RES, RELU>(a4, mc[nt], sc[nt] - 32, 1 << ((sc[nt] - 33) & 31), rw);
         else
-          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, p.relu ? 0 : -128, 127);
+          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, at.relu ? 0 : -128, 127);
       }
     asm volatile("" ::: "memory");
   };
   const std::true_type T{};
   const std::false_type F{};
-  if (p.res) {
+  if (at.res) {
     if (!fast) epilogue(F, T, F);
-    else if (p.relu) epilogue(T, T, T);
+    else if (at.relu) epilogue(T, T, T);
     else epilogue(T, T, F);
   } else {
     if (!fast) epilogue(F, F, F);
-    else if (p.relu) epilogue(T, F, T);
+    else if (at.relu) epilogue(T, F, T);
     else epilogue(T, F, F);
   }
   const v4i o = *reinterpret_cast<const v4i*>(st + 16 * (lane & (32 * NT - 1)));
   if (RAGGED && p.yragged) {                        // (uniform)
-    if (y_ok) store_row16(p.y + yrow, t_l, p.Tout, o);
+    if (y_ok) store_row16(at.y + yrow, t_l, p.Tout, o);
   } else {
     const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
-        p.y + (int64_t)at.b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
+        at.y + (int64_t)at.b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
     const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};
     __builtin_amdgcn_raw_buffer_store_b128(ov, yrs, y_ok ? (uint32_t)(lane >> 1) * (uint32_t)p.ypitch + (uint32_t)t_l : 0xfffffff0u, 0,
                                            kStoreThrough);
@@ -689,7 +740,7 @@ hipError_t launch_t(const SepParams& p, size_t lds, hipStream_t st) {
   if constexpr (MT <= 2) kernel = sep_small_kernel<KCH, MT, NA, NT, KS, RAGGED>;
   else kernel = sep_kernel<KCH, MT, NA, NT, RAGGED>;
   if (const hipError_t e = ensure_max_dynamic_lds((const void*)kernel, lds_raised); e != hipSuccess) return e;
-  return launch_kernel(kernel, dim3((unsigned)(8 * p.per_xcd)), dim3(64 * kWaves), lds, st, p);
+  return launch_kernel(kernel, dim3((unsigned)(8 * (p.per_xcd + p.per_xcd2))), dim3(64 * kWaves), lds, st, p);
 }
 
 // the instantiations of one tap range (ragged rows: at most 4 groups, more do not fit the registers)
