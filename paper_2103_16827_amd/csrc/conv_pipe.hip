@@ -59,7 +59,17 @@ struct CpGeom {
   int splits;         // workgroups per tile, each with a range of the chunks
   int tiles;          // B * n_tt * n_co * splits
   int per_xcd;        // ceil(tiles / 8): tiles of one XCD (the grid is 8 * per_xcd workgroups)
+  float r_nbt, r_splits, r_tt;   // reciprocals of B * n_tt, splits, n_tt
+  int fq_inv;         // ceil(2^16 / (rows / 4)): x / (rows / 4) = x fq_inv >> 16 for x < 256, rows <= 256
 };
+
+// v / d for wave-uniform operands, rd = 1.0f / d: below 2^24 the estimate is off by one at most
+__device__ __forceinline__ int divide(int v, int d, float rd) {
+  if (v >= 1 << 24) return v / d;
+  const int q = __builtin_amdgcn_readfirstlane((int)((float)v * rd));
+  const int r = v - q * d;
+  return r < 0 ? q - 1 : r >= d ? q + 1 : q;
+}
 
 // KG > 1: the taps of a chunk are split over KG groups of 4 waves that share the chunk in LDS, and their
 // accumulators are summed through LDS at the end.  A launch with fewer tiles than the chip has SIMDs to
@@ -69,6 +79,12 @@ template <int MT, int NT, int KG>
 __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeom g) {
   extern __shared__ __align__(16) unsigned char xs[];   // [3 buffers][rows][kXS]; KG > 1: the partial sums after that
   constexpr int TM = 16 * MT, TN = 64 * NT;
+  // All arguments of the loop in one go, and no integer division in front of the first load: with 16 waves the
+  // seven divisions and a dozen dependent scalar loads took 6900 cycles of the 25800 of a 256-channel layer of 800 frames.
+  asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.xbs), "s"(p.B), "s"(p.Cout), "s"(p.Tin), "s"(p.k),
+               "s"(p.stride), "s"(p.dil), "s"(p.pl), "s"(p.xpad));
+  asm volatile("" ::"s"(g.n_tt), "s"(g.n_co), "s"(g.rows), "s"(g.kchunks), "s"(g.co16n), "s"(g.splits), "s"(g.tiles), "s"(g.per_xcd),
+               "s"(g.r_nbt), "s"(g.r_splits), "s"(g.r_tt), "s"(g.fq_inv));
 
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;   // within the group
   const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8)) : 0;
@@ -86,12 +102,14 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   const int v = g.per_xcd ? (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
   if (v >= g.tiles) return;                         // whole workgroup, before any barrier
   const int nbt = p.B * g.n_tt;
-  const int cs = v / nbt, bt = v - cs * nbt;        // bt: (b, t_tile) of the tile
-  const int co_tile = cs / g.splits, split = cs - co_tile * g.splits;
-  const int c0 = split * g.kchunks / g.splits;      // this workgroup's chunks
-  const int nkc = (split + 1) * g.kchunks / g.splits - c0;
-  const int t_tile = bt % g.n_tt;
-  const int b = bt / g.n_tt;
+  const int cs = divide(v, nbt, g.r_nbt), bt = v - cs * nbt;   // bt: (b, t_tile) of the tile
+  const int co_tile = g.splits == 1 ? cs : divide(cs, g.splits, g.r_splits), split = cs - co_tile * g.splits;
+  int c0 = 0, nkc = g.kchunks;                      // this workgroup's chunks
+  if (g.splits > 1) {
+    c0 = divide(split * g.kchunks, g.splits, g.r_splits);
+    nkc = divide((split + 1) * g.kchunks, g.splits, g.r_splits) - c0;
+  }
+  const int b = divide(bt, g.n_tt, g.r_tt), t_tile = bt - b * g.n_tt;
 
   const int t0 = t_tile * TM;                       // first output frame of the tile
   const int f0 = t0 * p.stride - p.pl;              // first input frame the tile reads
@@ -110,7 +128,7 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   // (fq >> 2) & 3: then 16 consecutive lanes cover all 64 banks.  The rotation costs nothing: it
   // is folded into the byte selectors of the first transposition stage.
   const int nfq = g.rows >> 2;                      // frame quads per chunk (<= 64)
-  const int u_fq = tid % nfq, u_cg = tid / nfq;
+  const int u_cg = (tid * g.fq_inv) >> 16, u_fq = tid - u_cg * nfq;
   const int rot = (u_fq >> 2) & 3;
   const int u_f = fa + 4 * u_fq;                    // first input frame of the unit
   const bool u_on = u_cg < 4 && u_f >= 0 && u_f < p.Tin;
@@ -356,53 +374,102 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
     }
     __syncthreads();
     if (*reinterpret_cast<volatile unsigned*>(xs) + 1 != (unsigned)g.splits) return;   // whole workgroup
+    // (the sums of several ranges on their way at once where a wave has few of them)
+    constexpr int OB = MT * NT / KG <= 4 ? 4 : 1;
 #pragma unroll 1
-    for (int o = 1; o < g.splits; ++o) {
-      const __amdgpu_buffer_rsrc_t from = part_of(split + o < g.splits ? split + o : split + o - g.splits);
+    for (int o0 = 1; o0 < g.splits; o0 += OB) {
+      v4i in[OB][MT * NT / KG];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        if (owned(mt)) {
+      for (int i = 0; i < OB; ++i) {
+        const int o = split + min(o0 + i, g.splits - 1);   // (past the last range: loaded again, not added)
+        const __amdgpu_buffer_rsrc_t from = part_of(o < g.splits ? o : o - g.splits);
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            acc[mt][nt] += __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(from, poff, (mt * NT + nt) * 4096, 0));
+        for (int j = 0; j < MT * NT / KG; ++j)
+          in[i][j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(from, poff, (kg * (MT * NT / KG) + j) * 4096, 0));
+      }
+#pragma unroll
+      for (int i = 0; i < OB; ++i)
+        if (o0 + i < g.splits) {
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            if (owned(mt)) {
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += in[i][mt % (MT / KG) * NT + nt];
+            }
         }
     }
   }
 
   // ---- epilogue: lane (n, gi) holds frames t0 + 16 mt + 4 gi + (0..3) of channel co_w + 16 nt + n
-  const int lo = p.relu ? 0 : -128;
+  constexpr int NB = MT / KG;                       // frame groups that this wave finishes: kg NB + h
+  const int trow = p.Tout + p.ypad;                 // (pad bytes may be written)
+  const int tl = t0 + 16 * NB * kg + 4 * gi;
+  const int64_t orow = (int64_t)b * p.ybs + (int64_t)(co_w + n) * trow;
+  v4i fin[NB][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+    if (KG == 1 || mt / NB == kg) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) fin[mt % NB][nt] = acc[mt][nt];
+    }
+  bool on[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    const int co = co_w + 16 * nt + n;
-    if (co >= p.Cout) continue;
+    on[nt] = co_w + 16 * nt + n < p.Cout;
     const int32_t* const cl = reinterpret_cast<const int32_t*>(consts) + 16 * nt + n;
     const int32_t mc = cl[0], sc = cl[64], bv = p.bias ? cl[128] : 0;
-    const int trow = p.Tout + p.ypad;               // (pad bytes may be written)
-    const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * trow;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int t = t0 + 16 * mt + 4 * gi;
-      if (t >= p.Tout || (KG > 1 && mt * KG / MT != kg)) continue;
-      uint32_t rr = 0;
-      if (p.res) rr = load_row_u32(p.res + orow, t, trow);
-      int32_t radd[4];
+    for (int h = 0; h < NB; ++h)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) radd[i] = (int32_t)(int8_t)(rr >> (8 * i));
+      for (int i = 0; i < 4; ++i) fin[h][nt][i] = dyadic_rescale(fin[h][nt][i] + bv, mc, sc);
+  }
+  // residual operands (dense-residual layers have several): the rows of RB of them on their way at once
+  if (p.res) {
+    constexpr int RB = NB * NT <= 4 ? 6 : NB * NT <= 10 ? 3 : 2;
+    const int count = 1 + p.n_res_more;
 #pragma unroll 1
-      for (int r = 0; r < p.n_res_more; ++r) {       // dense-residual layers: further operands
-        const uint32_t rw = load_row_u32(p.res_more[r] + orow, t, trow);
+    for (int r0 = 0; r0 < count; r0 += RB) {
+      uint32_t d[RB][NB][NT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) radd[i] += (int32_t)(int8_t)(rw >> (8 * i));
-      }
-      uint32_t pk = 0;
+      for (int r = 0; r < RB; ++r)
+        if (r0 + r < count) {                       // (uniform)
+          const int8_t* const src = (r0 + r == 0 ? p.res : p.res_more[r0 + r - 1]) + orow;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int32_t v = dyadic_rescale(acc[mt][nt][i] + bv, mc, sc) + radd[i];
-        pk |= (uint32_t)(clamp_i8(v, lo) & 0xff) << (8 * i);
-      }
-      store_row_u32(p.y + orow, t, trow, pk);
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+              const int t = tl + 16 * h;
+              d[r][h][nt] = 0;
+              if (on[nt] && t < p.Tout) d[r][h][nt] = load_u32(src + (int64_t)(16 * nt) * trow + min(t, trow - 4));
+            }
+        }
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+        if (r0 + r < count) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+              const int t = tl + 16 * h;
+              const uint32_t w = t > trow - 4 ? d[r][h][nt] >> (8 * (t - (trow - 4))) : d[r][h][nt];   // (load_row_u32)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) fin[h][nt][i] += (int32_t)(int8_t)(w >> (8 * i));
+            }
+        }
     }
   }
+  const int lo = p.relu ? 0 : -128;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int h = 0; h < NB; ++h) {
+      const int t = tl + 16 * h;
+      if (!on[nt] || t >= p.Tout) continue;
+      uint32_t pk = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) pk |= (uint32_t)(clamp_i8(fin[h][nt][i], lo) & 0xff) << (8 * i);
+      store_row_u32(p.y + orow + (int64_t)(16 * nt) * trow, t, trow, pk);
+    }
 }
 
 int lds_rows(const ConvParams& p, int TM) {
@@ -500,6 +567,10 @@ hipError_t launch_t(const ConvParams& p, int splits, hipStream_t st) {
   const int64_t blocks = (int64_t)p.B * g.n_tt * g.n_co * splits;
   g.tiles = (int)blocks;
   g.per_xcd = tuning().cp_plain_order ? 0 : (int)((blocks + 7) / 8);
+  g.r_nbt = 1.0f / (float)(p.B * g.n_tt);
+  g.r_splits = 1.0f / (float)splits;
+  g.r_tt = 1.0f / (float)g.n_tt;
+  g.fq_inv = (65536 + g.rows / 4 - 1) / (g.rows / 4);
   const size_t lds = lds_bytes(p, CpTile{MT, NT, KG, 1});
   if (lds > 64 * 1024) {
     static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
