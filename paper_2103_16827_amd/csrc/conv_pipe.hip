@@ -81,8 +81,9 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   constexpr int TM = 16 * MT, TN = 64 * NT;
   // All arguments of the loop in one go, and no integer division in front of the first load: with 16 waves the
   // seven divisions and a dozen dependent scalar loads took 6900 cycles of the 25800 of a 256-channel layer of 800 frames.
-  asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.xbs), "s"(p.B), "s"(p.Cout), "s"(p.Tin), "s"(p.k),
-               "s"(p.stride), "s"(p.dil), "s"(p.pl), "s"(p.xpad));
+  // (Those of the epilogue only where they need no spill: not in the tall tiles of two groups.)
+  asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.xbs), "s"(p.B), "s"(p.Tin), "s"(p.k), "s"(p.stride), "s"(p.dil), "s"(p.pl), "s"(p.xpad));
+  if constexpr (KG == 1 || MT < 8) asm volatile("" ::"s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.Cout));
   asm volatile("" ::"s"(g.n_tt), "s"(g.n_co), "s"(g.rows), "s"(g.kchunks), "s"(g.co16n), "s"(g.splits), "s"(g.tiles), "s"(g.per_xcd),
                "s"(g.r_nbt), "s"(g.r_splits), "s"(g.r_tt), "s"(g.fq_inv));
 
