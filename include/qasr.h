@@ -289,8 +289,8 @@ qasr_status qasr_plan_slot_buffers(const int32_t* in_slot, const int32_t* res_sl
  * output, each rounded up to 256 bytes, their rows to 16 frames where some length is not a multiple of
  * 16; and, where dense layers with taps have too few tiles to fill the chip, room for the partial
  * sums of their split contractions (int32; the largest layer's, plus 4 KiB of counters).  For the
- * Jasper-10x5 shape that is 3 MiB at one utterance of 200 input frames, 8 at 1 x 800, 12 at 1 x 1600, 20 at
- * 4 x 800 and nothing from 8 x 800 on.  Known at create time because every shape and scale of the
+ * Jasper-10x5 shape that is 20 MiB at 4 x 800 and nothing from 8 x 800 on or at 1 x 1600 and below, where
+ * conv_few runs these layers and splits a contraction inside a workgroup.  Known at create time because every shape and scale of the
  * integer model is static (Sec. 2.1: static quantisation, nothing is sized at inference).  HOST only. */
 size_t qasr_encoder_workspace_bytes(const qasr_encoder* e);
 
@@ -365,7 +365,8 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
  *     pointwise pair; one less for a pair that runs together with the pointwise layer before it, a residual
  *     projection of the same tensor; -1 if i is out of range), and in *kernel (unless NULL) the kernel's
  *     name: "sep" for these, "pw_wide" for pointwise layers of the pw_pipe, pw_tile and gemm_mfma families
- *     that this kernel runs faster, else the family's.  HOST only. */
+ *     and "conv_few" for layers of the conv_pipe family that these kernels run faster, else the family's.  HOST
+ *     only. */
 int32_t qasr_encoder_num_ops(const qasr_encoder* e);
 const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i);
 int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** kernel);

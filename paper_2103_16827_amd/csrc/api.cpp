@@ -74,7 +74,7 @@ ConvParams make_params(const qasr_conv1d_desc* d, const int8_t* x, const int8_t*
   return p;
 }
 
-enum class Kernel { Generic, DwMfma, DwPipe, GemmMfma, PwTile, PwPipe, PwWide, ConvPipe };
+enum class Kernel { Generic, DwMfma, DwPipe, GemmMfma, PwTile, PwPipe, PwWide, ConvPipe, ConvFew };
 
 // the family whose shapes a layer has
 Kernel family_of(const ConvParams& p) {
@@ -92,14 +92,16 @@ Kernel family_of(const ConvParams& p) {
   return Kernel::Generic;
 }
 
-// The kernel that runs a layer.  The one place that decides it: the two families of the benchmark's widths
-// hand launches of some sizes to pw_wide.  It depends on lengths, row pitches and pointers (their alignment),
-// not on act_lut, so a layer may get another kernel in another call (a float forward gives the ends of an
-// encoder padded rows); whoever asks goes by the answer for the call at hand, also for the activation.
+// The kernel that runs a layer.  The one place that decides it: the two pointwise families of the benchmark's
+// widths hand launches of some sizes to pw_wide, dense layers of few frames go to conv_few.  It depends on
+// lengths, row pitches and pointers (their alignment), not on act_lut, so a layer may get another kernel in
+// another call (a float forward gives the ends of an encoder padded rows); whoever asks goes by the answer for
+// the call at hand, also for the activation.
 Kernel pick_kernel(const ConvParams& p) {
   const Kernel f = family_of(p);
   if (f == Kernel::PwTile && qasr::pw_wide_better(p, false)) return Kernel::PwWide;
   if (f == Kernel::PwPipe && qasr::pw_wide_better(p, true)) return Kernel::PwWide;
+  if (f == Kernel::ConvPipe && qasr::conv_few_better(p, p.part != nullptr)) return Kernel::ConvFew;
   return f;
 }
 
@@ -116,10 +118,13 @@ const char* kernel_name(Kernel k) {
     case Kernel::PwWide: return "pw_wide";
     case Kernel::GemmMfma: return "gemm_mfma";
     case Kernel::ConvPipe: return "conv_pipe";
+    case Kernel::ConvFew: return "conv_few";
     default: return "conv_generic";
   }
 }
-const char* family_name(Kernel k) { return kernel_name(k == Kernel::PwWide ? Kernel::GemmMfma : k); }
+const char* family_name(Kernel k) {
+  return kernel_name(k == Kernel::PwWide ? Kernel::GemmMfma : k == Kernel::ConvFew ? Kernel::ConvPipe : k);
+}
 
 qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
   hipError_t e;
@@ -131,6 +136,7 @@ qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
     case Kernel::PwPipe: e = qasr::launch_pw_pipe(p, st); break;
     case Kernel::PwWide: e = qasr::launch_pw_wide(p, st); break;
     case Kernel::ConvPipe: e = qasr::launch_conv_pipe(p, st); break;
+    case Kernel::ConvFew: e = qasr::launch_conv_few(p, st); break;
     default: e = qasr::launch_conv_generic(p, st); break;
   }
   return hip_status(e);

@@ -513,7 +513,7 @@ double unit_cycles(const ConvParams& p, const CpTile& c, int64_t n, int chunks) 
   return (double)(n / occ) * T(occ) + T(n % occ);
 }
 
-bool pick(const ConvParams& p, bool split, CpTile& best_tile) {
+bool pick(const ConvParams& p, bool split, CpTile& best_tile, double& best) {
   if (tuning().no_conv_pipe) return false;                // tuning: fall through to gemm_mfma
   if (p.depthwise || p.Cin % 64 != 0 || !p.w_packed || p.k < 2) return false;
   if (p.Cout < 64) return false;
@@ -524,7 +524,7 @@ bool pick(const ConvParams& p, bool split, CpTile& best_tile) {
   static const CpTile tiles[] = {{8, 4, 1, 1}, {7, 4, 1, 1}, {6, 4, 1, 1}, {5, 4, 1, 1}, {4, 4, 1, 1}, {10, 2, 1, 1}, {9, 2, 1, 1}, {8, 2, 1, 1}, {7, 2, 1, 1}, {6, 2, 1, 1},
                                  {5, 2, 1, 1}, {4, 2, 1, 1}, {6, 4, 2, 1}, {4, 4, 2, 1}, {10, 2, 2, 1}, {8, 2, 2, 1}, {6, 2, 2, 1}, {4, 2, 2, 1}, {4, 2, 4, 1}};
   const int force_s = tuning().cp_s;
-  double best = 1e300;
+  best = 1e300;
   bool found = false;
   for (const CpTile& c : tiles) {
     if ((force_mt && c.MT != force_mt) || (force_nt && c.NT != force_nt) || (force_mt && c.KG != (force_kg ? force_kg : 1))) continue;
@@ -586,12 +586,21 @@ hipError_t launch_t(const ConvParams& p, int splits, hipStream_t st) {
 
 bool conv_pipe_supported(const ConvParams& p) {
   CpTile c;
-  return pick(p, false, c);
+  double t;
+  return pick(p, false, c, t);
+}
+
+bool conv_few_better(const ConvParams& p, bool split) {
+  CpTile c;
+  double few, pipe;
+  if (tuning().cp_mt || !conv_few_cycles(p, few)) return false;
+  return tuning().conv_few_force || !pick(p, split, c, pipe) || few < pipe;
 }
 
 size_t conv_pipe_split_bytes(const ConvParams& p) {
   CpTile c;
-  return pick(p, true, c) ? part_bytes(p, c) : 0;
+  double t;
+  return pick(p, true, c, t) && !conv_few_better(p, true) ? part_bytes(p, c) : 0;
 }
 
 hipError_t launch_conv_split_clear(unsigned* counters, hipStream_t st) {
@@ -600,8 +609,9 @@ hipError_t launch_conv_split_clear(unsigned* counters, hipStream_t st) {
 
 hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st) {
   CpTile c;
-  bool ok = pick(p, p.part != nullptr, c);
-  if (!ok || (int64_t)part_bytes(p, c) > p.part_bytes) ok = pick(p, false, c);   // (tuning changed since the room was made)
+  double t;
+  bool ok = pick(p, p.part != nullptr, c, t);
+  if (!ok || (int64_t)part_bytes(p, c) > p.part_bytes) ok = pick(p, false, c, t);   // (tuning changed since the room was made)
   if (!ok) return hipErrorInvalidValue;
 #define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KG == K) return launch_t<M, N, K>(p, c.S, st);
   QASR_CASE(8, 4, 1) QASR_CASE(7, 4, 1) QASR_CASE(6, 4, 1) QASR_CASE(5, 4, 1) QASR_CASE(4, 4, 1) QASR_CASE(10, 2, 1) QASR_CASE(9, 2, 1)

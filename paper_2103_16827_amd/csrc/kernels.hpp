@@ -58,6 +58,13 @@ size_t conv_pipe_split_bytes(const ConvParams& p);
 hipError_t launch_conv_split_clear(unsigned* counters, hipStream_t st);
 hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st);
 
+// The same layers in launches of few frames: all input channels of a small tile in LDS, the weights streamed by 16
+// free-running waves, no workspace.  conv_few_better: whether it is the faster choice for a layer that conv_pipe takes
+// (split: there is a workspace for that to split its contraction); conv_few_cycles: its estimate, on conv_pipe's scale.
+bool conv_few_cycles(const ConvParams& p, double& cycles);
+bool conv_few_better(const ConvParams& p, bool split);
+hipError_t launch_conv_few(const ConvParams& p, hipStream_t st);
+
 // Measured ceilings (probe.hip): a streaming copy of `bytes` (a multiple of 16) and a register-resident
 // int8 matrix-core loop of probe_mfma_ops(iters) operations that writes probe_mfma_workgroups() int32.
 hipError_t launch_probe_copy(const void* src, void* dst, size_t bytes, hipStream_t st);

@@ -35,6 +35,12 @@ Tuning read_env() {
     int mt = 0, nt = 0, kg = 0, s = 0;
     if (sscanf(e, "%d,%d,%d,%d", &mt, &nt, &kg, &s) >= 1) { t.cp_mt = mt; t.cp_nt = nt; t.cp_kg = kg; t.cp_s = s; }
   }
+  t.no_conv_few = getenv("QASR_NO_CONV_FEW") != nullptr;
+  t.conv_few_force = getenv("QASR_CONV_FEW") != nullptr;
+  if (const char* e = getenv("QASR_CF")) {
+    int mt = 0, wc = 0;
+    if (sscanf(e, "%d,%d", &mt, &wc) >= 1) { t.cf_mt = mt; t.cf_wc = wc; }
+  }
   t.no_sep = getenv("QASR_NO_SEP") != nullptr;
   t.no_pw_wide = getenv("QASR_NO_PW_WIDE") != nullptr;
   t.pw_wide_force = getenv("QASR_PW_WIDE") != nullptr;

@@ -6,6 +6,8 @@
 //   QASR_DWP = "R,S"                        dw_pipe: rows per iteration, batch splits
 //   QASR_DW_R                               dw_mfma: strips per wave
 //   QASR_CP_TILE = "MT,NT[,KG[,S]]"         conv_pipe: tile, wave groups the taps and workgroups the chunks are split over
+//   QASR_NO_CONV_FEW, QASR_CONV_FEW         conv_few: never / wherever it can
+//   QASR_CF = "MT,WC"                       conv_few: groups per tile, 32-channel columns per tile (0: free)
 //   QASR_CP_PLAIN_ORDER                     conv_pipe: tile = workgroup index (no per-XCD runs of the channel-major order)
 //   QASR_PWT_MT                             pw_tile: groups per tile
 //   QASR_PWP_NOPIPE                         pw_pipe: no epilogue under the next pass's products
@@ -26,11 +28,11 @@
 namespace qasr {
 
 struct Tuning {
-  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false, no_sep = false, no_pw_wide = false, pw_wide_force = false;
+  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false, no_sep = false, no_pw_wide = false, pw_wide_force = false, no_conv_few = false, conv_few_force = false;
   int pwp_mt = 0, pwp_split = 0;
   int dwp_r = 0, dwp_s = 0;
   int dw_r = 0;
-  int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0;
+  int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0, cf_mt = 0, cf_wc = 0;
   int pwt_mt = 0;
   int sep_mt = 0, sep_nt = 0, sep_ks = 0, pww_mt = 0, pww_ks = 0;
   int slot_depth = 4;

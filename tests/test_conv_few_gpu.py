@@ -1,0 +1,65 @@
+"""Dense layers of few frames (csrc/conv_few.hip): every tile, fewer steps than wave groups and more than rings, taps that
+wrap over several chunks per step, ragged rows and channels, strides, dilations, several residual operands, tiles of more
+than 1024 transposition units; the choice the library makes for small encoders, replayed as a graph."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2103_16827_amd as Q
+import qasr_workloads as W
+from gpu_util import GpuNet, dev, gpu_layer
+from test_gpu_parity import draw, layer_case, run_layer_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    dict(name="k2_one_chunk", B=1, Cin=64, Cout=64, T=16, k=2, packed=True),
+    dict(name="k3_chunks5", B=2, Cin=320, Cout=130, T=67, k=3, packed=True, s_lo=20, s_hi=44),
+    dict(name="k11_res", B=2, Cin=256, Cout=256, T=101, k=11, packed=True, res=True, relu=False),
+    dict(name="k13_s2", B=1, Cin=128, Cout=200, T=150, k=13, stride=2, pad=(6, 6), packed=True, bias=False),
+    dict(name="k29_d2", B=1, Cin=768, Cout=96, T=130, k=29, dil=2, packed=True),
+    dict(name="k5_T4", B=3, Cin=192, Cout=64, T=4, k=5, packed=True),
+]
+
+
+@pytest.mark.parametrize("tile", ["1,1", "2,1", "3,1", "4,1", "1,2", "2,2", "3,2", "4,2"])
+@pytest.mark.parametrize("kw", SHAPES, ids=[c["name"] for c in SHAPES])
+def test_tiles(kw, tile, tuning_env):
+    tuning_env("QASR_CONV_FEW", "1")
+    tuning_env("QASR_CF", tile)
+    case = layer_case(**kw)
+    assert run_layer_case(case) == "conv_pipe"                # (the family)
+
+
+@pytest.mark.parametrize("n_res", [2, 5, 12])
+def test_several_residuals(n_res, tuning_env):
+    tuning_env("QASR_CONV_FEW", "1")
+    op, p, x, _, packed = layer_case("few_res", 2, 256, 192, 77, k=11, packed=True)
+    rs = [draw(55 + r, (2, op.Cout, op.Tout), -128, 127, np.int8) for r in range(n_res)]
+    print(f"[case] dense 256 -> 192 k=11 with {n_res} residuals", flush=True)
+    assert np.array_equal(gpu_layer(op, 2, p, x, rs, packed=packed), oracle.run_op(op, p, x, rs))
+
+
+@pytest.mark.parametrize("B,T", [(1, 60), (2, 211)])
+def test_small_encoder_takes_it(B, T):
+    net = W.jasper(B, T, 3, widths=(256, 512), kernels=(11, 17), per_width=1, C_epi=320, k_epi=29, C_epi2=128)
+    params, x = W.draw_net_params(net, 8), W.draw_input(net, 8)
+    print(f"[case] small Jasper B={B} T={T}", flush=True)
+    ref = oracle.encoder_forward(net, params, x)
+    g = GpuNet(net, params)
+    assert "conv_few" in [g.enc.op_launch(i)[1] for i in range(g.enc.n_ops)]
+    assert np.array_equal(g.forward(dev(x)).cpu().numpy(), ref)
+    g.check_guards()
+    y = torch.zeros(ref.shape, dtype=torch.int8, device="cuda")
+    ws = torch.full((max(1, g.enc.workspace_bytes),), 77, dtype=torch.int8, device="cuda")
+    xd = dev(x)
+    graph = g.enc.graph(xd, y, ws)
+    for _ in range(3):
+        y.zero_()
+        graph.launch()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy(), ref)
+        g.forward(xd)
+    graph.close()
+    g.enc.close()
