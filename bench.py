@@ -49,13 +49,13 @@ def op_algorithmic(op, B):
 
 def launch_algorithmic(ops, B):
     """The same of one launch: of a depthwise + pointwise pair, the tensor between the two is neither
-    written nor read; a projection in the pair's launch reads the input that the pair reads."""
+    written nor read; layers side by side read a common input once."""
     byts, macs = (sum(v) for v in zip(*(op_algorithmic(o, B) for o in ops)))
     for a, b in zip(ops, ops[1:]):
-        if b.depthwise:
-            byts -= B * b.Cin * b.Tin
-        else:
+        if b.in_slot == a.out_slot:
             byts -= B * a.Cout * a.Tout + B * b.Cin * b.Tin
+        elif b.in_slot == a.in_slot:
+            byts -= B * b.Cin * b.Tin
     return byts, macs
 
 

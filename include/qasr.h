@@ -363,7 +363,8 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
  *   qasr_encoder_op_launch: what qasr_encoder_forward launches for it over 16-byte aligned x and y:
  *     the op that the launch begins with (i; i - 1 where op i is the pointwise half of a depthwise +
  *     pointwise pair; one less for a pair that runs together with the pointwise layer before it, a residual
- *     projection of the same tensor; -1 if i is out of range), and in *kernel (unless NULL) the kernel's
+ *     projection of the same tensor; the first of consecutive pointwise layers of equal output shape that run
+ *     together; -1 if i is out of range), and in *kernel (unless NULL) the kernel's
  *     name: "sep" for these, "pw_wide" for pointwise layers of the pw_pipe, pw_tile and gemm_mfma families
  *     and "conv_few" for layers of the conv_pipe family that these kernels run faster, else the family's.  HOST
  *     only. */

@@ -173,6 +173,9 @@ struct qasr_encoder {
     // This pointwise op (a block's residual projection) and the pair after it read the same tensor and touch none of
     // each other's: the three may run as one launch.
     bool sep_proj = false;
+    // This and the next multi - 1 ops are pointwise layers of equal output shape that touch none of each other's
+    // outputs (the projections of a dense-residual block): they may run as one launch.  At the first of them; else 0.
+    int32_t multi = 0;
     int32_t in_channels = 0;  // channels of the slot read (p.Cin, or more for a channel-prefix view)
   };
   std::vector<Op> ops;
@@ -878,6 +881,26 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
       qasr_encoder::Op &r = e->ops[i], &dw = e->ops[i + 1], &pw = e->ops[i + 2];   // (their slots are buffers)
       r.sep_proj = r.in_channels == dw.in_channels && r.out_slot != dw.in_slot && r.out_slot != pw.out_slot && r.out_slot != pw.res_slot;
     }
+    // ---- runs of independent pointwise layers of equal output shape
+    for (int32_t i = 0; i + 1 < n_ops;) {
+      auto plain = [&](int32_t j) {
+        const qasr_op& o = ops[j];
+        return o.d.groups == 1 && o.d.k == 1 && o.d.stride == 1 && o.d.pad_left == 0 && o.d.pad_right == 0 && o.res_slot < 0 && !o.act &&
+               !e->ops[j].sep_proj;
+      };
+      int32_t n = 0;
+      while (i + n < n_ops && n < qasr::kMaxMulti && plain(i + n) && ops[i + n].d.Cout == ops[i].d.Cout &&
+             ops[i + n].d.Tin == ops[i].d.Tin) {
+        bool apart = true;                    // (slots are buffers by now; the last op of all writes the caller's output)
+        for (int32_t j = 0; j < n && apart; ++j)
+          apart = e->ops[i + j].out_slot != e->ops[i + n].in_slot && e->ops[i + j].out_slot != e->ops[i + n].out_slot &&
+                  e->ops[i + n].out_slot != e->ops[i + j].in_slot;
+        if (!apart || i + n + 1 == n_ops) break;
+        ++n;
+      }
+      if (n > 1) e->ops[i].multi = n;
+      i += n > 1 ? n : 1;
+    }
     hipError_t he = img_bytes ? hipMalloc((void**)&e->sep_images, img_bytes) : hipSuccess;
     for (int32_t i = 0; i < n_ops && he == hipSuccess; ++i) {
       qasr_encoder::Op& op = e->ops[i];
@@ -936,6 +959,18 @@ static bool runs_as_pair(const qasr_encoder* e, size_t i) {
   return qasr::sep_supported(p, q);
 }
 
+// whether the multi ops from op i on run as one launch
+static bool runs_as_multi(const qasr_encoder* e, size_t i) {
+  const int32_t n = e->ops[i].multi;
+  if (n < 2) return false;
+  ConvParams p[qasr::kMaxMulti];
+  for (int32_t j = 0; j < n; ++j) {
+    p[j] = e->ops[i + j].p;
+    rows_of(e, i + j, 0, 0, p[j]);
+  }
+  return qasr::pw_multi_better(p, n);
+}
+
 // the same for op i, a projection, with ops i + 1 and i + 2
 static bool runs_with_pair(const qasr_encoder* e, size_t i) {
   if (!e->ops[i].sep_proj) return false;
@@ -951,6 +986,11 @@ int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** ke
   for (int32_t first = i; first >= 0 && first >= i - 2; --first)
     if (runs_with_pair(e, (size_t)first)) {
       if (kernel) *kernel = "sep";
+      return first;
+    }
+  for (int32_t first = i; first >= 0 && first > i - qasr::kMaxMulti; --first)
+    if (e->ops[first].multi > i - first && runs_as_multi(e, (size_t)first)) {
+      if (kernel) *kernel = "pw_wide";
       return first;
     }
   const bool second = i > 0 && runs_as_pair(e, (size_t)i - 1);
@@ -1036,6 +1076,17 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     bind(i, p);
     if (i > 0)
       if (const hipError_t be = begin(i); be != hipSuccess) return hip_status(be);
+    if (op.multi > 1 && how.pairs) {
+      ConvParams l[qasr::kMaxMulti];
+      l[0] = p;
+      for (int32_t j = 1; j < op.multi; ++j) bind(i + j, l[j]);
+      if (qasr::pw_multi_better(l, op.multi)) {
+        const hipError_t me = qasr::launch_pw_multi(l, op.multi, st);
+        if (me != hipSuccess) return hip_status(me);
+        i += (size_t)op.multi - 1;
+        continue;
+      }
+    }
     if (op.sep_proj && how.pairs) {
       ConvParams d, q;
       bind(i + 1, d);

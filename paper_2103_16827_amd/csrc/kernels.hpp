@@ -47,6 +47,11 @@ hipError_t launch_pw_pipe(const ConvParams& p, hipStream_t st);
 bool pw_wide_supported(const ConvParams& p);
 bool pw_wide_better(const ConvParams& p, bool pipe);
 hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st);
+// Several pointwise layers of equal output shape, none of which reads what another writes, in one launch of pw_wide's
+// tiles; pw_multi_better: whether they can and it is the faster way.
+constexpr int kMaxMulti = 12;
+bool pw_multi_better(const ConvParams* p, int n);
+hipError_t launch_pw_multi(const ConvParams* p, int n, hipStream_t st);
 
 // Dense convolution (k >= 2) as an implicit GEMM pipelined over (chunk, tap) steps; needs packed
 // weights, Cin % 64 == 0, Cout >= 64.

@@ -54,18 +54,15 @@ __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
 template <int TW>
 __host__ __device__ constexpr int swizzle(int row) { return TW == 8 ? row & 7 : (row >> 2) & 3; }
 
-// RAGGED: rows of x, y or the residual that are not padded to whole 16-byte aligned units
+// RAGGED: rows of x, y or the residual that are not padded to whole 16-byte aligned units; v: (tile, split)
 template <int MT, int NT, int KS, bool RAGGED>
-__global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) {
+__device__ __forceinline__ void pw_wide_tile(const ConvParams& p, const PwwGeom& g, int v) {
   constexpr int TW = MT > 4 ? 8 : 4;                // units per LDS row
   constexpr int NWC = 16 / KS;                      // waves over the output channels
   extern __shared__ __align__(128) unsigned char xs[];   // tile; then partial sums, staged rows; table
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave % NWC, ks = wave / NWC;
-  // consecutive workgroups go round-robin to the 8 XCDs: each takes a contiguous run of (tile, split)
-  const int v = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= g.per_xcd || v >= g.wgs) return;                 // whole workgroup
   const int tile = v / g.splits, cs = v - tile * g.splits;
   const int g0 = tile * MT;
   const int xpitch = p.Tin + p.xpad, ypitch = p.Tout + p.ypad;
@@ -295,6 +292,44 @@ __global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) 
   }
 }
 
+template <int MT, int NT, int KS, bool RAGGED>
+__global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) {
+  // consecutive workgroups go round-robin to the 8 XCDs: each takes a contiguous run of (tile, split)
+  const int v = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= g.per_xcd || v >= g.wgs) return;                 // whole workgroup
+  pw_wide_tile<MT, NT, KS, RAGGED>(p, g, v);
+}
+
+// Several layers of equal output shape and nothing in common but that none reads what another writes (the projections of
+// a dense-residual block: 55 launches of about 5 us in a Jasper-10x5, each of a few workgroups that wait for their
+// first loads): the workgroups of all of them in one launch, 10 in all.  A whole Jasper-10x5 dense-residual forward, us,
+// one by one / together: 1 x 208 frames 791 / 563, 2 x 811 1074 / 837, 4 x 800 1409 / 1167, 16 x 800 2687 / 2517.
+struct PwMulti {
+  struct Item {
+    const int8_t *x, *w;
+    const int32_t *bias, *m, *s;
+    int8_t* y;
+    int64_t xbs;
+    int32_t Cin, relu;
+  } item[kMaxMulti];
+  int wgs1;                                         // workgroups of one layer
+  float r_wgs1;                                     // its reciprocal
+};
+
+template <int MT, int NT, int KS>
+__global__ __launch_bounds__(1024) void pw_multi_kernel(ConvParams p, PwwGeom g, PwMulti l) {
+  const int v = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= g.per_xcd || v >= g.wgs) return;                 // whole workgroup
+  int i = __builtin_amdgcn_readfirstlane((int)((float)v * l.r_wgs1));            // (v < 2^22: off by one at most)
+  if (v < i * l.wgs1) --i;
+  if (v >= (i + 1) * l.wgs1) ++i;
+  const PwMulti::Item& q = l.item[i];
+  p.x = q.x; p.w = q.w; p.bias = q.bias; p.m = q.m; p.s = q.s; p.y = q.y; p.xbs = q.xbs; p.relu = q.relu;
+  p.Cin = q.Cin;
+  g.kch = q.Cin / 64;
+  pw_wide_tile<MT, NT, KS, false>(p, g, v - i * l.wgs1);
+}
+
 struct Choice { int MT, NT, KS; };
 
 // LDS: the tile; over it, or after it if there is room (KS = 1), the staged rows (and what the last wave's
@@ -318,10 +353,10 @@ bool ragged_rows(const ConvParams& p) {
          (uintptr_t)p.y % 16 || (uintptr_t)p.res % 16;
 }
 
-// The tile with the least time (us) on the busiest compute unit: its matrix pipes (17.7 cycles per
-// product), its LDS port and its 64 bytes per cycle from the L2, whichever is longest, plus the chain of
+// The tile with the least time (us) on the busiest compute unit, for `layers` such layers at once that have at least
+// least_cin input channels: its matrix pipes (17.7 cycles per product), its LDS port and its 64 bytes per cycle from the L2, whichever is longest, plus the chain of
 // first loads and last stores and the epilogue's instructions.
-bool pick(const ConvParams& p, int cus, Choice& best, double& us) {
+bool pick(const ConvParams& p, int cus, int layers, int least_cin, Choice& best, double& us) {
   if (p.depthwise || p.k != 1 || p.stride != 1 || p.pl != 0 || p.Tout != p.Tin || p.n_res_more) return false;
   if (!p.w_packed || (uintptr_t)p.w % 16 || p.Tin < 4 || p.Cin % 64) return false;
   const int64_t G = (int64_t)p.B * ((p.Tin + 15) / 16);
@@ -333,8 +368,8 @@ bool pick(const ConvParams& p, int cus, Choice& best, double& us) {
   for (const Choice& c : all) {
     const int TW = c.MT > 4 ? 8 : 4, nch = 16 / c.KS * c.NT * 16;
     if ((tuning().pww_mt && c.MT != tuning().pww_mt) || (tuning().pww_ks && c.KS != tuning().pww_ks)) continue;
-    if (c.KS > kch || (p.Cin * TW + 1023) / 1024 > kMaxLoads || lds_bytes(p, c) > 160 * 1024) continue;
-    const int64_t splits = (p.Cout + nch - 1) / nch, wgs = (G + c.MT - 1) / c.MT * splits;
+    if (c.KS > least_cin / 64 || (p.Cin * TW + 1023) / 1024 > kMaxLoads || lds_bytes(p, c) > 160 * 1024) continue;
+    const int64_t splits = (p.Cout + nch - 1) / nch, wgs = (G + c.MT - 1) / c.MT * splits * layers;
     if (wgs > max_workgroups(1024)) continue;       // (the other families' tiles cover more frames per thread)
     const int steps = (kch + c.KS - 1) / c.KS;
     const double mfma = c.MT * c.NT * steps * 17.7 * 4, lds = 16.0 * c.MT * steps * 8;
@@ -347,22 +382,29 @@ bool pick(const ConvParams& p, int cus, Choice& best, double& us) {
   return us < 1e300;
 }
 
-template <int MT, int NT, int KS, bool RAGGED>
-hipError_t launch_t(const ConvParams& p, hipStream_t st) {
-  const Choice c{MT, NT, KS};
+// for `layers` layers like p, of which p has the most input channels
+PwwGeom geometry(const ConvParams& p, const Choice& c, int layers) {
+  const int MT = c.MT, NT = c.NT, KS = c.KS;
   PwwGeom g;
   g.gpr = (p.Tin + 15) / 16;
   g.G = p.B * g.gpr;
   g.kch = p.Cin / 64;
   g.co16n = (p.Cout + 15) / 16;
   g.splits = (p.Cout + 16 / KS * NT * 16 - 1) / (16 / KS * NT * 16);
-  g.wgs = (g.G + MT - 1) / MT * g.splits;
+  g.wgs = (g.G + MT - 1) / MT * g.splits * layers;
   g.per_xcd = (g.wgs + 7) / 8;
-  const size_t lds = lds_bytes(p, c);
   const Lds l = lds_layout(p, c);
   g.stage_off = l.stage_off;
   g.own_stage = l.own_stage;
   g.lut_off = l.lut_off;
+  return g;
+}
+
+template <int MT, int NT, int KS, bool RAGGED>
+hipError_t launch_t(const ConvParams& p, hipStream_t st) {
+  const Choice c{MT, NT, KS};
+  const PwwGeom g = geometry(p, c, 1);
+  const size_t lds = lds_bytes(p, c);
   static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
   if (const hipError_t e = ensure_max_dynamic_lds((const void*)pw_wide_kernel<MT, NT, KS, RAGGED>, lds_raised); e != hipSuccess)
     return e;
@@ -374,7 +416,7 @@ hipError_t launch_t(const ConvParams& p, hipStream_t st) {
 bool pw_wide_supported(const ConvParams& p) {
   Choice c;
   double t;
-  return !tuning().no_pw_wide && pick(p, 256, c, t);
+  return !tuning().no_pw_wide && pick(p, 256, 1, p.Cin, c, t);
 }
 
 // Where this kernel is the faster one, in 16-frame groups G.  Measured on single layers whose weights and
@@ -417,9 +459,68 @@ bool pw_wide_better(const ConvParams& p, bool pipe) {
 hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st) {
   Choice c;
   double t;
-  if (!pick(p, compute_units(), c, t)) return hipErrorInvalidValue;
+  if (!pick(p, compute_units(), 1, p.Cin, c, t)) return hipErrorInvalidValue;
   const bool ragged = ragged_rows(p);
 #define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KS == K) return ragged ? launch_t<M, N, K, true>(p, st) : launch_t<M, N, K, false>(p, st);
+  QASR_CASE(1, 2, 1) QASR_CASE(2, 2, 1) QASR_CASE(4, 2, 1) QASR_CASE(7, 2, 1)
+  QASR_CASE(1, 2, 2) QASR_CASE(2, 2, 2) QASR_CASE(4, 2, 2) QASR_CASE(7, 2, 2)
+  QASR_CASE(1, 2, 4) QASR_CASE(2, 2, 4) QASR_CASE(4, 2, 4)
+  QASR_CASE(1, 1, 8) QASR_CASE(2, 1, 8) QASR_CASE(4, 1, 8)
+#undef QASR_CASE
+  return hipErrorInvalidValue;
+}
+
+// the tile for all of them, by the layer with the most input channels
+static bool pick_multi(const ConvParams* p, int n, int cus, int& most, Choice& c, double& us) {
+  most = 0;
+  int least = 0;
+  for (int i = 1; i < n; ++i) {
+    if (p[i].Cin > p[most].Cin) most = i;
+    if (p[i].Cin < p[least].Cin) least = i;
+  }
+  return pick(p[most], cus, n, p[least].Cin, c, us);
+}
+
+// Layers one by one take at least 4.7 us each (launch and first loads), whichever kernel runs them; a chip that each of
+// them fills has kernels up to a fifth faster than this one, which is the line.  At 16 x 1600 frames and 512 channels
+// it divides blocks of a few layers from the others: together wherever it can be 4165 us, by this rule 4172, never 4232.
+bool pw_multi_better(const ConvParams* p, int n) {
+  if (n < 2 || n > kMaxMulti || tuning().no_pw_wide || tuning().no_pw_multi) return false;
+  const ConvParams& f = p[0];
+  Choice c;
+  int most;
+  double t, one_by_one = 0.0;
+  for (int i = 0; i < n; ++i) {
+    const ConvParams& q = p[i];
+    if (q.res || q.act_lut || q.n_res_more || ragged_rows(q) || q.B != f.B || q.Cout != f.Cout || q.Tin != f.Tin ||
+        q.Tout != f.Tout || q.xpad != f.xpad || q.ypad != f.ypad || q.ybs != f.ybs || !pick(q, 256, 1, q.Cin, c, t))
+      return false;
+    one_by_one += t + 1.2;
+  }
+  return pick_multi(p, n, 256, most, c, t) && (tuning().pw_multi_force || t + 1.2 < 0.8 * one_by_one);
+}
+
+template <int MT, int NT, int KS>
+static hipError_t launch_multi_t(const ConvParams& most, const ConvParams* p, int n, hipStream_t st) {
+  const Choice c{MT, NT, KS};
+  const PwwGeom g = geometry(most, c, n);
+  const size_t lds = lds_bytes(most, c);
+  PwMulti l{};
+  for (int i = 0; i < n; ++i) l.item[i] = {p[i].x, p[i].w, p[i].bias, p[i].m, p[i].s, p[i].y, p[i].xbs, p[i].Cin, p[i].relu};
+  l.wgs1 = g.wgs / n;
+  l.r_wgs1 = 1.0f / (float)l.wgs1;
+  static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
+  if (const hipError_t e = ensure_max_dynamic_lds((const void*)pw_multi_kernel<MT, NT, KS>, lds_raised); e != hipSuccess) return e;
+  return launch_kernel(pw_multi_kernel<MT, NT, KS>, dim3((unsigned)(8 * g.per_xcd)), dim3(1024), lds, st, most, g, l);
+}
+
+hipError_t launch_pw_multi(const ConvParams* p, int n, hipStream_t st) {
+  if (!pw_multi_better(p, n)) return hipErrorInvalidValue;
+  Choice c;
+  int most;
+  double t;
+  if (!pick_multi(p, n, compute_units(), most, c, t)) return hipErrorInvalidValue;
+#define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KS == K) return launch_multi_t<M, N, K>(p[most], p, n, st);
   QASR_CASE(1, 2, 1) QASR_CASE(2, 2, 1) QASR_CASE(4, 2, 1) QASR_CASE(7, 2, 1)
   QASR_CASE(1, 2, 2) QASR_CASE(2, 2, 2) QASR_CASE(4, 2, 2) QASR_CASE(7, 2, 2)
   QASR_CASE(1, 2, 4) QASR_CASE(2, 2, 4) QASR_CASE(4, 2, 4)

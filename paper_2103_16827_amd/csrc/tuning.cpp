@@ -41,6 +41,8 @@ Tuning read_env() {
     int mt = 0, wc = 0;
     if (sscanf(e, "%d,%d", &mt, &wc) >= 1) { t.cf_mt = mt; t.cf_wc = wc; }
   }
+  t.no_pw_multi = getenv("QASR_NO_PW_MULTI") != nullptr;
+  t.pw_multi_force = getenv("QASR_PW_MULTI") != nullptr;
   t.no_sep = getenv("QASR_NO_SEP") != nullptr;
   t.no_pw_wide = getenv("QASR_NO_PW_WIDE") != nullptr;
   t.pw_wide_force = getenv("QASR_PW_WIDE") != nullptr;
