@@ -45,6 +45,22 @@ struct ConvParams {
 };
 constexpr int kMaxMoreRes = 11;
 
+// v / d for wave-uniform operands, rd = 1.0f / d: below 2^24 the estimate is off by one at most
+__device__ __forceinline__ int divide_uniform(int v, int d, float rd) {
+  if (v >= 1 << 24) return v / d;
+  const int q = __builtin_amdgcn_readfirstlane((int)((float)v * rd));
+  const int r = v - q * d;
+  return r < 0 ? q - 1 : r >= d ? q + 1 : q;
+}
+
+// q = d w + r for 0 <= q < d + 8, rd = 1.0f / d, per lane (the quotient is at most 8: the estimate is off by one at most)
+__device__ __forceinline__ void split_near(int q, int d, float rd, int& w, int& r) {
+  w = (int)((float)q * rd);
+  r = q - w * d;
+  if (r < 0) { --w; r += d; }
+  if (r >= d) { ++w; r -= d; }
+}
+
 // bytes >= keep of a 16-byte chunk set to zero (1 <= keep <= 15)
 typedef int chunk16 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ chunk16 keep_bytes(chunk16 v, int keep) {

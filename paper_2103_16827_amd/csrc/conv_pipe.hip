@@ -63,14 +63,6 @@ struct CpGeom {
   int fq_inv;         // ceil(2^16 / (rows / 4)): x / (rows / 4) = x fq_inv >> 16 for x < 256, rows <= 256
 };
 
-// v / d for wave-uniform operands, rd = 1.0f / d: below 2^24 the estimate is off by one at most
-__device__ __forceinline__ int divide(int v, int d, float rd) {
-  if (v >= 1 << 24) return v / d;
-  const int q = __builtin_amdgcn_readfirstlane((int)((float)v * rd));
-  const int r = v - q * d;
-  return r < 0 ? q - 1 : r >= d ? q + 1 : q;
-}
-
 // KG > 1: the taps of a chunk are split over KG groups of 4 waves that share the chunk in LDS, and their
 // accumulators are summed through LDS at the end.  A launch with fewer tiles than the chip has SIMDs to
 // feed leaves one wave per SIMD, which spends most of a step waiting (a 64 x 128 tile: 128 cycles of
@@ -103,14 +95,14 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   const int v = g.per_xcd ? (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
   if (v >= g.tiles) return;                         // whole workgroup, before any barrier
   const int nbt = p.B * g.n_tt;
-  const int cs = divide(v, nbt, g.r_nbt), bt = v - cs * nbt;   // bt: (b, t_tile) of the tile
-  const int co_tile = g.splits == 1 ? cs : divide(cs, g.splits, g.r_splits), split = cs - co_tile * g.splits;
+  const int cs = divide_uniform(v, nbt, g.r_nbt), bt = v - cs * nbt;   // bt: (b, t_tile) of the tile
+  const int co_tile = g.splits == 1 ? cs : divide_uniform(cs, g.splits, g.r_splits), split = cs - co_tile * g.splits;
   int c0 = 0, nkc = g.kchunks;                      // this workgroup's chunks
   if (g.splits > 1) {
-    c0 = divide(split * g.kchunks, g.splits, g.r_splits);
-    nkc = divide((split + 1) * g.kchunks, g.splits, g.r_splits) - c0;
+    c0 = divide_uniform(split * g.kchunks, g.splits, g.r_splits);
+    nkc = divide_uniform((split + 1) * g.kchunks, g.splits, g.r_splits) - c0;
   }
-  const int b = divide(bt, g.n_tt, g.r_tt), t_tile = bt - b * g.n_tt;
+  const int b = divide_uniform(bt, g.n_tt, g.r_tt), t_tile = bt - b * g.n_tt;
 
   const int t0 = t_tile * TM;                       // first output frame of the tile
   const int f0 = t0 * p.stride - p.pl;              // first input frame the tile reads

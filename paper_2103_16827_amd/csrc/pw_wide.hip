@@ -42,6 +42,7 @@ struct PwwGeom {
   int stage_off;        // of the staged rows in LDS
   int own_stage;        // ... which do not overlap the tile
   int lut_off;          // of the activation's table
+  float r_splits, r_gpr;   // reciprocals of splits, gpr
 };
 
 __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
@@ -55,7 +56,7 @@ template <int TW>
 __host__ __device__ constexpr int swizzle(int row) { return TW == 8 ? row & 7 : (row >> 2) & 3; }
 
 // RAGGED: rows of x, y or the residual that are not padded to whole 16-byte aligned units; v: (tile, split)
-template <int MT, int NT, int KS, bool RAGGED>
+template <int MT, int NT, int KS, bool RAGGED, bool MULTI>
 __device__ __forceinline__ void pw_wide_tile(const ConvParams& p, const PwwGeom& g, int v) {
   constexpr int TW = MT > 4 ? 8 : 4;                // units per LDS row
   constexpr int NWC = 16 / KS;                      // waves over the output channels
@@ -63,34 +64,57 @@ __device__ __forceinline__ void pw_wide_tile(const ConvParams& p, const PwwGeom&
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave % NWC, ks = wave / NWC;
-  const int tile = v / g.splits, cs = v - tile * g.splits;
+  // All arguments of the first loads in one go; no integer division and, on whole rows, no address per load.  With them
+  // the last of the sixteen waves had asked for its part of the tile after 3000 to 7600 cycles, 1300 to 4500 of
+  // them such arithmetic.  Single layers, us, before / now: 512 -> 512 G=13 5.1 / 4.5, G=200 6.8 / 6.6; 256 -> 256 G=100
+  // 5.25 / 4.85, G=1600 9.1 / 8.6; 2048 -> 512 G=50 8.4 / 7.9.
+  // (MULTI: a layer's own arguments arrive later, a level further from the kernel's.)
+  asm volatile("" ::"s"(p.Tin), "s"(p.xpad), "s"(g.G), "s"(g.gpr), "s"(g.splits), "s"(g.r_splits), "s"(g.r_gpr));
+  if constexpr (!MULTI) asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.xbs), "s"(p.Cin), "s"(g.kch));
+  const int tile = divide_uniform(v, g.splits, g.r_splits), cs = v - tile * g.splits;
   const int g0 = tile * MT;
   const int xpitch = p.Tin + p.xpad, ypitch = p.Tout + p.ypad;
+  const int b0 = divide_uniform(g0, g.gpr, g.r_gpr), q0 = g0 - b0 * g.gpr;   // batch item of the tile's first unit; unit of its row
+  // unit u < 8 of the tile: batch item after b0, first frame
+  auto unit = [&](int u, int& db, int& t) __attribute__((always_inline)) {
+    split_near(q0 + u, g.gpr, g.r_gpr, db, t);
+    t *= 16;
+  };
 
   // ---- tile: thread -> unit tid % TW of rows tid / TW, + 1024 / TW, ...
   {
-    const int u = tid & (TW - 1), gq = g0 + u;
-    const bool on = u < MT && gq < g.G;
-    const int b = on ? gq / g.gpr : 0, t = on ? 16 * (gq - b * g.gpr) : 0;
-    const int8_t* const src = p.x + (int64_t)b * p.xbs + (int64_t)(tid / TW) * xpitch;
+    const int u = tid & (TW - 1), row0 = tid / TW, step = 1024 / TW;
+    const bool on = u < MT && g0 + u < g.G;
+    int db, t;
+    unit(u, db, t);
     v4i r[kMaxLoads];
-    const int n = (p.Cin * TW + 1023) / 1024;       // (uniform)
+    const int wrow = wave * (64 / TW);              // first of the wave's rows (Cin is a multiple of 64: all of them or none)
+    if constexpr (RAGGED) {
+      const int8_t* const src = p.x + (int64_t)(b0 + (on ? db : 0)) * p.xbs + (int64_t)row0 * xpitch;
 #pragma unroll
-    for (int i = 0; i < kMaxLoads; ++i) {
-      r[i] = (v4i){0, 0, 0, 0};
-      const int row = tid / TW + i * (1024 / TW);
-      if (i < n && on && row < p.Cin) {
-        const int8_t* const s = src + (int64_t)i * (1024 / TW) * xpitch;
-        r[i] = RAGGED ? load_row16(s, t, p.Tin) : *reinterpret_cast<const v4i*>(s + t);
+      for (int i = 0; i < kMaxLoads; ++i) {
+        r[i] = (v4i){0, 0, 0, 0};
+        if (wrow + i * step < p.Cin && on) r[i] = load_row16(src + (int64_t)i * step * xpitch, t, p.Tin);
       }
+    } else {
+      const __amdgpu_buffer_rsrc_t xrs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(p.x) + (int64_t)b0 * p.xbs, 0, 0x7ffffff0, 0x00027000);
+      // (outside the tile: past the end of the buffer, which reads zeros)
+      const uint32_t at = on ? (uint32_t)db * (uint32_t)p.xbs + (uint32_t)row0 * (uint32_t)xpitch + (uint32_t)t : 0xfffffff0u;
+#pragma unroll
+      for (int i = 0; i < kMaxLoads; ++i)
+        if (wrow + i * step < p.Cin) {
+          const v4u w = __builtin_amdgcn_raw_buffer_load_b128(xrs, at, i * step * xpitch, 0);
+          r[i] = (v4i){(int)w.x, (int)w.y, (int)w.z, (int)w.w};
+        }
     }
     if (p.act_lut && tid < 64)
       reinterpret_cast<uint32_t*>(xs + g.lut_off)[tid] = reinterpret_cast<const uint32_t*>(p.act_lut)[tid];
+    static_assert(swizzle<TW>(1024 / TW) == 0, "a thread's rows share the swizzle");
+    unsigned char* const dst = xs + row0 * (16 * TW) + ((u ^ swizzle<TW>(row0)) << 4);
 #pragma unroll
-    for (int i = 0; i < kMaxLoads; ++i) {
-      const int row = tid / TW + i * (1024 / TW);
-      if (i < n && row < p.Cin) *reinterpret_cast<v4i*>(xs + row * (16 * TW) + ((u ^ swizzle<TW>(row)) << 4)) = r[i];
-    }
+    for (int i = 0; i < kMaxLoads; ++i)
+      if (wrow + i * step < p.Cin) *reinterpret_cast<v4i*>(dst + i * (step * 16 * TW)) = r[i];
   }
 
   // ---- products: input channel chunks ks, ks + KS, ... x 16 NT output channels
@@ -178,16 +202,14 @@ __device__ __forceinline__ void pw_wide_tile(const ConvParams& p, const PwwGeom&
   const unsigned char* const lut = xs + g.lut_off;
   const int row_l = lane / TW, slot_l = lane & (TW - 1);
   // (offsets from the tile's first batch item: 32 bits)
-  const int b0 = g0 / g.gpr;
   const int64_t ybase = (int64_t)b0 * p.ybs;
   auto piece = [&](int it, uint32_t& at, int& t) __attribute__((always_inline)) {   // of the residual / output
     const int row = wave * RPW + it * RPI + row_l;
-    const int u = slot_l ^ swizzle<TW>(row), gq = g0 + u, co = cs * (16 * RPW) + row;
-    const bool ok = it * RPI + row_l < RPW && u < MT && gq < g.G && co < p.Cout;
-    const int b = ok ? gq / g.gpr : b0;
-    t = ok ? 16 * (gq - b * g.gpr) : 0;
-    at = (uint32_t)(b - b0) * (uint32_t)p.ybs + (uint32_t)co * (uint32_t)ypitch;
-    return ok;
+    const int u = slot_l ^ swizzle<TW>(row), co = cs * (16 * RPW) + row;
+    int db;
+    unit(u, db, t);
+    at = (uint32_t)db * (uint32_t)p.ybs + (uint32_t)co * (uint32_t)ypitch;
+    return it * RPI + row_l < RPW && u < MT && g0 + u < g.G && co < p.Cout;
   };
   v4i rr[NI];
   if (p.res) {
@@ -297,7 +319,7 @@ __global__ __launch_bounds__(1024) void pw_wide_kernel(ConvParams p, PwwGeom g) 
   // consecutive workgroups go round-robin to the 8 XCDs: each takes a contiguous run of (tile, split)
   const int v = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= g.per_xcd || v >= g.wgs) return;                 // whole workgroup
-  pw_wide_tile<MT, NT, KS, RAGGED>(p, g, v);
+  pw_wide_tile<MT, NT, KS, RAGGED, false>(p, g, v);
 }
 
 // Several layers of equal output shape and nothing in common but that none reads what another writes (the projections of
@@ -320,14 +342,12 @@ template <int MT, int NT, int KS>
 __global__ __launch_bounds__(1024) void pw_multi_kernel(ConvParams p, PwwGeom g, PwMulti l) {
   const int v = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= g.per_xcd || v >= g.wgs) return;                 // whole workgroup
-  int i = __builtin_amdgcn_readfirstlane((int)((float)v * l.r_wgs1));            // (v < 2^22: off by one at most)
-  if (v < i * l.wgs1) --i;
-  if (v >= (i + 1) * l.wgs1) ++i;
+  const int i = divide_uniform(v, l.wgs1, l.r_wgs1);
   const PwMulti::Item& q = l.item[i];
   p.x = q.x; p.w = q.w; p.bias = q.bias; p.m = q.m; p.s = q.s; p.y = q.y; p.xbs = q.xbs; p.relu = q.relu;
   p.Cin = q.Cin;
   g.kch = q.Cin / 64;
-  pw_wide_tile<MT, NT, KS, false>(p, g, v - i * l.wgs1);
+  pw_wide_tile<MT, NT, KS, false, true>(p, g, v - i * l.wgs1);
 }
 
 struct Choice { int MT, NT, KS; };
@@ -360,7 +380,8 @@ bool pick(const ConvParams& p, int cus, int layers, int least_cin, Choice& best,
   if (p.depthwise || p.k != 1 || p.stride != 1 || p.pl != 0 || p.Tout != p.Tin || p.n_res_more) return false;
   if (!p.w_packed || (uintptr_t)p.w % 16 || p.Tin < 4 || p.Cin % 64) return false;
   const int64_t G = (int64_t)p.B * ((p.Tin + 15) / 16);
-  if (G > 0x3fffffff || 8 * p.ybs > 0x7ffffff0LL) return false;      // 32-bit offsets within a tile's batch items
+  // 32-bit offsets within a tile's batch items (and from the first of them to the last row)
+  if (G > 0x3fffffff || 8 * p.ybs > 0x7ffffff0LL || 8 * p.xbs + (int64_t)p.Cin * (p.Tin + p.xpad) > 0x7ffffff0LL) return false;
   static const Choice all[] = {{1, 2, 1}, {2, 2, 1}, {4, 2, 1}, {7, 2, 1}, {1, 2, 2}, {2, 2, 2}, {4, 2, 2}, {7, 2, 2},
                                {1, 2, 4}, {2, 2, 4}, {4, 2, 4}, {1, 1, 8}, {2, 1, 8}, {4, 1, 8}};
   const int kch = p.Cin / 64;
@@ -397,6 +418,8 @@ PwwGeom geometry(const ConvParams& p, const Choice& c, int layers) {
   g.stage_off = l.stage_off;
   g.own_stage = l.own_stage;
   g.lut_off = l.lut_off;
+  g.r_splits = 1.0f / (float)g.splits;
+  g.r_gpr = 1.0f / (float)g.gpr;
   return g;
 }
 
@@ -423,20 +446,20 @@ bool pw_wide_supported(const ConvParams& p) {
 // tensors come from memory (us, the other kernel / this one), 50 shapes at up to 14 sizes each; with these
 // lines the choice is within 1 % of the better kernel on average.
 //   pw_tile (one pass after another per workgroup):
-//     257 to 512 channels are one workgroup's here, which stays ahead: 640 -> 512 G=50 9.6 / 6.0, G=1000 10.8 / 9.9,
-//       G=3200 28.3 / 26.7; 384 -> 384 G=400 7.9 / 6.9, G=1400 10.3 / 8.7 (but G=560 8.1 / 8.7);
+//     257 to 512 channels are one workgroup's here, which stays ahead: 640 -> 512 G=50 9.4 / 5.3, G=1000 11.9 / 10.7,
+//       G=3200 29.2 / 26.3; 384 -> 384 G=400 8.1 / 7.0, G=1400 10.7 / 8.5 (but G=550 8.1 / 8.4);
 //     beyond 512, workgroups share a tile, which pays while all of them (of 7 groups x 512 channels) run at once:
-//       640 -> 768 G=200 13.5 / 7.7, G=700 15.0 / 12.4, G=900 (258 workgroups) 15.4 / 21.2; with 1024 input channels pw_tile has LDS for 128 channels at a time only: 1024 -> 1000
-//       G=200 35.9 / 9.8, G=2000 49.5 / 44.7;
-//     up to 256 channels, the input channels are split over the waves: 1024 -> 29 G=200 7.0 / 5.5, G=700 7.4 / 6.8, G=1400
-//       8.9 / 9.8; 512 -> 128 G=104 5.5 / 5.5, G=400 5.7 / 6.1; 256 -> 128 G=104 4.4 / 5.1;
+//       640 -> 768 G=200 14.3 / 8.3, G=700 15.4 / 12.3, G=900 (258 workgroups) 15.7 / 19.8; with 1024 input channels pw_tile
+//       has LDS for 128 channels at a time only: 1024 -> 1000 G=200 36.9 / 10.2, G=2000 52.1 / 49.5;
+//     up to 256 channels, the input channels are split over the waves: 1024 -> 29 G=200 6.6 / 4.9, G=700 6.8 / 5.8, G=1400
+//       8.0 / 8.4; 512 -> 128 G=100 5.5 / 4.7, G=400 5.6 / 5.4; 256 -> 128 G=100 4.7 / 4.8;
 //   pw_pipe with 1024 and 2048 input channels (streamed through a ring, a barrier per 64 of them):
-//     2048 -> 512 G=100 11.9 / 9.5, G=200 10.9 / 10.4, G=300 12.2 / 14.6; 1024 -> 1024 G=50 8.1 / 8.0, G=200 8.0 / 9.6;
+//     2048 -> 512 G=100 11.6 / 9.3, G=200 11.8 / 10.8, G=300 12.0 / 12.8; 1024 -> 1024 G=50 8.1 / 7.4, G=200 8.9 / 10.1;
 //   pw_pipe whose passes cannot be split over workgroups (not a power of two, or the last one is partial) and are not
-//     the lean form's: 512 -> 768 G=200 10.5 / 7.4, G=300 (lean) 6.9 / 7.9, G=1600 15.8 / 22.2; 512 -> 1000 G=100
-//     13.1 / 7.0, G=800 13.2 / 11.3, G=1600 18.0 / 22.0; 256 -> 384 G=100 6.3 / 5.6, G=300 6.6 / 6.7;
-//   all else is pw_pipe's: 512 -> 2048 G=400 11.4 / 12.2, G=1400 32.8 / 42.3; 512 -> 1024 G=350 7.3 / 9.9, G=1600 19.9 / 23.3;
-//     512 -> 512 G=200 5.7 / 6.6, G=1600 11.7 / 12.9.
+//     the lean form's: 512 -> 768 G=200 11.1 / 7.5, G=300 (lean) 7.2 / 7.9, G=1600 16.5 / 20.7; 512 -> 1000 G=100
+//     13.5 / 6.9, G=800 14.7 / 11.9, G=1600 20.1 / 23.2; 256 -> 384 G=100 6.3 / 5.0, G=300 6.5 / 6.2;
+//   all else is pw_pipe's: 512 -> 2048 G=400 12.5 / 12.5, G=1400 33.5 / 40.6; 512 -> 1024 G=350 7.8 / 10.1, G=1600 19.8 / 24.0;
+//     512 -> 512 G=200 5.9 / 6.7, G=1600 12.0 / 12.3.
 // (Host only, before any device is asked: for the whole chip's 256 units.)
 bool pw_wide_better(const ConvParams& p, bool pipe) {
   const Tuning& t = tuning();
