@@ -126,6 +126,8 @@ hipError_t launch_a(const ConvParams& p, int splits, hipStream_t st) {
   g.splits = splits;
   g.pps = g.passes / splits;
   g.nopipe = tuning().pwp_nopipe ? 1 : 0;
+  g.r_gpr = 1.0f / (float)g.gpr;
+  g.r_grid = 1.0f / (float)(8 * g.tiles_per_xcd);
   static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
   if (const hipError_t e = ensure_max_dynamic_lds((const void*)pw_pipe_kernel<MT, KCH, ACT>, lds_raised); e != hipSuccess)
     return e;
@@ -145,6 +147,8 @@ hipError_t launch_lean(const ConvParams& p, hipStream_t st) {
   g.splits = g.passes;
   g.pps = 1;
   g.nopipe = 1;
+  g.r_gpr = 1.0f / (float)g.gpr;
+  g.r_grid = 1.0f / (float)(8 * g.tiles_per_xcd);
   static std::atomic<uint64_t> lds_raised{0};
   if (const hipError_t e = ensure_max_dynamic_lds((const void*)pw_lean_kernel<MT, KCH>, lds_raised, lds_bytes_lean_c<KCH>());
       e != hipSuccess)
