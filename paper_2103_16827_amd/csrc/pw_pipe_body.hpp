@@ -31,8 +31,11 @@ struct PwpGeom {
   int tiles, tiles_per_xcd;
   int splits, pps;   // workgroups per tile (each takes pps consecutive passes of the output channels)
   int nopipe;        // tuning: every pass does its epilogue right after its own products
-  float r_gpr, r_grid;   // reciprocals of gpr and 8 tiles_per_xcd (the stand-alone kernels)
 };
+
+// Where a workgroup and a lane are, if the kernel has found out already (the stand-alone ones: with host-side reciprocals
+// instead of three integer divisions): which part of the passes; batch item and group of the lane's unit.
+struct PwpPlace { bool given = false; int part = 0, b_l = 0, t16_l = 0; };
 
 __device__ __forceinline__ v2i lds_read_tr8(const unsigned char* p) {
   return __builtin_amdgcn_ds_read_tr8_b64_v2i32(
@@ -71,7 +74,7 @@ constexpr int kLeanResAfter = 5;   // 512 input channels: residual rows requeste
 // products of the other by chance instead of by construction.
 template <int MT, int KCH, bool ACT, bool TEAM, int LOOK = kLookW, bool LEAN = false>
 __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom& g, unsigned vblock,
-                                             unsigned char* const xs, int tid) {
+                                             unsigned char* const xs, int tid, const PwpPlace at = PwpPlace()) {
   constexpr int NB = MT * NT;                     // epilogue blocks of a pass
   static_assert(KCH == 4 || KCH == 8 || KCH == 16 || KCH == 32, "instantiated input widths");
   static_assert(KCH % LOOK == 0, "ring slot of a chunk");
@@ -90,11 +93,7 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
   // When the tiles alone do not fill the chip, `splits` workgroups share a tile, each with its own
   // run of passes (the tile's workgroups have the same blockIdx & 7: same XCD, the activation tile
   // comes out of that L2 for all but the first).
-  // (no integer divisions before the first loads; the arguments of those in one go)
-  if constexpr (!TEAM)
-    asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.res), "s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.xbs), "s"(p.ybs), "s"(p.Cout), "s"(p.Tin),
-                 "s"(p.Tout), "s"(g.G), "s"(g.gpr), "s"(g.tiles), "s"(g.tiles_per_xcd), "s"(g.r_gpr), "s"(g.r_grid));
-  const int part = TEAM ? 0 : divide_uniform((int)vblock, 8 * g.tiles_per_xcd, g.r_grid);
+  const int part = TEAM ? 0 : at.given ? at.part : (int)(vblock / (unsigned)(8 * g.tiles_per_xcd));
   const int bx = (int)vblock - part * (8 * g.tiles_per_xcd);
   const int pb = part * g.pps;                                                     // first pass of this workgroup
   const int tile = TEAM ? bx : (bx & 7) * g.tiles_per_xcd + (bx >> 3);
@@ -110,15 +109,7 @@ __device__ __forceinline__ void pw_pipe_tile(const ConvParams& p, const PwpGeom&
   const int u_l = (lane & 7) ^ (lane >> 3);
   const int gq_l = g0 + u_l;
   const bool u_ok = u_l < MT && gq_l < g.G;
-  int b_l, t16_l;
-  if constexpr (TEAM) {
-    b_l = gq_l / g.gpr;
-    t16_l = gq_l - b_l * g.gpr;
-  } else {
-    const int b0 = divide_uniform(g0, g.gpr, g.r_gpr);
-    split_near(g0 - b0 * g.gpr + u_l, g.gpr, g.r_gpr, b_l, t16_l);
-    b_l += b0;
-  }
+  const int b_l = at.given ? at.b_l : gq_l / g.gpr, t16_l = at.given ? at.t16_l : gq_l - b_l * g.gpr;
   const int64_t yoff_l = (int64_t)b_l * p.ybs + 16 * t16_l;       // of this lane's unit
   constexpr int XCH = KCH < 8 ? KCH : 8;          // activation chunks resident in LDS
   unsigned char* const stage0 = xs + XCH * 8192 + wave * (LEAN ? 16 * 128 : 2 * ROWS * 128);
