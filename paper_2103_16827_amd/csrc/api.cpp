@@ -886,7 +886,7 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
       auto plain = [&](int32_t j) {
         const qasr_op& o = ops[j];
         return o.d.groups == 1 && o.d.k == 1 && o.d.stride == 1 && o.d.pad_left == 0 && o.d.pad_right == 0 && o.res_slot < 0 && !o.act &&
-               !e->ops[j].sep_proj;
+               !e->ops[j].sep_proj && !(j > 0 && e->ops[j - 1].sep);       // (those go out with a pair)
       };
       int32_t n = 0;
       while (i + n < n_ops && n < qasr::kMaxMulti && plain(i + n) && ops[i + n].d.Cout == ops[i].d.Cout &&

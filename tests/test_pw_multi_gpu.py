@@ -89,3 +89,26 @@ def test_dense_residual_stack():
     assert np.array_equal(g.forward(dev(x)).cpu().numpy(), oracle.encoder_forward(net, params, x))
     g.check_guards()
     g.enc.close()
+
+
+def test_second_half_of_a_pair_stays_with_it():
+    """a pointwise layer that runs with the depthwise layer before it does not begin a launch of several"""
+    b = _Builder("multi_pair", 95, 1, 64, 90)
+    b.op("in", 256, k=3)
+    src = (b.cur, b.C)
+    b.op("dw", 256, k=33, groups=256, relu=False, bias=False)
+    b.op("pw", 256)
+    r = b.op("proj", 256, relu=False, advance=False, src=src)
+    b.op("conv", 256, k=3, res=r)
+    b.op("out", 29, relu=False)
+    net = b.done()
+    params = W.draw_net_params(net, 8)
+    x = W.draw_input(net, 8)
+    g = GpuNet(net, params)
+    i = [o.name for o in net.ops].index("dw")
+    assert [g.enc.op_launch(j)[0] for j in (i, i + 1, i + 2)] == [i, i, i + 2]
+    ms = g.enc.forward_timed(dev(x), g.y, g.ws)
+    assert ms[i] > 0 and ms[i + 1] == 0 and ms[i + 2] > 0
+    assert np.array_equal(g.forward(dev(x)).cpu().numpy(), oracle.encoder_forward(net, params, x))
+    g.check_guards()
+    g.enc.close()
