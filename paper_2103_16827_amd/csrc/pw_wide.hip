@@ -55,7 +55,8 @@ __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
 template <int TW>
 __host__ __device__ constexpr int swizzle(int row) { return TW == 8 ? row & 7 : (row >> 2) & 3; }
 
-// RAGGED: rows of x, y or the residual that are not padded to whole 16-byte aligned units; v: (tile, split)
+// RAGGED: rows of x, y or the residual that are not padded to whole 16-byte aligned units, or x of items too large for the
+// other form's 32-bit offsets; v: (tile, split)
 template <int MT, int NT, int KS, bool RAGGED, bool MULTI>
 __device__ __forceinline__ void pw_wide_tile(const ConvParams& p, const PwwGeom& g, int v) {
   constexpr int TW = MT > 4 ? 8 : 4;                // units per LDS row
@@ -373,6 +374,12 @@ bool ragged_rows(const ConvParams& p) {
          (uintptr_t)p.y % 16 || (uintptr_t)p.res % 16;
 }
 
+// whether a tile's part of x lies within 32-bit offsets of its first batch item (7 groups: they reach into so many more items)
+bool near_x(const ConvParams& p) {
+  const int64_t gpr = (p.Tin + 15) / 16, more = (gpr + 5) / gpr;
+  return (more < p.B ? more : p.B - 1) * p.xbs + (int64_t)p.Cin * (p.Tin + p.xpad) <= 0x7ffffff0LL;
+}
+
 // The tile with the least time (us) on the busiest compute unit, for `layers` such layers at once that have at least
 // least_cin input channels: its matrix pipes (17.7 cycles per product), its LDS port and its 64 bytes per cycle from the L2, whichever is longest, plus the chain of
 // first loads and last stores and the epilogue's instructions.
@@ -380,8 +387,7 @@ bool pick(const ConvParams& p, int cus, int layers, int least_cin, Choice& best,
   if (p.depthwise || p.k != 1 || p.stride != 1 || p.pl != 0 || p.Tout != p.Tin || p.n_res_more) return false;
   if (!p.w_packed || (uintptr_t)p.w % 16 || p.Tin < 4 || p.Cin % 64) return false;
   const int64_t G = (int64_t)p.B * ((p.Tin + 15) / 16);
-  // 32-bit offsets within a tile's batch items (and from the first of them to the last row)
-  if (G > 0x3fffffff || 8 * p.ybs > 0x7ffffff0LL || 8 * p.xbs + (int64_t)p.Cin * (p.Tin + p.xpad) > 0x7ffffff0LL) return false;
+  if (G > 0x3fffffff || 8 * p.ybs > 0x7ffffff0LL) return false;   // (y: 32-bit offsets within a tile's batch items)
   static const Choice all[] = {{1, 2, 1}, {2, 2, 1}, {4, 2, 1}, {7, 2, 1}, {1, 2, 2}, {2, 2, 2}, {4, 2, 2}, {7, 2, 2},
                                {1, 2, 4}, {2, 2, 4}, {4, 2, 4}, {1, 1, 8}, {2, 1, 8}, {4, 1, 8}};
   const int kch = p.Cin / 64;
@@ -483,7 +489,7 @@ hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st) {
   Choice c;
   double t;
   if (!pick(p, compute_units(), 1, p.Cin, c, t)) return hipErrorInvalidValue;
-  const bool ragged = ragged_rows(p);
+  const bool ragged = ragged_rows(p) || !near_x(p);
 #define QASR_CASE(M, N, K) if (c.MT == M && c.NT == N && c.KS == K) return ragged ? launch_t<M, N, K, true>(p, st) : launch_t<M, N, K, false>(p, st);
   QASR_CASE(1, 2, 1) QASR_CASE(2, 2, 1) QASR_CASE(4, 2, 1) QASR_CASE(7, 2, 1)
   QASR_CASE(1, 2, 2) QASR_CASE(2, 2, 2) QASR_CASE(4, 2, 2) QASR_CASE(7, 2, 2)
@@ -515,7 +521,7 @@ bool pw_multi_better(const ConvParams* p, int n) {
   double t, one_by_one = 0.0;
   for (int i = 0; i < n; ++i) {
     const ConvParams& q = p[i];
-    if (q.res || q.act_lut || q.n_res_more || ragged_rows(q) || q.B != f.B || q.Cout != f.Cout || q.Tin != f.Tin ||
+    if (q.res || q.act_lut || q.n_res_more || ragged_rows(q) || !near_x(q) || q.B != f.B || q.Cout != f.Cout || q.Tin != f.Tin ||
         q.Tout != f.Tout || q.xpad != f.xpad || q.ypad != f.ypad || q.ybs != f.ybs || !pick(q, 256, 1, q.Cin, c, t))
       return false;
     one_by_one += t + 1.2;

@@ -25,6 +25,13 @@ def test_shapes_with_one_choice(Cin, Cout, wide, G):
     assert (launched(Cin, Cout, G) == "pw_wide") == wide
 
 
+@pytest.mark.parametrize("B,Cin,T,stride", [(4, 64, 1 << 22, 0), (1, 2048, 1 << 21, 0), (64, 64, 1 << 22, 0), (2, 64, 32, 1 << 33),
+                                            (40, 64, 16, 1 << 29), (2, 64, 33, 1 << 31)])
+def test_large_inputs_keep_the_kernel(B, Cin, T, stride):
+    """Items of 256 MiB and more, and views whose items lie far apart."""
+    assert Q.conv1d_launch_name(make_desc(B, Cin, 16, T, x_batch_stride=stride, flags=Q.FLAG_W_PACKED)) == "pw_wide"
+
+
 POINTWISE = [c for c in PIPE + REAL + STRIDED if c.get("k", 1) == 1 and c.get("packed")]
 
 

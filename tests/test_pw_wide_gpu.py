@@ -5,9 +5,10 @@ import pytest
 
 import paper_2103_16827_amd as Q
 import qasr_workloads as W
-from gpu_util import desc_of, dev, GpuNet
+from gpu_util import desc_of, dev, Guarded, GpuNet
 from qasr_workloads.nets import _Builder
 import numpy as np
+import torch
 import oracle
 from test_gpu_parity import layer_case, run_layer_case
 
@@ -50,6 +51,28 @@ def test_tiles(kw, tile, tuning_env):
 def test_edges_and_batch_strides(kw, extra, tuning_env):
     tuning_env("QASR_PW_WIDE", "1")
     run_wide(layer_case(**kw), extra)
+
+
+@pytest.mark.parametrize("B,T,stride", [(3, 48, 1 << 28), (3, 48, 1 << 30), (8, 16, 1 << 28), (9, 16, 1 << 29), (2, 112, (1 << 31) + 64), (2, 31, (1 << 31) + 1)])
+def test_items_far_apart(B, T, stride):
+    """A view whose batch items lie so far apart that a tile's offsets do or do not fit 32 bits."""
+    op, p, x, _, _ = layer_case("w_far", B, 192, 80, T, packed=True)
+    d = desc_of(op, B)
+    d.x_batch_stride = stride
+    wp = torch.empty(Q.packed_weight_bytes(d), dtype=torch.int8, device="cuda")
+    Q.pack_weights(d, dev(p["w"]), wp)
+    d.flags |= Q.FLAG_W_PACKED
+    assert Q.conv1d_launch_name(d) == "pw_wide"
+    n = op.Cin * T
+    far = torch.empty((B - 1) * stride + n, dtype=torch.int8, device="cuda")
+    for b in range(B):
+        far[b * stride:b * stride + n] = dev(x[b]).reshape(-1)
+    y = Guarded(B * op.Cout * T)
+    print(f"[case] {B} items {stride} bytes apart, T={T}", flush=True)
+    Q.conv1d_int8(d, far, wp, dev(p["bias"]), dev(p["m"]), dev(p["s"]), None, y.view)
+    torch.cuda.synchronize()
+    y.check()
+    assert np.array_equal(y.view.cpu().numpy().reshape(B, op.Cout, T), oracle.run_op(op, p, x))
 
 
 @pytest.mark.parametrize("T", [80, 61])
