@@ -107,7 +107,8 @@ bool plan(const ConvParams& d, const ConvParams& q, int cus, bool proj, Geometry
   if (d.Cout != 256 && d.Cout != 512) return false;
   if (q.depthwise || q.k != 1 || q.stride != 1 || q.pl != 0 || !q.w_packed || q.Cin != d.Cout || q.n_res_more || q.act_lut)
     return false;
-  if (q.Cout % 256 || q.Cout > 2048 || (uintptr_t)q.w % 16 || q.Cin != d.Cout) return false;
+  if (q.Cout % 256 || q.Cout > 2048 || (uintptr_t)q.w % 16) return false;
+  if (q.Tout != q.Tin) return false;                     // (padded on the right: it reads zeros there, not what the tile holds)
   if (d.Tout != q.Tin && (d.Tout + 15) / 16 * 16 != q.Tin) return false;            // (q may run over the pitch)
   // 32-bit offsets within 16 rows of x and a batch item of y
   if ((int64_t)16 * (d.Tin + d.xpad) > 0x7fffffffLL || (int64_t)q.Cout * (q.Tout + q.ypad) > 0x7fffff00LL) return false;
@@ -128,7 +129,7 @@ bool sep_projection_supported(const ConvParams& d, const ConvParams& q, const Co
   Geometry g;
   SepChoice c;
   if (!plan(d, q, 256, true, g, c) || c.ragged) return false;
-  return !r.depthwise && r.k == 1 && r.stride == 1 && r.pl == 0 && r.w_packed && !r.res && !r.n_res_more && !r.act_lut &&
+  return !r.depthwise && r.k == 1 && r.stride == 1 && r.pl == 0 && r.Tout == r.Tin && r.w_packed && !r.res && !r.n_res_more && !r.act_lut &&
          r.B == d.B && r.Cin == d.Cin && r.Cout == q.Cout && r.xbs == d.xbs && r.Tin + r.xpad == d.Tin + d.xpad && r.ybs == q.ybs &&
          r.Tout + r.ypad == q.Tout + q.ypad && (r.Tout + 15) / 16 == (q.Tout + 15) / 16 && (uintptr_t)r.w % 16 == 0 &&
          (uintptr_t)r.y % 16 == 0 && r.x == d.x;

@@ -76,3 +76,24 @@ def test_pair_is_the_whole_encoder(T):
     """Input and output are the caller's dense rows: loaded and stored at any byte address."""
     print(f"[case] separable module T={T}", flush=True)
     check(W.separable_module(3, 256, T, 33))
+
+
+@pytest.mark.parametrize("T", [47, 48])
+def test_padded_pointwise_layers_stay_apart(T):
+    """Pointwise layers padded on the right: frames past their input are zeros to them."""
+    b = _Builder("sep_padded", 96, 2, 64, T)
+    b.op("in", 256, k=3)
+    r = b.op("proj", 256, relu=False, pad=(0, 1), advance=False)
+    b.op("dw", 256, k=33, groups=256, relu=False, bias=False, pad=(16, 17))
+    b.op("pw", 256, res=r)
+    b.op("dw2", 256, k=33, groups=256, relu=False, bias=False)
+    b.op("pw2", 256, pad=(0, 1))
+    b.op("out", 29, relu=False)
+    net = b.done()
+    params, x = W.draw_net_params(net, 6), W.draw_input(net, 6)
+    g = GpuNet(net, params)
+    print(f"[case] padded pointwise layers, T={T}", flush=True)
+    assert [g.enc.op_launch(i)[0] for i in range(1, 6)] == [1, 2, 2, 4, 5]
+    assert np.array_equal(g.forward(dev(x)).cpu().numpy(), oracle.encoder_forward(net, params, x))
+    g.check_guards()
+    g.enc.close()
