@@ -54,6 +54,39 @@ def partial_write_hazards(asm_text: str):
     return bad
 
 
+def _registers(operands: str):
+    """Numbers of the vector registers named in an operand list."""
+    regs = set()
+    for m in re.finditer(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b", operands):
+        regs |= {int(m.group(3))} if m.group(3) else set(range(int(m.group(1)), int(m.group(2)) + 1))
+    return regs
+
+
+def ring_copies(asm_text: str):
+    """(kernel, instruction) for every copy, between a kernel's first and last matrix product, out of a register that a
+    hand-issued 16-byte load fills.  To the compiler such a register holds its value from the `asm` statement on, so it
+    may move it while the load is on its way (it has, where it indexed a ring at run time): the copy is then
+    what was there before, and the data lands in a register that belongs to something else."""
+    bad = []
+    for part in re.split(r"\n(?=_Z\w+:)", asm_text)[1:]:
+        ins, by_hand = [], False
+        for line in part.split(".Lfunc_end")[0].splitlines()[1:]:
+            line = line.strip()
+            if "#ASMSTART" in line or "#ASMEND" in line:
+                by_hand = "#ASMSTART" in line
+            elif line and line[0] not in ";." and not line.endswith(":"):
+                ins.append((line.split(";")[0].strip(), by_hand))
+        ring = set()
+        for text, by_hand in ins:
+            if by_hand and re.match(r"(global|buffer)_load_dwordx4 ", text):
+                ring |= _registers(text.split(",")[0])
+        products = [i for i, (text, _) in enumerate(ins) if text.startswith("v_mfma")]
+        for text, _ in ins[products[0]:products[-1]] if products else []:
+            if re.match(r"v_(mov|accvgpr|swap|pk_mov)", text) and _registers(text.partition(",")[2]) & ring:
+                bad.append((part.split(":")[0], text))
+    return bad
+
+
 def source_with_local_includes(src: str, seen=None) -> str:
     """Text of a source file followed by that of every header of this directory it includes."""
     seen = set() if seen is None else seen
@@ -73,15 +106,17 @@ def build(verbose: bool = False) -> str:
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
     procs = []
-    sdwa_sources = []
+    asm_sources = []
     for src in sources():
         obj = os.path.join(bdir, os.path.basename(src) + ".o")
         cmd = [hipcc, "-x", "hip", "-c", src, "-o", obj] + [f for f in HIPCC_FLAGS if f != "-shared"]
-        if "_sdwa" in source_with_local_includes(src):   # hand-written partial register writes: device assembly too
+        with open(src) as f:
+            rings = "gload16(" in f.read()
+        if rings or "_sdwa" in source_with_local_includes(src):   # rings of hand-issued loads, hand-written partial register writes: device assembly too
             asm = os.path.join(bdir, os.path.basename(src) + ".gfx950.s")
             acmd = [hipcc, "-x", "hip", "--cuda-device-only", "-S", src, "-o", asm] + \
                    [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC", "-Rpass-analysis=kernel-resource-usage")]
-            sdwa_sources.append((src, asm, subprocess.Popen(acmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+            asm_sources.append((src, asm, subprocess.Popen(acmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
@@ -121,16 +156,19 @@ def build(verbose: bool = False) -> str:
             f.write(" ".join(r) + "\n")
     # The pipelined kernels count their own vector-memory requests; a spill adds requests nobody
     # counted and moves registers that loads in flight still own.  Such a build must never run.
-    for src, asm, pr in sdwa_sources:
+    for src, asm, pr in asm_sources:
         out, _ = pr.communicate()
         if pr.returncode != 0:
             raise RuntimeError(f"no device assembly for {src}:\n{out}")
         with open(asm) as f:
-            bad = partial_write_hazards(f.read())
-        if bad:
-            if os.path.exists(LIB):
-                os.remove(LIB)
-            raise RuntimeError(f"{asm}: register read right after a partial write: {bad[0][0]} | {bad[0][1]}")
+            text = f.read()
+        for what, bad in (("register read right after a partial write", partial_write_hazards(text)),
+                          ("copy of a register whose load may be on its way", ring_copies(text))):
+            if bad:
+                if os.path.exists(LIB):
+                    os.remove(LIB)
+                raise RuntimeError(f"{asm}: {what}: {bad[0][0]} | {bad[0][1]}")
+        os.remove(asm)
     if not recs:       # no figures parsed (the remark's format changed?): nothing was checked
         if os.path.exists(LIB):
             os.remove(LIB)

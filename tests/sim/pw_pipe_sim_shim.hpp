@@ -1,5 +1,6 @@
-// Host stand-ins for what one tile of the pipelined pointwise kernel (csrc/pw_pipe_body.hpp) asks of
-// the GPU, so that the tile function can be compiled for the CPU and run lane by lane: every
+// Host stand-ins for what one tile of the pipelined pointwise kernel (csrc/pw_pipe_body.hpp), and the other
+// kernels that count their requests (dw_pipe, conv_pipe, conv_few), ask of
+// the GPU, so that they can be compiled for the CPU and run lane by lane: every
 // vector-memory request, wait, barrier and use of loaded data is recorded instead of executed, and
 // every global address is checked against the operand arrays.  Test infrastructure: nothing of
 // the product includes this file.  Values are not simulated (a matrix product returns its
@@ -31,7 +32,7 @@ using std::min;
 
 namespace sim {
 
-enum Kind { ISSUE_LDS, ISSUE_REG, STORE, WAIT, USE_REG, USE_LDS, BARRIER, UNIFORM };
+enum Kind { ISSUE_LDS, ISSUE_REG, STORE, WAIT, USE_REG, USE_LDS, BARRIER, UNIFORM, LDS_WRITE };
 struct Ev { Kind k; int64_t a, b; };
 struct Region { const char* name; const unsigned char* p; size_t n; bool writable; };
 
@@ -72,6 +73,12 @@ inline const Region& region_of(const void* p, size_t n, bool write) {
     }
   fail("global access outside every operand array");
 }
+// a store of n bytes: inside a writable operand, counted if that is the output
+inline void count_store(const void* p, size_t n) {
+  const Region& r = region_of(p, n, true);
+  if (r.p != S().y_base || !S().count_stores) return;
+  for (size_t i = 0; i < n; ++i) ++(*S().written)[(size_t)((const unsigned char*)p - r.p) + i];
+}
 inline size_t lds_off(const void* p, size_t n) {
   const unsigned char* q = (const unsigned char*)p;
   if (q < S().lds || q + n > S().lds + S().lds_bytes) fail("LDS address outside the workgroup's allocation");
@@ -83,8 +90,8 @@ struct Wave { std::vector<std::vector<Ev>> lanes; };
 
 // (the lanes of a wave read different bytes of the same LDS rows: a use is compared by kind only)
 // what only some lanes of a wave may take part in: a load under a lane predicate, and the use of its register
-inline bool maskable(Kind k) { return k == ISSUE_LDS || k == ISSUE_REG || k == USE_REG; }
-inline bool same(const Ev& a, const Ev& b) { return a.k == b.k && (a.k == USE_LDS || (a.a == b.a && a.b == b.b)); }
+inline bool maskable(Kind k) { return k == ISSUE_LDS || k == ISSUE_REG || k == USE_REG || k == LDS_WRITE; }
+inline bool same(const Ev& a, const Ev& b) { return a.k == b.k && (a.k == USE_LDS || a.k == LDS_WRITE || (a.a == b.a && a.b == b.b)); }
 
 // merge the 64 lane streams: events are equal across lanes except that a lane may skip a
 // load (masked out) that others issue
@@ -239,6 +246,13 @@ inline int32_t reg_load(const void* p, int bytes) {
   return (int32_t)(kUidTag | (uint32_t)uid);
 }
 inline int32_t gload4(const void* p) { return reg_load(p, 4); }
+inline int32_t gload4(const void* base, uint32_t off) { return reg_load((const unsigned char*)base + off, 4); }
+inline v4i gload16(const void* base, uint32_t off) {
+  sim::region_of((const unsigned char*)base + off, 16, false);
+  const int uid = sim::S().next_uid++;
+  sim::rec(sim::ISSUE_REG, uid);
+  return (v4i){(int)(kUidTag | (uint32_t)uid), 0, 0, 0};
+}
 inline int32_t gload_i8(const void* p) { return reg_load(p, 1); }
 inline void tie(int32_t& v) {
   if (((uint32_t)v & 0xff000000u) == kUidTag) {
@@ -259,21 +273,13 @@ template <typename V>
 inline void sim_buffer_store16(V, SimRsrc r, uint32_t off, int, int) {
   sim::rec(sim::STORE);
   if ((uint64_t)off + 16 > r.num) return;                  // rejected by the bounds check, as on the chip
-  sim::region_of(r.p + off, 16, true);
-  auto& st = sim::S();
-  const size_t o = (size_t)(r.p + off - st.y_base);
-  if (st.count_stores)
-    for (int i = 0; i < 16; ++i) ++(*st.written)[o + i];
+  sim::count_store(r.p + off, 16);
 }
 #define __builtin_amdgcn_raw_buffer_store_b128(v, r, off, soff, aux) sim_buffer_store16(v, r, off, soff, aux)
 inline void sim_buffer_store4(uint32_t, SimRsrc r, uint32_t off, int, int) {
   sim::rec(sim::STORE);
   if ((uint64_t)off + 4 > r.num) return;
-  sim::region_of(r.p + off, 4, true);
-  auto& st = sim::S();
-  const size_t o = (size_t)(r.p + off - st.y_base);
-  if (st.count_stores)
-    for (int i = 0; i < 4; ++i) ++(*st.written)[o + i];
+  sim::count_store(r.p + off, 4);
 }
 #define __builtin_amdgcn_raw_buffer_store_b32(v, r, off, soff, aux) sim_buffer_store4(v, r, off, soff, aux)
 inline uint64_t __ballot(bool pred) {
@@ -287,12 +293,25 @@ inline uint64_t __ballot(bool pred) {
   if (i >= st.ballots.size()) sim::fail("a ballot the first round did not see");
   return st.ballots[i];
 }
-// a plain 16-byte LDS read of loaded rows (the generator of the depthwise replay routes the one such
-// read of that kernel here)
+// a plain 16-byte LDS read or write (the generators route a kernel's own here)
 inline v4i sim_lds_read16(const void* p) {
   sim::rec(sim::USE_LDS, (int64_t)sim::lds_off(p, 16));
   return (v4i){0, 0, 0, 0};
 }
+inline void sim_lds_write16(void* p, v4i) { sim::rec(sim::LDS_WRITE, (int64_t)sim::lds_off(p, 16)); }
+// blocks of 16 bytes in LDS, read and written by index
+struct SimLdsBlock {
+  unsigned char* p;
+  operator v4i() const { return sim_lds_read16(p); }
+  void operator=(v4i v) const { sim_lds_write16(p, v); }
+};
+struct SimLdsBlocks {
+  unsigned char* p;
+  explicit SimLdsBlocks(void* q) : p((unsigned char*)q) {}
+  SimLdsBlock operator[](int i) const { return SimLdsBlock{p + 16 * (int64_t)i}; }
+  SimLdsBlock operator*() const { return SimLdsBlock{p}; }
+  SimLdsBlocks operator+(int i) const { return SimLdsBlocks(p + 16 * (int64_t)i); }
+};
 inline int sim_uniform(int x) { sim::rec(sim::UNIFORM, x); return x; }
 inline unsigned sim_uniform(unsigned x) { sim::rec(sim::UNIFORM, (int64_t)x); return x; }
 #define __builtin_amdgcn_readfirstlane(x) sim_uniform(x)

@@ -377,3 +377,18 @@ def test_slot_buffer_plan_rejects_bad_wiring():
         Q.plan_slot_buffers([0], [-1], [1], 2, 17)
     with pytest.raises(Q.QasrError):
         Q.plan_slot_buffers([0, 1], [-1, -1], [1, 1], 2, 1)       # writes the slot it reads
+
+
+def test_build_refuses_copies_out_of_a_ring_of_loads():
+    """A register that a hand-issued load fills is not moved between the first and the last matrix product."""
+    from paper_2103_16827_amd.build import ring_copies
+
+    def kernel(*loop):
+        return "\t.text\n_Z1kv:\n" + "\n".join((
+            ";;#ASMSTART", "\tglobal_load_dwordx4 v[8:11], v1, s[2:3]", ";;#ASMEND", "\tv_mov_b32_e32 v20, v9",
+            "\tv_mfma_i32_16x16x64_i8 v[0:3], v[4:7], v[8:11], v[0:3]") + loop + (
+            "\tv_mfma_i32_16x16x64_i8 v[0:3], v[4:7], v[8:11], v[0:3]", "\tv_mov_b32_e32 v9, v20", ".Lfunc_end0:")) + "\n"
+    assert ring_copies(kernel()) == []
+    assert ring_copies(kernel("\tv_mov_b32_e32 v9, v20", "\tv_mov_b32_e32 v20, v12")) == []
+    for copy in ("v_mov_b32_e32 v20, v11", "v_mov_b64_e32 v[20:21], v[10:11]", "v_accvgpr_write_b32 a0, v8"):
+        assert ring_copies(kernel("\t" + copy)) == [("_Z1kv", copy)]

@@ -113,7 +113,7 @@ def function_returns(body):
 def test_the_splitter_sees_the_kernels():
     src = sources()
     names = {n for t in src.values() for n, _ in functions(t)}
-    for want in ("pw_pipe_kernel", "pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel", "team_kernel", "conv_pipe_kernel"):
+    for want in ("pw_pipe_kernel", "pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel", "team_kernel", "conv_pipe_kernel", "conv_few_kernel"):
         assert want in names, (want, sorted(names))
 
 
@@ -134,7 +134,7 @@ def test_every_function_with_hand_counted_loads_drains_them_before_it_ends():
                     f"{fname}:{name}: a return after a request without wait_vm<0>() in between"
             checked.append(f"{fname}:{name}")
     # the kernels known to use the wrappers are all among the checked ones
-    for want in ("pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel"):
+    for want in ("pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel", "conv_pipe_kernel", "conv_few_kernel"):
         assert any(c.endswith(":" + want) for c in checked), checked
 
 

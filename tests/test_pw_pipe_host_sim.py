@@ -149,3 +149,88 @@ def test_short_form_rescale_is_the_64_bit_one(tmp_path):
     assert c.returncode == 0, c.stderr[-3000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "values right" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
+
+
+# ---- the dense kernels, replayed the same way
+
+def generate_conv(tmp, name, mutate=None):
+    """conv_pipe.hip or conv_few.hip without its includes: kernel, planner and launcher; the kernel's 16-byte LDS
+    accesses go through the recording stand-ins, the statements that only ask for arguments are left out."""
+    body = open(os.path.join(CSRC, name + ".hip")).read()
+    if mutate:
+        body = mutate(body)
+    body = re.sub(r"#include [^\n]*\n", "", body)
+    edits = [("const v4i*>(arow + 16 * mt * p.stride * kXS)", None), ("const v4i*>(xs + abase + (uint32_t)(row * kXS))", None)]
+    n = 0
+    for e, _ in edits:                               # the operand reads
+        n += body.count("*reinterpret_cast<" + e)
+        body = body.replace("*reinterpret_cast<" + e, "sim_lds_read16(" + e[len("const v4i*>("):])
+    assert n == 1, (name, n)
+    body, n = re.subn(r"\*reinterpret_cast<v4i\*>\((dst \+ \(\(e \+ rot\) & 3\) \* kXS)\) =\s*(\(v4i\)\{[^}]*\});", r"sim_lds_write16(\1, \2);", body)
+    assert n == 1, (name, n)                         # the transposed rows
+    body, n = re.subn(r"v4i\* const red = reinterpret_cast<v4i\*>\(", "SimLdsBlocks const red(", body)
+    assert n == 1, (name, n)                         # the sums
+    body = body.replace("+= *slot(", "+= (v4i)*slot(").replace("a += red[", "a += (v4i)red[")
+    body = body.replace("*reinterpret_cast<volatile unsigned*>(xs) + 1", "sim_arrival() + 1")
+    body = re.sub(r'asm volatile\(""\s*::"s"[^;]*;', ";", body)
+    body = body.replace('asm volatile("s_waitcnt vmcnt(0)" ::: "memory");', "wait_vm<0>();")
+    assert "asm" not in re.sub(r"//[^\n]*", "", body), name
+    body, n = re.subn(r"extern __shared__ [^;]*;", "unsigned char* const xs = sim::S().lds;", body)
+    assert n == 1, (name, n)
+    open(os.path.join(tmp, name + "_stripped.hpp"), "w").write(body)
+    m = re.search(r"__device__ __forceinline__ int divide_uniform.*?\n\}\n", open(os.path.join(CSRC, "common.hpp")).read(), flags=re.S)
+    assert m, "divide_uniform not found in common.hpp"
+    open(os.path.join(tmp, "divide_extract.hpp"), "w").write("namespace qasr {\n" + m.group(0) + "}\n")
+    generate(tmp)          # (ConvParams)
+
+
+def build_and_run_conv(tmp, name, small=False):
+    exe = os.path.join(tmp, name + "_sim")
+    # (registers that no load was asked to fill are tied with the others: they hold zeros, not an earlier lane's tags)
+    cmd = [CLANG, "-std=c++17", "-O0", "-g0", "-ftrivial-auto-var-init=zero", "-Wno-unknown-attributes", "-Wno-ignored-attributes", "-I", tmp, "-I", SIM,
+           os.path.join(SIM, "conv_sim_main.cpp"), "-o", exe]
+    cmd += ["-DSIM_FEW"] if name == "conv_few" else []
+    cmd += ["-DSIM_SMALL"] if small else ["-fsanitize=address,undefined", "-fno-sanitize=shift,signed-integer-overflow", "-fno-sanitize-recover=all"]
+    c = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
+    assert c.returncode == 0, c.stderr[-6000:]
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:verify_asan_link_order=0", UBSAN_OPTIONS="halt_on_error=1")
+    return subprocess.run([exe], capture_output=True, text=True, timeout=900, env=env)
+
+
+@pytest.mark.skipif(not os.path.exists(CLANG), reason="no host clang beside the HIP toolchain")
+@pytest.mark.parametrize("name,cases", [("conv_few", 7), ("conv_pipe", 15)])
+def test_request_bookkeeping_of_the_dense_kernels_replays_cleanly(tmp_path, name, cases):
+    generate_conv(str(tmp_path), name)
+    r = build_and_run_conv(str(tmp_path), name)
+    assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-3000:])
+    assert "all cases passed" in r.stdout and r.stdout.count("ok ") >= cases, r.stdout
+
+
+CONV_MISTAKES = {
+    # a wait that allows one request too many: for the next step's weights, for the rows of the tile
+    "few_weights": ("conv_few", "wait_vm<(W - 2) * NT>();", "wait_vm<(W - 2) * NT + 1>();"),
+    "few_rows": ("conv_few", "wait_vm_dyn(min(steps, W - 1) * NT);", "wait_vm_dyn(min(steps, W - 1) * NT + 1);"),
+    # the sums go where other waves may still read the tile
+    "few_barrier": ("conv_few", "  __syncthreads();                                  // the tile has been read by all\n", ""),
+    "pipe_weights": ("conv_pipe", "wait_vm<(kW - 2) * NT>();", "wait_vm<(kW - 2) * NT + 1>();"),
+    "pipe_weights_and_rows": ("conv_pipe", "wait_vm<(kW - 2) * NT + 16>();", "wait_vm<(kW - 2) * NT + 17>();"),
+    "pipe_rows": ("conv_pipe", "else wait_vm<2 * NT>();", "else wait_vm<2 * NT + 1>();"),
+    "pipe_constants": ("conv_pipe", "  wait_vm<(kW - 1) * NT>();\n  v4i acc", "  if (kg) wait_vm<(kW - 1) * NT>();\n  v4i acc"),
+    "pipe_drain": ("conv_pipe", "  wait_vm<0>();                                     // what the weight stream asked for past its end\n", ""),
+    # two buffers for three chunks
+    "pipe_buffers": ("conv_pipe", "const int nbuf = buf == 2 ? 0 : buf + 1;", "const int nbuf = buf == 1 ? 0 : buf + 1;"),
+    "pipe_sums": ("conv_pipe", "    v4i* const red = reinterpret_cast<v4i*>(xs + 3 * bufbytes + kConstBytes);", "    v4i* const red = reinterpret_cast<v4i*>(xs);"),
+}
+
+
+@pytest.mark.skipif(not os.path.exists(CLANG), reason="no host clang beside the HIP toolchain")
+@pytest.mark.parametrize("what", sorted(CONV_MISTAKES))
+def test_the_dense_replays_catch_planted_mistakes(tmp_path, what):
+    name, a, b = CONV_MISTAKES[what]
+
+    def mutate(body):
+        assert body.count(a) == 1, what
+        return body.replace(a, b)
+    generate_conv(str(tmp_path), name, mutate)
+    r = build_and_run_conv(str(tmp_path), name, small=True)
+    assert r.returncode != 0 and "SIM FAILURE" in r.stderr, (r.stdout[-2000:], r.stderr[-2000:])
