@@ -23,7 +23,7 @@ struct ConvParams {
   int32_t relu;
   int32_t w_packed;      // groups == 1, Cin % 64 == 0: weights are in MFMA operand order (below)
   // dense-residual layers: further residual operands (same shape and stride as `res`), all added
-  // to the rescaled value before the one clamp; only conv_pipe and conv_generic read them
+  // to the rescaled value before the one clamp; only conv_pipe, conv_few and conv_generic read them
   int32_t n_res_more;
   const int8_t* res_more[11];
   // unary activation fused into the epilogue: 256 bytes, entry (code + 128) = the activation's int8
@@ -45,12 +45,16 @@ struct ConvParams {
 };
 constexpr int kMaxMoreRes = 11;
 
-// v / d for wave-uniform operands, rd = 1.0f / d: below 2^24 the estimate is off by one at most
-__device__ __forceinline__ int divide_uniform(int v, int d, float rd) {
-  if (v >= 1 << 24) return v / d;
+// v / d for wave-uniform operands, 0 <= v < 2^24 (a launch's limit on its workgroups, say), rd = 1.0f / d: the estimate is
+// off by one at most
+__device__ __forceinline__ int divide_uniform24(int v, int d, float rd) {
   const int q = __builtin_amdgcn_readfirstlane((int)((float)v * rd));
   const int r = v - q * d;
   return r < 0 ? q - 1 : r >= d ? q + 1 : q;
+}
+// the same for any v >= 0
+__device__ __forceinline__ int divide_uniform(int v, int d, float rd) {
+  return v >= 1 << 24 ? v / d : divide_uniform24(v, d, rd);
 }
 
 // q = d w + r for 0 <= q < d + 8, rd = 1.0f / d, per lane (the quotient is at most 8: the estimate is off by one at most)

@@ -33,7 +33,7 @@ constexpr int kXS = 80;       // LDS row pitch in bytes: 64 channels + 16 pad
 constexpr int kLds = 160 * 1024;
 
 struct FewGeom {
-  int n_tt, n_co;     // frame tiles per batch item, channel tiles
+  int n_tt;           // frame tiles per batch item
   int rows;           // LDS rows per chunk (input frames incl. halo, rounded to 4)
   int kchunks;        // Cin / 64
   int co16n;          // ceil(Cout / 16)
@@ -42,12 +42,6 @@ struct FewGeom {
   int jstep;          // KG / kchunks
   float r_nbt, r_tt, r_rows;   // reciprocals of B * n_tt, n_tt, rows
 };
-
-__device__ __forceinline__ int divide(int v, int d, float rd) {   // (0 <= v < 2^24: the estimate is off by one at most)
-  const int q = __builtin_amdgcn_readfirstlane((int)((float)v * rd));
-  const int r = v - q * d;
-  return r < 0 ? q - 1 : r >= d ? q + 1 : q;
-}
 
 template <int MT> struct Ring { static constexpr int W = MT == 4 ? 6 : 8; };   // steps of weights (registers)
 
@@ -66,9 +60,9 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
   // channel tile first, then batch item, then frame tile; XCD x takes a contiguous run of that order (conv_pipe.hip)
   const int v = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= g.per_xcd || v >= g.tiles) return;               // whole workgroup
-  const int nbt = p.B * g.n_tt;
-  const int co_tile = divide(v, nbt, g.r_nbt), bt = v - co_tile * nbt;
-  const int b = divide(bt, g.n_tt, g.r_tt), t0 = (bt - b * g.n_tt) * (16 * MT);
+  const int nbt = p.B * g.n_tt;                     // (workgroups: < 2^22)
+  const int co_tile = divide_uniform24(v, nbt, g.r_nbt), bt = v - co_tile * nbt;
+  const int b = divide_uniform24(bt, g.n_tt, g.r_tt), t0 = (bt - b * g.n_tt) * (16 * MT);
   const int f0 = t0 * p.stride - p.pl;              // first input frame the tile reads
   const int fa = f0 & ~3, foff = f0 - fa;           // rounded down to a dword (also if negative)
   const int xpitch = p.Tin + p.xpad;
@@ -318,11 +312,10 @@ hipError_t launch_t(const ConvParams& p, hipStream_t st) {
   const Choice c{MT, WC};
   FewGeom g;
   g.n_tt = (p.Tout + 16 * MT - 1) / (16 * MT);
-  g.n_co = (p.Cout + 32 * WC - 1) / (32 * WC);
   g.rows = lds_rows(p, 16 * MT);
   g.kchunks = p.Cin / 64;
   g.co16n = (p.Cout + 15) / 16;
-  g.tiles = p.B * g.n_tt * g.n_co;
+  g.tiles = p.B * g.n_tt * ((p.Cout + 32 * WC - 1) / (32 * WC));
   g.per_xcd = (g.tiles + 7) / 8;
   g.units = g.kchunks * g.rows;
   g.jstep = 16 / WC / g.kchunks;

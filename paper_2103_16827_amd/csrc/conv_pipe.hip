@@ -6,8 +6,8 @@
 //
 // Roles and layouts are those of gemm_mfma.hip: the A operand is the activation tile transposed
 // (rows = output frames, K = input channels), the B operand the weight tile (packed form: 1 KiB
-// contiguous per wave-wide load); a workgroup of 4 waves owns 16 MT output frames of one batch
-// item and 256 output channels (64 per wave); each 64-channel chunk of the tile (with the time
+// contiguous per wave-wide load); a workgroup owns 16 MT output frames of one batch item and 64 NT
+// output channels, 16 NT for each of the 4 waves of a group (up to four groups share the taps); each 64-channel chunk of the tile (with the time
 // halo the taps need) is transposed in registers (4x4 byte blocks, v_perm_b32) into LDS rows
 // [frame][64 channels], 80-byte pitch, so that a tap is a row offset.
 //
@@ -73,7 +73,8 @@ __global__ __launch_bounds__(256 * KG) void conv_pipe_kernel(ConvParams p, CpGeo
   constexpr int TM = 16 * MT, TN = 64 * NT;
   // All arguments of the loop in one go, and no integer division in front of the first load: with 16 waves the
   // seven divisions and a dozen dependent scalar loads took 6900 cycles of the 25800 of a 256-channel layer of 800 frames.
-  // (Those of the epilogue only where they need no spill: not in the tall tiles of two groups.)
+  // (Those of the epilogue only where they need no spill: not in the tall tiles of two groups.  n_co is asked for and not
+  // used: without it the registers fall otherwise and 16 x 1600 frames of a Jasper take 3671 us for 3652.)
   asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.xbs), "s"(p.B), "s"(p.Tin), "s"(p.k), "s"(p.stride), "s"(p.dil), "s"(p.pl), "s"(p.xpad));
   if constexpr (KG == 1 || MT < 8) asm volatile("" ::"s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.Cout));
   asm volatile("" ::"s"(g.n_tt), "s"(g.n_co), "s"(g.rows), "s"(g.kchunks), "s"(g.co16n), "s"(g.splits), "s"(g.tiles), "s"(g.per_xcd),

@@ -70,13 +70,6 @@ __host__ __device__ inline int small_row_bytes(int C, int units, int MT, int NA)
   return ((rows > 2048 ? rows : 2048) + 15) & ~15;
 }
 
-// v / d for 0 <= v < 2^24 and wave-uniform operands, rd = 1.0f / d: the estimate is off by one at most
-__device__ __forceinline__ int divide(int v, int d, float rd) {
-  const int q = __builtin_amdgcn_readfirstlane((int)((float)v * rd));
-  const int r = v - q * d;
-  return r < 0 ? q - 1 : r >= d ? q + 1 : q;
-}
-
 // The workgroup's tile and output channels, without a division (two 64-bit ones were 290 instructions in front
 // of the first load).  All arguments are read first, in one go: asked for where they are used, they were a
 // dozen dependent scalar loads.
@@ -109,9 +102,9 @@ __device__ __forceinline__ bool place(const SepParams& p, Place& at) {
   at.res = at.proj ? nullptr : p.res;
   at.y = at.proj ? p.y2 : p.y;
   at.relu = at.proj ? p.relu2 : p.relu;
-  const int tile = p.splits == 1 ? v : divide(v, p.splits, p.r_splits);
+  const int tile = p.splits == 1 ? v : divide_uniform24(v, p.splits, p.r_splits);   // (workgroups: < 2^22)
   at.cs = v - tile * p.splits;
-  at.b = divide(tile, p.tpr, p.r_tpr);
+  at.b = divide_uniform24(tile, p.tpr, p.r_tpr);
   const int ti = tile - at.b * p.tpr;
   at.g0 = ti * p.g_base + min(ti, p.g_more);
   at.gn = p.g_base + (ti < p.g_more ? 1 : 0);       // <= MT

@@ -178,7 +178,7 @@ def generate_conv(tmp, name, mutate=None):
     body, n = re.subn(r"extern __shared__ [^;]*;", "unsigned char* const xs = sim::S().lds;", body)
     assert n == 1, (name, n)
     open(os.path.join(tmp, name + "_stripped.hpp"), "w").write(body)
-    m = re.search(r"__device__ __forceinline__ int divide_uniform.*?\n\}\n", open(os.path.join(CSRC, "common.hpp")).read(), flags=re.S)
+    m = re.search(r"__device__ __forceinline__ int divide_uniform24.*?\n\}\n.*?int divide_uniform\(.*?\n\}\n", open(os.path.join(CSRC, "common.hpp")).read(), flags=re.S)
     assert m, "divide_uniform not found in common.hpp"
     open(os.path.join(tmp, "divide_extract.hpp"), "w").write("namespace qasr {\n" + m.group(0) + "}\n")
     generate(tmp)          # (ConvParams)
