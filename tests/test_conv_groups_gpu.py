@@ -1,6 +1,6 @@
 """Dense layers whose taps are split over groups of waves (csrc/conv_pipe.hip, KG > 1): uneven tap splits,
-as many groups as taps, one chunk and several, ragged frames and channels, strides, several residual
-operands, the choice the library makes by itself for small launches.  In an encoder the chunks are split
+as many groups as taps, one chunk and several, ragged frames and channels, strides; several residual
+operands, as many at once as fit and more, and in the kernel the library chooses for small launches.  In an encoder the chunks are split
 over workgroups as well (S > 1): as many as chunks, uneven ranges, with and without groups, replays."""
 import functools
 
@@ -9,8 +9,9 @@ import pytest
 import torch
 
 import oracle
+import paper_2103_16827_amd as Q
 import qasr_workloads as W
-from gpu_util import GpuNet, dev, gpu_layer
+from gpu_util import GpuNet, desc_of, dev, gpu_layer
 from test_gpu_parity import draw, layer_case, run_layer_case
 
 pytestmark = pytest.mark.gpu
@@ -31,11 +32,17 @@ def test_forced_groups(kw, tile, tuning_env):
     assert run_layer_case(layer_case(**kw)) == "conv_pipe"
 
 
-@pytest.mark.parametrize("n_res", [0, 1, 5])
-def test_small_launch_with_residuals(n_res):
+@pytest.mark.parametrize("tile,kernel", [("", "conv_few"), ("4,2,4", "conv_pipe"), ("4,2,1", "conv_pipe"), ("10,2,2", "conv_pipe"),
+                                         ("5,4,1", "conv_pipe")])
+@pytest.mark.parametrize("n_res", [0, 1, 5, 12])
+def test_small_launch_with_residuals(n_res, tile, kernel, tuning_env):
+    """(conv_pipe asks for the rows of 6, 3, 3 and 2 operands at once in these tiles.)"""
+    if tile:
+        tuning_env("QASR_CP_TILE", tile)
     op, p, x, _, packed = layer_case("small", 2, 640, 640, 203, k=21, packed=True)
+    assert Q.conv1d_launch_name(desc_of(op, 2, Q.FLAG_W_PACKED)) == kernel
     rs = [draw(77 + r, (2, op.Cout, op.Tout), -128, 127, np.int8) for r in range(n_res)]
-    print(f"[case] dense 640 -> 640 k=21 with {n_res} residuals", flush=True)
+    print(f"[case] dense 640 -> 640 k=21 with {n_res} residuals, tile {tile} of {kernel}", flush=True)
     ref = oracle.run_op(op, p, x, rs if n_res > 1 else (rs[0] if rs else None))
     got = gpu_layer(op, 2, p, x, rs if n_res > 1 else (rs[0] if rs else None), packed=packed)
     assert np.array_equal(got, ref)

@@ -796,7 +796,7 @@ def test_w6a8_six_bit_weight_codes_in_int8_storage(cfg):
 
 
 @pytest.mark.parametrize("n_res,shape", [
-    (2, dict(B=2, Cin=128, Cout=328, T=428, k=11, packed=True)),       # pipelined dense kernel, ragged tiles
+    (2, dict(B=2, Cin=128, Cout=328, T=428, k=11, packed=True)),       # dense, ragged tiles
     (12, dict(B=1, Cin=64, Cout=64, T=96, k=3, packed=True)),          # the maximum number of operands
     (3, dict(B=2, Cin=20, Cout=7, T=53, k=5, packed=False)),           # general kernel
     (4, dict(B=2, Cin=16, Cout=16, T=64, k=9, dw=True, packed=False)), # depthwise: general kernel too
@@ -838,7 +838,7 @@ def test_jasper_dense_residual_batch2():
     y = check_encoder(net, 1)
     g = GpuNet(net, W.draw_net_params(net, 1))
     ks = g.kernels()
-    assert all(ks[i] == "conv_pipe" for i, o in enumerate(net.ops) if o.more_res)
+    assert all(ks[i] == "conv_pipe" for i, o in enumerate(net.ops) if o.more_res)   # (the family)
     g.enc.close()
 
 
