@@ -288,9 +288,10 @@ qasr_status qasr_plan_slot_buffers(const int32_t* in_slot, const int32_t* res_sl
 /* Bytes of workspace qasr_encoder_forward needs: all buffers of the plan above except the input and the
  * output, each rounded up to 256 bytes, their rows to 16 frames where some length is not a multiple of
  * 16; and, where dense layers with taps have too few tiles to fill the chip, room for the partial
- * sums of their split contractions (int32; the largest layer's, plus 4 KiB of counters).  For the
- * Jasper-10x5 shape that is 20 MiB at 4 x 800 and nothing from 8 x 800 on or at 1 x 1600 and below, where
- * conv_few runs these layers and splits a contraction inside a workgroup.  Known at create time because every shape and scale of the
+ * sums of their split contractions (int32; the largest layer's, plus 4 KiB of counters).  How much that is
+ * follows the tile chosen for each layer and neither grows nor shrinks with the frames: for the Jasper-10x5
+ * shape nothing at 1 x 800, 7 MiB at 1 x 1200, nothing at 1 x 1600, 16 MiB at 1 x 3000, 20 at 4 x 800, 18 at 8 x 600, nothing
+ * at 8 x 800 and 16 x 1600.  Known at create time because every shape and scale of the
  * integer model is static (Sec. 2.1: static quantisation, nothing is sized at inference).  HOST only. */
 size_t qasr_encoder_workspace_bytes(const qasr_encoder* e);
 
