@@ -12,9 +12,9 @@
 //   - the waves are WC column waves x 16 / WC groups that take the (chunk, tap) steps in turn; a wave has W - 1
 //     steps of 2 KiB on their way, up to 224 KB per unit;
 //   - the groups' sums meet in LDS, a block of 16 x 16 per wave, no workspace.
-// us a layer, conv_pipe / here: 2 x 406 frames, 256 channels, 11 taps 11.3 / 6.0, 512, 17 taps 15.2 / 10.6, 640, 21 taps
-// 23.4 / 18.4; 1 x 104 frames 10.4 / 5.5, 12.8 / 8.9, 14.6 / 11.1; Jasper-10x5 at 1 x 208 input frames 763 -> 551, with
-// dense residuals at 2 x 811 1308 -> 1073.  What is left: the transposition (16 dword loads per 64 bytes x 4 frames, 10.7
+// us a layer in chains of six, conv_pipe / here: 2 x 406 frames, 256 channels, 11 taps 11.6 / 7.2, 512, 17 taps 16.6 / 10.8,
+// 640, 21 taps 20.5 / 17.0; 1 x 104 frames 10.9 / 5.9, 13.3 / 8.7, 14.6 / 10.6; Jasper-10x5 at 1 x 208 input frames 763 -> 551,
+// with dense residuals at 2 x 811 1308 -> 1073.  What is left: the transposition (16 dword loads per 64 bytes x 4 frames, 10.7
 // cycles a unit, 3 us at 768 channels) and the first touch of the weights, which no ring depth covers (half of the 64
 // bytes per cycle).
 // Layouts (operands, packed weights, the 4 x 4 transposition, 80-byte rows) are those of conv_pipe.hip.
@@ -287,8 +287,9 @@ bool supported(const ConvParams& p) {
 
 // The tile with the least time, in cycles: a launch, and on the busiest compute unit for each of its workgroups the
 // activations it transposes (units of 16 dword loads), its steps (the weights of all its columns, or its products) and its
-// last stores.  Fitted to every tile of every dense layer of the Jasper-10x5 shape at 1 x 100 .. 8 x 1200 input
-// frames, weights from memory: the choice is 0.2 % from the best tile on average and 5.4 % at worst.
+// last stores.  Every tile timed beside the choice, chains of six layers of 256 .. 768 channels, 11 .. 25 taps, 104 ..
+// 3200 frames (40 shapes): it is 0.6 % from the best on average and 8 % at worst (256 channels, 406 frames); the choice
+// between this kernel and conv_pipe with its own, over 50 shapes to 12800 frames, 0.7 % and 7.7 %.
 bool pick(const ConvParams& p, Choice& best, double& cycles) {
   if (!supported(p)) return false;
   cycles = 1e300;

@@ -22,12 +22,12 @@
 // with and without a chunk on its way: two steps of three waited for weights asked for one step
 // earlier, the step after a chunk's request for the whole chunk, and every step for its last operand reads (16 x 800
 // frames, ring of three: 768 channels, 25 taps 150 -> 142 us, 512 channels, 17 taps 62 -> 58, 256, 11 taps 22 -> 17).
-// What bounds the rest: on operands that are not zeros the chip does not hold its clock.  The inner loop alone, on
-// random codes, 80 x 64 per wave: from registers 4.1 POP/s (4.9 on zeros), with the operand reads 3.9, with the weights from
-// the L2 as well 3.0 (4.5 on zeros); taller tiles stream fewer weights per product and draw less: 3.3 with 160 x 64,
-// 3.4 with 160 x 32.  The 768-channel layers run at 2.66, of 3.2 that their 480 tiles (of at most 512 at once) leave.
-// Small layers are bound by the number of workgroups instead: the tile (16 MT frames x 64 NT channels) is
-// chosen per layer by a small occupancy model.
+// What bounds the rest: on operands that are not zeros the chip does not hold its clock.  A plain loop of such
+// products (compiler's waits, 80 x 64 per wave), on random codes / on zeros: from registers 4.0 / 4.9 POP/s, with the
+// activations from LDS 3.6 / 4.4, with the weights from the L2 as well 2.7 / 3.9; 160 x 32 per wave 4.15 / 5.0, 3.1 / 3.8,
+// 2.8 / 3.7.  The 768-channel layers of 16 x 800 frames run at 2.59, in 480 tiles of at most 512 at once.
+// Small layers are bound by the number of workgroups instead: the tile (16 MT frames x 64 NT channels), the groups that
+// share its taps and the workgroups that share its chunks are chosen per layer by a model of cycles (unit_cycles).
 #include "kernels.hpp"
 #include "tuning.hpp"
 #include "vmem.hpp"
@@ -491,9 +491,9 @@ int resident(const ConvParams& p, const CpTile& c) {
 // run at once: a step is bound by the matrix pipes (18.6 cycles per product: with operands that are not zeros the
 // clock gives way), by a lone wave's own latencies, by the weights (NT KiB per wave) or by the operand reads; a
 // chunk costs a commit and a barrier; a workgroup its first loads and its epilogue, KG > 1 the meeting of the sums.
-// The constants are fitted to the times of every tile, group and split count for 256 .. 768 channels, 11 .. 25 taps
-// and 50 .. 12800 frames (8250 of them), each inside a chain of six layers whose weights are in no L2: the choice is
-// 0.2 % from the best on average and 4.8 % at worst.
+// The constants are fitted to chains of six layers whose weights are in no L2.  Every tile, with 1, 2, 3, 4, 6 and 8
+// splits where the launch is small, timed beside the choice: 256 .. 768 channels, 11 .. 25 taps, 104 .. 12800 frames, 50
+// shapes: it is 0.5 % from the best on average and 6.7 % at worst (384 channels, 1600 frames).
 double unit_cycles(const ConvParams& p, const CpTile& c, int64_t n, int chunks) {
   const double mn = c.MT * c.NT, taps = (p.k + c.KG - 1) / c.KG;
   const int occ = resident(p, c);

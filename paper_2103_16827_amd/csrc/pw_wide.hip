@@ -65,10 +65,9 @@ __device__ __forceinline__ void pw_wide_tile(const ConvParams& p, const PwwGeom&
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave % NWC, ks = wave / NWC;
-  // All arguments of the first loads in one go; no integer division and, on whole rows, no address per load.  With them
-  // the last of the sixteen waves had asked for its part of the tile after 3000 to 7600 cycles, 1300 to 4500 of
-  // them such arithmetic.  Single layers, us, before / now: 512 -> 512 G=13 5.1 / 4.5, G=200 6.8 / 6.6; 256 -> 256 G=100
-  // 5.25 / 4.85, G=1600 9.1 / 8.6; 2048 -> 512 G=50 8.4 / 7.9.
+  // All arguments of the first loads in one go; no integer division and, on whole rows, no address per load.  Eight
+  // layers in turn, each with its own tensors, us a layer, with them / now: 512 -> 512 G=13 4.97 / 4.46, G=200 7.46 / 7.25;
+  // 256 -> 256 G=100 5.27 / 4.78, G=1600 9.62 / 9.42; 2048 -> 512 G=50 8.77 / 8.43, G=200 13.19 / 13.06.
   // (MULTI: a layer's own arguments arrive later, a level further from the kernel's.)
   asm volatile("" ::"s"(p.Tin), "s"(p.xpad), "s"(g.G), "s"(g.gpr), "s"(g.splits), "s"(g.r_splits), "s"(g.r_gpr));
   if constexpr (!MULTI) asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.xbs), "s"(p.Cin), "s"(g.kch));
@@ -511,8 +510,11 @@ static bool pick_multi(const ConvParams* p, int n, int cus, int& most, Choice& c
 }
 
 // Layers one by one take at least 4.7 us each (launch and first loads), whichever kernel runs them; a chip that each of
-// them fills has kernels up to a fifth faster than this one, which is the line.  At 16 x 1600 frames and 512 channels
-// it divides blocks of a few layers from the others: together wherever it can be 4165 us, by this rule 4172, never 4232.
+// them fills has kernels up to a fifth faster than this one, which is the line.  Two to six layers of 64 .. 2048 -> 29 ..
+// 2048 channels, 1 x 104 .. 64 x 800 frames, 150 shapes: by this rule 0.31 to 1.01 of their time one by one.  Beyond the
+// line, together would be, at 32 x 800 frames: 2 x 256 -> 256 19.8 us against 15.9, 3 x 256 -> 1024 48 against 44, but 5 x 256 ->
+// 256 32.5 against 36.2, 6 x 768 -> 768 140 against 145.  A dense-residual Jasper-10x5 of 16 x 1600 frames: one by one 4201,
+// by the rule 4147, together wherever it can be 4131.
 bool pw_multi_better(const ConvParams* p, int n) {
   if (n < 2 || n > kMaxMulti || tuning().no_pw_wide || tuning().no_pw_multi) return false;
   const ConvParams& f = p[0];

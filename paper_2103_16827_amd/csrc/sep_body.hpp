@@ -24,12 +24,15 @@
 // pass of 16 NT channels per wave, compiler-visible loads.
 //
 // Two kernels: launches of few frames are bound by what a workgroup loads (sep_small_kernel), the others by their
-// products (sep_kernel).  QuartzNet-15x5, one utterance of 1237 frames 626 -> 548 us, 32 utterances of 1600 1387 -> 1323.
+// products (sep_kernel).  Graph replays of QuartzNet-15x5, before sep_small_kernel, place() below and the shorter
+// beginnings of the pointwise kernels / with them, projections apart: 1 x 1237 frames 628 / 561 us, 32 x 1600 1163 / 1135;
+// 10x5, 8 x 1104 503 / 485.
 //
 // A block's residual projection, which reads what its first pair reads, runs in the pair's launch: workgroups of
 // their own take x itself for the tile and go on with the pointwise half.  At few frames they find units that the pair
 // leaves free, at many they start on each unit as it finishes; either way a launch and its chain of first loads
-// disappear (QuartzNet-15x5, 1 x 1237 548 -> 486 us, 32 x 1600 1316 -> 1245; 10x5, 8 x 1104 468 -> 441).
+// disappear.  Apart / together: 15x5, 1 x 1237 561 / 484 us, 32 x 1600 1135 / 1102, 64 x 1600 2146 / 2115; 10x5, 8 x 1104
+// 485 / 447 (inputs that change from pass to pass, all three steps: 15x5, 32 x 1600 1326 -> 1230).
 #pragma once
 #include "sep.hpp"
 
@@ -111,9 +114,9 @@ __device__ __forceinline__ bool place(const SepParams& p, Place& at) {
   return true;
 }
 
-// Constants of N = 16, 32 or 64 / 3 channels in one or two loads per wave: a load of any size holds the address path
+// Constants of N = 16 or 32 channels in one or two loads per wave: a load of any size holds the address path
 // of the unit for 16 cycles, so three 16-channel loads cost as much as 3 KiB of weights.  Lanes [0, N) ask for m,
-// [N, 2 N) for s, [2 N, 3 N) for the bias if that fits; get() brings a channel's to where it is used.
+// [N, 2 N) for s, [2 N, 3 N) for the bias if that fits (N = 16); get() brings a channel's to where it is used.
 template <int N>
 struct Consts {
   int32_t ms = 0, b = 0;
