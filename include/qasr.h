@@ -365,8 +365,9 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
  *     the op that the launch begins with (i; i - 1 where op i is the pointwise half of a depthwise +
  *     pointwise pair; one less for a pair that runs together with the pointwise layer before it, a residual
  *     projection of the same tensor; the first of consecutive pointwise layers of equal output shape that run
- *     together; -1 if i is out of range), and in *kernel (unless NULL) the kernel's
- *     name: "sep" for these, "pw_wide" for pointwise layers of the pw_pipe, pw_tile and gemm_mfma families
+ *     together; the first of a chain of pointwise layers, each the only reader of the one before, or the depthwise
+ *     layer in front of them; -1 if i is out of range), and in *kernel (unless NULL) the kernel's
+ *     name: "pw_chain" for chains, "sep" for pairs, "pw_wide" for pointwise layers of the pw_pipe, pw_tile and gemm_mfma families
  *     and "conv_few" for layers of the conv_pipe family that these kernels run faster, else the family's.  HOST
  *     only. */
 int32_t qasr_encoder_num_ops(const qasr_encoder* e);
@@ -375,7 +376,7 @@ int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** ke
 /* 1 if op i's activation (qasr_op.act) is applied inside the layer's own kernel over 16-byte aligned x and
  * y (a unary activation after a layer that pw_pipe, pw_wide or dw_pipe runs, through a 256-entry table of
  * the activation's int8 outputs built at create time), 0 if it runs as the separate in-place pass or
- * the op has none; -1 if i is out of range.  Same bits either way.  (In a pair it always is.) */
+ * the op has none; -1 if i is out of range.  Same bits either way.  (In a pair it always is, in a chain a GLU too.) */
 int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i);
 
 /* Runs of layers in one launch (EXPERIMENTAL: only with QASR_TEAM set in the environment when the

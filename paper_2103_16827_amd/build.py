@@ -64,7 +64,7 @@ def _registers(operands: str):
 
 def ring_copies(asm_text: str):
     """(kernel, instruction) for every copy, between a kernel's first and last matrix product, out of a register that a
-    hand-issued 16-byte load fills.  To the compiler such a register holds its value from the `asm` statement on, so it
+    hand-issued 16-byte load further up fills.  To the compiler such a register holds its value from the `asm` statement on, so it
     may move it while the load is on its way (it has, where it indexed a ring at run time): the copy is then
     what was there before, and the data lands in a register that belongs to something else."""
     bad = []
@@ -76,13 +76,12 @@ def ring_copies(asm_text: str):
                 by_hand = "#ASMSTART" in line
             elif line and line[0] not in ";." and not line.endswith(":"):
                 ins.append((line.split(";")[0].strip(), by_hand))
+        products = [i for i, (text, _) in enumerate(ins) if text.startswith("v_mfma")]
         ring = set()
-        for text, by_hand in ins:
+        for i, (text, by_hand) in enumerate(ins[:products[-1]] if products else []):
             if by_hand and re.match(r"(global|buffer)_load_dwordx4 ", text):
                 ring |= _registers(text.split(",")[0])
-        products = [i for i, (text, _) in enumerate(ins) if text.startswith("v_mfma")]
-        for text, _ in ins[products[0]:products[-1]] if products else []:
-            if re.match(r"v_(mov|accvgpr|swap|pk_mov)", text) and _registers(text.partition(",")[2]) & ring:
+            elif i > products[0] and re.match(r"v_(mov|accvgpr|swap|pk_mov)", text) and _registers(text.partition(",")[2]) & ring:
                 bad.append((part.split(":")[0], text))
     return bad
 
@@ -111,7 +110,7 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(bdir, os.path.basename(src) + ".o")
         cmd = [hipcc, "-x", "hip", "-c", src, "-o", obj] + [f for f in HIPCC_FLAGS if f != "-shared"]
         with open(src) as f:
-            rings = "gload16(" in f.read()
+            rings = re.search(r"gload16(_into\b|\()", f.read())
         if rings or "_sdwa" in source_with_local_includes(src):   # rings of hand-issued loads, hand-written partial register writes: device assembly too
             asm = os.path.join(bdir, os.path.basename(src) + ".gfx950.s")
             acmd = [hipcc, "-x", "hip", "--cuda-device-only", "-S", src, "-o", asm] + \

@@ -67,6 +67,11 @@ __global__ __launch_bounds__(256) void act_table_kernel(ActParams c, uint8_t* ta
   table[threadIdx.x] = (uint8_t)rescale_clamp(c.kind == 2 ? q * sg : sg, c.m, c.s);
 }
 
+// the sigmoid codes that the GLU kernel builds per workgroup, written out once
+__global__ __launch_bounds__(256) void glu_table_kernel(ActParams c, uint16_t* table) {
+  table[threadIdx.x] = (uint16_t)sigmoid_code_dev((int)threadIdx.x - 128, c);
+}
+
 // x, y: [B][C T] int8 per batch item (strides xbs, ybs); grid = (blocks, B)
 __global__ __launch_bounds__(256) void act_unary_kernel(ActParams c, const int8_t* x, int8_t* y,
                                                         int64_t n, int64_t xbs, int64_t ybs, int vec_ok) {
@@ -470,6 +475,10 @@ hipError_t launch_softmax_small(const SoftmaxSmall& p, hipStream_t st) {
 hipError_t launch_act_table(const ActParams& c, uint8_t* table, hipStream_t st) {
   hipLaunchKernelGGL(act_table_kernel, dim3(1), dim3(256), 0, st, c, table);
   return hipGetLastError();
+}
+
+hipError_t launch_glu_table(const ActParams& c, uint16_t* table, hipStream_t st) {
+  return launch_kernel(glu_table_kernel, dim3(1), dim3(256), 0, st, c, table);
 }
 
 hipError_t launch_act(const ActParams& c, const int8_t* x, int8_t* y, int32_t B, int64_t n, int64_t xbs, int64_t ybs,

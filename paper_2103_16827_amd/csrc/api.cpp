@@ -2,6 +2,7 @@
 // encoder executor (a flat op list over activation slots).  See include/qasr.h.
 #include "../../include/qasr.h"
 #include "kernels.hpp"
+#include "pw_chain.hpp"
 #include "sep.hpp"
 #include "team.hpp"
 #include "tuning.hpp"
@@ -166,6 +167,7 @@ struct qasr_encoder {
     bool act_fused = false;   // the layer's own kernel applies it (for 16-byte aligned, dense input and output)
     qasr::ActParams act;   // applied in place to the output when has_act
     const uint8_t* act_table = nullptr;   // unary activations: one int8 output per int8 code (kernels with applies_act_table)
+    const uint8_t* glu_table = nullptr;   // a GLU's 256 sigmoid codes of 16 bits (chains)
     // This depthwise op and the pointwise op after it may run as one launch (sep.hpp): nothing else reads
     // what it writes.  Its weight image.
     bool sep = false;
@@ -176,6 +178,10 @@ struct qasr_encoder {
     // This and the next multi - 1 ops are pointwise layers of equal output shape that touch none of each other's
     // outputs (the projections of a dense-residual block): they may run as one launch.  At the first of them; else 0.
     int32_t multi = 0;
+    // This and the next chain - 1 ops are pointwise layers of which each but the first reads what the one before writes, and
+    // nobody else does: they may run as one launch.  At every op that such a run can begin with; at a depthwise op, whose pair
+    // begins one, the number of pointwise layers after it; else 0.
+    int32_t chain = 0;
     int32_t in_channels = 0;  // channels of the slot read (p.Cin, or more for a channel-prefix view)
   };
   std::vector<Op> ops;
@@ -665,6 +671,15 @@ qasr_status qasr_plan_slot_buffers(const int32_t* in_slot, const int32_t* res_sl
   return QASR_OK;
 }
 
+// op as part of a chain (its tensors and rows are the caller's business)
+static void chain_op(const qasr_encoder::Op& op, qasr::ChainOp& c) {
+  c.p = op.p;
+  c.glu = op.glu_table != nullptr;
+  c.table = c.glu ? op.glu_table : op.act_table;
+  c.glu_m = c.glu ? op.act.m : 0;
+  c.glu_s = c.glu ? op.act.s : 1;
+}
+
 // may_pitch: rows may get a pitch of their own
 static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_slots, bool may_pitch, qasr_encoder** out) {
   if (!ops || !out) return QASR_ERR_NULL;
@@ -732,7 +747,7 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
     slot[o.out_slot].C = o.d.Cout;
     slot[o.out_slot].T = Tout;
     if (has_packed_form(&o.d)) packed_bytes += round256(packed_bytes_of(&o.d));
-    if (o.act && o.act->kind != QASR_ACT_GLU) packed_bytes += 256;   // room for a fused activation's table
+    if (o.act) packed_bytes += o.act->kind != QASR_ACT_GLU ? 256 : 512;   // room for a fused activation's table
   }
 
   qasr_encoder* e = new (std::nothrow) qasr_encoder();
@@ -845,11 +860,45 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
           return hip_status(te);
         }
         op.act_table = table;
+      } else {
+        uint16_t* const table = reinterpret_cast<uint16_t*>(e->packed + poff);
+        poff += 512;
+        const hipError_t te = qasr::launch_glu_table(op.act, table, nullptr);
+        if (te != hipSuccess) {
+          qasr_encoder_destroy(e);
+          return hip_status(te);
+        }
+        op.glu_table = reinterpret_cast<const uint8_t*>(table);
       }
     }
   }
   if (split_bytes && e->split_off) e->ws_bytes =   // (an encoder that needs no workspace goes on needing none)
       e->split_off + round256(split_bytes) + round256(4 * qasr::kConvSplitCounters);
+  // op i + 1 reads what op i writes, as its input and nothing else, and no other op does
+  auto read_by_next_only = [&](int32_t i) {
+    const qasr_op &o = ops[i], &q = ops[i + 1];
+    if (q.in_slot != o.out_slot || q.res_slot == o.out_slot) return false;
+    for (int32_t r = 0; r < q.n_more_res; ++r)
+      if (q.more_res_slots[r] == o.out_slot) return false;
+    for (int32_t j = i + 2; j < n_ops && ops[j - 1].out_slot != o.out_slot; ++j) {
+      if (ops[j].in_slot == o.out_slot || ops[j].res_slot == o.out_slot) return false;
+      for (int32_t r = 0; r < ops[j].n_more_res; ++r)
+        if (ops[j].more_res_slots[r] == o.out_slot) return false;
+    }
+    return true;
+  };
+  // only the first half of op i's channels, a GLU's products, is ever read, and by other ops only
+  auto read_by_half = [&](int32_t i) {
+    const qasr_op& o = ops[i];
+    for (int32_t j = i + 1; j < n_ops; ++j) {
+      if (ops[j].in_slot == o.out_slot && 2 * ops[j].d.Cin > o.d.Cout) return false;
+      if (ops[j].res_slot == o.out_slot) return false;
+      for (int32_t r = 0; r < ops[j].n_more_res; ++r)
+        if (ops[j].more_res_slots[r] == o.out_slot) return false;
+      if (ops[j].out_slot == o.out_slot) return true;
+    }
+    return i + 1 < n_ops;
+  };
   // ---- depthwise + pointwise pairs that run as one launch
   if (!e->pitched && qasr::tuning().team) {
     // (the experimental team kernel takes such layers one by one)
@@ -860,13 +909,8 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
       const qasr_op &o = ops[i], &q = ops[i + 1];
       if (o.d.groups == 1 || q.in_slot != o.out_slot || q.res_slot == o.out_slot || o.out_slot == 0) continue;
       if ((o.act && o.act->kind == QASR_ACT_GLU) || q.act) continue;
-      bool only = e->ops[i + 1].out_slot != e->ops[i].in_slot || i + 2 == n_ops;   // (tiles read their neighbours' input)
-      for (int32_t r = 0; r < q.n_more_res; ++r) only = only && q.more_res_slots[r] != o.out_slot;
-      for (int32_t j = i + 2; j < n_ops && only && ops[j - 1].out_slot != o.out_slot; ++j) {
-        only = ops[j].in_slot != o.out_slot && ops[j].res_slot != o.out_slot;
-        for (int32_t r = 0; r < ops[j].n_more_res; ++r) only = only && ops[j].more_res_slots[r] != o.out_slot;
-      }
-      if (!only) continue;
+      if (e->ops[i + 1].out_slot == e->ops[i].in_slot && i + 2 != n_ops) continue;   // (tiles read their neighbours' input)
+      if (!read_by_next_only(i)) continue;
       ConvParams dp = e->ops[i].p, qp = e->ops[i + 1].p;
       rows_of(e, i, row_pad(dp.Tin), row_pad(dp.Tout), dp);
       rows_of(e, i + 1, row_pad(qp.Tin), row_pad(qp.Tout), qp);
@@ -900,6 +944,35 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
       }
       if (n > 1) e->ops[i].multi = n;
       i += n > 1 ? n : 1;
+    }
+    // ---- runs of pointwise layers, each the only reader of the one before
+    for (int32_t i = 0; i + 1 < n_ops; ++i) {
+      auto plain = [&](int32_t j) {
+        const qasr_op& o = ops[j];
+        return o.d.groups == 1 && o.d.k == 1 && o.d.stride == 1 && o.d.pad_left == 0 && o.d.pad_right == 0 && o.res_slot < 0 &&
+               (!o.act || o.act->kind != QASR_ACT_GLU || read_by_half(j));
+      };
+      int32_t n = 0;
+      while (i + n < n_ops && n < qasr::kMaxChain && plain(i + n)) {
+        ++n;
+        if (i + n == n_ops || !read_by_next_only(i + n - 1)) break;
+      }
+      for (; n > 1; --n) {                    // (slots are buffers by now; the last op of all writes the caller's output)
+        if (i + n < n_ops && e->ops[i + n - 1].out_slot == e->ops[i].in_slot) continue;
+        qasr::ChainOp c[qasr::kMaxChain];
+        for (int32_t j = 0; j < n; ++j) {
+          chain_op(e->ops[i + j], c[j]);
+          rows_of(e, i + j, row_pad(c[j].p.Tin), row_pad(c[j].p.Tout), c[j].p);
+        }
+        if (qasr::pw_chain_supported(nullptr, c, n)) break;
+      }
+      e->ops[i].chain = n > 1 ? n : 0;
+    }
+    for (int32_t i = 0; i + 1 < n_ops; ++i) {  // ... and the depthwise layer before them (whose tiles read their neighbours' input)
+      qasr_encoder::Op& op = e->ops[i];
+      const int32_t n = op.sep ? e->ops[i + 1].chain : 0;
+      if (n < 2 || (i + 1 + n < n_ops && e->ops[i + n].out_slot == op.in_slot)) continue;
+      op.chain = n;
     }
     hipError_t he = img_bytes ? hipMalloc((void**)&e->sep_images, img_bytes) : hipSuccess;
     for (int32_t i = 0; i < n_ops && he == hipSuccess; ++i) {
@@ -971,6 +1044,20 @@ static bool runs_as_multi(const qasr_encoder* e, size_t i) {
   return qasr::pw_multi_better(p, n);
 }
 
+// the ops that run as one launch, a chain, from op i on (0: none)
+static int32_t runs_as_chain(const qasr_encoder* e, size_t i) {
+  const int32_t n = e->ops[i].chain, from_dw = e->ops[i].sep ? 1 : 0;
+  if (n < 2) return 0;
+  qasr::ChainOp c[qasr::kMaxChain];
+  for (int32_t j = 0; j < n; ++j) {
+    chain_op(e->ops[i + from_dw + j], c[j]);
+    rows_of(e, i + from_dw + j, 0, 0, c[j].p);
+  }
+  ConvParams d = e->ops[i].p;
+  rows_of(e, i, 0, 0, d);
+  return qasr::pw_chain_better(from_dw ? &d : nullptr, c, n) ? n + from_dw : 0;
+}
+
 // the same for op i, a projection, with ops i + 1 and i + 2
 static bool runs_with_pair(const qasr_encoder* e, size_t i) {
   if (!e->ops[i].sep_proj) return false;
@@ -983,23 +1070,25 @@ static bool runs_with_pair(const qasr_encoder* e, size_t i) {
 
 int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** kernel) {
   if (!e || i < 0 || i >= (int32_t)e->ops.size()) return -1;
-  for (int32_t first = i; first >= 0 && first >= i - 2; --first)
-    if (runs_with_pair(e, (size_t)first)) {
-      if (kernel) *kernel = "sep";
-      return first;
+  for (int32_t first = 0;;) {                       // launch after launch, as a forward goes
+    const char* name = "sep";
+    int32_t n = runs_as_chain(e, (size_t)first);
+    if (n) name = "pw_chain";
+    else if (runs_as_multi(e, (size_t)first)) n = e->ops[first].multi, name = "pw_wide";
+    else if (runs_with_pair(e, (size_t)first)) n = 3;
+    else if (runs_as_pair(e, (size_t)first)) n = 2;
+    else n = 1, name = nullptr;
+    if (first + n <= i) {
+      first += n;
+      continue;
     }
-  for (int32_t first = i; first >= 0 && first > i - qasr::kMaxMulti; --first)
-    if (e->ops[first].multi > i - first && runs_as_multi(e, (size_t)first)) {
-      if (kernel) *kernel = "pw_wide";
-      return first;
+    if (kernel) {
+      ConvParams p = e->ops[i].p;
+      rows_of(e, (size_t)i, 0, 0, p);
+      *kernel = name ? name : kernel_name(pick_kernel(p));
     }
-  const bool second = i > 0 && runs_as_pair(e, (size_t)i - 1);
-  if (kernel) {
-    ConvParams p = e->ops[i].p;
-    rows_of(e, (size_t)i, 0, 0, p);
-    *kernel = second || runs_as_pair(e, (size_t)i) ? "sep" : kernel_name(pick_kernel(p));
+    return first;
   }
-  return second ? i - 1 : i;
 }
 
 int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i) {
@@ -1076,6 +1165,25 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     bind(i, p);
     if (i > 0)
       if (const hipError_t be = begin(i); be != hipSuccess) return hip_status(be);
+    if (how.pairs) {
+      // a chain of pointwise layers, from a depthwise layer on or by itself
+      if (const int32_t cn = op.chain; cn > 1) {
+        const int32_t from_dw = op.sep ? 1 : 0;
+        qasr::ChainOp c[qasr::kMaxChain];
+        for (int32_t j = 0; j < cn; ++j) {
+          chain_op(e->ops[i + from_dw + j], c[j]);
+          bind(i + from_dw + j, c[j].p);
+        }
+        ConvParams d = p;
+        d.act_lut = op.act_table;
+        if (qasr::pw_chain_better(from_dw ? &d : nullptr, c, cn)) {
+          const hipError_t ce = qasr::launch_pw_chain(from_dw ? &d : nullptr, op.sep_img, c, cn, st);
+          if (ce != hipSuccess) return hip_status(ce);
+          i += (size_t)(cn + from_dw) - 1;
+          continue;
+        }
+      }
+    }
     if (op.multi > 1 && how.pairs) {
       ConvParams l[qasr::kMaxMulti];
       l[0] = p;

@@ -47,6 +47,8 @@ hipError_t launch_pw_pipe(const ConvParams& p, hipStream_t st);
 bool pw_wide_supported(const ConvParams& p);
 bool pw_wide_better(const ConvParams& p, bool pipe);
 hipError_t launch_pw_wide(const ConvParams& p, hipStream_t st);
+// its model of a layer's time on the whole chip, us without the launch; false where it does not take the layer
+bool pw_wide_us(const ConvParams& p, double& us);
 // Several pointwise layers of equal output shape, none of which reads what another writes, in one launch of pw_wide's
 // tiles; pw_multi_better: whether they can and it is the faster way.
 constexpr int kMaxMulti = 12;
@@ -93,10 +95,12 @@ struct ActParams {
   int32_t kind, m, s, u;
   int64_t q_ln2, q_b, q_c;
 };
-// x: B items of n (2 n for GLU: value half, gate half) int8 at stride xbs; y: B items of n int8
-// at stride ybs; y may be x itself when the strides are equal.
 // table[code + 128] = int8 output of the unary activation (sigmoid, swish) for every int8 code
 hipError_t launch_act_table(const ActParams& c, uint8_t* table, hipStream_t st);
+// table[code + 128] = 16-bit sigmoid code of a GLU's gate, for every int8 code
+hipError_t launch_glu_table(const ActParams& c, uint16_t* table, hipStream_t st);
+// x: B items of n (2 n for GLU: value half, gate half) int8 at stride xbs; y: B items of n int8
+// at stride ybs; y may be x itself when the strides are equal.
 hipError_t launch_act(const ActParams& c, const int8_t* x, int8_t* y, int32_t B, int64_t n, int64_t xbs,
                       int64_t ybs, hipStream_t st);
 // rows x L int32 logits -> int8 probabilities at scale 2^-7 (kind, m, s unused).

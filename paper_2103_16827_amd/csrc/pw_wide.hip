@@ -447,6 +447,11 @@ bool pw_wide_supported(const ConvParams& p) {
   return !tuning().no_pw_wide && pick(p, 256, 1, p.Cin, c, t);
 }
 
+bool pw_wide_us(const ConvParams& p, double& us) {
+  Choice c;
+  return pick(p, 256, 1, p.Cin, c, us);
+}
+
 // Where this kernel is the faster one, in 16-frame groups G.  Measured on single layers whose weights and
 // tensors come from memory (us, the other kernel / this one), 50 shapes at up to 14 sizes each; with these
 // lines the choice is within 1 % of the better kernel on average.

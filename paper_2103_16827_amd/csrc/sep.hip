@@ -137,6 +137,26 @@ bool sep_projection_supported(const ConvParams& d, const ConvParams& q, const Co
          (uintptr_t)r.y % 16 == 0 && r.x == d.x;
 }
 
+static void fill_dw(const ConvParams& d, const Geometry& g, int MT, DwParams& p) {
+  p.x = d.x; p.dbias = d.bias; p.dm = d.m; p.ds = d.s; p.lut = d.act_lut;
+  p.xbs = d.xbs; p.xpitch = d.Tin + d.xpad; p.Tin = d.Tin;
+  p.o16 = -((d.pl + g.delta) / 16);
+  p.nk = g.nk;
+  p.units = units_of(d, g, MT);
+  p.dwoff = g.delta >> 2;
+  p.drelu = d.relu;
+  p.units_inv = (65536 + p.units - 1) / p.units;
+}
+
+bool dw_small_params(const ConvParams& d, int MT, DwParams& p, int& NA) {
+  Geometry g;
+  if (!geometry(d, g) || MT > 2 || d.Cout % 256 || d.Tin < 4 || x_ragged(d)) return false;
+  fill_dw(d, g, MT, p);
+  NA = g.NA;
+  const int C = d.Cout / sep::kWaves;               // rows a wave brings in at a time
+  return p.units <= sep::kMaxUnits && (int64_t)C * p.xpitch <= 0x7fffffffLL && C * p.units <= 64 * sep::row_loads(C, MT, NA);
+}
+
 size_t sep_image_bytes(const ConvParams& d) {
   Geometry g;
   return geometry(d, g) ? rows_image_bytes(d.Cout, g.NA) + (size_t)d.Cout / 16 * g.NA * 1024 : 0;
@@ -154,13 +174,8 @@ static hipError_t launch(const ConvParams& d, const uint32_t* img, const ConvPar
   SepChoice c;
   if (!plan(d, q, compute_units(), r != nullptr, g, c)) return hipErrorInvalidValue;
   SepParams p{};
-  p.x = d.x; p.img = c.MT <= 2 ? img : img + rows_image_bytes(d.Cout, g.NA) / 4; p.dbias = d.bias; p.dm = d.m; p.ds = d.s; p.lut = d.act_lut;
-  p.xbs = d.xbs; p.xpitch = d.Tin + d.xpad; p.Tin = d.Tin;
-  p.o16 = -((d.pl + g.delta) / 16);
-  p.nk = g.nk;
-  p.units = units_of(d, g, c.MT);
-  p.dwoff = g.delta >> 2;
-  p.drelu = d.relu;
+  fill_dw(d, g, c.MT, p);
+  p.img = c.MT <= 2 ? img : img + rows_image_bytes(d.Cout, g.NA) / 4;
   p.w = q.w; p.bias = q.bias; p.m = q.m; p.s = q.s; p.res = q.res; p.y = q.y;
   p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.Tout = q.Tout; p.relu = q.relu;
   const int gpr = (q.Tout + 15) / 16;
@@ -170,7 +185,6 @@ static hipError_t launch(const ConvParams& d, const uint32_t* img, const ConvPar
   p.yragged = y_ragged(q);
   p.splits = c.splits;
   p.wgs = d.B * p.tpr * p.splits;                // (< 2^22: pick)
-  p.units_inv = (65536 + p.units - 1) / p.units;
   p.r_splits = 1.0f / (float)p.splits;
   p.r_tpr = 1.0f / (float)p.tpr;
   const int C = c.MT <= 2 ? 4 * c.KCH : 16;      // rows a wave brings in at a time

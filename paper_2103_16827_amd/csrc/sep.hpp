@@ -6,8 +6,9 @@
 
 namespace qasr {
 
-struct SepParams {
-  // depthwise half: x rows (pitch xpitch, batch stride xbs, Tin frames), weight image (sep_image_*)
+// a depthwise layer whose output stays in LDS
+struct DwParams {
+  // x rows (pitch xpitch, batch stride xbs, Tin frames), weight image (sep_image_*)
   const int8_t* x;
   const uint32_t* img;
   const int32_t *dbias, *dm, *ds;    // dbias may be null
@@ -19,6 +20,10 @@ struct SepParams {
   int32_t units;                     // 16-byte chunks per row in LDS (odd: 16 rows then start in different banks)
   int32_t dwoff;                     // dwords between a row's start and the first window
   int32_t drelu;
+  int32_t units_inv;                 // ceil(2^16 / units): L / units = L units_inv >> 16 for L < 512, units <= 15
+};
+
+struct SepParams : DwParams {
   // pointwise half
   const int8_t* w;                   // packed (common.hpp)
   const int32_t *bias, *m, *s;       // bias may be null
@@ -38,9 +43,11 @@ struct SepParams {
   const int32_t *bias2, *m2, *s2;
   int8_t* y2;
   int32_t relu2, wgs2, per_xcd2;
-  int32_t units_inv;                 // ceil(2^16 / units): L / units = L units_inv >> 16 for L < 512, units <= 15
   float r_splits, r_tpr;             // reciprocals of the two
 };
+
+// The depthwise half's parameters for tiles of MT <= 2 groups (all but img); false if d is none that it takes.  NA: quads of taps.
+bool dw_small_params(const ConvParams& d, int MT, DwParams& p, int& NA);
 
 struct SepChoice { int KCH, MT, NA, NT, KS, splits; bool ragged; };   // KS: wave groups over the pointwise half's input channels
 

@@ -35,14 +35,13 @@
 // 485 / 447 (inputs that change from pass to pass, all three steps: 15x5, 32 x 1600 1326 -> 1230).
 #pragma once
 #include "sep.hpp"
+#include "vmem.hpp"
 
 #include <type_traits>
 
 namespace qasr {
 namespace sep {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kStoreThrough = 17;    // sc0 sc1: the output rows are written through (see pw_pipe_body.hpp)
@@ -129,6 +128,13 @@ struct Consts {
     const int which = lane / N;
     const int32_t* const q = which == 0 ? pm : which == 1 ? ps : (N == 16 && pb) ? pb : pm;
     ms = q[c0 + (lane & (N - 1))];
+  }
+  // by requests that the caller waits for (N = 32), without a branch between a request and its register's use
+  __device__ __forceinline__ void load_by_hand(const int32_t* pm, const int32_t* ps, const int32_t* pb, int c0, int lane) {
+    static_assert(N == 32, "m and s in one request");
+    bias = pb != nullptr;
+    gload4_into(ms, (lane < 32 ? pm : ps) + c0 + (lane & 31));
+    gload4_into(b, (bias ? pb : pm) + c0 + (lane & 31));
   }
   __device__ __forceinline__ int32_t get(int32_t v, int from) const { return __builtin_amdgcn_ds_bpermute(4 * from, v); }
   __device__ __forceinline__ int32_t m(int c) const { return get(ms, c); }
@@ -421,6 +427,155 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   }
 }
 
+// The depthwise layer of a wave's CPW channels for MT <= 2 groups of frames: rows and weights by as few requests as can be, weights as
+// they are (sep_image's first part), which become Toeplitz rows by one byte permutation per dword.
+template <int CPW, int MT, int NA, bool RAGGED>
+struct DwSmall {
+  static_assert(MT <= 2, "two units per row");
+  static constexpr int NL = row_loads(CPW, MT, NA);
+  static constexpr int WS = NA | 1;                 // 16-byte units of a weight row in LDS (odd: 16 rows in different banks)
+  static constexpr int NWL = (CPW * NA + 63) / 64;
+  v4i wr[NWL], xr[NL];
+  uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
+  Consts<CPW> dc;
+
+  // (the bias first: it is on one path only)
+  __device__ __forceinline__ void load_bias(const DwParams& p, int c_wave, int lane) { dc.load_bias(p.dbias, c_wave, lane); }
+  __device__ __forceinline__ void load(const DwParams& p, int b, int g0, int c_wave, int lane) {
+    // weights: chunk L of the wave's CPW x NA
+    {
+      const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
+#pragma unroll
+      for (int j = 0; j < NWL; ++j) wr[j] = src[min(lane + 64 * j, CPW * NA - 1)];
+    }
+    dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
+    // rows: chunk L of the wave's CPW x units; chunks outside [0, Tin) are zero, the chunk a row ends in is masked
+    {
+      const int8_t* const xw = p.x + (int64_t)b * p.xbs + (int64_t)c_wave * p.xpitch;
+      const int t_last = p.Tin & ~15;
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
+        const int t = 16 * (g0 + p.o16 + u);
+        const bool on = ch < CPW && t >= 0 && t < p.Tin;
+        if (on) in |= 1u << j;
+        if (t == t_last) last |= 1u << j;
+        xr[j] = (v4i){0, 0, 0, 0};
+        if (RAGGED) {
+          if (on) xr[j] = t == t_last ? load_row16(xw + ch * p.xpitch, t, p.Tin) : *reinterpret_cast<const unaligned_chunk16*>(xw + ch * p.xpitch + t);
+        } else if (64 * j < CPW * p.units) {          // (uniform; lanes without a chunk read the first one and drop it)
+          xr[j] = *reinterpret_cast<const v4i*>(xw + (on ? ch * p.xpitch + t : 0));
+        }
+      }
+    }
+  }
+  // into LDS: CPW rows at rows (small_row_bytes), CPW weight rows of 16 WS bytes at wlds
+  __device__ __forceinline__ void lay(const DwParams& p, unsigned char* rows, unsigned char* wlds, int lane) {
+#pragma unroll
+    for (int j = 0; j < NWL; ++j) {
+      const int L = lane + 64 * j, ch = L / NA;
+      if (L < CPW * NA) *reinterpret_cast<v4i*>(wlds + 16 * (ch * WS + L - ch * NA)) = wr[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      v4i r = xr[j];
+      if (!RAGGED) {
+        if (!(in & (1u << j))) r = (v4i){0, 0, 0, 0};
+        if (last & (1u << j)) r = keep_bytes(r, p.Tin & 15);
+      }
+      if (lane + 64 * j < CPW * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = r;
+    }
+    asm volatile("" ::: "memory");                    // (lanes read what other lanes of the wave wrote: LDS is in order)
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // NB blocks of 16 channels from block b0 on, side by side: lane -> channel lane / 4 of the block, frames 4 (lane % 4) + (0..3) of a group
+  template <int NB>
+  __device__ __forceinline__ void multiply(const DwParams& p, const unsigned char* rows, const unsigned char* wlds, int lane, int b0,
+                                           v4i (&dacc)[NB][MT]) const {
+    const int ch_l = lane >> 2, n_l = lane & 3;
+    // Toeplitz row m = lane % 4 of four taps: bytes 4 - m .. 7 - m of (this dword, the one before)
+    const uint32_t sel = 0x07060504u - 0x01010101u * (uint32_t)n_l;
+    const unsigned char* const win = rows + (16 * b0 + ch_l) * (16 * p.units) + 4 * (n_l + p.dwoff);
+    const unsigned char* const wrow = wlds + (16 * b0 + ch_l) * (16 * WS);
+    constexpr int LA = 2, WQ = MT + LA;               // quads read ahead
+    uint32_t wd[NB][WQ][4];
+    v4i aq[NB][LA + 1];
+    uint32_t before[NB];
+    auto read_win = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+      for (int blk = 0; blk < NB; ++blk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          wd[blk][a % WQ][i] = *reinterpret_cast<const uint32_t*>(win + 256 * blk * p.units + 16 * a + 4 * i);
+    };
+    auto read_taps = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+      for (int blk = 0; blk < NB; ++blk) aq[blk][a % (LA + 1)] = *reinterpret_cast<const v4i*>(wrow + 256 * blk * WS + 16 * a);
+    };
+#pragma unroll
+    for (int a = 0; a < LA; ++a) read_taps(a);
+#pragma unroll
+    for (int a = 0; a < MT + LA - 1; ++a) read_win(a);
+#pragma unroll
+    for (int blk = 0; blk < NB; ++blk) {
+      const int32_t db = dc.bias_of(16 * (b0 + blk) + ch_l);
+      before[blk] = 0;
+#pragma unroll
+      for (int q = 0; q < MT; ++q) dacc[blk][q] = (v4i){db, db, db, db};
+    }
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      if (a + LA < NA) {
+        read_taps(a + LA);
+        read_win(a + MT + LA - 1);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t t[NB];
+#pragma unroll
+        for (int blk = 0; blk < NB; ++blk) {
+          const uint32_t d = (uint32_t)aq[blk][a % (LA + 1)][i];
+          t[blk] = __builtin_amdgcn_perm(d, before[blk], sel);
+          before[blk] = d;
+        }
+        if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
+#pragma unroll
+          for (int q = 0; q < MT; ++q)
+#pragma unroll
+            for (int blk = 0; blk < NB; ++blk)
+              dacc[blk][q] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)t[blk], (int)wd[blk][(a + q) % WQ][i], dacc[blk][q], 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // put(block, group, the lane's four frames) of the finished blocks
+  template <int NB, typename Put>
+  __device__ __forceinline__ void finish(const DwParams& p, const unsigned char* lut, int lane, int b0, const v4i (&dacc)[NB][MT], Put put) const {
+    const int ch_l = lane >> 2;
+#pragma unroll
+    for (int blk = 0; blk < NB; ++blk) {
+      const int32_t m = dc.m(16 * (b0 + blk) + ch_l), s = dc.s(16 * (b0 + blk) + ch_l);
+      auto form = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+          const int32_t a4[4] = {dacc[blk][q][0], dacc[blk][q][1], dacc[blk][q][2], dacc[blk][q][3]};
+          uint32_t pk;
+          if constexpr (decltype(fast_tag)::value)
+            pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
+          else
+            pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
+          if (p.lut) pk = through_table(lut, pk);
+          put(b0 + blk, q, pk);
+        }
+      };
+      if (!__all(s >= kShortMin && s <= kShortMax)) form(std::false_type{}, std::false_type{});
+      else if (p.drelu) form(std::true_type{}, std::true_type{});
+      else form(std::true_type{}, std::false_type{});
+    }
+  }
+};
+
 // ---- Tiles of one and two groups: launches of few frames, where the products are nothing and the loads
 // everything.  A load instruction of any size holds a compute unit's address path for 16 cycles; with 16 waves asking
 // for weight images of four bytes per tap, for constants three at a time and for two blocks' rows apart, one workgroup
@@ -445,10 +600,8 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   extern __shared__ __align__(128) unsigned char lds[];   // [Cin][128 B] tile, [kWaves] row buffers and tables
   constexpr int CPW = KCH * 64 / kWaves;            // depthwise channels per wave
   constexpr int NBLK = CPW / 16;                    // in blocks of 16
-  constexpr int NL = row_loads(CPW, MT, NA);
-  constexpr int WS = NA | 1;                        // 16-byte units of a weight row in LDS (odd: 16 rows in different banks)
-  constexpr int NWL = (CPW * NA + 63) / 64;
-  static_assert(WS <= 8, "weights fit the wave's tile rows");
+  using Dw = DwSmall<CPW, MT, NA, RAGGED>;
+  static_assert(Dw::WS <= 8, "weights fit the wave's tile rows");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   Place at;
@@ -467,9 +620,9 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   // ---- everything is asked for; what only some launches have comes first, so that the waits for the rest stay exact
   uint32_t lut_word = 0;
   if (p.lut) lut_word = reinterpret_cast<const uint32_t*>(p.lut)[lane];
-  Consts<CPW> dc;
+  Dw dw;
   Consts<16 * NT> pc;
-  dc.load_bias(p.dbias, c_wave, lane);
+  dw.load_bias(p, c_wave, lane);
   pc.load_bias(at.bias, co_w, lane);
   // residual and output: lane -> row lane / 2 of the wave's 16 NT, unit lane % 2
   const int u_l = lane & 1, t_l = 16 * (g0 + u_l);
@@ -477,35 +630,9 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   const int64_t yrow = (int64_t)at.b * p.ybs + (int64_t)(co_w + (lane >> 1)) * p.ypitch;
   v4i rr = {0, 0, 0, 0};
   if (at.res && y_ok) rr = RAGGED && p.yragged ? load_row16(at.res + yrow, t_l, p.Tout) : *reinterpret_cast<const v4i*>(at.res + yrow + t_l);
-  v4i wr[NWL], xr[NL], tr = {0, 0, 0, 0};
-  uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
+  v4i tr = {0, 0, 0, 0};
   if (RAGGED || !at.proj) {
-    // weights: chunk L of the wave's CPW x NA
-    {
-      const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
-#pragma unroll
-      for (int j = 0; j < NWL; ++j) wr[j] = src[min(lane + 64 * j, CPW * NA - 1)];
-    }
-    dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
-    // rows: chunk L of the wave's CPW x units; chunks outside [0, Tin) are zero, the chunk a row ends in is masked
-    {
-      const int8_t* const xw = p.x + (int64_t)at.b * p.xbs + (int64_t)c_wave * p.xpitch;
-      const int t_last = p.Tin & ~15;
-#pragma unroll
-      for (int j = 0; j < NL; ++j) {
-        const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
-        const int t = 16 * (g0 + p.o16 + u);
-        const bool on = ch < CPW && t >= 0 && t < p.Tin;
-        if (on) in |= 1u << j;
-        if (t == t_last) last |= 1u << j;
-        xr[j] = (v4i){0, 0, 0, 0};
-        if (RAGGED) {
-          if (on) xr[j] = t == t_last ? load_row16(xw + ch * p.xpitch, t, p.Tin) : *reinterpret_cast<const unaligned_chunk16*>(xw + ch * p.xpitch + t);
-        } else if (64 * j < CPW * p.units) {          // (uniform; lanes without a chunk read the first one and drop it)
-          xr[j] = *reinterpret_cast<const v4i*>(xw + (on ? ch * p.xpitch + t : 0));
-        }
-      }
-    }
+    dw.load(p, at.b, g0, c_wave, lane);
   } else {                                          // the projection's tile: unit tid % 2 of row tid / 2
     if ((tid >> 1) < 64 * KCH && u_l < at.gn)
       tr = *reinterpret_cast<const v4i*>(p.x + (int64_t)at.b * p.xbs + (int64_t)(tid >> 1) * p.xpitch + t_l);
@@ -525,103 +652,17 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
 
   if (RAGGED || !at.proj) {
     // ---- depthwise half
-#pragma unroll
-    for (int j = 0; j < NWL; ++j) {
-      const int L = lane + 64 * j, ch = L / NA;
-      if (L < CPW * NA) *reinterpret_cast<v4i*>(wlds + 16 * (ch * WS + L - ch * NA)) = wr[j];
-    }
-#pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      v4i r = xr[j];
-      if (!RAGGED) {
-        if (!(in & (1u << j))) r = (v4i){0, 0, 0, 0};
-        if (last & (1u << j)) r = keep_bytes(r, p.Tin & 15);
-      }
-      if (lane + 64 * j < CPW * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = r;
-    }
-    asm volatile("" ::: "memory");                    // (lanes read what other lanes of the wave wrote: LDS is in order)
-    __builtin_amdgcn_sched_barrier(0);
-    const int ch_l = lane >> 2, n_l = lane & 3;
-    // Toeplitz row m = lane % 4 of four taps: bytes 4 - m .. 7 - m of (this dword, the one before)
-    const uint32_t sel = 0x07060504u - 0x01010101u * (uint32_t)n_l;
-    const unsigned char* const win = rows + ch_l * (16 * p.units) + 4 * (n_l + p.dwoff);
-    const unsigned char* const wrow = wlds + ch_l * (16 * WS);
-    constexpr int LA = 2, WQ = MT + LA;               // quads read ahead
-    uint32_t wd[NBLK][WQ][4];
-    v4i aq[NBLK][LA + 1];
-    uint32_t before[NBLK];
-    auto read_win = [&](int a) __attribute__((always_inline)) {
-#pragma unroll
-      for (int blk = 0; blk < NBLK; ++blk)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          wd[blk][a % WQ][i] = *reinterpret_cast<const uint32_t*>(win + 256 * blk * p.units + 16 * a + 4 * i);
-    };
-    auto read_taps = [&](int a) __attribute__((always_inline)) {
-#pragma unroll
-      for (int blk = 0; blk < NBLK; ++blk) aq[blk][a % (LA + 1)] = *reinterpret_cast<const v4i*>(wrow + 256 * blk * WS + 16 * a);
-    };
-#pragma unroll
-    for (int a = 0; a < LA; ++a) read_taps(a);
-#pragma unroll
-    for (int a = 0; a < MT + LA - 1; ++a) read_win(a);
+    dw.lay(p, rows, wlds, lane);
     v4i dacc[NBLK][MT];
-#pragma unroll
-    for (int blk = 0; blk < NBLK; ++blk) {
-      const int32_t db = dc.bias_of(16 * blk + ch_l);
-      before[blk] = 0;
-#pragma unroll
-      for (int q = 0; q < MT; ++q) dacc[blk][q] = (v4i){db, db, db, db};
-    }
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-      if (a + LA < NA) {
-        read_taps(a + LA);
-        read_win(a + MT + LA - 1);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t t[NBLK];
-#pragma unroll
-        for (int blk = 0; blk < NBLK; ++blk) {
-          const uint32_t d = (uint32_t)aq[blk][a % (LA + 1)][i];
-          t[blk] = __builtin_amdgcn_perm(d, before[blk], sel);
-          before[blk] = d;
-        }
-        if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
-#pragma unroll
-          for (int q = 0; q < MT; ++q)
-#pragma unroll
-            for (int blk = 0; blk < NBLK; ++blk)
-              dacc[blk][q] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)t[blk], (int)wd[blk][(a + q) % WQ][i], dacc[blk][q], 0, 0, 0);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    dw.template multiply<NBLK>(p, rows, wlds, lane, 0, dacc);
 #pragma unroll
     for (int kc = FIRST; kc < KC; ++kc) load_w(kc);
     // dword n_l of group q, row (channel) ch of the tile; the tile's unit q of a row sits in slot q ^ (row & 7)
+    const int ch_l = lane >> 2, n_l = lane & 3;
     const uint32_t tw = (uint32_t)((c_wave + ch_l) * 128 + 4 * n_l) | (uint32_t)((ch_l & 7) << 4);
-#pragma unroll
-    for (int blk = 0; blk < NBLK; ++blk) {
-      const int32_t m = dc.m(16 * blk + ch_l), s = dc.s(16 * blk + ch_l);
-      auto finish = [&](auto fast_tag, auto relu_tag) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < MT; ++q) {
-          const int32_t a4[4] = {dacc[blk][q][0], dacc[blk][q][1], dacc[blk][q][2], dacc[blk][q][3]};
-          uint32_t pk;
-          if constexpr (decltype(fast_tag)::value)
-            pk = requant_short4<false, decltype(relu_tag)::value>(a4, m, s - 32, 1 << ((s - 33) & 31), 0u);
-          else
-            pk = requant_pack4<false, false>(a4, m, s, 0, 0u, p.drelu ? 0 : -128, 127);
-          if (p.lut) pk = through_table(lut, pk);
-          *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
-        }
-      };
-      if (!__all(s >= kShortMin && s <= kShortMax)) finish(std::false_type{}, std::false_type{});
-      else if (p.drelu) finish(std::true_type{}, std::true_type{});
-      else finish(std::true_type{}, std::false_type{});
-    }
+    dw.template finish<NBLK>(p, lut, lane, 0, dacc, [&](int blk, int q, uint32_t pk) __attribute__((always_inline)) {
+      *reinterpret_cast<uint32_t*>(xs + 16 * 128 * blk + (tw ^ (uint32_t)(q << 4))) = pk;
+    });
   } else {
     const int row = tid >> 1;
     if (row < 64 * KCH) *reinterpret_cast<v4i*>(xs + row * 128 + ((u_l ^ (row & 7)) << 4)) = tr;

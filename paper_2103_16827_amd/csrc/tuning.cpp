@@ -43,6 +43,9 @@ Tuning read_env() {
   }
   t.no_pw_multi = getenv("QASR_NO_PW_MULTI") != nullptr;
   t.pw_multi_force = getenv("QASR_PW_MULTI") != nullptr;
+  t.no_pw_chain = getenv("QASR_NO_PW_CHAIN") != nullptr;
+  t.pw_chain_force = getenv("QASR_PW_CHAIN") != nullptr;
+  if (const char* e = getenv("QASR_CHAIN_MT")) t.chain_mt = atoi(e);
   t.no_sep = getenv("QASR_NO_SEP") != nullptr;
   t.no_pw_wide = getenv("QASR_NO_PW_WIDE") != nullptr;
   t.pw_wide_force = getenv("QASR_PW_WIDE") != nullptr;

@@ -18,6 +18,8 @@
 //                                           (default 4; 0 = the caller's slots are the buffers)
 //   QASR_NO_PW_WIDE, QASR_PW_WIDE            pw_wide: never / wherever it can
 //   QASR_NO_PW_MULTI, QASR_PW_MULTI         encoder: several pointwise layers in one launch: never / wherever possible
+//   QASR_NO_PW_CHAIN, QASR_PW_CHAIN         encoder: chains of pointwise layers in one launch: never / wherever possible
+//   QASR_CHAIN_MT                           the same: groups per tile
 //   QASR_PWW = "MT,KS"                      pw_wide: groups per tile, wave groups over the input channels (0: free)
 //   QASR_NO_SEP                             encoder: no depthwise + pointwise pair in one launch
 //   QASR_SEP = "MT,NT[,KS]"                 the same: groups per tile, 16-channel columns per wave (0: free), wave groups over
@@ -29,13 +31,13 @@
 namespace qasr {
 
 struct Tuning {
-  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false, no_sep = false, no_pw_wide = false, pw_wide_force = false, no_conv_few = false, conv_few_force = false, no_pw_multi = false, pw_multi_force = false;
+  bool no_pw_pipe = false, no_conv_pipe = false, team = false, cp_plain_order = false, no_pw_lean = false, pw_lean_force = false, pw_lean_no_res = false, pwp_nopipe = false, no_sep = false, no_pw_wide = false, pw_wide_force = false, no_conv_few = false, conv_few_force = false, no_pw_multi = false, pw_multi_force = false, no_pw_chain = false, pw_chain_force = false;
   int pwp_mt = 0, pwp_split = 0;
   int dwp_r = 0, dwp_s = 0;
   int dw_r = 0;
   int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0, cf_mt = 0, cf_wc = 0;
   int pwt_mt = 0;
-  int sep_mt = 0, sep_nt = 0, sep_ks = 0, pww_mt = 0, pww_ks = 0;
+  int sep_mt = 0, sep_nt = 0, sep_ks = 0, pww_mt = 0, pww_ks = 0, chain_mt = 0;
   int slot_depth = 4;
 };
 

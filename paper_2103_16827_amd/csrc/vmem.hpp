@@ -91,6 +91,15 @@ __device__ __forceinline__ int32_t gload_i8(const void* p) {   // one sign-exten
   asm volatile("global_load_sbyte %0, %1, off" : "=v"(r) : "v"(p) : "memory");
   return r;
 }
+// Into a register that is the caller's, who also waits: one of a ring that lives on from block to block stays in place, and a
+// function that only asks can end before the data is there.
+template <int OFF>
+__device__ __forceinline__ void gload16_into(v4i& r, const void* base, uint32_t off) {
+  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "+v"(r) : "v"(off), "s"(base), "n"(OFF) : "memory");
+}
+__device__ __forceinline__ void gload4_into(int32_t& r, const void* p) {
+  asm volatile("global_load_dword %0, %1, off" : "+v"(r) : "v"(p) : "memory");
+}
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
