@@ -300,7 +300,10 @@ size_t qasr_encoder_workspace_bytes(const qasr_encoder* e);
  * Enqueues at most n_ops kernels (plus one per activation, plus one where contractions are split)
  * and returns; allocates nothing; may be captured into a HIP graph.  A depthwise layer and the pointwise layer that is the only
  * reader of its output run as one launch where their shapes allow (same bits), and with them a pointwise layer
- * of the pair's input just before it, whose output neither of them reads. */
+ * of the pair's input just before it, whose output neither of them reads; so do consecutive pointwise layers of which each is the
+ * only reader of the one before, from such a pair on or by themselves, where that is the faster way.
+ * y may overlap x if the last op does not read slot 0: layers of which one reads x and the last writes y then keep
+ * launches of their own. */
 qasr_status qasr_encoder_forward(const qasr_encoder* e, const int8_t* x, int8_t* y,
                                  void* workspace, size_t workspace_bytes, void* stream);
 
@@ -361,7 +364,7 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
 /* Number of ops, and the name of the kernel family op i belongs to by its shape (depthwise:
  * "dw_pipe", "dw_mfma"; pointwise: "pw_pipe", "pw_tile"; dense and any other pointwise shape:
  * "conv_pipe", "gemm_mfma"; any shape: "conv_generic"; static storage, NULL if i is out of range).
- *   qasr_encoder_op_launch: what qasr_encoder_forward launches for it over 16-byte aligned x and y:
+ *   qasr_encoder_op_launch: what qasr_encoder_forward launches for it over 16-byte aligned x and y that do not overlap:
  *     the op that the launch begins with (i; i - 1 where op i is the pointwise half of a depthwise +
  *     pointwise pair; one less for a pair that runs together with the pointwise layer before it, a residual
  *     projection of the same tensor; the first of consecutive pointwise layers of equal output shape that run

@@ -1125,8 +1125,17 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     return QASR_ERR_WORKSPACE;
   int8_t* ws = (int8_t*)workspace;
   const size_t n = e->ops.size();
+  // y may lie over x, which is read before the last op begins: such a call gets no launch whose tiles would write y while others of
+  // it still read x
+  const bool y_over_x = overlaps(x, e->in_rows * (e->in_T + xpad), y, e->out_rows * (e->out_T + ypad));
+  auto keeps_apart = [&](size_t first, size_t count) {
+    if (!y_over_x || first + count != n) return false;
+    for (size_t j = first; j + 1 < n; ++j)
+      if (e->ops[j].in_slot == 0 || e->ops[j].res_slot == 0) return true;
+    return false;
+  };
   // (the team kernel's loads want 16-byte aligned tensors, like the kernels it replaces)
-  const bool use_team = how.team && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);
+  const bool use_team = how.team && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0) && !y_over_x;
   // room for the partial sums of split contractions, and their counters (zero between layers from here on)
   split = split && e->ws_bytes > e->split_off;
   const size_t split_bytes = split ? e->ws_bytes - e->split_off - round256(4 * qasr::kConvSplitCounters) : 0;
@@ -1176,7 +1185,7 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
         }
         ConvParams d = p;
         d.act_lut = op.act_table;
-        if (qasr::pw_chain_better(from_dw ? &d : nullptr, c, cn)) {
+        if (!keeps_apart(i, (size_t)(cn + from_dw)) && qasr::pw_chain_better(from_dw ? &d : nullptr, c, cn)) {
           const hipError_t ce = qasr::launch_pw_chain(from_dw ? &d : nullptr, op.sep_img, c, cn, st);
           if (ce != hipSuccess) return hip_status(ce);
           i += (size_t)(cn + from_dw) - 1;
@@ -1200,7 +1209,7 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
       bind(i + 1, d);
       bind(i + 2, q);
       d.act_lut = e->ops[i + 1].act_table;
-      if (projection_with_pair(p, d, q)) {
+      if (!keeps_apart(i, 3) && projection_with_pair(p, d, q)) {
         const hipError_t se = qasr::launch_sep(d, e->ops[i + 1].sep_img, q, p, st);
         if (se != hipSuccess) return hip_status(se);
         i += 2;
@@ -1211,7 +1220,7 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
       ConvParams q;
       bind(i + 1, q);
       p.act_lut = op.act_table;                  // (of the activation between the two)
-      if (qasr::sep_supported(p, q)) {
+      if (!keeps_apart(i, 2) && qasr::sep_supported(p, q)) {
         const hipError_t se = qasr::launch_sep(p, op.sep_img, q, st);
         if (se != hipSuccess) return hip_status(se);
         ++i;
