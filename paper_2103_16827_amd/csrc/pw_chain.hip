@@ -421,15 +421,23 @@ bool pw_chain_supported(const ConvParams* dw, const ChainOp* op, int n) {
   return plan(dw, op, n, 256, pl);
 }
 
-// The chain's time, a fixed part and the stream (blocks of 256 KiB) per round of workgroups, against its layers' by pw_wide's
-// model.  On 19 sizes from 1 x 32 to 64 x 400 frames of Conformers with and without activations and of four kinds of pointwise
-// chains, as measured: what the rule takes runs in 0.57 to 0.97 of the time of separate launches, one case in 1.05 (1024 ->
-// 1024 -> 1024 at 12 x 400); what it leaves would have, up to 0.76 (512 -> 2048 -> 512 at 9 x 400, whose separate launches take longer
-// than their model says).  Beyond 512 groups the chain needs a second round, 1.0 to 1.4 of the separate launches.
+// The chain's time, a fixed part and the stream (blocks of 256 KiB), against its layers' by pw_wide's model.  It takes launches
+// whose workgroups run at once, one per unit: 256 tiles, which a batch item's frames begin anew (20 x 400 frames are 260 of two
+// groups); a second round streams all weights again, 1.03 to 1.6 of the separate launches.  Rows of more than 512 channels are not
+// written under the last pass, 1 us per 512 more (512 -> 512 -> 1024 at 4 x 800 frames 12.8 us as a chain, 12.2 apart); where a
+// chain of two layers, which saves one launch only, has two groups per workgroup, 2 beyond 1024 (512 -> 512 -> 2048 at 16 x 512
+// 21.7 / 20.4), and half a us per 512 more that come in before the first product (2048 -> 512 -> 512 there 20.7 / 18.5).  Over
+// odd rows at either end the separate layers take longer than their model by more than that (512 -> 512 -> 1024 at 4 x 799 frames
+// 16.3 / 21.0), from about 50 groups on (512 -> 512 -> 512 -> 1024 at 1 x 104, 7 groups, 17.0 / 15.4).
+// Both sides at 23 sizes of Conformers with and without activations, 16 sizes of 27 kinds of chains and 9 odd ones of 8,
+// profiles/merged_launches.txt: what the rule takes runs in 0.56 to 1.00 of the time of separate launches, one case of exactly 256
+// workgroups in 1.02 (1024 -> 512 -> 512 at 1 x 4096); what it leaves would have, up to 0.79
+// (512 -> 512 -> 512 at 1 x 400, whose stream is shorter than its fixed part says) and over odd rows 0.58 (512 -> 2048 -> 512 at 16 x 399).
 bool pw_chain_better(const ConvParams* dw, const ChainOp* op, int n) {
   Plan pl;
   if (!plan(dw, op, n, 256, pl)) return false;
   if (tuning().pw_chain_force) return true;
+  if (pl.wgs > 256) return false;
   double blocks = 0.0, apart = dw ? 2.0 : 0.0;
   for (int i = 0; i < n; ++i) {
     double us;
@@ -437,8 +445,13 @@ bool pw_chain_better(const ConvParams* dw, const ChainOp* op, int n) {
     blocks += (double)op[i].p.Cin * op[i].p.Cout / (256 * 1024);
     apart += us + 1.2 + (op[i].glu ? 3.2 : 0.0);
   }
-  const double round = (pl.MT == 1 ? 7.0 + 2.05 * blocks : 7.5 + 2.2 * blocks) + (dw ? 2.0 : 0.0);
-  return (double)((pl.wgs + 255) / 256) * round < apart;
+  const double out = ((op[n - 1].glu ? op[n - 1].p.Cout / 2 : op[n - 1].p.Cout) - 512) / 512.0, in = (op[0].p.Cin - 512) / 512.0;
+  const bool two = n == 2 && pl.MT == 2;
+  const ConvParams &f = op[0].p, &e = op[n - 1].p;
+  const bool odd = pl.wgs * pl.MT >= 48 && ((!dw && ragged(f.Tin + f.xpad, f.xbs, f.x)) || ragged(e.Tout + e.ypad, e.ybs, e.y));
+  const double rows = odd ? 0.0 : two ? (out > 1.0 ? 2.0 * out - 1.0 : out) + 0.5 * in : out;
+  const double chain = (pl.MT == 1 ? 7.0 + 2.05 * blocks : 7.5 + 2.2 * blocks) + (dw ? 2.0 : 0.0) + rows;
+  return chain < apart;
 }
 
 hipError_t launch_pw_chain(const ConvParams* dw, const uint32_t* img, const ChainOp* op, int n, hipStream_t st) {
