@@ -62,27 +62,105 @@ def _registers(operands: str):
     return regs
 
 
-def ring_copies(asm_text: str):
-    """(kernel, instruction) for every copy, between a kernel's first and last matrix product, out of a register that a
-    hand-issued 16-byte load further up fills.  To the compiler such a register holds its value from the `asm` statement on, so it
-    may move it while the load is on its way (it has, where it indexed a ring at run time): the copy is then
-    what was there before, and the data lands in a register that belongs to something else."""
-    bad = []
+def _kernels(asm_text: str):
+    """(name, instructions, successors) of every function in device assembly: each instruction with whether an `asm` statement
+    put it there, and the indexes of those that can run right after it."""
     for part in re.split(r"\n(?=_Z\w+:)", asm_text)[1:]:
-        ins, by_hand = [], False
+        ins, at, by_hand = [], {}, False
         for line in part.split(".Lfunc_end")[0].splitlines()[1:]:
             line = line.strip()
-            if "#ASMSTART" in line or "#ASMEND" in line:
+            label = re.match(r"(\.L\w+):", line)
+            if label:
+                at[label.group(1)] = len(ins)
+            elif "#ASMSTART" in line or "#ASMEND" in line:
                 by_hand = "#ASMSTART" in line
             elif line and line[0] not in ";." and not line.endswith(":"):
                 ins.append((line.split(";")[0].strip(), by_hand))
+        after = []
+        for i, (text, _) in enumerate(ins):
+            jump = re.match(r"s_(c?branch)\w*\s+(\.L\w+)", text)
+            nxt = [] if text.startswith("s_endpgm") or (jump and jump.group(1) == "branch") else [i + 1]
+            after.append([j for j in nxt + ([at[jump.group(2)]] if jump else []) if j < len(ins)])
+        yield part.split(":")[0], ins, after
+
+
+def _reached(starts, after):
+    """Indexes that can run after one of `starts` has."""
+    seen, todo = set(), [j for i in starts for j in after[i]]
+    while todo:
+        i = todo.pop()
+        if i not in seen:
+            seen.add(i)
+            todo += after[i]
+    return seen
+
+
+def _copies_out_of(text: str):
+    """Registers that an instruction copies from (none if it is no copy)."""
+    return _registers(text.partition(",")[2]) if re.match(r"v_(mov|accvgpr|swap|pk_mov)", text) else set()
+
+
+def ring_copies(asm_text: str):
+    """(kernel, instruction) for every copy, after one matrix product and before another on some path, out of a register that a
+    hand-issued 16-byte load fills which can have run before, further up or an iteration earlier.  To the compiler such a
+    register holds its value from the `asm` statement on, so it may move it while the load is on its way (it has, where it indexed a ring at run time): the copy is then
+    what was there before, and the data lands in a register that belongs to something else."""
+    bad = []
+    for name, ins, after in _kernels(asm_text):
         products = [i for i, (text, _) in enumerate(ins) if text.startswith("v_mfma")]
-        ring = set()
-        for i, (text, by_hand) in enumerate(ins[:products[-1]] if products else []):
+        before = [[] for _ in ins]
+        for i, nxt in enumerate(after):
+            for j in nxt:
+                before[j].append(i)
+        between = _reached(products, after) & _reached(products, before)
+        ring = {}                                     # register -> its loads
+        for i, (text, by_hand) in enumerate(ins):
             if by_hand and re.match(r"(global|buffer)_load_dwordx4 ", text):
-                ring |= _registers(text.split(",")[0])
-            elif i > products[0] and re.match(r"v_(mov|accvgpr|swap|pk_mov)", text) and _registers(text.partition(",")[2]) & ring:
-                bad.append((part.split(":")[0], text))
+                for r in _registers(text.split(",")[0]):
+                    ring.setdefault(r, []).append(i)
+        later = {}                                    # ... -> what can run after one of them
+        for i in sorted(between):
+            for r in _copies_out_of(ins[i][0]) & set(ring):
+                if r not in later:
+                    later[r] = _reached(ring[r], after)
+                if i in later[r]:
+                    bad.append((name, ins[i][0]))
+                    break
+    return bad
+
+
+def copies_in_flight(asm_text: str):
+    """(kernel, instruction) for every copy out of a register whose hand-issued load (of any size) need not have completed on
+    some path, wherever in the kernel it stands.  Loads complete in the order of their requests: one is complete after
+    `vmcnt(N)` if at least N requests came after it."""
+    bad = []
+    for name, ins, after in _kernels(asm_text):
+        state = [None] * len(ins)                     # at each instruction: register -> fewest requests after its load
+        todo = [0] if ins else []
+        if ins:
+            state[0] = {}
+        while todo:
+            i = todo.pop()
+            text, by_hand = ins[i]
+            out = dict(state[i])
+            wait = re.match(r"s_waitcnt\b.*vmcnt\((\d+)\)", text)
+            if wait:
+                out = {r: n for r, n in out.items() if n < int(wait.group(1))}
+            if re.match(r"v_|(ds|global|buffer|flat|scratch)_(read|load)", text) and not by_hand:
+                for r in _registers(text.split(",")[0]):   # (another value from here on)
+                    out.pop(r, None)
+            if re.match(r"(global|buffer|flat|scratch)_(load|store|atomic)", text):
+                out = {r: min(n + 1, 63) for r, n in out.items()}
+                if by_hand and "_load_" in text and "_lds_" not in text:
+                    out.update(dict.fromkeys(_registers(text.split(",")[0]), 0))
+            for j in after[i]:
+                new = dict(state[j] or {})
+                for r, n in out.items():
+                    new[r] = min(n, new.get(r, 63))
+                if new != state[j]:
+                    state[j] = new
+                    todo.append(j)
+        bad += [(name, text) for i, (text, _) in enumerate(ins) if state[i] and _copies_out_of(text) & set(state[i])]
     return bad
 
 
@@ -162,7 +240,7 @@ def build(verbose: bool = False) -> str:
         with open(asm) as f:
             text = f.read()
         for what, bad in (("register read right after a partial write", partial_write_hazards(text)),
-                          ("copy of a register whose load may be on its way", ring_copies(text))):
+                          ("copy of a register whose load may be on its way", ring_copies(text) or copies_in_flight(text))):
             if bad:
                 if os.path.exists(LIB):
                     os.remove(LIB)

@@ -392,3 +392,50 @@ def test_build_refuses_copies_out_of_a_ring_of_loads():
     assert ring_copies(kernel("\tv_mov_b32_e32 v9, v20", "\tv_mov_b32_e32 v20, v12")) == []
     for copy in ("v_mov_b32_e32 v20, v11", "v_mov_b64_e32 v[20:21], v[10:11]", "v_accvgpr_write_b32 a0, v8"):
         assert ring_copies(kernel("\t" + copy)) == [("_Z1kv", copy)]
+
+
+def _assembly(*lines):
+    return "\t.text\n_Z1kv:\n" + "\n".join(l if l[0] in ";." else "\t" + l for l in lines) + "\n.Lfunc_end0:\n"
+
+
+def _by_hand(load):
+    return ";;#ASMSTART", load, ";;#ASMEND"
+
+
+RING, MFMA = "global_load_dwordx4 v[8:11], v1, s[2:3]", "v_mfma_i32_16x16x64_i8 v[0:3], v[4:7], v[8:11], v[0:3]"
+
+
+def test_build_refuses_copies_that_a_loop_brings_after_the_load():
+    """At a loop's top out of what a request at its bottom fills; not out of registers that are only set there, before any request."""
+    from paper_2103_16827_amd.build import ring_copies
+    copy = "v_mov_b32_e32 v30, v8"
+    loop = (".LBB0_1:", copy, MFMA, *_by_hand(RING), "s_cbranch_scc1 .LBB0_1")
+    assert ring_copies(_assembly(MFMA, *loop, MFMA, "s_endpgm")) == [("_Z1kv", copy)]
+    assert ring_copies(_assembly(*loop, "s_endpgm")) == [("_Z1kv", copy)]          # the last product is the loop's own
+    # products, then the ring set to zero, then the loop that fills it
+    zero = ("v_mov_b32_e32 v8, 0", "v_mov_b32_e32 v9, v8")
+    rest = (*_by_hand(RING), ".LBB0_2:", MFMA, *_by_hand(RING), "s_cbranch_scc1 .LBB0_2", MFMA, "s_endpgm")
+    assert ring_copies(_assembly(MFMA, *zero, *rest)) == []
+    assert ring_copies(_assembly(".LBB0_1:", MFMA, *zero, "s_cbranch_scc0 .LBB0_1", *rest)) == []
+    assert ring_copies(_assembly(".LBB0_1:", MFMA, *zero, *_by_hand(RING), MFMA, "s_cbranch_scc0 .LBB0_1", "s_endpgm")) == [("_Z1kv", zero[1])]
+
+
+def test_build_refuses_copies_of_what_has_not_been_waited_for():
+    """Before the first product too, and out of registers that smaller requests fill; waits count the requests after a load."""
+    from paper_2103_16827_amd.build import copies_in_flight
+    word, copy = "global_load_dword v20, v[2:3], off", "v_mov_b32_e32 v30, v20"
+    other = "global_load_lds_dwordx4 v[4:5], off"
+    in_flight = [("_Z1kv", copy)]
+    assert copies_in_flight(_assembly(*_by_hand(word), copy, "s_endpgm")) == in_flight
+    assert copies_in_flight(_assembly(*_by_hand(word), "s_waitcnt vmcnt(0)", copy, "s_endpgm")) == []
+    assert copies_in_flight(_assembly(*_by_hand(word), other, other, "s_waitcnt vmcnt(2) lgkmcnt(0)", copy, "s_endpgm")) == []
+    assert copies_in_flight(_assembly(*_by_hand(word), other, other, "s_waitcnt vmcnt(3)", copy, "s_endpgm")) == in_flight
+    # one request is skipped on some path
+    skipped = (*_by_hand(word), other, "s_cbranch_execz .LBB0_1", other, ".LBB0_1:")
+    assert copies_in_flight(_assembly(*skipped, "s_waitcnt vmcnt(1)", copy, "s_endpgm")) == []
+    assert copies_in_flight(_assembly(*skipped, "s_waitcnt vmcnt(2)", copy, "s_endpgm")) == in_flight
+    # over a loop's back edge
+    assert copies_in_flight(_assembly(".LBB0_1:", copy, *_by_hand(word), "s_cbranch_scc1 .LBB0_1", "s_endpgm")) == in_flight
+    # another value in the register, a load that the compiler waits for by itself
+    assert copies_in_flight(_assembly(*_by_hand(word), "v_mov_b32_e32 v20, 0", copy, "s_endpgm")) == []
+    assert copies_in_flight(_assembly(word, copy, "s_endpgm")) == []
