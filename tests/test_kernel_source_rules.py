@@ -5,7 +5,8 @@ wave from ending, or a function from returning into code that reuses the registe
 rows, while such a load is still in flight.  The rules checked here, on the text of the sources:
 
   1. every function that issues such loads reaches `wait_vm<0>()` after its last request, and no
-     `return` between the first request and the end comes without one;
+     `return` between the first request and the end comes without one; functions that only ask, for the caller's registers,
+     are named (ASKS), and a call of one counts as a request of its caller;
   2. those sources never read a layer operand through a plain dereference (`p.m[c]`, `*p.bias`):
      a load the compiler does see makes it wait for everything outstanding, and a hand count that
      was right becomes a stall (or, with its registers reassigned, wrong data).
@@ -16,7 +17,10 @@ import re
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2103_16827_amd", "csrc")
 
-LOADS = r"\b(?:direct_load16_scope\s*<[^>]*>|direct_load16_dev|direct_load16|direct_load4|gload16|gload4|gload_i8|bload16)\s*\("
+# functions that leave what they ask for on its way (a kernel's ring, its constants): pw_chain.hip, sep_body.hpp
+ASKS = ("load_step", "load_steps", "items", "load_by_hand")
+LOADS = (r"\b(?:direct_load16_scope\s*<[^>]*>|direct_load16_dev|direct_load16|direct_load4|gload16|gload4|gload_i8|bload16"
+         r"|gload16_into\s*<[^;]*?>|gload4_into|(?:load_step|load_steps|items)\s*<[^;()]*>|load_by_hand)\s*\(")
 WAIT0 = r"\bwait_vm\s*<\s*0\s*>\s*\(\s*\)"
 OPERANDS = r"(?:bias|m|s|w|x|res|act_lut)"
 
@@ -113,29 +117,56 @@ def function_returns(body):
 def test_the_splitter_sees_the_kernels():
     src = sources()
     names = {n for t in src.values() for n, _ in functions(t)}
-    for want in ("pw_pipe_kernel", "pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel", "team_kernel", "conv_pipe_kernel", "conv_few_kernel"):
+    for want in ("pw_pipe_kernel", "pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel", "team_kernel", "conv_pipe_kernel", "conv_few_kernel", "pw_chain_kernel", *ASKS):
         assert want in names, (want, sorted(names))
+
+
+def undrained(name, body):
+    """What is wrong with a function that issues hand-counted loads, or None (False: it issues none)."""
+    loads = [m.start() for m in re.finditer(LOADS, body)]
+    if not loads:
+        return False
+    waits = [m.start() for m in re.finditer(WAIT0, body)]
+    if name in ASKS:
+        return "a return where only requests are made" if function_returns(body) else None
+    if not (waits and waits[-1] > loads[-1]):
+        return "no wait_vm<0>() after its last request"
+    for r in function_returns(body):
+        before = [q for q in loads if q < r]
+        if before and not any(before[-1] < w < r for w in waits):    # (else it leaves before anything was requested)
+            return "a return after a request without wait_vm<0>() in between"
+    return None
 
 
 def test_every_function_with_hand_counted_loads_drains_them_before_it_ends():
     checked = []
     for fname, text in sources().items():
         for name, body in functions(text):
-            loads = [m.start() for m in re.finditer(LOADS, body)]
-            if not loads:
-                continue
-            waits = [m.start() for m in re.finditer(WAIT0, body)]
-            assert waits and waits[-1] > loads[-1], f"{fname}:{name}: no wait_vm<0>() after its last request"
-            for r in function_returns(body):
-                if r < loads[0]:
-                    continue              # leaves before anything was requested
-                before = [q for q in loads if q < r]
-                assert any(before[-1] < w < r for w in waits), \
-                    f"{fname}:{name}: a return after a request without wait_vm<0>() in between"
-            checked.append(f"{fname}:{name}")
+            wrong = undrained(name, body)
+            assert not wrong, f"{fname}:{name}: {wrong}"
+            if wrong is None:
+                checked.append(f"{fname}:{name}")
     # the kernels known to use the wrappers are all among the checked ones
-    for want in ("pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel", "conv_pipe_kernel", "conv_few_kernel"):
+    for want in ("pw_pipe_tile", "dw_pipe_kernel", "pw_tile_kernel", "conv_pipe_kernel", "conv_few_kernel", "pw_chain_kernel", *ASKS):
         assert any(c.endswith(":" + want) for c in checked), checked
+
+
+def test_requests_into_the_callers_registers_are_seen():
+    """Every wrapper of vmem.hpp counts as a request, and a function that only asks and is not known to is refused."""
+    vmem = strip_comments(open(os.path.join(CSRC, "vmem.hpp")).read())
+    asks = [n for n, body in functions(vmem) if re.search(r"(?:global|buffer)_load", body) or n.startswith("direct_load")]
+    assert {"gload16_into", "gload4_into", "gload16", "direct_load4"} <= set(asks)
+    for n in asks:
+        call = f"{n}<{'true' if 'scope' in n else 'I * 8'}>(r, p);" if n in ("gload16_into", "direct_load16_scope") else f"{n}(r, p);"
+        assert re.search(LOADS, call), n
+    (name, body), = functions("template <int I> __device__ void other(v4i& r) { gload16_into<(I & 3) * 1024>(r, p, o); }")
+    assert undrained(name, body) and undrained("load_step", body) is None
+    assert undrained("load_step", "{ if (a) return; gload4_into(r, p); }")
+    # ... and what asks through one that is known to
+    assert undrained("k", "{ load_steps<0, D / 2>(wb, w0, w1, wlane); }") and undrained("k", "{ items<MT, true, 0>(acc, wb, ar, a0, n, w0, w1, l); }")
+    (kernel,) = [b for n, b in functions(sources()["pw_chain.hip"]) if n == "pw_chain_kernel"]
+    assert undrained("pw_chain_kernel", kernel) is None
+    assert undrained("pw_chain_kernel", kernel.replace("wait_vm<0>();", ""))
 
 
 def test_the_checker_catches_a_missing_drain():
