@@ -376,10 +376,11 @@ qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, i
 int32_t qasr_encoder_num_ops(const qasr_encoder* e);
 const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i);
 int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** kernel);
-/* 1 if op i's activation (qasr_op.act) is applied inside the layer's own kernel over 16-byte aligned x and
- * y (a unary activation after a layer that pw_pipe, pw_wide or dw_pipe runs, through a 256-entry table of
- * the activation's int8 outputs built at create time), 0 if it runs as the separate in-place pass or
- * the op has none; -1 if i is out of range.  Same bits either way.  (In a pair it always is, in a chain a GLU too.) */
+/* About op i as a launch of its own (qasr_encoder_forward_layerwise): 1 if its activation (qasr_op.act) is applied inside the
+ * layer's kernel over 16-byte aligned x and y (a unary activation after a layer that pw_pipe, pw_wide or dw_pipe runs, through a
+ * 256-entry table of the activation's int8 outputs built at create time), 0 if it runs as the separate in-place pass or the op has
+ * none; -1 if i is out of range.  In a pair or a chain (qasr_encoder_op_launch: "sep", "pw_chain") every activation, GLUs too, is
+ * applied in that launch, whatever this says.  Same bits either way. */
 int32_t qasr_encoder_op_act_fused(const qasr_encoder* e, int32_t i);
 
 /* Runs of layers in one launch (EXPERIMENTAL: only with QASR_TEAM set in the environment when the

@@ -728,9 +728,9 @@ def test_conformer_shaped_batch16_with_integer_activations():
 
 
 def test_which_activations_run_inside_the_layer_kernel():
-    """Swish after the 512 -> 2048 layers and after the depthwise convolutions goes through the
-    producing kernel's epilogue table; the GLU keeps the separate in-place pass (the parity test
-    above covers both routes: it runs this very encoder)."""
+    """Layer by layer, Swish after the 512 -> 2048 layers and after the depthwise convolutions goes through the
+    producing kernel's epilogue table; the GLU keeps the separate in-place pass.  (The parity test above runs
+    this encoder in chains, which apply all three; test_pw_chain_gpu.py runs it without them.)"""
     net = W.build_config(5)
     g = GpuNet(net, W.draw_net_params(net, 1))
     kinds = {}
