@@ -3,6 +3,7 @@ odd frame counts, tiles without their second group, bias and relu, both forms of
 where a chain may not be formed."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import qasr_workloads as W
@@ -142,3 +143,180 @@ def test_the_library_chooses_chains_for_a_conformer():
     net = W.conformer_shaped(16, 400, 4, layers=2, nonlinear=True)
     check(net, {"L0.ffn1": ("L0.ffn1", "pw_chain"), "L0.pw1": ("L0.ffn1", "pw_chain"), "L0.dw": ("L0.dw", "pw_chain"),
                 "L1.pw1": ("L0.dw", "pw_chain"), "L1.pw2": ("L1.dw", "sep")})
+
+
+def test_activations_in_separate_launches(tuning_env):
+    """The Conformer whose layers the library runs as chains, without them: Swish in the layers' epilogues, GLU in place."""
+    tuning_env("QASR_NO_PW_CHAIN", "1")
+    net = W.conformer_shaped(16, 400, 4, layers=2, nonlinear=True)
+    check(net, {o.name: (o.name if not o.name.endswith("pw2") else o.name[:-3] + "dw", None) for o in net.ops})
+
+
+def test_chains_apply_what_layers_by_themselves_do_apart():
+    net = W.conformer_shaped(16, 400, 4, layers=2, nonlinear=True)
+    g = GpuNet(net, W.draw_net_params(net, 1))
+    seen = {(o.act, g.enc.op_launch(i)[1], g.enc.op_act_fused(i)) for i, o in enumerate(net.ops) if o.act}
+    assert seen >= {(ACT_GLU, "pw_chain", False), (ACT_SWISH, "pw_chain", True)}
+    g.enc.close()
+
+
+@pytest.mark.parametrize("s", [20, 33, 62])
+@pytest.mark.parametrize("relu", [True, False])
+def test_relu_and_rescales_of_the_depthwise_layer(s, relu, tuning_env):
+    """Its epilogue's three forms; the other layers keep theirs."""
+    tuning_env(FORCE, "1")
+    net = conformer_tail(2, 45, 31, False)
+    net.ops[1].flags = 1 if relu else 0
+    params = W.draw_net_params(net, 4)
+    params[1]["s"] = np.full_like(params[1]["s"], s)
+    if s == 20:
+        params[1]["m"] = params[1]["m"] >> 18            # (codes over the whole range, not two)
+    x = W.draw_input(net, 4)
+    ref, outs = oracle.encoder_forward(net, params, x, keep=True)
+    assert s == 62 or len(np.unique(outs[1])) > 16
+    g = GpuNet(net, params)
+    assert g.enc.op_launch(1) == (1, "pw_chain")
+    assert np.array_equal(g.forward(dev(x)).cpu().numpy(), ref)
+    g.check_guards()
+    g.enc.close()
+
+
+@pytest.mark.parametrize("B,T", [(1, 16 * 300), (3, 16 * 100 - 5)])
+def test_more_tiles_than_units(B, T, tuning_env):
+    """A second round of workgroups, which only a forced chain has."""
+    tuning_env(FORCE, "1")
+    tuning_env("QASR_CHAIN_MT", "1")
+    check(pointwise(B, T, (512, 512, 512)), {"p1": ("p0", "pw_chain")})
+
+
+def to_the_output(B, T, k=31):
+    b = _Builder("to_the_output", 91, B, 512, T)
+    b.op("in", 512, relu=False)
+    b.op("dw", 512, k=k, groups=512, relu=False)
+    b.op("pw", 512)
+    b.op("up", 1024, relu=False)
+    return b.done()
+
+
+@pytest.mark.parametrize("MT", ["1", "2"])
+@pytest.mark.parametrize("B,T", [(1, 61), (2, 100), (3, 16), (2, 33)])
+def test_from_a_depthwise_layer_to_the_output(B, T, MT, tuning_env):
+    tuning_env(FORCE, "1")
+    tuning_env("QASR_CHAIN_MT", MT)
+    check(to_the_output(B, T), {"dw": ("dw", "pw_chain"), "up": ("dw", "pw_chain")})
+
+
+@pytest.mark.parametrize("net", [lambda: pointwise(2, 48, (512, 1024, 512)), lambda: pointwise(2, 37, (512, 1024, 512)),
+                                 lambda: to_the_output(2, 48), lambda: to_the_output(2, 61)])
+@pytest.mark.parametrize("dx,dy", [(1, 0), (0, 1), (3, 5), (16, 4)])
+def test_input_and_output_at_any_address(net, dx, dy, tuning_env):
+    tuning_env(FORCE, "1")
+    net = net()
+    params = W.draw_net_params(net, 8)
+    x = W.draw_input(net, 8)
+    ref = oracle.encoder_forward(net, params, x)
+    g = GpuNet(net, params)
+    xr = torch.full((x.size + dx,), 9, dtype=torch.int8, device="cuda")
+    yr = torch.full((ref.size + dy + 64,), 9, dtype=torch.int8, device="cuda")
+    xr[dx:] = dev(x).reshape(-1)
+    y = yr[dy:dy + ref.size]
+    g.enc.forward(xr[dx:], y, g.ws)
+    assert np.array_equal(y.cpu().numpy().reshape(ref.shape), ref)
+    assert bool((yr[:dy] == 9).all()) and bool((yr[dy + ref.size:] == 9).all())
+    g.check_guards()
+    g.enc.close()
+
+
+@pytest.mark.parametrize("nonlinear", [False, True])
+@pytest.mark.parametrize("B,T", [(2, 45), (2, 48)])
+def test_other_entry_points(B, T, nonlinear, tuning_env):
+    """Float features (rows of the network's ends rounded up to 16 frames), the library's own workspace, a graph replayed between
+    eager forwards."""
+    tuning_env(FORCE, "1")
+    b = _Builder("entries", 90, B, 512, T)
+    sw, glu = (ACT_SWISH, ACT_GLU) if nonlinear else (0, 0)
+    for i in range(2):
+        b.op(f"dw{i}", 512, k=32 - i, groups=512, relu=False, act=sw)
+        b.op(f"pw{i}", 512, relu=False)
+        b.op(f"up{i}", 1024, act=sw)
+        b.op(f"gate{i}", 1024, relu=False, act=glu)
+        b.op(f"half{i}", 256, relu=False, Cin=512, x_batch_stride=1024 * T)
+        b.op(f"back{i}", 512, relu=False)
+    net = b.done()
+    params = W.draw_net_params(net, 7)
+    xf = np.random.default_rng(7).normal(0, 2, (B, 512, T)).astype(np.float32)
+    x = oracle.quantize(xf, 4.0)
+    ref = oracle.encoder_forward(net, params, x)
+    g = GpuNet(net, params)
+    names = [g.enc.op_launch(i) for i in range(g.enc.n_ops)]
+    assert names[7] == (6, "pw_chain") and (T % 16 or names[1] == (0, "pw_chain"))
+    ws = torch.full((g.enc.workspace_bytes_f32,), 77, dtype=torch.int8, device="cuda")
+    y = torch.empty(ref.shape, dtype=torch.float32, device="cuda")
+    g.enc.forward_f32(dev(xf), 4.0, 0.25, y, ws)
+    assert np.array_equal(y.cpu().numpy(), ref.astype(np.float32) * np.float32(0.25))
+    xd = dev(x)
+    g.enc.forward_static(xd, g.y)
+    assert np.array_equal(g.y.cpu().numpy(), ref)
+    graph = g.enc.graph(xd, g.y, g.ws)
+    for i in range(3):
+        other = W.draw_input(net, 20 + i)
+        xd.copy_(torch.from_numpy(other))
+        want = g.enc.forward_layerwise(xd, torch.empty_like(g.y), g.ws).cpu().numpy()
+        g.ws.fill_(77)
+        g.y.zero_()
+        graph.launch()
+        assert np.array_equal(g.y.cpu().numpy(), want)
+    xd.copy_(torch.from_numpy(x))
+    graph.launch()
+    assert np.array_equal(g.y.cpu().numpy(), ref)
+    graph.close()
+    g.check_guards()
+    g.enc.close()
+
+
+def slots(net, *wires):
+    for o, (i, j) in zip(net.ops, wires):
+        o.in_slot, o.out_slot = i, j
+    net.n_slots = 1 + max(max(w) for w in wires)
+    return net
+
+
+def test_a_chain_does_not_write_what_it_reads(tuning_env):
+    """Where its last output would lie over its first input, a chain is shorter, or does not begin with its depthwise layer."""
+    tuning_env(FORCE, "1")
+    tuning_env("QASR_SLOT_DEPTH", "0")                # (slots are buffers)
+    b = _Builder("over_itself", 89, 2, 512, 75)
+    for n in ("in", "a", "b", "c", "d"):
+        b.op(n, 512, relu=n == "b")
+    b.op("end", 64, relu=False)
+    wires = ((0, 1), (1, 2), (2, 1), (1, 2), (2, 1), (1, 3))
+    # (from `in` on: four layers to slot 2; then d alone)
+    check(slots(b.done(), *wires), {"in": ("in", "pw_chain"), "c": ("in", "pw_chain"), "d": ("d", None)})
+    b = _Builder("over_itself_later", 88, 2, 512, 75)
+    b.op("first", 512, k=3)
+    for n in ("a", "b", "c", "d"):
+        b.op(n, 512, relu=n == "b")
+    b.op("end", 64, relu=False)
+    # (a to d would read and write slot 1)
+    check(slots(b.done(), *wires), {"a": ("a", "pw_chain"), "c": ("a", "pw_chain"), "d": ("d", None)})
+    b = _Builder("over_its_depthwise_input", 87, 2, 512, 75)
+    b.op("in", 512, relu=False)
+    b.op("dw", 512, k=31, groups=512, relu=False)
+    b.op("pw", 512)
+    b.op("up", 1024)
+    b.op("down", 512, relu=False)
+    b.op("end", 64, relu=False)
+    net = b.done()
+    # (dw to down would read and write slot 1, whose neighbouring frames other workgroups read)
+    check(slots(net, (0, 1), (1, 2), (2, 3), (3, 2), (2, 1), (1, 4)), {"dw": ("dw", "sep"), "pw": ("dw", "sep"), "up": ("up", "pw_chain"), "down": ("up", "pw_chain")})
+    # (... and with a slot of its own it is one launch)
+    check(slots(net, (0, 1), (1, 2), (2, 3), (3, 2), (2, 4), (4, 1)), {"dw": ("dw", "pw_chain"), "down": ("dw", "pw_chain")})
+
+
+@pytest.mark.parametrize("depth", ["0", "1", "2"])
+@pytest.mark.parametrize("nonlinear", [False, True])
+def test_fewer_buffers(depth, nonlinear, tuning_env):
+    tuning_env(FORCE, "1")
+    tuning_env("QASR_SLOT_DEPTH", depth)
+    net = W.conformer_shaped(2, 75, 4, layers=3, nonlinear=nonlinear)
+    check(net, {"L0.ffn1": ("L0.ffn1", "pw_chain")})
