@@ -964,7 +964,7 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
           chain_op(e->ops[i + j], c[j]);
           rows_of(e, i + j, row_pad(c[j].p.Tin), row_pad(c[j].p.Tout), c[j].p);
         }
-        if (qasr::pw_chain_supported(nullptr, c, n)) break;
+        if (qasr::pw_chain_supported(c, n)) break;
       }
       e->ops[i].chain = n > 1 ? n : 0;
     }

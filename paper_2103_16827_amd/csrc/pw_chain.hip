@@ -355,7 +355,7 @@ __global__ __launch_bounds__(64 * kWaves) void pw_chain_kernel(ChainParams p) {
 struct Plan { int MT, NA, buf[2], const_off, table_off, rows_off, row_bytes, taps_off, lds; int64_t wgs; DwParams dw; };
 
 bool plan(const ConvParams* dw, const ChainOp* op, int n, int cus, Plan& pl) {
-  if (tuning().no_pw_chain || n < (dw ? 1 : 2) || n > kMaxChain) return false;
+  if (tuning().no_pw_chain || n < 2 || n > kMaxChain) return false;
   const ConvParams &f = op[0].p, &e = op[n - 1].p;
   int consts = 0;
   for (int i = 0; i < n; ++i) {
@@ -416,9 +416,9 @@ hipError_t launch_t(const ChainParams& p, size_t lds, hipStream_t st) {
 
 }  // namespace
 
-bool pw_chain_supported(const ConvParams* dw, const ChainOp* op, int n) {
+bool pw_chain_supported(const ChainOp* op, int n) {
   Plan pl;
-  return plan(dw, op, n, 256, pl);
+  return plan(nullptr, op, n, 256, pl);
 }
 
 // The chain's time, a fixed part and the stream (blocks of 256 KiB), against its layers' by pw_wide's model.  It takes launches

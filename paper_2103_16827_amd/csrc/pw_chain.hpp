@@ -35,15 +35,15 @@ struct ChainParams {
 
 // op[0..n): pointwise layers of which each but the first reads exactly what the one before writes, and nobody else does; table: the
 // activation's of its output, or null; glu: that is a GLU's.  dw: the depthwise layer whose output, read by op[0] and nobody else,
-// it starts from, or null (its weight image: sep.hpp's).  Whether they can run as one launch, and whether that is the faster way:
-// only their geometry, and of their pointers the alignment, are looked at.
+// it starts from, or null (its weight image: sep.hpp's).  Whether the pointwise layers can run as one launch, and whether all of them
+// can and that is the faster way: only their geometry, and of their pointers the alignment, are looked at.
 struct ChainOp {
   ConvParams p;
   const uint8_t* table;
   bool glu;
   int32_t glu_m, glu_s;
 };
-bool pw_chain_supported(const ConvParams* dw, const ChainOp* op, int n);
+bool pw_chain_supported(const ChainOp* op, int n);
 bool pw_chain_better(const ConvParams* dw, const ChainOp* op, int n);
 // dw->x or op[0].p.x and op[n - 1].p.y set; the others' are not used
 hipError_t launch_pw_chain(const ConvParams* dw, const uint32_t* img, const ChainOp* op, int n, hipStream_t st);
