@@ -1,5 +1,5 @@
 // Host stand-ins for what one tile of the pipelined pointwise kernel (csrc/pw_pipe_body.hpp), and the other
-// kernels that count their requests (dw_pipe, conv_pipe, conv_few), ask of
+// kernels that count their requests (dw_pipe, conv_pipe, conv_few, pw_chain), ask of
 // the GPU, so that they can be compiled for the CPU and run lane by lane: every
 // vector-memory request, wait, barrier and use of loaded data is recorded instead of executed, and
 // every global address is checked against the operand arrays.  Test infrastructure: nothing of
@@ -94,8 +94,8 @@ inline bool maskable(Kind k) { return k == ISSUE_LDS || k == ISSUE_REG || k == U
 inline bool same(const Ev& a, const Ev& b) { return a.k == b.k && (a.k == USE_LDS || a.k == LDS_WRITE || (a.a == b.a && a.b == b.b)); }
 
 // merge the 64 lane streams: events are equal across lanes except that a lane may skip a
-// load (masked out) that others issue
-inline std::vector<Ev> merge(const Wave& w) {
+// load (masked out) that others issue; lanes_of, if given, gets the lanes' own events behind each of the wave's
+inline std::vector<Ev> merge(const Wave& w, std::vector<std::vector<Ev>>* lanes_of = nullptr) {
   std::vector<size_t> pos(64, 0);
   std::vector<Ev> out;
   for (;;) {
@@ -134,9 +134,13 @@ inline std::vector<Ev> merge(const Wave& w) {
     }
     const Ev c = *cand;
     out.push_back(c);
+    if (lanes_of) lanes_of->emplace_back();
     int advanced = 0, top = -1;
     for (int l = 0; l < 64; ++l)
-      if (pos[l] < w.lanes[l].size() && same(w.lanes[l][pos[l]], c)) { ++pos[l]; ++advanced; top = l; }
+      if (pos[l] < w.lanes[l].size() && same(w.lanes[l][pos[l]], c)) {
+        if (lanes_of) lanes_of->back().push_back(w.lanes[l][pos[l]]);
+        ++pos[l]; ++advanced; top = l;
+      }
     // a load into LDS reaches as far as its highest participating lane (recorded: 64 lanes' worth)
     if (c.k == ISSUE_LDS) out.back().b = c.b / 64 * (top + 1);
     if (!maskable(c.k) && advanced != 64) fail("a wave-uniform event is missing in some lanes");
@@ -254,6 +258,9 @@ inline v4i gload16(const void* base, uint32_t off) {
   return (v4i){(int)(kUidTag | (uint32_t)uid), 0, 0, 0};
 }
 inline int32_t gload_i8(const void* p) { return reg_load(p, 1); }
+template <int OFF>
+inline void gload16_into(v4i& r, const void* base, uint32_t off) { r = gload16((const unsigned char*)base + OFF, off); }
+inline void gload4_into(int32_t& r, const void* p) { r = reg_load(p, 4); }
 inline void tie(int32_t& v) {
   if (((uint32_t)v & 0xff000000u) == kUidTag) {
     const int uid = (int)((uint32_t)v & 0x00ffffffu);
