@@ -4,8 +4,9 @@
 // Frames are independent here, so a workgroup of 16 waves can take its one or two 16-frame groups through all layers: the
 // tensors between them, up to 2048 channels wide, stay in LDS, four launches and the chains of first loads in front of each of
 // them (about 5 us) become one.  What bounds it is the weights: every workgroup streams all of them once, 64 bytes per
-// cycle of its unit's path from the L2 (2.75 MiB: 20 us of the 32 to 35 it takes; products and operand reads, which pass under
-// it, are half of that), so it pays while the frames make few tiles for each unit.  Therefore
+// cycle of its unit's path from the L2 (2.75 MiB, by the counters 3.2 MB with rows and constants: 21 us of the 32 to 36 it takes,
+// 91 % of them out of the L2; the products, which pass under it, are 8 us of the matrix pipes), so it pays while the frames make
+// few tiles for each unit.  Therefore
 //   - a wave's weights are ONE stream over layers, passes and blocks, requested 8 steps ahead by hand (vmem.hpp) across
 //     every epilogue and barrier; barriers stand between layers only, and wait for LDS alone;
 //   - workgroups take passes and blocks in different orders (turned below): in step, all of a die's would miss its L2 on the same
