@@ -33,7 +33,7 @@
  *    values, never out-of-bounds accesses).
  *  - The int32 accumulator wraps on overflow; the caller guarantees
  *    fan_in * 128 * 128 + |bias| < 2^31.
- *  - y must not overlap x or residual.
+ *  - y must not overlap x or residual (whole encoders: qasr_encoder_forward).
  */
 #ifndef QASR_H_
 #define QASR_H_
