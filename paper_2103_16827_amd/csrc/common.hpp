@@ -97,6 +97,10 @@ __device__ __forceinline__ chunk16 load_row16(const int8_t* row, int t, int T) {
   return v;
 }
 __device__ __forceinline__ void store_row16(int8_t* row, int t, int T, chunk16 v) {
+  if (t + 16 <= T) {
+    *reinterpret_cast<unaligned_chunk16*>(row + t) = v;
+    return;
+  }
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
     const int td = t + 4 * d;

@@ -116,11 +116,11 @@ __global__ __launch_bounds__(64 * kWaves) void pw_chain_kernel(ChainParams p) {
   // ---- what the first layer reads: a plane of 16 bytes per row for each unit
   constexpr int CPW = 512 / kWaves;                 // depthwise channels of a wave
   using Dw = DwSmall<CPW, MT, NA ? NA : 3, false>;
-  static_assert(Dw::WS == (NA ? NA : 3), "a wave's weight rows are one run in LDS");
   Dw dw;
+  uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
   unsigned char* const rows = lds + p.rows_off + wave * p.row_bytes;
   unsigned char* const lut = rows + p.row_bytes - 256;
-  unsigned char* const taps = lds + p.taps_off + wave * (CPW * Dw::WS * 16);
+  unsigned char* const taps = lds + p.taps_off + wave * (CPW * (NA ? NA : 3) * 16);
   if constexpr (NA > 0) {
     // as DwSmall::load and lay, but straight into LDS; what lies outside the rows is put right after the wait
     const int8_t* const xw = p.dw.x + (int64_t)b * p.dw.xbs + (int64_t)(wave * CPW) * p.dw.xpitch;
@@ -128,8 +128,8 @@ __global__ __launch_bounds__(64 * kWaves) void pw_chain_kernel(ChainParams p) {
     for (int j = 0; j < Dw::NL; ++j) {
       const int L = lane + 64 * j, ch = (L * p.dw.units_inv) >> 16, t = 16 * (g0 + p.dw.o16 + L - ch * p.dw.units);
       const bool on = t >= 0 && t < p.dw.Tin;
-      if (on) dw.in |= 1u << j;
-      if (t == (p.dw.Tin & ~15)) dw.last |= 1u << j;
+      if (on) in |= 1u << j;
+      if (t == (p.dw.Tin & ~15)) last |= 1u << j;
       if (L < CPW * p.dw.units) direct_load16(xw + (on ? ch * p.dw.xpitch + t : 0), rows + 1024 * j);
     }
 #pragma unroll
@@ -222,15 +222,15 @@ __global__ __launch_bounds__(64 * kWaves) void pw_chain_kernel(ChainParams p) {
     for (int j = 0; j < Dw::NL; ++j)
       if (lane + 64 * j < CPW * p.dw.units) {
         v4i* const c = reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j));
-        if (!(dw.in & (1u << j))) *c = (v4i){0, 0, 0, 0};
-        else if (dw.last & (1u << j)) *c = keep_bytes(*c, p.dw.Tin & 15);
+        if (!(in & (1u << j))) *c = (v4i){0, 0, 0, 0};
+        else if (last & (1u << j)) *c = keep_bytes(*c, p.dw.Tin & 15);
       }
     asm volatile("" ::: "memory");                  // (lanes read what other lanes of the wave wrote: LDS is in order)
     // (one block of 16 channels after the other: the weights on their way hold half of the registers)
 #pragma unroll
     for (int blk = 0; blk < CPW / 16; ++blk) {
       v4i dacc[1][MT];
-      dw.template multiply<1>(p.dw, rows, taps, lane, blk, dacc);
+      dw.template multiply<1>(p.dw, p.dw.units, rows, taps, lane, blk, dacc);
       unsigned char* const to = lds + p.buf[0] + (wave * CPW + (lane >> 2)) * 16 + 4 * (lane & 3);
       dw.template finish<1>(p.dw, lut, lane, blk, dacc, [&](int bk, int q, uint32_t pk) __attribute__((always_inline)) {
         *reinterpret_cast<uint32_t*>(to + q * 8192 + bk * 256) = pk;
@@ -391,7 +391,7 @@ bool plan(const ConvParams* dw, const ChainOp* op, int n, int cus, Plan& pl) {
       c.rows_off = 512 * 16 * MT;
       c.row_bytes = sep::small_row_bytes(32, c.dw.units, MT, c.NA) + 256;
       c.taps_off = c.rows_off + kWaves * c.row_bytes;
-      const int end = c.taps_off + 512 * 16 * (c.NA | 1);
+      const int end = c.taps_off + 512 * 16 * c.NA;
       if (end > c.const_off) c.const_off = end;
     }
     c.table_off = c.const_off + consts;

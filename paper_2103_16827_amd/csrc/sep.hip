@@ -56,9 +56,9 @@ __global__ __launch_bounds__(256) void sep_image_kernel(const int8_t* __restrict
   img[idx] = taps(16 * blk + (lane >> 2), 4 * (4 * a + i) - (lane & 3) - r);
 }
 
-size_t lds_bytes(int KCH, int units, int MT, int NA) {
-  const int rows = MT <= 2 ? sep::small_row_bytes(4 * KCH, units, MT, NA) : sep::row_bytes(units, MT, NA);
-  return (size_t)KCH * 8192 + sep::kWaves * (size_t)(rows + 256);
+size_t lds_bytes(int KCH, int units, int MT, int NA, int NT, int KS) {
+  const int rows = MT <= 2 ? sep::small_row_bytes(4 * KCH, sep::row_units(MT, NA), MT, NA) : sep::row_bytes(units, MT, NA);
+  return (size_t)KCH * 8192 + sep::kWaves * (size_t)(rows + 256) + (MT <= 2 ? 12 * (size_t)(256 / KS * NT) : 0);
 }
 
 // Tile (MT groups x 256 NT output channels per workgroup) with the least time on the busiest compute
@@ -80,11 +80,11 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
         const int units = units_of(d, g, MT);
         if (units > sep::kMaxUnits) continue;
         if (MT <= 2 && (int64_t)4 * c.KCH * (d.Tin + d.xpad) > 0x7fffffffLL) continue;   // 32-bit offsets within a wave's rows
-        const size_t lds = lds_bytes(c.KCH, units, MT, c.NA);
+        const size_t lds = lds_bytes(c.KCH, units, MT, c.NA, NT, KS);
         if (lds > 160 * 1024) continue;
         const int splits = q.Cout / (256 / KS * NT);
         const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
-        if (wgs * (proj ? 2 : 1) > max_workgroups(64 * sep::kWaves)) continue;
+        if (wgs * (proj ? 2 : 1) > max_workgroups(64 * sep::kWaves) || wgs * ((groups_per_row + MT - 1) / MT) > 1LL << 32) continue;   // (place)
         const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 4 / KS;
         const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 64.0 * units * 16;
         const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
@@ -112,6 +112,7 @@ bool plan(const ConvParams& d, const ConvParams& q, int cus, bool proj, Geometry
   if (d.Tout != q.Tin && (d.Tout + 15) / 16 * 16 != q.Tin) return false;            // (q may run over the pitch)
   // 32-bit offsets within 16 rows of x and a batch item of y
   if ((int64_t)16 * (d.Tin + d.xpad) > 0x7fffffffLL || (int64_t)q.Cout * (q.Tout + q.ypad) > 0x7fffff00LL) return false;
+  if (d.xbs >= 1LL << 32 || q.ybs >= 1LL << 32) return false;
   if (d.Tin < 4 || q.Tout < 4) return false;
   c.ragged = x_ragged(d) || y_ragged(q);
   return pick(d, q, g, (q.Tout + 15) / 16, cus, proj, c);
@@ -131,6 +132,7 @@ bool sep_projection_supported(const ConvParams& d, const ConvParams& q, const Co
   Geometry g;
   SepChoice c;
   if (!plan(d, q, 256, true, g, c) || c.ragged) return false;
+  if ((int64_t)32 * (d.Tin + d.xpad) > 0x7fffffffLL) return false;   // 32-bit offsets within a wave's rows of the tile
   return !r.depthwise && r.k == 1 && r.stride == 1 && r.pl == 0 && r.Tout == r.Tin && r.w_packed && !r.res && !r.n_res_more && !r.act_lut &&
          r.B == d.B && r.Cin == d.Cin && r.Cout == q.Cout && r.xbs == d.xbs && r.Tin + r.xpad == d.Tin + d.xpad && r.ybs == q.ybs &&
          r.Tout + r.ypad == q.Tout + q.ypad && (r.Tout + 15) / 16 == (q.Tout + 15) / 16 && (uintptr_t)r.w % 16 == 0 &&
@@ -146,6 +148,9 @@ static void fill_dw(const ConvParams& d, const Geometry& g, int MT, DwParams& p)
   p.dwoff = g.delta >> 2;
   p.drelu = d.relu;
   p.units_inv = (65536 + p.units - 1) / p.units;
+  const int need = (g.delta + 16 * MT + d.dil * (d.k - 1) + 15) / 16;
+  p.row_lanes_log2 = need > 8 ? 4 : need > 4 ? 3 : 2;
+  p.row_step = (int32_t)((64 >> p.row_lanes_log2) * (int64_t)p.xpitch);
 }
 
 bool dw_small_params(const ConvParams& d, int MT, DwParams& p, int& NA) {
@@ -176,8 +181,9 @@ static hipError_t launch(const ConvParams& d, const uint32_t* img, const ConvPar
   SepParams p{};
   fill_dw(d, g, c.MT, p);
   p.img = c.MT <= 2 ? img : img + rows_image_bytes(d.Cout, g.NA) / 4;
-  p.w = q.w; p.bias = q.bias; p.m = q.m; p.s = q.s; p.res = q.res; p.y = q.y;
-  p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.Tout = q.Tout; p.relu = q.relu;
+  p.pw[0] = {q.w, q.bias, q.m, q.s, q.res, q.y, q.relu, 0};
+  if (r) p.pw[1] = {r->w, r->bias, r->m, r->s, nullptr, r->y, r->relu, 0};
+  p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.Tout = q.Tout;
   const int gpr = (q.Tout + 15) / 16;
   p.tpr = (gpr + c.MT - 1) / c.MT;
   p.g_base = gpr / p.tpr;
@@ -185,17 +191,11 @@ static hipError_t launch(const ConvParams& d, const uint32_t* img, const ConvPar
   p.yragged = y_ragged(q);
   p.splits = c.splits;
   p.wgs = d.B * p.tpr * p.splits;                // (< 2^22: pick)
-  p.r_splits = 1.0f / (float)p.splits;
-  p.r_tpr = 1.0f / (float)p.tpr;
-  const int C = c.MT <= 2 ? 4 * c.KCH : 16;      // rows a wave brings in at a time
-  if (C * p.units > 64 * sep::row_loads(C, c.MT, c.NA)) return hipErrorInvalidValue;
+  p.splits_inv = 0xffffffffu / (uint32_t)p.splits;
+  p.tpr_inv = 0xffffffffu / (uint32_t)p.tpr;
+  if (c.MT > 2 && 16 * p.units > 64 * sep::row_loads(16, c.MT, c.NA)) return hipErrorInvalidValue;
   p.per_xcd = (p.wgs + 7) / 8;
-  if (r) {
-    p.w2 = r->w; p.bias2 = r->bias; p.m2 = r->m; p.s2 = r->s; p.y2 = r->y; p.relu2 = r->relu;
-    p.wgs2 = p.wgs;
-    p.per_xcd2 = p.per_xcd;
-  }
-  const size_t lds = lds_bytes(c.KCH, p.units, c.MT, c.NA);
+  const size_t lds = lds_bytes(c.KCH, p.units, c.MT, c.NA, c.NT, c.KS);
   switch (c.NA) {
     case 3: return launch_sep_na3(c, p, lds, st);
     case 4: return launch_sep_na4(c, p, lds, st);

@@ -21,29 +21,29 @@ struct DwParams {
   int32_t dwoff;                     // dwords between a row's start and the first window
   int32_t drelu;
   int32_t units_inv;                 // ceil(2^16 / units): L / units = L units_inv >> 16 for L < 512, units <= 15
+  int32_t row_lanes_log2, row_step;  // small tiles: lanes that bring a row in; bytes between the first rows of two requests
 };
 
-struct SepParams : DwParams {
-  // pointwise half
+struct SepPointwise {
   const int8_t* w;                   // packed (common.hpp)
   const int32_t *bias, *m, *s;       // bias may be null
   const int8_t* res;                 // may be null
   int8_t* y;
-  int64_t ybs;
-  int32_t ypitch, relu;
+  int32_t relu, pad_;
+};
+struct SepParams : DwParams {
+  // pointwise half: [0] the pair's; [1] a second pointwise layer of x itself (a block's residual projection), by workgroups of its
+  // own in the same launch (blockIdx.z): widths, rows and tiles of the first, no residual
+  SepPointwise pw[2];
+  int64_t ybs;                       // both batch strides < 2^32
+  int32_t ypitch;
   int32_t Tout, yragged;             // frames per row; rows (y and residual) not padded to whole aligned chunks
   // tiles: the 16-frame groups of a row (batch item) make tpr tiles of g_base groups, the first g_more of them
   // one group more
   int32_t tpr, g_base, g_more;
   int32_t splits;                    // workgroups per tile, each with its own run of output channels
-  int32_t wgs, per_xcd;              // workgroups in all, and per XCD
-  // a second pointwise layer of x itself (a block's residual projection), by workgroups of its own in the same
-  // launch: widths, rows and tiles of the first; wgs2 == 0: none
-  const int8_t* w2;
-  const int32_t *bias2, *m2, *s2;
-  int8_t* y2;
-  int32_t relu2, wgs2, per_xcd2;
-  float r_splits, r_tpr;             // reciprocals of the two
+  int32_t wgs, per_xcd;              // workgroups in all (of one layer), and per XCD
+  uint32_t splits_inv, tpr_inv;      // (2^32 - 1) / the two: v / d = (v + 1) inv >> 32 while (v + 1) d <= 2^32
 };
 
 // The depthwise half's parameters for tiles of MT <= 2 groups (all but img); false if d is none that it takes.  NA: quads of taps.

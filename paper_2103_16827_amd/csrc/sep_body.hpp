@@ -53,12 +53,68 @@ __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
       (v2i __attribute__((address_space(3)))*)(const_cast<unsigned char*>(p)));
 }
 
+constexpr uint32_t kNone = 0xfffffff0u;             // an offset beyond every buffer's range: the load returns zeros
+
+// Rows of x come as 16-frame chunks, zeros where a row has none, one request per 64 chunks, with no branch around it and nothing
+// merged into its register: for `r = 0; if (there) r = load` the compiler moved registers, and to do that waited for all
+// that was on its way, a round trip to memory before the pointwise half's weights were even asked for.  Chunks that
+// do not exist are out of a buffer's range and come back as zeros; ragged rows (no alignment, no pad) are read past their
+// end, the tensor's last ones from inside it.  The frames past a row's end are cleared in LDS, by the tiles that have any.
+//
+// 16 bytes at off from `rows`, the first of C rows; `tail`: they are the tensor's last
+template <int C, bool RAGGED>
+__device__ __forceinline__ uint32_t last_start(const DwParams& p, bool tail) {
+  return RAGGED && tail ? (uint32_t)((C - 1) * p.xpitch + p.Tin - 16) : kNone;
+}
+template <int C, bool RAGGED>
+__device__ __forceinline__ v4i load_chunk(const DwParams& p, const int8_t* rows, bool tail, uint32_t off, uint32_t step) {
+  if constexpr (RAGGED) {
+    const uint32_t o = off == kNone ? 0u : min(off + step, last_start<C, RAGGED>(p, tail));
+    return *reinterpret_cast<const unaligned_chunk16*>(rows + o);
+  } else {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(rows), 0, C * p.xpitch, 0x00027000);
+    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, off, step, 0));
+  }
+}
+// what it brought as it goes to LDS
+template <int C, bool RAGGED>
+__device__ __forceinline__ v4i whole_chunk(const DwParams& p, bool tail, uint32_t off, uint32_t step, v4i v) {
+  if constexpr (RAGGED) {
+    const uint32_t end = last_start<C, RAGGED>(p, tail);
+    if (__any(off != kNone && off + step > end)) {  // (the tensor's last tile) moved down; zeros come in
+      const int n = off != kNone && off + step > end ? (int)(off + step - end) : 0;
+      if (n & 8) v = (v4i){v[2], v[3], 0, 0};
+      if (n & 4) v = (v4i){v[1], v[2], v[3], 0};
+      v4i r;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[i] = (int)__builtin_amdgcn_alignbyte(i < 3 ? (uint32_t)v[i + 1] : 0u, (uint32_t)v[i], (uint32_t)n & 3u);
+      v = r;
+    }
+    if (off == kNone) v = (v4i){0, 0, 0, 0};
+  }
+  return v;
+}
+// C rows in LDS, `pitch` bytes apart, whose first chunk starts at frame 16 c0
+template <int C>
+__device__ __forceinline__ void clear_past_end(const DwParams& p, unsigned char* rows, int pitch, int c0, int lane) {
+  const int u = (p.Tin >> 4) - c0;                  // the chunk a row ends in
+  if ((p.Tin & 15) && (uint32_t)(16 * u) < (uint32_t)pitch && lane < C) {   // (uniform but for the lane)
+    asm volatile("" ::: "memory");                  // (lanes read what other lanes of the wave wrote: LDS is in order)
+    v4i* const q = reinterpret_cast<v4i*>(rows + lane * pitch + 16 * u);
+    *q = keep_bytes(*q, p.Tin & 15);
+  }
+}
+
 // 64-lane loads that bring in C rows: at most (MT + NA + 1) | 1 chunks each (units_of: the first chunk starts up to
 // 15 frames early, NA quads hold up to 16 NA - 3 frames of taps)
 constexpr int row_loads(int C, int MT, int NA) {
   const int u = (MT + NA + 1) | 1;
   return (C * (u < kMaxUnits ? u : kMaxUnits) + 63) / 64;
 }
+
+// 16-byte units per row in LDS of the small kernel (odd: 16 rows then start in different banks) and the lanes that bring a row in
+constexpr int row_units(int MT, int NA) { return (MT + NA + 1) | 1; }
+constexpr int max_row_lanes_log2(int MT, int NA) { return MT + NA + 1 > 8 ? 4 : 3; }
 
 // bytes of a wave's row buffer: 16 rows and what the windows of the last row read past it, at least
 // the 16 x 128 bytes of the output staging; of the small kernel's: all C rows, at least
@@ -67,50 +123,46 @@ __host__ __device__ inline int row_bytes(int units, int MT, int NA) {
   const int rows = 15 * 16 * units + 16 * (MT + NA) + 32;
   return ((rows > 2048 ? rows : 2048) + 15) & ~15;
 }
-__host__ __device__ inline int small_row_bytes(int C, int units, int MT, int NA) {
+__host__ __device__ constexpr inline int small_row_bytes(int C, int units, int MT, int NA) {
   const int rows = (C - 1) * 16 * units + 16 * (MT + NA) + 32;
   return ((rows > 2048 ? rows : 2048) + 15) & ~15;
 }
 
-// The workgroup's tile and output channels, without a division (two 64-bit ones were 290 instructions in front
-// of the first load).  All arguments are read first, in one go: asked for where they are used, they were a
-// dozen dependent scalar loads.
-struct Place {
-  int b, g0, gn, cs;
-  bool proj;                                        // of the second pointwise layer: the tile is x itself
-  const int8_t* w;
-  const int32_t *bias, *m, *s;
-  const int8_t* res;
-  int8_t* y;
-  int relu;
-};
-__device__ __forceinline__ bool place(const SepParams& p, Place& at) {
-  asm volatile("" ::"s"(p.x), "s"(p.img), "s"(p.dbias), "s"(p.dm), "s"(p.ds), "s"(p.lut), "s"(p.xbs), "s"(p.xpitch), "s"(p.Tin),
-               "s"(p.o16), "s"(p.nk), "s"(p.units), "s"(p.dwoff), "s"(p.drelu), "s"(p.units_inv));
-  asm volatile("" ::"s"(p.w), "s"(p.bias), "s"(p.m), "s"(p.s), "s"(p.res), "s"(p.y), "s"(p.ybs), "s"(p.ypitch), "s"(p.relu),
-               "s"(p.Tout), "s"(p.yragged), "s"(p.tpr), "s"(p.splits), "s"(p.wgs), "s"(p.per_xcd), "s"(p.g_base), "s"(p.g_more),
-               "s"(p.r_splits), "s"(p.r_tpr));
-  asm volatile("" ::"s"(p.w2), "s"(p.bias2), "s"(p.m2), "s"(p.s2), "s"(p.y2), "s"(p.relu2), "s"(p.wgs2), "s"(p.per_xcd2));
+// The workgroup's tile and output channels.  Every scalar instruction costs a unit 16 cycles for 16 waves, the first loads wait
+// for all of these: no division, no selection between the two layers' arguments.  All arguments are read first, in one
+// go: asked for where they are used, they were a dozen dependent scalar loads.
+struct Place { int b, g0, gn, cs; };
+// two neighbours of the arguments (an asm statement takes 30 operands, a second one would wait before its own are asked for)
+__device__ __forceinline__ uint64_t and_next(const int32_t& a) {
+  uint64_t v;
+  __builtin_memcpy(&v, &a, 8);
+  return v;
+}
+__device__ __forceinline__ uint32_t workgroup(const SepParams& p, const SepPointwise& q) {
+  asm volatile("" ::"s"(q.w), "s"(q.bias), "s"(q.m), "s"(q.s), "s"(q.res), "s"(q.y), "s"(q.relu), "s"(p.ybs), "s"(and_next(p.ypitch)),
+               "s"(and_next(p.yragged)), "s"(and_next(p.g_base)), "s"(and_next(p.splits)), "s"(p.per_xcd), "s"(p.splits_inv), "s"(p.tpr_inv),
+               "s"(p.x), "s"(p.img), "s"(p.dbias), "s"(p.dm), "s"(p.ds), "s"(p.lut), "s"(p.xbs), "s"(and_next(p.xpitch)), "s"(and_next(p.o16)),
+               "s"(and_next(p.units)), "s"(and_next(p.drelu)), "s"(and_next(p.row_lanes_log2)));
   // consecutive workgroups go round-robin to the 8 XCDs: each XCD takes a contiguous run of tiles
   // (neighbours share halo rows, the workgroups of one tile its rows), first of the pair, then of the projection
-  const int xcd = (int)(blockIdx.x & 7), nth = (int)(blockIdx.x >> 3);
-  at.proj = nth >= p.per_xcd;
-  const int v = at.proj ? xcd * p.per_xcd2 + nth - p.per_xcd : xcd * p.per_xcd + nth;
-  if (at.proj ? nth - p.per_xcd >= p.per_xcd2 || v >= p.wgs2 : v >= p.wgs) return false;   // whole workgroup
-  at.w = at.proj ? p.w2 : p.w;
-  at.bias = at.proj ? p.bias2 : p.bias;
-  at.m = at.proj ? p.m2 : p.m;
-  at.s = at.proj ? p.s2 : p.s;
-  at.res = at.proj ? nullptr : p.res;
-  at.y = at.proj ? p.y2 : p.y;
-  at.relu = at.proj ? p.relu2 : p.relu;
-  const int tile = p.splits == 1 ? v : divide_uniform24(v, p.splits, p.r_splits);   // (workgroups: < 2^22)
-  at.cs = v - tile * p.splits;
-  at.b = divide_uniform24(tile, p.tpr, p.r_tpr);
-  const int ti = tile - at.b * p.tpr;
+  return (blockIdx.x & 7) * (uint32_t)p.per_xcd + (blockIdx.x >> 3);
+}
+__device__ __forceinline__ Place place(const SepParams& p, uint32_t v) {
+  Place at;
+  const uint32_t tile = __umulhi(v + 1, p.splits_inv);
+  at.cs = (int)(v - tile * (uint32_t)p.splits);
+  uint32_t above = tile + 1;
+  asm("" : "+s"(above));                            // (or the sum is carried out in 64 bits)
+  at.b = (int)__umulhi(above, p.tpr_inv);
+  const int ti = (int)tile - at.b * p.tpr;
   at.g0 = ti * p.g_base + min(ti, p.g_more);
   at.gn = p.g_base + (ti < p.g_more ? 1 : 0);       // <= MT
-  return true;
+  return at;
+}
+// the first element of batch item b
+template <typename T>
+__device__ __forceinline__ T* item(T* x, int64_t stride, int b) {
+  return x + (uint64_t)(uint32_t)stride * (uint32_t)b;
 }
 
 // Constants of N = 16 or 32 channels in one or two loads per wave: a load of any size holds the address path
@@ -159,8 +211,11 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   constexpr bool TIGHT = MT * NT > 8;               // (registers)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  Place at;
-  if (!place(p, at)) return;
+  const SepPointwise& pw = p.pw[blockIdx.z];
+  const bool proj = blockIdx.z != 0;
+  const uint32_t v = workgroup(p, pw);
+  if (v >= (uint32_t)p.wgs) return;                 // whole workgroup
+  const Place at = place(p, v);
   const int b = at.b, g0 = at.g0, gn = at.gn, cs = at.cs;
 
   unsigned char* const xs = lds;
@@ -170,39 +225,28 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   uint32_t lut_word = 0;
   if (p.lut) lut_word = reinterpret_cast<const uint32_t*>(p.lut)[lane];
 
-  // ---- depthwise half: 16 channels at a time.  Chunk L of the 16 rows (row L / units, chunk L % units)
-  // is loaded by lane L % 64; chunks outside [0, Tin) are zero, the chunk a row ends in is masked.
+  // ---- depthwise half: 16 channels at a time
   const int c_wave = wave * CPW;
-  int32_t xoff[NL];                                 // byte offset of the chunk within the 16 rows
-  uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
-  const int t_last = p.Tin & ~15;
+  uint32_t xoff[NL];                                // chunk L of 16 rows: chunk L % units of row L / units
 #pragma unroll
   for (int j = 0; j < NL; ++j) {
-    const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
-    const int t = 16 * (g0 + p.o16 + u);
-    if (ch < 16 && t >= 0 && t < p.Tin) in |= 1u << j;
-    if (t == t_last) last |= 1u << j;
-    xoff[j] = ch * p.xpitch + t;
+    const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, c = g0 + p.o16 + L - ch * p.units;
+    xoff[j] = (uint32_t)c < (uint32_t)((p.Tin + 15) >> 4) && ch < 16 ? (uint32_t)(ch * p.xpitch + 16 * c) : kNone;
   }
-  const int8_t* const xw = p.x + (int64_t)b * p.xbs + (int64_t)c_wave * p.xpitch;
+  const int8_t* const xw = item(p.x, p.xbs, b) + (int64_t)c_wave * p.xpitch;
   v4i xr[NL];
+  auto tail = [&](int blk) __attribute__((always_inline)) { return blk == NBLK - 1 && wave == kWaves - 1; };
   auto load_rows = [&](int blk) __attribute__((always_inline)) {
-    const int8_t* const src = xw + (int64_t)(16 * blk) * p.xpitch;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      xr[j] = (v4i){0, 0, 0, 0};
-      if (in & (1u << j)) {
-        if (RAGGED && (last & (1u << j))) xr[j] = load_row16(src + xoff[j] - t_last, t_last, p.Tin);
-        else xr[j] = *reinterpret_cast<const unaligned_chunk16*>(src + xoff[j]);
-      }
-    }
+    for (int j = 0; j < NL; ++j) xr[j] = load_chunk<16, RAGGED>(p, xw + (int64_t)(16 * blk) * p.xpitch, tail(blk), xoff[j], 0u);
   };
-  auto put_rows = [&]() __attribute__((always_inline)) {
+  auto put_rows = [&](int blk) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      if (!RAGGED && (last & (1u << j))) xr[j] = keep_bytes(xr[j], p.Tin & 15);
-      if (lane + 64 * j < 16 * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = xr[j];
+      const v4i r = whole_chunk<16, RAGGED>(p, tail(blk), xoff[j], 0u, xr[j]);
+      if (lane + 64 * j < 16 * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = r;
     }
+    clear_past_end<16>(p, rows, 16 * p.units, g0 + p.o16, lane);
   };
   const int ch_l = lane >> 2, n_l = lane & 3;
   v4i aw[3];                                        // weight quads, two steps ahead
@@ -217,14 +261,14 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   const int n = lane & 15, gi = lane >> 4;
   const int co_w = (cs * kWaves + wave) * 16 * NT;
   v4i wb[3][NT];
-  const v4i* const wsrc = reinterpret_cast<const v4i*>(at.w) + (int64_t)(co_w >> 4) * (KCH * 64) + lane;
+  const v4i* const wsrc = reinterpret_cast<const v4i*>(pw.w) + (int64_t)(co_w >> 4) * (KCH * 64) + lane;
   auto load_w = [&](int kc) __attribute__((always_inline)) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) wb[kc % 3][nt] = wsrc[(nt * KCH + kc) * 64];
   };
   Consts<16 * NT> pc;
 
-  if (RAGGED || !at.proj) {
+  if (RAGGED || !proj) {
     dc.load_bias(p.dbias, c_wave, lane);
     load_rows(0);
     load_quad_weights(0, 0);
@@ -234,7 +278,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
 #pragma unroll
     for (int blk = 0; blk < NBLK; ++blk) {
-      put_rows();
+      put_rows(blk);
       asm volatile("" ::: "memory");                  // (lanes read what other lanes of the wave wrote: LDS is in order)
       __builtin_amdgcn_sched_barrier(0);
       // window quads a .. a + MT - 1 are what step quad a multiplies; one more is on its way
@@ -291,7 +335,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   } else {
     // the projection's tile: unit tid % 8 of rows tid / 8, + 128, ...
     const int u = tid & 7;
-    const int8_t* const src = p.x + (int64_t)b * p.xbs + (int64_t)(tid >> 3) * p.xpitch + 16 * (g0 + u);
+    const int8_t* const src = item(p.x, p.xbs, b) + (int64_t)(tid >> 3) * p.xpitch + 16 * (g0 + u);
     v4i r[KCH / 2];
 #pragma unroll
     for (int i = 0; i < KCH / 2; ++i)
@@ -310,8 +354,8 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     load_w(0);
     load_w(1);
   }
-  pc.load_bias(at.bias, co_w, lane);
-  pc.load(at.m, at.s, at.bias, co_w, lane);
+  pc.load_bias(pw.bias, co_w, lane);
+  pc.load(pw.m, pw.s, pw.bias, co_w, lane);
   // residual rows and output rows: lane -> (row lane / 8 of 8, slot lane % 8), the unit in that slot
   const int u_l = (lane & 7) ^ (lane >> 3);
   const bool u_ok = u_l < gn;
@@ -323,7 +367,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int8_t* const row = at.res + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch;
+        const int8_t* const row = pw.res + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch;
         if (u_ok) rr[nt][h] = RAGGED && p.yragged ? load_row16(row, t_l, p.Tout) : *reinterpret_cast<const v4i*>(row + t_l);
       }
   };
@@ -340,7 +384,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
 #pragma unroll
   for (int kc = 0; kc < KCH; ++kc) {
     if (kc + 2 < KCH) load_w(kc + 2);
-    if (kc + 2 == KCH && at.res) load_res();         // (into what the weight ring no longer needs)
+    if (kc + 2 == KCH && pw.res) load_res();         // (into what the weight ring no longer needs)
     __builtin_amdgcn_sched_barrier(0);
     const unsigned char* ab = xs + kc * 8192;
     v2i ar[3][2];
@@ -374,10 +418,10 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   const uint32_t sbase = (uint32_t)(n * 128 + 4 * gi) | (uint32_t)((n & 7) << 4);
   bool ok = true;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (at.res ? kShortMaxRes : kShortMax);
+  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (pw.res ? kShortMaxRes : kShortMax);
   const bool fast = __all(ok);
   const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
-      at.y + (int64_t)b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
+      item(pw.y, p.ybs, b) + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
   const uint32_t ylane = (uint32_t)(lane >> 3) * (uint32_t)p.ypitch + (uint32_t)t_l;
   auto epilogue = [&](auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
@@ -397,7 +441,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
         if constexpr (FAST)
           *sp = requant_short4<RES, RELU>(a4, mc[nt], sc[nt] - 32, 1 << ((sc[nt] - 33) & 31), rw);
         else
-          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, at.relu ? 0 : -128, 127);
+          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, pw.relu ? 0 : -128, 127);
         if (mt & 1) __builtin_amdgcn_sched_barrier(0);
       }
       asm volatile("" ::: "memory");
@@ -405,7 +449,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       for (int h = 0; h < 2; ++h) {
         const v4i o = *reinterpret_cast<const v4i*>(st + 1024 * h + 16 * lane);
         if (RAGGED && p.yragged) {                  // (uniform)
-          if (u_ok) store_row16(at.y + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch, t_l, p.Tout, o);
+          if (u_ok) store_row16(pw.y + yrow + (int64_t)(16 * nt + 8 * h) * p.ypitch, t_l, p.Tout, o);
           continue;
         }
         const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};
@@ -416,13 +460,13 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   };
   const std::true_type T{};
   const std::false_type F{};
-  if (at.res) {
+  if (pw.res) {
     if (!fast) epilogue(F, T, F);
-    else if (at.relu) epilogue(T, T, T);
+    else if (pw.relu) epilogue(T, T, T);
     else epilogue(T, T, F);
   } else {
     if (!fast) epilogue(F, F, F);
-    else if (at.relu) epilogue(T, F, T);
+    else if (pw.relu) epilogue(T, F, T);
     else epilogue(T, F, F);
   }
 }
@@ -433,70 +477,60 @@ template <int CPW, int MT, int NA, bool RAGGED>
 struct DwSmall {
   static_assert(MT <= 2, "two units per row");
   static constexpr int NL = row_loads(CPW, MT, NA);
-  static constexpr int WS = NA | 1;                 // 16-byte units of a weight row in LDS (odd: 16 rows in different banks)
   static constexpr int NWL = (CPW * NA + 63) / 64;
-  v4i wr[NWL], xr[NL];
-  uint32_t in = 0, last = 0;                        // bit j: chunk j has frames; ... and its row ends inside it
   Consts<CPW> dc;
 
   // (the bias first: it is on one path only)
   __device__ __forceinline__ void load_bias(const DwParams& p, int c_wave, int lane) { dc.load_bias(p.dbias, c_wave, lane); }
-  __device__ __forceinline__ void load(const DwParams& p, int b, int g0, int c_wave, int lane) {
-    // weights: chunk L of the wave's CPW x NA
-    {
-      const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
+  // A row's chunks are brought in by 1 << row_lanes_log2 lanes each, so that requests differ by a uniform offset.  (Dividing
+  // chunk numbers by the units of a row took 9 vector instructions per request, and each, scalar ones too, is 16 cycles of a unit for 16
+  // waves.)  Rows are RU units apart in LDS.
+  static constexpr int RU = row_units(MT, NA);
+  static constexpr int NX = (CPW << max_row_lanes_log2(MT, NA)) / 64;
+  static constexpr int kWeightBytes = NWL * 1024;   // of a wave's weight rows in LDS, NA 16-byte units each
+  v4i wr[NWL], xr[NX];
+  uint32_t xoff;
+  __device__ __forceinline__ uint32_t step(const DwParams& p, int j) const { return (uint32_t)j * (uint32_t)p.row_step; }
+  __device__ __forceinline__ void load(const DwParams& p, int b, int g0, int wave, int lane) {
+    const int c_wave = wave * CPW;
+    // weights: as they lie, to the end of the last load (after the rows follow the Toeplitz operands)
+    const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
 #pragma unroll
-      for (int j = 0; j < NWL; ++j) wr[j] = src[min(lane + 64 * j, CPW * NA - 1)];
-    }
+    for (int j = 0; j < NWL; ++j) wr[j] = src[lane + 64 * j];
     dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
-    // rows: chunk L of the wave's CPW x units; chunks outside [0, Tin) are zero, the chunk a row ends in is masked
-    {
-      const int8_t* const xw = p.x + (int64_t)b * p.xbs + (int64_t)c_wave * p.xpitch;
-      const int t_last = p.Tin & ~15;
+    const int u = lane & ((1 << p.row_lanes_log2) - 1), c = g0 + p.o16 + u;
+    xoff = (uint32_t)c < (uint32_t)((p.Tin + 15) >> 4) && u < RU ? (uint32_t)((lane >> p.row_lanes_log2) * p.xpitch + 16 * c) : kNone;
+    const int8_t* const xw = item(p.x, p.xbs, b) + (uint64_t)(uint32_t)c_wave * (uint32_t)p.xpitch;
 #pragma unroll
-      for (int j = 0; j < NL; ++j) {
-        const int L = lane + 64 * j, ch = (L * p.units_inv) >> 16, u = L - ch * p.units;
-        const int t = 16 * (g0 + p.o16 + u);
-        const bool on = ch < CPW && t >= 0 && t < p.Tin;
-        if (on) in |= 1u << j;
-        if (t == t_last) last |= 1u << j;
-        xr[j] = (v4i){0, 0, 0, 0};
-        if (RAGGED) {
-          if (on) xr[j] = t == t_last ? load_row16(xw + ch * p.xpitch, t, p.Tin) : *reinterpret_cast<const unaligned_chunk16*>(xw + ch * p.xpitch + t);
-        } else if (64 * j < CPW * p.units) {          // (uniform; lanes without a chunk read the first one and drop it)
-          xr[j] = *reinterpret_cast<const v4i*>(xw + (on ? ch * p.xpitch + t : 0));
-        }
-      }
-    }
+    for (int j = 0; j < NX; ++j)                      // (uniform; what is not loaded is not used)
+      if (j < 1 || j < CPW >> (6 - p.row_lanes_log2)) xr[j] = load_chunk<CPW, RAGGED>(p, xw, wave == kWaves - 1, xoff, step(p, j));
   }
-  // into LDS: CPW rows at rows (small_row_bytes), CPW weight rows of 16 WS bytes at wlds
-  __device__ __forceinline__ void lay(const DwParams& p, unsigned char* rows, unsigned char* wlds, int lane) {
+  // into LDS: CPW rows at rows (small_row_bytes), weight rows at wlds
+  __device__ __forceinline__ void lay(const DwParams& p, unsigned char* rows, unsigned char* wlds, int g0, int wave, int lane) {
 #pragma unroll
-    for (int j = 0; j < NWL; ++j) {
-      const int L = lane + 64 * j, ch = L / NA;
-      if (L < CPW * NA) *reinterpret_cast<v4i*>(wlds + 16 * (ch * WS + L - ch * NA)) = wr[j];
-    }
+    for (int j = 0; j < NWL; ++j) *reinterpret_cast<v4i*>(wlds + 16 * lane + 1024 * j) = wr[j];
+    const int u = lane & ((1 << p.row_lanes_log2) - 1);
+    unsigned char* const to = rows + 16 * ((lane >> p.row_lanes_log2) * RU + u);
+    if (max_row_lanes_log2(MT, NA) < 4 || u < RU) {
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      v4i r = xr[j];
-      if (!RAGGED) {
-        if (!(in & (1u << j))) r = (v4i){0, 0, 0, 0};
-        if (last & (1u << j)) r = keep_bytes(r, p.Tin & 15);
-      }
-      if (lane + 64 * j < CPW * p.units) *reinterpret_cast<v4i*>(rows + 16 * (lane + 64 * j)) = r;
+      for (int j = 0; j < NX; ++j)
+        if (j < 1 || j < CPW >> (6 - p.row_lanes_log2))
+          *reinterpret_cast<v4i*>(to + j * ((1024 * RU) >> p.row_lanes_log2)) =
+              whole_chunk<CPW, RAGGED>(p, wave == kWaves - 1, xoff, step(p, j), xr[j]);
     }
+    clear_past_end<CPW>(p, rows, 16 * RU, g0 + p.o16, lane);
     asm volatile("" ::: "memory");                    // (lanes read what other lanes of the wave wrote: LDS is in order)
     __builtin_amdgcn_sched_barrier(0);
   }
   // NB blocks of 16 channels from block b0 on, side by side: lane -> channel lane / 4 of the block, frames 4 (lane % 4) + (0..3) of a group
   template <int NB>
-  __device__ __forceinline__ void multiply(const DwParams& p, const unsigned char* rows, const unsigned char* wlds, int lane, int b0,
+  __device__ __forceinline__ void multiply(const DwParams& p, int units, const unsigned char* rows, const unsigned char* wlds, int lane, int b0,
                                            v4i (&dacc)[NB][MT]) const {
     const int ch_l = lane >> 2, n_l = lane & 3;
     // Toeplitz row m = lane % 4 of four taps: bytes 4 - m .. 7 - m of (this dword, the one before)
     const uint32_t sel = 0x07060504u - 0x01010101u * (uint32_t)n_l;
-    const unsigned char* const win = rows + (16 * b0 + ch_l) * (16 * p.units) + 4 * (n_l + p.dwoff);
-    const unsigned char* const wrow = wlds + (16 * b0 + ch_l) * (16 * WS);
+    const unsigned char* const win = rows + (16 * b0 + ch_l) * (16 * units) + 4 * (n_l + p.dwoff);
+    const unsigned char* const wrow = wlds + (16 * b0 + ch_l) * (16 * NA);
     constexpr int LA = 2, WQ = MT + LA;               // quads read ahead
     uint32_t wd[NB][WQ][4];
     v4i aq[NB][LA + 1];
@@ -506,11 +540,11 @@ struct DwSmall {
       for (int blk = 0; blk < NB; ++blk)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          wd[blk][a % WQ][i] = *reinterpret_cast<const uint32_t*>(win + 256 * blk * p.units + 16 * a + 4 * i);
+          wd[blk][a % WQ][i] = *reinterpret_cast<const uint32_t*>(win + 256 * blk * units + 16 * a + 4 * i);
     };
     auto read_taps = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
-      for (int blk = 0; blk < NB; ++blk) aq[blk][a % (LA + 1)] = *reinterpret_cast<const v4i*>(wrow + 256 * blk * WS + 16 * a);
+      for (int blk = 0; blk < NB; ++blk) aq[blk][a % (LA + 1)] = *reinterpret_cast<const v4i*>(wrow + 256 * blk * NA + 16 * a);
     };
 #pragma unroll
     for (int a = 0; a < LA; ++a) read_taps(a);
@@ -589,7 +623,12 @@ struct DwSmall {
 //     nothing waits in between;
 //   - both blocks of 16 channels are multiplied side by side; residual and output rows are two 16-byte
 //     units wide, one load and one store per wave.
-// 288 loads, 13400 cycles.  In a chain of such pairs over 50 groups, us a launch: 512 -> 512, k = 75 8.53 -> 7.87,
+//   - nothing is merged into a register that is being loaded and no wait stands before the last request (load_chunk), requests
+//     differ by uniform offsets, and what every wave would work out for itself is left to the host or done once for all: each
+//     instruction, scalar ones above all, is 16 cycles of a unit for 16 waves.  512 -> 512, k = 75 over 50 groups: 13750 -> 12900
+//     cycles a workgroup; QuartzNet-5x5, 1 x 1600 frames 180 -> 162 us, 15x5, 1 x 1237 473 -> 424, 32 x 1600 1275 -> 1237, 10x5,
+//     8 x 1104 438 -> 404.
+// Before the last of these 288 loads, 13400 cycles.  In a chain of such pairs over 50 groups, us a launch: 512 -> 512, k = 75 8.53 -> 7.87,
 // 7.54 with KS = 2 below; k = 51 7.91 -> 7.09, 6.67; 256 -> 256, k = 33 5.58 -> 4.99, 4.83.
 // KS = 2, where twice as many workgroups still find units of their own: the waves are two groups over the input
 // channels of the pointwise half, a workgroup has half as many output channels, its half of the weights and of the
@@ -601,14 +640,17 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   constexpr int CPW = KCH * 64 / kWaves;            // depthwise channels per wave
   constexpr int NBLK = CPW / 16;                    // in blocks of 16
   using Dw = DwSmall<CPW, MT, NA, RAGGED>;
-  static_assert(Dw::WS <= 8, "weights fit the wave's tile rows");
+  static_assert(Dw::kWeightBytes <= CPW * 128, "weights fit the wave's tile rows");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  Place at;
-  if (!place(p, at)) return;
+  const SepPointwise& pw = p.pw[blockIdx.z];
+  const bool proj = blockIdx.z != 0;
+  const uint32_t v = workgroup(p, pw);
+  if (v >= (uint32_t)p.wgs) return;                 // whole workgroup
+  const Place at = place(p, v);
   const int g0 = at.g0, c_wave = wave * CPW;
   unsigned char* const xs = lds;
-  const int rb = small_row_bytes(CPW, p.units, MT, NA) + 256;
+  constexpr int rb = small_row_bytes(CPW, row_units(MT, NA), MT, NA) + 256;
   unsigned char* const rows = lds + KCH * 64 * 128 + wave * rb;
   unsigned char* const lut = rows + rb - 256;       // (every wave its own copy: no barrier)
   unsigned char* const wlds = xs + c_wave * 128;
@@ -621,25 +663,41 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   uint32_t lut_word = 0;
   if (p.lut) lut_word = reinterpret_cast<const uint32_t*>(p.lut)[lane];
   Dw dw;
-  Consts<16 * NT> pc;
   dw.load_bias(p, c_wave, lane);
-  pc.load_bias(at.bias, co_w, lane);
   // residual and output: lane -> row lane / 2 of the wave's 16 NT, unit lane % 2
   const int u_l = lane & 1, t_l = 16 * (g0 + u_l);
   const bool y_ok = u_l < at.gn && lane < 32 * NT && ks == 0;
   const int64_t yrow = (int64_t)at.b * p.ybs + (int64_t)(co_w + (lane >> 1)) * p.ypitch;
   v4i rr = {0, 0, 0, 0};
-  if (at.res && y_ok) rr = RAGGED && p.yragged ? load_row16(at.res + yrow, t_l, p.Tout) : *reinterpret_cast<const v4i*>(at.res + yrow + t_l);
-  v4i tr = {0, 0, 0, 0};
-  if (RAGGED || !at.proj) {
-    dw.load(p, at.b, g0, c_wave, lane);
-  } else {                                          // the projection's tile: unit tid % 2 of row tid / 2
-    if ((tid >> 1) < 64 * KCH && u_l < at.gn)
-      tr = *reinterpret_cast<const v4i*>(p.x + (int64_t)at.b * p.xbs + (int64_t)(tid >> 1) * p.xpitch + t_l);
+  const uint32_t yoff = y_ok ? (uint32_t)(lane >> 1) * (uint32_t)p.ypitch + (uint32_t)t_l : kNone;
+  if (pw.res) {
+    if (RAGGED && p.yragged) {
+      if (y_ok) rr = load_row16(pw.res + yrow, t_l, p.Tout);
+    } else {
+      const __amdgpu_buffer_rsrc_t rrs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<int8_t*>(item(pw.res, p.ybs, at.b)) + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
+      rr = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rrs, yoff, 0, 0));
+    }
   }
-  pc.load(at.m, at.s, at.bias, co_w, lane);
+  v4i tr;
+  if (RAGGED || !proj) {
+    dw.load(p, at.b, g0, wave, lane);
+  } else {                                          // the projection's tile: unit tid % 2 of row tid / 2
+    const int row0 = 32 * wave;
+    const __amdgpu_buffer_rsrc_t xrs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(item(p.x, p.xbs, at.b)) + (int64_t)row0 * p.xpitch, 0,
+                                          row0 < 64 * KCH ? 32 * p.xpitch : 0, 0x00027000);
+    tr = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+                                     xrs, u_l < at.gn ? (uint32_t)(lane >> 1) * (uint32_t)p.xpitch + (uint32_t)t_l : kNone, 0, 0));
+  }
+  // constants of the workgroup's output channels, m | s | bias: 256 of one of them by a wave
+  constexpr int CO = NWC * 16 * NT, CL = (CO + 255) / 256;
+  int32_t* const cst = reinterpret_cast<int32_t*>(lds + KCH * 64 * 128 + kWaves * rb);
+  const int c_of = wave / CL, c_at = 256 * (wave % CL) + 4 * (lane & (CO < 256 ? CO / 4 - 1 : 63));
+  v4i cr;
+  if (c_of < 3) cr = *reinterpret_cast<const unaligned_chunk16*>((c_of == 0 ? pw.m : c_of == 1 ? pw.s : pw.bias ? pw.bias : pw.m) + at.cs * CO + c_at);
   v4i wb[KC][NT];
-  const v4i* const wsrc = reinterpret_cast<const v4i*>(at.w) + (int64_t)(co_w >> 4) * (KCH * 64) + ks * (KC * 64) + lane;
+  const v4i* const wsrc = reinterpret_cast<const v4i*>(pw.w) + (int64_t)(co_w >> 4) * (KCH * 64) + ks * (KC * 64) + lane;
   auto load_w = [&](int kc) __attribute__((always_inline)) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) wb[kc][nt] = wsrc[(nt * KCH + kc) * 64];
@@ -649,12 +707,16 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   for (int kc = 0; kc < FIRST; ++kc) load_w(kc);
   __builtin_amdgcn_sched_barrier(0);
   if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
+  auto lay_constants = [&]() __attribute__((always_inline)) {
+    if (c_of < 3) *reinterpret_cast<v4i*>(cst + c_of * CO + c_at) = c_of < 2 || pw.bias ? cr : (v4i){0, 0, 0, 0};
+  };
 
-  if (RAGGED || !at.proj) {
+  if (RAGGED || !proj) {
     // ---- depthwise half
-    dw.lay(p, rows, wlds, lane);
+    dw.lay(p, rows, wlds, g0, wave, lane);
+    lay_constants();
     v4i dacc[NBLK][MT];
-    dw.template multiply<NBLK>(p, rows, wlds, lane, 0, dacc);
+    dw.template multiply<NBLK>(p, Dw::RU, rows, wlds, lane, 0, dacc);
 #pragma unroll
     for (int kc = FIRST; kc < KC; ++kc) load_w(kc);
     // dword n_l of group q, row (channel) ch of the tile; the tile's unit q of a row sits in slot q ^ (row & 7)
@@ -666,6 +728,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   } else {
     const int row = tid >> 1;
     if (row < 64 * KCH) *reinterpret_cast<v4i*>(xs + row * 128 + ((u_l ^ (row & 7)) << 4)) = tr;
+    lay_constants();
 #pragma unroll
     for (int kc = FIRST; kc < KC; ++kc) load_w(kc);
   }
@@ -687,10 +750,10 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   int32_t mc[NT], sc[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    int32_t bv = pc.bias_of(16 * nt + n);
-    if (ks != 0) bv = 0;
-    mc[nt] = pc.m(16 * nt + n);
-    sc[nt] = pc.s(16 * nt + n);
+    const int32_t* const c = cst + 16 * (wc * NT + nt) + n;
+    const int32_t bv = ks != 0 ? 0 : c[2 * CO];
+    mc[nt] = c[0];
+    sc[nt] = c[CO];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = (v4i){bv, bv, bv, bv};
   }
@@ -725,7 +788,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
   unsigned char* const st = rows;
   bool ok = true;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (at.res ? kShortMaxRes : kShortMax);
+  for (int nt = 0; nt < NT; ++nt) ok = ok && sc[nt] >= kShortMin && sc[nt] <= (pw.res ? kShortMaxRes : kShortMax);
   const bool fast = __all(ok);
   auto epilogue = [&](auto fast_tag, auto res_tag, auto relu_tag) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value, RES = decltype(res_tag)::value, RELU = decltype(relu_tag)::value;
@@ -743,30 +806,29 @@ __global__ __launch_bounds__(64 * kWaves) void sep_small_kernel(SepParams p) {
         if constexpr (FAST)
           *sp = requant_short4<RES, RELU>(a4, mc[nt], sc[nt] - 32, 1 << ((sc[nt] - 33) & 31), rw);
         else
-          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, at.relu ? 0 : -128, 127);
+          *sp = requant_pack4<false, true>(a4, mc[nt], sc[nt], 0, rw, pw.relu ? 0 : -128, 127);
       }
     asm volatile("" ::: "memory");
   };
   const std::true_type T{};
   const std::false_type F{};
-  if (at.res) {
+  if (pw.res) {
     if (!fast) epilogue(F, T, F);
-    else if (at.relu) epilogue(T, T, T);
+    else if (pw.relu) epilogue(T, T, T);
     else epilogue(T, T, F);
   } else {
     if (!fast) epilogue(F, F, F);
-    else if (at.relu) epilogue(T, F, T);
+    else if (pw.relu) epilogue(T, F, T);
     else epilogue(T, F, F);
   }
   const v4i o = *reinterpret_cast<const v4i*>(st + 16 * (lane & (32 * NT - 1)));
   if (RAGGED && p.yragged) {                        // (uniform)
-    if (y_ok) store_row16(at.y + yrow, t_l, p.Tout, o);
+    if (y_ok) store_row16(pw.y + yrow, t_l, p.Tout, o);
   } else {
     const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
-        at.y + (int64_t)at.b * p.ybs + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
+        item(pw.y, p.ybs, at.b) + (int64_t)co_w * p.ypitch, 0, 0x7ffffff0, 0x00027000);
     const v4u ov = {(unsigned)o.x, (unsigned)o.y, (unsigned)o.z, (unsigned)o.w};
-    __builtin_amdgcn_raw_buffer_store_b128(ov, yrs, y_ok ? (uint32_t)(lane >> 1) * (uint32_t)p.ypitch + (uint32_t)t_l : 0xfffffff0u, 0,
-                                           kStoreThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(ov, yrs, yoff, 0, kStoreThrough);
   }
 }
 
@@ -777,7 +839,7 @@ hipError_t launch_t(const SepParams& p, size_t lds, hipStream_t st) {
   if constexpr (MT <= 2) kernel = sep_small_kernel<KCH, MT, NA, NT, KS, RAGGED>;
   else kernel = sep_kernel<KCH, MT, NA, NT, RAGGED>;
   if (const hipError_t e = ensure_max_dynamic_lds((const void*)kernel, lds_raised); e != hipSuccess) return e;
-  return launch_kernel(kernel, dim3((unsigned)(8 * (p.per_xcd + p.per_xcd2))), dim3(64 * kWaves), lds, st, p);
+  return launch_kernel(kernel, dim3((unsigned)(8 * p.per_xcd), 1, p.pw[1].w ? 2 : 1), dim3(64 * kWaves), lds, st, p);
 }
 
 // the instantiations of one tap range (ragged rows: at most 4 groups, more do not fit the registers)
