@@ -32,28 +32,20 @@ int units_of(const ConvParams& d, const Geometry& g, int MT) {
   return need | 1;
 }
 
-// Two images of the weights.  Rows [C][16 NA bytes]: tap j sits at byte r + j dil (sep_small_kernel).  After them, at
-// a multiple of 256 bytes, Toeplitz operands [C / 16][NA][64 lanes][4 dwords]; dword i of quad a, lane (channel block
-// b = lane / 4, row m = lane % 4) holds the weights of kappa = 4 (4 a + i) .. + 3: tap j sits at kappa = m + r + j dil.
-size_t rows_image_bytes(int C, int NA) { return ((size_t)C * NA * 16 + 255) & ~(size_t)255; }
+// The weights as the kernels load them: rows [C][16 NA bytes], tap j at byte r + j dil, zeros between, and up to the end
+// of the last wave's last load.
+size_t image_bytes(int C, int NA) { return (size_t)C * NA * 16 + 1024; }
 __global__ __launch_bounds__(256) void sep_image_kernel(const int8_t* __restrict__ w, int C, int k, int dil, int r, int NA,
-                                                        uint32_t* __restrict__ rows, uint32_t* __restrict__ img) {
-  const int n = C / 16 * NA * 256, nr = C * NA * 4;
-  const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (idx >= n) return;
-  auto taps = [&](int c, int rel0) {                // four bytes from tap position rel0 on
-    uint32_t v = 0;
+                                                        uint32_t* __restrict__ rows) {
+  const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x), c = idx / (4 * NA);
+  if (idx >= C * NA * 4 + 256) return;
+  uint32_t v = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int rel = rel0 + e;
-      const int j = rel >= 0 ? rel / dil : -1;
-      if (j >= 0 && j < k && j * dil == rel) v |= (uint32_t)(uint8_t)w[(int64_t)c * k + j] << (8 * e);
-    }
-    return v;
-  };
-  if (idx < nr) rows[idx] = taps(idx / (4 * NA), 4 * (idx % (4 * NA)) - r);
-  const int i = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) % NA, blk = (idx >> 8) / NA;
-  img[idx] = taps(16 * blk + (lane >> 2), 4 * (4 * a + i) - (lane & 3) - r);
+  for (int e = 0; e < 4; ++e) {
+    const int rel = 4 * (idx % (4 * NA)) - r + e, j = rel >= 0 ? rel / dil : -1;
+    if (c < C && j >= 0 && j < k && j * dil == rel) v |= (uint32_t)(uint8_t)w[(int64_t)c * k + j] << (8 * e);
+  }
+  rows[idx] = v;
 }
 
 size_t lds_bytes(int KCH, int units, int MT, int NA, int NT, int KS) {
@@ -164,14 +156,14 @@ bool dw_small_params(const ConvParams& d, int MT, DwParams& p, int& NA) {
 
 size_t sep_image_bytes(const ConvParams& d) {
   Geometry g;
-  return geometry(d, g) ? rows_image_bytes(d.Cout, g.NA) + (size_t)d.Cout / 16 * g.NA * 1024 : 0;
+  return geometry(d, g) ? image_bytes(d.Cout, g.NA) : 0;
 }
 
 hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st) {
   Geometry g;
   if (!geometry(d, g) || d.Cout % 16) return hipErrorInvalidValue;
-  return launch_kernel(sep_image_kernel, dim3((unsigned)(d.Cout / 16 * g.NA)), dim3(256), 0, st, d.w, d.Cout, d.k, d.dil, g.r,
-                       g.NA, img, img + rows_image_bytes(d.Cout, g.NA) / 4);
+  return launch_kernel(sep_image_kernel, dim3((unsigned)((d.Cout * g.NA * 4 + 256 + 255) / 256)), dim3(256), 0, st, d.w, d.Cout, d.k, d.dil, g.r,
+                       g.NA, img);
 }
 
 static hipError_t launch(const ConvParams& d, const uint32_t* img, const ConvParams& q, const ConvParams* r, hipStream_t st) {
@@ -180,7 +172,7 @@ static hipError_t launch(const ConvParams& d, const uint32_t* img, const ConvPar
   if (!plan(d, q, compute_units(), r != nullptr, g, c)) return hipErrorInvalidValue;
   SepParams p{};
   fill_dw(d, g, c.MT, p);
-  p.img = c.MT <= 2 ? img : img + rows_image_bytes(d.Cout, g.NA) / 4;
+  p.img = img;
   p.pw[0] = {q.w, q.bias, q.m, q.s, q.res, q.y, q.relu, 0};
   if (r) p.pw[1] = {r->w, r->bias, r->m, r->s, nullptr, r->y, r->relu, 0};
   p.ybs = q.ybs; p.ypitch = q.Tout + q.ypad; p.Tout = q.Tout;

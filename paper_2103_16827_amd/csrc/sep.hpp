@@ -8,7 +8,7 @@ namespace qasr {
 
 // a depthwise layer whose output stays in LDS
 struct DwParams {
-  // x rows (pitch xpitch, batch stride xbs, Tin frames), weight image (sep_image_*)
+  // x rows (pitch xpitch, batch stride xbs, Tin frames), weights (sep_image)
   const int8_t* x;
   const uint32_t* img;
   const int32_t *dbias, *dm, *ds;    // dbias may be null

@@ -165,6 +165,9 @@ __device__ __forceinline__ T* item(T* x, int64_t stride, int b) {
   return x + (uint64_t)(uint32_t)stride * (uint32_t)b;
 }
 
+// Toeplitz row m of four taps: bytes 4 - m .. 7 - m of (a weight row's dword, the one before), by one byte permutation
+__device__ __forceinline__ uint32_t toeplitz_bytes(int m) { return 0x07060504u - 0x01010101u * (uint32_t)m; }
+
 // Constants of N = 16 or 32 channels in one or two loads per wave: a load of any size holds the address path
 // of the unit for 16 cycles, so three 16-channel loads cost as much as 3 KiB of weights.  Lanes [0, N) ask for m,
 // [N, 2 N) for s, [2 N, 3 N) for the bias if that fits (N = 16); get() brings a channel's to where it is used.
@@ -213,6 +216,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SepPointwise& pw = p.pw[blockIdx.z];
   const bool proj = blockIdx.z != 0;
+  __builtin_amdgcn_s_setprio(3);                    // (a wave that has its loads on the way goes behind those that have not)
   const uint32_t v = workgroup(p, pw);
   if (v >= (uint32_t)p.wgs) return;                 // whole workgroup
   const Place at = place(p, v);
@@ -249,9 +253,12 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     clear_past_end<16>(p, rows, 16 * p.units, g0 + p.o16, lane);
   };
   const int ch_l = lane >> 2, n_l = lane & 3;
-  v4i aw[3];                                        // weight quads, two steps ahead
-  const v4i* const asrc = reinterpret_cast<const v4i*>(p.img) + (int64_t)(wave * NBLK) * (NA * 64) + lane;
-  auto load_quad_weights = [&](int blk, int a) __attribute__((always_inline)) { aw[a % 3] = asrc[(blk * NA + a) * 64]; };
+  // weights: rows of 16 NA bytes, each block's over the tile rows that its outputs are written to
+  constexpr int NWL = (CPW * NA + 63) / 64;
+  static_assert(NA <= 8, "a block's weights fit its tile rows");
+  unsigned char* const wlds = xs + c_wave * 128;
+  const unsigned char* const wrow = wlds + ch_l * (16 * NA);
+  const uint32_t sel = toeplitz_bytes(n_l);
   Consts<CPW> dc;
   const unsigned char* const win = rows + ch_l * (16 * p.units) + 4 * (n_l + p.dwoff);
   // dword n_l of group q, row (channel) ch of the tile; the tile's unit q of a row sits in slot q ^ (row & 7)
@@ -270,11 +277,18 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
 
   if (RAGGED || !proj) {
     dc.load_bias(p.dbias, c_wave, lane);
+    v4i wr[NWL];
+#pragma unroll
+    for (int j = 0; j < NWL; ++j) wr[j] = reinterpret_cast<const v4i*>(p.img)[c_wave * NA + lane + 64 * j];   // (to the end of the last load)
     load_rows(0);
-    load_quad_weights(0, 0);
-    load_quad_weights(0, 1);
     dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
     __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+    for (int j = 0; j < NWL; ++j) {
+      const int L = lane + 64 * j;
+      if (L < CPW * NA) *reinterpret_cast<v4i*>(wlds + 16 * L + (L < 16 * NA ? 0 : 2048 - 256 * NA)) = wr[j];
+    }
     if (p.lut) reinterpret_cast<uint32_t*>(lut)[lane] = lut_word;
 #pragma unroll
     for (int blk = 0; blk < NBLK; ++blk) {
@@ -282,11 +296,14 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       asm volatile("" ::: "memory");                  // (lanes read what other lanes of the wave wrote: LDS is in order)
       __builtin_amdgcn_sched_barrier(0);
       // window quads a .. a + MT - 1 are what step quad a multiplies; one more is on its way
-      uint32_t wd[MT + 1][4];
+      uint32_t wd[MT + 1][4], before = 0;
+      v4i aq[2];
+      auto read_taps = [&](int a) __attribute__((always_inline)) { aq[a & 1] = *reinterpret_cast<const v4i*>(wrow + 2048 * blk + 16 * a); };
       auto read_quad = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) wd[a % (MT + 1)][i] = *reinterpret_cast<const uint32_t*>(win + 16 * a + 4 * i);
       };
+      read_taps(0);
 #pragma unroll
       for (int a = 0; a < MT; ++a) read_quad(a);
       v4i acc[MT];
@@ -295,22 +312,24 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       for (int q = 0; q < MT; ++q) acc[q] = (v4i){db, db, db, db};
 #pragma unroll
       for (int a = 0; a < NA; ++a) {
-        if (a + 1 < NA) read_quad(a + MT);
-        if (a + 2 < NA) load_quad_weights(blk, a + 2);
+        if (a + 1 < NA) {
+          read_taps(a + 1);
+          read_quad(a + MT);
+        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t d = (uint32_t)aq[a & 1][i], t = __builtin_amdgcn_perm(d, before, sel);
+          before = d;
           if (4 * a + i < 4 * (NA - 1) + 1 || 4 * a + i < p.nk) {
 #pragma unroll
             for (int q = 0; q < MT; ++q)
-              acc[q] = __builtin_amdgcn_mfma_i32_4x4x4i8(aw[a % 3][i], (int)wd[(a + q) % (MT + 1)][i], acc[q], 0, 0, 0);
+              acc[q] = __builtin_amdgcn_mfma_i32_4x4x4i8((int)t, (int)wd[(a + q) % (MT + 1)][i], acc[q], 0, 0, 0);
           }
+        }
         __builtin_amdgcn_sched_barrier(0);
         if (a == 1 && blk + 1 < NBLK) load_rows(blk + 1);   // on their way under the rest of the block
       }
-      if (blk + 1 < NBLK) {
-        load_quad_weights(blk + 1, 0);
-        load_quad_weights(blk + 1, 1);
-      } else if (!TIGHT) {
+      if (blk + 1 == NBLK && !TIGHT) {
         load_w(0);
         load_w(1);
       }
@@ -333,6 +352,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       else finish(std::true_type{}, std::false_type{});
     }
   } else {
+    __builtin_amdgcn_s_setprio(0);
     // the projection's tile: unit tid % 8 of rows tid / 8, + 128, ...
     const int u = tid & 7;
     const int8_t* const src = item(p.x, p.xbs, b) + (int64_t)(tid >> 3) * p.xpitch + 16 * (g0 + u);
@@ -527,8 +547,7 @@ struct DwSmall {
   __device__ __forceinline__ void multiply(const DwParams& p, int units, const unsigned char* rows, const unsigned char* wlds, int lane, int b0,
                                            v4i (&dacc)[NB][MT]) const {
     const int ch_l = lane >> 2, n_l = lane & 3;
-    // Toeplitz row m = lane % 4 of four taps: bytes 4 - m .. 7 - m of (this dword, the one before)
-    const uint32_t sel = 0x07060504u - 0x01010101u * (uint32_t)n_l;
+    const uint32_t sel = toeplitz_bytes(n_l);
     const unsigned char* const win = rows + (16 * b0 + ch_l) * (16 * units) + 4 * (n_l + p.dwoff);
     const unsigned char* const wrow = wlds + (16 * b0 + ch_l) * (16 * NA);
     constexpr int LA = 2, WQ = MT + LA;               // quads read ahead
