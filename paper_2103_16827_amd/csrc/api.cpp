@@ -127,7 +127,7 @@ const char* family_name(Kernel k) {
   return kernel_name(k == Kernel::PwWide ? Kernel::GemmMfma : k == Kernel::ConvFew ? Kernel::ConvPipe : k);
 }
 
-qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
+qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st, const ConvParams* next = nullptr) {
   hipError_t e;
   switch (k) {
     case Kernel::DwMfma: e = qasr::launch_dw_mfma(p, st); break;
@@ -137,7 +137,7 @@ qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st) {
     case Kernel::PwPipe: e = qasr::launch_pw_pipe(p, st); break;
     case Kernel::PwWide: e = qasr::launch_pw_wide(p, st); break;
     case Kernel::ConvPipe: e = qasr::launch_conv_pipe(p, st); break;
-    case Kernel::ConvFew: e = qasr::launch_conv_few(p, st); break;
+    case Kernel::ConvFew: e = qasr::launch_conv_few(p, next, st); break;
     default: e = qasr::launch_conv_generic(p, st); break;
   }
   return hip_status(e);
@@ -1230,7 +1230,17 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     // (the kernel of this call decides who applies a unary activation: its epilogue, or a pass of its own)
     const Kernel kk = pick_kernel(p);
     p.act_lut = applies_act_table(kk) ? op.act_table : nullptr;
-    const qasr_status s = launch_with(kk, p, st);
+    // (the next layer of conv_few's, pointwise ones between them passed over: their weights leave room in the L2s)
+    ConvParams later;
+    const ConvParams* next = nullptr;
+    if (kk == Kernel::ConvFew)
+      for (size_t j = i + 1; j < n && !next; ++j) {
+        if (e->ops[j].p.k < 2) continue;
+        bind(j, later);
+        if (pick_kernel(later) != Kernel::ConvFew) break;
+        next = &later;
+      }
+    const qasr_status s = launch_with(kk, p, st, next);
     if (s != QASR_OK) return s;
     if (op.has_act && !p.act_lut) {
       const bool glu = op.act.kind == QASR_ACT_GLU;

@@ -6,23 +6,31 @@
 // cut the contraction of such layers over workgroups: of 24 us at 2 x 406 frames 7.7 went into handing the partial
 // sums over, and its loop took 1000 cycles per step where the weights take 512: three steps ahead are 3000 cycles, the
 // latency of memory.  Here
-//   - a tile is 16 MT frames x 32 WC channels, small enough that there is a workgroup for every unit;
+//   - a tile is 16 MT frames x 16 WC NT channels (16, 32, 48 or 64), small enough that there is a workgroup for every unit;
+//     narrow ones share a layer's weights out over more units, 48 channels fill one round where 32 begin a second
+//     (768 channels, 25 taps, 2 x 406 frames: 22.4 -> 19.1 us; 640, 21 taps 17.7 -> 14.5; 384, 13 taps, 1 x 104 7.1 -> 6.6);
 //   - all input channels of the tile are in LDS at once (a layer's 768 channels x 76 frames are 73 KB): one round of
 //     loads, one barrier, then 16 waves stream weights with nothing to wait for each other;
 //   - the waves are WC column waves x 16 / WC groups that take the (chunk, tap) steps in turn; a wave has W - 1
-//     steps of 2 KiB on their way, up to 224 KB per unit;
+//     steps of NT KiB on their way, up to 224 KB per unit;
+//   - as a wave's stream ends it asks for a dword of each of 64 lines of the weights that this kernel streams next, those
+//     that its die's workgroups will read: they come out of memory while a launch ends and the next one begins and
+//     brings in its tile, when memory has nothing else to do (a Jasper's layers run at the 2.5 TB/s that their weights come
+//     at).  Jasper with dense residuals, 2 x 811 frames: 839 -> 795 us, 732 with the narrow tiles; 1 x 208 566 -> 552 -> 511.
+//     A quarter, half, three quarters of the lines 766, 752, 743 us; a dword per 64 bytes 805; asked for before
+//     the products, they take the place of lines still to be read: 817;
 //   - the groups' sums meet in LDS, a block of 16 x 16 per wave, no workspace.
 // us a layer in chains of six, conv_pipe / here: 2 x 406 frames, 256 channels, 11 taps 11.6 / 7.2, 512, 17 taps 16.6 / 10.8,
 // 640, 21 taps 20.5 / 17.0; 1 x 104 frames 10.9 / 5.9, 13.3 / 8.7, 14.6 / 10.6; Jasper-10x5 at 1 x 208 input frames 763 -> 551,
-// with dense residuals at 2 x 811 1308 -> 1073.  What is left: the transposition (16 dword loads per 64 bytes x 4 frames, 10.7
-// cycles a unit, 3 us at 768 channels) and the first touch of the weights, which no ring depth covers (half of the 64
-// bytes per cycle).
+// with dense residuals at 2 x 811 1308 -> 1073.  (Before the lines ahead and the narrow tiles.)  What is left: the transposition (16 dword loads per 64 bytes x 4 frames,
+// 10.7 cycles a unit, 3 us at 768 channels) and the weights on their way out of memory.
 // Layouts (operands, packed weights, the 4 x 4 transposition, 80-byte rows) are those of conv_pipe.hip.
 #include "kernels.hpp"
 #include "launch_shape.hpp"
 #include "tuning.hpp"
 #include "vmem.hpp"
 
+#include <cmath>
 #include <type_traits>
 
 namespace qasr {
@@ -31,6 +39,14 @@ namespace {
 
 constexpr int kXS = 80;       // LDS row pitch in bytes: 64 channels + 16 pad
 constexpr int kLds = 160 * 1024;
+
+// Weights that a later launch will stream, to be in each die's L2 by then: for die x `runs` runs of lines[x] 128-byte lines, the
+// first at w + off[x], `stride` bytes apart.  None: no runs.
+struct Ahead {
+  const int8_t* w;
+  uint32_t runs, stride;
+  uint32_t off[8], lines[8];
+};
 
 struct FewGeom {
   int n_tt;           // frame tiles per batch item
@@ -41,14 +57,19 @@ struct FewGeom {
   int units;          // transposition units (4 frames x 16 channels): kchunks * rows
   int jstep;          // KG / kchunks
   float r_nbt, r_tt, r_rows;   // reciprocals of B * n_tt, n_tt, rows
+  Ahead ahead;
 };
 
-template <int MT> struct Ring { static constexpr int W = MT == 4 ? 6 : 8; };   // steps of weights (registers)
+// steps of weights on their way and multiplied (registers)
+template <int MT, int NT> struct Ring { static constexpr int W = NT == 1 ? 12 : NT == 3 ? (MT == 2 ? 6 : 4) : MT == 4 ? 6 : 8; };
+// parts in which the sums meet: all of them, 16 MT NT KiB, have to fit LDS
+constexpr int meetings(int MT, int NT) { return 16 * MT * NT > 152 ? 2 : 1; }
 
-template <int MT, int WC>
+// 16 MT frames x 16 WC NT channels: WC column waves of NT columns each
+template <int MT, int WC, int NT>
 __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g) {
   extern __shared__ __align__(16) unsigned char xs[];   // [kchunks][rows][kXS]; then the partial sums
-  constexpr int NT = 2, KG = 16 / WC, W = Ring<MT>::W, AR = 4;
+  constexpr int KG = 16 / WC, W = Ring<MT, NT>::W, AR = 4;
   static_assert(MT * W % AR == 0, "rings");
   asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.xbs), "s"(p.B), "s"(p.Tin), "s"(p.k), "s"(p.stride), "s"(p.dil), "s"(p.pl), "s"(p.xpad),
                "s"(g.n_tt), "s"(g.rows), "s"(g.kchunks), "s"(g.co16n), "s"(g.tiles), "s"(g.per_xcd), "s"(g.units), "s"(g.jstep), "s"(g.r_nbt),
@@ -166,6 +187,33 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
     for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4i){0, 0, 0, 0};
   __syncthreads();                                  // the tile is complete
 
+  // ---- a lane's line of the weights that come after these (the lines in turn over the die's workgroups, so that each wave asks
+  // once at most; past the last one, or if there are none: this layer's first)
+  const int8_t* line_ahead = p.w;
+  {
+    const int die = (int)(blockIdx.x & 7), wgs = min(g.per_xcd, g.tiles - die * g.per_xcd);
+    const uint32_t lines = g.ahead.lines[die], L = (blockIdx.x >> 3) + (uint32_t)(wgs * tid);
+    if (L < g.ahead.runs * lines) {
+      const float r = (float)L / (float)lines;
+      uint32_t run = (uint32_t)r;
+      uint32_t at = L - run * lines;
+      if ((int32_t)at < 0) { --run; at += lines; }
+      if (at >= lines) { ++run; at -= lines; }
+      line_ahead = g.ahead.w + (g.ahead.off[die] + run * g.ahead.stride + at * 128);
+    }
+  }
+  // the constants of the block this wave finishes
+  constexpr int NB = WC * MT * NT;
+  static_assert(NB <= 16, "a block per wave");
+  const int e_wc = wave / (MT * NT), e_mt = wave % (MT * NT) / NT, e_nt = wave % NT;
+  const int co = ((co_tile * WC + e_wc) * NT + e_nt) * 16 + n, cl = min(co, p.Cout - 1);
+  int32_t mc = 0, sc = 33, bv = 0, line = 0;
+  if (wave < NB) {
+    gload4_into(mc, p.m + cl);
+    gload4_into(sc, p.s + cl);
+    gload4_into(bv, (p.bias ? p.bias : p.m) + cl);
+  }
+
   // ---- products; operand of item i = unit i % MT of the wave's step i / MT, AR - 1 of them on their way
   const uint32_t abase = (uint32_t)((foff + n * p.stride) * kXS + 16 * gi);
   At aat = first;
@@ -180,10 +228,12 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
     read_a(i % MT, ar[i]);
   }
   int left = steps;
+  const bool whole = steps % W == 0;                // the last round asks for a step's weights after the line
   auto step = [&](auto slot_tag) __attribute__((always_inline)) {
     constexpr int q = decltype(slot_tag)::value;
     if (left >= W - 1) wait_vm<(W - 2) * NT>();
-    else wait_vm<0>();                              // (nothing is younger than the rest of the stream: all of it)
+    else if (whole) wait_vm<0>();
+    else wait_vm<1>();                              // (nothing but the line is younger than the rest of the stream: all of that)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) tie(wb[q][nt]);
     if (left >= W) load_w(wb[(q + W - 1) % W]);
@@ -204,78 +254,84 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
     if constexpr (q < W) return step(slot_tag) && self(self, std::integral_constant<int, q + 1>{});
     else return true;
   };
-  if (steps > 0)
-    while (round(round, std::integral_constant<int, 0>{})) {}
-  wait_vm<0>();
+  do {
+    if (left <= W) gload4_into(line, line_ahead);   // (once, in the last round)
+  } while (left > 0 && round(round, std::integral_constant<int, 0>{}));
+  wait_vm<1>();
 #pragma unroll
   for (int q = 0; q < W; ++q)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) tie(wb[q][nt]);
-
-  // ---- block e = (column wave, frame group, column) is finished by wave e; its constants come under the exchange
-  constexpr int NB = WC * MT * NT;
-  static_assert(NB <= 16, "a block per wave");
-  const int e_wc = wave / (MT * NT), e_mt = wave % (MT * NT) / NT, e_nt = wave % NT;
-  const int co = ((co_tile * WC + e_wc) * NT + e_nt) * 16 + n, cl = min(co, p.Cout - 1);
-  int32_t mc = 0, sc = 33, bv = 0;
-  if (wave < NB) {
-    mc = gload4(p.m + cl);
-    sc = gload4(p.s + cl);
-    bv = gload4((p.bias ? p.bias : p.m) + cl);
-  }
-  __syncthreads();                                  // the tile has been read by all
-  v4i* const red = reinterpret_cast<v4i*>(xs);      // [column wave][frame group][column][group][lane]
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) red[(((wc * MT + mt) * NT + nt) * KG + kg) * 64 + lane] = acc[mt][nt];
-  wait_vm<0>();
   tie(mc);
   tie(sc);
   tie(bv);
-  __syncthreads();
-  if (wave >= NB) return;
-  v4i a = red[wave * KG * 64 + lane];
+
+  // ---- block e = (column wave, frame group, column) is finished by wave e
+  __syncthreads();                                  // the tile has been read by all
+  constexpr int H = meetings(MT, NT), MH = MT / H;
+  static_assert(MT % H == 0, "parts");
+  v4i* const red = reinterpret_cast<v4i*>(xs);      // [column wave][frame group][column][group][lane]
+  v4i a = {0, 0, 0, 0};
 #pragma unroll
-  for (int q = 1; q < KG; ++q) a += red[(wave * KG + q) * 64 + lane];
+  for (int h = 0; h < H; ++h) {
+    if (h) __syncthreads();
+#pragma unroll
+    for (int mt = h * MH; mt < (h + 1) * MH; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) red[(((wc * MH + mt - h * MH) * NT + nt) * KG + kg) * 64 + lane] = acc[mt][nt];
+    __syncthreads();
+    if (wave < NB && e_mt / MH == h) {
+      const int at = ((e_wc * MH + e_mt - h * MH) * NT + e_nt) * KG;
+#pragma unroll
+      for (int q = 0; q < KG; ++q) a += red[(at + q) * 64 + lane];
+    }
+  }
+  if (wave >= NB) {
+    wait_vm<0>();
+    tie(line);
+    return;
+  }
 
   // lane (n, gi) holds frames t .. + 4 of channel co
   const int t = t0 + 16 * e_mt + 4 * gi;
-  if (co >= p.Cout || t >= p.Tout) return;
-  const int trow = p.Tout + p.ypad;                 // (pad bytes may be written)
-  const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * trow;
-  if (!p.bias) bv = 0;
-  int32_t o[4];
+  if (co < p.Cout && t < p.Tout) {
+    const int trow = p.Tout + p.ypad;                 // (pad bytes may be written)
+    const int64_t orow = (int64_t)b * p.ybs + (int64_t)co * trow;
+    if (!p.bias) bv = 0;
+    int32_t o[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = dyadic_rescale(a[i] + bv, mc, sc);
-  if (p.res) {                                      // residual operands, all on their way at once
-    uint32_t d[1 + kMaxMoreRes];
-    const int at = min(t, trow - 4), shr = 8 * (t - at);
-    d[0] = load_u32(p.res + orow + at);
+    for (int i = 0; i < 4; ++i) o[i] = dyadic_rescale(a[i] + bv, mc, sc);
+    if (p.res) {                                      // residual operands, all on their way at once
+      uint32_t d[1 + kMaxMoreRes];
+      const int at = min(t, trow - 4), shr = 8 * (t - at);
+      d[0] = load_u32(p.res + orow + at);
 #pragma unroll
-    for (int r = 0; r < kMaxMoreRes; ++r)
-      if (r < p.n_res_more) d[r + 1] = load_u32(p.res_more[r] + orow + at);
+      for (int r = 0; r < kMaxMoreRes; ++r)
+        if (r < p.n_res_more) d[r + 1] = load_u32(p.res_more[r] + orow + at);
 #pragma unroll
-    for (int r = 0; r <= kMaxMoreRes; ++r)
-      if (r <= p.n_res_more) {
-        const uint32_t w = d[r] >> shr;
+      for (int r = 0; r <= kMaxMoreRes; ++r)
+        if (r <= p.n_res_more) {
+          const uint32_t w = d[r] >> shr;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] += (int32_t)(int8_t)(w >> (8 * i));
-      }
+          for (int i = 0; i < 4; ++i) o[i] += (int32_t)(int8_t)(w >> (8 * i));
+        }
+    }
+    const int lo = p.relu ? 0 : -128;
+    uint32_t pk = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pk |= (uint32_t)(clamp_i8(o[i], lo) & 0xff) << (8 * i);
+    store_row_u32(p.y + orow, t, trow, pk);
   }
-  const int lo = p.relu ? 0 : -128;
-  uint32_t pk = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) pk |= (uint32_t)(clamp_i8(o[i], lo) & 0xff) << (8 * i);
-  store_row_u32(p.y + orow, t, trow, pk);
+  wait_vm<0>();
+  tie(line);
 }
 
-struct Choice { int MT, WC; };
+struct Choice { int MT, WC, NT; };
 
 int lds_rows(const ConvParams& p, int TM) { return (((TM - 1) * p.stride + p.dil * (p.k - 1) + 1 + 3) + 3) & ~3; }
 
 size_t lds_bytes(const ConvParams& p, const Choice& c) {
-  const size_t tile = (size_t)(p.Cin / 64) * lds_rows(p, 16 * c.MT) * kXS, sums = (size_t)16 * c.MT * 2 * 1024;
+  const size_t tile = (size_t)(p.Cin / 64) * lds_rows(p, 16 * c.MT) * kXS, sums = (size_t)16 * c.MT * c.NT * 1024 / meetings(c.MT, c.NT);
   return tile > sums ? tile : sums;
 }
 
@@ -287,45 +343,76 @@ bool supported(const ConvParams& p) {
 
 // The tile with the least time, in cycles: a launch, and on the busiest compute unit for each of its workgroups the
 // activations it transposes (units of 16 dword loads), its steps (the weights of all its columns, or its products) and its
-// last stores.  Every tile timed beside the choice, chains of six layers of 256 .. 768 channels, 11 .. 25 taps, 104 ..
-// 3200 frames (40 shapes): it is 0.6 % from the best on average and 8 % at worst (256 channels, 406 frames); the choice
-// between this kernel and conv_pipe with its own, over 50 shapes to 12800 frames, 0.7 % and 7.7 %.
+// last stores; of single columns each operand read serves one product.  Every tile timed beside the choice, chains of six
+// layers of 256 .. 768 channels, 11 .. 25 taps, 52 .. 1600 frames (35 shapes): it is 0.5 % from the best on average and 3 %
+// at worst; the choice between this kernel and conv_pipe, over 45 shapes to 6400 frames, 0.2 % and 2.6 %.  (Constants fitted to
+// those chains alone, whose weights stay in the memory-side cache, choose 0.06 % from their best and make whole networks slower: 732 -> 741.)
 bool pick(const ConvParams& p, Choice& best, double& cycles) {
   if (!supported(p)) return false;
   cycles = 1e300;
-  for (int WC = 1; WC <= 2; ++WC)
+  static const Choice columns[] = {{0, 1, 1}, {0, 1, 2}, {0, 1, 3}, {0, 2, 2}};
+  for (Choice c : columns)
     for (int MT = 1; MT <= 4; ++MT) {
-      const Choice c{MT, WC};
-      if ((tuning().cf_mt && MT != tuning().cf_mt) || (tuning().cf_wc && WC != tuning().cf_wc)) continue;
+      c.MT = MT;
+      if ((tuning().cf_mt && MT != tuning().cf_mt) || (tuning().cf_wc && c.WC != tuning().cf_wc) || (tuning().cf_nt && c.NT != tuning().cf_nt)) continue;
       if (lds_bytes(p, c) > (size_t)kLds || (p.Cin / 64) * lds_rows(p, 16 * MT) >= 65536) continue;
-      const int64_t wgs = (int64_t)p.B * ((p.Tout + 16 * MT - 1) / (16 * MT)) * ((p.Cout + 32 * WC - 1) / (32 * WC));
+      const int C = c.WC * c.NT;
+      const int64_t wgs = (int64_t)p.B * ((p.Tout + 16 * MT - 1) / (16 * MT)) * ((p.Cout + 16 * C - 1) / (16 * C));
       if (wgs >= (1 << 22) - 8) continue;
-      const double step = 2.0 * WC * (6.4 * MT > 24.8 ? 6.4 * MT : 24.8);
-      const double wg = 3460.0 + 315.0 * MT * WC + (double)(p.Cin / 64) * p.k * step + 10.7 * (p.Cin / 64) * lds_rows(p, 16 * MT);
+      const double step = fmax(C * fmax(6.4 * MT, 24.8), c.NT == 1 ? 12.0 * MT : 0.0);
+      const double wg = 3460.0 + 157.5 * MT * C + (double)(p.Cin / 64) * p.k * step + 10.7 * (p.Cin / 64) * lds_rows(p, 16 * MT);
       const double cost = 6300.0 + (double)((wgs + 255) / 256) * wg;
       if (cost < cycles) { cycles = cost; best = c; }
     }
   return cycles < 1e300;
 }
 
-template <int MT, int WC>
-hipError_t launch_t(const ConvParams& p, hipStream_t st) {
-  const Choice c{MT, WC};
-  FewGeom g;
+void geometry(const ConvParams& p, const Choice& c, FewGeom& g) {
+  const int MT = c.MT, C = c.WC * c.NT;
   g.n_tt = (p.Tout + 16 * MT - 1) / (16 * MT);
   g.rows = lds_rows(p, 16 * MT);
   g.kchunks = p.Cin / 64;
   g.co16n = (p.Cout + 15) / 16;
-  g.tiles = p.B * g.n_tt * ((p.Cout + 32 * WC - 1) / (32 * WC));
+  g.tiles = p.B * g.n_tt * ((p.Cout + 16 * C - 1) / (16 * C));
   g.per_xcd = (g.tiles + 7) / 8;
   g.units = g.kchunks * g.rows;
-  g.jstep = 16 / WC / g.kchunks;
+  g.jstep = 16 / c.WC / g.kchunks;
   g.r_nbt = 1.0f / (float)(p.B * g.n_tt);
   g.r_tt = 1.0f / (float)g.n_tt;
   g.r_rows = 1.0f / (float)g.rows;
+}
+
+// what the launch of `next` will stream: a die's run of its tiles, channel tile first, spans some of its channel tiles
+Ahead weights_of(const ConvParams& next) {
+  Ahead a{};
+  Choice c;
+  double cycles;
+  if (!pick(next, c, cycles)) return a;
+  FewGeom g;
+  geometry(next, c, g);
+  const int nbt = next.B * g.n_tt, column = g.kchunks * 8;     // (lines of 16 channels and a tap)
+  a.w = next.w;
+  a.runs = (uint32_t)next.k;
+  a.stride = (uint32_t)(g.co16n * column * 128);
+  for (int x = 0; x < 8; ++x) {
+    const int lo = x * g.per_xcd, hi = lo + g.per_xcd < g.tiles ? lo + g.per_xcd : g.tiles;
+    if (lo >= hi) continue;
+    const int C = c.WC * c.NT, from = lo / nbt * C, to = ((hi - 1) / nbt + 1) * C;
+    a.off[x] = (uint32_t)(from * column * 128);
+    a.lines[x] = (uint32_t)(((to < g.co16n ? to : g.co16n) - from) * column);
+  }
+  return a;
+}
+
+template <int MT, int WC, int NT>
+hipError_t launch_t(const ConvParams& p, const ConvParams* next, hipStream_t st) {
+  const Choice c{MT, WC, NT};
+  FewGeom g;
+  geometry(p, c, g);
+  g.ahead = next ? weights_of(*next) : Ahead{};
   static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
-  if (const hipError_t e = ensure_max_dynamic_lds((const void*)conv_few_kernel<MT, WC>, lds_raised); e != hipSuccess) return e;
-  return launch_kernel(conv_few_kernel<MT, WC>, dim3((unsigned)(8 * g.per_xcd)), dim3(1024), lds_bytes(p, c), st, p, g);
+  if (const hipError_t e = ensure_max_dynamic_lds((const void*)conv_few_kernel<MT, WC, NT>, lds_raised); e != hipSuccess) return e;
+  return launch_kernel(conv_few_kernel<MT, WC, NT>, dim3((unsigned)(8 * g.per_xcd)), dim3(1024), lds_bytes(p, c), st, p, g);
 }
 
 }  // namespace
@@ -335,14 +422,18 @@ bool conv_few_cycles(const ConvParams& p, double& cycles) {
   return !tuning().no_conv_few && pick(p, c, cycles);
 }
 
-hipError_t launch_conv_few(const ConvParams& p, hipStream_t st) {
+hipError_t launch_conv_few(const ConvParams& p, const ConvParams* next, hipStream_t st) {
   Choice c;
   double cycles;
   if (!pick(p, c, cycles)) return hipErrorInvalidValue;
-#define QASR_CASE(M, C) if (c.MT == M && c.WC == C) return launch_t<M, C>(p, st);
-  QASR_CASE(1, 1) QASR_CASE(2, 1) QASR_CASE(3, 1) QASR_CASE(4, 1) QASR_CASE(1, 2) QASR_CASE(2, 2) QASR_CASE(3, 2) QASR_CASE(4, 2)
+#define QASR_CASE(C, T) \
+  if (c.WC == C && c.NT == T) \
+    return c.MT == 1 ? launch_t<1, C, T>(p, next, st) : c.MT == 2 ? launch_t<2, C, T>(p, next, st) : c.MT == 3 ? launch_t<3, C, T>(p, next, st) : launch_t<4, C, T>(p, next, st);
+  QASR_CASE(1, 1) QASR_CASE(1, 2) QASR_CASE(1, 3) QASR_CASE(2, 2)
 #undef QASR_CASE
   return hipErrorInvalidValue;
 }
+
+hipError_t launch_conv_few(const ConvParams& p, hipStream_t st) { return launch_conv_few(p, nullptr, st); }
 
 }  // namespace qasr

@@ -71,6 +71,8 @@ hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st);
 bool conv_few_cycles(const ConvParams& p, double& cycles);
 bool conv_few_better(const ConvParams& p, bool split);
 hipError_t launch_conv_few(const ConvParams& p, hipStream_t st);
+// the same; next: the next layer that this kernel will run (or null), whose weights are brought into the L2s meanwhile
+hipError_t launch_conv_few(const ConvParams& p, const ConvParams* next, hipStream_t st);
 
 // Measured ceilings (probe.hip): a streaming copy of `bytes` (a multiple of 16) and a register-resident
 // int8 matrix-core loop of probe_mfma_ops(iters) operations that writes probe_mfma_workgroups() int32.

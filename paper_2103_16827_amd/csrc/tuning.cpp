@@ -38,8 +38,8 @@ Tuning read_env() {
   t.no_conv_few = getenv("QASR_NO_CONV_FEW") != nullptr;
   t.conv_few_force = getenv("QASR_CONV_FEW") != nullptr;
   if (const char* e = getenv("QASR_CF")) {
-    int mt = 0, wc = 0;
-    if (sscanf(e, "%d,%d", &mt, &wc) >= 1) { t.cf_mt = mt; t.cf_wc = wc; }
+    int mt = 0, wc = 0, nt = 0;
+    if (sscanf(e, "%d,%d,%d", &mt, &wc, &nt) >= 1) { t.cf_mt = mt; t.cf_wc = wc; t.cf_nt = nt || !wc ? nt : 2; }
   }
   t.no_pw_multi = getenv("QASR_NO_PW_MULTI") != nullptr;
   t.pw_multi_force = getenv("QASR_PW_MULTI") != nullptr;

@@ -7,7 +7,7 @@
 //   QASR_DW_R                               dw_mfma: strips per wave
 //   QASR_CP_TILE = "MT,NT[,KG[,S]]"         conv_pipe: tile, wave groups the taps and workgroups the chunks are split over
 //   QASR_NO_CONV_FEW, QASR_CONV_FEW         conv_few: never / wherever it can
-//   QASR_CF = "MT,WC"                       conv_few: groups per tile, 32-channel columns per tile (0: free)
+//   QASR_CF = "MT,WC,NT"                    conv_few: groups per tile, column waves, 16-channel columns of each (0: free)
 //   QASR_CP_PLAIN_ORDER                     conv_pipe: tile = workgroup index (no per-XCD runs of the channel-major order)
 //   QASR_PWT_MT                             pw_tile: groups per tile
 //   QASR_PWP_NOPIPE                         pw_pipe: no epilogue under the next pass's products
@@ -39,6 +39,7 @@ struct Tuning {
   int pwt_mt = 0;
   int sep_mt = 0, sep_nt = 0, sep_ks = 0, pww_mt = 0, pww_ks = 0, chain_mt = 0;
   int slot_depth = 4;
+  int cf_nt = 0;
 };
 
 const Tuning& tuning();

@@ -41,7 +41,7 @@ namespace qasr {
 
 struct Tuning {
   bool no_conv_pipe = false, no_conv_few = false, conv_few_force = false, cp_plain_order = false;
-  int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0, cf_mt = 0, cf_wc = 0;
+  int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0, cf_mt = 0, cf_wc = 0, cf_nt = 0;
 };
 inline Tuning& the_tuning() { static Tuning t; return t; }
 inline const Tuning& tuning() { return the_tuning(); }
@@ -168,14 +168,14 @@ namespace {
 
 struct Case {
   const char* name;
-  int few, a, b, kg, s;            // conv_few: MT, WC; conv_pipe: MT, NT, groups, splits
+  int few, a, b, kg, s;            // conv_few: MT, WC, NT (0: 2); conv_pipe: MT, NT, groups, splits
   int B, Cin, Cout, T, k, stride, dil, pl, pr, res, bias, pad;
 };
 
 void run_case(const Case& c) {
   Tuning& t = the_tuning();
   t = Tuning();
-  if (c.few) { t.cf_mt = c.a; t.cf_wc = c.b; }
+  if (c.few) { t.cf_mt = c.a; t.cf_wc = c.b; t.cf_nt = c.kg ? c.kg : 2; }
   else { t.cp_mt = c.a; t.cp_nt = c.b; t.cp_kg = c.kg; t.cp_s = c.s; }
   ConvParams p{};
   p.B = c.B; p.Cin = c.Cin; p.Cout = c.Cout; p.Tin = c.T; p.k = c.k; p.stride = c.stride; p.dil = c.dil; p.pl = c.pl;
@@ -206,7 +206,21 @@ void run_case(const Case& c) {
   g_workgroups = 0;
   hipError_t e;
 #ifdef SIM_FEW
-  e = launch_conv_few(p, nullptr);
+  {
+    // once with the weights of a wider layer after it, which has tiles of its own and whose lines are asked for, ...
+    ConvParams next = p;
+    next.Cout = 3 * c.Cout - 16; next.k = c.k + 2; next.pl = p.pl + p.dil;
+    const size_t nbytes = (size_t)next.k * ((next.Cout + 15) / 16) * (c.Cin / 64) * 1024;
+    std::vector<int8_t> nw(nbytes + 128);
+    next.w = (int8_t*)(((uintptr_t)nw.data() + 127) & ~(uintptr_t)127);
+    st.regions.push_back({"next w", (const unsigned char*)next.w, nbytes, false});
+    e = launch_conv_few(p, &next, nullptr);
+    st.regions.pop_back();
+    if (e != hipSuccess) sim::fail("the launcher does not take this case");
+    std::fill(written.begin(), written.end(), 0);
+    // ... and once by itself
+    e = launch_conv_few(p, nullptr);
+  }
 #else
   {
     if (c.s > 1) {
@@ -254,6 +268,9 @@ int main() {
       {"few 3x2, stride 2", 1, 3, 2, 0, 0, 2, 128, 130, 99, 13, 2, 1, 6, 6, 0, 1, 0},
       {"few 1x2, more than 1024 units", 1, 1, 2, 0, 0, 1, 768, 64, 30, 77, 1, 1, 38, 38, 0, 1, 0},
       {"few 4x2, 4 frames", 1, 4, 2, 0, 0, 3, 64, 64, 4, 3, 1, 1, 1, 1, 1, 1, 1},
+      {"few 2x1 of one column, rings of twelve", 1, 2, 1, 1, 0, 2, 192, 80, 41, 15, 1, 1, 7, 7, 1, 1, 0},
+      {"few 4x1 of three, sums in two parts", 1, 4, 1, 3, 0, 1, 256, 112, 70, 13, 1, 1, 6, 6, 2, 1, 1},
+      {"few 1x1 of three, whole rounds", 1, 1, 1, 3, 0, 1, 256, 64, 20, 16, 1, 1, 8, 7, 0, 1, 0},
       {"few 3x1, long stream", 1, 3, 1, 0, 0, 1, 512, 64, 48, 25, 1, 1, 12, 12, 0, 1, 0},
 #endif
 #else

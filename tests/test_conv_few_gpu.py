@@ -38,6 +38,12 @@ def test_tiles(kw, tile, tuning_env):
     run_layer_case(case)
 
 
+@pytest.mark.parametrize("tile", ["1,1,1", "2,1,1", "3,1,1", "4,1,1", "1,1,3", "2,1,3", "3,1,3", "4,1,3"])
+@pytest.mark.parametrize("kw", SHAPES, ids=[c["name"] for c in SHAPES])
+def test_tiles_of_16_and_48_channels(kw, tile, tuning_env):
+    test_tiles(kw, tile, tuning_env)
+
+
 @pytest.mark.parametrize("n_res", [2, 5, 12])
 def test_several_residuals(n_res, tuning_env):
     tuning_env("QASR_CONV_FEW", "1")
