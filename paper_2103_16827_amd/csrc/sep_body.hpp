@@ -14,8 +14,9 @@
 // With a 4-row Toeplitz operand A[m, kappa] = w[kappa - m - r] (4 kappa per step) and
 // B[kappa, n] = x[4 n + kappa], block b, column n, row m yields frame 16 q + 4 n + m of channel b: a lane
 // ends with 4 consecutive frames of one channel, ready to be packed.  Against the 16-row form of
-// dw_pipe.hip the operand is 4 instead of 16 bytes per tap, small enough to be read as a prebuilt image,
-// and a tile of a few groups wastes no columns (16 x 16 x 64 wants 256 frames of a channel).  It runs
+// dw_pipe.hip the operand is 4 instead of 16 bytes per tap, small enough to be made from a channel's row of weights
+// in LDS by one byte permutation per dword, and a tile of a few groups wastes no columns (16 x 16 x 64 wants 256 frames of a
+// channel).  (The operand as a prebuilt image is four times the bytes through the address path: 15x5, 32 x 1600 1208 -> 1172 us.)  It runs
 // at 10 cycles per product, (k + 3) / 4 products per 16 frames of 16 channels: at k = 75 that is 5 us
 // for 512 channels x 112 frames.  The window dwords are read one by one: a 16-byte LDS read at a 4-byte aligned
 // address measured 59 cycles against 16.
