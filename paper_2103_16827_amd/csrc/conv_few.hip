@@ -9,8 +9,14 @@
 //   - a tile is 16 MT frames x 16 WC NT channels (16, 32, 48 or 64), small enough that there is a workgroup for every unit;
 //     narrow ones share a layer's weights out over more units, 48 channels fill one round where 32 begin a second
 //     (768 channels, 25 taps, 2 x 406 frames: 22.4 -> 19.1 us; 640, 21 taps 17.7 -> 14.5; 384, 13 taps, 1 x 104 7.1 -> 6.6);
-//   - all input channels of the tile are in LDS at once (a layer's 768 channels x 76 frames are 73 KB): one round of
+//   - all input channels of the tile are in LDS at once (a layer's 768 channels x 96 frames are 92 KB): one round of
 //     loads, one barrier, then 16 waves stream weights with nothing to wait for each other;
+//   - they come 8 frames per lane and request, from multiples of 8 on: a unit of the chip takes as long for 4 bytes per lane, and
+//     a thread has one unit at most (of 4 frames a 768-channel tile had 1104, and the second round waited for the
+//     weights too).  us a layer in chains of six, units of 4 / 8 frames: 1 x 406 frames, 256 channels, 11 taps 6.38 / 5.97, 512, 17 taps
+//     9.95 / 9.42, 768, 25 taps 15.7 / 14.9; 2 x 406 7.10 / 6.55, 10.9 / 10.7, 19.8 / 18.8.  From multiples of 4 on, where half of the
+//     requests are not aligned, 8.5, 11.7, 16.1; 9.2, 12.3, 19.3.  Rows at odd addresses, 2 x 811 frames of one layer: 256 channels 7.41 / 6.56,
+//     640, 21 taps 25.7 / 24.7;
 //   - the waves are WC column waves x 16 / WC groups that take the (chunk, tap) steps in turn; a wave has W - 1
 //     steps of NT KiB on their way, up to 224 KB per unit;
 //   - as a wave's stream ends it asks for a dword of each of 64 lines of the weights that this kernel streams next, those
@@ -22,8 +28,8 @@
 //   - the groups' sums meet in LDS, a block of 16 x 16 per wave, no workspace.
 // us a layer in chains of six, conv_pipe / here: 2 x 406 frames, 256 channels, 11 taps 11.6 / 7.2, 512, 17 taps 16.6 / 10.8,
 // 640, 21 taps 20.5 / 17.0; 1 x 104 frames 10.9 / 5.9, 13.3 / 8.7, 14.6 / 10.6; Jasper-10x5 at 1 x 208 input frames 763 -> 551,
-// with dense residuals at 2 x 811 1308 -> 1073.  (Before the lines ahead and the narrow tiles.)  What is left: the transposition (16 dword loads per 64 bytes x 4 frames,
-// 10.7 cycles a unit, 3 us at 768 channels) and the weights on their way out of memory.
+// with dense residuals at 2 x 811 1308 -> 1073.  (Before the lines ahead, the narrow tiles and the units of 8 frames.)  What is left: the weights on their way
+// out of memory and through the unit's 64 bytes per cycle, and the transposition (about 8 cycles per 64 bytes, 4 us at 768 channels).
 // Layouts (operands, packed weights, the 4 x 4 transposition, 80-byte rows) are those of conv_pipe.hip.
 #include "kernels.hpp"
 #include "launch_shape.hpp"
@@ -41,7 +47,7 @@ constexpr int kXS = 80;       // LDS row pitch in bytes: 64 channels + 16 pad
 constexpr int kLds = 160 * 1024;
 
 // Weights that a later launch will stream, to be in each die's L2 by then: for die x `runs` runs of lines[x] 128-byte lines, the
-// first at w + off[x], `stride` bytes apart.  None: no runs.
+// first at w + off[x], `stride` bytes apart.  None: no runs, but w can be read all the same.
 struct Ahead {
   const int8_t* w;
   uint32_t runs, stride;
@@ -50,13 +56,13 @@ struct Ahead {
 
 struct FewGeom {
   int n_tt;           // frame tiles per batch item
-  int rows;           // LDS rows per chunk (input frames incl. halo, rounded to 4)
+  int rows;           // LDS rows per chunk (input frames incl. halo, rounded to 8)
   int kchunks;        // Cin / 64
   int co16n;          // ceil(Cout / 16)
   int tiles, per_xcd;
-  int units;          // transposition units (4 frames x 16 channels): kchunks * rows
+  int units;          // transposition units (8 frames x 16 channels): kchunks * rows / 2 (<= 1024: the rows fit LDS)
   int jstep;          // KG / kchunks
-  float r_nbt, r_tt, r_rows;   // reciprocals of B * n_tt, n_tt, rows
+  float r_nbt, r_tt, r_rows;   // reciprocals of B * n_tt, n_tt, rows / 2
   Ahead ahead;
 };
 
@@ -85,7 +91,7 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
   const int co_tile = divide_uniform24(v, nbt, g.r_nbt), bt = v - co_tile * nbt;
   const int b = divide_uniform24(bt, g.n_tt, g.r_tt), t0 = (bt - b * g.n_tt) * (16 * MT);
   const int f0 = t0 * p.stride - p.pl;              // first input frame the tile reads
-  const int fa = f0 & ~3, foff = f0 - fa;           // rounded down to a dword (also if negative)
+  const int fa = f0 & ~7, foff = f0 - fa;           // rounded down to eight frames (also if negative)
   const int xpitch = p.Tin + p.xpad;
 
   // ---- weights: steps kg, kg + KG, ... of the flat list (tap, chunk), in the order of the packed weights: together
@@ -115,70 +121,76 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
     advance(wat);
   };
 
-  // ---- activations: unit = frames 4 fq .. + 4 of the 16 channels of column group cg of chunk kc (conv_pipe.hip);
-  // unit index = (kc * 4 + cg) * (rows / 4) + fq
-  const int nfq = g.rows >> 2;
+  // ---- activations: unit = frames 8 fq .. + 8 of the 16 channels of column group cg of chunk kc (conv_pipe.hip), one per thread
+  // at most; unit index = (kc * 4 + cg) * (rows / 8) + fq.  16 lanes with consecutive fq write rows 640 bytes apart, which is two
+  // of 16 sets of banks: they write their eight rows in an order turned by (fq >> 1) & 7, within the half by the
+  // byte selectors and between the halves by a swap, and cover all banks.
+  const int nfq = g.rows >> 3;
   const int8_t* const xb = p.x + (int64_t)b * p.xbs;
-  int32_t xr[4][4];
-  int u_fq, u_cg, u_kc, u_f;
-  bool u_on;
-  auto issue_unit = [&](int unit) __attribute__((always_inline)) {
-    // (unit < 2^16: the estimate of unit / rows, then of the rest by rows / 4, is off by one at most)
-    const int uu = min(unit, g.units - 1);
-    u_kc = (int)((float)uu * g.r_rows);
-    int r = uu - u_kc * g.rows;
-    if (r < 0) { --u_kc; r += g.rows; }
-    if (r >= g.rows) { ++u_kc; r -= g.rows; }
-    u_cg = (r >= nfq ? 1 : 0) + (r >= 2 * nfq ? 1 : 0) + (r >= 3 * nfq ? 1 : 0);
-    u_fq = r - u_cg * nfq;
-    u_f = fa + 4 * u_fq;
-    u_on = u_f >= 0 && u_f < p.Tin;
-    // (a unit at a row's end is loaded from inside the row, those outside any frame from its start, and dropped)
-    const int at = u_on ? min(u_f, p.Tin - 4) : 0;
-    const uint32_t off = (uint32_t)((64 * u_kc + 8 * u_cg) * xpitch + at);   // (Cin x pitch < 2^31)
+  v2i xr[4][4];
+  // (unit < 2^16: the estimate of unit / (rows / 2) is off by one at most)
+  const int uu = min(tid, g.units - 1), half_rows = g.rows >> 1;
+  int u_kc = (int)((float)uu * g.r_rows), u_r = uu - u_kc * half_rows;
+  if (u_r < 0) { --u_kc; u_r += half_rows; }
+  if (u_r >= half_rows) { ++u_kc; u_r -= half_rows; }
+  const int u_cg = (u_r >= nfq ? 1 : 0) + (u_r >= 2 * nfq ? 1 : 0) + (u_r >= 3 * nfq ? 1 : 0);
+  const int u_fq = u_r - u_cg * nfq, u_f = fa + 8 * u_fq;
+  // (what lies over a row's end is loaded from inside the row and moved, what lies outside dropped; rows shorter than eight frames are
+  // loaded to their end, from the row before on, the first ones from their start)
+  int u_at = max(min(u_f, p.Tin - 8), min(p.Tin - 8, 0));
+  if (u_kc + u_cg == 0) u_at = max(u_at, 0);
+  if (64 * wave < g.units) {                        // (uniform)
+    const uint32_t off = (uint32_t)((64 * u_kc + 8 * u_cg) * xpitch + u_at);   // (Cin x pitch < 2^31)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) xr[i][e] = gload4(xb + (int64_t)(4 * ((i & 1) + 8 * (i >> 1)) + e) * xpitch, off);
-  };
-  auto commit_unit = [&](int unit) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) tie(xr[i][e]);
-    if (unit >= g.units) return;
-    const int rot = (u_fq >> 2) & 3, shr = u_on ? 8 * (u_f - min(u_f, p.Tin - 4)) : 0;
-    const uint32_t f0s = rot, f1s = (rot + 1) & 3, f2s = (rot + 2) & 3, f3s = (rot + 3) & 3;
-    const uint32_t sel_lo = f0s | ((4 + f0s) << 8) | (f1s << 16) | ((4 + f1s) << 24);
-    const uint32_t sel_hi = f2s | ((4 + f2s) << 8) | (f3s << 16) | ((4 + f3s) << 24);
-    unsigned char* const dst = xs + (u_kc * g.rows + 4 * u_fq) * kXS + 16 * u_cg;
-    uint32_t c[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint32_t r[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) r[e] = u_on ? (uint32_t)xr[i][e] >> shr : 0u;
-      const uint32_t lo01 = __builtin_amdgcn_perm(r[1], r[0], sel_lo), hi01 = __builtin_amdgcn_perm(r[1], r[0], sel_hi);
-      const uint32_t lo23 = __builtin_amdgcn_perm(r[3], r[2], sel_lo), hi23 = __builtin_amdgcn_perm(r[3], r[2], sel_hi);
-      c[i][0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
-      c[i][1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
-      c[i][2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
-      c[i][3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      *reinterpret_cast<v4i*>(dst + ((e + rot) & 3) * kXS) = (v4i){(int)c[0][e], (int)c[1][e], (int)c[2][e], (int)c[3][e]};
-  };
-  issue_unit(tid);
+      for (int e = 0; e < 4; ++e) xr[i][e] = gload8(xb + (int64_t)(4 * ((i & 1) + 8 * (i >> 1)) + e) * xpitch, off);
+  }
+  // byte selectors: a half's frames where they lie in the eight, zeros for those that there are not
+  const bool swap = (u_fq >> 3) & 1;
+  uint32_t half[2];
+  {
+    const int there = u_f >= 0 ? min(p.Tin - u_f, 8) : 0;           // (u_f is a multiple of 8)
+    const uint64_t kept = there > 0 ? ~0ull >> (64 - 8 * there) : 0ull;
+    const uint32_t lo = (uint32_t)kept, hi = (uint32_t)(kept >> 32), up = 0x01010101u * (uint32_t)(u_f - u_at);
+    const uint32_t s_lo = ((0x03020100u + up) & lo) | (0x0c0c0c0cu & ~lo), s_hi = ((0x07060504u + up) & hi) | (0x0c0c0c0cu & ~hi);
+    half[0] = swap ? s_hi : s_lo;
+    half[1] = swap ? s_lo : s_hi;
+  }
 #pragma unroll
   for (int q = 0; q < W - 1; ++q)
     if (q < steps) load_w(wb[q]);
   wait_vm_dyn(min(steps, W - 1) * NT);
-  commit_unit(tid);
-  for (int u = tid + 1024; u - tid < g.units; u += 1024) {   // (uniform)
-    issue_unit(u);
-    wait_vm<0>();
-    commit_unit(u);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tie(xr[i][e]);
+  if (tid < g.units) {
+    const int rot = (u_fq >> 1) & 3;
+    const uint32_t f0s = rot, f1s = (rot + 1) & 3, f2s = (rot + 2) & 3, f3s = (rot + 3) & 3;
+    const uint32_t sel_lo = f0s | ((4 + f0s) << 8) | (f1s << 16) | ((4 + f1s) << 24);
+    const uint32_t sel_hi = f2s | ((4 + f2s) << 8) | (f3s << 16) | ((4 + f3s) << 24);
+    unsigned char* const unit = xs + (u_kc * g.rows + 8 * u_fq) * kXS + 16 * u_cg;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      unsigned char* const dst = unit + ((h != 0) != swap ? 4 * kXS : 0);
+      uint32_t c[4][4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = __builtin_amdgcn_perm((uint32_t)xr[i][e].y, (uint32_t)xr[i][e].x, half[h]);
+        const uint32_t lo01 = __builtin_amdgcn_perm(r[1], r[0], sel_lo), hi01 = __builtin_amdgcn_perm(r[1], r[0], sel_hi);
+        const uint32_t lo23 = __builtin_amdgcn_perm(r[3], r[2], sel_lo), hi23 = __builtin_amdgcn_perm(r[3], r[2], sel_hi);
+        c[i][0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+        c[i][1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+        c[i][2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+        c[i][3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<v4i*>(dst + ((e + rot) & 3) * kXS) = (v4i){(int)c[0][e], (int)c[1][e], (int)c[2][e], (int)c[3][e]};
+    }
   }
   v4i acc[MT][NT];
 #pragma unroll
@@ -188,8 +200,8 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
   __syncthreads();                                  // the tile is complete
 
   // ---- a lane's line of the weights that come after these (the lines in turn over the die's workgroups, so that each wave asks
-  // once at most; past the last one, or if there are none: this layer's first)
-  const int8_t* line_ahead = p.w;
+  // once at most; past the last one, or if there are none: the first)
+  const int8_t* line_ahead = g.ahead.w;
   {
     const int die = (int)(blockIdx.x & 7), wgs = min(g.per_xcd, g.tiles - die * g.per_xcd);
     const uint32_t lines = g.ahead.lines[die], L = (blockIdx.x >> 3) + (uint32_t)(wgs * tid);
@@ -328,7 +340,7 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
 
 struct Choice { int MT, WC, NT; };
 
-int lds_rows(const ConvParams& p, int TM) { return (((TM - 1) * p.stride + p.dil * (p.k - 1) + 1 + 3) + 3) & ~3; }
+int lds_rows(const ConvParams& p, int TM) { return (((TM - 1) * p.stride + p.dil * (p.k - 1) + 1 + 7) + 7) & ~7; }
 
 size_t lds_bytes(const ConvParams& p, const Choice& c) {
   const size_t tile = (size_t)(p.Cin / 64) * lds_rows(p, 16 * c.MT) * kXS, sums = (size_t)16 * c.MT * c.NT * 1024 / meetings(c.MT, c.NT);
@@ -342,11 +354,12 @@ bool supported(const ConvParams& p) {
 }
 
 // The tile with the least time, in cycles: a launch, and on the busiest compute unit for each of its workgroups the
-// activations it transposes (units of 16 dword loads), its steps (the weights of all its columns, or its products) and its
+// activations it transposes (64 bytes at a time), its steps (the weights of all its columns, or its products) and its
 // last stores; of single columns each operand read serves one product.  Every tile timed beside the choice, chains of six
-// layers of 256 .. 768 channels, 11 .. 25 taps, 52 .. 1600 frames (35 shapes): it is 0.5 % from the best on average and 3 %
-// at worst; the choice between this kernel and conv_pipe, over 45 shapes to 6400 frames, 0.2 % and 2.6 %.  (Constants fitted to
-// those chains alone, whose weights stay in the memory-side cache, choose 0.06 % from their best and make whole networks slower: 732 -> 741.)
+// layers of 256 .. 768 channels, 11 .. 25 taps, 104 .. 3200 frames (35 shapes): it is 0.8 % from the best on average and 2.9 %
+// at worst; the choice between this kernel and conv_pipe, over 50 shapes to 3200 frames, 0.4 % and 4.9 % (768 channels, 4 x 400
+// frames, 35.2 us for 33.6; with 7 cycles per 64 bytes transposed 1.0 % and 17 %, with 10.7, of the units of 4 frames, 0.5 % and 14 %).
+// (Constants fitted to those chains alone, whose weights stay in the memory-side cache, make whole networks slower: 732 -> 741.)
 bool pick(const ConvParams& p, Choice& best, double& cycles) {
   if (!supported(p)) return false;
   cycles = 1e300;
@@ -360,7 +373,7 @@ bool pick(const ConvParams& p, Choice& best, double& cycles) {
       const int64_t wgs = (int64_t)p.B * ((p.Tout + 16 * MT - 1) / (16 * MT)) * ((p.Cout + 16 * C - 1) / (16 * C));
       if (wgs >= (1 << 22) - 8) continue;
       const double step = fmax(C * fmax(6.4 * MT, 24.8), c.NT == 1 ? 12.0 * MT : 0.0);
-      const double wg = 3460.0 + 157.5 * MT * C + (double)(p.Cin / 64) * p.k * step + 10.7 * (p.Cin / 64) * lds_rows(p, 16 * MT);
+      const double wg = 3460.0 + 157.5 * MT * C + (double)(p.Cin / 64) * p.k * step + 8.5 * (p.Cin / 64) * lds_rows(p, 16 * MT);
       const double cost = 6300.0 + (double)((wgs + 255) / 256) * wg;
       if (cost < cycles) { cycles = cost; best = c; }
     }
@@ -375,11 +388,11 @@ void geometry(const ConvParams& p, const Choice& c, FewGeom& g) {
   g.co16n = (p.Cout + 15) / 16;
   g.tiles = p.B * g.n_tt * ((p.Cout + 16 * C - 1) / (16 * C));
   g.per_xcd = (g.tiles + 7) / 8;
-  g.units = g.kchunks * g.rows;
+  g.units = g.kchunks * g.rows / 2;
   g.jstep = 16 / c.WC / g.kchunks;
   g.r_nbt = 1.0f / (float)(p.B * g.n_tt);
   g.r_tt = 1.0f / (float)g.n_tt;
-  g.r_rows = 1.0f / (float)g.rows;
+  g.r_rows = 2.0f / (float)g.rows;
 }
 
 // what the launch of `next` will stream: a die's run of its tiles, channel tile first, spans some of its channel tiles
@@ -410,6 +423,7 @@ hipError_t launch_t(const ConvParams& p, const ConvParams* next, hipStream_t st)
   FewGeom g;
   geometry(p, c, g);
   g.ahead = next ? weights_of(*next) : Ahead{};
+  if (!g.ahead.w) g.ahead.w = p.w;
   static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
   if (const hipError_t e = ensure_max_dynamic_lds((const void*)conv_few_kernel<MT, WC, NT>, lds_raised); e != hipSuccess) return e;
   return launch_kernel(conv_few_kernel<MT, WC, NT>, dim3((unsigned)(8 * g.per_xcd)), dim3(1024), lds_bytes(p, c), st, p, g);

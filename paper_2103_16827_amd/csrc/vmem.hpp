@@ -81,6 +81,11 @@ __device__ __forceinline__ v4i gload16(const void* base, uint32_t off) {
   asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
   return r;
 }
+__device__ __forceinline__ v2i gload8(const void* base, uint32_t off) {
+  v2i r;
+  asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
+  return r;
+}
 __device__ __forceinline__ int32_t gload4(const void* base, uint32_t off) {
   int32_t r;
   asm volatile("global_load_dword %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
@@ -126,6 +131,7 @@ __device__ __forceinline__ void wait_vm_dyn(int n) {
 }
 // makes every later use of v depend on this point of the (volatile-ordered) instruction stream
 __device__ __forceinline__ void tie(v4i& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void tie(v2i& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void tie(int32_t& v) { asm volatile("" : "+v"(v)); }
 
 }  // namespace qasr

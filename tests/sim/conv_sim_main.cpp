@@ -268,6 +268,9 @@ int main() {
       {"few 3x2, stride 2", 1, 3, 2, 0, 0, 2, 128, 130, 99, 13, 2, 1, 6, 6, 0, 1, 0},
       {"few 1x2, more than 1024 units", 1, 1, 2, 0, 0, 1, 768, 64, 30, 77, 1, 1, 38, 38, 0, 1, 0},
       {"few 4x2, 4 frames", 1, 4, 2, 0, 0, 3, 64, 64, 4, 3, 1, 1, 1, 1, 1, 1, 1},
+      {"few 1x1, 5 frames, one chunk", 1, 1, 1, 0, 0, 1, 64, 64, 5, 3, 1, 1, 1, 1, 0, 1, 0},
+      {"few 1x1, 7 frames, two chunks", 1, 1, 1, 0, 0, 2, 128, 64, 7, 4, 1, 1, 2, 1, 0, 1, 0},
+      {"few 2x1, 9 frames, wide padding", 1, 2, 1, 0, 0, 2, 64, 64, 9, 27, 1, 1, 13, 13, 0, 1, 0},
       {"few 2x1 of one column, rings of twelve", 1, 2, 1, 1, 0, 2, 192, 80, 41, 15, 1, 1, 7, 7, 1, 1, 0},
       {"few 4x1 of three, sums in two parts", 1, 4, 1, 3, 0, 1, 256, 112, 70, 13, 1, 1, 6, 6, 2, 1, 1},
       {"few 1x1 of three, whole rounds", 1, 1, 1, 3, 0, 1, 256, 64, 20, 16, 1, 1, 8, 7, 0, 1, 0},

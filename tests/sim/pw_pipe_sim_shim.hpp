@@ -257,6 +257,18 @@ inline v4i gload16(const void* base, uint32_t off) {
   sim::rec(sim::ISSUE_REG, uid);
   return (v4i){(int)(kUidTag | (uint32_t)uid), 0, 0, 0};
 }
+inline v2i gload8(const void* base, uint32_t off) {
+  const unsigned char* const p = (const unsigned char*)base + off;
+  sim::region_of(p, 8, false);
+  int64_t v;
+  std::memcpy(&v, p, 8);
+  auto& st = sim::S();
+  const int uid = st.next_uid++;
+  if ((size_t)uid >= st.reg_values.size()) st.reg_values.resize(uid + 1);
+  st.reg_values[uid] = (int32_t)v;
+  sim::rec(sim::ISSUE_REG, uid);
+  return (v2i){(int)(kUidTag | (uint32_t)uid), (int)(v >> 32)};
+}
 inline int32_t gload_i8(const void* p) { return reg_load(p, 1); }
 template <int OFF>
 inline void gload16_into(v4i& r, const void* base, uint32_t off) { r = gload16((const unsigned char*)base + OFF, off); }
@@ -267,6 +279,11 @@ inline void tie(int32_t& v) {
     sim::rec(sim::USE_REG, uid);
     v = sim::S().reg_values[uid];
   }
+}
+inline void tie(v2i& v) {
+  int32_t x = v.x;
+  tie(x);
+  v.x = x;
 }
 
 }  // namespace qasr

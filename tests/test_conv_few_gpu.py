@@ -44,6 +44,18 @@ def test_tiles_of_16_and_48_channels(kw, tile, tuning_env):
     test_tiles(kw, tile, tuning_env)
 
 
+@pytest.mark.parametrize("T", [4, 5, 7, 8, 9, 15, 17, 23])
+def test_rows_about_eight_frames_long(T, tuning_env):
+    """A unit of eight frames over a row's end, over both rows' ends, and rows that are shorter than one."""
+    tuning_env("QASR_CONV_FEW", "1")
+    for B, Cin, pad in ((1, 64, (1, 1)), (2, 128, (0, 2)), (3, 64, (13, 13))):
+        k = pad[0] + pad[1] + 1
+        print(f"[case] dense {Cin} -> 64 k={k} B={B} T={T}", flush=True)
+        case = layer_case("few_frames", B, Cin, 64, T, k=k, pad=pad, packed=True)
+        assert takes_few(case[0], B)
+        run_layer_case(case)
+
+
 @pytest.mark.parametrize("n_res", [2, 5, 12])
 def test_several_residuals(n_res, tuning_env):
     tuning_env("QASR_CONV_FEW", "1")

@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "..", "paper_2103_16827_amd", "csrc")
 
 # functions that leave what they ask for on its way (a kernel's ring, its constants): pw_chain.hip, sep_body.hpp
 ASKS = ("load_step", "load_steps", "items", "load_by_hand")
-LOADS = (r"\b(?:direct_load16_scope\s*<[^>]*>|direct_load16_dev|direct_load16|direct_load4|gload16|gload4|gload_i8|bload16"
+LOADS = (r"\b(?:direct_load16_scope\s*<[^>]*>|direct_load16_dev|direct_load16|direct_load4|gload16|gload8|gload4|gload_i8|bload16"
          r"|gload16_into\s*<[^;]*?>|gload4_into|(?:load_step|load_steps|items)\s*<[^;()]*>|load_by_hand)\s*\(")
 WAIT0 = r"\bwait_vm\s*<\s*0\s*>\s*\(\s*\)"
 OPERANDS = r"(?:bias|m|s|w|x|res|act_lut)"
