@@ -532,7 +532,7 @@ struct DwSmall {
     for (int j = 0; j < NWL; ++j) *reinterpret_cast<v4i*>(wlds + 16 * lane + 1024 * j) = wr[j];
     const int u = lane & ((1 << p.row_lanes_log2) - 1);
     unsigned char* const to = rows + 16 * ((lane >> p.row_lanes_log2) * RU + u);
-    if (max_row_lanes_log2(MT, NA) < 4 || u < RU) {
+    if ((1 << max_row_lanes_log2(MT, NA)) <= RU || u < RU) {   // (what lies past a row is the next one's, past the last row the table's)
 #pragma unroll
       for (int j = 0; j < NX; ++j)
         if (j < 1 || j < CPW >> (6 - p.row_lanes_log2))

@@ -94,6 +94,16 @@ def test_longer_taps_keep_the_pair(tuning_env):
     check(conformer_tail(1, 64, 51, True), {"pw": ("dw", "sep"), "gate": ("up", "pw_chain")})
 
 
+@pytest.mark.parametrize("MT", ["1", "2", "4"])
+@pytest.mark.parametrize("k", [45, 53, 69, 87])
+def test_a_pairs_table_beside_its_rows(k, MT, tuning_env):
+    """Every range of taps: rows in LDS end where the activation's table begins."""
+    tuning_env(FORCE, "1")
+    tuning_env("QASR_SEP", MT)
+    for T in (16, 64, 213):
+        check(conformer_tail(1, T, k, True), {"pw": ("dw", "sep")})
+
+
 @pytest.mark.parametrize("glu_s", [30, 45])
 def test_activations_of_a_chain(glu_s, tuning_env):
     tuning_env(FORCE, "1")
