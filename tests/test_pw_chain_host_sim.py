@@ -61,6 +61,7 @@ def generate_chain(tmp, mutate=None):
         "namespace qasr {\n" + span(read("sep.hpp"), r"struct DwParams \{", r"\n\};") + "namespace sep {\ntypedef unsigned v4u __attribute__((ext_vector_type(4)));\n"
         + "".join(span(sep, b, e) for b, e in ((r"constexpr int kStoreThrough", r";"), (r"constexpr int kWaves", r";"), (r"constexpr int kMaxUnits", r";"),
                                                (r"constexpr int row_loads\(", r"\n\}"), (r"inline int small_row_bytes\(", r"\n\}"),
+                                               (r"uint32_t toeplitz_bytes\(", r"\}"),
                                                (r"template <int N>\nstruct Consts \{", r"\n\};")))
         + small + "}\n" + span(plan, r"struct Geometry \{", r"\nbool geometry\(.*?\n\}") + span(plan, r"bool x_ragged\(", r"\n") + span(plan, r"int units_of\(", r"\n\}")
         + span(plan, r"static void fill_dw\(", r"\n\}") + span(plan, r"bool dw_small_params\(", r"\n\}") + span(header, r"constexpr int kMaxChain", r";")
