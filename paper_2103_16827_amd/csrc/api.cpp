@@ -97,14 +97,15 @@ Kernel family_of(const ConvParams& p) {
 // widths hand launches of some sizes to pw_wide, dense layers of few frames go to conv_few.  It depends on
 // lengths, row pitches and pointers (their alignment), not on act_lut, so a layer may get another kernel in
 // another call (a float forward gives the ends of an encoder padded rows); whoever asks goes by the answer for
-// the call at hand, also for the activation.
-Kernel pick_kernel(const ConvParams& p) {
+// the call at hand, also for the activation.  split: there is room for the partial sums of a split contraction.
+Kernel pick_kernel(const ConvParams& p, bool split) {
   const Kernel f = family_of(p);
   if (f == Kernel::PwTile && qasr::pw_wide_better(p, false)) return Kernel::PwWide;
   if (f == Kernel::PwPipe && qasr::pw_wide_better(p, true)) return Kernel::PwWide;
-  if (f == Kernel::ConvPipe && qasr::conv_few_better(p, p.part != nullptr)) return Kernel::ConvFew;
+  if (f == Kernel::ConvPipe && qasr::conv_few_better(p, split)) return Kernel::ConvFew;
   return f;
 }
+Kernel pick_kernel(const ConvParams& p) { return pick_kernel(p, p.part != nullptr); }
 
 // kernels whose epilogue applies a unary activation's table (ConvParams::act_lut)
 bool applies_act_table(Kernel k) { return k == Kernel::PwPipe || k == Kernel::PwWide || k == Kernel::DwPipe; }
@@ -1018,6 +1019,9 @@ const char* qasr_encoder_op_kernel(const qasr_encoder* e, int32_t i) {
   return family_name(e->ops[i].family);
 }
 
+// whether a forward's workspace has room for the partial sums of split contractions
+static bool has_split_room(const qasr_encoder* e) { return e->ws_bytes > e->split_off; }
+
 // the pair at op i may take the projection r before it along
 static bool projection_with_pair(const ConvParams& r, const ConvParams& d, const ConvParams& q) {
   return qasr::sep_supported(d, q) && qasr::sep_projection_supported(d, q, r);
@@ -1085,7 +1089,7 @@ int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** ke
     if (kernel) {
       ConvParams p = e->ops[i].p;
       rows_of(e, (size_t)i, 0, 0, p);
-      *kernel = name ? name : kernel_name(pick_kernel(p));
+      *kernel = name ? name : kernel_name(pick_kernel(p, has_split_room(e)));
     }
     return first;
   }
@@ -1137,7 +1141,7 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
   // (the team kernel's loads want 16-byte aligned tensors, like the kernels it replaces)
   const bool use_team = how.team && !e->runs.empty() && ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0) && !y_over_x;
   // room for the partial sums of split contractions, and their counters (zero between layers from here on)
-  split = split && e->ws_bytes > e->split_off;
+  split = split && has_split_room(e);
   const size_t split_bytes = split ? e->ws_bytes - e->split_off - round256(4 * qasr::kConvSplitCounters) : 0;
   if (const hipError_t be = begin(0); be != hipSuccess) return hip_status(be);
   if (split) {

@@ -9,6 +9,7 @@ import oracle
 import paper_2103_16827_amd as Q
 import qasr_workloads as W
 from gpu_util import GpuNet, desc_of, dev, gpu_layer
+from qasr_workloads.nets import _Builder
 from test_gpu_parity import draw, layer_case, run_layer_case
 
 pytestmark = pytest.mark.gpu
@@ -87,4 +88,28 @@ def test_small_encoder_takes_it(B, T):
         assert np.array_equal(y.cpu().numpy(), ref)
         g.forward(xd)
     graph.close()
+    g.enc.close()
+
+
+@pytest.mark.parametrize("C,k,B,T,splits", [(768, 25, 4, 400, True), (768, 25, 2, 800, True), (256, 11, 2, 406, False),
+                                            (768, 25, 1, 104, False)])
+def test_the_kernel_named_is_the_one_that_runs(C, k, B, T, splits):
+    """Between the two dense kernels the forward chooses with the room that it has for partial sums; what is written there tells
+    whether conv_pipe ran in several parts (the room is the largest such layer's: without one there is none)."""
+    b = _Builder("two_layers", 91, B, 64, T)
+    b.op("in", C)
+    b.op("dense", C, k=k)
+    net = b.done()
+    g = GpuNet(net, W.draw_net_params(net, 8))
+    pitch = (T + 15) // 16 * 16
+    slot, counters = (B * C * pitch + 255) // 256 * 256, 4096
+    room = g.enc.workspace_bytes - slot - counters
+    print(f"[case] {C} -> {C} k={k} B={B} T={T}: {g.enc.op_launch(1)}, room {room}", flush=True)
+    g.ws.fill_(77)
+    g.forward(dev(W.draw_input(net, 8)))
+    torch.cuda.synchronize()
+    ran_in_parts = room > 0 and bool((g.ws[slot:slot + room] != 77).any())
+    assert ran_in_parts == splits
+    assert g.enc.op_launch(1) == (1, "conv_pipe" if ran_in_parts else "conv_few")
+    g.check_guards()
     g.enc.close()
