@@ -98,14 +98,19 @@ Kernel family_of(const ConvParams& p) {
 // lengths, row pitches and pointers (their alignment), not on act_lut, so a layer may get another kernel in
 // another call (a float forward gives the ends of an encoder padded rows); whoever asks goes by the answer for
 // the call at hand, also for the activation.  split: there is room for the partial sums of a split contraction.
-Kernel pick_kernel(const ConvParams& p, bool split) {
-  const Kernel f = family_of(p);
-  if (f == Kernel::PwTile && qasr::pw_wide_better(p, false)) return Kernel::PwWide;
-  if (f == Kernel::PwPipe && qasr::pw_wide_better(p, true)) return Kernel::PwWide;
-  if (f == Kernel::ConvPipe && qasr::conv_few_better(p, split)) return Kernel::ConvFew;
-  return f;
+struct Choice {
+  Kernel k = Kernel::Generic;
+  qasr::FewTile few{};         // ConvFew's
+};
+Choice choose(const ConvParams& p, bool split) {
+  Choice c;
+  c.k = family_of(p);
+  if (c.k == Kernel::PwTile && qasr::pw_wide_better(p, false)) c.k = Kernel::PwWide;
+  else if (c.k == Kernel::PwPipe && qasr::pw_wide_better(p, true)) c.k = Kernel::PwWide;
+  else if (c.k == Kernel::ConvPipe && qasr::conv_few_better(p, split, c.few)) c.k = Kernel::ConvFew;
+  return c;
 }
-Kernel pick_kernel(const ConvParams& p) { return pick_kernel(p, p.part != nullptr); }
+Choice choose(const ConvParams& p) { return choose(p, p.part != nullptr); }
 
 // kernels whose epilogue applies a unary activation's table (ConvParams::act_lut)
 bool applies_act_table(Kernel k) { return k == Kernel::PwPipe || k == Kernel::PwWide || k == Kernel::DwPipe; }
@@ -128,9 +133,10 @@ const char* family_name(Kernel k) {
   return kernel_name(k == Kernel::PwWide ? Kernel::GemmMfma : k == Kernel::ConvFew ? Kernel::ConvPipe : k);
 }
 
-qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st, const ConvParams* next = nullptr) {
+// next: a layer that ConvFew runs later, as next_choice says (or null)
+qasr_status launch_with(const Choice& c, const ConvParams& p, hipStream_t st, const ConvParams* next = nullptr, const Choice& next_choice = Choice()) {
   hipError_t e;
-  switch (k) {
+  switch (c.k) {
     case Kernel::DwMfma: e = qasr::launch_dw_mfma(p, st); break;
     case Kernel::DwPipe: e = qasr::launch_dw_pipe(p, st); break;
     case Kernel::GemmMfma: e = qasr::launch_gemm_mfma(p, st); break;
@@ -138,13 +144,13 @@ qasr_status launch_with(Kernel k, const ConvParams& p, hipStream_t st, const Con
     case Kernel::PwPipe: e = qasr::launch_pw_pipe(p, st); break;
     case Kernel::PwWide: e = qasr::launch_pw_wide(p, st); break;
     case Kernel::ConvPipe: e = qasr::launch_conv_pipe(p, st); break;
-    case Kernel::ConvFew: e = qasr::launch_conv_few(p, next, st); break;
+    case Kernel::ConvFew: e = qasr::launch_conv_few(p, c.few, next, next_choice.few, st); break;
     default: e = qasr::launch_conv_generic(p, st); break;
   }
   return hip_status(e);
 }
 
-qasr_status launch(const ConvParams& p, hipStream_t st) { return launch_with(pick_kernel(p), p, st); }
+qasr_status launch(const ConvParams& p, hipStream_t st) { return launch_with(choose(p), p, st); }
 
 // frames between rows of an encoder's own tensors: the row length rounded up to 16
 int32_t row_pad(int32_t T) { return (16 - T % 16) % 16; }
@@ -353,7 +359,7 @@ const char* qasr_conv1d_kernel_name(const qasr_conv1d_desc* d) {
 const char* qasr_conv1d_launch_name(const qasr_conv1d_desc* d) {
   if (check_desc(d) != QASR_OK) return nullptr;
   const ConvParams p = make_params(d, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-  return kernel_name(pick_kernel(p));
+  return kernel_name(choose(p).k);
 }
 
 qasr_status qasr_conv1d_int8(const qasr_conv1d_desc* d, const int8_t* x, const int8_t* w,
@@ -842,7 +848,7 @@ static qasr_status create_encoder(const qasr_op* ops, int32_t n_ops, int32_t n_s
       ConvParams rp = op.p;               // (the pointers are unknown yet: the choice for aligned ones)
       rows_of(e, i, 0, 0, rp);
       op.family = family_of(rp);
-      op.act_fused = o.act && o.act->kind != QASR_ACT_GLU && applies_act_table(pick_kernel(rp));
+      op.act_fused = o.act && o.act->kind != QASR_ACT_GLU && applies_act_table(choose(rp).k);
       if (op.family == Kernel::ConvPipe) split_bytes = std::max(split_bytes, qasr::conv_pipe_split_bytes(rp));
     }
     if (o.act) {
@@ -1089,7 +1095,7 @@ int32_t qasr_encoder_op_launch(const qasr_encoder* e, int32_t i, const char** ke
     if (kernel) {
       ConvParams p = e->ops[i].p;
       rows_of(e, (size_t)i, 0, 0, p);
-      *kernel = name ? name : kernel_name(pick_kernel(p, has_split_room(e)));
+      *kernel = name ? name : kernel_name(choose(p, has_split_room(e)).k);
     }
     return first;
   }
@@ -1164,6 +1170,8 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
     for (int32_t r = 0; r < op.n_more_res; ++r)
       p.res_more[r] = op.more_res_slots[r] == 0 ? x : ws + e->slot_off[op.more_res_slots[r]];
   };
+  Choice chosen;                                    // layer chosen_for's, which the one before has asked for
+  size_t chosen_for = n;                            // (n: none)
   for (size_t i = 0; i < n; ++i) {
     if (use_team && e->run_of[i] >= 0) {
       const qasr_encoder::TeamRun& r = e->runs[e->run_of[i]];
@@ -1232,19 +1240,22 @@ static qasr_status forward_impl(const qasr_encoder* e, const int8_t* x, int8_t* 
       }
     }
     // (the kernel of this call decides who applies a unary activation: its epilogue, or a pass of its own)
-    const Kernel kk = pick_kernel(p);
-    p.act_lut = applies_act_table(kk) ? op.act_table : nullptr;
+    const Choice c = chosen_for == i ? chosen : choose(p);
+    p.act_lut = applies_act_table(c.k) ? op.act_table : nullptr;
     // (the next layer of conv_few's, pointwise ones between them passed over: their weights leave room in the L2s)
     ConvParams later;
     const ConvParams* next = nullptr;
-    if (kk == Kernel::ConvFew)
-      for (size_t j = i + 1; j < n && !next; ++j) {
-        if (e->ops[j].p.k < 2) continue;
+    if (c.k == Kernel::ConvFew) {
+      size_t j = i + 1;
+      while (j < n && e->ops[j].p.k < 2) ++j;
+      if (j < n) {
         bind(j, later);
-        if (pick_kernel(later) != Kernel::ConvFew) break;
-        next = &later;
+        chosen = choose(later);
+        chosen_for = j;
+        if (chosen.k == Kernel::ConvFew) next = &later;
       }
-    const qasr_status s = launch_with(kk, p, st, next);
+    }
+    const qasr_status s = launch_with(c, p, st, next, chosen);
     if (s != QASR_OK) return s;
     if (op.has_act && !p.act_lut) {
       const bool glu = op.act.kind == QASR_ACT_GLU;

@@ -338,13 +338,21 @@ __global__ __launch_bounds__(1024) void conv_few_kernel(ConvParams p, FewGeom g)
   tie(line);
 }
 
-struct Choice { int MT, WC, NT; };
-
 int lds_rows(const ConvParams& p, int TM) { return (((TM - 1) * p.stride + p.dil * (p.k - 1) + 1 + 7) + 7) & ~7; }
 
-size_t lds_bytes(const ConvParams& p, const Choice& c) {
+size_t lds_bytes(const ConvParams& p, const FewTile& c) {
   const size_t tile = (size_t)(p.Cin / 64) * lds_rows(p, 16 * c.MT) * kXS, sums = (size_t)16 * c.MT * c.NT * 1024 / meetings(c.MT, c.NT);
   return tile > sums ? tile : sums;
+}
+
+int64_t workgroups(const ConvParams& p, const FewTile& c) {
+  const int C = 16 * c.WC * c.NT;
+  return (int64_t)p.B * ((p.Tout + 16 * c.MT - 1) / (16 * c.MT)) * ((p.Cout + C - 1) / C);
+}
+
+// what the kernel takes for granted of a layer's tile
+bool fits(const ConvParams& p, const FewTile& c) {
+  return lds_bytes(p, c) <= (size_t)kLds && (p.Cin / 64) * lds_rows(p, 16 * c.MT) < 65536 && workgroups(p, c) < (1 << 22) - 8;
 }
 
 bool supported(const ConvParams& p) {
@@ -360,33 +368,30 @@ bool supported(const ConvParams& p) {
 // at worst; the choice between this kernel and conv_pipe, over 50 shapes to 3200 frames, 0.4 % and 4.9 % (768 channels, 4 x 400
 // frames, 35.2 us for 33.6; with 7 cycles per 64 bytes transposed 1.0 % and 17 %, with 10.7, of the units of 4 frames, 0.5 % and 14 %).
 // (Constants fitted to those chains alone, whose weights stay in the memory-side cache, make whole networks slower: 732 -> 741.)
-bool pick(const ConvParams& p, Choice& best, double& cycles) {
+bool pick(const ConvParams& p, FewTile& best, double& cycles) {
   if (!supported(p)) return false;
   cycles = 1e300;
-  static const Choice columns[] = {{0, 1, 1}, {0, 1, 2}, {0, 1, 3}, {0, 2, 2}};
-  for (Choice c : columns)
+  static const FewTile columns[] = {{0, 1, 1}, {0, 1, 2}, {0, 1, 3}, {0, 2, 2}};
+  for (FewTile c : columns)
     for (int MT = 1; MT <= 4; ++MT) {
       c.MT = MT;
       if ((tuning().cf_mt && MT != tuning().cf_mt) || (tuning().cf_wc && c.WC != tuning().cf_wc) || (tuning().cf_nt && c.NT != tuning().cf_nt)) continue;
-      if (lds_bytes(p, c) > (size_t)kLds || (p.Cin / 64) * lds_rows(p, 16 * MT) >= 65536) continue;
+      if (!fits(p, c)) continue;
       const int C = c.WC * c.NT;
-      const int64_t wgs = (int64_t)p.B * ((p.Tout + 16 * MT - 1) / (16 * MT)) * ((p.Cout + 16 * C - 1) / (16 * C));
-      if (wgs >= (1 << 22) - 8) continue;
       const double step = fmax(C * fmax(6.4 * MT, 24.8), c.NT == 1 ? 12.0 * MT : 0.0);
       const double wg = 3460.0 + 157.5 * MT * C + (double)(p.Cin / 64) * p.k * step + 8.5 * (p.Cin / 64) * lds_rows(p, 16 * MT);
-      const double cost = 6300.0 + (double)((wgs + 255) / 256) * wg;
+      const double cost = 6300.0 + (double)((workgroups(p, c) + 255) / 256) * wg;
       if (cost < cycles) { cycles = cost; best = c; }
     }
   return cycles < 1e300;
 }
 
-void geometry(const ConvParams& p, const Choice& c, FewGeom& g) {
-  const int MT = c.MT, C = c.WC * c.NT;
-  g.n_tt = (p.Tout + 16 * MT - 1) / (16 * MT);
-  g.rows = lds_rows(p, 16 * MT);
+void geometry(const ConvParams& p, const FewTile& c, FewGeom& g) {
+  g.n_tt = (p.Tout + 16 * c.MT - 1) / (16 * c.MT);
+  g.rows = lds_rows(p, 16 * c.MT);
   g.kchunks = p.Cin / 64;
   g.co16n = (p.Cout + 15) / 16;
-  g.tiles = p.B * g.n_tt * ((p.Cout + 16 * C - 1) / (16 * C));
+  g.tiles = (int)workgroups(p, c);
   g.per_xcd = (g.tiles + 7) / 8;
   g.units = g.kchunks * g.rows / 2;
   g.jstep = 16 / c.WC / g.kchunks;
@@ -396,11 +401,8 @@ void geometry(const ConvParams& p, const Choice& c, FewGeom& g) {
 }
 
 // what the launch of `next` will stream: a die's run of its tiles, channel tile first, spans some of its channel tiles
-Ahead weights_of(const ConvParams& next) {
+Ahead weights_of(const ConvParams& next, const FewTile& c) {
   Ahead a{};
-  Choice c;
-  double cycles;
-  if (!pick(next, c, cycles)) return a;
   FewGeom g;
   geometry(next, c, g);
   const int nbt = next.B * g.n_tt, column = g.kchunks * 8;     // (lines of 16 channels and a tap)
@@ -418,11 +420,11 @@ Ahead weights_of(const ConvParams& next) {
 }
 
 template <int MT, int WC, int NT>
-hipError_t launch_t(const ConvParams& p, const ConvParams* next, hipStream_t st) {
-  const Choice c{MT, WC, NT};
+hipError_t launch_t(const ConvParams& p, const Ahead& ahead, hipStream_t st) {
+  const FewTile c{MT, WC, NT};
   FewGeom g;
   geometry(p, c, g);
-  g.ahead = next ? weights_of(*next) : Ahead{};
+  g.ahead = ahead;
   if (!g.ahead.w) g.ahead.w = p.w;
   static std::atomic<uint64_t> lds_raised{0};   // per instantiation, a bit per device
   if (const hipError_t e = ensure_max_dynamic_lds((const void*)conv_few_kernel<MT, WC, NT>, lds_raised); e != hipSuccess) return e;
@@ -431,23 +433,19 @@ hipError_t launch_t(const ConvParams& p, const ConvParams* next, hipStream_t st)
 
 }  // namespace
 
-bool conv_few_cycles(const ConvParams& p, double& cycles) {
-  Choice c;
-  return !tuning().no_conv_few && pick(p, c, cycles);
+bool conv_few_cycles(const ConvParams& p, FewTile& tile, double& cycles) {
+  return !tuning().no_conv_few && pick(p, tile, cycles);
 }
 
-hipError_t launch_conv_few(const ConvParams& p, const ConvParams* next, hipStream_t st) {
-  Choice c;
-  double cycles;
-  if (!pick(p, c, cycles)) return hipErrorInvalidValue;
+hipError_t launch_conv_few(const ConvParams& p, const FewTile& c, const ConvParams* next, const FewTile& next_tile, hipStream_t st) {
+  if (!supported(p) || !fits(p, c)) return hipErrorInvalidValue;
+  const Ahead ahead = next && supported(*next) && fits(*next, next_tile) ? weights_of(*next, next_tile) : Ahead{};
 #define QASR_CASE(C, T) \
   if (c.WC == C && c.NT == T) \
-    return c.MT == 1 ? launch_t<1, C, T>(p, next, st) : c.MT == 2 ? launch_t<2, C, T>(p, next, st) : c.MT == 3 ? launch_t<3, C, T>(p, next, st) : launch_t<4, C, T>(p, next, st);
+    return c.MT == 1 ? launch_t<1, C, T>(p, ahead, st) : c.MT == 2 ? launch_t<2, C, T>(p, ahead, st) : c.MT == 3 ? launch_t<3, C, T>(p, ahead, st) : launch_t<4, C, T>(p, ahead, st);
   QASR_CASE(1, 1) QASR_CASE(1, 2) QASR_CASE(1, 3) QASR_CASE(2, 2)
 #undef QASR_CASE
   return hipErrorInvalidValue;
 }
-
-hipError_t launch_conv_few(const ConvParams& p, hipStream_t st) { return launch_conv_few(p, nullptr, st); }
 
 }  // namespace qasr

@@ -583,17 +583,18 @@ bool conv_pipe_supported(const ConvParams& p) {
   return pick(p, false, c, t);
 }
 
-bool conv_few_better(const ConvParams& p, bool split) {
+bool conv_few_better(const ConvParams& p, bool split, FewTile& tile) {
   CpTile c;
   double few, pipe;
-  if (tuning().cp_mt || !conv_few_cycles(p, few)) return false;
+  if (tuning().cp_mt || !conv_few_cycles(p, tile, few)) return false;
   return tuning().conv_few_force || !pick(p, split, c, pipe) || few < pipe;
 }
 
 size_t conv_pipe_split_bytes(const ConvParams& p) {
   CpTile c;
+  FewTile few;
   double t;
-  return pick(p, true, c, t) && !conv_few_better(p, true) ? part_bytes(p, c) : 0;
+  return pick(p, true, c, t) && !conv_few_better(p, true, few) ? part_bytes(p, c) : 0;
 }
 
 hipError_t launch_conv_split_clear(unsigned* counters, hipStream_t st) {

@@ -66,13 +66,15 @@ hipError_t launch_conv_split_clear(unsigned* counters, hipStream_t st);
 hipError_t launch_conv_pipe(const ConvParams& p, hipStream_t st);
 
 // The same layers in launches of few frames: all input channels of a small tile in LDS, the weights streamed by 16
-// free-running waves, no workspace.  conv_few_better: whether it is the faster choice for a layer that conv_pipe takes
-// (split: there is a workspace for that to split its contraction); conv_few_cycles: its estimate, on conv_pipe's scale.
-bool conv_few_cycles(const ConvParams& p, double& cycles);
-bool conv_few_better(const ConvParams& p, bool split);
-hipError_t launch_conv_few(const ConvParams& p, hipStream_t st);
-// the same; next: the next layer that this kernel will run (or null), whose weights are brought into the L2s meanwhile
-hipError_t launch_conv_few(const ConvParams& p, const ConvParams* next, hipStream_t st);
+// free-running waves, no workspace.  A tile is MT groups of 16 frames and WC column waves of NT 16-channel columns each.
+// conv_few_cycles: the fastest tile and its estimate, on conv_pipe's scale; conv_few_better: whether that is the faster
+// choice for a layer that conv_pipe takes (split: there is a workspace for that to split its contraction).  A launch takes the
+// tile that was chosen, for the layer and for the next one: models are evaluated once per layer and forward.
+struct FewTile { int MT, WC, NT; };
+bool conv_few_cycles(const ConvParams& p, FewTile& tile, double& cycles);
+bool conv_few_better(const ConvParams& p, bool split, FewTile& tile);
+// next: the next layer that this kernel will run, with its tile (or null), whose weights are brought into the L2s meanwhile
+hipError_t launch_conv_few(const ConvParams& p, const FewTile& tile, const ConvParams* next, const FewTile& next_tile, hipStream_t st);
 
 // Measured ceilings (probe.hip): a streaming copy of `bytes` (a multiple of 16) and a register-resident
 // int8 matrix-core loop of probe_mfma_ops(iters) operations that writes probe_mfma_workgroups() int32.

@@ -44,7 +44,9 @@ struct Tuning {
   int cp_mt = 0, cp_nt = 0, cp_kg = 0, cp_s = 0, cf_mt = 0, cf_wc = 0, cf_nt = 0;
 };
 inline Tuning& the_tuning() { static Tuning t; return t; }
-inline const Tuning& tuning() { return the_tuning(); }
+inline int g_tuning_asked = 0;                   // (every choice of a tile asks)
+inline const Tuning& tuning() { ++g_tuning_asked; return the_tuning(); }
+struct FewTile { int MT, WC, NT; };
 
 inline int32_t dyadic_rescale(int32_t A, int32_t m, int32_t s) { return dyadic_rescale64(A, m, std::max(1, std::min(62, s))); }
 inline int32_t clamp_i8(int32_t v, int32_t lo) { return std::min(127, std::max(lo, v)); }
@@ -72,7 +74,7 @@ inline unsigned sim_arrival() { return g_arrival; }
 #ifdef SIM_FEW
 #include "conv_few_stripped.hpp"
 #else
-namespace qasr { inline bool conv_few_cycles(const ConvParams&, double&) { return false; } }
+namespace qasr { inline bool conv_few_cycles(const ConvParams&, FewTile&, double&) { return false; } }
 #include "conv_pipe_stripped.hpp"
 #endif
 
@@ -214,12 +216,19 @@ void run_case(const Case& c) {
     std::vector<int8_t> nw(nbytes + 128);
     next.w = (int8_t*)(((uintptr_t)nw.data() + 127) & ~(uintptr_t)127);
     st.regions.push_back({"next w", (const unsigned char*)next.w, nbytes, false});
-    e = launch_conv_few(p, &next, nullptr);
+    FewTile tile, next_tile;
+    double cycles;
+    if (!conv_few_cycles(p, tile, cycles) || tile.MT != t.cf_mt || tile.WC != t.cf_wc || tile.NT != t.cf_nt) sim::fail("another tile");
+    t = Tuning();
+    if (!conv_few_cycles(next, next_tile, cycles)) sim::fail("the next layer has no tile");
+    g_tuning_asked = 0;
+    e = launch_conv_few(p, tile, &next, next_tile, nullptr);
     st.regions.pop_back();
     if (e != hipSuccess) sim::fail("the launcher does not take this case");
     std::fill(written.begin(), written.end(), 0);
     // ... and once by itself
-    e = launch_conv_few(p, nullptr);
+    e = launch_conv_few(p, tile, nullptr, FewTile{}, nullptr);
+    if (g_tuning_asked) sim::fail("a launch chooses a tile again");
   }
 #else
   {
