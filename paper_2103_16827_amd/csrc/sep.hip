@@ -34,7 +34,8 @@ int units_of(const ConvParams& d, const Geometry& g, int MT) {
 
 // The weights as the kernels load them: rows [C][16 NA bytes], tap j at byte r + j dil, zeros between, and up to the end
 // of the last wave's last load.
-size_t image_bytes(int C, int NA) { return (size_t)C * NA * 16 + 1024; }
+size_t weight_bytes(int C, int NA) { return (size_t)C * NA * 16; }
+size_t image_bytes(int C, int NA) { return weight_bytes(C, NA) + 1024; }
 __global__ __launch_bounds__(256) void sep_image_kernel(const int8_t* __restrict__ w, int C, int k, int dil, int r, int NA,
                                                         uint32_t* __restrict__ rows) {
   const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x), c = idx / (4 * NA);
@@ -55,8 +56,12 @@ size_t lds_bytes(int KCH, int units, int MT, int NA, int NT, int KS) {
 
 // Tile (MT groups x 256 NT output channels per workgroup) with the least time on the busiest compute
 // unit, one workgroup at a time: its matrix pipes (10 cycles per 4x4x4 product, 17.7 per 16x16x64 one),
-// half hidden under them its 64 bytes per cycle from the L2 (weight image and packed weights, which every
-// workgroup streams whole), and the latency of its first loads and last stores.
+// its 64 bytes per cycle from the L2 (weight rows and packed weights, which every workgroup streams whole, and rows), and the
+// latency of its first loads and last stores.  Every tile timed (profiles/pair_tile_choice.txt), 436 pairs and 378 pairs with
+// projection of 256 or 512 channels, 33 to 93 taps, 16 to 51200 frames: the choice is 0.2 and 1.2 % from the best on average.  (With
+// the weight rows at four times their bytes, as when they were a prebuilt operand, and all bytes half hidden, 0.5 and 3.9: 512
+// channels, 45 taps, 45 x 1265 frames 43.9 us for 34.9.)  What it is furthest from the best by, up to 27 % (256 channels, 63 taps, 52 x 483
+// frames with a projection): it knows of no two workgroups on a unit, which some of 256 channels are.
 bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int groups_per_row, int cus, bool proj, SepChoice& c) {
   static const int MTs[] = {1, 2, 4, 7};
   c.KCH = d.Cout / 64;
@@ -78,13 +83,13 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
         const int64_t wgs = (int64_t)d.B * ((groups_per_row + MT - 1) / MT) * splits;
         if (wgs * (proj ? 2 : 1) > max_workgroups(64 * sep::kWaves) || wgs * ((groups_per_row + MT - 1) / MT) > 1LL << 32) continue;   // (place)
         const double mfma = c.KCH / 2 * MT * g.nk * 10.0 * 2 + MT * NT * c.KCH * 17.7 * 4 / KS;
-        const double bytes = c.KCH * 4.0 * c.NA * 1024 + NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 64.0 * units * 16;
-        const double work = (mfma + 0.5 * bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
+        const double bytes = (double)weight_bytes(d.Cout, c.NA) + NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 64.0 * units * 16;
+        const double work = (mfma + bytes / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
         const int64_t n = (wgs + cus - 1) / cus;
-        double cost = (double)n * (3.5 + work);
+        double cost = (double)n * (2.5 + work);
         if (proj) {                                 // as many workgroups again, without the depthwise half: as a list
-          const double work2 = (MT * NT * c.KCH * 17.7 * 4 / KS + 0.5 * (NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 1024.0 * MT) / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
-          const double list = (double)wgs * (5.0 + work + work2) / cus;
+          const double work2 = (MT * NT * c.KCH * 17.7 * 4 / KS + (NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 1024.0 * MT) / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
+          const double list = (double)wgs * (6.0 + work + work2) / cus;
           if (list > cost) cost = list;
         }
         if (cost < best) { best = cost; c.MT = MT; c.NT = NT; c.KS = KS; c.splits = splits; }
@@ -112,10 +117,13 @@ bool plan(const ConvParams& d, const ConvParams& q, int cus, bool proj, Geometry
 
 }  // namespace
 
-bool sep_supported(const ConvParams& d, const ConvParams& q) {
+bool sep_choice(const ConvParams& d, const ConvParams& q, bool projection, SepChoice& c) {
   Geometry g;
+  return plan(d, q, 256, projection, g, c);
+}
+bool sep_supported(const ConvParams& d, const ConvParams& q) {
   SepChoice c;
-  return plan(d, q, 256, false, g, c);
+  return sep_choice(d, q, false, c);
 }
 
 // Wherever it can: blocks of a projection and a pair, 256 or 512 -> 256 .. 2048 channels, 1 x 104 .. 64 x 800 frames, take

@@ -53,6 +53,8 @@ struct SepChoice { int KCH, MT, NA, NT, KS, splits; bool ragged; };   // KS: wav
 
 // Can depthwise op d and pointwise op q (q reads d's output and nobody else does) run as one launch?
 bool sep_supported(const ConvParams& d, const ConvParams& q);
+// ... and with which tile, on 256 units (projection: a pointwise layer of d's input goes along); false if they cannot
+bool sep_choice(const ConvParams& d, const ConvParams& q, bool projection, SepChoice& c);
 // The images of a depthwise layer's weights (sep.hip)
 size_t sep_image_bytes(const ConvParams& d);
 hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st);

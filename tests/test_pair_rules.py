@@ -1,5 +1,5 @@
-"""Which layers may run as a depthwise + pointwise pair, and take a projection along (csrc/sep.hip), by their geometry:
-the library's own rules, asked by a small host program (no GPU)."""
+"""Which layers may run as a depthwise + pointwise pair, and take a projection along (csrc/sep.hip), by their geometry, and
+with which tile: the library's own rules, asked by a small host program (no GPU)."""
 import os
 import subprocess
 
@@ -42,13 +42,27 @@ int main() {
     expect("longer pair", T, qasr::sep_supported(dl, ql), true);
     expect("padded projection of a longer pair", T, qasr::sep_projection_supported(dl, ql, layer(2, 256, 256, T, 1, 0, 1, 0)), false);
   }
+  // tiles (groups of 16 frames, 16-channel columns per wave), where another takes 1.2 to 1.35 of their time
+  struct { int C, k, B, T; bool projection; int MT, NT; } tiles[] = {
+    {512, 45, 45, 1265, false, 4, 2}, {512, 45, 36, 1720, false, 4, 2},
+    {512, 75, 2, 368, true, 1, 1}, {512, 81, 3, 697, true, 2, 1}, {512, 45, 6, 352, true, 2, 1}, {512, 57, 9, 304, true, 2, 2},
+    {512, 69, 39, 70, true, 2, 2}, {512, 51, 8, 800, true, 4, 2}, {512, 63, 7, 832, true, 4, 2}, {256, 87, 3, 960, true, 2, 1},
+  };
+  for (const auto& t : tiles) {
+    const ConvParams d = layer(t.B, t.C, t.C, t.T, t.k, (t.k - 1) / 2, (t.k - 1) / 2, 1), q = layer(t.B, t.C, t.C, t.T, 1, 0, 0, 0);
+    qasr::SepChoice c{};
+    if (!qasr::sep_choice(d, q, t.projection, c) || c.MT != t.MT || c.NT != t.NT) {
+      std::printf("%d channels, %d taps, %d x %d frames: tile %d x %d\n", t.C, t.k, t.B, t.T, c.MT, c.NT);
+      ++failed;
+    }
+  }
   return failed != 0;
 }
 """
 
 
 @pytest.mark.skipif(not os.path.exists(CLANG), reason="no host clang beside the HIP toolchain")
-def test_padded_pointwise_layers_keep_launches_of_their_own(tmp_path):
+def test_padded_pointwise_layers_keep_launches_of_their_own_and_tiles_are_the_fastest(tmp_path):
     src, exe = tmp_path / "pairs.hip", tmp_path / "pairs"
     src.write_text(MAIN)
     subprocess.check_call([CLANG, "-x", "hip", "--offload-host-only", "--offload-arch=gfx950", "-std=c++17", "-I", os.path.join(PKG, "csrc"), str(src),
