@@ -57,11 +57,12 @@ size_t lds_bytes(int KCH, int units, int MT, int NA, int NT, int KS) {
 // Tile (MT groups x 256 NT output channels per workgroup) with the least time on the busiest compute
 // unit, one workgroup at a time: its matrix pipes (10 cycles per 4x4x4 product, 17.7 per 16x16x64 one),
 // its 64 bytes per cycle from the L2 (weight rows and packed weights, which every workgroup streams whole, and rows), and the
-// latency of its first loads and last stores.  Every tile timed (profiles/pair_tile_choice.txt), 436 pairs and 378 pairs with
-// projection of 256 or 512 channels, 33 to 93 taps, 16 to 51200 frames: the choice is 0.2 and 1.2 % from the best on average.  (With
-// the weight rows at four times their bytes, as when they were a prebuilt operand, and all bytes half hidden, 0.5 and 3.9: 512
-// channels, 45 taps, 45 x 1265 frames 43.9 us for 34.9.)  What it is furthest from the best by, up to 27 % (256 channels, 63 taps, 52 x 483
-// frames with a projection): it knows of no two workgroups on a unit, which some of 256 channels are.
+// latency of its first loads and last stores.  With a projection there are as many workgroups again, without the depthwise
+// half: a list, in which one costs less where two fit on a unit (256 channels) or each has half a tile's products.
+// Every tile timed beside the choice (profiles/pair_tile_choice.txt), weights in no L2 as in a network: 320 pairs and 320 with
+// projection, of 256 or 512 channels, 33 to 87 taps, 32 to 26000 frames.  The choice is 0.1 and 1.0 % from the best on average, 7 and
+// 28 % at worst (256 channels, 33 taps, 14 x 1034 frames: of a pair it knows of no two workgroups on a unit).  With the weight rows at four
+// times their bytes, as when they were a prebuilt operand, all bytes half hidden and 5.0 for every list, it was 0.6 and 5.9 % from it.
 bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int groups_per_row, int cus, bool proj, SepChoice& c) {
   static const int MTs[] = {1, 2, 4, 7};
   c.KCH = d.Cout / 64;
@@ -88,8 +89,9 @@ bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int group
         const int64_t n = (wgs + cus - 1) / cus;
         double cost = (double)n * (2.5 + work);
         if (proj) {                                 // as many workgroups again, without the depthwise half: as a list
+          const double each = c.KCH == 4 ? 4.5 : KS == 2 ? 5.0 : 8.0;
           const double work2 = (MT * NT * c.KCH * 17.7 * 4 / KS + (NT * 16.0 * c.KCH * 1024 / KS + c.KCH * 1024.0 * MT) / 64) / 2200.0 + 1.0 + 0.1 * MT * NT;
-          const double list = (double)wgs * (6.0 + work + work2) / cus;
+          const double list = (double)wgs * (each + work + work2) / cus;
           if (list > cost) cost = list;
         }
         if (cost < best) { best = cost; c.MT = MT; c.NT = NT; c.KS = KS; c.splits = splits; }
