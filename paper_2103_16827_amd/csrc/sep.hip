@@ -60,7 +60,7 @@ size_t lds_bytes(int KCH, int units, int MT, int NA, int NT, int KS) {
 // latency of its first loads and last stores.  With a projection there are as many workgroups again, without the depthwise
 // half: a list, in which one costs less where two fit on a unit (256 channels) or each has half a tile's products.
 // Every tile timed beside the choice (profiles/pair_tile_choice.txt), weights in no L2 as in a network: 320 pairs and 320 with
-// projection, of 256 or 512 channels, 33 to 87 taps, 32 to 26000 frames.  The choice is 0.1 and 1.0 % from the best on average, 7 and
+// projection, of 256 or 512 channels, 33 to 87 taps, 32 to 26000 frames.  The choice is 0.2 and 1.1 % from the best on average, 9 and
 // 28 % at worst (256 channels, 33 taps, 14 x 1034 frames: of a pair it knows of no two workgroups on a unit).  With the weight rows at four
 // times their bytes, as when they were a prebuilt operand, all bytes half hidden and 5.0 for every list, it was 0.6 and 5.9 % from it.
 bool pick(const ConvParams& d, const ConvParams& q, const Geometry& g, int groups_per_row, int cus, bool proj, SepChoice& c) {

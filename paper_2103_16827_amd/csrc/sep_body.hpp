@@ -205,6 +205,8 @@ __device__ __forceinline__ uint32_t through_table(const unsigned char* lut, uint
 }
 
 // ---- Tiles of four and seven groups: enough products per step to cover the loads of the next ones.
+// (Waves that still have loads to ask for before those that have not, by s_setprio: 0.998 of the time without on average over 100 shapes,
+// 256 to 512 channels, 33 to 75 taps, 52 to 51200 frames: nothing, and left out.)
 // RAGGED: x or y (and the residual) are the caller's, rows of any length at any address
 template <int KCH, int MT, int NA, int NT, bool RAGGED>
 __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
@@ -217,7 +219,6 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SepPointwise& pw = p.pw[blockIdx.z];
   const bool proj = blockIdx.z != 0;
-  __builtin_amdgcn_s_setprio(3);                    // (a wave that has its loads on the way goes behind those that have not)
   const uint32_t v = workgroup(p, pw);
   if (v >= (uint32_t)p.wgs) return;                 // whole workgroup
   const Place at = place(p, v);
@@ -284,7 +285,6 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     load_rows(0);
     dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int j = 0; j < NWL; ++j) {
       const int L = lane + 64 * j;
@@ -353,7 +353,6 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
       else finish(std::true_type{}, std::false_type{});
     }
   } else {
-    __builtin_amdgcn_s_setprio(0);
     // the projection's tile: unit tid % 8 of rows tid / 8, + 128, ...
     const int u = tid & 7;
     const int8_t* const src = item(p.x, p.xbs, b) + (int64_t)(tid >> 3) * p.xpitch + 16 * (g0 + u);
