@@ -60,11 +60,13 @@ struct FewGeom {
   int kchunks;        // Cin / 64
   int co16n;          // ceil(Cout / 16)
   int tiles, per_xcd;
-  int units;          // transposition units (8 frames x 16 channels): kchunks * rows / 2 (<= 1024: the rows fit LDS)
+  int units;          // transposition units (8 frames x 16 channels): kchunks * rows / 2, one per thread at most
   int jstep;          // KG / kchunks
   float r_nbt, r_tt, r_rows;   // reciprocals of B * n_tt, n_tt, rows / 2
   Ahead ahead;
 };
+
+static_assert(kLds / kXS / 2 <= 1024, "a tile whose rows fit LDS has a unit per thread at most");
 
 // steps of weights on their way and multiplied (registers)
 template <int MT, int NT> struct Ring { static constexpr int W = NT == 1 ? 12 : NT == 3 ? (MT == 2 ? 6 : 4) : MT == 4 ? 6 : 8; };

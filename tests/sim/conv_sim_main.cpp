@@ -7,7 +7,8 @@
 //   * every register that a request fills is complete when it is tied, and every one is tied;
 //   * no request into LDS is outstanding at a barrier, nothing is outstanding when a wave ends;
 //   * no 16 bytes of LDS are written by one wave and read or written by another between the same two barriers;
-//   * every output byte is written exactly once (pad bytes between rows at most once).
+//   * every output byte is written exactly once (pad bytes between rows at most once);
+//   * conv_few asks ahead for the lines of the next layer's weights that the same die will read, once each.
 #include "pw_pipe_sim_shim.hpp"
 
 #include <atomic>
@@ -174,6 +175,44 @@ struct Case {
   int B, Cin, Cout, T, k, stride, dil, pl, pr, res, bias, pad;
 };
 
+#ifdef SIM_FEW
+// A workgroup's die is its number modulo 8; a launch gives die x the x-th of eight equal runs of its tiles, channel tile first.
+int tiles_of(const ConvParams& p, const FewTile& t, int die, int& first) {
+  const int bt = p.B * ((p.Tout + 16 * t.MT - 1) / (16 * t.MT)), ch = 16 * t.WC * t.NT, tiles = bt * ((p.Cout + ch - 1) / ch), run = (tiles + 7) / 8;
+  first = die * run;
+  return std::max(0, std::min(run, tiles - first));
+}
+
+// Whether the workgroups of each die have asked, once each, for the lines that the next layer's workgroups on that die will read: all
+// of them, or from the first on as many as there are lanes (idle lanes ask for the first line of the weights).
+void check_lines(const ConvParams& p, const FewTile& tile, const ConvParams& next, const FewTile& next_tile, size_t bytes) {
+  const int bt = next.B * ((next.Tout + 16 * next_tile.MT - 1) / (16 * next_tile.MT)), columns = (next.Cout + 15) / 16, chunks = next.Cin / 64;
+  for (int die = 0; die < 8; ++die) {
+    int first = 0;
+    const int lanes = tiles_of(p, tile, die, first) * 1024, n = tiles_of(next, next_tile, die, first);
+    std::set<int64_t> reads;                        // lines of 128 bytes
+    for (int v = first; v < first + n; ++v)
+      for (int c = 0; c < next_tile.WC * next_tile.NT; ++c)
+        for (int j = 0; j < next.k; ++j)
+          for (int kc = 0; kc < chunks; ++kc)
+            for (int l = 0; l < 8; ++l)
+              if (v / bt * next_tile.WC * next_tile.NT + c < columns)
+                reads.insert((((int64_t)j * columns + v / bt * next_tile.WC * next_tile.NT + c) * chunks + kc) * 8 + l);
+    std::map<int64_t, int> asked;
+    for (const auto& [wg, at] : sim::S().asked)
+      if ((int)(wg & 7) == die && at >= (const unsigned char*)next.w && at < (const unsigned char*)next.w + bytes) ++asked[(at - (const unsigned char*)next.w) / 128];
+    int64_t i = 0;
+    for (int64_t line : reads) {
+      const auto it = asked.find(line);
+      if (i++ < lanes ? it == asked.end() || (line && it->second != 1) : line && it != asked.end())
+        sim::fail("die " + std::to_string(die) + ": line " + std::to_string(line) + " is asked for " + std::to_string(it == asked.end() ? 0 : it->second) + " times");
+    }
+    for (const auto& [line, times] : asked)
+      if (line && !reads.count(line)) sim::fail("die " + std::to_string(die) + " asks for line " + std::to_string(line) + ", which it does not read");
+  }
+}
+#endif
+
 void run_case(const Case& c) {
   Tuning& t = the_tuning();
   t = Tuning();
@@ -207,24 +246,45 @@ void run_case(const Case& c) {
   g_name = c.name;
   g_workgroups = 0;
   hipError_t e;
+  auto check_output = [&](int times) {
+    st.where = c.name;
+    st.lane = st.wave = -1;
+    size_t bytes = 0;
+    for (int b = 0; b < c.B; ++b)
+      for (int co = 0; co < c.Cout; ++co)
+        for (int q = 0; q < p.Tout + p.ypad; ++q) {
+          const int n = written[(size_t)b * p.ybs + (size_t)co * (p.Tout + p.ypad) + q];
+          if (q < p.Tout ? n != times : n > times) sim::fail("item " + std::to_string(b) + " channel " + std::to_string(co) + " frame " +
+                                                             std::to_string(q) + " is written " + std::to_string(n) + " times");
+          bytes += q < p.Tout;
+        }
+    return bytes;
+  };
 #ifdef SIM_FEW
   {
-    // once with the weights of a wider layer after it, which has tiles of its own and whose lines are asked for, ...
-    ConvParams next = p;
-    next.Cout = 3 * c.Cout - 16; next.k = c.k + 2; next.pl = p.pl + p.dil;
-    const size_t nbytes = (size_t)next.k * ((next.Cout + 15) / 16) * (c.Cin / 64) * 1024;
-    std::vector<int8_t> nw(nbytes + 128);
-    next.w = (int8_t*)(((uintptr_t)nw.data() + 127) & ~(uintptr_t)127);
-    st.regions.push_back({"next w", (const unsigned char*)next.w, nbytes, false});
     FewTile tile, next_tile;
     double cycles;
     if (!conv_few_cycles(p, tile, cycles) || tile.MT != t.cf_mt || tile.WC != t.cf_wc || tile.NT != t.cf_nt) sim::fail("another tile");
     t = Tuning();
-    if (!conv_few_cycles(next, next_tile, cycles)) sim::fail("the next layer has no tile");
+    // once with the weights of a wider layer of more taps (or fewer, if those fit no tile) after it, which has tiles of its own
+    // and whose lines are asked for, ...
+    ConvParams next = p;
+    next.Cout = 3 * c.Cout - 16; next.k = c.k + 2; next.pl = p.pl + p.dil;
+    if (!conv_few_cycles(next, next_tile, cycles)) {
+      next.k = c.k - 2; next.pl = p.pl - p.dil;
+      if (!conv_few_cycles(next, next_tile, cycles)) sim::fail("the next layer has no tile");
+    }
+    const size_t nbytes = (size_t)next.k * ((next.Cout + 15) / 16) * (c.Cin / 64) * 1024;
+    std::vector<int8_t> nw(nbytes + 128);
+    next.w = (int8_t*)(((uintptr_t)nw.data() + 127) & ~(uintptr_t)127);
+    st.regions.push_back({"next w", (const unsigned char*)next.w, nbytes, false});
     g_tuning_asked = 0;
+    st.asked.clear();
     e = launch_conv_few(p, tile, &next, next_tile, nullptr);
     st.regions.pop_back();
     if (e != hipSuccess) sim::fail("the launcher does not take this case");
+    check_output(1);
+    check_lines(p, tile, next, next_tile, nbytes);
     std::fill(written.begin(), written.end(), 0);
     // ... and once by itself
     e = launch_conv_few(p, tile, nullptr, FewTile{}, nullptr);
@@ -248,19 +308,8 @@ void run_case(const Case& c) {
     e = launch_conv_pipe(p, nullptr);
   }
 #endif
-  st.where = c.name;
-  st.lane = st.wave = -1;
   if (e != hipSuccess) sim::fail("the launcher does not take this case");
-  const int times = c.few || c.s < 1 ? 1 : c.s;
-  size_t bytes = 0;
-  for (int b = 0; b < c.B; ++b)
-    for (int co = 0; co < c.Cout; ++co)
-      for (int q = 0; q < p.Tout + p.ypad; ++q) {
-        const int n = written[(size_t)b * p.ybs + (size_t)co * (p.Tout + p.ypad) + q];
-        if (q < p.Tout ? n != times : n > times) sim::fail("item " + std::to_string(b) + " channel " + std::to_string(co) + " frame " +
-                                                           std::to_string(q) + " is written " + std::to_string(n) + " times");
-        bytes += q < p.Tout;
-      }
+  const size_t bytes = check_output(c.few || c.s < 1 ? 1 : c.s);
   std::printf("ok %-52s %ld workgroups, %zu output bytes\n", c.name, g_workgroups, bytes);
 }
 
@@ -272,10 +321,13 @@ int main() {
       //  name                                  few  a   b kg  s   B  Cin Cout   T   k st dil pl pr res bias pad
       {"few 1x1, 2 steps for 16 groups", 1, 1, 1, 0, 0, 1, 64, 64, 16, 2, 1, 1, 0, 1, 0, 1, 0},
       {"few 2x2, odd everything, dilation", 1, 2, 2, 0, 0, 2, 320, 80, 37, 17, 1, 2, 16, 16, 1, 0, 0},
+      {"few 1x1 of one column, several tiles per die", 1, 1, 1, 1, 0, 2, 64, 64, 100, 3, 1, 1, 1, 1, 0, 1, 0},
 #ifndef SIM_SMALL
       {"few 4x1, ring of six, three residuals", 1, 4, 1, 0, 0, 1, 320, 64, 70, 11, 1, 1, 5, 5, 3, 1, 1},
       {"few 3x2, stride 2", 1, 3, 2, 0, 0, 2, 128, 130, 99, 13, 2, 1, 6, 6, 0, 1, 0},
-      {"few 1x2, more than 1024 units", 1, 1, 2, 0, 0, 1, 768, 64, 30, 77, 1, 1, 38, 38, 0, 1, 0},
+      {"few 1x2, long taps", 1, 1, 2, 0, 0, 1, 768, 64, 30, 77, 1, 1, 38, 38, 0, 1, 0},
+      {"few 1x1, 1024 units: all of LDS", 1, 1, 1, 0, 0, 1, 512, 64, 20, 30, 1, 8, 116, 116, 0, 1, 0},
+      {"few 1x1, 60 units", 1, 1, 1, 0, 0, 2, 64, 64, 25, 14, 1, 7, 45, 46, 0, 1, 0},
       {"few 4x2, 4 frames", 1, 4, 2, 0, 0, 3, 64, 64, 4, 3, 1, 1, 1, 1, 1, 1, 1},
       {"few 1x1, 5 frames, one chunk", 1, 1, 1, 0, 0, 1, 64, 64, 5, 3, 1, 1, 1, 1, 0, 1, 0},
       {"few 1x1, 7 frames, two chunks", 1, 1, 1, 0, 0, 2, 128, 64, 7, 4, 1, 1, 2, 1, 0, 1, 0},

@@ -55,6 +55,7 @@ struct State {
   size_t ballot_idx = 0;
   bool second_round = false;
   std::vector<int32_t> reg_values;       // value behind each register-load tag (index = uid)
+  std::vector<std::pair<unsigned, const unsigned char*>> asked;   // dword loads into registers: workgroup, address
 };
 inline State& S() { static State s; return s; }
 
@@ -246,6 +247,7 @@ inline int32_t reg_load(const void* p, int bytes) {
   const int uid = st.next_uid++;
   if ((size_t)uid >= st.reg_values.size()) st.reg_values.resize(uid + 1);
   st.reg_values[uid] = v;
+  if (bytes == 4) st.asked.push_back({blockIdx.x, (const unsigned char*)p});
   sim::rec(sim::ISSUE_REG, uid);
   return (int32_t)(kUidTag | (uint32_t)uid);
 }

@@ -1,6 +1,6 @@
 """Dense layers of few frames (csrc/conv_few.hip): every tile, fewer steps than wave groups and more than rings, taps that
-wrap over several chunks per step, ragged rows and channels, strides, dilations, several residual operands, tiles of more
-than 1024 transposition units; the choice the library makes for small encoders, replayed as a graph."""
+wrap over several chunks per step, ragged rows and channels, strides, dilations, several residual operands, a transposition unit
+for every thread and for fewer than a wave; the choice the library makes for small encoders, replayed as a graph."""
 import numpy as np
 import pytest
 import torch
@@ -55,6 +55,17 @@ def test_rows_about_eight_frames_long(T, tuning_env):
         case = layer_case("few_frames", B, Cin, 64, T, k=k, pad=pad, packed=True)
         assert takes_few(case[0], B)
         run_layer_case(case)
+
+
+@pytest.mark.parametrize("B,Cin,T,k,dil,pad,units", [(1, 512, 20, 30, 8, (116, 116), 1024), (2, 64, 25, 14, 7, (45, 46), 60)])
+def test_units_for_all_threads_and_for_less_than_a_wave(B, Cin, T, k, dil, pad, units, tuning_env):
+    """A unit is 8 rows of LDS x 16 channels, one per thread at most: 160 KiB hold 1024."""
+    tuning_env("QASR_CONV_FEW", "1")
+    tuning_env("QASR_CF", "1,1,1")
+    assert units == Cin // 64 * ((15 + dil * (k - 1) + 1 + 7 + 7) // 8 * 8) // 2
+    case = layer_case("few_units", B, Cin, 64, T, k=k, dil=dil, pad=pad, packed=True)
+    assert takes_few(case[0], B)
+    run_layer_case(case)
 
 
 @pytest.mark.parametrize("n_res", [2, 5, 12])

@@ -198,7 +198,7 @@ def build_and_run_conv(tmp, name, small=False):
 
 
 @pytest.mark.skipif(not os.path.exists(CLANG), reason="no host clang beside the HIP toolchain")
-@pytest.mark.parametrize("name,cases", [("conv_few", 7), ("conv_pipe", 15)])
+@pytest.mark.parametrize("name,cases", [("conv_few", 16), ("conv_pipe", 15)])
 def test_request_bookkeeping_of_the_dense_kernels_replays_cleanly(tmp_path, name, cases):
     generate_conv(str(tmp_path), name)
     r = build_and_run_conv(str(tmp_path), name)
@@ -212,6 +212,10 @@ CONV_MISTAKES = {
     "few_rows": ("conv_few", "wait_vm_dyn(min(steps, W - 1) * NT);", "wait_vm_dyn(min(steps, W - 1) * NT + 1);"),
     # the sums go where other waves may still read the tile
     "few_barrier": ("conv_few", "  __syncthreads();                                  // the tile has been read by all\n", ""),
+    # the next layer's lines: none, another die's, the same ones by several workgroups
+    "few_no_lines": ("conv_few", "if (L < g.ahead.runs * lines) {", "if (L < 0u * lines) {"),
+    "few_lines_of_another_die": ("conv_few", "a.off[x] = (uint32_t)(from * column * 128);", "a.off[x] = 0;"),
+    "few_lines_twice": ("conv_few", "L = (blockIdx.x >> 3) + (uint32_t)(wgs * tid);", "L = (uint32_t)tid;"),
     "pipe_weights": ("conv_pipe", "wait_vm<(kW - 2) * NT>();", "wait_vm<(kW - 2) * NT + 1>();"),
     "pipe_weights_and_rows": ("conv_pipe", "wait_vm<(kW - 2) * NT + 16>();", "wait_vm<(kW - 2) * NT + 17>();"),
     "pipe_rows": ("conv_pipe", "else wait_vm<2 * NT>();", "else wait_vm<2 * NT + 1>();"),
