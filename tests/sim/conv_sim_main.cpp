@@ -326,8 +326,8 @@ int main() {
       {"few 4x1, ring of six, three residuals", 1, 4, 1, 0, 0, 1, 320, 64, 70, 11, 1, 1, 5, 5, 3, 1, 1},
       {"few 3x2, stride 2", 1, 3, 2, 0, 0, 2, 128, 130, 99, 13, 2, 1, 6, 6, 0, 1, 0},
       {"few 1x2, long taps", 1, 1, 2, 0, 0, 1, 768, 64, 30, 77, 1, 1, 38, 38, 0, 1, 0},
-      {"few 1x1, 1024 units: all of LDS", 1, 1, 1, 0, 0, 1, 512, 64, 20, 30, 1, 8, 116, 116, 0, 1, 0},
-      {"few 1x1, 60 units", 1, 1, 1, 0, 0, 2, 64, 64, 25, 14, 1, 7, 45, 46, 0, 1, 0},
+      {"few 1x1, 1024 units: all of LDS", 1, 1, 1, 1, 0, 1, 1024, 64, 20, 15, 1, 7, 49, 49, 0, 1, 0},
+      {"few 1x1, 60 units", 1, 1, 1, 1, 0, 2, 64, 64, 25, 14, 1, 7, 45, 46, 0, 1, 0},
       {"few 4x2, 4 frames", 1, 4, 2, 0, 0, 3, 64, 64, 4, 3, 1, 1, 1, 1, 1, 1, 1},
       {"few 1x1, 5 frames, one chunk", 1, 1, 1, 0, 0, 1, 64, 64, 5, 3, 1, 1, 1, 1, 0, 1, 0},
       {"few 1x1, 7 frames, two chunks", 1, 1, 1, 0, 0, 2, 128, 64, 7, 4, 1, 1, 2, 1, 0, 1, 0},

@@ -57,7 +57,7 @@ def test_rows_about_eight_frames_long(T, tuning_env):
         run_layer_case(case)
 
 
-@pytest.mark.parametrize("B,Cin,T,k,dil,pad,units", [(1, 512, 20, 30, 8, (116, 116), 1024), (2, 64, 25, 14, 7, (45, 46), 60)])
+@pytest.mark.parametrize("B,Cin,T,k,dil,pad,units", [(1, 1024, 20, 15, 7, (49, 49), 1024), (2, 64, 25, 14, 7, (45, 46), 60)])
 def test_units_for_all_threads_and_for_less_than_a_wave(B, Cin, T, k, dil, pad, units, tuning_env):
     """A unit is 8 rows of LDS x 16 channels, one per thread at most: 160 KiB hold 1024."""
     tuning_env("QASR_CONV_FEW", "1")
