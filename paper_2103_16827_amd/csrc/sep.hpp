@@ -4,6 +4,8 @@
 #pragma once
 #include "common.hpp"
 
+#include <cstddef>
+
 namespace qasr {
 
 // a depthwise layer whose output stays in LDS
@@ -45,6 +47,22 @@ struct SepParams : DwParams {
   int32_t wgs, per_xcd;              // workgroups in all (of one layer), and per XCD
   uint32_t splits_inv, tpr_inv;      // (2^32 - 1) / the two: v / d = (v + 1) inv >> 32 while (v + 1) d <= 2^32
 };
+
+// the kernels read these in pairs (sep_body.hpp: and_next)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winvalid-offsetof"
+#define QASR_NEIGHBOURS(a, b) static_assert(offsetof(SepParams, b) == offsetof(SepParams, a) + 4, #a " and " #b " are read as one")
+QASR_NEIGHBOURS(ypitch, Tout);
+QASR_NEIGHBOURS(yragged, tpr);
+QASR_NEIGHBOURS(g_base, g_more);
+QASR_NEIGHBOURS(splits, wgs);
+QASR_NEIGHBOURS(xpitch, Tin);
+QASR_NEIGHBOURS(o16, nk);
+QASR_NEIGHBOURS(units, dwoff);
+QASR_NEIGHBOURS(drelu, units_inv);
+QASR_NEIGHBOURS(row_lanes_log2, row_step);
+#undef QASR_NEIGHBOURS
+#pragma clang diagnostic pop
 
 // The depthwise half's parameters for tiles of MT <= 2 groups (all but img); false if d is none that it takes.  NA: quads of taps.
 bool dw_small_params(const ConvParams& d, int MT, DwParams& p, int& NA);
