@@ -18,7 +18,7 @@
 //     requests are not aligned, 8.5, 11.7, 16.1; 9.2, 12.3, 19.3.  Rows at odd addresses, 2 x 811 frames of one layer: 256 channels 7.41 / 6.56,
 //     640, 21 taps 25.7 / 24.7;
 //   - the waves are WC column waves x 16 / WC groups that take the (chunk, tap) steps in turn; a wave has W - 1
-//     steps of NT KiB on their way, up to 224 KB per unit;
+//     steps of NT KiB on their way, up to 240 KiB per unit (2 x 48 channels; 144 to 224 the others);
 //   - as a wave's stream ends it asks for a dword of each of 64 lines of the weights that this kernel streams next, those
 //     that its die's workgroups will read: they come out of memory while a launch ends and the next one begins and
 //     brings in its tile, when memory has nothing else to do (a Jasper's layers run at the 2.5 TB/s that their weights come

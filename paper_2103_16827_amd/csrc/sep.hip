@@ -32,14 +32,13 @@ int units_of(const ConvParams& d, const Geometry& g, int MT) {
   return need | 1;
 }
 
-// The weights as the kernels load them: rows [C][16 NA bytes], tap j at byte r + j dil, zeros between, and up to the end
-// of the last wave's last load.
+// The weights as the kernels load them: rows [C][16 NA bytes], tap j at byte r + j dil, zeros between and after the last.
 size_t weight_bytes(int C, int NA) { return (size_t)C * NA * 16; }
-size_t image_bytes(int C, int NA) { return weight_bytes(C, NA) + 1024; }
+size_t image_bytes(int C, int NA) { return weight_bytes(C, NA) + DwParams::kImageTail; }
 __global__ __launch_bounds__(256) void sep_image_kernel(const int8_t* __restrict__ w, int C, int k, int dil, int r, int NA,
                                                         uint32_t* __restrict__ rows) {
   const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x), c = idx / (4 * NA);
-  if (idx >= C * NA * 4 + 256) return;
+  if (idx >= C * NA * 4 + DwParams::kImageTail / 4) return;
   uint32_t v = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -172,7 +171,7 @@ size_t sep_image_bytes(const ConvParams& d) {
 hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st) {
   Geometry g;
   if (!geometry(d, g) || d.Cout % 16) return hipErrorInvalidValue;
-  return launch_kernel(sep_image_kernel, dim3((unsigned)((d.Cout * g.NA * 4 + 256 + 255) / 256)), dim3(256), 0, st, d.w, d.Cout, d.k, d.dil, g.r,
+  return launch_kernel(sep_image_kernel, dim3((unsigned)((image_bytes(d.Cout, g.NA) / 4 + 255) / 256)), dim3(256), 0, st, d.w, d.Cout, d.k, d.dil, g.r,
                        g.NA, img);
 }
 

@@ -10,9 +10,10 @@ namespace qasr {
 
 // a depthwise layer whose output stays in LDS
 struct DwParams {
-  // x rows (pitch xpitch, batch stride xbs, Tin frames), weights (sep_image)
+  // x rows (pitch xpitch, batch stride xbs, Tin frames), weights (sep.hip: image)
   const int8_t* x;
   const uint32_t* img;
+  static constexpr int kImageTail = 1024;   // bytes of zeros after the weights, into which a wave's last load may run
   const int32_t *dbias, *dm, *ds;    // dbias may be null
   const uint8_t* lut;                // table of a unary activation between the two layers, or null
   int64_t xbs;
@@ -73,7 +74,7 @@ struct SepChoice { int KCH, MT, NA, NT, KS, splits; bool ragged; };   // KS: wav
 bool sep_supported(const ConvParams& d, const ConvParams& q);
 // ... and with which tile, on 256 units (projection: a pointwise layer of d's input goes along); false if they cannot
 bool sep_choice(const ConvParams& d, const ConvParams& q, bool projection, SepChoice& c);
-// The images of a depthwise layer's weights (sep.hip)
+// A depthwise layer's weights as the kernels load them (sep.hip: image)
 size_t sep_image_bytes(const ConvParams& d);
 hipError_t launch_sep_image(const ConvParams& d, uint32_t* img, hipStream_t st);
 // d.x, q.res, q.y set; d.y and q.x are not used

@@ -205,8 +205,8 @@ __device__ __forceinline__ uint32_t through_table(const unsigned char* lut, uint
 }
 
 // ---- Tiles of four and seven groups: enough products per step to cover the loads of the next ones.
-// (Waves that still have loads to ask for before those that have not, by s_setprio: 0.998 of the time without on average over 100 shapes,
-// 256 to 512 channels, 33 to 75 taps, 52 to 51200 frames: nothing, and left out.)
+// (Waves that still have loads to ask for put before those that have not, by s_setprio: without it pairs take 0.998 of the time with it, on
+// average over 100 shapes of 256 and 512 channels, 33 to 75 taps, 52 to 51200 frames: nothing, and left out.)
 // RAGGED: x or y (and the residual) are the caller's, rows of any length at any address
 template <int KCH, int MT, int NA, int NT, bool RAGGED>
 __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
@@ -258,6 +258,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
   // weights: rows of 16 NA bytes, each block's over the tile rows that its outputs are written to
   constexpr int NWL = (CPW * NA + 63) / 64;
   static_assert(NA <= 8, "a block's weights fit its tile rows");
+  static_assert(16 * (64 * NWL - CPW * NA) <= DwParams::kImageTail, "the last wave's last load ends inside the image");
   unsigned char* const wlds = xs + c_wave * 128;
   const unsigned char* const wrow = wlds + ch_l * (16 * NA);
   const uint32_t sel = toeplitz_bytes(n_l);
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
     dc.load_bias(p.dbias, c_wave, lane);
     v4i wr[NWL];
 #pragma unroll
-    for (int j = 0; j < NWL; ++j) wr[j] = reinterpret_cast<const v4i*>(p.img)[c_wave * NA + lane + 64 * j];   // (to the end of the last load)
+    for (int j = 0; j < NWL; ++j) wr[j] = reinterpret_cast<const v4i*>(p.img)[c_wave * NA + lane + 64 * j];   // (the last wave's into the image's tail)
     load_rows(0);
     dc.load(p.dm, p.ds, p.dbias, c_wave, lane);
     __builtin_amdgcn_sched_barrier(0);
@@ -492,12 +493,13 @@ __global__ __launch_bounds__(64 * kWaves) void sep_kernel(SepParams p) {
 }
 
 // The depthwise layer of a wave's CPW channels for MT <= 2 groups of frames: rows and weights by as few requests as can be, weights as
-// they are (sep_image's first part), which become Toeplitz rows by one byte permutation per dword.
+// they are (sep.hip: image), which become Toeplitz rows by one byte permutation per dword.
 template <int CPW, int MT, int NA, bool RAGGED>
 struct DwSmall {
   static_assert(MT <= 2, "two units per row");
   static constexpr int NL = row_loads(CPW, MT, NA);
   static constexpr int NWL = (CPW * NA + 63) / 64;
+  static_assert(16 * (64 * NWL - CPW * NA) <= DwParams::kImageTail, "the last wave's last load ends inside the image");
   Consts<CPW> dc;
 
   // (the bias first: it is on one path only)
@@ -513,7 +515,7 @@ struct DwSmall {
   __device__ __forceinline__ uint32_t step(const DwParams& p, int j) const { return (uint32_t)j * (uint32_t)p.row_step; }
   __device__ __forceinline__ void load(const DwParams& p, int b, int g0, int wave, int lane) {
     const int c_wave = wave * CPW;
-    // weights: as they lie, to the end of the last load (after the rows follow the Toeplitz operands)
+    // weights: as they lie, whole loads (up to 1008 bytes past a wave's rows: the next wave's, or the image's tail)
     const v4i* const src = reinterpret_cast<const v4i*>(p.img) + c_wave * NA;
 #pragma unroll
     for (int j = 0; j < NWL; ++j) wr[j] = src[lane + 64 * j];
@@ -634,7 +636,7 @@ struct DwSmall {
 // for weight images of four bytes per tap, for constants three at a time and for two blocks' rows apart, one workgroup
 // (512 -> 256 channels, k = 75) had 592 loads, 9500 of the 15300 cycles it took, and up to ten round trips
 // one after the other.  Here
-//   - the weights come as they are, zero-padded rows of 16 NA bytes (sep_image's first part), are laid into the
+//   - the weights come as they are, zero-padded rows of 16 NA bytes (sep.hip: image), are laid into the
 //     wave's own rows of the pointwise tile, which are written later, and become Toeplitz rows by one byte
 //     permutation per dword;
 //   - rows, weights and constants of all the wave's channels are asked for at once, with them the residual, constants and
