@@ -366,9 +366,9 @@ bool supported(const ConvParams& p) {
 // The tile with the least time, in cycles: a launch, and on the busiest compute unit for each of its workgroups the
 // activations it transposes (64 bytes at a time), its steps (the weights of all its columns, or its products) and its
 // last stores; of single columns each operand read serves one product.  Every tile timed beside the choice, chains of six
-// layers of 256 .. 768 channels, 11 .. 25 taps, 104 .. 3200 frames (35 shapes): it is 0.8 % from the best on average and 2.9 %
-// at worst; the choice between this kernel and conv_pipe, over 50 shapes to 3200 frames, 0.4 % and 4.9 % (768 channels, 4 x 400
-// frames, 35.2 us for 33.6; with 7 cycles per 64 bytes transposed 1.0 % and 17 %, with 10.7, of the units of 4 frames, 0.5 % and 14 %).
+// layers of 256 .. 768 channels, 11 .. 25 taps, 52 .. 3200 frames (50 shapes, profiles/dense_tile_choice.txt): it is 0.3 % from the best on average
+// and 1.6 % at worst; the choice between this kernel and conv_pipe, over 60 shapes to 12800 frames, 0.3 % and 4.1 % (768 channels, 4 x 400
+// frames, 35.6 us for 34.1; with 7 cycles per 64 bytes transposed it was up to 17 %, with 10.7, of the units of 4 frames, 14 % off).
 // (Constants fitted to those chains alone, whose weights stay in the memory-side cache, make whole networks slower: 732 -> 741.)
 bool pick(const ConvParams& p, FewTile& best, double& cycles) {
   if (!supported(p)) return false;

@@ -492,8 +492,8 @@ int resident(const ConvParams& p, const CpTile& c) {
 // clock gives way), by a lone wave's own latencies, by the weights (NT KiB per wave) or by the operand reads; a
 // chunk costs a commit and a barrier; a workgroup its first loads and its epilogue, KG > 1 the meeting of the sums.
 // The constants are fitted to chains of six layers whose weights are in no L2.  Every tile, with 1, 2, 3, 4, 6 and 8
-// splits where the launch is small, timed beside the choice: 256 .. 768 channels, 11 .. 25 taps, 104 .. 12800 frames, 50
-// shapes: it is 0.5 % from the best on average and 6.7 % at worst (384 channels, 1600 frames).
+// splits where the launch is small, timed beside the choice: 256 .. 768 channels, 11 .. 25 taps, 52 .. 12800 frames, 60
+// shapes: it is 0.4 % from the best on average and 8.0 % at worst (384 channels, 2 x 800 frames).
 double unit_cycles(const ConvParams& p, const CpTile& c, int64_t n, int chunks) {
   const double mn = c.MT * c.NT, taps = (p.k + c.KG - 1) / c.KG;
   const int occ = resident(p, c);
