@@ -355,7 +355,9 @@ void qasr_encoder_graph_destroy(qasr_encoder_graph* g);
  * for the op that a launch begins with, the interval between the events around the launch (and its
  * separate activation pass, if any) minus an equal share of what the inner events cost; 0 for an op
  * that ran in the launch before (qasr_encoder_op_launch).  The forward is also run once without the
- * inner events in the same call; the times add up to that run's duration.  For profiling only: it
+ * inner events in the same call; the times add up to that run's duration.  What a launch does for a later one is in its own
+ * time: a dense layer that "conv_few" runs (qasr_encoder_op_launch) asks for the weights of the next such layer as it ends, so
+ * times of single layers are not those of the layers by themselves; sums over a network are.  For profiling only: it
  * runs the forward twice, synchronises and creates/destroys events. */
 qasr_status qasr_encoder_forward_timed(const qasr_encoder* e, const int8_t* x, int8_t* y,
                                        void* workspace, size_t workspace_bytes, void* stream,
